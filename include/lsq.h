@@ -149,12 +149,13 @@ int lsq_set_cache_refresh(int mode);
  * to the last bits, not always bit for bit.  Default: on. */
 int lsq_set_layernorm_fusion(int on);
 
-/* Few rows alive (float16 models with heads of 64 and d = 256 or 512, beam <= 4: with wider models
- * the separate kernels are faster): each attention sublayer of a decoder layer runs as one launch up to its output
- * projection (sec. 2.1 taken further; lsq_k_self_attention_block, lsq_k_cross_attention_block)
- * while at most max_rows rows are alive.  0 switches this off; default and largest value 64.  Same
- * tokens as the separate kernels; scores equal to float16 rounding (other summation orders).  Also
- * off when lsq_set_layernorm_fusion(0).  May be called at any time. */
+/* Few rows alive (float16 models with heads of 64): fewer, larger launches while at most max_rows rows
+ * are alive.  Models with d = 256, 512, 768 or 1024 and d_ffn = 4 d run ALL decoder layers of a step as one
+ * launch; other shapes with d = 256 or 512 and beam <= 4 run each attention sublayer of a decoder
+ * layer as one launch up to its output projection (sec. 2.1 taken further;
+ * lsq_k_self_attention_block, lsq_k_cross_attention_block).  0 switches both off; default and largest
+ * value 64.  Same tokens as the separate kernels; scores equal to float16 rounding (other summation
+ * orders).  Also off when lsq_set_layernorm_fusion(0).  May be called at any time. */
 int lsq_set_attention_blocks(int max_rows);
 
 /* Plain beam search of float16 models: the logit product also leaves, for every row and every 32

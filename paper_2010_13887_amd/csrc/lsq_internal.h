@@ -150,6 +150,35 @@ hipError_t launch_encoder_attention(int dtype, const void* qkv, const int32_t* r
                                     const int32_t* off, const int32_t* len, void* out, int rows, int H,
                                     int d, int causal, hipStream_t s);
 
+// All decoder layers of a step in one launch, few rows (kernels_stack.hip).  Matrices: fragment-ordered copies; the
+// pointers are those of layer 0, layer l's lie packed_stride / plain_stride bytes further on for each layer.
+constexpr int kStackRowsMax = 64;
+struct StackArgs {
+  const half_t *Wqkv, *Wo, *Wq, *Woc, *W1, *W2;
+  const half_t *bqkv, *bo, *bq, *boc, *b1, *b2, *ln1g, *ln1b, *ln2g, *ln2b, *ln3g, *ln3b;
+  size_t packed_stride, plain_stride;
+  char* cache;              // [layer][K | V][row][position][d]
+  size_t cache_stride;      // bytes of one layer's K (or V)
+  const char* cross;
+  size_t cross_stride;      // bytes of one layer's cross K/V
+  const int32_t *anc, *src_off, *src_len, *tpos, *tokens, *len;
+  const half_t *x0, *E, *lnfg, *lnfb;
+  const float* pe;
+  half_t *hidden, *x_out;   // normalised rows for the vocabulary product; pre-LN: the residual stream
+  char* exchange;           // two sets of set_bytes each
+  size_t set_bytes;
+  int32_t* state;           // [0] launches so far, [1 + p] rows of set p to be refilled, [4] arrivals
+  int* error;               // pinned host memory: set when a wait ran out
+  int M, beam, layers, T, anc_ld;
+  float eps;
+  int groups, rows_per_group;   // filled in by the launcher
+};
+size_t stack_exchange_bytes(int arch, int M, int d, int layers);   // of one set
+bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers);
+bool stack_supported(int arch, int M, int d);   // of a supported shape: these rows, on the current device
+hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init
+hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
+
 // Diverse beam search: the search kernels work on one group of every sentence at a time.  A sentence's
 // k_all rows are split into groups of kg; this launch takes group goff / kg (rows goff .. goff+kg-1 of
 // each sentence).  pen_tok [sentences, pen_ld] / pen_n [sentences]: tokens taken at this step by the

@@ -40,12 +40,12 @@ int fail(int code, const char* fmt, ...) {
 // per kernel class.  Events come from a host-side pool that only grows.
 enum ProfClass {
   PC_EMBED, PC_GEMM_QKV, PC_ATTN_SELF, PC_GEMM_DD, PC_LAYERNORM, PC_ATTN_CROSS, PC_GEMM_FFN1, PC_GEMM_FFN2,
-  PC_GEMM_VOCAB, PC_ROW_TOPK, PC_REFINE, PC_REORDER, PC_GEMM_OUT, PC_ATTN_CROSS_Q, PC_SELF_BLOCK, PC_CROSS_BLOCK, PC_ROW_TOPK_GROUPS, PC_RETRIEVE_RERANK, PC_COUNT
+  PC_GEMM_VOCAB, PC_ROW_TOPK, PC_REFINE, PC_REORDER, PC_GEMM_OUT, PC_ATTN_CROSS_Q, PC_SELF_BLOCK, PC_CROSS_BLOCK, PC_ROW_TOPK_GROUPS, PC_RETRIEVE_RERANK, PC_STACK, PC_COUNT
 };
 const char* const kProfNames[PC_COUNT] = {"embed", "gemm_qkv", "attn_self", "gemm_dxd", "add_layernorm",
                                           "attn_cross", "gemm_ffn1", "gemm_ffn2", "gemm_vocab", "row_topk",
                                           "beam_refine", "cache_reorder", "gemm_out", "attn_cross_q", "self_block",
-                                          "cross_block", "row_topk_groups", "retrieve_rerank"};
+                                          "cross_block", "row_topk_groups", "retrieve_rerank", "decoder_stack"};
 struct Prof {
   bool on = false;
   std::vector<hipEvent_t> pool;   // pairs: [2i] start, [2i+1] stop
@@ -181,6 +181,7 @@ constexpr unsigned char kCanaryByte = 0xA5;
 struct Plan {
   std::vector<size_t> canaries;       // red zones behind the regions that live as long as the model
   std::vector<size_t> dec_canaries;   // ... behind the decoder's intermediates (valid from the end of lsq_encode on)
+  size_t stack_exchange, stack_set, stack_state;   // decoder stack in one launch (few rows); stack_set = 0: not for this shape
   size_t weights, wpacked, pe, cache, cross, score, tokens, len, fin, parent, anc, pen_tok, pen_n, cand_plain, cap, order, src_off, src_len, active, step_state,
       cand_score, cand_idx, out_ids, out_lens, out_scores, scratch, total;
   // encoder view of scratch
@@ -221,6 +222,9 @@ Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   p.src_off = take((size_t)(B + 1) * 4);
   p.src_len = take((size_t)B * 4);
   p.active = take((size_t)(T + 1) * 4);
+  p.stack_set = stack_shape_supported(hp.dtype, hp.arch, hp.H, hp.d, hp.F, hp.n_dec) ? stack_exchange_bytes(hp.arch, (int)M, hp.d, hp.n_dec) : 0;
+  p.stack_exchange = take(2 * p.stack_set);
+  p.stack_state = take(8 * 4);
   p.step_state = take(4 * 4);   // [0] position counter, [1] arrival counter, [2] position of step 0
   const size_t kk = std::max(k, hp.sample_topk);   // survivors per row
   p.cand_score = take(M * kk * 4);
@@ -320,6 +324,8 @@ struct Ctx {
   std::map<int, bool> graph_hidden_in_alt; // ... and where that step leaves its final hidden rows
   std::vector<int> alive_at;   // alive_at[t] = sentences whose cap exceeds t: the prefix step t works on
   char* E = nullptr;
+  bool stack_ok = false;        // the decoder stack kernel takes this model
+  StackArgs stack{};            // ... with these arguments (all but those of a translation)
   std::vector<GptLayer> gpt;
   char *lnfg = nullptr, *lnfb = nullptr;
   int prompt_len = 0;
@@ -374,6 +380,69 @@ int sublayer(int cls, const void* in, const void* W, const void* bias, const voi
   TIMED(PC_LAYERNORM, launch_add_layernorm_partials(hp.dtype, x, y, partials, S, bias, g_, b_, M, d, hp.eps, s, x_in));
   return LSQ_OK;
 }
+
+// Arguments of the decoder stack kernel that a model fixes.  It finds layer l's tensors at a constant distance from
+// layer 0's, which is how tensor_walk lays them out.
+void setup_stack() {
+  const HParams& hp = g.hp;
+  const Plan& p = g.plan;
+  g.stack_ok = false;
+  if (!p.stack_set) return;
+  const int d = hp.d, F = hp.F, L = hp.n_dec;
+  const size_t es = esz();
+  StackArgs& a = g.stack;
+  a = StackArgs{};
+  struct Ref { const half_t** at; const char* p0; const char* p1; const char* pl; };
+  std::vector<Ref> packed, plain;
+  auto mat = [&](const half_t** at, auto get, int N, int K) {
+    auto of = [&](int l) { return (const char*)gemm_packed_weights(get(l), N, K); };
+    packed.push_back({at, of(0), of(std::min(1, L - 1)), of(L - 1)});
+  };
+  auto vec = [&](const half_t** at, auto get) { plain.push_back({at, get(0), get(std::min(1, L - 1)), get(L - 1)}); };
+#define LSQ_OF(layers, member) [&](int l) { return g.layers[l].member; }
+#define LSQ_COMMON(layers)                                                                                        \
+  mat(&a.Wqkv, LSQ_OF(layers, Wqkv), 3 * d, d); mat(&a.Wo, LSQ_OF(layers, Wo), d, d);                              \
+  mat(&a.W1, LSQ_OF(layers, W1), F, d); mat(&a.W2, LSQ_OF(layers, W2), d, F);                                      \
+  vec(&a.bqkv, LSQ_OF(layers, bqkv)); vec(&a.bo, LSQ_OF(layers, bo)); vec(&a.b1, LSQ_OF(layers, b1));              \
+  vec(&a.b2, LSQ_OF(layers, b2)); vec(&a.ln1g, LSQ_OF(layers, ln1g)); vec(&a.ln1b, LSQ_OF(layers, ln1b));          \
+  vec(&a.ln2g, LSQ_OF(layers, ln2g)); vec(&a.ln2b, LSQ_OF(layers, ln2b));
+  if (hp.arch == 1) {
+    LSQ_COMMON(gpt)
+  } else {
+    LSQ_COMMON(dec)
+    mat(&a.Wq, LSQ_OF(dec, Wq), d, d); mat(&a.Woc, LSQ_OF(dec, Woc), d, d);
+    vec(&a.bq, LSQ_OF(dec, bq)); vec(&a.boc, LSQ_OF(dec, boc));
+    vec(&a.ln3g, LSQ_OF(dec, ln3g)); vec(&a.ln3b, LSQ_OF(dec, ln3b));
+  }
+#undef LSQ_COMMON
+#undef LSQ_OF
+  auto regular = [&](std::vector<Ref>& refs, size_t* stride) {
+    *stride = 0;
+    for (auto& r : refs) {
+      if (!r.p0 || !r.p1 || !r.pl) return false;
+      if (&r == &refs[0]) *stride = (size_t)(r.p1 - r.p0);
+      if (r.p1 != r.p0 + *stride * (L > 1) || r.pl != r.p0 + *stride * (size_t)(L - 1)) return false;
+      *r.at = (const half_t*)r.p0;
+    }
+    return true;
+  };
+  if (!regular(packed, &a.packed_stride) || !regular(plain, &a.plain_stride)) return;
+  a.cache = g.ws + p.cache;
+  a.cache_stride = (size_t)g.max_batch * g.beam * g.max_len * d * es;
+  a.cross = g.ws + p.cross;
+  a.cross_stride = (size_t)g.max_batch * g.max_len * 2 * d * es;
+  a.src_off = at<int32_t>(p.src_off); a.src_len = at<int32_t>(p.src_len); a.tpos = at<int32_t>(p.step_state);
+  a.tokens = at<int32_t>(p.tokens); a.len = at<int32_t>(p.len);
+  a.E = (const half_t*)g.E; a.pe = at<float>(p.pe);
+  a.lnfg = (const half_t*)g.lnfg; a.lnfb = (const half_t*)g.lnfb;
+  a.exchange = g.ws + p.stack_exchange; a.set_bytes = p.stack_set;
+  a.state = at<int32_t>(p.stack_state); a.error = g.pinned + g.pinned_ints - 2;
+  a.layers = L; a.T = g.max_len; a.anc_ld = g.max_len + 1; a.eps = hp.eps;
+  a.beam = g.beam;
+  g.stack_ok = true;
+}
+
+bool use_stack(int M) { return g.stack_ok && g.fuse_ln && M <= g.block_rows && stack_supported(g.hp.arch, M, g.hp.d); }
 
 // All launches of one decode step for the first B sentences (B*k rows).  Nothing here depends on
 // the step index: kernels read it from the device-side counter (step_state[0]), the cache and
@@ -448,7 +517,14 @@ int launch_step(int B) {
     pending.on = false;
     return LSQ_OK;
   };
-  for (int l = 0; l < hp.n_dec; ++l) {
+  const bool stack = use_stack(M);
+  if (stack) {
+    StackArgs a = g.stack;
+    a.M = M; a.anc = anc; a.x0 = (const half_t*)x0; a.hidden = (half_t*)x_home;
+    TIMED(PC_STACK, launch_decoder_stack(hp.arch, a, d, s));
+    x = x_home;
+  }
+  for (int l = 0; l < (stack ? 0 : hp.n_dec); ++l) {
     const DecLayer& L = g.dec[l];
     char* Kc = g.ws + p.cache + (size_t)(2 * l) * slab;
     char* Vc = Kc + slab;
@@ -625,7 +701,12 @@ int launch_step_gpt(int B) {
     if (attention_blocks_supported(dt, M, 1, H, d)) nq = 1;
     if (M * H > 256 && M % 2 == 0 && attention_blocks_supported(dt, M, 2, H, d)) nq = 2;
   }
-  if (nq) {
+  const bool stack = use_stack(M);
+  if (stack) {
+    StackArgs a = g.stack;
+    a.M = M; a.anc = nullptr; a.hidden = (half_t*)y; a.x_out = (half_t*)x;
+    TIMED(PC_STACK, launch_decoder_stack(hp.arch, a, d, s));
+  } else if (nq) {
     char* x_alt = g.ws + p.d_x2;
     float* ffn_slabs = (float*)tmp;
     float* head_slabs = (float*)(g.ws + p.d_tmp2);
@@ -658,7 +739,7 @@ int launch_step_gpt(int B) {
     TIMED(PC_EMBED, launch_embed_last(dt, g.E, at<float>(p.pe), at<int32_t>(p.tokens), at<int32_t>(p.len), x, M, d, T, step, 1.0f, s));
     TIMED(PC_LAYERNORM, launch_add_layernorm_partials(dt, x, y, nullptr, 0, nullptr, g.gpt[0].ln1g, g.gpt[0].ln1b, M, d, hp.eps, s));
   }
-  for (int l = 0; l < (nq ? 0 : hp.n_dec); ++l) {
+  for (int l = 0; l < (nq || stack ? 0 : hp.n_dec); ++l) {
     const GptLayer& L = g.gpt[l];
     char* Kc = g.ws + p.cache + (size_t)(2 * l) * slab;
     char* Vc = Kc + slab;
@@ -737,12 +818,18 @@ int enqueue_step() {
   return LSQ_OK;
 }
 
+// after a wait for the stream: whether a workgroup of the decoder stack kernel gave up waiting for the others
+int stack_waits_ended() {
+  if (g.pinned[g.pinned_ints - 2]) return fail(LSQ_E_HIP, "decoder stack kernel: a workgroup waited too long for the others");
+  return LSQ_OK;
+}
+
 int read_active(int step, int* out) {
   int32_t* slot = g.pinned + g.pinned_ints - 1;
   HIPCHK(hipMemcpyAsync(slot, at<int32_t>(g.plan.active) + step, 4, hipMemcpyDeviceToHost, g.stream));
   HIPCHK(hipStreamSynchronize(g.stream));
   *out = *slot;
-  return LSQ_OK;
+  return stack_waits_ended();
 }
 
 // Decoder-only model: "encode" takes the prompts (all of one length P), runs the blocks over their
@@ -943,8 +1030,11 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
 
   for (size_t c : plan.canaries) HIPCHK(hipMemsetAsync(g.ws + c, kCanaryByte, kCanaryBytes, g.stream));
   HIPCHK(hipStreamSynchronize(g.stream));
-  g.pinned_ints = (size_t)3 * max_batch * max_len + 4 * (size_t)max_batch + 2 + (size_t)max_batch * (max_len + 2) + 8;
+  g.pinned_ints = (size_t)3 * max_batch * max_len + 4 * (size_t)max_batch + 2 + (size_t)max_batch * (max_len + 2) + 8;   // the last two: error flag of the decoder stack kernel, active count
   HIPCHK(hipHostMalloc((void**)&g.pinned, g.pinned_ints * 4, hipHostMallocDefault));
+
+  g.pinned[g.pinned_ints - 2] = 0;
+  if (plan.stack_set) HIPCHK(launch_stack_reset(g.ws + plan.stack_exchange, 2 * plan.stack_set, (int32_t*)(g.ws + plan.stack_state), g.stream));
 
   g.hp = hp;
   g.plan = plan;
@@ -959,6 +1049,7 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
       L.ln2g = dev[i++]; L.ln2b = dev[i++]; L.W1 = dev[i++]; L.b1 = dev[i++]; L.W2 = dev[i++]; L.b2 = dev[i++];
     }
     g.lnfg = dev[i++]; g.lnfb = dev[i++];
+    setup_stack();
     g.state = 2;
     return LSQ_OK;
   }
@@ -974,6 +1065,7 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
     L.ln2g = dev[i++]; L.ln2b = dev[i++];
     L.W1 = dev[i++]; L.b1 = dev[i++]; L.W2 = dev[i++]; L.b2 = dev[i++]; L.ln3g = dev[i++]; L.ln3b = dev[i++];
   }
+  setup_stack();
   g.state = 2;
   return LSQ_OK;
 }
@@ -996,6 +1088,10 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
     R += n;
   }
   HIPCHK(hipStreamSynchronize(g.stream));   // the staging buffer may still feed an earlier copy
+  if (g.pinned[g.pinned_ints - 2]) {   // an earlier translation was given up: its exchange regions are in no known state
+    HIPCHK(launch_stack_reset(g.ws + g.plan.stack_exchange, 2 * g.plan.stack_set, at<int32_t>(g.plan.stack_state), g.stream));
+    g.pinned[g.pinned_ints - 2] = 0;
+  }
   const int groups = hp.arch == 0 ? g.groups_next : 1;
   if (g.beam % groups != 0) return fail(LSQ_E_ARG, "beam %d is not a multiple of %d groups", g.beam, groups);
   const bool anc_on = hp.arch == 0 && g.beam > 1 && g.refresh_mode == 1;
@@ -1242,7 +1338,7 @@ int lsq_get_beams(int32_t* out_ids, int32_t* out_lens, float* out_scores) {
   HIPCHK(hipMemcpyAsync(out_lens, g.ws + p.out_lens, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
   HIPCHK(hipMemcpyAsync(out_scores, g.ws + p.out_scores, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
   HIPCHK(hipStreamSynchronize(g.stream));
-  return LSQ_OK;
+  return stack_waits_ended();
 }
 
 void lsq_free(void) {
