@@ -31,6 +31,22 @@ __global__ void __launch_bounds__(256) embed_last_kernel(const T* __restrict__ E
   embed_row<T>(E + (size_t)id * d, pe + (size_t)t * d, x + (size_t)r * d, d, scale, threadIdx.x & 63, 64);
 }
 
+// A translation's ids, lengths and tables: a dozen arrays of a few KB.  As copies of their own they cost about 10 us each.
+__global__ void __launch_bounds__(256) staging_kernel(const Staging st) {
+  for (int a = 0; a < st.count; ++a) {
+    int32_t* d = st.dst[a];
+    const int32_t* s = st.src[a];
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < st.n[a]; i += gridDim.x * 256) d[i] = s ? s[i] : 0;
+  }
+}
+
+hipError_t launch_staging(const Staging& st, hipStream_t s) {
+  int most = 1;
+  for (int a = 0; a < st.count; ++a) most = max(most, st.n[a]);
+  staging_kernel<<<min(128, (most + 255) / 256), 256, 0, s>>>(st);
+  return hipGetLastError();
+}
+
 hipError_t launch_embed_rows(int dtype, const void* E, const float* pe, const int32_t* ids,
                              const int32_t* pos, void* x, int rows, int d, float scale, hipStream_t s) {
   if (rows <= 0) return hipSuccess;

@@ -549,6 +549,23 @@ __device__ __forceinline__ void rerank_sync() {
   }
 }
 
+// The end of a unit's part in a step: `unfinished` of its sentences go on.  Arrivals (low half) and unfinished
+// sentences (high half) are counted in one word, so that a unit makes one returning atomic; the last of `units` to
+// arrive leaves the count in active[t], advances the position counter -- every unit read it at its start, and the only
+// other readers are kernels launched later -- and tells the host (report, pinned memory: step number and count in one
+// word; nothing else is read on the strength of it).
+__device__ __forceinline__ void end_of_step(int32_t* active, int t, int32_t* step_state, int next_pos, int unfinished, int units,
+                                            unsigned long long* report, int fixed_count = -1) {
+  const int old = atomicAdd(&step_state[1], 1 + (unfinished << 16));
+  if ((old & 0xFFFF) != units - 1) return;
+  const int n = fixed_count >= 0 ? fixed_count : (old >> 16) + unfinished;
+  step_state[1] = 0;
+  active[t] = n;
+  step_state[0] = next_pos;
+  if (report)
+    __hip_atomic_store(report, ((unsigned long long)(t + 1) << 32) | (unsigned)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // cand_score / cand_idx: the sentence's k*k survivors at [(row - first row of the launch's unit) ...]: pointers to the
 // pairs of row `base` (global memory, or LDS when the retrieve stage ran in the same workgroup).
 template <bool ALONE>
@@ -559,7 +576,8 @@ __device__ __forceinline__ void rerank_sentence(const float* cand_score_b, const
                                                 int32_t* __restrict__ active, int k, int V, int T1, int t_base,
                                                 int32_t* __restrict__ step_state, int eos, int32_t* __restrict__ anc,
                                                 const SearchGroups& gr, const NextInput& nx, int b, int lane,
-                                                int* sh_parent, int* sh_tok, int& sh_unfinished, int& sh_taken) {
+                                                int* sh_parent, int* sh_tok, int& sh_unfinished, int& sh_taken,
+                                                unsigned long long* report) {
   const int t = t_base + (step_state ? step_state[0] : 0);
   const int kk = k * k;
   const int k_all = gr.k_all > 1 ? gr.k_all : k;           // rows of a sentence (k_all == 1: no groups)
@@ -662,15 +680,9 @@ __device__ __forceinline__ void rerank_sentence(const float* cand_score_b, const
   if (lane < k_all && (lane < gr.goff || lane >= gr.goff + k)) others = fin[b * k_all + lane] ? 0 : 1;
   others = __any(others) ? 1 : 0;
   if (lane == 0) {
-    if (sh_unfinished || others) atomicAdd(step_state ? active + t : active, 1);   // per-step counters, or the caller's one
-    if (step_state) {
-      // the last sentence to get here advances the step counter: every workgroup read it at its
-      // start, before its own increment, and the only other readers are kernels launched later
-      if (atomicAdd(&step_state[1], 1) == (int)gridDim.x - 1) {
-        step_state[1] = 0;
-        step_state[0] = t + 1 - t_base;
-      }
-    }
+    const int go_on = sh_unfinished || others ? 1 : 0;
+    if (step_state) end_of_step(active, t, step_state, t + 1 - t_base, go_on, (int)gridDim.x, report);
+    else if (go_on) atomicAdd(active, 1);   // the caller's counter
   }
 }
 
@@ -682,7 +694,8 @@ __global__ void __launch_bounds__(64) beam_refine_kernel(const float* __restrict
                                                          const int32_t* __restrict__ cap,
                                                          int32_t* __restrict__ active, int k, int V, int T1,
                                                          int t_base, int32_t* __restrict__ step_state, int eos,
-                                                         int32_t* __restrict__ anc, SearchGroups gr, NextInput nx) {
+                                                         int32_t* __restrict__ anc, SearchGroups gr, NextInput nx,
+                                                         unsigned long long* report) {
   __shared__ int sh_parent[LSQ_MAX_BEAM_], sh_tok[LSQ_MAX_BEAM_];
   __shared__ int sh_unfinished, sh_taken;
   const int b = blockIdx.x;
@@ -690,7 +703,7 @@ __global__ void __launch_bounds__(64) beam_refine_kernel(const float* __restrict
   const size_t first = ((size_t)b * k_all + gr.goff) * k;   // the pairs of the unit's first row
   rerank_sentence<true>(cand_score + first, cand_idx + first, gr.out_plain ? gr.out_plain + first : nullptr, score, tokens, len,
                         fin, parent, cap, active, k, V, T1, t_base, step_state, eos, anc, gr, nx, b, (int)threadIdx.x,
-                        sh_parent, sh_tok, sh_unfinished, sh_taken);
+                        sh_parent, sh_tok, sh_unfinished, sh_taken, report);
 }
 
 // Retrieve and re-rank in one launch (plain beam search from the logit product's group statistics): a workgroup
@@ -700,7 +713,8 @@ __global__ void __launch_bounds__(64 * LSQ_MAX_BEAM_) retrieve_rerank_kernel(
     const float* __restrict__ logits, const float* __restrict__ stats, float* __restrict__ score, int32_t* __restrict__ tokens,
     int32_t* __restrict__ len, int32_t* __restrict__ fin, int32_t* __restrict__ parent, const int32_t* __restrict__ cap,
     int32_t* __restrict__ active, int k, int V, int G, int T1, int32_t* __restrict__ step_state, int eos,
-    int32_t* __restrict__ anc, NextInput nx, float* __restrict__ cand_out_s, int32_t* __restrict__ cand_out_i) {
+    int32_t* __restrict__ anc, NextInput nx, float* __restrict__ cand_out_s, int32_t* __restrict__ cand_out_i,
+    unsigned long long* report) {
   __shared__ int ql[LSQ_MAX_BEAM_][kTopkGroupsQ];
   __shared__ float cs[LSQ_MAX_BEAM_][kTopkGroupsC];
   __shared__ int ci[LSQ_MAX_BEAM_][kTopkGroupsC];
@@ -719,33 +733,34 @@ __global__ void __launch_bounds__(64 * LSQ_MAX_BEAM_) retrieve_rerank_kernel(
   }
   if (wave != 0) return;
   rerank_sentence<false>(cand_s, cand_i, nullptr, score, tokens, len, fin, parent, cap, active, k, V, T1, 0, step_state, eos,
-                         anc, one_group(), nx, b, lane, sh_parent, sh_tok, sh_unfinished, sh_taken);
+                         anc, one_group(), nx, b, lane, sh_parent, sh_tok, sh_unfinished, sh_taken, report);
 }
 
 hipError_t launch_beam_refine(const float* cand_score, const int32_t* cand_idx, float* score, int32_t* tokens,
                               int32_t* len, int32_t* fin, int32_t* parent, const int32_t* cap,
                               int32_t* active, int batch, int k, int V, int T, int t_base, int32_t* step_state,
-                              int eos, int32_t* anc, hipStream_t s, const SearchGroups& gr, const NextInput& nx) {
+                              int eos, int32_t* anc, hipStream_t s, const SearchGroups& gr, const NextInput& nx,
+                              unsigned long long* report) {
   if (batch <= 0) return hipSuccess;
   if (k < 1 || k > LSQ_MAX_BEAM_) return hipErrorInvalidValue;
   if (gr.k_all > 1 && (gr.kg != k || gr.k_all % k != 0 || gr.k_all > LSQ_MAX_BEAM_ || gr.goff % k != 0 || gr.goff + k > gr.k_all))
     return hipErrorInvalidValue;
   beam_refine_kernel<<<batch, 64, 0, s>>>(cand_score, cand_idx, score, tokens, len, fin, parent, cap, active,
-                                          k, V, T + 1, t_base, step_state, eos, anc, gr, nx);
+                                          k, V, T + 1, t_base, step_state, eos, anc, gr, nx, report);
   return hipGetLastError();
 }
 
 hipError_t launch_retrieve_rerank(const float* logits, const float* stats, float* score, int32_t* tokens, int32_t* len,
                                   int32_t* fin, int32_t* parent, const int32_t* cap, int32_t* active, int batch, int k,
                                   int V, int T, int32_t* step_state, int eos, int32_t* anc, hipStream_t s,
-                                  const NextInput& nx, float* cand_score, int32_t* cand_idx) {
+                                  const NextInput& nx, float* cand_score, int32_t* cand_idx, unsigned long long* report) {
   if (batch <= 0) return hipSuccess;
   if (!topk_groups_supported(V, k, 0) || !stats || !step_state) return hipErrorInvalidValue;
   const int G = (V + 31) / 32;
   dim3 g(batch), b(64 * k);
 #define LSQ_RR(GPL_)                                                                                                     \
   retrieve_rerank_kernel<GPL_><<<g, b, 0, s>>>(logits, stats, score, tokens, len, fin, parent, cap, active, k, V, G, T + 1, \
-                                               step_state, eos, anc, nx, cand_score, cand_idx)
+                                               step_state, eos, anc, nx, cand_score, cand_idx, report)
   if (G <= 64 * 4) LSQ_RR(4);
   else if (G <= 64 * 16) LSQ_RR(16);
   else LSQ_RR(32);
@@ -955,7 +970,8 @@ __global__ void __launch_bounds__(64) sample_kernel(const float* __restrict__ ca
                                                     int32_t* __restrict__ step_state, int rows, int k, float topp,
                                                     int T1, unsigned seed_lo, unsigned seed_hi, int n_new,
                                                     int32_t* __restrict__ fin, const int32_t* __restrict__ cap,
-                                                    const int32_t* __restrict__ order, int eos) {
+                                                    const int32_t* __restrict__ order, int eos,
+                                                    unsigned long long* report) {
   const int r = blockIdx.x * 64 + threadIdx.x;
   const int pos = step_state[0], t = pos - step_state[2];   // position of the token just fed; step index
   bool unfinished = false;
@@ -964,15 +980,7 @@ __global__ void __launch_bounds__(64) sample_kernel(const float* __restrict__ ca
     unfinished = sample_row(cand_logit + (size_t)r * k, cand_idx + (size_t)r * k, r, tokens, len, logp, k, topp, T1, seed_lo,
                             seed_hi, pos, t, fin, cap, order, eos, tok);
   const int alive = __popcll(__ballot(unfinished));
-  if (threadIdx.x == 0) {
-    if (fin && alive) atomicAdd(active + t, alive);
-    __threadfence();
-    if (atomicAdd(&step_state[1], 1) == (int)gridDim.x - 1) {
-      step_state[1] = 0;
-      if (!fin) active[t] = (t + 1 < n_new) ? rows : 0;
-      step_state[0] = pos + 1;
-    }
-  }
+  if (threadIdx.x == 0) end_of_step(active, t, step_state, pos + 1, alive, (int)gridDim.x, report, fin ? -1 : t + 1 < n_new ? rows : 0);
 }
 
 // Retrieve (the k largest logits from the logit product's group statistics) and draw in one launch: a wavefront
@@ -987,7 +995,8 @@ __global__ void __launch_bounds__(256) retrieve_sample_kernel(const float* __res
                                                               int n_new, int32_t* __restrict__ fin,
                                                               const int32_t* __restrict__ cap,
                                                               const int32_t* __restrict__ order, int eos, NextInput nx,
-                                                              float* __restrict__ cand_out_s, int32_t* __restrict__ cand_out_i) {
+                                                              float* __restrict__ cand_out_s, int32_t* __restrict__ cand_out_i,
+                                                              unsigned long long* report) {
   __shared__ int ql[4][kTopkGroupsQ];
   __shared__ float cs[4][kTopkGroupsC];
   __shared__ int ci[4][kTopkGroupsC];
@@ -1025,33 +1034,27 @@ __global__ void __launch_bounds__(256) retrieve_sample_kernel(const float* __res
     if (nx.dtype == DT_F16) next_input_rows<half_t>(nx, &next_tok[wave], r, 1, pos + 1, lane);
     else next_input_rows<float>(nx, &next_tok[wave], r, 1, pos + 1, lane);
   }
-  if (lane == 0) {
-    if (fin && unfinished) atomicAdd(active + t, 1);
-    __threadfence();
-    if (atomicAdd(&step_state[1], 1) == rows - 1) {   // one count per row: the last row advances the position
-      step_state[1] = 0;
-      if (!fin) active[t] = (t + 1 < n_new) ? rows : 0;
-      step_state[0] = pos + 1;
-    }
-  }
+  // one count per row: the last row advances the position
+  if (lane == 0) end_of_step(active, t, step_state, pos + 1, unfinished ? 1 : 0, rows, report, fin ? -1 : t + 1 < n_new ? rows : 0);
 }
 
 hipError_t launch_sample(const float* cand_logit, const int32_t* cand_idx, int32_t* tokens, int32_t* len,
                          float* logp, int32_t* active, int32_t* step_state, int rows, int k, float topp, int T,
                          unsigned long long seed, int n_new, hipStream_t s, int32_t* fin, const int32_t* cap,
-                         const int32_t* order, int eos) {
+                         const int32_t* order, int eos, unsigned long long* report) {
   if (rows <= 0) return hipSuccess;
   if (k < 1 || k > LSQ_MAX_TOPK_ || !(topp > 0.f) || (fin && !cap)) return hipErrorInvalidValue;
   sample_kernel<<<(rows + 63) / 64, 64, 0, s>>>(cand_logit, cand_idx, tokens, len, logp, active, step_state, rows, k,
                                                 topp, T + 1, (unsigned)(seed & 0xFFFFFFFFull), (unsigned)(seed >> 32),
-                                                n_new, fin, cap, order, eos);
+                                                n_new, fin, cap, order, eos, report);
   return hipGetLastError();
 }
 
 hipError_t launch_retrieve_sample(const float* logits, const float* stats, int32_t* tokens, int32_t* len, float* logp,
                                   int32_t* active, int32_t* step_state, int rows, int V, int k, float topp, int T,
                                   unsigned long long seed, int n_new, hipStream_t s, int32_t* fin, const int32_t* cap,
-                                  const int32_t* order, int eos, const NextInput& nx, float* cand_score, int32_t* cand_idx) {
+                                  const int32_t* order, int eos, const NextInput& nx, float* cand_score, int32_t* cand_idx,
+                                  unsigned long long* report) {
   if (rows <= 0) return hipSuccess;
   if (!topk_groups_supported(V, k, 1) || !stats || !(topp > 0.f) || (fin && !cap)) return hipErrorInvalidValue;
   const int G = (V + 31) / 32;
@@ -1059,7 +1062,7 @@ hipError_t launch_retrieve_sample(const float* logits, const float* stats, int32
   const unsigned lo = (unsigned)(seed & 0xFFFFFFFFull), hi = (unsigned)(seed >> 32);
 #define LSQ_RS(GPL_)                                                                                                    \
   retrieve_sample_kernel<GPL_><<<g, b, 0, s>>>(logits, stats, tokens, len, logp, active, step_state, rows, V, G, k, topp, \
-                                               T + 1, lo, hi, n_new, fin, cap, order, eos, nx, cand_score, cand_idx)
+                                               T + 1, lo, hi, n_new, fin, cap, order, eos, nx, cand_score, cand_idx, report)
   if (G <= 64 * 4) LSQ_RS(4);
   else if (G <= 64 * 16) LSQ_RS(16);
   else LSQ_RS(32);

@@ -102,6 +102,17 @@ bool embed_layernorm_supported(int d);
 hipError_t launch_embed_layernorm(int dtype, const void* E, const float* pe, const int32_t* tokens, const int32_t* len,
                                   void* x, void* y, const void* g, const void* b, int rows, int d, int T,
                                   const int32_t* tp, float scale, float eps, hipStream_t s);
+// Small host arrays to where the kernels want them, all in one launch: dst[i][0 .. n[i]) = src[i][..], src in pinned
+// host memory (nullptr: zeros).
+struct Staging {
+  static constexpr int kMax = 12;
+  int32_t* dst[kMax];
+  const int32_t* src[kMax];
+  int n[kMax];
+  int count;
+  void add(int32_t* d, const int32_t* s_, size_t m) { dst[count] = d; src[count] = s_; n[count] = (int)m; ++count; }
+};
+hipError_t launch_staging(const Staging& st, hipStream_t s);
 hipError_t launch_scatter_kv(int dtype, const void* qkv, const int32_t* sent, const int32_t* pos, void* Kc,
                              void* Vc, int rows, int d, int T, hipStream_t s);
 // x_in (post-LN only): the residual is read from there instead of x, which is then only written
@@ -208,7 +219,8 @@ hipError_t launch_row_topk(int dtype, const void* logits, const float* score, co
 hipError_t launch_sample(const float* cand_logit, const int32_t* cand_idx, int32_t* tokens, int32_t* len,
                          float* logp, int32_t* active, int32_t* step_state, int rows, int k, float topp, int T,
                          unsigned long long seed, int n_new, hipStream_t s, int32_t* fin = nullptr,
-                         const int32_t* cap = nullptr, const int32_t* order = nullptr, int eos = -1);
+                         const int32_t* cap = nullptr, const int32_t* order = nullptr, int eos = -1,
+                         unsigned long long* report = nullptr);
 // step = t_base + (step_state ? step_state[0] : 0).  `active` points at the counter array indexed
 // by step.  With step_state != null the last workgroup to finish advances step_state[0]
 // (step_state[1] is its arrival counter and must be zero at launch).  anc != null: the slab table
@@ -234,20 +246,23 @@ hipError_t launch_beam_refine(const float* cand_score, const int32_t* cand_idx, 
                               int32_t* tokens, int32_t* len, int32_t* fin, int32_t* parent,
                               const int32_t* cap, int32_t* active, int batch, int k, int V, int T,
                               int t_base, int32_t* step_state, int eos, int32_t* anc, hipStream_t s,
-                              const SearchGroups& groups = one_group(), const NextInput& next = no_next_input());
+                              const SearchGroups& groups = one_group(), const NextInput& next = no_next_input(),
+                              unsigned long long* report = nullptr);   // pinned host word: (steps taken, unfinished) after the step
 // launch_row_topk_groups (raw) and launch_sample in one launch; next.E given: the rows' next decoder input as well
 hipError_t launch_retrieve_sample(const float* logits, const float* stats, int32_t* tokens, int32_t* len, float* logp,
                                   int32_t* active, int32_t* step_state, int rows, int V, int k, float topp, int T,
                                   unsigned long long seed, int n_new, hipStream_t s, int32_t* fin = nullptr,
                                   const int32_t* cap = nullptr, const int32_t* order = nullptr, int eos = -1,
                                   const NextInput& next = no_next_input(), float* cand_score = nullptr,
-                                  int32_t* cand_idx = nullptr);   // cand_*: the candidates are also left there
+                                  int32_t* cand_idx = nullptr,   // cand_*: the candidates are also left there
+                                  unsigned long long* report = nullptr);
 // launch_row_topk_groups and launch_beam_refine (no groups, device-side step counter) in one launch
 hipError_t launch_retrieve_rerank(const float* logits, const float* stats, float* score, int32_t* tokens, int32_t* len,
                                   int32_t* fin, int32_t* parent, const int32_t* cap, int32_t* active, int batch, int k,
                                   int V, int T, int32_t* step_state, int eos, int32_t* anc, hipStream_t s,
                                   const NextInput& next = no_next_input(), float* cand_score = nullptr,
-                                  int32_t* cand_idx = nullptr);   // cand_*: the survivors are also left there
+                                  int32_t* cand_idx = nullptr,   // cand_*: the survivors are also left there
+                                   unsigned long long* report = nullptr);
 // npos = npos_base + (tp ? *tp : 0); the grid covers npos_max positions
 hipError_t launch_cache_reorder(int dtype, void* cache, const int32_t* parent, int layers, int batch,
                                 int rows_total, int k, int T, int d, int npos_base, const int32_t* tp,

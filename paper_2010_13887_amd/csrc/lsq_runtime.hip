@@ -297,6 +297,12 @@ size_t device_weight_bytes(const HParams& hp) {
   return up(off);
 }
 
+struct HostPage {
+  unsigned long long step;   // (steps taken << 32) | unfinished sentences, by the last kernel of every step
+  int32_t error;             // a workgroup of the decoder stack kernel gave up waiting
+};
+constexpr size_t kResultsMax = 32u << 20;   // bytes of results the host keeps pinned
+
 struct Ctx {
   int state = 0;   // 0 nothing, 1 workspace set, 2 model loaded, 3 sentences encoded
   char* ws = nullptr;
@@ -331,7 +337,9 @@ struct Ctx {
   int prompt_len = 0;
   std::vector<EncLayer> enc;
   std::vector<DecLayer> dec;
-  int32_t* pinned = nullptr;   // host staging: ids, positions, sentence map, offsets, lengths, caps, 1 count
+  HostPage* page = nullptr;    // what the GPU tells the host (coherent pinned memory)
+  int32_t* results = nullptr;  // pinned: hypotheses, lengths, scores as the finalisation leaves them (nullptr: too large)
+  int32_t* pinned = nullptr;   // host staging: ids, positions, sentence map, offsets, lengths, caps
   size_t pinned_ints = 0;
 } g;
 
@@ -436,7 +444,7 @@ void setup_stack() {
   a.E = (const half_t*)g.E; a.pe = at<float>(p.pe);
   a.lnfg = (const half_t*)g.lnfg; a.lnfb = (const half_t*)g.lnfb;
   a.exchange = g.ws + p.stack_exchange; a.set_bytes = p.stack_set;
-  a.state = at<int32_t>(p.stack_state); a.error = g.pinned + g.pinned_ints - 2;
+  a.state = at<int32_t>(p.stack_state); a.error = &g.page->error;
   a.layers = L; a.T = g.max_len; a.anc_ld = g.max_len + 1; a.eps = hp.eps;
   a.beam = g.beam;
   g.stack_ok = true;
@@ -472,6 +480,7 @@ int launch_step(int B) {
   if (hp.sample_topk > 0 && !g.sample_fold)
     TIMED(PC_EMBED, launch_embed_last(dt, g.E, at<float>(p.pe), at<int32_t>(p.tokens), at<int32_t>(p.len), x, M, d, T, step, sqrtf((float)d), s));
   char* x_alt = g.ws + p.d_x2;
+  unsigned long long* const report = &g.page->step;
   const NextInput next = {g.E, at<float>(p.pe), g.ws + p.d_x0, d, dt, sqrtf((float)d)};
   // after a swap of the two hidden-state buffers: the input buffer never becomes one of them
   auto swapped = [&]() { if (x_alt == x0 && x0 != x_home) x_alt = x_home; };
@@ -610,7 +619,7 @@ int launch_step(int B) {
                                                        at<int32_t>(p.len), at<float>(p.score), at<int32_t>(p.active), step, M, V,
                                                        hp.sample_topk, hp.topp, T, (unsigned long long)hp.seed, 0, s,
                                                        at<int32_t>(p.fin), at<int32_t>(p.cap), at<int32_t>(p.order), hp.eos, next,
-                                                       at<float>(p.cand_score), at<int32_t>(p.cand_idx)));
+                                                       at<float>(p.cand_score), at<int32_t>(p.cand_idx), report));
       return LSQ_OK;
     }
     if (from_stats)
@@ -623,7 +632,7 @@ int launch_step(int B) {
     TIMED(PC_REFINE, launch_sample(at<float>(p.cand_score), at<int32_t>(p.cand_idx), at<int32_t>(p.tokens),
                                    at<int32_t>(p.len), at<float>(p.score), at<int32_t>(p.active), step, M,
                                    hp.sample_topk, hp.topp, T, (unsigned long long)hp.seed, 0, s, at<int32_t>(p.fin),
-                                   at<int32_t>(p.cap), at<int32_t>(p.order), hp.eos));
+                                   at<int32_t>(p.cap), at<int32_t>(p.order), hp.eos, report));
     return LSQ_OK;
   }
   if (g.groups > 1) {
@@ -638,7 +647,7 @@ int launch_step(int B) {
       TIMED(PC_REFINE, launch_beam_refine(at<float>(p.cand_score), at<int32_t>(p.cand_idx), at<float>(p.score),
                                           at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
                                           at<int32_t>(p.parent), at<int32_t>(p.cap), at<int32_t>(p.active), B, kg, V,
-                                          T, 0, step, hp.eos, anc, s, gr, next));
+                                          T, 0, step, hp.eos, anc, s, gr, next, report));
     }
     if (!anc)
       TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
@@ -650,7 +659,7 @@ int launch_step(int B) {
     TIMED(PC_RETRIEVE_RERANK, launch_retrieve_rerank((const float*)logits, at<float>(p.d_stats), at<float>(p.score),
                                                      at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
                                                      at<int32_t>(p.parent), at<int32_t>(p.cap), at<int32_t>(p.active), B, k, V, T,
-                                                     step, hp.eos, anc, s, next, at<float>(p.cand_score), at<int32_t>(p.cand_idx)));
+                                                     step, hp.eos, anc, s, next, at<float>(p.cand_score), at<int32_t>(p.cand_idx), report));
     if (!anc)
       TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
                                              0, step, T, s));
@@ -668,7 +677,7 @@ int launch_step(int B) {
   TIMED(PC_REFINE, launch_beam_refine(at<float>(p.cand_score), at<int32_t>(p.cand_idx), at<float>(p.score),
                             at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
                             at<int32_t>(p.parent), at<int32_t>(p.cap), at<int32_t>(p.active), B, k, V, T, 0,
-                            step, hp.eos, anc, s, one_group(), next));
+                            step, hp.eos, anc, s, one_group(), next, report));
   if (!anc)
     TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
                                            0, step, T, s));
@@ -766,7 +775,7 @@ int launch_step_gpt(int B) {
     TIMED(PC_RETRIEVE_RERANK, launch_retrieve_sample((const float*)logits, at<float>(p.d_stats), at<int32_t>(p.tokens),
                                                      at<int32_t>(p.len), at<float>(p.score), at<int32_t>(p.active), step, M, V, ks,
                                                      hp.topp, T, (unsigned long long)hp.seed, hp.cap_extra, s, nullptr, nullptr, nullptr,
-                                                     -1, no_next_input(), at<float>(p.cand_score), at<int32_t>(p.cand_idx)));
+                                                     -1, no_next_input(), at<float>(p.cand_score), at<int32_t>(p.cand_idx), &g.page->step));
     return LSQ_OK;
   }
   if (from_stats)
@@ -777,18 +786,20 @@ int launch_step_gpt(int B) {
                                        at<int32_t>(p.cand_idx), s));
   TIMED(PC_REFINE, launch_sample(at<float>(p.cand_score), at<int32_t>(p.cand_idx), at<int32_t>(p.tokens),
                                  at<int32_t>(p.len), at<float>(p.score), at<int32_t>(p.active), step, M, ks, hp.topp, T,
-                                 (unsigned long long)hp.seed, hp.cap_extra, s));
+                                 (unsigned long long)hp.seed, hp.cap_extra, s, nullptr, nullptr, nullptr, -1, &g.page->step));
   return LSQ_OK;
 }
 
 // One decode step: replay the captured graph for this number of live sentences, capturing it on
 // first use.  Graphs need a capturable (non-default) stream and are bypassed while per-kernel
-// timing is on.
+// timing is on, and for steps of a few launches (decoder stack kernel): between two graphs pass about 5 us, more than
+// those launches take on their own (Transformer-base, 1 sentence: 125.2 us a step replayed, 120.0 launched; the 15
+// launches of the tiny model: 69 and 83).
 int enqueue_step() {
   const int B = g.alive_at[g.t];
   auto launch = [&](int n) { return g.hp.arch == 1 ? launch_step_gpt(n) : launch_step(n); };
   g.hidden_in_alt = false;   // launch_step says otherwise
-  if (!g.use_graphs || g.stream == nullptr || g_prof.on) {
+  if (!g.use_graphs || g.stream == nullptr || g_prof.on || use_stack(B * g.beam)) {
     int rc = launch(B);
     if (rc) return rc;
     g.t += 1;
@@ -820,15 +831,33 @@ int enqueue_step() {
 
 // after a wait for the stream: whether a workgroup of the decoder stack kernel gave up waiting for the others
 int stack_waits_ended() {
-  if (g.pinned[g.pinned_ints - 2]) return fail(LSQ_E_HIP, "decoder stack kernel: a workgroup waited too long for the others");
+  if (*(volatile int32_t*)&g.page->error) return fail(LSQ_E_HIP, "decoder stack kernel: a workgroup waited too long for the others");
   return LSQ_OK;
 }
 
-int read_active(int step, int* out) {
-  int32_t* slot = g.pinned + g.pinned_ints - 1;
-  HIPCHK(hipMemcpyAsync(slot, at<int32_t>(g.plan.active) + step, 4, hipMemcpyDeviceToHost, g.stream));
+// Waits until `steps` steps of this translation are done and returns how many sentences go on.  The step's last kernel
+// writes both into pinned memory, where they are seen several microseconds before a copy of the counter and a wait for
+// the stream would have returned; the stream is asked now and then, in case it ended without them.
+int read_active(int steps, int* out) {
+  const volatile unsigned long long* word = &g.page->step;
+  for (unsigned spin = 1;; ++spin) {
+    const unsigned long long v = *word;
+    if ((int)(v >> 32) == steps) { *out = (int)(v & 0xFFFFFFFFu); return stack_waits_ended(); }
+    if (spin % 65536 == 0) {
+      const hipError_t e = hipStreamQuery(g.stream);
+      if (e != hipErrorNotReady) {
+        HIPCHK(e);
+        break;
+      }
+    }
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
+  }
+  int32_t n = 0;
+  HIPCHK(hipMemcpyAsync(&n, at<int32_t>(g.plan.active) + steps - 1, 4, hipMemcpyDeviceToHost, g.stream));
   HIPCHK(hipStreamSynchronize(g.stream));
-  *out = *slot;
+  *out = n;
   return stack_waits_ended();
 }
 
@@ -872,19 +901,14 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
   h_step[0] = P - 1; h_step[1] = 0; h_step[2] = P - 1; h_step[3] = 0;
   g.alive_at.assign(g.max_len + 1, 0);
   for (int t = 0; t < n_new && t <= g.max_len; ++t) g.alive_at[t] = batch;
+  Staging st{};
   if (R > 0) {
-    HIPCHK(hipMemcpyAsync(g.ws + p.e_ids, h_ids, (size_t)R * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(g.ws + p.e_pos, h_pos, (size_t)R * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(g.ws + p.e_sent, h_sent, (size_t)R * 4, hipMemcpyHostToDevice, s));
+    st.add(at<int32_t>(p.e_ids), h_ids, R); st.add(at<int32_t>(p.e_pos), h_pos, R); st.add(at<int32_t>(p.e_sent), h_sent, R);
   }
-  HIPCHK(hipMemcpyAsync(g.ws + p.src_off, h_off, (size_t)(batch + 1) * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.src_len, h_len, (size_t)batch * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.order, h_order, (size_t)batch * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.tokens, h_tok, (size_t)batch * (T + 1) * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.len, h_row, (size_t)batch * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.step_state, h_step, 16, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemsetAsync(g.ws + p.score, 0, (size_t)batch * 4, s));
-  HIPCHK(hipMemsetAsync(g.ws + p.active, 0, (size_t)(T + 1) * 4, s));
+  st.add(at<int32_t>(p.src_off), h_off, batch + 1); st.add(at<int32_t>(p.src_len), h_len, batch); st.add(at<int32_t>(p.order), h_order, batch);
+  st.add(at<int32_t>(p.tokens), h_tok, (size_t)batch * (T + 1)); st.add(at<int32_t>(p.len), h_row, batch);
+  st.add(at<int32_t>(p.step_state), h_step, 4); st.add(at<int32_t>(p.score), nullptr, batch); st.add(at<int32_t>(p.active), nullptr, T + 1);
+  HIPCHK(launch_staging(st, s));
 
   const int dt = hp.dtype, d = hp.d, F = hp.F, H = hp.H;
   const size_t es = esz();
@@ -1030,10 +1054,13 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
 
   for (size_t c : plan.canaries) HIPCHK(hipMemsetAsync(g.ws + c, kCanaryByte, kCanaryBytes, g.stream));
   HIPCHK(hipStreamSynchronize(g.stream));
-  g.pinned_ints = (size_t)3 * max_batch * max_len + 4 * (size_t)max_batch + 2 + (size_t)max_batch * (max_len + 2) + 8;   // the last two: error flag of the decoder stack kernel, active count
-  HIPCHK(hipHostMalloc((void**)&g.pinned, g.pinned_ints * 4, hipHostMallocDefault));
+  g.pinned_ints = (size_t)3 * max_batch * max_len + 4 * (size_t)max_batch + 2 + (size_t)max_batch * (max_len + 2) + 8;
+  HIPCHK(hipHostMalloc((void**)&g.pinned, g.pinned_ints * 4, hipHostMallocCoherent));
+  HIPCHK(hipHostMalloc((void**)&g.page, sizeof(HostPage), hipHostMallocCoherent));
+  *g.page = HostPage{0, 0};
+  const size_t result_bytes = (size_t)max_batch * beam * (max_len + 2) * 4;
+  if (result_bytes <= kResultsMax) HIPCHK(hipHostMalloc((void**)&g.results, result_bytes, hipHostMallocCoherent));
 
-  g.pinned[g.pinned_ints - 2] = 0;
   if (plan.stack_set) HIPCHK(launch_stack_reset(g.ws + plan.stack_exchange, 2 * plan.stack_set, (int32_t*)(g.ws + plan.stack_state), g.stream));
 
   g.hp = hp;
@@ -1088,10 +1115,11 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
     R += n;
   }
   HIPCHK(hipStreamSynchronize(g.stream));   // the staging buffer may still feed an earlier copy
-  if (g.pinned[g.pinned_ints - 2]) {   // an earlier translation was given up: its exchange regions are in no known state
+  if (g.page->error) {   // an earlier translation was given up: its exchange regions are in no known state
     HIPCHK(launch_stack_reset(g.ws + g.plan.stack_exchange, 2 * g.plan.stack_set, at<int32_t>(g.plan.stack_state), g.stream));
-    g.pinned[g.pinned_ints - 2] = 0;
+    g.page->error = 0;
   }
+  g.page->step = 0;
   const int groups = hp.arch == 0 ? g.groups_next : 1;
   if (g.beam % groups != 0) return fail(LSQ_E_ARG, "beam %d is not a multiple of %d groups", g.beam, groups);
   const bool anc_on = hp.arch == 0 && g.beam > 1 && g.refresh_mode == 1;
@@ -1144,13 +1172,11 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
   }
   h_off[batch] = r;
   hipStream_t s = g.stream;
-  HIPCHK(hipMemcpyAsync(g.ws + p.e_ids, h_ids, (size_t)R * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.e_pos, h_pos, (size_t)R * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.e_sent, h_sent, (size_t)R * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.src_off, h_off, (size_t)(batch + 1) * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.src_len, h_len, (size_t)batch * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.cap, h_cap, (size_t)batch * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(g.ws + p.order, h_order, (size_t)batch * 4, hipMemcpyHostToDevice, s));
+  Staging st{};
+  st.add(at<int32_t>(p.e_ids), h_ids, R); st.add(at<int32_t>(p.e_pos), h_pos, R); st.add(at<int32_t>(p.e_sent), h_sent, R);
+  st.add(at<int32_t>(p.src_off), h_off, batch + 1); st.add(at<int32_t>(p.src_len), h_len, batch);
+  st.add(at<int32_t>(p.cap), h_cap, batch); st.add(at<int32_t>(p.order), h_order, batch);
+  HIPCHK(launch_staging(st, s));
 
   const int dt = hp.dtype, d = hp.d, F = hp.F, H = hp.H;
   const size_t es = esz();
@@ -1215,7 +1241,7 @@ int lsq_decode_steps(int n) {
     ++issued;
   }
   int active = 0;
-  int rc = read_active(g.t - 1, &active);
+  int rc = read_active(g.t, &active);
   if (rc) return rc;
   if (active == 0) g.done = true;
   return active;
@@ -1330,14 +1356,24 @@ int lsq_get_beams(int32_t* out_ids, int32_t* out_lens, float* out_scores) {
   if (!out_ids || !out_lens || !out_scores) return fail(LSQ_E_ARG, "an output pointer is null");
   const Plan& p = g.plan;
   const int M = g.batch * g.beam, T = g.max_len;
-  HIPCHK(launch_finalize(at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.out_ids),
-                         at<int32_t>(p.out_lens), at<float>(p.out_scores), at<int32_t>(p.order), g.batch, g.beam,
-                         T, g.hp.arch == 1 ? 0.0f : g.hp.alpha, g.hp.pad, g.hp.arch == 1 ? g.prompt_len : 1,
+  // straight into pinned host memory where that is kept: one wait instead of three copies into pageable memory
+  int32_t* ids = g.results ? g.results : at<int32_t>(p.out_ids);
+  int32_t* lens = g.results ? ids + (size_t)M * T : at<int32_t>(p.out_lens);
+  float* scores = g.results ? (float*)(lens + M) : at<float>(p.out_scores);
+  HIPCHK(launch_finalize(at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), ids, lens, scores, at<int32_t>(p.order),
+                         g.batch, g.beam, T, g.hp.arch == 1 ? 0.0f : g.hp.alpha, g.hp.pad, g.hp.arch == 1 ? g.prompt_len : 1,
                          g.stream));
-  HIPCHK(hipMemcpyAsync(out_ids, g.ws + p.out_ids, (size_t)M * T * 4, hipMemcpyDeviceToHost, g.stream));
-  HIPCHK(hipMemcpyAsync(out_lens, g.ws + p.out_lens, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
-  HIPCHK(hipMemcpyAsync(out_scores, g.ws + p.out_scores, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
+  if (!g.results) {
+    HIPCHK(hipMemcpyAsync(out_ids, ids, (size_t)M * T * 4, hipMemcpyDeviceToHost, g.stream));
+    HIPCHK(hipMemcpyAsync(out_lens, lens, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
+    HIPCHK(hipMemcpyAsync(out_scores, scores, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
+  }
   HIPCHK(hipStreamSynchronize(g.stream));
+  if (g.results) {
+    memcpy(out_ids, ids, (size_t)M * T * 4);
+    memcpy(out_lens, lens, (size_t)M * 4);
+    memcpy(out_scores, scores, (size_t)M * 4);
+  }
   return stack_waits_ended();
 }
 
@@ -1351,6 +1387,8 @@ void lsq_free(void) {
   if (g.pinned) {
     if (g.stream || g.state >= 2) (void)hipStreamSynchronize(g.stream);
     (void)hipHostFree(g.pinned);
+    (void)hipHostFree(g.page);
+    if (g.results) (void)hipHostFree(g.results);
   }
   gemm_clear_packed();
   g = Ctx{};
