@@ -337,17 +337,26 @@ __device__ __forceinline__ void topk_groups_row(const float* __restrict__ logits
   for (int q = 0; q < GPL; ++q) cg[q] = (q * 64 + lane < G) ? cand_of(gm[q]) : -INFINITY;
   // R: every lane's best group value is the value of a distinct token; the k-th largest of those 64 is
   // reached by k tokens, so it is a valid threshold (at most the k-th largest group value, and close to it
-  // when there are many more groups than k).  Ranked by (value, lane): 64 broadcasts, whatever k.
+  // when there are many more groups than k).
   float lm = -INFINITY;
 #pragma unroll
   for (int q = 0; q < GPL; ++q) lm = fmaxf(lm, cg[q]);
-  int lrank = 0;
+  float R = -INFINITY;   // fewer than k groups: -inf, every token passes
+  if (k <= LSQ_MAX_BEAM_) {   // k rounds of the wavefront's maximum, one lane leaving each time
+    float left = lm;
+    for (int i = 0; i < k; ++i) {
+      R = wave_max(left);
+      if (lane == (int)__builtin_ctzll(__ballot(left == R))) left = -INFINITY;
+    }
+  } else {
+    int lrank = 0;
 #pragma unroll
-  for (int c = 0; c < 64; ++c) {
-    const float o = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lm), c));
-    lrank += (o > lm || (o == lm && c < lane)) ? 1 : 0;
+    for (int c = 0; c < 64; ++c) {
+      const float o = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lm), c));
+      lrank += (o > lm || (o == lm && c < lane)) ? 1 : 0;
+    }
+    R = wave_max(lrank == k - 1 ? lm : -INFINITY);
   }
-  const float R = wave_max(lrank == k - 1 ? lm : -INFINITY);   // fewer than k groups: -inf, every token passes
   // the groups that reach R
   int nq = 0;
 #pragma unroll
@@ -566,50 +575,65 @@ __device__ __forceinline__ void end_of_step(int32_t* active, int t, int32_t* ste
     __hip_atomic_store(report, ((unsigned long long)(t + 1) << 32) | (unsigned)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// What the re-rank stage reads besides the candidates, requested together (one trip to memory instead of one per
+// phase) and, where the retrieve stage runs in the same kernel, before that one: the step, the state of the beam a
+// candidate continues (lane c continues beam c / k whatever its rank turns out to be), the sentence's length cap and
+// this lane's first position of the k token histories and slab tables.
+// No request sits behind a test of something that is itself read from memory: lanes past the k*k candidates repeat the
+// last one and positions past the step repeat the last position of the histories (both discarded later), so every load
+// can leave before the step counter has arrived.
+struct RerankState {
+  int t, plen, pfin, cap_b;
+  int h[LSQ_MAX_BEAM_], ha[LSQ_MAX_BEAM_];
+};
+__device__ __forceinline__ void rerank_history(RerankState& st, const int32_t* __restrict__ tokens, const int32_t* __restrict__ anc,
+                                               int base, int k, int T1, int p) {
+  const int pc = min(p, T1 - 1);
+#pragma unroll
+  for (int i = 0; i < LSQ_MAX_BEAM_; ++i)
+    if (i < k) {
+      st.h[i] = tokens[(size_t)(base + i) * T1 + pc];
+      st.ha[i] = anc ? anc[(size_t)(base + i) * T1 + pc] : 0;
+    }
+}
+__device__ __forceinline__ RerankState rerank_request(const int32_t* __restrict__ tokens, const int32_t* __restrict__ len,
+                                                      const int32_t* __restrict__ fin, const int32_t* __restrict__ cap,
+                                                      const int32_t* __restrict__ anc, int k, int T1, int t_base,
+                                                      const int32_t* __restrict__ step_state, const SearchGroups& gr, int b, int lane) {
+  RerankState st;
+  const int base = b * (gr.k_all > 1 ? gr.k_all : k) + gr.goff, j = min(lane, k * k - 1) / k;
+  st.t = t_base + (step_state ? step_state[0] : 0);
+  st.plen = len[base + j];
+  st.pfin = fin[base + j];
+  st.cap_b = cap[b];
+  rerank_history(st, tokens, anc, base, k, T1, lane);
+  return st;
+}
+
 // cand_score / cand_idx: the sentence's k*k survivors at [(row - first row of the launch's unit) ...]: pointers to the
 // pairs of row `base` (global memory, or LDS when the retrieve stage ran in the same workgroup).
 template <bool ALONE>
 __device__ __forceinline__ void rerank_sentence(const float* cand_score_b, const int32_t* cand_idx_b, const float* plain_b,
                                                 float* __restrict__ score, int32_t* __restrict__ tokens,
                                                 int32_t* __restrict__ len, int32_t* __restrict__ fin,
-                                                int32_t* __restrict__ parent, const int32_t* __restrict__ cap,
+                                                int32_t* __restrict__ parent,
                                                 int32_t* __restrict__ active, int k, int V, int T1, int t_base,
                                                 int32_t* __restrict__ step_state, int eos, int32_t* __restrict__ anc,
                                                 const SearchGroups& gr, const NextInput& nx, int b, int lane,
                                                 int* sh_parent, int* sh_tok, int& sh_unfinished, int& sh_taken,
-                                                unsigned long long* report) {
-  const int t = t_base + (step_state ? step_state[0] : 0);
+                                                unsigned long long* report, RerankState st) {
+  const int t = st.t, plen = st.plen, pfin = st.pfin, cap_b = st.cap_b;
   const int kk = k * k;
   const int k_all = gr.k_all > 1 ? gr.k_all : k;           // rows of a sentence (k_all == 1: no groups)
   const int base = b * k_all + gr.goff;                    // first row of this group
   if (lane == 0) { sh_unfinished = 0; sh_taken = 0; }
   if (lane < LSQ_MAX_BEAM_) sh_tok[lane] = -1;
-  // Everything the kernel reads is requested here, before any of it is used (one trip to memory
-  // instead of one per phase): the candidates, the state of the beam a candidate continues (lane
-  // c continues beam c / k whatever its rank turns out to be), the sentence's length cap and this
-  // lane's first position of the k token histories and slab tables.
-  // No request sits behind a test of something that is itself read from memory: lanes past the
-  // k*k candidates repeat the last one and positions past the step repeat the last position of the
-  // histories (both discarded below), so every load can leave before the step counter has arrived.
   const int cl = min(lane, kk - 1);
   const int j = cl / k;
   float s = cand_score_b[cl];
   float plain = plain_b ? plain_b[cl] : s;
   int tok = cand_idx_b[cl];
-  const int plen = len[base + j], pfin = fin[base + j];
-  const int cap_b = cap[b];
   int p = lane;
-  int h[LSQ_MAX_BEAM_], ha[LSQ_MAX_BEAM_];
-  auto fetch = [&]() {
-    const int pc = min(p, T1 - 1);
-#pragma unroll
-    for (int i = 0; i < LSQ_MAX_BEAM_; ++i)
-      if (i < k) {
-        h[i] = tokens[(size_t)(base + i) * T1 + pc];
-        ha[i] = anc ? anc[(size_t)(base + i) * T1 + pc] : 0;
-      }
-  };
-  fetch();
   if (lane >= kk) { s = -INFINITY; plain = -INFINITY; tok = -1; }
   long flat = -1;
   if (tok >= 0) flat = (long)(gr.goff + j) * V + tok;
@@ -634,14 +658,14 @@ __device__ __forceinline__ void rerank_sentence(const float* cand_score_b, const
         int src = sh_parent[i], val = 0, vala = 0;
 #pragma unroll
         for (int jj = 0; jj < LSQ_MAX_BEAM_; ++jj)
-          if (jj == src) { val = h[jj]; vala = ha[jj]; }
+          if (jj == src) { val = st.h[jj]; vala = st.ha[jj]; }
         if (src != i) {
           tokens[(size_t)(base + i) * T1 + p] = val;
           if (anc) anc[(size_t)(base + i) * T1 + p] = vala;
         }
       }
     p += 64;
-    if (p <= t && p < T1) fetch();   // a history longer than 64 positions: one more trip per 64
+    if (p <= t && p < T1) rerank_history(st, tokens, anc, base, k, T1, p);   // a history longer than 64 positions: one more trip per 64
   }
   if (anc && lane < k && t + 1 < T1) anc[(size_t)(base + lane) * T1 + t + 1] = gr.goff + lane;
   rerank_sync<ALONE>();
@@ -666,23 +690,24 @@ __device__ __forceinline__ void rerank_sentence(const float* cand_score_b, const
     if (!nfin) sh_unfinished = 1;
   }
   rerank_sync<ALONE>();
+  if (gr.pen_n && lane == 0) gr.pen_n[b] = gr.last ? 0 : gr.pen_n[b] + sh_taken;
+  // the sentence is still active if any hypothesis of any group is unfinished (the other groups'
+  // rows were settled by earlier launches, or passes, of this step)
+  if (gr.last) {
+    int others = 0;
+    if (lane < k_all && (lane < gr.goff || lane >= gr.goff + k)) others = fin[b * k_all + lane] ? 0 : 1;
+    others = __any(others) ? 1 : 0;
+    if (lane == 0) {
+      const int go_on = sh_unfinished || others ? 1 : 0;
+      if (step_state) end_of_step(active, t, step_state, t + 1 - t_base, go_on, (int)gridDim.x, report);
+      else if (go_on) atomicAdd(active, 1);   // the caller's counter
+    }
+  }
   // The next step's decoder input of these rows (one launch less per step).  A row that no candidate won
   // (fewer live candidates than beams) embeds nothing: it is dead and stays so.
   if (nx.E && t + 1 < T1 - 1) {
     if (nx.dtype == DT_F16) next_input_rows<half_t>(nx, sh_tok, base, k, t + 1, lane);
     else next_input_rows<float>(nx, sh_tok, base, k, t + 1, lane);
-  }
-  if (gr.pen_n && lane == 0) gr.pen_n[b] = gr.last ? 0 : gr.pen_n[b] + sh_taken;
-  if (!gr.last) return;
-  // the sentence is still active if any hypothesis of any group is unfinished (the other groups'
-  // rows were settled by earlier launches of this step)
-  int others = 0;
-  if (lane < k_all && (lane < gr.goff || lane >= gr.goff + k)) others = fin[b * k_all + lane] ? 0 : 1;
-  others = __any(others) ? 1 : 0;
-  if (lane == 0) {
-    const int go_on = sh_unfinished || others ? 1 : 0;
-    if (step_state) end_of_step(active, t, step_state, t + 1 - t_base, go_on, (int)gridDim.x, report);
-    else if (go_on) atomicAdd(active, 1);   // the caller's counter
   }
 }
 
@@ -701,9 +726,10 @@ __global__ void __launch_bounds__(64) beam_refine_kernel(const float* __restrict
   const int b = blockIdx.x;
   const int k_all = gr.k_all > 1 ? gr.k_all : k;
   const size_t first = ((size_t)b * k_all + gr.goff) * k;   // the pairs of the unit's first row
+  const RerankState st = rerank_request(tokens, len, fin, cap, anc, k, T1, t_base, step_state, gr, b, (int)threadIdx.x);
   rerank_sentence<true>(cand_score + first, cand_idx + first, gr.out_plain ? gr.out_plain + first : nullptr, score, tokens, len,
-                        fin, parent, cap, active, k, V, T1, t_base, step_state, eos, anc, gr, nx, b, (int)threadIdx.x,
-                        sh_parent, sh_tok, sh_unfinished, sh_taken, report);
+                        fin, parent, active, k, V, T1, t_base, step_state, eos, anc, gr, nx, b, (int)threadIdx.x,
+                        sh_parent, sh_tok, sh_unfinished, sh_taken, report, st);
 }
 
 // Retrieve and re-rank in one launch (plain beam search from the logit product's group statistics): a workgroup
@@ -724,6 +750,8 @@ __global__ void __launch_bounds__(64 * LSQ_MAX_BEAM_) retrieve_rerank_kernel(
   __shared__ int sh_unfinished, sh_taken;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int b = blockIdx.x;
+  RerankState st = {};
+  if (wave == 0) st = rerank_request(tokens, len, fin, cap, anc, k, T1, 0, step_state, one_group(), b, lane);
   topk_groups_row<GPL>(logits, stats, score, fin, b * k + wave, V, G, k, eos, cand_s + wave * k, cand_i + wave * k, lane,
                        ql[wave], cs[wave], ci[wave]);
   __syncthreads();   // blockDim.x = 64 k: every wavefront has a row
@@ -732,8 +760,64 @@ __global__ void __launch_bounds__(64 * LSQ_MAX_BEAM_) retrieve_rerank_kernel(
     cand_out_i[(size_t)b * k * k + threadIdx.x] = cand_i[threadIdx.x];
   }
   if (wave != 0) return;
-  rerank_sentence<false>(cand_s, cand_i, nullptr, score, tokens, len, fin, parent, cap, active, k, V, T1, 0, step_state, eos,
-                         anc, one_group(), nx, b, lane, sh_parent, sh_tok, sh_unfinished, sh_taken, report);
+  rerank_sentence<false>(cand_s, cand_i, nullptr, score, tokens, len, fin, parent, active, k, V, T1, 0, step_state, eos,
+                         anc, one_group(), nx, b, lane, sh_parent, sh_tok, sh_unfinished, sh_taken, report, st);
+}
+
+// Diverse beam search from the group statistics, all groups of a sentence in one launch: every row's k_all best tokens
+// without a penalty hold its kg best with one (at most k_all - kg tokens carry a penalty, all others keep their order), so
+// the wavefronts retrieve those once, and the first one then takes the groups in turn: penalties of the tokens the earlier
+// groups took, the kg best of every row of the group, re-rank.  6 launches of 7 and 13 us for three groups before.
+template <int GPL>
+__global__ void __launch_bounds__(64 * LSQ_MAX_BEAM_) retrieve_rerank_groups_kernel(
+    const float* __restrict__ logits, const float* __restrict__ stats, float* __restrict__ score, int32_t* __restrict__ tokens,
+    int32_t* __restrict__ len, int32_t* __restrict__ fin, int32_t* __restrict__ parent, const int32_t* __restrict__ cap,
+    int32_t* __restrict__ active, int kg, int k_all, int V, int G, int T1, int32_t* __restrict__ step_state, int eos,
+    int32_t* __restrict__ anc, float strength, NextInput nx, unsigned long long* report) {
+  __shared__ int ql[LSQ_MAX_BEAM_][kTopkGroupsQ];
+  __shared__ float cs[LSQ_MAX_BEAM_][kTopkGroupsC];
+  __shared__ int ci[LSQ_MAX_BEAM_][kTopkGroupsC];
+  __shared__ float row_s[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
+  __shared__ int row_i[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
+  __shared__ float cand_s[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_], cand_p[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
+  __shared__ int cand_i[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
+  __shared__ int sh_parent[LSQ_MAX_BEAM_], sh_tok[LSQ_MAX_BEAM_];
+  __shared__ int sh_unfinished, sh_taken, taken[LSQ_MAX_BEAM_], n_taken;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int b = blockIdx.x;
+  topk_groups_row<GPL>(logits, stats, score, fin, b * k_all + wave, V, G, k_all, eos, row_s + wave * k_all, row_i + wave * k_all,
+                       lane, ql[wave], cs[wave], ci[wave]);
+  if (threadIdx.x == 0) n_taken = 0;
+  __syncthreads();
+  if (wave != 0) return;
+  for (int g0 = 0; g0 < k_all; g0 += kg) {
+    // pen_tok / pen_n are this sentence's own here: indexed from the sentence's number on with a stride of 0
+    SearchGroups gr{kg, k_all, g0, taken, &n_taken - b, 0, strength, nullptr, g0 + kg == k_all ? 1 : 0};
+    const RerankState st = rerank_request(tokens, len, fin, cap, anc, kg, T1, 0, step_state, gr, b, lane);
+    const int i = min(lane / k_all, kg - 1), c = lane % k_all, row = g0 + i;   // candidate c of the group's row i
+    const bool mine = lane < kg * k_all;
+    const bool done = fin[b * k_all + row] != 0;
+    const float plain = row_s[row * k_all + c];
+    const int tok = row_i[row * k_all + c];
+    int cnt = 0;
+    for (int p = 0; p < n_taken; ++p) cnt += taken[p] == tok ? 1 : 0;
+    const float val = done || cnt == 0 ? plain : __fsub_rn(plain, __fmul_rn(strength, (float)cnt));
+    int rank = 0;
+    for (int o = 0; o < k_all; ++o) {   // among the row's candidates; empty slots (-1) come last
+      const int src = min(i * k_all + o, 63);
+      const float v2 = __shfl(val, src, kWave);
+      const int t2 = __shfl(tok, src, kWave);
+      rank += o != c && t2 >= 0 && (tok < 0 || precedes(v2, t2, val, tok)) ? 1 : 0;
+      if (tok < 0 && t2 < 0 && o < c) ++rank;
+    }
+    if (mine && rank < kg) {
+      cand_s[i * kg + rank] = val; cand_p[i * kg + rank] = plain; cand_i[i * kg + rank] = tok;
+    }
+    rerank_sync<false>();
+    rerank_sentence<false>(cand_s, cand_i, cand_p, score, tokens, len, fin, parent, active, kg, V, T1, 0, step_state, eos, anc, gr,
+                           nx, b, lane, sh_parent, sh_tok, sh_unfinished, sh_taken, report, st);
+    rerank_sync<false>();
+  }
 }
 
 hipError_t launch_beam_refine(const float* cand_score, const int32_t* cand_idx, float* score, int32_t* tokens,
@@ -765,6 +849,24 @@ hipError_t launch_retrieve_rerank(const float* logits, const float* stats, float
   else if (G <= 64 * 16) LSQ_RR(16);
   else LSQ_RR(32);
 #undef LSQ_RR
+  return hipGetLastError();
+}
+
+hipError_t launch_retrieve_rerank_groups(const float* logits, const float* stats, float* score, int32_t* tokens, int32_t* len,
+                                         int32_t* fin, int32_t* parent, const int32_t* cap, int32_t* active, int batch, int kg,
+                                         int k_all, int V, int T, int32_t* step_state, int eos, int32_t* anc, float strength,
+                                         hipStream_t s, const NextInput& nx, unsigned long long* report) {
+  if (batch <= 0) return hipSuccess;
+  if (!topk_groups_supported(V, k_all, 0) || !stats || !step_state || kg < 1 || k_all % kg != 0) return hipErrorInvalidValue;
+  const int G = (V + 31) / 32;
+  dim3 g(batch), b(64 * k_all);
+#define LSQ_RG(GPL_)                                                                                                              \
+  retrieve_rerank_groups_kernel<GPL_><<<g, b, 0, s>>>(logits, stats, score, tokens, len, fin, parent, cap, active, kg, k_all, V, G, \
+                                                      T + 1, step_state, eos, anc, strength, nx, report)
+  if (G <= 64 * 4) LSQ_RG(4);
+  else if (G <= 64 * 16) LSQ_RG(16);
+  else LSQ_RG(32);
+#undef LSQ_RG
   return hipGetLastError();
 }
 
@@ -963,6 +1065,45 @@ __device__ __forceinline__ bool sample_row(const float* cl, const int32_t* ci, i
   return unfinished;
 }
 
+// The same draw by the row's wavefront, lane j holding candidate j: the running sums are taken in the same order, the
+// searches are ballots.  (One lane alone kept both arrays in scratch memory: 18 us for k = 32.)
+struct SampleState { int place, cap_r; float logp_r; };
+__device__ __forceinline__ bool sample_row_wave(const float* cl, const int32_t* ci, int r, int lane, int32_t* __restrict__ tokens,
+                                                int32_t* __restrict__ len, float* __restrict__ logp, int k, float topp, int T1,
+                                                unsigned seed_lo, unsigned seed_hi, int pos, int t, int32_t* __restrict__ fin,
+                                                int eos, const SampleState& st, int& tok_out) {
+  const int jl = min(lane, k - 1);
+  const float e = expf(cl[jl] - cl[0]);
+  const int cand = ci[jl];
+  float run = 0.f, cum = INFINITY;   // lanes past k reach every mass and are never the first to
+  for (int j = 0; j < k; ++j) {
+    run += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, e), j));
+    if (lane == j) cum = run;
+  }
+  int n = k;
+  if (topp < 1.0f) {
+    const float thresh = __fmul_rn(topp, run);
+    const unsigned long long reach = __ballot(lane < k && cum >= thresh);
+    n = reach ? (int)__builtin_ctzll(reach) + 1 : k;
+  }
+  const float total = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cum), n - 1));
+  const unsigned word = philox4x32_10_first((unsigned)t, (unsigned)st.place, 0u, 0u, seed_lo, seed_hi);
+  const float u = (float)(word >> 8) * 5.9604644775390625e-08f;   // 2^-24
+  const float target = __fmul_rn(u, total);
+  const unsigned long long above = __ballot(lane < n - 1 && cum > target);
+  const int j = above ? (int)__builtin_ctzll(above) : n - 1;
+  const int tok = __builtin_amdgcn_readlane(cand, j);
+  tok_out = tok;
+  const bool unfinished = !(tok == eos || pos + 1 >= st.cap_r);
+  if (lane == j) {
+    tokens[(size_t)r * T1 + pos + 1] = tok;
+    len[r] = pos + 1;
+    logp[r] = st.logp_r + logf(e / total);
+    if (fin) fin[r] = unfinished ? 0 : 1;
+  }
+  return fin && unfinished;
+}
+
 __global__ void __launch_bounds__(64) sample_kernel(const float* __restrict__ cand_logit,
                                                     const int32_t* __restrict__ cand_idx,
                                                     int32_t* __restrict__ tokens, int32_t* __restrict__ len,
@@ -1006,7 +1147,9 @@ __global__ void __launch_bounds__(256) retrieve_sample_kernel(const float* __res
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + wave;
   if (r >= rows) return;
+  // everything besides the candidates is requested before they are looked for
   const int pos = step_state[0], t = pos - step_state[2];
+  const SampleState st = {order ? order[r] : r, fin ? cap[r] : 0, logp[r]};
   const bool done = fin && fin[r];   // the same in every lane
   if (!done) {
     topk_groups_row<GPL>(logits, stats, nullptr, nullptr, r, V, G, k, eos, cand_s[wave], cand_i[wave], lane, ql[wave], cs[wave],
@@ -1020,13 +1163,13 @@ __global__ void __launch_bounds__(256) retrieve_sample_kernel(const float* __res
     cand_out_i[(size_t)r * k + lane] = cand_i[wave][lane];
   }
   bool unfinished = false;
-  if (lane == 0) {
-    int tok = -1;
-    if (!done)
-      unfinished = sample_row(cand_s[wave], cand_i[wave], r, tokens, len, logp, k, topp, T1, seed_lo, seed_hi, pos, t, fin, cap,
-                              order, eos, tok);
-    next_tok[wave] = tok;
-  }
+  int tok = -1;
+  if (!done)
+    unfinished = sample_row_wave(cand_s[wave], cand_i[wave], r, lane, tokens, len, logp, k, topp, T1, seed_lo, seed_hi, pos, t, fin,
+                                 eos, st, tok);
+  // one count per row: the last row advances the position
+  if (lane == 0) end_of_step(active, t, step_state, pos + 1, unfinished ? 1 : 0, rows, report, fin ? -1 : t + 1 < n_new ? rows : 0);
+  if (lane == 0) next_tok[wave] = tok;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -1034,8 +1177,6 @@ __global__ void __launch_bounds__(256) retrieve_sample_kernel(const float* __res
     if (nx.dtype == DT_F16) next_input_rows<half_t>(nx, &next_tok[wave], r, 1, pos + 1, lane);
     else next_input_rows<float>(nx, &next_tok[wave], r, 1, pos + 1, lane);
   }
-  // one count per row: the last row advances the position
-  if (lane == 0) end_of_step(active, t, step_state, pos + 1, unfinished ? 1 : 0, rows, report, fin ? -1 : t + 1 < n_new ? rows : 0);
 }
 
 hipError_t launch_sample(const float* cand_logit, const int32_t* cand_idx, int32_t* tokens, int32_t* len,

@@ -263,6 +263,11 @@ hipError_t launch_retrieve_rerank(const float* logits, const float* stats, float
                                   const NextInput& next = no_next_input(), float* cand_score = nullptr,
                                   int32_t* cand_idx = nullptr,   // cand_*: the survivors are also left there
                                    unsigned long long* report = nullptr);
+// diverse beam search: all groups of all sentences (k_all hypotheses in groups of kg) in one launch
+hipError_t launch_retrieve_rerank_groups(const float* logits, const float* stats, float* score, int32_t* tokens, int32_t* len,
+                                         int32_t* fin, int32_t* parent, const int32_t* cap, int32_t* active, int batch, int kg,
+                                         int k_all, int V, int T, int32_t* step_state, int eos, int32_t* anc, float strength,
+                                         hipStream_t s, const NextInput& next, unsigned long long* report);
 // npos = npos_base + (tp ? *tp : 0); the grid covers npos_max positions
 hipError_t launch_cache_reorder(int dtype, void* cache, const int32_t* parent, int layers, int batch,
                                 int rows_total, int k, int T, int d, int npos_base, const int32_t* tp,

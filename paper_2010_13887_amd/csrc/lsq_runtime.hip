@@ -607,7 +607,7 @@ int launch_step(int B) {
   // groups as the groups)
   const bool sampling = hp.sample_topk > 0;
   const bool from_stats = (sampling && g.sample_fold) ||
-                          (g.topk_stats && g.groups == 1 && gemm_writes_stats(dt, M, V, d) &&
+                          (g.topk_stats && (g.groups == 1 || g.merge_rerank) && gemm_writes_stats(dt, M, V, d) &&
                            topk_groups_supported(V, sampling ? hp.sample_topk : k, sampling ? 1 : 0));
   if (from_stats) { lo.stats = at<float>(p.d_stats); lo.stats_groups = (V + 31) / 32; }
   if (int rc = product(PC_GEMM_VOCAB, g.E, nullptr, lo, V, 0)) return rc;
@@ -639,7 +639,12 @@ int launch_step(int B) {
     // diverse beam search: the groups of a sentence choose one after the other, each steered away
     // from the tokens the earlier ones took at this step
     const int kg = k / g.groups;
-    for (int gi = 0; gi < g.groups; ++gi) {
+    if (from_stats)
+      TIMED(PC_RETRIEVE_RERANK, launch_retrieve_rerank_groups((const float*)logits, at<float>(p.d_stats), at<float>(p.score),
+                                                              at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
+                                                              at<int32_t>(p.parent), at<int32_t>(p.cap), at<int32_t>(p.active), B, kg, k,
+                                                              V, T, step, hp.eos, anc, g.strength, s, next, report));
+    for (int gi = 0; gi < g.groups && !from_stats; ++gi) {
       SearchGroups gr{kg, k, gi * kg, at<int32_t>(p.pen_tok), at<int32_t>(p.pen_n), k, g.strength,
                       at<float>(p.cand_plain), gi + 1 == g.groups ? 1 : 0};
       TIMED(PC_ROW_TOPK, launch_row_topk(DT_F32, logits, at<float>(p.score), at<int32_t>(p.fin), B * kg, V, kg, hp.eos,
