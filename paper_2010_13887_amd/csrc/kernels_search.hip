@@ -363,6 +363,7 @@ __device__ __forceinline__ void topk_groups_row(const float* __restrict__ logits
   for (int q = 0; q < GPL; ++q) {
     const bool in = q * 64 + lane < G && cg[q] >= R;
     const unsigned long long mask = __ballot(in);
+    if (mask == 0) continue;   // nearly always
     if (in) {
       const int at = nq + __popcll(mask & ((1ull << lane) - 1ull));
       if (at < QMAX) ql_w[at] = q * 64 + lane;
@@ -389,6 +390,7 @@ __device__ __forceinline__ void topk_groups_row(const float* __restrict__ logits
         const float c = cand_of(xs[u]);
         const bool in = vs[u] < V && c >= R;
         const unsigned long long mask = __ballot(in);
+        if (mask == 0) continue;
         if (in) {
           const int at = nc + __popcll(mask & ((1ull << lane) - 1ull));
           if (at < CMAX) { cs_w[at] = c; ci_w[at] = vs[u]; }
@@ -546,15 +548,14 @@ __device__ __forceinline__ void next_input_rows(const NextInput& nx, const int* 
 // group width, the group's rows start at beam slot goff of the sentence's k_all).  Lane c < k*k owns
 // survivor (beam c / k of the group, slot c % k).
 // ALONE: the wavefront is the whole workgroup (its barriers are the workgroup's); otherwise other wavefronts of the
-// workgroup have finished their part and this one orders its own LDS and memory traffic.
+// workgroup have finished their part, and LDS and memory serve this one's accesses in the order it makes them.
 template <bool ALONE>
 __device__ __forceinline__ void rerank_sync() {
   if constexpr (ALONE) {
     __syncthreads();
   } else {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   }
 }
 
@@ -563,16 +564,34 @@ __device__ __forceinline__ void rerank_sync() {
 // arrive leaves the count in active[t], advances the position counter -- every unit read it at its start, and the only
 // other readers are kernels launched later -- and tells the host (report, pinned memory: step number and count in one
 // word; nothing else is read on the strength of it).
-__device__ __forceinline__ void end_of_step(int32_t* active, int t, int32_t* step_state, int next_pos, int unfinished, int units,
-                                            unsigned long long* report, int fixed_count = -1) {
-  const int old = atomicAdd(&step_state[1], 1 + (unfinished << 16));
-  if ((old & 0xFFFF) != units - 1) return;
-  const int n = fixed_count >= 0 ? fixed_count : (old >> 16) + unfinished;
+// In two halves: what is issued in between hides the atomic's way to memory and back.
+__device__ __forceinline__ int step_arrive(int32_t* step_state, int unfinished) { return atomicAdd(&step_state[1], 1 + (unfinished << 16)); }
+__device__ __forceinline__ void step_finish(int before, int32_t* active, int t, int32_t* step_state, int next_pos, int unfinished,
+                                            int units, unsigned long long* report, int fixed_count = -1) {
+  if ((before & 0xFFFF) != units - 1) return;
+  const int n = fixed_count >= 0 ? fixed_count : (before >> 16) + unfinished;
   step_state[1] = 0;
   active[t] = n;
   step_state[0] = next_pos;
   if (report)
     __hip_atomic_store(report, ((unsigned long long)(t + 1) << 32) | (unsigned)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// Rank of candidate `lane` (score s) among a unit's n candidates in LDS: higher score first, lower index first among equal
+// scores -- the rows' lists are sorted and stand one behind the other, so that is the lower (beam, token).  Empty slots
+// (token -1) do not count.  Every lane reads every candidate: broadcasts, four at a time.
+template <int n>
+__device__ __forceinline__ int candidate_rank(const float* cand_s, const int* cand_i, float s, int lane) {
+  int rank = 0;
+#pragma unroll
+  for (int c = 0; c < n; c += 4) {
+    const floatx4 s4 = *reinterpret_cast<const floatx4*>(cand_s + c);
+    const int4 t4 = *reinterpret_cast<const int4*>(cand_i + c);
+    const int t[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      rank += c + e < n && t[e] >= 0 && (s4[e] > s || (s4[e] == s && c + e < lane)) ? 1 : 0;
+  }
+  return rank;
 }
 
 // What the re-rank stage reads besides the candidates, requested together (one trip to memory instead of one per
@@ -635,15 +654,12 @@ __device__ __forceinline__ void rerank_sentence(const float* cand_score_b, const
   int tok = cand_idx_b[cl];
   int p = lane;
   if (lane >= kk) { s = -INFINITY; plain = -INFINITY; tok = -1; }
-  long flat = -1;
-  if (tok >= 0) flat = (long)(gr.goff + j) * V + tok;
-  // rank among the k*k candidates: lane c's pair is read straight from its registers
+  const int flat = tok >= 0 ? (gr.goff + j) * V + tok : -1;   // at most 8 x 65536
   int rank = 0;
   for (int c = 0; c < kk; ++c) {
     const float s2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s), c));
-    const int t2 = __builtin_amdgcn_readlane(tok, c);
-    const long f2 = t2 >= 0 ? (long)(gr.goff + c / k) * V + t2 : -1;
-    if (f2 >= 0 && (s2 > s || (s2 == s && f2 < flat))) ++rank;
+    const int f2 = __builtin_amdgcn_readlane(flat, c);
+    rank += f2 >= 0 && (s2 > s || (s2 == s && f2 < flat)) ? 1 : 0;
   }
   const bool win = flat >= 0 && rank < k;
   if (win) sh_parent[rank] = j;
@@ -699,7 +715,7 @@ __device__ __forceinline__ void rerank_sentence(const float* cand_score_b, const
     others = __any(others) ? 1 : 0;
     if (lane == 0) {
       const int go_on = sh_unfinished || others ? 1 : 0;
-      if (step_state) end_of_step(active, t, step_state, t + 1 - t_base, go_on, (int)gridDim.x, report);
+      if (step_state) step_finish(step_arrive(step_state, go_on), active, t, step_state, t + 1 - t_base, go_on, (int)gridDim.x, report);
       else if (go_on) atomicAdd(active, 1);   // the caller's counter
     }
   }
@@ -733,35 +749,92 @@ __global__ void __launch_bounds__(64) beam_refine_kernel(const float* __restrict
 }
 
 // Retrieve and re-rank in one launch (plain beam search from the logit product's group statistics): a workgroup
-// per sentence, wavefront w retrieves row w's k best into LDS, the first wavefront then re-ranks the sentence.
-template <int GPL>
-__global__ void __launch_bounds__(64 * LSQ_MAX_BEAM_) retrieve_rerank_kernel(
+// per sentence, wavefront w retrieves row w's k best into LDS; every wavefront then ranks the sentence's k*k candidates
+// (the same in all of them) and settles hypothesis w: its history, state and next decoder input.  A chain of memory trips
+// of about a microsecond each -- statistics, logits of the qualifying groups, embedding rows -- with everything else
+// requested up front.  Same bookkeeping as rerank_sentence.
+template <int GPL, int K>
+__global__ void __launch_bounds__(64 * K) retrieve_rerank_kernel(
     const float* __restrict__ logits, const float* __restrict__ stats, float* __restrict__ score, int32_t* __restrict__ tokens,
     int32_t* __restrict__ len, int32_t* __restrict__ fin, int32_t* __restrict__ parent, const int32_t* __restrict__ cap,
-    int32_t* __restrict__ active, int k, int V, int G, int T1, int32_t* __restrict__ step_state, int eos,
+    int32_t* __restrict__ active, int V, int G, int T1, int32_t* __restrict__ step_state, int eos,
     int32_t* __restrict__ anc, NextInput nx, float* __restrict__ cand_out_s, int32_t* __restrict__ cand_out_i,
     unsigned long long* report) {
   __shared__ int ql[LSQ_MAX_BEAM_][kTopkGroupsQ];
   __shared__ float cs[LSQ_MAX_BEAM_][kTopkGroupsC];
   __shared__ int ci[LSQ_MAX_BEAM_][kTopkGroupsC];
-  __shared__ float cand_s[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
-  __shared__ int cand_i[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
-  __shared__ int sh_parent[LSQ_MAX_BEAM_], sh_tok[LSQ_MAX_BEAM_];
-  __shared__ int sh_unfinished, sh_taken;
+  __shared__ __attribute__((aligned(16))) float cand_s[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
+  __shared__ __attribute__((aligned(16))) int cand_i[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
+  __shared__ int sh_tok[LSQ_MAX_BEAM_];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int b = blockIdx.x;
-  RerankState st = {};
-  if (wave == 0) st = rerank_request(tokens, len, fin, cap, anc, k, T1, 0, step_state, one_group(), b, lane);
-  topk_groups_row<GPL>(logits, stats, score, fin, b * k + wave, V, G, k, eos, cand_s + wave * k, cand_i + wave * k, lane,
+  constexpr int k = K, kk = K * K;   // known to the compiler: a wavefront on its own takes 8 cycles for every instruction
+  const int b = blockIdx.x, base = b * k, row = base + wave;
+  RerankState st = rerank_request(tokens, len, fin, cap, anc, k, T1, 0, step_state, one_group(), b, lane);
+  topk_groups_row<GPL>(logits, stats, score, fin, row, V, G, k, eos, cand_s + wave * k, cand_i + wave * k, lane,
                        ql[wave], cs[wave], ci[wave]);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the histories are here before any wavefront of the sentence overwrites them
   __syncthreads();   // blockDim.x = 64 k: every wavefront has a row
-  if (cand_out_s && (int)threadIdx.x < k * k) {   // the survivors, for whoever inspects them afterwards
-    cand_out_s[(size_t)b * k * k + threadIdx.x] = cand_s[threadIdx.x];
-    cand_out_i[(size_t)b * k * k + threadIdx.x] = cand_i[threadIdx.x];
+  if (cand_out_s && (int)threadIdx.x < kk) {   // the survivors, for whoever inspects them afterwards
+    cand_out_s[(size_t)b * kk + threadIdx.x] = cand_s[threadIdx.x];
+    cand_out_i[(size_t)b * kk + threadIdx.x] = cand_i[threadIdx.x];
   }
-  if (wave != 0) return;
-  rerank_sentence<false>(cand_s, cand_i, nullptr, score, tokens, len, fin, parent, active, k, V, T1, 0, step_state, eos,
-                         anc, one_group(), nx, b, lane, sh_parent, sh_tok, sh_unfinished, sh_taken, report, st);
+  // the embedding rows this row's candidates would need, touched so that the one that wins is near by then
+  int touched = 0;
+  if (nx.E) {
+    const unsigned row_bytes = (unsigned)nx.d * (nx.dtype == DT_F16 ? 2 : 4);
+    for (int i = lane >> 4; i < k; i += 4)
+      for (unsigned o = (lane & 15) * 128; o < row_bytes; o += 2048)
+        touched += *reinterpret_cast<const int*>(reinterpret_cast<const char*>(nx.E) + (size_t)max(cand_i[wave * k + i], 0) * row_bytes + o);
+  }
+  const int t = st.t, cl = min(lane, kk - 1), j = cl / k;
+  const float s = lane < kk ? cand_s[cl] : -INFINITY;
+  const int tok = lane < kk ? cand_i[cl] : -1;
+  const int rank = candidate_rank<kk>(cand_s, cand_i, s, lane);
+  const bool win = tok >= 0 && rank < k;
+  const int nlen = st.pfin ? st.plen : st.plen + 1;
+  const int nfin = st.pfin || tok == eos || nlen >= st.cap_b ? 1 : 0;
+  const int go_on = __any(win && !nfin) ? 1 : 0;
+  int before = 0;
+  if (wave == 0 && lane == 0) before = step_arrive(step_state, go_on);
+  const unsigned long long mine = __ballot(win && rank == wave);   // at most one lane: hypothesis w's candidate
+  const int from = mine ? __builtin_amdgcn_readlane(j, (int)__builtin_ctzll(mine)) : wave;
+  if (lane == 0) sh_tok[wave] = -1;
+  rerank_sync<false>();
+  if (win && rank == wave) {
+    sh_tok[wave] = st.pfin ? eos : tok;   // what the row feeds the decoder next (a finished row: anything valid)
+    if (!st.pfin) tokens[(size_t)row * T1 + nlen] = tok;
+    len[row] = nlen;
+    fin[row] = nfin;
+    score[row] = s;
+    parent[row] = j;
+  }
+  // token history, positions 0..t, and the table that says which slab holds position p of it (cache refreshing without
+  // moving the cache; position t + 1 is written by the row itself)
+  for (int p = lane, p0 = 0; p0 <= t && p0 < T1; p0 += 64, p += 64) {
+    if (p0 > 0) {   // a history longer than 64 positions: one more trip per 64
+      rerank_history(st, tokens, anc, base, k, T1, p);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    }
+    int val = 0, vala = 0;
+#pragma unroll
+    for (int i = 0; i < LSQ_MAX_BEAM_; ++i)
+      if (i == from) { val = st.h[i]; vala = st.ha[i]; }
+    if (from != wave && p <= t && p < T1) {
+      tokens[(size_t)row * T1 + p] = val;
+      if (anc) anc[(size_t)row * T1 + p] = vala;
+    }
+  }
+  if (anc && lane == 0 && t + 1 < T1) anc[(size_t)row * T1 + t + 1] = wave;
+  rerank_sync<false>();
+  // The next step's decoder input of this row (one launch less per step).  A row that no candidate won
+  // (fewer live candidates than beams) embeds nothing: it is dead and stays so.
+  if (nx.E && t + 1 < T1 - 1) {
+    if (nx.dtype == DT_F16) next_input_rows<half_t>(nx, &sh_tok[wave], row, 1, t + 1, lane);
+    else next_input_rows<float>(nx, &sh_tok[wave], row, 1, t + 1, lane);
+  }
+  asm volatile("" ::"v"(touched));
+  if (wave == 0 && lane == 0) step_finish(before, active, t, step_state, t + 1, go_on, (int)gridDim.x, report);
 }
 
 // Diverse beam search from the group statistics, all groups of a sentence in one launch: every row's k_all best tokens
@@ -842,12 +915,17 @@ hipError_t launch_retrieve_rerank(const float* logits, const float* stats, float
   if (!topk_groups_supported(V, k, 0) || !stats || !step_state) return hipErrorInvalidValue;
   const int G = (V + 31) / 32;
   dim3 g(batch), b(64 * k);
-#define LSQ_RR(GPL_)                                                                                                     \
-  retrieve_rerank_kernel<GPL_><<<g, b, 0, s>>>(logits, stats, score, tokens, len, fin, parent, cap, active, k, V, G, T + 1, \
-                                               step_state, eos, anc, nx, cand_score, cand_idx, report)
-  if (G <= 64 * 4) LSQ_RR(4);
-  else if (G <= 64 * 16) LSQ_RR(16);
-  else LSQ_RR(32);
+#define LSQ_RR(GPL_, K_)                                                                                                       \
+  retrieve_rerank_kernel<GPL_, K_><<<g, b, 0, s>>>(logits, stats, score, tokens, len, fin, parent, cap, active, V, G, T + 1, \
+                                                   step_state, eos, anc, nx, cand_score, cand_idx, report)
+#define LSQ_RK(K_)                          \
+  case K_:                                  \
+    if (G <= 64 * 4) LSQ_RR(4, K_);         \
+    else if (G <= 64 * 16) LSQ_RR(16, K_);  \
+    else LSQ_RR(32, K_);                    \
+    break
+  switch (k) { LSQ_RK(1); LSQ_RK(2); LSQ_RK(3); LSQ_RK(4); LSQ_RK(5); LSQ_RK(6); LSQ_RK(7); LSQ_RK(8); }
+#undef LSQ_RK
 #undef LSQ_RR
   return hipGetLastError();
 }
@@ -1121,7 +1199,8 @@ __global__ void __launch_bounds__(64) sample_kernel(const float* __restrict__ ca
     unfinished = sample_row(cand_logit + (size_t)r * k, cand_idx + (size_t)r * k, r, tokens, len, logp, k, topp, T1, seed_lo,
                             seed_hi, pos, t, fin, cap, order, eos, tok);
   const int alive = __popcll(__ballot(unfinished));
-  if (threadIdx.x == 0) end_of_step(active, t, step_state, pos + 1, alive, (int)gridDim.x, report, fin ? -1 : t + 1 < n_new ? rows : 0);
+  if (threadIdx.x == 0)
+    step_finish(step_arrive(step_state, alive), active, t, step_state, pos + 1, alive, (int)gridDim.x, report, fin ? -1 : t + 1 < n_new ? rows : 0);
 }
 
 // Retrieve (the k largest logits from the logit product's group statistics) and draw in one launch: a wavefront
@@ -1154,9 +1233,7 @@ __global__ void __launch_bounds__(256) retrieve_sample_kernel(const float* __res
   if (!done) {
     topk_groups_row<GPL>(logits, stats, nullptr, nullptr, r, V, G, k, eos, cand_s[wave], cand_i[wave], lane, ql[wave], cs[wave],
                          ci[wave], 1);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    rerank_sync<false>();
   }
   if (!done && cand_out_s && lane < k) {   // the candidates, for whoever inspects them afterwards
     cand_out_s[(size_t)r * k + lane] = cand_s[wave][lane];
@@ -1168,15 +1245,14 @@ __global__ void __launch_bounds__(256) retrieve_sample_kernel(const float* __res
     unfinished = sample_row_wave(cand_s[wave], cand_i[wave], r, lane, tokens, len, logp, k, topp, T1, seed_lo, seed_hi, pos, t, fin,
                                  eos, st, tok);
   // one count per row: the last row advances the position
-  if (lane == 0) end_of_step(active, t, step_state, pos + 1, unfinished ? 1 : 0, rows, report, fin ? -1 : t + 1 < n_new ? rows : 0);
-  if (lane == 0) next_tok[wave] = tok;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  int before = 0;
+  if (lane == 0) { before = step_arrive(step_state, unfinished ? 1 : 0); next_tok[wave] = tok; }
+  rerank_sync<false>();
   if (nx.E && pos + 1 < T1 - 1) {
     if (nx.dtype == DT_F16) next_input_rows<half_t>(nx, &next_tok[wave], r, 1, pos + 1, lane);
     else next_input_rows<float>(nx, &next_tok[wave], r, 1, pos + 1, lane);
   }
+  if (lane == 0) step_finish(before, active, t, step_state, pos + 1, unfinished ? 1 : 0, rows, report, fin ? -1 : t + 1 < n_new ? rows : 0);
 }
 
 hipError_t launch_sample(const float* cand_logit, const int32_t* cand_idx, int32_t* tokens, int32_t* len,
