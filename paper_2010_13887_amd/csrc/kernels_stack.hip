@@ -19,6 +19,8 @@
 //
 // All workgroups must be resident at once: the launcher checks the occupancy, and every wait is bounded (kSpinLimit
 // polls, then the error flag is set, nothing is waited for any more and the launch runs to its end).
+#include <unordered_map>
+
 #include "lsq_internal.h"
 
 namespace lsq {
@@ -104,7 +106,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   __shared__ __attribute__((aligned(16))) float part2[kWaves][kRows][16];
   __shared__ float att_o[kWaves][64], att_m[kWaves], att_l[kWaves];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.groups, bid = blockIdx.x;
   const int grp = (bid >> 3) % G, j = (bid >> 3) / G * 8 + (bid & 7);
   const int r0 = grp * a.rows_per_group, rows = min(a.rows_per_group, a.M - r0);
@@ -119,9 +122,9 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   auto at = [&](int l, int region) { return (grp * row_bytes + (l * Rg::size + region) * D) * rp; };
 
   // ---- matrix fragments: lane (n = lane & 15, kc = lane >> 4) of a 32-wide k-step holds W[col + n][32 s + 8 kc ..]
-  const int fm = lane & 7, kc = lane >> 4;
+  int fm = lane & 7, kc = lane >> 4;
   auto frag_lane = [&](int nt) { return (unsigned)(kc >> 1) * 1024 + ((lane & (nt - 1)) + 32 * (kc & 1)) * 16; };
-  const unsigned lane16 = frag_lane(16), lane_nt = frag_lane(NT), lane_qt = frag_lane(QT);
+  unsigned lane16 = frag_lane(16), lane_nt = frag_lane(NT), lane_qt = frag_lane(QT);
   auto frag_col = [&](const half_t* Wp, int K, int col) {   // its first k-step, in bytes
     return reinterpret_cast<const char*>(Wp) + (size_t)(col >> 5) * (K / 16) * 1024 + (col & 31) * 16;
   };
@@ -247,11 +250,13 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   };
 
   // ---- attention of one (row, head) pair per team of NSH wavefronts; a lane group of 8 holds a key's 64 values
-  const int team = wave / NSH, ash = wave % NSH, gk = lane >> 3, c8 = (lane & 7) * 8;
+  const int team = wave / NSH, ash = wave % NSH;
+  int gk = lane >> 3, c8 = (lane & 7) * 8;
   const int pair = j + W * team, am = min(pair / H, rows - 1), ah = pair % H;
   const bool attends = pair < rows * H;
   const int arow = r0 + am, sent = arow / a.beam;
-  const int jfirst = ash + gk * NSH, jstep = 8 * NSH;
+  const int jstep = 8 * NSH;
+  int jfirst = ash + gk * NSH;
   int slot0[U];
   const bool table = !PRE && a.anc != nullptr;
   const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
@@ -408,6 +413,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   // ======== the layers.  Every matrix slice is requested at least one exchange before it is multiplied.
   load_units(wq, layer_w(a.Wqkv, 0), 3 * (D / 16));
   for (int l = 0; l < a.layers; ++l) {
+    // What is derived from a thread's place is derived anew in every layer instead of waiting in registers: without it d = 1024
+    // spills (32 rows 204 -> 174 us a step's layers); d = 512 gains 2 %, d = 768 would lose 2 %.
+    if constexpr (DK != 3) {
+      asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(lane16), "+v"(lane_nt), "+v"(lane_qt));
+      asm volatile("" : "+v"(gk), "+v"(c8), "+v"(jfirst));
+    }
     half_t* Kc = reinterpret_cast<half_t*>(a.cache + (size_t)(2 * l) * a.cache_stride);
     half_t* Vc = reinterpret_cast<half_t*>(a.cache + (size_t)(2 * l + 1) * a.cache_stride);
     // A. the layer's input rows; q, k, v
@@ -526,6 +537,516 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same for more rows: a group takes up to 16 MB rows through all layers with W = d / 16 workgroups.
+//
+// What every workgroup has to read decides here, not the number of exchanges, so the work is cut differently:
+//   * workgroup r of a group owns row r: it alone adds up the partial sums of the sublayers' projections, keeps the
+//     residual row and publishes the normalised one (float16) -- one exchange more, but the 16 KB of partial sums of a row
+//     are read once and not by everybody;
+//   * products with d columns are split 4-fold over k (64 columns and a quarter of k per workgroup): each reads a quarter
+//     of the input rows and leaves a float slab; the query product's slabs are added by the attention that needs them;
+//   * input rows are staged in LDS by all threads.
+// Exchange regions exist for two layers; a workgroup that publishes into layer l's resets what it wrote for layer l - 1
+// at the same place (consumed by then: it could not have got here otherwise) and has waited for the acknowledgement
+// before its next publication but one, on which everybody's way to layer l + 1 depends.  A launch starts with the slot
+// after the one the last launch ended with, and cleans that one first.
+template <bool PRE> struct RowsRegion {   // bytes per row / d
+  static constexpr int xi = 0, qkv = 2, ctx = 8, os = 10, x1 = 26, ff = 28, fs = 36;
+  static constexpr int qs = PRE ? 0 : 52, ctx2 = PRE ? 0 : 68, cs = PRE ? 0 : 70, x2 = PRE ? 0 : 86, size = PRE ? 52 : 88;
+};
+
+template <int DK, int MB, bool PRE>
+__global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const StackArgs a) {
+  constexpr int D = 256 * DK, H = D / 64, W = D / 16, R = 16 * MB, CG = D / 64;
+  constexpr int TEAMS = R / 4, NSH = kWaves / TEAMS;
+  constexpr int U = 4;                              // keys of a lane group in flight
+  constexpr int KS = 2 * DK;                        // k-steps of a quarter of k
+  constexpr int CHX = MB * DK;                      // 16-byte pieces per thread of R rows of d halves
+  constexpr int CHQ = (MB * DK + 3) / 4;            // ... of a quarter of them
+  using Rg = RowsRegion<PRE>;
+  typedef half_t half2_t __attribute__((ext_vector_type(2)));
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+  __shared__ __attribute__((aligned(16))) half_t st[R][D + 8];             // staged input rows
+  __shared__ __attribute__((aligned(16))) float part[kWaves][4][R][16];
+  __shared__ __attribute__((aligned(16))) half_t xrow[D];                  // the residual of the row this workgroup owns
+  __shared__ float stat[DK][2];
+  __shared__ float att_o[kWaves][64], att_m[kWaves], att_l[kWaves];
+
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = a.groups, bid = blockIdx.x;
+  const int grp = (bid >> 3) % G, j = (bid >> 3) / G * 8 + (bid & 7);
+  const int cg = j >> 2, ks = j & 3;
+  const int rp = a.rows_per_group, r0 = grp * rp, rows = min(rp, a.M - r0);
+  const int start = a.state[0], dirty = a.state[1], pos = *a.tpos;
+  const bool owner = j < rows;
+
+  Exchange ex;
+  ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange, (short)0, (int)(2 * a.set_bytes), 0x00027000);
+  ex.error = a.error;
+  ex.dead = false;
+  const int group_bytes = Rg::size * D * rp;
+  auto at = [&](int l, int region) { return ((start + l) & 1) * (int)a.set_bytes + grp * group_bytes + region * D * rp; };
+  const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
+  auto other = [&](int l) { return ((start + l) & 1) ? -(int)a.set_bytes : (int)a.set_bytes; };   // from layer l's slot to the other
+  auto put4 = [&](int l, int base, int lo, float v0, float v1, float v2, float v3) {
+    const u32x4 w = {publish_word(__builtin_bit_cast(unsigned, v0)), publish_word(__builtin_bit_cast(unsigned, v1)),
+                     publish_word(__builtin_bit_cast(unsigned, v2)), publish_word(__builtin_bit_cast(unsigned, v3))};
+    __builtin_amdgcn_raw_buffer_store_b128(w, ex.rsrc, lo, base, kAgent);
+    __builtin_amdgcn_raw_buffer_store_b128(s4, ex.rsrc, lo, base + other(l), kAgent);
+  };
+  auto put4h = [&](int l, int base, int lo, half_t h0, half_t h1, half_t h2, half_t h3) {
+    const u32x2 w = {publish_word(__builtin_bit_cast(unsigned, half2_t{h0, h1})), publish_word(__builtin_bit_cast(unsigned, half2_t{h2, h3}))};
+    __builtin_amdgcn_raw_buffer_store_b64(w, ex.rsrc, lo, base, kAgent);
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{kSentinel, kSentinel}, ex.rsrc, lo, base + other(l), kAgent);
+  };
+
+  {   // the slot the last launch ended with: this group's part (needed from layer 1 on), and what no group of this launch has
+    char* old = a.exchange + ((start + 1) & 1) * a.set_bytes;
+    const int mine_end = min(dirty, (grp + 1) * group_bytes);
+    for (int o = grp * group_bytes + (j * kThreads + tid) * 16; o < mine_end; o += W * kThreads * 16)
+      __builtin_amdgcn_raw_buffer_store_b128(s4, ex.rsrc, o, (int)(old - a.exchange), kAgent);
+    for (int o = G * group_bytes + (bid * kThreads + tid) * 16; o < dirty; o += (int)gridDim.x * kThreads * 16)
+      __builtin_amdgcn_raw_buffer_store_b128(s4, ex.rsrc, o, (int)(old - a.exchange), kAgent);
+  }
+
+  // ---- matrix fragments (see decoder_stack_kernel)
+  int fm = lane & 15, kc = lane >> 4;
+  unsigned lane16 = (unsigned)(kc >> 1) * 1024 + (fm + 32 * (kc & 1)) * 16;
+  auto frag = [&](const half_t* Wp, int K, int col, int kstep) {
+    return reinterpret_cast<const char*>(Wp) + (size_t)(col >> 5) * (K / 16) * 1024 + (col & 31) * 16 + (size_t)kstep * 2048;
+  };
+  half8_t wq[3][DK], wo[KS], w1[4][DK], w2[4][DK];
+  auto load_units = [&](auto& w, const half_t* Wp) {   // units j + W i of 16 columns, this wavefront's eighth of k
+    constexpr int N = sizeof(w) / sizeof(w[0]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const char* p = frag(Wp, D, (j + W * i) * 16, wave * DK);
+#pragma unroll
+      for (int s = 0; s < DK; ++s) w[i][s] = *reinterpret_cast<const half8_t*>(p + s * 2048 + lane16);
+    }
+  };
+  auto load_quarter = [&](auto& w, const half_t* Wp) {   // 16 columns (wave & 3) of this workgroup's 64, its quarter of k
+    constexpr int N = sizeof(w) / sizeof(w[0]);
+    const char* p = frag(Wp, D, cg * 64 + (wave & 3) * 16, ks * KS);
+#pragma unroll
+    for (int s = 0; s < N; ++s) w[s] = *reinterpret_cast<const half8_t*>(p + s * 2048 + lane16);
+  };
+  auto load_ffn2 = [&](auto& w, const half_t* Wp) {   // this workgroup's 64 columns, this wavefront's eighth of its quarter of 4d
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const char* p = frag(Wp, 4 * D, cg * 64 + i * 16, ks * (D / 32) + wave * DK);
+#pragma unroll
+      for (int s = 0; s < DK; ++s) w[i][s] = *reinterpret_cast<const half8_t*>(p + s * 2048 + lane16);
+    }
+  };
+  auto pin = [] { asm volatile("" ::: "memory"); };
+
+  auto layer_w = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(p) + (size_t)l * a.packed_stride); };
+  auto layer_p = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(p) + (size_t)l * a.plain_stride); };
+  auto half4_at = [](const half_t* b, unsigned col) { return *reinterpret_cast<const half4_t*>(reinterpret_cast<const char*>(b) + col * 2u); };
+
+  // ---- the owner's part: residual row + partial sums of a projection -> normalised row.  Thread t has columns 4t .. 4t+3.
+  unsigned oc = min(tid * 4, D - 4);
+  const bool oact = tid * 4 < D;
+  auto own_publish = [&](float (&v)[4], half4_t g4, half4_t b4, int l, int region_out, half_t* out_y) {
+    // mean and centred sum of squares of each wavefront's 256 values, then of the row
+    float sm = (v[0] + v[1]) + (v[2] + v[3]);
+    sm = wave_sum(sm) * (1.0f / 256);
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q += (v[i] - sm) * (v[i] - sm);
+    q = wave_sum(q);
+    if (lane == 0 && wave < DK) { stat[wave][0] = sm; stat[wave][1] = q; }
+    __syncthreads();
+    float mean = 0.f, m2 = 0.f;
+#pragma unroll
+    for (int w = 0; w < DK; ++w) mean += stat[w][0];
+    mean *= 1.0f / DK;
+#pragma unroll
+    for (int w = 0; w < DK; ++w) m2 += stat[w][1] + 256.0f * (stat[w][0] - mean) * (stat[w][0] - mean);
+    const float var = m2 * (1.0f / D) + a.eps, rs = __builtin_amdgcn_rsqf(var), rstd = rs * (1.5f - 0.5f * var * rs * rs);
+    if (oact) {
+      half_t h[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) h[i] = (half_t)((float)g4[i] * ((v[i] - mean) * rstd) + (float)b4[i]);
+      if (region_out >= 0) put4h(l, at(l, region_out) + j * (D * 2), oc * 2, h[0], h[1], h[2], h[3]);
+      if (!PRE) *reinterpret_cast<half4_t*>(&xrow[oc]) = half4_t{h[0], h[1], h[2], h[3]};
+      if (out_y) *reinterpret_cast<half4_t*>(out_y + (size_t)(r0 + j) * D + oc) = half4_t{h[0], h[1], h[2], h[3]};
+    }
+    __syncthreads();
+  };
+  auto own_norm = [&](int lin, int region_in, const half_t* bias, const half_t* g, const half_t* b, int l, int region_out,
+                      half_t* out_x, half_t* out_y) {
+    if (!owner) return;
+    const half4_t bi = half4_at(bias, oc), g4 = half4_at(g, oc), b4 = half4_at(b, oc);
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (wave < DK) {
+      u32x4 raw[4];
+      const int base = at(lin, region_in) + j * 256;
+      const int lo = (int)(oc >> 6) * (rp * 256) + (int)(oc & 63) * 4;
+      ex.wait([&](int i) { return base + i * (CG * 256) * rp; }, [&](int) { return lo; }, raw);
+      const half4_t x4 = *reinterpret_cast<const half4_t*>(&xrow[oc]);
+      const floatx4 f0 = __builtin_bit_cast(floatx4, raw[0]), f1 = __builtin_bit_cast(floatx4, raw[1]),
+                    f2 = __builtin_bit_cast(floatx4, raw[2]), f3 = __builtin_bit_cast(floatx4, raw[3]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[i] = (float)x4[i] + ((((f0[i] + f1[i]) + f2[i]) + f3[i]) + (float)bi[i]);
+        if (PRE) v[i] = (float)(half_t)v[i];
+      }
+      if constexpr (PRE) {
+        const half4_t h = {(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
+        *reinterpret_cast<half4_t*>(&xrow[oc]) = h;
+        if (out_x) *reinterpret_cast<half4_t*>(out_x + (size_t)(r0 + j) * D + oc) = h;
+      }
+    }
+    own_publish(v, g4, b4, l, region_out, out_y);
+  };
+
+  // ---- staging: `pieces` of 16 bytes per thread; all of a workgroup's accesses so far are acknowledged on the way
+  auto stage_rows = [&](auto& raw, int base, int cols, int col0) {   // rows of d halves, `cols` columns from col0
+    constexpr int N = sizeof(raw) / sizeof(raw[0]);
+    const int t = tid;
+    const int per_row = cols / 8;   // rows the group does not have: its last one again
+    auto row_of = [&](int p) { return min(p / per_row, rows - 1); };
+    ex.wait([&](int) { return base + col0 * 2; },
+            [&](int i) { const int p = i * kThreads + t; return row_of(p) * (D * 2) + p % per_row * 16; }, raw);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int p = i * kThreads + t;
+      if (p < R * per_row) *reinterpret_cast<u32x4*>(&st[p / per_row][p % per_row * 8]) = raw[i];
+    }
+    __syncthreads();
+  };
+  auto stage_units = [&](int base) {   // a quarter of the FFN activations: d columns in units of 16
+    u32x4 raw[CHX];
+    const int t = tid;
+    constexpr int per_unit = R * 2;
+    ex.wait([&](int) { return base; },
+            [&](int i) { const int p = i * kThreads + t; return p / per_unit * (rp * 32) + min(p % per_unit >> 1, rows - 1) * 32 + (p & 1) * 16; }, raw);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < CHX; ++i) {
+      const int p = i * kThreads + t;
+      *reinterpret_cast<u32x4*>(&st[p % per_unit >> 1][p / per_unit * 16 + (p & 1) * 8]) = raw[i];
+    }
+    __syncthreads();
+  };
+
+  // ---- products
+  const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  auto multiply_units = [&](const auto& w) {   // an eighth of the staged columns per wavefront
+    constexpr int N = sizeof(w) / sizeof(w[0]);
+    floatx4 acc[N][MB];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int b = 0; b < MB; ++b) acc[i][b] = zero4;
+#pragma unroll
+    for (int s = 0; s < DK; ++s)
+#pragma unroll
+      for (int b = 0; b < MB; ++b) {
+        const half8_t x8 = *reinterpret_cast<const half8_t*>(&st[b * 16 + fm][(wave * DK + s) * 32 + kc * 8]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i][s], x8, acc[i][b], 0, 0, 0);
+      }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int b = 0; b < MB; ++b) *reinterpret_cast<floatx4*>(&part[wave][i][b * 16 + fm][kc * 4]) = acc[i][b];
+  };
+  // four columns of a unit and row per thread: unit tid / (4 R), row, columns
+  int ui = tid / (4 * R), um = tid % (4 * R) / 4, un = tid % 4 * 4;
+  auto total4 = [&](int i) {
+    floatx4 v = *reinterpret_cast<const floatx4*>(&part[0][i][um][un]);
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) v += *reinterpret_cast<const floatx4*>(&part[w][i][um][un]);
+    return v;
+  };
+  auto project_quarter = [&](const auto& w, int l, int region_in, int region_out, auto request) {   // ks-th quarter of k, 64 columns
+    u32x4 raw[CHQ];
+    stage_rows(raw, at(l, region_in), D / 4, ks * (D / 4));
+    if (wave < 4 * MB) {
+      floatx4 acc[2] = {zero4, zero4};
+      const int b = wave >> 2;
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[s], *reinterpret_cast<const half8_t*>(&st[b * 16 + fm][s * 32 + kc * 8]), acc[s & 1], 0, 0, 0);
+      acc[0] += acc[1];
+      const int m = b * 16 + fm;
+      if (m < rows)
+        put4(l, at(l, region_out) + (ks * CG + cg) * rp * 256, m * 256 + (wave & 3) * 64 + kc * 16, acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
+    }
+    request();
+    pin();
+  };
+
+  // ---- attention (see decoder_stack_kernel)
+  const int team = wave / NSH, ash = wave % NSH;
+  int gk = lane >> 3, c8 = (lane & 7) * 8;
+  const int pair = j + W * team, am = min(pair / H, rows - 1), ah = pair % H;
+  const bool attends = pair < rows * H;
+  const int arow = r0 + am, sent = arow / a.beam;
+  const int jstep = 8 * NSH;
+  int jfirst = ash + gk * NSH;
+  int slot0[U];
+  const bool table = !PRE && a.anc != nullptr;
+  const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
+  auto slot_of = [&](int p) { return table ? min(max(slots[p], 0), a.beam - 1) : 0; };
+#pragma unroll
+  for (int u = 0; u < U; ++u) slot0[u] = slot_of(max(min(jfirst + u * jstep, pos - 1), 0));
+  int src_off = 0, src_len = 0;
+  if constexpr (!PRE) { src_off = a.src_off[sent]; src_len = a.src_len[sent]; }
+  auto dot8 = [](const half8_t& x, const half8_t& y) {
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_fdot2(half2_t{x[2 * i], x[2 * i + 1]}, half2_t{y[2 * i], y[2 * i + 1]}, s, false);
+    return s;
+  };
+  half8_t kn[U], vn[U];
+  auto request_keys = [&](bool self, const half_t* Kb, const half_t* Vb, int nkeys, int jb) {
+    const size_t own = self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0;
+    const char* Kh = reinterpret_cast<const char*>(Kb + own + ah * 64);
+    const char* Vh = reinterpret_cast<const char*>(Vb + own + ah * 64);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u > 0 && jb - gk * NSH + u * jstep >= nkeys) continue;
+      const int p = max(min(jb + u * jstep, nkeys - 1), 0);
+      const unsigned o = ((self ? ((jb == jfirst ? slot0[u] : slot_of(p)) * a.T + p) * D : p * (2 * D)) + c8) * 2u;
+      kn[u] = *reinterpret_cast<const half8_t*>(Kh + o);
+      vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
+    }
+  };
+  // the first keys and values have been requested (request_keys from jfirst on) an exchange earlier
+  auto attend = [&](int l, bool self, const half_t* Kb, const half_t* Vb, int nkeys, const half_t* bias_q) {
+    if (attends) {
+      half8_t bq8 = {};
+      if (!self) bq8 = *reinterpret_cast<const half8_t*>(reinterpret_cast<const char*>(bias_q) + (unsigned)(ah * 64 + c8) * 2u);
+      pin();
+      constexpr float qscale = 0.125f * 1.44269504088896340736f;
+      half8_t q, knew, vnew;
+      if (self) {
+        u32x4 raw[3];
+        const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 32;
+        ex.wait([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
+        q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
+      } else {
+        u32x4 raw[8];   // four slabs of the head's 64 columns
+        const int base = at(l, Rg::qs) + (ah * rp + am) * 256;
+        ex.wait([&](int i) { return base + (i >> 1) * (CG * 256) * rp; }, [&](int i) { return c8 * 4 + (i & 1) * 16; }, raw);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          float v = __builtin_bit_cast(floatx4, raw[i >> 2])[i & 3];
+#pragma unroll
+          for (int sl = 1; sl < 4; ++sl) v += __builtin_bit_cast(floatx4, raw[sl * 2 + (i >> 2)])[i & 3];
+          q[i] = (half_t)(v + (float)bq8[i]);
+        }
+      }
+      float m = -INFINITY, z = 0.f, acc[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+      for (int jb = jfirst; jb - gk * NSH < nkeys; jb += U * jstep) {
+        float sc[U], mx = m;
+        half8_t vv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          sc[u] = -INFINITY;
+          if (jb - gk * NSH + u * jstep >= nkeys) continue;
+          const float s = group_sum<8>(dot8(q, kn[u])) * qscale;
+          if (jb + u * jstep < nkeys) sc[u] = s;
+          vv[u] = vn[u];
+          mx = fmaxf(mx, sc[u]);
+        }
+        const int jn = jb + U * jstep;
+        if (jn - gk * NSH < nkeys) request_keys(self, Kb, Vb, nkeys, jn);
+        for_lane_bits<8>([&](auto bit) { mx = max_lane_xor<decltype(bit)::value>(mx); });
+        const float corr = __builtin_amdgcn_exp2f(m - mx);
+        m = mx;
+        z *= corr;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] *= corr;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (jb - gk * NSH + u * jstep >= nkeys) continue;
+          const bool live = jb + u * jstep < nkeys;
+          const float p = live ? __builtin_amdgcn_exp2f(sc[u] - mx) : 0.f;
+          z += p;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc[i] += p * (live ? (float)vv[u][i] : 0.f);
+        }
+      }
+      if (self && ash == NSH - 1) {
+        const float s = group_sum<8>(dot8(q, knew)) * qscale, mx = fmaxf(m, s);
+        const float corr = __builtin_amdgcn_exp2f(m - mx), p = gk == 0 ? __builtin_amdgcn_exp2f(s - mx) : 0.f;
+        m = mx;
+        z = z * corr + p;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = acc[i] * corr + p * (float)vnew[i];
+      }
+      for_lane_bits<8>([&](auto bit) {
+        constexpr int O = decltype(bit)::value;
+        z = add_lane_xor<O>(z);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = add_lane_xor<O>(acc[i]);
+      });
+      if (gk == 0) {
+        *reinterpret_cast<floatx4*>(&att_o[wave][c8]) = floatx4{acc[0], acc[1], acc[2], acc[3]};
+        *reinterpret_cast<floatx4*>(&att_o[wave][c8 + 4]) = floatx4{acc[4], acc[5], acc[6], acc[7]};
+        if (lane == 0) { att_m[wave] = m; att_l[wave] = z; }
+      }
+    }
+    __syncthreads();
+    const int tm = tid >> 4, c = (tid & 15) * 4, pr = j + W * tm;   // four values of a pair's context each
+    if (tm < TEAMS && pr < rows * H) {
+      float mx = -INFINITY, z = 0.f;
+      floatx4 o = zero4;
+#pragma unroll
+      for (int w = 0; w < NSH; ++w) mx = fmaxf(mx, att_m[tm * NSH + w]);
+#pragma unroll
+      for (int w = 0; w < NSH; ++w) {
+        const float cw = __builtin_amdgcn_exp2f(att_m[tm * NSH + w] - mx);
+        z += att_l[tm * NSH + w] * cw;
+        o += *reinterpret_cast<const floatx4*>(&att_o[tm * NSH + w][c]) * cw;
+      }
+      const float inv = 1.0f / z;
+      put4h(l, at(l, self ? Rg::ctx : Rg::ctx2), pr / H * (D * 2) + (pr % H * 64 + c) * 2, (half_t)(o[0] * inv), (half_t)(o[1] * inv),
+            (half_t)(o[2] * inv), (half_t)(o[3] * inv));
+    }
+  };
+
+  // ======== the layers
+  load_units(wq, layer_w(a.Wqkv, 0));
+  for (int l = 0; l < a.layers; ++l) {
+    // What is derived from a thread's place is derived anew in every layer instead of waiting in registers: without it d = 1024
+    // spills (128 rows 275 -> 266 us a step's layers); narrower models would lose 2 to 4 %.
+    if constexpr (DK == 4) {
+      asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(lane16), "+v"(oc), "+v"(ui), "+v"(um), "+v"(un));
+      asm volatile("" : "+v"(gk), "+v"(c8), "+v"(jfirst));
+    }
+    half_t* Kc = reinterpret_cast<half_t*>(a.cache + (size_t)(2 * l) * a.cache_stride);
+    half_t* Vc = reinterpret_cast<half_t*>(a.cache + (size_t)(2 * l + 1) * a.cache_stride);
+    // the layer's input rows
+    if (l == 0) {
+      if (owner) {
+        const int r = r0 + j;
+        half4_t h = {};
+        if constexpr (PRE) {
+          const half4_t g4 = half4_at(a.ln1g, oc), b4 = half4_at(a.ln1b, oc);
+          const half4_t e4 = half4_at(a.E + (size_t)a.tokens[(size_t)r * (a.T + 1) + a.len[r]] * D, oc);
+          const floatx4 p4 = *reinterpret_cast<const floatx4*>(a.pe + (size_t)pos * D + oc);
+          float v[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) { h[i] = (half_t)__fadd_rn((float)e4[i], p4[i]); v[i] = (float)h[i]; }
+          if (oact) *reinterpret_cast<half4_t*>(&xrow[oc]) = h;
+          own_publish(v, g4, b4, l, Rg::xi, nullptr);
+        } else {
+          h = half4_at(a.x0 + (size_t)r * D, oc);
+          if (oact) {
+            *reinterpret_cast<half4_t*>(&xrow[oc]) = h;
+            put4h(l, at(l, Rg::xi) + j * (D * 2), oc * 2, h[0], h[1], h[2], h[3]);
+          }
+          __syncthreads();
+        }
+      }
+    } else {
+      if constexpr (PRE) own_norm(l - 1, Rg::fs, layer_p(a.b2, l - 1), layer_p(a.ln1g, l), layer_p(a.ln1b, l), l, Rg::xi, nullptr, nullptr);
+      else own_norm(l - 1, Rg::fs, layer_p(a.b2, l - 1), layer_p(a.ln3g, l - 1), layer_p(a.ln3b, l - 1), l, Rg::xi, nullptr, nullptr);
+    }
+    // q, k, v
+    {
+      const int qcol = (j + W * ui) * 16 + un;
+      half4_t qb = {};
+      const bool qlive = ui < 3 && um < rows;
+      if (qlive) qb = half4_at(layer_p(a.bqkv, l), qcol);
+      if (attends) request_keys(true, Kc, Vc, pos, jfirst);   // needs nothing of this step
+      pin();
+      u32x4 raw[CHX];
+      stage_rows(raw, at(l, Rg::xi), D, 0);
+      multiply_units(wq);
+      load_quarter(wo, layer_w(a.Wo, l));
+      pin();
+      __syncthreads();
+      if (qlive) {
+        const floatx4 v = total4(ui);
+        half_t h[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[i] = (half_t)(v[i] + (float)qb[i]);
+        put4h(l, at(l, Rg::qkv) + j * rp * 32, (W * ui * rp + um) * 32 + un * 2, h[0], h[1], h[2], h[3]);
+        if (qcol >= D) {
+          char* cache = reinterpret_cast<char*>((qcol < 2 * D ? Kc : Vc) + ((size_t)r0 * a.T + pos) * D);
+          *reinterpret_cast<half4_t*>(cache + (unsigned)(um * a.T * D + (qcol < 2 * D ? qcol - D : qcol - 2 * D)) * 2u) = half4_t{h[0], h[1], h[2], h[3]};
+        }
+      }
+    }
+    attend(l, true, Kc, Vc, pos, nullptr);
+    project_quarter(wo, l, Rg::ctx, Rg::os, [&] {
+      if constexpr (PRE) load_units(w1, layer_w(a.W1, l));
+      else load_quarter(wo, layer_w(a.Wq, l));
+    });
+    if constexpr (PRE) {
+      own_norm(l, Rg::os, layer_p(a.bo, l), layer_p(a.ln2g, l), layer_p(a.ln2b, l), l, Rg::x1, nullptr, nullptr);
+    } else {
+      const half_t* kvb = reinterpret_cast<const half_t*>(a.cross + (size_t)l * a.cross_stride) + (size_t)src_off * 2 * D;
+      own_norm(l, Rg::os, layer_p(a.bo, l), layer_p(a.ln1g, l), layer_p(a.ln1b, l), l, Rg::x1, nullptr, nullptr);
+      if (attends) request_keys(false, kvb, kvb + D, src_len, jfirst);
+      pin();
+      project_quarter(wo, l, Rg::x1, Rg::qs, [&] { load_quarter(wo, layer_w(a.Woc, l)); });
+      attend(l, false, kvb, kvb + D, src_len, layer_p(a.bq, l));
+      project_quarter(wo, l, Rg::ctx2, Rg::cs, [&] { load_units(w1, layer_w(a.W1, l)); });
+      own_norm(l, Rg::cs, layer_p(a.boc, l), layer_p(a.ln2g, l), layer_p(a.ln2b, l), l, Rg::x2, nullptr, nullptr);
+    }
+    // first FFN product
+    {
+      const int fcol = (j + W * ui) * 16 + un;
+      const bool flive = ui < 4 && um < rows;
+      half4_t fb = {};
+      if (flive) fb = half4_at(layer_p(a.b1, l), fcol);
+      u32x4 raw[CHX];
+      stage_rows(raw, at(l, PRE ? Rg::x1 : Rg::x2), D, 0);
+      multiply_units(w1);
+      load_ffn2(w2, layer_w(a.W2, l));
+      pin();
+      __syncthreads();
+      if (flive) {
+        const floatx4 v = total4(ui);
+        half_t h[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float t = v[i] + (float)fb[i];
+          h[i] = (half_t)(PRE ? tanh_gelu(t) : fmaxf(t, 0.f));
+        }
+        put4h(l, at(l, Rg::ff) + j * rp * 32, (W * ui * rp + um) * 32 + un * 2, h[0], h[1], h[2], h[3]);
+      }
+    }
+    // second FFN product
+    stage_units(at(l, Rg::ff) + ks * (D / 16) * rp * 32);
+    multiply_units(w2);
+    if (l + 1 < a.layers) load_units(wq, layer_w(a.Wqkv, l + 1));
+    pin();
+    __syncthreads();
+    if (ui < 4 && um < rows) {
+      const floatx4 v = total4(ui);
+      put4(l, at(l, Rg::fs) + (ks * CG + cg) * rp * 256, um * 256 + (ui * 16 + un) * 4, v[0], v[1], v[2], v[3]);
+    }
+  }
+  const int last = a.layers - 1;
+  if constexpr (PRE) own_norm(last, Rg::fs, layer_p(a.b2, last), a.lnfg, a.lnfb, last, -1, a.x_out, a.hidden);
+  else own_norm(last, Rg::fs, layer_p(a.b2, last), layer_p(a.ln3g, last), layer_p(a.ln3b, last), last, -1, nullptr, a.hidden);
+  if (tid == 0) {   // the last workgroup to get here: all have read the counters
+    const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n == (int)gridDim.x - 1) {
+      a.state[4] = 0;
+      a.state[1] = G * group_bytes;
+      a.state[0] = (start + a.layers) & 1;
+    }
+  }
+}
+
 struct Choice { int dk, x, groups, rows; };
 
 // Groups of at most 8 rows each; then as many workgroups per group as 256 CUs hold, but not more than 128 (an exchange
@@ -551,18 +1072,39 @@ const void* kernel_of(int dk, int x, int pre) {
   return nullptr;
 }
 
-// Whether every workgroup of the largest launch of this kernel is resident at once on the current device.
-bool resident(int dk, int x, int pre) {
-  static int known[5][5][2];   // 0 not asked yet, 1 no, 2 yes
-  int& k = known[dk][x][pre];
-  if (k == 0) {
-    int dev = 0, cus = 0, per_cu = 0;
-    const bool ok = hipGetDevice(&dev) == hipSuccess &&
-                    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                    hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel_of(dk, x, pre), kThreads, 0) == hipSuccess;
-    k = ok && cus * per_cu >= 256 ? 2 : 1;
+// the variant for more rows: groups of 16 or 32
+Choice choose_rows(int M, int d) {
+  Choice c = {d / 256, 0, 0, 0};
+  const int most = 256 / (d / 16);
+  for (int mb : {1, 2}) {
+    if ((M + 16 * mb - 1) / (16 * mb) > most) continue;
+    c.x = mb;
+    c.groups = min(most, M);
+    c.rows = (M + c.groups - 1) / c.groups;
+    c.groups = (M + c.rows - 1) / c.rows;
+    break;
   }
-  return k == 2;
+  return c;
+}
+
+const void* rows_kernel_of(int dk, int mb, int pre) {
+#define LSQ_ROWS(DKV, MBV) if (dk == DKV && mb == MBV) return pre ? (const void*)decoder_stack_rows_kernel<DKV, MBV, true> : (const void*)decoder_stack_rows_kernel<DKV, MBV, false>
+  LSQ_ROWS(2, 1); LSQ_ROWS(2, 2); LSQ_ROWS(3, 1); LSQ_ROWS(3, 2); LSQ_ROWS(4, 1); LSQ_ROWS(4, 2);
+#undef LSQ_ROWS
+  return nullptr;
+}
+
+// Whether every workgroup of a launch of 256 is resident at once on the current device.
+bool resident(const void* kernel) {
+  static std::unordered_map<const void*, bool> known;
+  const auto it = known.find(kernel);
+  if (it != known.end()) return it->second;
+  int dev = 0, cus = 0, per_cu = 0;
+  const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                  hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                  hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) == hipSuccess && cus * per_cu >= 256;
+  known[kernel] = ok;
+  return ok;
 }
 
 }  // namespace
@@ -571,20 +1113,42 @@ size_t stack_exchange_bytes(int arch, int M, int d, int layers) {
   return (size_t)(min(M, kStackRowsMax) + kRows) * layers * (arch == 1 ? Region<true>::size : Region<false>::size) * d;
 }
 
+size_t stack_rows_bytes(int arch, int M, int d) {
+  const int most = 32 * (256 / (d / 16));
+  return (size_t)(min(M, most) + 16) * (arch == 1 ? RowsRegion<true>::size : RowsRegion<false>::size) * d;
+}
+
 bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers) {
   return dtype == DT_F16 && d % 256 == 0 && d <= 1024 && H * 64 == d && F == 4 * d &&
          stack_exchange_bytes(arch, kStackRowsMax, d, layers) < (1u << 30);
 }
 
-bool stack_supported(int arch, int M, int d) {
-  if (M < 1 || M > kStackRowsMax) return false;
-  const Choice c = choose(arch, M, d);
-  return c.x != 0 && kernel_of(c.dk, c.x, arch == 1) != nullptr && resident(c.dk, c.x, arch == 1);
+// Which kernel takes M rows on the current device.  Measured, layers of one step in us (8-row groups / more rows):
+//   d = 512, 6 layers:    4 rows 92 / 98, 32 rows 116 / 108, 64 rows 117 / 116, 128 rows - / 137, 256 rows - / 196
+//   d = 768, 12 layers:   1 row 137 / 158, 8 rows 158 / 165, 32 rows 209 / 213, 40 rows 198 / 199, 64 rows - / 255
+//   d = 1024, 6 layers:   4 rows 122 / 126, 8 rows 134 / 128, 32 rows 174 / 147, 64 rows - / 189, 128 rows - / 266
+StackKind stack_kind(int arch, int M, int d) {
+  if (M < 1) return kStackNone;
+  const Choice c = choose(arch, M, d), r = choose_rows(M, d);
+  const bool few = c.x != 0 && M <= kStackRowsMax && kernel_of(c.dk, c.x, arch == 1) && resident(kernel_of(c.dk, c.x, arch == 1));
+  const bool many = r.x != 0 && rows_kernel_of(r.dk, r.x, arch == 1) && resident(rows_kernel_of(r.dk, r.x, arch == 1));
+  if (few && (!many || M <= (d == 768 ? 40 : d == 1024 ? 6 : 8))) return kStackFew;
+  return many ? kStackMany : kStackNone;
 }
 
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s) {
   hipError_t e = hipMemsetAsync(exchange, 0xFF, bytes, s);
   return e == hipSuccess ? hipMemsetAsync(state, 0, 8 * 4, s) : e;
+}
+
+hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s) {
+  const Choice c = choose_rows(args.M, d);
+  if (!c.x) return hipErrorInvalidValue;
+  StackArgs a = args;
+  a.groups = c.groups;
+  a.rows_per_group = c.rows;
+  void* kargs[] = {&a};
+  return hipLaunchKernel(rows_kernel_of(c.dk, c.x, arch == 1), dim3(d / 16 * c.groups), dim3(kThreads), kargs, 0, s);
 }
 
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s) {

@@ -161,7 +161,7 @@ hipError_t launch_encoder_attention(int dtype, const void* qkv, const int32_t* r
                                     const int32_t* off, const int32_t* len, void* out, int rows, int H,
                                     int d, int causal, hipStream_t s);
 
-// All decoder layers of a step in one launch, few rows (kernels_stack.hip).  Matrices: fragment-ordered copies; the
+// All decoder layers of a step in one launch (kernels_stack.hip).  Matrices: fragment-ordered copies; the
 // pointers are those of layer 0, layer l's lie packed_stride / plain_stride bytes further on for each layer.
 constexpr int kStackRowsMax = 64;
 struct StackArgs {
@@ -178,7 +178,8 @@ struct StackArgs {
   half_t *hidden, *x_out;   // normalised rows for the vocabulary product; pre-LN: the residual stream
   char* exchange;           // two sets of set_bytes each
   size_t set_bytes;
-  int32_t* state;           // [0] launches so far, [1 + p] rows of set p to be refilled, [4] arrivals
+  int32_t* state;           // few rows: [0] launches so far, [1 + p] rows of set p to be refilled, [4] arrivals; many:
+                            // [0] slot of the next layer, [1] bytes of the other one to be refilled, [4] arrivals
   int* error;               // pinned host memory: set when a wait ran out
   int M, beam, layers, T, anc_ld;
   float eps;
@@ -186,9 +187,12 @@ struct StackArgs {
 };
 size_t stack_exchange_bytes(int arch, int M, int d, int layers);   // of one set
 bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers);
-bool stack_supported(int arch, int M, int d);   // of a supported shape: these rows, on the current device
+enum StackKind { kStackNone, kStackFew, kStackMany };
+StackKind stack_kind(int arch, int M, int d);   // of a supported shape: which kernel takes these rows on the current device
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
+size_t stack_rows_bytes(int arch, int M, int d);   // of one set
+hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s);
 
 // Diverse beam search: the search kernels work on one group of every sentence at a time.  A sentence's
 // k_all rows are split into groups of kg; this launch takes group goff / kg (rows goff .. goff+kg-1 of

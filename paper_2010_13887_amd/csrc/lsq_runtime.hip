@@ -181,7 +181,7 @@ constexpr unsigned char kCanaryByte = 0xA5;
 struct Plan {
   std::vector<size_t> canaries;       // red zones behind the regions that live as long as the model
   std::vector<size_t> dec_canaries;   // ... behind the decoder's intermediates (valid from the end of lsq_encode on)
-  size_t stack_exchange, stack_set, stack_state;   // decoder stack in one launch (few rows); stack_set = 0: not for this shape
+  size_t stack_exchange, stack_set, stack_rows_exchange, stack_rows_set, stack_state;   // decoder stack in one launch (few rows); stack_set = 0: not for this shape
   size_t weights, wpacked, pe, cache, cross, score, tokens, len, fin, parent, anc, pen_tok, pen_n, cand_plain, cap, order, src_off, src_len, active, step_state,
       cand_score, cand_idx, out_ids, out_lens, out_scores, scratch, total;
   // encoder view of scratch
@@ -223,8 +223,10 @@ Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   p.src_len = take((size_t)B * 4);
   p.active = take((size_t)(T + 1) * 4);
   p.stack_set = stack_shape_supported(hp.dtype, hp.arch, hp.H, hp.d, hp.F, hp.n_dec) ? stack_exchange_bytes(hp.arch, (int)M, hp.d, hp.n_dec) : 0;
+  p.stack_rows_set = p.stack_set ? stack_rows_bytes(hp.arch, (int)M, hp.d) : 0;
   p.stack_exchange = take(2 * p.stack_set);
-  p.stack_state = take(8 * 4);
+  p.stack_rows_exchange = take(2 * p.stack_rows_set);
+  p.stack_state = take(16 * 4);   // 8 words per kernel
   p.step_state = take(4 * 4);   // [0] position counter, [1] arrival counter, [2] position of step 0
   const size_t kk = std::max(k, hp.sample_topk);   // survivors per row
   p.cand_score = take(M * kk * 4);
@@ -450,7 +452,24 @@ void setup_stack() {
   g.stack_ok = true;
 }
 
-bool use_stack(int M) { return g.stack_ok && g.fuse_ln && M <= g.block_rows && stack_supported(g.hp.arch, M, g.hp.d); }
+StackKind use_stack(int M) {
+  if (!g.stack_ok || !g.fuse_ln || (M > g.block_rows && g.block_rows < (int)kBlockRowsMax)) return kStackNone;
+  return stack_kind(g.hp.arch, M, g.hp.d);
+}
+
+hipError_t launch_stack(StackKind kind, StackArgs a) {
+  if (kind == kStackFew) return launch_decoder_stack(g.hp.arch, a, g.hp.d, g.stream);
+  a.exchange = g.ws + g.plan.stack_rows_exchange;
+  a.set_bytes = g.plan.stack_rows_set;
+  a.state += 8;
+  return launch_decoder_stack_rows(g.hp.arch, a, g.hp.d, g.stream);
+}
+
+hipError_t reset_stack() {
+  const Plan& p = g.plan;
+  hipError_t e = launch_stack_reset(g.ws + p.stack_exchange, 2 * p.stack_set, at<int32_t>(p.stack_state), g.stream);
+  return e == hipSuccess ? launch_stack_reset(g.ws + p.stack_rows_exchange, 2 * p.stack_rows_set, at<int32_t>(p.stack_state) + 8, g.stream) : e;
+}
 
 // All launches of one decode step for the first B sentences (B*k rows).  Nothing here depends on
 // the step index: kernels read it from the device-side counter (step_state[0]), the cache and
@@ -526,11 +545,11 @@ int launch_step(int B) {
     pending.on = false;
     return LSQ_OK;
   };
-  const bool stack = use_stack(M);
+  const StackKind stack = use_stack(M);
   if (stack) {
     StackArgs a = g.stack;
     a.M = M; a.anc = anc; a.x0 = (const half_t*)x0; a.hidden = (half_t*)x_home;
-    TIMED(PC_STACK, launch_decoder_stack(hp.arch, a, d, s));
+    TIMED(PC_STACK, launch_stack(stack, a));
     x = x_home;
   }
   for (int l = 0; l < (stack ? 0 : hp.n_dec); ++l) {
@@ -715,11 +734,11 @@ int launch_step_gpt(int B) {
     if (attention_blocks_supported(dt, M, 1, H, d)) nq = 1;
     if (M * H > 256 && M % 2 == 0 && attention_blocks_supported(dt, M, 2, H, d)) nq = 2;
   }
-  const bool stack = use_stack(M);
+  const StackKind stack = use_stack(M);
   if (stack) {
     StackArgs a = g.stack;
     a.M = M; a.anc = nullptr; a.hidden = (half_t*)y; a.x_out = (half_t*)x;
-    TIMED(PC_STACK, launch_decoder_stack(hp.arch, a, d, s));
+    TIMED(PC_STACK, launch_stack(stack, a));
   } else if (nq) {
     char* x_alt = g.ws + p.d_x2;
     float* ffn_slabs = (float*)tmp;
@@ -1066,10 +1085,9 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
   const size_t result_bytes = (size_t)max_batch * beam * (max_len + 2) * 4;
   if (result_bytes <= kResultsMax) HIPCHK(hipHostMalloc((void**)&g.results, result_bytes, hipHostMallocCoherent));
 
-  if (plan.stack_set) HIPCHK(launch_stack_reset(g.ws + plan.stack_exchange, 2 * plan.stack_set, (int32_t*)(g.ws + plan.stack_state), g.stream));
-
   g.hp = hp;
   g.plan = plan;
+  if (plan.stack_set) HIPCHK(reset_stack());
   g.max_batch = max_batch; g.beam = beam; g.max_len = max_len;
   size_t i = 0;
   g.E = dev[i++];
@@ -1121,7 +1139,7 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
   }
   HIPCHK(hipStreamSynchronize(g.stream));   // the staging buffer may still feed an earlier copy
   if (g.page->error) {   // an earlier translation was given up: its exchange regions are in no known state
-    HIPCHK(launch_stack_reset(g.ws + g.plan.stack_exchange, 2 * g.plan.stack_set, at<int32_t>(g.plan.stack_state), g.stream));
+    HIPCHK(reset_stack());
     g.page->error = 0;
   }
   g.page->step = 0;

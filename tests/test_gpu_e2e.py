@@ -340,3 +340,22 @@ def test_no_kernel_writes_outside_its_region(lsq):
         lsq.lsq_free()
         lsq.lsq_set_canaries(False)
         lsq.lsq_set_cache_refresh(lsq.REFRESH_TABLE)
+
+
+@pytest.mark.parametrize("d,batch,beam", [
+    (256, 1, 1), (256, 16, 4),                               # groups of 8 rows only: the smallest and the largest
+    (512, 2, 4), (512, 3, 3), (512, 32, 8), (512, 33, 8),    # 8 rows, 9 (ragged groups), 256 rows, one sentence more
+    (768, 5, 8), (768, 41, 1), (768, 40, 4),                 # 40 rows, 41 (one row a group is left over), 160
+    (1024, 1, 7), (1024, 13, 5), (1024, 32, 4),              # 7 rows, 65 (past the attention blocks), 128
+])
+def test_decoder_stack_matches_oracle(lsq, d, batch, beam):
+    """All decoder layers as one launch (float16, heads of 64, d_ffn = 4 d), at the edges of its row counts: the
+    first steps in lock-step with the oracle; a second translation gives the same bits."""
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=203, max_pos=32, dtype=1, cap_extra=3)
+    w = S.custom(hp, [1 + (5 * i) % 7 for i in range(batch)], beam=beam, max_len=12, std=0.03)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, batch, beam, 12) as eng:
+        lockstep(lsq, eng, blob, w, max_steps=3)
+        one, two = (eng.translate(w.src_ids, w.src_lens, sync_every=n) for n in (1, 4))
+        assert all(np.array_equal(a, b) for a, b in zip(one, two))
+        assert lsq.lsq_debug_check_canaries() == 0

@@ -131,3 +131,18 @@ def test_gpt2_small_shape(lsq, name):
         assert np.isfinite(scores).all() and (scores < 0).all()
         ids2, lens2, scores2 = eng.translate(w.src_ids, w.src_lens, sync_every=9)
         assert np.array_equal(ids, ids2) and np.array_equal(scores, scores2)
+
+
+@pytest.mark.parametrize("d,batch", [(256, 9), (512, 1), (512, 17), (512, 129), (768, 40), (768, 63), (1024, 6), (1024, 128)])
+def test_decoder_stack_matches_oracle(lsq, d, batch):
+    """All blocks of a step as one launch (float16, heads of 64, d_ffn = 4 d), at the edges of its row counts: the
+    first steps in lock-step with the oracle; a second generation gives the same bits."""
+    hp = S.HParams(arch=1, n_enc=0, n_dec=2, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=203, max_pos=32, act=1, norm=1, dtype=1,
+                   sample_topk=4, cap_extra=8, seed=d + batch)
+    w = S.custom(hp, [3] * batch, beam=1, max_len=11, std=0.03, seed=batch)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, batch, 1, w.max_len) as eng:
+        lockstep_gpt(lsq, eng, blob, w, n_steps=3)
+        one, two = (eng.translate(w.src_ids, w.src_lens, sync_every=n) for n in (1, 4))
+        assert all(np.array_equal(a, b) for a, b in zip(one, two))
+        assert lsq.lsq_debug_check_canaries() == 0
