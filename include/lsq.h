@@ -149,13 +149,14 @@ int lsq_set_cache_refresh(int mode);
  * to the last bits, not always bit for bit.  Default: on. */
 int lsq_set_layernorm_fusion(int on);
 
-/* Float16 models with heads of 64: fewer, larger launches while at most max_rows rows are alive.
- * Models with d = 256, 512, 768 or 1024 and d_ffn = 4 d run ALL decoder layers of a step as one
- * launch (max_rows = 64: also above 64 rows, up to 128 for d = 1024, 160 for 768, 256 for 512); other shapes with d = 256 or 512 and beam <= 4 run each attention sublayer of a decoder
- * layer as one launch up to its output projection (sec. 2.1 taken further;
- * lsq_k_self_attention_block, lsq_k_cross_attention_block).  0 switches both off; default and largest
- * value 64.  Same tokens as the separate kernels; scores equal to float16 rounding (other summation
- * orders).  Also off when lsq_set_layernorm_fusion(0).  May be called at any time. */
+/* Models with heads of 64: fewer, larger launches while at most max_rows rows are alive.  With d_ffn = 4 d
+ * and d = 256, 512, 768 or 1024 (float32: 256 or 512, encoder-decoder) ALL decoder layers of a step are one
+ * launch (max_rows = 64: also above 64 rows, up to 128 for d = 1024, 160 for 768, 256 for 512, float32 256);
+ * other float16 shapes with d = 256 or 512 and beam <= 4 run each attention sublayer of a decoder layer as one
+ * launch up to its output projection (sec. 2.1 taken further; lsq_k_self_attention_block,
+ * lsq_k_cross_attention_block).  0 switches both off; default and largest value 64.  Same tokens as the separate
+ * kernels; scores equal to rounding (other summation orders).  Also off when lsq_set_layernorm_fusion(0).  May
+ * be called at any time. */
 int lsq_set_attention_blocks(int max_rows);
 
 /* Plain beam search of float16 models: the logit product also leaves, for every row and every 32

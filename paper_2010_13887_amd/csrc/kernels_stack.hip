@@ -19,62 +19,20 @@
 //
 // All workgroups must be resident at once: the launcher checks the occupancy, and every wait is bounded (kSpinLimit
 // polls, then the error flag is set, nothing is waited for any more and the launch runs to its end).
-#include <unordered_map>
-
-#include "lsq_internal.h"
+#include "stack_exchange.h"
 
 namespace lsq {
 
 namespace {
 
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr unsigned kSentinel = 0xFFFFFFFFu;
-constexpr int kAgent = 16;             // cache policy of agent scope: sc1
-constexpr int kSpinLimit = 1 << 19;    // polls of about a microsecond
 constexpr int kRows = 8;               // rows of a group
 constexpr int kMinRows = 4;            // a writer's piece is at least as large as for these: several writers in one line slow each other down
-constexpr int kThreads = 512, kWaves = 8;
 
 // Byte offsets of a row's intermediates inside one layer's region (d: row width)
 template <bool PRE> struct Region {
   static constexpr int qkv = 0, ctx = 6, u1 = 8;
   static constexpr int q2 = PRE ? 0 : 12, ctx2 = PRE ? 0 : 14, u2 = PRE ? 0 : 16;   // cross-attention: post-LN models
   static constexpr int ff = PRE ? 10 : 20, u3 = PRE ? 18 : 28, size = PRE ? 20 : 32;
-};
-
-__device__ __forceinline__ unsigned publish_word(unsigned v) { return v == kSentinel ? 0x7FFF7FFFu : v; }   // one NaN for another
-
-struct Exchange {
-  __amdgpu_buffer_rsrc_t rsrc;
-  int* error;
-  bool dead;
-
-  // v[i] = the 16 bytes at base(i) + lane(i) once all of them have been written (base: the same in all lanes)
-  template <int N, typename B, typename L>
-  __device__ __forceinline__ void wait(B base, L lane, u32x4 (&v)[N]) {
-    for (int left = dead ? 1 : kSpinLimit;;) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane(i), base(i), kAgent);
-      unsigned worst = 0;
-#pragma unroll
-      for (int i = 0; i < N; ++i) worst = max(max(worst, max(v[i].x, v[i].y)), max(v[i].z, v[i].w));
-      if (__all(worst != kSentinel)) return;
-      if (--left == 0) break;
-      __builtin_amdgcn_s_sleep(1);
-      asm volatile("" ::: "memory");
-    }
-    dead = true;
-    __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
-  __device__ __forceinline__ void put(int base, int lane, unsigned v) {
-    __builtin_amdgcn_raw_buffer_store_b32(publish_word(v), rsrc, lane, base, kAgent);
-  }
-  __device__ __forceinline__ void put(int base, int lane, float v) { put(base, lane, __builtin_bit_cast(unsigned, v)); }
-  __device__ __forceinline__ void put2(int base, int lane, half_t a, half_t b) {
-    typedef half_t half2_t __attribute__((ext_vector_type(2)));
-    put(base, lane, __builtin_bit_cast(unsigned, half2_t{a, b}));
-  }
 };
 
 __device__ __forceinline__ float tanh_gelu(float v) {
@@ -1092,19 +1050,6 @@ const void* rows_kernel_of(int dk, int mb, int pre) {
   LSQ_ROWS(2, 1); LSQ_ROWS(2, 2); LSQ_ROWS(3, 1); LSQ_ROWS(3, 2); LSQ_ROWS(4, 1); LSQ_ROWS(4, 2);
 #undef LSQ_ROWS
   return nullptr;
-}
-
-// Whether every workgroup of a launch of 256 is resident at once on the current device.
-bool resident(const void* kernel) {
-  static std::unordered_map<const void*, bool> known;
-  const auto it = known.find(kernel);
-  if (it != known.end()) return it->second;
-  int dev = 0, cus = 0, per_cu = 0;
-  const bool ok = hipGetDevice(&dev) == hipSuccess &&
-                  hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                  hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) == hipSuccess && cus * per_cu >= 256;
-  known[kernel] = ok;
-  return ok;
 }
 
 }  // namespace

@@ -187,12 +187,18 @@ struct StackArgs {
 };
 size_t stack_exchange_bytes(int arch, int M, int d, int layers);   // of one set
 bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers);
-enum StackKind { kStackNone, kStackFew, kStackMany };
+enum StackKind { kStackNone, kStackFew, kStackMany, kStackF32 };
 StackKind stack_kind(int arch, int M, int d);   // of a supported shape: which kernel takes these rows on the current device
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
 size_t stack_rows_bytes(int arch, int M, int d);   // of one set
 hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s);
+// float32 (kernels_stack_f32.hip): the matrices are copies made by launch_pack_f32 (16-column units), vectors, cache and rows float32
+size_t stack_f32_bytes(int M, int d);
+bool stack_f32_shape_supported(int dtype, int arch, int H, int d, int F);
+bool stack_f32_supported(int M, int d);   // of a supported shape: these rows, on the current device
+hipError_t launch_pack_f32(const void* plain, void* packed, int N, int K, hipStream_t s);
+hipError_t launch_decoder_stack_f32(const StackArgs& args, int d, hipStream_t s);
 
 // Diverse beam search: the search kernels work on one group of every sentence at a time.  A sentence's
 // k_all rows are split into groups of kg; this launch takes group goff / kg (rows goff .. goff+kg-1 of

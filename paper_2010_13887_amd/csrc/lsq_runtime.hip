@@ -181,7 +181,7 @@ constexpr unsigned char kCanaryByte = 0xA5;
 struct Plan {
   std::vector<size_t> canaries;       // red zones behind the regions that live as long as the model
   std::vector<size_t> dec_canaries;   // ... behind the decoder's intermediates (valid from the end of lsq_encode on)
-  size_t stack_exchange, stack_set, stack_rows_exchange, stack_rows_set, stack_state;   // decoder stack in one launch (few rows); stack_set = 0: not for this shape
+  size_t stack_exchange, stack_set, stack_rows_exchange, stack_rows_set, stack_state;   // decoder stack in one launch (few rows); stack_rows_set = 0: not for this shape
   size_t weights, wpacked, pe, cache, cross, score, tokens, len, fin, parent, anc, pen_tok, pen_n, cand_plain, cap, order, src_off, src_len, active, step_state,
       cand_score, cand_idx, out_ids, out_lens, out_scores, scratch, total;
   // encoder view of scratch
@@ -224,6 +224,7 @@ Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   p.active = take((size_t)(T + 1) * 4);
   p.stack_set = stack_shape_supported(hp.dtype, hp.arch, hp.H, hp.d, hp.F, hp.n_dec) ? stack_exchange_bytes(hp.arch, (int)M, hp.d, hp.n_dec) : 0;
   p.stack_rows_set = p.stack_set ? stack_rows_bytes(hp.arch, (int)M, hp.d) : 0;
+  if (stack_f32_shape_supported(hp.dtype, hp.arch, hp.H, hp.d, hp.F)) p.stack_rows_set = stack_f32_bytes((int)M, hp.d);
   p.stack_exchange = take(2 * p.stack_set);
   p.stack_rows_exchange = take(2 * p.stack_rows_set);
   p.stack_state = take(16 * 4);   // 8 words per kernel
@@ -281,7 +282,8 @@ size_t blob_bytes(const HParams& hp) {
 
 // Fragment-ordered second copies of the float16 matrices (products of at most 64 rows read these).
 size_t packed_weight_bytes(const HParams& hp) {
-  if (hp.dtype != DT_F16) return 0;
+  if (hp.dtype != DT_F16)   // the decoder's matrices, for the stack kernel
+    return stack_f32_shape_supported(hp.dtype, hp.arch, hp.H, hp.d, hp.F) ? (size_t)hp.n_dec * 14 * hp.d * hp.d * 4 : 0;
   std::vector<TensorDesc> ts;
   tensor_walk(hp, &ts);
   size_t n = 0;
@@ -393,18 +395,27 @@ int sublayer(int cls, const void* in, const void* W, const void* bias, const voi
 
 // Arguments of the decoder stack kernel that a model fixes.  It finds layer l's tensors at a constant distance from
 // layer 0's, which is how tensor_walk lays them out.
-void setup_stack() {
+int setup_stack() {
   const HParams& hp = g.hp;
   const Plan& p = g.plan;
   g.stack_ok = false;
-  if (!p.stack_set) return;
+  if (!p.stack_rows_set) return LSQ_OK;
   const int d = hp.d, F = hp.F, L = hp.n_dec;
   const size_t es = esz();
   StackArgs& a = g.stack;
   a = StackArgs{};
   struct Ref { const half_t** at; const char* p0; const char* p1; const char* pl; };
   std::vector<Ref> packed, plain;
+  char* next = g.ws + p.wpacked;   // float32: copies are made here, layer after layer
+  hipError_t e = hipSuccess;
   auto mat = [&](const half_t** at, auto get, int N, int K) {
+    if (hp.dtype == DT_F32) {
+      a.packed_stride = (size_t)14 * d * d * 4;
+      for (int l = 0; l < L && e == hipSuccess; ++l) e = launch_pack_f32(get(l), next + l * a.packed_stride, N, K, g.stream);
+      *at = (const half_t*)next;
+      next += (size_t)N * K * 4;
+      return;
+    }
     auto of = [&](int l) { return (const char*)gemm_packed_weights(get(l), N, K); };
     packed.push_back({at, of(0), of(std::min(1, L - 1)), of(L - 1)});
   };
@@ -436,7 +447,9 @@ void setup_stack() {
     }
     return true;
   };
-  if (!regular(packed, &a.packed_stride) || !regular(plain, &a.plain_stride)) return;
+  HIPCHK(e);
+  if (hp.dtype == DT_F16 && !regular(packed, &a.packed_stride)) return LSQ_OK;
+  if (!regular(plain, &a.plain_stride)) return LSQ_OK;
   a.cache = g.ws + p.cache;
   a.cache_stride = (size_t)g.max_batch * g.beam * g.max_len * d * es;
   a.cross = g.ws + p.cross;
@@ -450,10 +463,12 @@ void setup_stack() {
   a.layers = L; a.T = g.max_len; a.anc_ld = g.max_len + 1; a.eps = hp.eps;
   a.beam = g.beam;
   g.stack_ok = true;
+  return LSQ_OK;
 }
 
 StackKind use_stack(int M) {
   if (!g.stack_ok || !g.fuse_ln || (M > g.block_rows && g.block_rows < (int)kBlockRowsMax)) return kStackNone;
+  if (g.hp.dtype == DT_F32) return stack_f32_supported(M, g.hp.d) ? kStackF32 : kStackNone;
   return stack_kind(g.hp.arch, M, g.hp.d);
 }
 
@@ -462,12 +477,13 @@ hipError_t launch_stack(StackKind kind, StackArgs a) {
   a.exchange = g.ws + g.plan.stack_rows_exchange;
   a.set_bytes = g.plan.stack_rows_set;
   a.state += 8;
+  if (kind == kStackF32) return launch_decoder_stack_f32(a, g.hp.d, g.stream);
   return launch_decoder_stack_rows(g.hp.arch, a, g.hp.d, g.stream);
 }
 
 hipError_t reset_stack() {
   const Plan& p = g.plan;
-  hipError_t e = launch_stack_reset(g.ws + p.stack_exchange, 2 * p.stack_set, at<int32_t>(p.stack_state), g.stream);
+  hipError_t e = !p.stack_set ? hipSuccess : launch_stack_reset(g.ws + p.stack_exchange, 2 * p.stack_set, at<int32_t>(p.stack_state), g.stream);
   return e == hipSuccess ? launch_stack_reset(g.ws + p.stack_rows_exchange, 2 * p.stack_rows_set, at<int32_t>(p.stack_state) + 8, g.stream) : e;
 }
 
@@ -1087,7 +1103,7 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
 
   g.hp = hp;
   g.plan = plan;
-  if (plan.stack_set) HIPCHK(reset_stack());
+  if (plan.stack_rows_set) HIPCHK(reset_stack());
   g.max_batch = max_batch; g.beam = beam; g.max_len = max_len;
   size_t i = 0;
   g.E = dev[i++];
@@ -1099,7 +1115,7 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
       L.ln2g = dev[i++]; L.ln2b = dev[i++]; L.W1 = dev[i++]; L.b1 = dev[i++]; L.W2 = dev[i++]; L.b2 = dev[i++];
     }
     g.lnfg = dev[i++]; g.lnfb = dev[i++];
-    setup_stack();
+    if (int rc = setup_stack()) return rc;
     g.state = 2;
     return LSQ_OK;
   }
@@ -1115,7 +1131,7 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
     L.ln2g = dev[i++]; L.ln2b = dev[i++];
     L.W1 = dev[i++]; L.b1 = dev[i++]; L.W2 = dev[i++]; L.b2 = dev[i++]; L.ln3g = dev[i++]; L.ln3b = dev[i++];
   }
-  setup_stack();
+  if (int rc = setup_stack()) return rc;
   g.state = 2;
   return LSQ_OK;
 }

@@ -1,0 +1,67 @@
+// What the decoder stack kernels hand each other intermediates with (see kernels_stack.hip).
+#pragma once
+#include <unordered_map>
+
+#include "lsq_internal.h"
+
+namespace lsq {
+
+namespace {
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr unsigned kSentinel = 0xFFFFFFFFu;
+constexpr int kAgent = 16;             // cache policy of agent scope: sc1
+constexpr int kSpinLimit = 1 << 19;    // polls of about a microsecond
+constexpr int kThreads = 512, kWaves = 8;
+
+__device__ __forceinline__ unsigned publish_word(unsigned v) { return v == kSentinel ? 0x7FFF7FFFu : v; }   // one NaN for another
+
+struct Exchange {
+  __amdgpu_buffer_rsrc_t rsrc;
+  int* error;
+  bool dead;
+
+  // v[i] = the 16 bytes at base(i) + lane(i) once all of them have been written (base: the same in all lanes)
+  template <int N, typename B, typename L>
+  __device__ __forceinline__ void wait(B base, L lane, u32x4 (&v)[N]) {
+    for (int left = dead ? 1 : kSpinLimit;;) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane(i), base(i), kAgent);
+      unsigned worst = 0;
+#pragma unroll
+      for (int i = 0; i < N; ++i) worst = max(max(worst, max(v[i].x, v[i].y)), max(v[i].z, v[i].w));
+      if (__all(worst != kSentinel)) return;
+      if (--left == 0) break;
+      __builtin_amdgcn_s_sleep(1);
+      asm volatile("" ::: "memory");
+    }
+    dead = true;
+    __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  __device__ __forceinline__ void put(int base, int lane, unsigned v) {
+    __builtin_amdgcn_raw_buffer_store_b32(publish_word(v), rsrc, lane, base, kAgent);
+  }
+  __device__ __forceinline__ void put(int base, int lane, float v) { put(base, lane, __builtin_bit_cast(unsigned, v)); }
+  __device__ __forceinline__ void put2(int base, int lane, half_t a, half_t b) {
+    typedef half_t half2_t __attribute__((ext_vector_type(2)));
+    put(base, lane, __builtin_bit_cast(unsigned, half2_t{a, b}));
+  }
+};
+
+// Whether every workgroup of a launch of 256 is resident at once on the current device.
+inline bool resident(const void* kernel) {
+  static std::unordered_map<const void*, bool> known;
+  const auto it = known.find(kernel);
+  if (it != known.end()) return it->second;
+  int dev = 0, cus = 0, per_cu = 0;
+  const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                  hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                  hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) == hipSuccess && cus * per_cu >= 256;
+  known[kernel] = ok;
+  return ok;
+}
+
+}  // namespace
+
+}  // namespace lsq

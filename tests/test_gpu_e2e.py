@@ -342,17 +342,19 @@ def test_no_kernel_writes_outside_its_region(lsq):
         lsq.lsq_set_cache_refresh(lsq.REFRESH_TABLE)
 
 
-@pytest.mark.parametrize("d,batch,beam", [
-    (256, 1, 1), (256, 16, 4),                               # groups of 8 rows only: the smallest and the largest
-    (512, 2, 4), (512, 3, 3), (512, 32, 8), (512, 33, 8),    # 8 rows, 9 (ragged groups), 256 rows, one sentence more
-    (768, 5, 8), (768, 41, 1), (768, 40, 4),                 # 40 rows, 41 (one row a group is left over), 160
-    (1024, 1, 7), (1024, 13, 5), (1024, 32, 4),              # 7 rows, 65 (past the attention blocks), 128
+@pytest.mark.parametrize("d,batch,beam,dtype", [
+    (256, 1, 1, 1), (256, 16, 4, 1),                               # groups of 8 rows only: the smallest and the largest
+    (512, 2, 4, 1), (512, 3, 3, 1), (512, 32, 8, 1), (512, 33, 8, 1),    # 8 rows, 9 (ragged groups), 256 rows, one sentence more
+    (768, 5, 8, 1), (768, 41, 1, 1), (768, 40, 4, 1),                 # 40 rows, 41 (one row a group is left over), 160
+    (1024, 1, 7, 1), (1024, 13, 5, 1), (1024, 32, 4, 1),              # 7 rows, 65 (past the attention blocks), 128
+    (256, 1, 1, 0), (256, 64, 4, 0), (256, 65, 4, 0),         # float32: one row, 256 rows, too many for one launch
+    (512, 2, 8, 0), (512, 11, 3, 0), (512, 33, 4, 0), (512, 32, 8, 0),   # 16 rows, 33 (5 a group), 132 (17), 256
 ])
-def test_decoder_stack_matches_oracle(lsq, d, batch, beam):
-    """All decoder layers as one launch (float16, heads of 64, d_ffn = 4 d), at the edges of its row counts: the
+def test_decoder_stack_matches_oracle(lsq, d, batch, beam, dtype):
+    """All decoder layers as one launch (heads of 64, d_ffn = 4 d), at the edges of its row counts: the
     first steps in lock-step with the oracle; a second translation gives the same bits."""
-    hp = S.HParams(n_enc=1, n_dec=2, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=203, max_pos=32, dtype=1, cap_extra=3)
-    w = S.custom(hp, [1 + (5 * i) % 7 for i in range(batch)], beam=beam, max_len=12, std=0.03)
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=203, max_pos=32, dtype=dtype, cap_extra=3)
+    w = S.custom(hp, [1 + (5 * i) % 7 for i in range(batch)], beam=beam, max_len=12, std=0.03 if dtype else 0.1)
     blob = w.blob(ln_jitter=0.1)
     with lsq.Engine(blob, batch, beam, 12) as eng:
         lockstep(lsq, eng, blob, w, max_steps=3)
