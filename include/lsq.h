@@ -159,7 +159,7 @@ int lsq_set_layernorm_fusion(int on);
  * be called at any time. */
 int lsq_set_attention_blocks(int max_rows);
 
-/* Plain beam search of float16 models: the logit product also leaves, for every row and every 32
+/* Beam search (float32 models: d a multiple of 8): the logit product also leaves, for every row and every 32
  * consecutive tokens, the largest logit and the sum of exponentials, and the retrieve stage (sec.
  * 2.2) takes its threshold and the softmax normaliser from those and reads only the logits of the
  * groups that reach the threshold (lsq_k_gemm_logits, lsq_k_row_topk_groups).  Diverse beam search: mode 1 only.

@@ -999,11 +999,13 @@ __global__ void __launch_bounds__(256) gemm_f32_stream_kernel(const float* __res
   __syncthreads();
   const int vg = wave;
   const int n = n0 + vg * 8 + (lane >> 5) * 4;
-  if (n >= N) return;
+  __shared__ float st_m[4][TM][32], st_z[4][TM][32];
+  const bool stats = out.stats != nullptr;   // the same in every thread
+  if (n >= N && !stats) return;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int m = mb + i * 32 + (lane & 31);
-    if (m >= M) continue;
+    if (m >= M && !stats) continue;
     float v[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1012,7 +1014,35 @@ __global__ void __launch_bounds__(256) gemm_f32_stream_kernel(const float* __res
       if (bias) v[e] += bias[min(n + e, N - 1)];
       v[e] = activate(v[e], act);
     }
-    store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp);
+    if (m < M && n < N) store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp);
+    if (stats) {   // as in gemm_f16_skinny_kernel
+      float mx = -INFINITY, z = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (n + e < N) mx = fmaxf(mx, v[e]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (n + e < N) z += __expf(v[e] - mx);
+      const float m2 = lane_xor<32>(mx), z2 = lane_xor<32>(z);
+      merge_stat(mx, z, m2, z2);
+      if (lane < 32) { st_m[wave][i][lane] = mx; st_z[wave][i][lane] = z; }
+    }
+  }
+  if (stats) {
+    __syncthreads();   // every thread of the workgroup gets here
+    if (wave == 0 && lane < 32) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int m = mb + i * 32 + lane;
+        if (m >= M) continue;
+        float mx = st_m[0][i][lane], z = st_z[0][i][lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) merge_stat(mx, z, st_m[w][i][lane], st_z[w][i][lane]);
+        float* st = out.stats + ((size_t)m * out.stats_groups + blockIdx.x) * 2;
+        st[0] = mx;
+        st[1] = z;
+      }
+    }
   }
 }
 
@@ -1258,9 +1288,10 @@ hipError_t launch_gemm_partials(int dtype, const void* A, const void* B, float* 
   return hipGetLastError();
 }
 
-// every float16 product kernel launch_gemm chooses for a float32 output can fill GemmOut::stats
+// every product kernel launch_gemm chooses for a float32 output (operands on 16 bytes) can fill GemmOut::stats
 bool gemm_writes_stats(int dtype, int M, int N, int K) {
-  return dtype == DT_F16 && M > 0 && N > 0 && K > 0 && K % 8 == 0;
+  (void)dtype;
+  return M > 0 && N > 0 && K > 0 && K % 8 == 0;
 }
 
 hipError_t launch_gemm(int dtype, const void* A, const void* B, const void* bias, const GemmOut& out, int M,
@@ -1269,7 +1300,7 @@ hipError_t launch_gemm(int dtype, const void* A, const void* B, const void* bias
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K <= 0) return hipErrorInvalidValue;
   if (b_packed && !(dtype == DT_F16 && M <= kSkinnyRows && K % 16 == 0)) return hipErrorInvalidValue;
-  if (out.stats && !(out.f32_out && gemm_writes_stats(dtype, M, N, K) && out.stats_groups >= (N + 31) / 32))
+  if (out.stats && !((out.f32_out || dtype == DT_F32) && gemm_writes_stats(dtype, M, N, K) && out.stats_groups >= (N + 31) / 32))
     return hipErrorInvalidValue;
   if (dtype == DT_F32) {
     if (K % 8 == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15) == 0) {
@@ -1292,6 +1323,7 @@ hipError_t launch_gemm(int dtype, const void* A, const void* B, const void* bias
       }
       return hipGetLastError();
     }
+    if (out.stats) return hipErrorInvalidValue;
     dim3 grid((N + 63) / 64, (M + 63) / 64), blk(256);   // odd K or unaligned operands: the plain tile kernel
     gemm_f32_kernel<<<grid, blk, 0, s>>>((const float*)A, (const float*)B, M, N, K, out.tpos, (const float*)bias, act, out);
     return hipGetLastError();
