@@ -21,12 +21,12 @@ struct RegionF32 {
   static constexpr int xi = 0, qkv = 4, ctx = 16, os = 20, x1 = 36, qs = 40, ctx2 = 56, cs = 60, x2 = 76, ff = 80, fs = 96, size = 112;
 };
 
-// Weights [N][K] -> [N / 16][K / 4][16 columns][4 k]: what the wavefronts below load is contiguous
-__global__ void __launch_bounds__(256) pack_f32_kernel(const floatx4* __restrict__ src, floatx4* __restrict__ dst, int K4, size_t n) {
+// Weights [N][K] -> [N / 16][K / 4][16 columns][4 k]: what the wavefronts below load is contiguous.  Rows past N: zeros.
+__global__ void __launch_bounds__(256) pack_f32_kernel(const floatx4* __restrict__ src, floatx4* __restrict__ dst, int N, int K4, size_t n) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  const size_t unit = i / 16 / K4, k4 = i / 16 % K4;
-  dst[i] = src[(unit * 16 + i % 16) * K4 + k4];
+  const size_t row = i / 16 / K4 * 16 + i % 16, k4 = i / 16 % K4;
+  dst[i] = row < (size_t)N ? src[row * K4 + k4] : floatx4{0.f, 0.f, 0.f, 0.f};
 }
 
 // DK: d / 256.  NB: blocks of 4 rows a group has at most.
@@ -434,9 +434,11 @@ bool stack_f32_supported(int M, int d) {
   return c.kernel && resident(c.kernel);
 }
 
+size_t pack_f32_bytes(int N, int K) { return (size_t)(N + 63) / 64 * 64 * K * 4; }
+
 hipError_t launch_pack_f32(const void* plain, void* packed, int N, int K, hipStream_t s) {
-  const size_t n = (size_t)N * K / 4;
-  pack_f32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const floatx4*)plain, (floatx4*)packed, K / 4, n);
+  const size_t n = pack_f32_bytes(N, K) / 16;
+  pack_f32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const floatx4*)plain, (floatx4*)packed, N, K / 4, n);
   return hipGetLastError();
 }
 

@@ -193,10 +193,11 @@ hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipS
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
 size_t stack_rows_bytes(int arch, int M, int d);   // of one set
 hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s);
-// float32 (kernels_stack_f32.hip): the matrices are copies made by launch_pack_f32 (16-column units), vectors, cache and rows float32
+// float32 (kernels_stack_f32.hip): the matrices are copies made by launch_pack_f32 (16-column units, columns up to a multiple of 64, K of 4), vectors, cache and rows float32
 size_t stack_f32_bytes(int M, int d);
 bool stack_f32_shape_supported(int dtype, int arch, int H, int d, int F);
 bool stack_f32_supported(int M, int d);   // of a supported shape: these rows, on the current device
+size_t pack_f32_bytes(int N, int K);
 hipError_t launch_pack_f32(const void* plain, void* packed, int N, int K, hipStream_t s);
 hipError_t launch_decoder_stack_f32(const StackArgs& args, int d, hipStream_t s);
 
@@ -252,6 +253,23 @@ struct NextInput {
   float scale;
 };
 inline NextInput no_next_input() { return NextInput{nullptr, nullptr, nullptr, 0, 0, 0.f}; }
+// One step of plain beam search with a small model in one launch (kernels_small.hip): the decoder's arguments are
+// StackArgs (float32: matrices packed by launch_pack_f32), the rest of the step's these.
+struct SearchArgs {
+  int d, F, H, V, T1, eos;
+  float qscale;              // log2(e) / sqrt(head size)
+  const void* Ep;            // packed copy of the embedding
+  float *logits, *stats, *score;
+  int32_t *tokens, *len, *fin, *parent;
+  const int32_t* cap;
+  int32_t *active, *step_state, *anc;
+  NextInput next;
+  float* cand_score;
+  int32_t* cand_idx;
+  unsigned long long* report;
+};
+bool small_step_supported(int arch, int H, int d, int F, int V, int k);
+hipError_t launch_small_step(int dtype, int batch, int k, const StackArgs& args, const SearchArgs& search, hipStream_t s);
 hipError_t launch_beam_refine(const float* cand_score, const int32_t* cand_idx, float* score,
                               int32_t* tokens, int32_t* len, int32_t* fin, int32_t* parent,
                               const int32_t* cap, int32_t* active, int batch, int k, int V, int T,

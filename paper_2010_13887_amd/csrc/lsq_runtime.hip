@@ -281,9 +281,15 @@ size_t blob_bytes(const HParams& hp) {
 }
 
 // Fragment-ordered second copies of the float16 matrices (products of at most 64 rows read these).
+// packed float32 matrices of one decoder layer of an encoder-decoder model
+size_t layer_bytes_f32(const HParams& hp) { return ((size_t)6 * hp.d * hp.d + (size_t)2 * hp.d * hp.F) * 4; }
+
 size_t packed_weight_bytes(const HParams& hp) {
-  if (hp.dtype != DT_F16)   // the decoder's matrices, for the stack kernel
-    return stack_f32_shape_supported(hp.dtype, hp.arch, hp.H, hp.d, hp.F) ? (size_t)hp.n_dec * 14 * hp.d * hp.d * 4 : 0;
+  if (hp.dtype != DT_F16) {   // the decoder's matrices, for the kernels that run whole steps
+    const bool small = small_step_supported(hp.arch, hp.H, hp.d, hp.F, hp.V, 1);
+    if (!small && !stack_f32_shape_supported(hp.dtype, hp.arch, hp.H, hp.d, hp.F)) return 0;
+    return hp.n_dec * layer_bytes_f32(hp) + (small ? pack_f32_bytes(hp.V, hp.d) : 0);
+  }
   std::vector<TensorDesc> ts;
   tensor_walk(hp, &ts);
   size_t n = 0;
@@ -336,6 +342,8 @@ struct Ctx {
   char* E = nullptr;
   bool stack_ok = false;        // the decoder stack kernel takes this model
   StackArgs stack{};            // ... with these arguments (all but those of a translation)
+  bool small_ok = false;        // a beam search step of this model can be one launch
+  SearchArgs search{};
   std::vector<GptLayer> gpt;
   char *lnfg = nullptr, *lnfb = nullptr;
   int prompt_len = 0;
@@ -399,7 +407,9 @@ int setup_stack() {
   const HParams& hp = g.hp;
   const Plan& p = g.plan;
   g.stack_ok = false;
-  if (!p.stack_rows_set) return LSQ_OK;
+  g.small_ok = false;
+  const bool small = small_step_supported(hp.arch, hp.H, hp.d, hp.F, hp.V, g.beam);
+  if (!p.stack_rows_set && !small) return LSQ_OK;
   const int d = hp.d, F = hp.F, L = hp.n_dec;
   const size_t es = esz();
   StackArgs& a = g.stack;
@@ -410,7 +420,7 @@ int setup_stack() {
   hipError_t e = hipSuccess;
   auto mat = [&](const half_t** at, auto get, int N, int K) {
     if (hp.dtype == DT_F32) {
-      a.packed_stride = (size_t)14 * d * d * 4;
+      a.packed_stride = layer_bytes_f32(hp);
       for (int l = 0; l < L && e == hipSuccess; ++l) e = launch_pack_f32(get(l), next + l * a.packed_stride, N, K, g.stream);
       *at = (const half_t*)next;
       next += (size_t)N * K * 4;
@@ -462,7 +472,18 @@ int setup_stack() {
   a.state = at<int32_t>(p.stack_state); a.error = &g.page->error;
   a.layers = L; a.T = g.max_len; a.anc_ld = g.max_len + 1; a.eps = hp.eps;
   a.beam = g.beam;
-  g.stack_ok = true;
+  g.stack_ok = p.stack_rows_set != 0;
+  if (small) {
+    char* E = g.ws + p.wpacked + L * layer_bytes_f32(hp);
+    if (hp.dtype == DT_F32) HIPCHK(launch_pack_f32(g.E, E, hp.V, d, g.stream));
+    const void* Ep = hp.dtype == DT_F32 ? E : gemm_packed_weights(g.E, hp.V, d);
+    g.search = SearchArgs{d, F, hp.H, hp.V, g.max_len + 1, hp.eos, 1.4426950408889634f / sqrtf((float)(d / hp.H)), Ep,
+                          (float*)(g.ws + p.d_logits), at<float>(p.d_stats), at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len),
+                          at<int32_t>(p.fin), at<int32_t>(p.parent), at<int32_t>(p.cap), at<int32_t>(p.active), at<int32_t>(p.step_state),
+                          nullptr, {g.E, at<float>(p.pe), g.ws + p.d_x0, d, hp.dtype, sqrtf((float)d)}, at<float>(p.cand_score),
+                          at<int32_t>(p.cand_idx), &g.page->step};
+    g.small_ok = Ep != nullptr;
+  }
   return LSQ_OK;
 }
 
@@ -470,6 +491,13 @@ StackKind use_stack(int M) {
   if (!g.stack_ok || !g.fuse_ln || (M > g.block_rows && g.block_rows < (int)kBlockRowsMax)) return kStackNone;
   if (g.hp.dtype == DT_F32) return stack_f32_supported(M, g.hp.d) ? kStackF32 : kStackNone;
   return stack_kind(g.hp.arch, M, g.hp.d);
+}
+
+// plain beam search with a small model: the whole step in one launch.  Up to as many sentences as the chip runs at once:
+// a workgroup's step takes as long as the separate launches of some hundred rows.
+bool use_small(int B) {
+  return g.small_ok && g.fuse_ln && (B * g.beam <= g.block_rows || g.block_rows == (int)kBlockRowsMax) && B <= 256 && g.groups == 1 &&
+         g.hp.sample_topk == 0 && g.topk_stats && g.merge_rerank;
 }
 
 hipError_t launch_stack(StackKind kind, StackArgs a) {
@@ -561,6 +589,17 @@ int launch_step(int B) {
     pending.on = false;
     return LSQ_OK;
   };
+  if (use_small(B)) {
+    StackArgs a = g.stack;
+    a.x0 = (const half_t*)x0; a.hidden = (half_t*)x_home;
+    SearchArgs se = g.search;
+    se.anc = anc;
+    TIMED(PC_STACK, launch_small_step(dt, B, k, a, se, s));
+    if (!anc)
+      TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
+                                             0, step, T, s));
+    return LSQ_OK;
+  }
   const StackKind stack = use_stack(M);
   if (stack) {
     StackArgs a = g.stack;
@@ -839,7 +878,7 @@ int enqueue_step() {
   const int B = g.alive_at[g.t];
   auto launch = [&](int n) { return g.hp.arch == 1 ? launch_step_gpt(n) : launch_step(n); };
   g.hidden_in_alt = false;   // launch_step says otherwise
-  if (!g.use_graphs || g.stream == nullptr || g_prof.on || use_stack(B * g.beam)) {
+  if (!g.use_graphs || g.stream == nullptr || g_prof.on || use_stack(B * g.beam) || use_small(B)) {
     int rc = launch(B);
     if (rc) return rc;
     g.t += 1;

@@ -361,3 +361,26 @@ def test_decoder_stack_matches_oracle(lsq, d, batch, beam, dtype):
         one, two = (eng.translate(w.src_ids, w.src_lens, sync_every=n) for n in (1, 4))
         assert all(np.array_equal(a, b) for a, b in zip(one, two))
         assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("d,heads,ffn,vocab,beam,dtype", [
+    (64, 4, 64, 31, 1, 0), (64, 2, 448, 1000, 8, 0), (128, 8, 512, 1001, 5, 0), (128, 4, 192, 97, 3, 0),
+    (64, 4, 512, 33, 8, 1), (128, 8, 64, 1024, 1, 1), (128, 4, 512, 65, 4, 1),
+])
+def test_small_model_step_matches_oracle(lsq, d, heads, ffn, vocab, beam, dtype):
+    """A whole step of a small model as one launch, at the edges of its shapes (row widths, head sizes, vocabularies that
+    end inside a group of 32 or a block of 64 columns, sources and histories of more than 64 positions)."""
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=d, n_heads=heads, d_ffn=ffn, vocab=vocab, max_pos=96, dtype=dtype, cap_extra=6)
+    w = S.custom(hp, [5, 1, 70, 64], beam=beam, max_len=75, std=0.3 if dtype == 0 else 0.08)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, 5, beam, 75) as eng:
+        lockstep(lsq, eng, blob, w, max_steps=4)
+        one, two = (eng.translate(w.src_ids, w.src_lens, sync_every=n) for n in (1, 5))
+        assert all(np.array_equal(a, b) for a, b in zip(one, two))
+        lsq.lsq_set_attention_blocks(0)
+        ids, lens, scores = eng.translate(w.src_ids, w.src_lens)
+        lsq.lsq_set_attention_blocks(64)
+        same = (ids == one[0]).all(axis=-1)
+        assert same.mean() >= (0.3 if dtype else 0.9)
+        np.testing.assert_allclose(scores[same], one[2][same], rtol=0, atol=5e-2 if dtype else 1e-3)
+        assert lsq.lsq_debug_check_canaries() == 0
