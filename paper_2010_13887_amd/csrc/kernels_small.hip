@@ -46,17 +46,8 @@ template <> struct Piece<half_t> {
 };
 
 struct SmallArgs { StackArgs st; SearchArgs se; };
-// The arguments are read where they are used, from the segment they arrive in: kept in registers from the start, as the
-// compiler would, they do not fit (1500 instructions of spilling; a translation of 8
-// steps 434 us instead of 392).
+// (1500 instructions of spilling with the arguments in registers: a translation of 8 steps 434 us instead of 392)
 using ArgsPtr = const __attribute__((address_space(4))) SmallArgs*;
-__device__ __forceinline__ ArgsPtr arguments() {
-  ArgsPtr p = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return p;
-}
-// a pointer that is known to lead to global memory
-template <typename U> __device__ __forceinline__ U* global(U* p) { return (U*)(__attribute__((address_space(1))) U*)p; }
 
 template <typename T, int K>
 __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
@@ -77,7 +68,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const ArgsPtr a0 = arguments();
+  const ArgsPtr a0 = arguments<SmallArgs>();
   const int b = blockIdx.x, r0 = b * K, D = a0->se.d, F = a0->se.F, H = a0->se.H, V = a0->se.V, G = (V + 31) / 32;
   const int layers = a0->st.layers, T1 = a0->se.T1, Tm = a0->st.T;
   const int pos = *global(a0->st.tpos);
@@ -170,7 +161,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
   const int VO = 3 * D, VN = VO + 3 * D, VF = VN + 6 * D, V2 = VF + F;   // after bqkv: bo, bq, boc; gains and shifts; b1; b2
   auto load_vectors = [&](int l) {
     float* to = vecs[l & 1];
-    const ArgsPtr p = arguments();
+    const ArgsPtr p = arguments<SmallArgs>();
     const size_t bytes = (size_t)l * p->st.plain_stride;
     auto copy = [&](const half_t* from, int at, int n) {
       const T* v = layer_of(from, bytes);
@@ -200,7 +191,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
     auto offset = [&](int key) {
       if (!self) return (unsigned)(min(key, last) * 2 * D + h * DH);
       int slab = slabs[row][key & 63];
-      if (c0 > 0 && table) slab = min(max(global(arguments()->se.anc)[(size_t)(r0 + row) * T1 + min(key, last)], 0), K - 1);
+      if (c0 > 0 && table) slab = min(max(global(arguments<SmallArgs>()->se.anc)[(size_t)(r0 + row) * T1 + min(key, last)], 0), K - 1);
       return (unsigned)((slab * Tm + min(key, last)) * D + h * DH);
     };
     unsigned vo[DQ];
@@ -277,13 +268,13 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
   auto request_stage = [&](int l, int stage) {
     int N, Kd;
     shape(stage, N, Kd);
-    const ArgsPtr p = arguments();
+    const ArgsPtr p = arguments<SmallArgs>();
     request(layer_of((&p->st.Wqkv)[stage], (size_t)l * p->st.packed_stride), N, Kd);   // Wqkv, Wo, Wq, Woc, W1, W2
   };
   auto request_unit = [&](int u) {   // of the embedding
     np = D / Pc::n;
     k0 = 0;
-    wp = Pc::at(reinterpret_cast<const T*>(global(arguments()->se.Ep)), D, u, 0, lane, G);
+    wp = Pc::at(reinterpret_cast<const T*>(global(arguments<SmallArgs>()->se.Ep)), D, u, 0, lane, G);
 #pragma unroll
     for (int i = 0; i < P; ++i)
       if (i < np) w[i] = *reinterpret_cast<const vec*>(wp + i * Pc::stride);
@@ -309,7 +300,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
   for (int l = 0, stage = 0; l < layers;) {
     // what is derived from a thread's place is derived anew instead of waiting in registers
     asm volatile("" : "+v"(tid), "+v"(lane));
-    const ArgsPtr p = arguments();
+    const ArgsPtr p = arguments<SmallArgs>();
     T* Kc = reinterpret_cast<T*>(global(p->st.cache) + (size_t)(2 * l) * p->st.cache_stride) + (size_t)r0 * Tm * D;
     T* Vc = reinterpret_cast<T*>(reinterpret_cast<char*>(Kc) + p->st.cache_stride);
     const T* kvb = reinterpret_cast<const T*>(global(p->st.cross) + (size_t)l * p->st.cross_stride) + (size_t)src_off * 2 * D;
@@ -345,7 +336,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
     stage = next;
     l = nl;
   }
-  const ArgsPtr a1 = arguments();
+  const ArgsPtr a1 = arguments<SmallArgs>();
   for (int i = tid; i < K * D; i += kThreads) reinterpret_cast<T*>(global(a1->st.hidden))[((size_t)r0 << ds) + i] = rowsT[XS + (i >> ds) * LX + (i & (D - 1))];
 
   // ======== logits and their group statistics: 64 columns per wavefront and turn
@@ -369,7 +360,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (wave >= K) return;   // barriers from here on are among the wavefronts that remain
-  const ArgsPtr e = arguments();
+  const ArgsPtr e = arguments<SmallArgs>();
   const NextInput next = {global(e->se.next.E), global(e->se.next.pe), global(e->se.next.x), e->se.next.d, e->se.next.dtype, e->se.next.scale};
   retrieve_rerank_sentence<4, K>(global(e->se.logits), global(e->se.stats), global(e->se.score), global(e->se.tokens), global(e->se.len),
                                  global(e->se.fin), global(e->se.parent), global(e->se.active), V, G, T1, global(e->se.step_state),

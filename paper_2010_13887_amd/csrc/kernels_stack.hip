@@ -106,8 +106,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   // two biases, unconverted: a conversion here would wait for everything requested before them
   auto bias_pair = [](const half_t* b, unsigned col) { return *reinterpret_cast<const half2_t*>(reinterpret_cast<const char*>(b) + col * 2u); };
   auto pin = [] { asm volatile("" ::: "memory"); };   // requests stay where they are written
-  auto layer_w = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(p) + (size_t)l * a.packed_stride); };
-  auto layer_p = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(p) + (size_t)l * a.plain_stride); };
+  auto layer_w = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(global(p)) + (size_t)l * now()->packed_stride); };
+  auto layer_p = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(global(p)) + (size_t)l * now()->plain_stride); };
 
   // ---- rows: all threads bring the residual sums of all rows into us, then wavefront m normalises row m into xs
   int piece_row[CH], piece_col[CH], piece_at[CH];
@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   };
 
   // ======== the layers.  Every matrix slice is requested at least one exchange before it is multiplied.
-  load_units(wq, layer_w(a.Wqkv, 0), 3 * (D / 16));
+  load_units(wq, layer_w(now()->Wqkv, 0), 3 * (D / 16));
   for (int l = 0; l < a.layers; ++l) {
     // What is derived from a thread's place is derived anew in every layer instead of waiting in registers: without it d = 1024
     // spills (32 rows 204 -> 174 us a step's layers); d = 512 gains 2 %, d = 768 would lose 2 %.
@@ -377,11 +377,11 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(lane16), "+v"(lane_nt), "+v"(lane_qt));
       asm volatile("" : "+v"(gk), "+v"(c8), "+v"(jfirst));
     }
-    half_t* Kc = reinterpret_cast<half_t*>(a.cache + (size_t)(2 * l) * a.cache_stride);
-    half_t* Vc = reinterpret_cast<half_t*>(a.cache + (size_t)(2 * l + 1) * a.cache_stride);
+    half_t* Kc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l) * now()->cache_stride);
+    half_t* Vc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l + 1) * now()->cache_stride);
     // A. the layer's input rows; q, k, v
     const int qi = tid >> 6, qm = (tid >> 3) & 7, qn = (tid & 7) * 2;   // unit, row, pair of columns this thread finishes
-    const half_t* bq3 = layer_p(a.bqkv, l);
+    const half_t* bq3 = layer_p(now()->bqkv, l);
     half2_t qb = {0, 0};
     const int qcol = (j + W * qi) * 16 + qn;
     const bool qlive = qi < UQ && qcol < 3 * D && qm < rows;
@@ -404,13 +404,13 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       }
       __syncthreads();
     } else {
-      if constexpr (PRE) gather_norm(l - 1, Rg::u3, layer_p(a.ln1g, l), layer_p(a.ln1b, l), nullptr, nullptr);
-      else gather_norm(l - 1, Rg::u3, layer_p(a.ln3g, l - 1), layer_p(a.ln3b, l - 1), nullptr, nullptr);
+      if constexpr (PRE) gather_norm(l - 1, Rg::u3, layer_p(now()->ln1g, l), layer_p(now()->ln1b, l), nullptr, nullptr);
+      else gather_norm(l - 1, Rg::u3, layer_p(now()->ln3g, l - 1), layer_p(now()->ln3b, l - 1), nullptr, nullptr);
     }
     multiply_units(wq);
-    load_cols(wo, layer_w(a.Wo, l), D, NT);
-    if constexpr (PRE) load_units(w1, layer_w(a.W1, l), 4 * (D / 16));
-    else load_cols(wc, layer_w(a.Wq, l), D, QT);
+    load_cols(wo, layer_w(now()->Wo, l), D, NT);
+    if constexpr (PRE) load_units(w1, layer_w(now()->W1, l), 4 * (D / 16));
+    else load_cols(wc, layer_w(now()->Wq, l), D, QT);
     pin();
     __syncthreads();
     if (qlive) {
@@ -425,23 +425,23 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     }
     // B, C. self-attention, its output projection
     attend(l, true, Kc, Vc, pos);
-    project(wo, l, Rg::ctx, false, Rg::u1, layer_p(a.bo, l), [&] {
-      if constexpr (PRE) load_cols(w2, layer_w(a.W2, l), 4 * D, NT);
-      else load_cols(we, layer_w(a.Woc, l), D, NT);
+    project(wo, l, Rg::ctx, false, Rg::u1, layer_p(now()->bo, l), [&] {
+      if constexpr (PRE) load_cols(w2, layer_w(now()->W2, l), 4 * D, NT);
+      else load_cols(we, layer_w(now()->Woc, l), D, NT);
     });
     if constexpr (!PRE) {
       // D. LayerNorm, query product of the cross-attention
       const int pm = tid / (QT / 2), pn = tid % (QT / 2) * 2;
       const bool plive = pm < rows && j * QT < D;
       half2_t pb = {0, 0};
-      if (plive) pb = bias_pair(layer_p(a.bq, l), j * QT + pn);
-      gather_norm(l, Rg::u1, layer_p(a.ln1g, l), layer_p(a.ln1b, l), nullptr, nullptr);
+      if (plive) pb = bias_pair(layer_p(now()->bq, l), j * QT + pn);
+      gather_norm(l, Rg::u1, layer_p(now()->ln1g, l), layer_p(now()->ln1b, l), nullptr, nullptr);
       floatx4 acc = zero4;
 #pragma unroll
       for (int s = 0; s < DK; ++s)
         acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wc[PRE ? 0 : s], *reinterpret_cast<const half8_t*>(&xs[fm][(wave * DK + s) * 32 + kc * 8]), acc, 0, 0, 0);
       if ((lane & 15) < kRows) *reinterpret_cast<floatx4*>(&part[wave][0][lane & 15][kc * 4]) = acc;
-      load_units(w1, layer_w(a.W1, l), 4 * (D / 16));
+      load_units(w1, layer_w(now()->W1, l), 4 * (D / 16));
       pin();
       __syncthreads();
       if (plive) {
@@ -450,15 +450,15 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
         ex.put2(at(l, Rg::q2) + j * rp * (QT * 2), pm * (QT * 2) + pn * 2, (half_t)(v0 + (float)pb[0]), (half_t)(v1 + (float)pb[1]));
       }
       // E, F. cross-attention, its output projection
-      const half_t* kvb = reinterpret_cast<const half_t*>(a.cross + (size_t)l * a.cross_stride) + (size_t)src_off * 2 * D;
+      const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
       attend(l, false, kvb, kvb + D, src_len);
-      project(we, l, Rg::ctx2, false, Rg::u2, layer_p(a.boc, l), [&] { load_cols(w2, layer_w(a.W2, l), 4 * D, NT); });
+      project(we, l, Rg::ctx2, false, Rg::u2, layer_p(now()->boc, l), [&] { load_cols(w2, layer_w(now()->W2, l), 4 * D, NT); });
     }
     // G. LayerNorm, first FFN product
     const int fcol = (j + W * qi) * 16 + qn;
     half2_t fb = {0, 0};
-    if (qi < NU && qm < rows) fb = bias_pair(layer_p(a.b1, l), fcol);
-    gather_norm(l, PRE ? Rg::u1 : Rg::u2, layer_p(a.ln2g, l), layer_p(a.ln2b, l), nullptr, nullptr);
+    if (qi < NU && qm < rows) fb = bias_pair(layer_p(now()->b1, l), fcol);
+    gather_norm(l, PRE ? Rg::u1 : Rg::u2, layer_p(now()->ln2g, l), layer_p(now()->ln2b, l), nullptr, nullptr);
     multiply_units(w1);
     __syncthreads();
     if (qi < NU && qm < rows) {
@@ -470,14 +470,14 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       ex.put2(at(l, Rg::ff) + j * rp * 32, (W * qi * rp + qm) * 32 + qn * 2, (half_t)v0, (half_t)v1);
     }
     // H. second FFN product
-    project(w2, l, Rg::ff, true, Rg::u3, layer_p(a.b2, l), [&] {
-      if (l + 1 < a.layers) load_units(wq, layer_w(a.Wqkv, l + 1), 3 * (D / 16));
+    project(w2, l, Rg::ff, true, Rg::u3, layer_p(now()->b2, l), [&] {
+      if (l + 1 < a.layers) load_units(wq, layer_w(now()->Wqkv, l + 1), 3 * (D / 16));
     });
   }
   // ======== the rows for the vocabulary product; everything else ends here
   if (j == 0) {
     if constexpr (PRE) gather_norm(a.layers - 1, Rg::u3, a.lnfg, a.lnfb, a.x_out, a.hidden);
-    else gather_norm(a.layers - 1, Rg::u3, layer_p(a.ln3g, a.layers - 1), layer_p(a.ln3b, a.layers - 1), nullptr, a.hidden);
+    else gather_norm(a.layers - 1, Rg::u3, layer_p(now()->ln3g, a.layers - 1), layer_p(now()->ln3b, a.layers - 1), nullptr, a.hidden);
   }
   {
     char* other = a.exchange + (size_t)(1 - parity) * a.set_bytes;

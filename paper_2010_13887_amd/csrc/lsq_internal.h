@@ -411,6 +411,18 @@ __device__ __forceinline__ void for_lane_bits(F&& f) {
   }
 }
 
+// The arguments of the running kernel (one struct) where they arrive.  A kernel with dozens of them reads those it needs
+// now and then from here, at the place of use: the compiler would keep them all in scalar registers from the start, and
+// spill.
+template <typename A>
+__device__ __forceinline__ const __attribute__((address_space(4))) A* arguments() {
+  auto p = (const __attribute__((address_space(4))) A*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+// a pointer that is known to lead to global memory
+template <typename U> __device__ __forceinline__ U* global(U* p) { return (U*)(__attribute__((address_space(1))) U*)p; }
+
 template <typename T> struct Vec8;
 template <> struct Vec8<half_t> {
   // the 16 bytes as they are in memory, for data that waits in registers before it is used
