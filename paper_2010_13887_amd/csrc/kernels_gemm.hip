@@ -9,16 +9,19 @@
 
 namespace lsq {
 
+// segment of column n (at most three: no division)
+__device__ __forceinline__ int segment_of(const GemmOut& o, int n) { return (n >= o.seg_n ? 1 : 0) + (n >= 2 * o.seg_n ? 1 : 0); }
+
 template <typename T>
 __device__ __forceinline__ void store_one(const GemmOut& o, int m, int n, float v, long tp) {
-  int s = n / o.seg_n;
+  int s = segment_of(o, n);
   reinterpret_cast<T*>(o.ptr[s])[(long)m * o.ld[s] + tp * o.tmul[s] + (n - s * o.seg_n)] = (T)v;
 }
 
 // Epilogue activation: 0 none, 1 ReLU, 2 tanh-GELU 0.5 x (1 + tanh(sqrt(2/pi) (x + 0.044715 x^3))).
 __device__ __forceinline__ float activate(float v, int act) {
   if (act == 1) return fmaxf(v, 0.f);
-  if (act == 2) return 0.5f * v * (1.0f + tanhf(0.7978845608028654f * (v + 0.044715f * v * v * v)));
+  if (act == 2) return tanh_gelu(v);
   return v;
 }
 
@@ -47,7 +50,7 @@ __device__ __forceinline__ void store4(const GemmOut& out, int m, int n, const f
     const float4_dword_aligned f = {v[0], v[1], v[2], v[3]};
     *reinterpret_cast<float4_dword_aligned*>(dst) = f;
   } else if (vec_ok == 1 && n + 3 < N) {
-    int s = n / out.seg_n;
+    int s = segment_of(out, n);
     OutT* dst = reinterpret_cast<OutT*>(out.ptr[s]) + (long)m * out.ld[s] + tp * out.tmul[s] + (n - s * out.seg_n);
     if constexpr (sizeof(OutT) == 2) {
       half4_t h = {(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
@@ -60,6 +63,51 @@ __device__ __forceinline__ void store4(const GemmOut& out, int m, int n, const f
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (n + e < N) store_one<OutT>(out, m, n + e, v[e], tp);
+  }
+}
+
+// A 32x32 accumulator block of a tile kernel, lane: row m = .. + (lane & 31), columns nb + 8 vg + 4 (lane >> 5) + 0..3; nb the
+// same in all lanes.  Where the block's columns lie in one segment its address is made once and the activation is chosen
+// once: with a segment and an activation looked up for every four values the epilogue of a 256x256 tile took 20 us.
+template <typename OutT, bool SPLIT>
+__device__ __forceinline__ void store_block(const GemmOut& out, int m, int nb, const floatx16& acc, const float (&bv)[4][4], int act,
+                                            int M, int N, int vec_ok, int slab, long tp) {
+  if (m >= M || nb >= N) return;
+  const int hf = ((int)threadIdx.x & 63) >> 5;
+  float v[4][4];
+#pragma unroll
+  for (int vg = 0; vg < 4; ++vg)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[vg][e] = acc[vg * 4 + e] + bv[vg][e];
+  if (act != 0) {
+    if (act == 1) {
+#pragma unroll
+      for (int vg = 0; vg < 4; ++vg)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[vg][e] = activate(v[vg][e], 1);
+    } else {
+#pragma unroll
+      for (int vg = 0; vg < 4; ++vg)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[vg][e] = activate(v[vg][e], 2);
+    }
+  }
+  const int s = segment_of(out, nb), n0 = s * out.seg_n;
+  if (vec_ok == 1 && (SPLIT || nb + 32 <= n0 + out.seg_n || n0 + out.seg_n >= N) && nb + 32 <= N) {
+    OutT* dst = SPLIT ? reinterpret_cast<OutT*>(out.ptr[0]) + ((size_t)slab * M + m) * N + nb
+                      : reinterpret_cast<OutT*>(out.ptr[s]) + tp * out.tmul[s] + (nb - n0) + (long)m * out.ld[s];
+    dst += hf * 4;
+#pragma unroll
+    for (int vg = 0; vg < 4; ++vg) {
+      if constexpr (sizeof(OutT) == 2) *reinterpret_cast<half4_t*>(dst + vg * 8) = half4_t{(half_t)v[vg][0], (half_t)v[vg][1], (half_t)v[vg][2], (half_t)v[vg][3]};
+      else *reinterpret_cast<floatx4*>(dst + vg * 8) = floatx4{v[vg][0], v[vg][1], v[vg][2], v[vg][3]};
+    }
+    return;
+  }
+#pragma unroll
+  for (int vg = 0; vg < 4; ++vg) {
+    const int n = nb + vg * 8 + hf * 4;
+    if (n < N) store4<OutT, SPLIT>(out, m, n, v[vg], M, N, vec_ok, slab, tp);
   }
 }
 
@@ -157,7 +205,7 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN) * KG) gemm_f16_kern
 
   const int tid = threadIdx.x, lane = tid & 63;
   constexpr int TILE_WAVES = (BM / WM) * (BN / WN);
-  const int wave = (tid >> 6) % TILE_WAVES, kgrp = (tid >> 6) / TILE_WAVES;   // wave tile, k-group
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wid % TILE_WAVES, kgrp = wid / TILE_WAVES;   // wave tile, k-group
   const long tp = tpos ? *tpos : 0;   // the counter's address is among the first arguments: requested at once, awaited by the epilogue
   const int mt = (M + BM - 1) / BM, nt = (N + BN - 1) / BN, total = mt * nt;
   int id = blockIdx.x;
@@ -340,24 +388,10 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN) * KG) gemm_f16_kern
 
   // epilogue: lane owns m = .. + (lane & 31) and, per group vg, n = .. + vg*8 + (lane>>5)*4 + 0..3
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = m0 + wm + i * 32 + (lane & 31);
-    if (m >= M) continue;
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int vg = 0; vg < 4; ++vg) {
-        const int n = n0 + wn + j * 32 + vg * 8 + (lane >> 5) * 4;
-        if (n >= N) continue;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[e] = activate(acc[i][j][vg * 4 + e] + bv[j][vg][e], act);
-        }
-        store4<OutT, SPLIT>(out, m, n, v, M, N, vec_ok, (int)blockIdx.y, tp);
-      }
-    }
-  }
+    for (int j = 0; j < TN; ++j)
+      store_block<OutT, SPLIT>(out, m0 + wm + i * 32 + (lane & 31), n0 + wn + j * 32, acc[i][j], bv[j], act, M, N, vec_ok, (int)blockIdx.y, tp);
   if constexpr (std::is_same<OutT, float>::value && !SPLIT) {
     // (largest, sum of exponentials) of every (row, 32-column group), as in the large-tile kernel below: a 32x32
     // block holds a group's 32 columns of a row in the two lanes (m, half 0) and (m, half 1)
@@ -527,17 +561,7 @@ __global__ void __launch_bounds__(64 * (BM / 32) * (BN / 32)) gemm_f16_direct_ke
 #undef LSQ_WAIT_VM
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] += acc2[e];
-  const int m = m0 + wm + (lane & 31);
-  if (m >= M) return;
-#pragma unroll
-  for (int vg = 0; vg < 4; ++vg) {
-    const int n = n0 + wn + vg * 8 + (lane >> 5) * 4;
-    if (n >= N) continue;
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = activate(acc[vg * 4 + e] + bv[vg][e], act);
-    store4<OutT, SPLIT>(out, m, n, v, M, N, vec_ok, (int)blockIdx.y, tp);
-  }
+  store_block<OutT, SPLIT>(out, m0 + wm + (lane & 31), n0 + wn, acc, bv, act, M, N, vec_ok, (int)blockIdx.y, tp);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -550,7 +574,7 @@ __global__ void __launch_bounds__(64 * (BM / 32) * (BN / 32)) gemm_f16_direct_ke
 // 256x256 tiles of eight 128x64 wave tiles -- 96 B of LDS reads per clock and CU at full matrix-core rate
 // instead of 192 -- 870-920).  K a multiple of BK; D register stages of global loads.
 template <int BM, int BN, int BK, int WM, int WN, int D, typename OutT>
-__global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN)) gemm_f16_large_kernel(const half_t* __restrict__ A, const half_t* __restrict__ B,
+__global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), BM * BN <= 128 * 128 && sizeof(OutT) == 2 ? 4 : 2) gemm_f16_large_kernel(const half_t* __restrict__ A, const half_t* __restrict__ B,
                                                        int M, int N, int K, const int32_t* __restrict__ tpos,
                                                        const half_t* __restrict__ bias, int act, int vec_ok,
                                                        GemmOut out) {
@@ -565,12 +589,16 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN)) gemm_f16_large_ker
   extern __shared__ __attribute__((aligned(16))) half_t lds_tiles[];
   half_t(*As)[BM * LDK] = reinterpret_cast<half_t(*)[BM * LDK]>(lds_tiles);
   half_t(*Bs)[BN * LDK] = reinterpret_cast<half_t(*)[BN * LDK]>(lds_tiles + 2 * BM * LDK);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const long tp = tpos ? *tpos : 0;
   const int mt = (M + BM - 1) / BM, nt = (N + BN - 1) / BN, total = mt * nt;
-  int id = blockIdx.x;
-  if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
-  const int m0 = (id % mt) * BM, n0 = (id / mt) * BN;
+  // Tiles of one XCD (workgroups 8 apart) are neighbours: consecutive ids run down 8 row tiles, then on to the next column
+  // tile, so that the XCD's L2 keeps those 8 row tiles while the columns pass by.
+  // (4096^3 166 -> 150 us)
+  const int xcd = (int)blockIdx.x & 7;
+  const int id = xcd * (total >> 3) + min(xcd, total & 7) + ((int)blockIdx.x >> 3);
+  const int first = id / (8 * nt) * 8, deep = min(8, mt - first), in = id - first * nt;
+  const int m0 = (first + in % deep) * BM, n0 = in / deep * BN;
   const int wm = (wave / WAVES_N) * WM, wn = (wave % WAVES_N) * WN;
   const int nk = K / BK;
   half8_t ra[D][AV], rb[D][BV];
@@ -673,22 +701,10 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN)) gemm_f16_large_ker
   }
   if (BIAS_LATE) load_bias();
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = m0 + wm + i * 32 + (lane & 31);
-    if (m >= M) continue;
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int vg = 0; vg < 4; ++vg) {
-        const int n = n0 + wn + j * 32 + vg * 8 + (lane >> 5) * 4;
-        if (n >= N) continue;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = activate(acc[i][j][vg * 4 + e] + bv[j][vg][e], act);
-        store4<OutT, false>(out, m, n, v, M, N, vec_ok, 0, tp);
-      }
-    }
-  }
+    for (int j = 0; j < TN; ++j)
+      store_block<OutT, false>(out, m0 + wm + i * 32 + (lane & 31), n0 + wn + j * 32, acc[i][j], bv[j], act, M, N, vec_ok, 0, tp);
   if constexpr (std::is_same<OutT, float>::value) {
     // (largest, sum of exponentials) of every (row, 32-column group): a wave tile holds a group's 32 columns of a
     // row in the two lanes (m, half 0) and (m, half 1)
@@ -1294,6 +1310,37 @@ bool gemm_writes_stats(int dtype, int M, int N, int K) {
   return M > 0 && N > 0 && K > 0 && K % 8 == 0;
 }
 
+// Products of 200 and more 128x128 tiles: which tiles.  256x256 (144 KB of LDS, eight wavefronts of 128x64) need the fewest LDS
+// reads per FLOP, 256x128 and 128x128 some 10 and 15 % more time per FLOP; but a last round of workgroups that leaves most
+// CUs idle costs as much as a full one.  So: the largest (share of the rounds' capacity that is work) x (rate of the tile).
+// Where that is below 0.9, the rows that fill whole rounds of 256x256 tiles go first, the rest as a product of its own.
+// Measured, us, 256x256 / 256x128 / 128x128: 7648 x 3072 x 768 73 / 70 / 72 (in two parts 66), 7648 x 768 x 3072 82 / 54 / 64 (float output), 3600 x
+// 4096 x 1024 53 / 60 / 57, 3600 x 1024 x 1024 34 / 22 / 17 (float), 32000 columns x 1024: 512 rows 55 / 59 / 65, 256 rows 47 / 31 / 35;
+// 7648 x 2304 x 768 65 / 64 / 58, in two parts 53.
+static hipError_t launch_large(const half_t* a, const half_t* b, const half_t* bi, const GemmOut& out, int M, int N, int K, int act,
+                               int vec_ok, hipStream_t s) {
+  auto share = [&](int bm, int bn, int slots) {
+    const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn), rounds = (tiles + slots - 1) / slots;
+    return (double)M * N / ((double)rounds * slots * bm * bn);
+  };
+  const double s256 = share(256, 256, 256), s2x1 = 0.9 * share(256, 128, 256), s128 = 0.85 * share(128, 128, out.f32_out ? 256 : 512);
+  const int nt = (N + 255) / 256;
+  const long whole = (long)((M + 255) / 256) * nt / 256 * 256;   // workgroups of the full rounds
+  const int first = (int)(whole / nt) * 256;                     // rows they take
+  if (s256 < 0.9 && s2x1 < 0.9 && s128 < 0.9 && first > 0 && first < M) {
+    GemmOut rest = out;
+    const int nseg = (N + out.seg_n - 1) / out.seg_n;
+    for (int i = 0; i < nseg; ++i) rest.ptr[i] = (char*)out.ptr[i] + (size_t)first * out.ld[i] * (out.f32_out ? 4 : 2);
+    if (out.stats) rest.stats = out.stats + (size_t)first * out.stats_groups * 2;
+    run_f16_large<256, 256, 64, 128, 64>(a, b, bi, out, first, N, K, act, vec_ok, s);
+    return launch_gemm(DT_F16, a + (size_t)first * K, b, bi, rest, M - first, N, K, act, s);
+  }
+  if (s256 >= s2x1 && s256 >= s128) run_f16_large<256, 256, 64, 128, 64>(a, b, bi, out, M, N, K, act, vec_ok, s);
+  else if (s2x1 >= s128) run_f16_large<256, 128, 64, 64, 64>(a, b, bi, out, M, N, K, act, vec_ok, s);
+  else run_f16_large<128, 128, 64, 64, 32>(a, b, bi, out, M, N, K, act, vec_ok, s);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm(int dtype, const void* A, const void* B, const void* bias, const GemmOut& out, int M,
                        int N, int K, int act /* activation: 0 none, 1 ReLU, 2 tanh-GELU */, hipStream_t s,
                        bool b_packed) {
@@ -1357,14 +1404,8 @@ hipError_t launch_gemm(int dtype, const void* A, const void* B, const void* bias
   else if (M <= 64 && wide)
     run_f16<64, 128, 64, 32, 32, 4>(a, b, bi, out, M, N, K, act, vec_ok, s);
   else if (tiles128 >= 200 && K % 64 == 0) {
-    // enough 128x128 tiles to fill the chip (vocabulary product from 65 rows up, encoder and prefill
-    // layers).  256x256 tiles (144 KB of LDS, eight wavefronts of 128x64) once there are about as many of
-    // those as CUs and more: half the LDS reads per FLOP (vocabulary product at 512 rows 54 -> 48 us,
-    // 4096^3 613 -> 870 TFLOP/s); otherwise 128x128 tiles (72 KB, two workgroups per CU, eight wavefronts
-    // of 64x32)
-    const long tiles256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-    if (tiles256 >= 256) run_f16_large<256, 256, 64, 128, 64>(a, b, bi, out, M, N, K, act, vec_ok, s);
-    else run_f16_large<128, 128, 64, 64, 32>(a, b, bi, out, M, N, K, act, vec_ok, s);
+    // enough 128x128 tiles to fill the chip (vocabulary product from 65 rows up, encoder and prefill layers)
+    return launch_large(a, b, bi, out, M, N, K, act, vec_ok, s);
   } else if (tiles128 >= 200)
     run_f16<128, 128, 64, 64, 32, 2>(a, b, bi, out, M, N, K, act, vec_ok, s);   // ragged k
   else if ((long)((M + 63) / 64) * ((N + 63) / 64) > 256) {

@@ -35,10 +35,6 @@ template <bool PRE> struct Region {
   static constexpr int ff = PRE ? 10 : 20, u3 = PRE ? 18 : 28, size = PRE ? 20 : 32;
 };
 
-__device__ __forceinline__ float tanh_gelu(float v) {
-  return 0.5f * v * (1.0f + tanhf(0.7978845608028654f * (v + 0.044715f * v * v * v)));
-}
-
 // DK: d / 256.  X: workgroups of a group per 16 columns of d (W = d / 16 * X): the products with d columns take 16 / X
 // columns per workgroup, those with 3d and 4d columns ceil(3 / X) and 4 / X units of 16.  PRE: pre-LN, no cross-attention.
 //

@@ -411,6 +411,12 @@ __device__ __forceinline__ void for_lane_bits(F&& f) {
   }
 }
 
+// 0.5 v (1 + tanh(u)), u = sqrt(2/pi) (v + 0.044715 v^3), as v / (1 + exp(-2u)): the same function without the cancellation
+// at negative v, and a tenth of the instructions of a tanh (256x256 tiles of an FFN product spent 10 of 40 us in it).
+__device__ __forceinline__ float tanh_gelu(float v) {
+  return v * __builtin_amdgcn_rcpf(1.0f + __expf(-1.5957691216057308f * (v + 0.044715f * v * v * v)));
+}
+
 // The arguments of the running kernel (one struct) where they arrive.  A kernel with dozens of them reads those it needs
 // now and then from here, at the place of use: the compiler would keep them all in scalar registers from the start, and
 // spill.

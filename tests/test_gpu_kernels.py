@@ -95,6 +95,22 @@ def test_gemm_gelu(env, M, N, K, half):
     np.testing.assert_allclose(C.cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
 
 
+@pytest.mark.parametrize("M,N,K", [(7393, 2304, 64), (7300, 2290, 128), (3000, 777, 64), (250, 32001, 64), (4096, 4090, 192)])
+@pytest.mark.parametrize("half_out", [False, True])
+def test_gemm_large_tiles(env, M, N, K, half_out):
+    """Products of hundreds of tiles: in two parts (full rounds of 256x256 tiles, then the other rows), 256x128 and 256x256
+    tiles, ragged rows and columns; the k-loop's shortest lengths."""
+    lsq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A = torch.randn(M, K, device="cuda", generator=g).half()
+    B = (torch.randn(N, K, device="cuda", generator=g) * 0.05).half()
+    bias = torch.randn(N, device="cuda", generator=g).half()
+    C = torch.empty(M, N, dtype=torch.float16 if half_out else torch.float32, device="cuda")
+    lsq.k_gemm(A, B, bias, C, relu=True)
+    ref = torch.relu(A.double() @ B.double().t() + bias.double())
+    assert ((C.double() - ref).abs() <= (1e-3 if half_out else 2e-6) * ref.abs() + 2e-5).all()
+
+
 @pytest.mark.parametrize("rows,d,K", [(1, 64, 64), (5, 512, 2048), (513, 1024, 1024), (512, 1024, 4096),
                                       (37, 2048, 264), (64, 1024, 4096), (9, 72, 40), (4, 100, 16), (3, 4104, 128)])
 @pytest.mark.parametrize("half", [False, True])
