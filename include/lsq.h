@@ -107,6 +107,11 @@ int lsq_decode_step(void);
  * finished leave the state unchanged. */
 int lsq_decode_steps(int n);
 
+/* Steps until nothing is unfinished (0), with a wait for the count of unfinished sentences after every n steps.
+ * n = 1: the next step is queued before the wait for the one before it, so that the device does not idle while
+ * the host reads a count (5 us of 119 a step); at most one step is issued after everything finished. */
+int lsq_decode_all(int n);
+
 /* Copies the hypotheses out, best first per sentence by length-normalised
  * score = score / len^alpha.  All outputs are host memory:
  * out_ids int32 [batch, beam, max_len] (tokens after BOS, through EOS if one

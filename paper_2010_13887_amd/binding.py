@@ -45,6 +45,7 @@ def load_library() -> C.CDLL:
         "lsq_encode": [vp, vp, i32, i32],
         "lsq_decode_step": [],
         "lsq_decode_steps": [i32],
+        "lsq_decode_all": [i32],
         "lsq_get_beams": [vp, vp, vp],
         "lsq_step_index": [],
         "lsq_set_graphs": [i32],
@@ -145,6 +146,10 @@ def lsq_decode_step() -> int:
 
 def lsq_decode_steps(n: int) -> int:
     return _check(load_library().lsq_decode_steps(n))
+
+
+def lsq_decode_all(n: int) -> int:
+    return _check(load_library().lsq_decode_all(n))
 
 
 def lsq_set_graphs(on: bool) -> None:
@@ -470,8 +475,7 @@ class Engine:
 
     def translate(self, src_ids, src_lens, sync_every: int = 1):
         self.encode(src_ids, src_lens)
-        while self.decode_steps(sync_every) > 0:
-            pass
+        lsq_decode_all(sync_every)
         return self.get_beams()
 
     def close(self) -> None:

@@ -921,7 +921,7 @@ int read_active(int steps, int* out) {
   const volatile unsigned long long* word = &g.page->step;
   for (unsigned spin = 1;; ++spin) {
     const unsigned long long v = *word;
-    if ((int)(v >> 32) == steps) { *out = (int)(v & 0xFFFFFFFFu); return stack_waits_ended(); }
+    if ((int)(v >> 32) >= steps) { *out = (int)(v & 0xFFFFFFFFu); return stack_waits_ended(); }
     if (spin % 65536 == 0) {
       const hipError_t e = hipStreamQuery(g.stream);
       if (e != hipErrorNotReady) {
@@ -1323,6 +1323,26 @@ int lsq_decode_steps(int n) {
   if (rc) return rc;
   if (active == 0) g.done = true;
   return active;
+}
+
+int lsq_decode_all(int n) {
+  if (g.state < 3) return fail(LSQ_E_STATE, "lsq_encode has not been called");
+  if (n < 1) return fail(LSQ_E_ARG, "n must be positive");
+  auto more = [] { return g.t < g.max_len && g.alive_at[g.t] > 0; };
+  const int ahead = n == 1 ? 1 : 0;
+  for (int seen = g.t; !g.done && (more() || seen < g.t);) {   // the count after `seen` steps is known
+    const int next = std::min(seen + n, g.max_len);
+    while (g.t < next + ahead && more()) {
+      int rc = enqueue_step();
+      if (rc) return rc;
+    }
+    seen = std::min(next, g.t);
+    int active = 0;
+    int rc = read_active(seen, &active);
+    if (rc) return rc;
+    if (active == 0) g.done = true;
+  }
+  return 0;
 }
 
 int lsq_profile_enable(int on) {
