@@ -720,12 +720,13 @@ static int cross_q_group(int batch, int H) {
   return GS;
 }
 
-// Ahead of the two separate launches from 256 rows on, and below that where its workgroups, of at least two sentences
-// each, fill the CUs in one round (whole translations, 16 heads of the big model: 32 sentences = 256 workgroups
-// 46.2 -> 45.4 ms, 30 and 28 sentences level, 48 sentences = 384 workgroups 51.9 -> 54.4 ms, 20 sentences level;
-// 8 heads of d = 512, 32 sentences = 256 workgroups of one sentence: 34.7 -> 34.8 ms).
+// Ahead of the two separate launches where its workgroups, of at least two sentences each, fill the CUs in one round (whole
+// translations, 16 heads of the big model: 32 sentences = 256 workgroups 46.2 -> 45.4 ms, 30 and 28 sentences level, 48
+// sentences = 384 workgroups 51.9 -> 54.4 ms, 20 sentences level; 8 heads of d = 512, 32 sentences = 256 workgroups of one
+// sentence: 34.7 -> 34.8 ms), but not above 256 rows (128 sentences of equal length level, of mixed lengths 67.5 -> 68.3 ms, d = 512,
+// 100 sentences 38.7 -> 42.0: a workgroup waits for its longest sentence).
 bool cross_attention_q_worthwhile(int batch, int beam, int H) {
-  if (batch * beam >= 256) return true;
+  if (batch * beam > 256) return false;
   const int GS = cross_q_group(batch, H);
   const long wgs = (long)((batch + GS - 1) / GS) * H;
   return GS >= 2 && wgs >= 240 && wgs <= 256;
