@@ -27,7 +27,7 @@ __global__ void __launch_bounds__(256) embed_last_kernel(const T* __restrict__ E
   int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
   const int t = *tp;   // decode-step counter, kept on the device
-  int id = tokens[(size_t)r * T1 + len[r]];
+  const int id = embedding_row(tokens[(size_t)r * T1 + len[r]]);
   embed_row<T>(E + (size_t)id * d, pe + (size_t)t * d, x + (size_t)r * d, d, scale, threadIdx.x & 63, 64);
 }
 
@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(64) embed_layernorm_kernel(const T* __restrict
   const int r = blockIdx.x, lane = threadIdx.x;
   if (r >= rows) return;
   const int t = *tp;
-  const int id = tokens[(size_t)r * T1 + len[r]];
+  const int id = embedding_row(tokens[(size_t)r * T1 + len[r]]);
   const T* e = E + (size_t)id * d;
   const float* per = pe + (size_t)t * d;
   float v[NV][8], gv[NV][8], bv[NV][8];

@@ -388,7 +388,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
         if constexpr (PRE) {
           half8_t g8[NV], b8[NV];
           load_gain(g8, b8, a.ln1g, a.ln1b);
-          const half_t* e = a.E + (size_t)a.tokens[(size_t)r * (a.T + 1) + a.len[r]] * D;
+          const half_t* e = a.E + (size_t)embedding_row(a.tokens[(size_t)r * (a.T + 1) + a.len[r]]) * D;
           embed_row<half_t>(e, a.pe + (size_t)pos * D, us[wave], D, 1.0f, lane, 64);
           normalise(g8, b8, nullptr, nullptr);   // reads what this wavefront wrote
         } else {
@@ -891,7 +891,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
         half4_t h = {};
         if constexpr (PRE) {
           const half4_t g4 = half4_at(a.ln1g, oc), b4 = half4_at(a.ln1b, oc);
-          const half4_t e4 = half4_at(a.E + (size_t)a.tokens[(size_t)r * (a.T + 1) + a.len[r]] * D, oc);
+          const half4_t e4 = half4_at(a.E + (size_t)embedding_row(a.tokens[(size_t)r * (a.T + 1) + a.len[r]]) * D, oc);
           const floatx4 p4 = *reinterpret_cast<const floatx4*>(a.pe + (size_t)pos * D + oc);
           float v[4];
 #pragma unroll

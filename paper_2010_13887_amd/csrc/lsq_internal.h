@@ -474,6 +474,9 @@ template <> struct Vec8<float> {
   }
 };
 
+// The embedding row of a token.  A sampled row without candidates (all of its logits NaN) appends -1; it reads row 0.
+__device__ __forceinline__ int embedding_row(int token) { return max(token, 0); }
+
 // x[r,:] = store(E[id_r,:] * sqrt(d) + PE[pos_r,:]).  Product and sum are rounded separately
 // (no fused multiply-add) so the fp32 value before storage is the textbook one.
 template <typename T>

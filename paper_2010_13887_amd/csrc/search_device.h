@@ -201,7 +201,7 @@ __device__ __forceinline__ void next_input_rows(const NextInput& nx, const int* 
       const int i = min(idx, total - 1) / cpr;
       col[u] = (min(idx, total - 1) - i * cpr) * 8;
       row[u] = (idx < total && tok[i] >= 0) ? base + i : -1;
-      e[u] = Vec8<T>::load_raw(E + (size_t)max(tok[i], 0) * d + col[u]);
+      e[u] = Vec8<T>::load_raw(E + (size_t)embedding_row(tok[i]) * d + col[u]);
       pa[u] = *reinterpret_cast<const floatx4*>(pe + col[u]);
       pb[u] = *reinterpret_cast<const floatx4*>(pe + col[u] + 4);
     }
@@ -339,7 +339,7 @@ __device__ __forceinline__ void retrieve_rerank_sentence(
     const unsigned row_bytes = (unsigned)nx.d * (nx.dtype == DT_F16 ? 2 : 4);
     for (int i = lane >> 4; i < k; i += 4)
       for (unsigned o = (lane & 15) * 128; o < row_bytes; o += 2048)
-        touched += *reinterpret_cast<const int*>(reinterpret_cast<const char*>(nx.E) + (size_t)max(sh.cand_i[wave * k + i], 0) * row_bytes + o);
+        touched += *reinterpret_cast<const int*>(reinterpret_cast<const char*>(nx.E) + (size_t)embedding_row(sh.cand_i[wave * k + i]) * row_bytes + o);
   }
   const int t = st.t, cl = min(lane, kk - 1), j = cl / k;
   const float s = lane < kk ? sh.cand_s[cl] : -INFINITY;

@@ -146,3 +146,42 @@ def test_decoder_stack_matches_oracle(lsq, d, batch):
         one, two = (eng.translate(w.src_ids, w.src_lens, sync_every=n) for n in (1, 4))
         assert all(np.array_equal(a, b) for a, b in zip(one, two))
         assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("d,batch,fusion", [(256, 2, True), (512, 12, True), (128, 3, True), (128, 3, False)])
+def test_row_without_candidates_reads_a_row_of_the_embedding(lsq, d, batch, fusion):
+    """Logits that are all NaN leave a sampled row without candidates: it appends -1, and its next decoder input comes from
+    embedding row 0, not from the memory before the table (the stack kernels, embedding with and without LayerNorm).
+    The workspace starts inside a larger allocation, so that what lies before the table is known."""
+    import torch
+    P = 5
+    hp = S.HParams(arch=1, n_enc=0, n_dec=1, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=301, max_pos=16, act=1, norm=1,
+                   dtype=1, sample_topk=4, cap_extra=4)
+    w = S.custom(hp, [P] * batch, beam=1, max_len=P + 4, std=0.05)
+    rng = np.random.default_rng(d)
+    t = {n: rng.standard_normal(s).astype(np.float16) * np.float16(0.25) for n, s in S.tensor_list(hp)
+         if n in ("E", "P", "dec0.Wqkv", "dec0.bqkv", "dec0.ln1_g", "dec0.ln1_b")}
+    blob = S.make_blob(hp, std=0.05, overrides={**t, "lnf_g": np.full(d, np.nan)})
+    n = lsq.lsq_workspace_bytes(blob, batch, 1, w.max_len)
+    before = 4096
+    memory = torch.full((before // 2 + (n + 1) // 2,), 3.0, dtype=torch.float16, device="cuda:0")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    lsq.lsq_set_workspace(memory.data_ptr() + before, n, stream.cuda_stream)
+    try:
+        lsq.lsq_init(blob, batch, 1, w.max_len)
+        lsq.lsq_set_layernorm_fusion(fusion)
+        lsq.lsq_encode(w.src_ids, w.src_lens)
+        assert lsq.lsq_decode_steps(2) == batch
+        tokens = lsq.lsq_debug_read(lsq.DBG.TOKENS, (batch, w.max_len + 1), np.int32)
+        assert (tokens[:, P:P + 2] == -1).all()
+        K = lsq.lsq_debug_read(lsq.DBG.CACHE_K, (batch, w.max_len, d))[:, P]
+    finally:
+        lsq.lsq_free()
+        lsq.lsq_set_layernorm_fusion(True)
+    f = {k: v.astype(np.float64) for k, v in t.items()}
+    x = f["E"][0] + f["P"][P]
+    y = (x - x.mean()) / np.sqrt(x.var() + 1e-5) * f["dec0.ln1_g"] + f["dec0.ln1_b"]
+    want = (y @ f["dec0.Wqkv"] + f["dec0.bqkv"])[d:2 * d]
+    # float16 input rows and results: 3 roundings of 2^-11 in the row, averaged over d products, one in the result
+    np.testing.assert_allclose(K, np.broadcast_to(want, K.shape), rtol=0, atol=2e-3 * np.abs(want).max())
