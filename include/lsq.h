@@ -195,6 +195,10 @@ int lsq_set_diversity(int groups, float strength);
 int lsq_set_canaries(int on);
 int lsq_debug_check_canaries(void);
 
+/* Test hook: the kernels that run all decoder layers of a step in one launch behave, from the next one on, as after a wait
+ * that ran out (every wait looks once and goes on).  Enqueued on the stream. */
+int lsq_debug_end_stack_waits(void);
+
 /* Number of decode steps taken since the last lsq_encode. */
 int lsq_step_index(void);
 

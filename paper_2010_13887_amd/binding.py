@@ -56,6 +56,7 @@ def load_library() -> C.CDLL:
         "lsq_set_topk_statistics": [i32],
         "lsq_set_canaries": [i32],
         "lsq_debug_check_canaries": [],
+        "lsq_debug_end_stack_waits": [],
         "lsq_k_layernorm_gemm": [i32, vp, i32, vp, vp, vp, vp, vp, C.c_float, vp, vp, vp, i32, i32, i32, i32, vp],
         "lsq_k_layernorm_cross_attention": [vp, i32, vp, vp, vp, vp, vp, C.c_float, vp, vp, vp, vp, vp, vp, i32, i32, i32,
                                             i32, vp],
@@ -180,6 +181,11 @@ def lsq_set_canaries(on: bool) -> None:
 def lsq_debug_check_canaries() -> int:
     """How many red zones have been written to (0 = none)."""
     return _check(load_library().lsq_debug_check_canaries())
+
+
+def lsq_debug_end_stack_waits() -> None:
+    """The decoder stack kernels behave from the next launch on as after a wait that ran out (test hook)."""
+    _check(load_library().lsq_debug_end_stack_waits())
 
 
 def lsq_set_diversity(groups: int = 1, strength: float = 0.0) -> None:

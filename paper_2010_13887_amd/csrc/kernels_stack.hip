@@ -18,7 +18,8 @@
 // the same XCD (blockIdx % 8), so that the groups share the weights they stream through that XCD's L2.
 //
 // All workgroups must be resident at once: the launcher checks the occupancy, and every wait is bounded (kSpinLimit
-// polls, then the error flag is set, nothing is waited for any more and the launch runs to its end).
+// polls, then the error flag is set, nothing is waited for any more, and this launch and those queued behind it run to their
+// end).
 #include "stack_exchange.h"
 
 namespace lsq {
@@ -69,8 +70,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
 
   Exchange ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
-  ex.error = a.error;
-  ex.dead = false;
+  ex.dead = a.state[kGaveUp] != 0;
   const int row_bytes = a.layers * Rg::size * D;
   const int rp = max(a.rows_per_group, kMinRows);   // rows a writer's piece has room for
   auto at = [&](int l, int region) { return (grp * row_bytes + (l * Rg::size + region) * D) * rp; };
@@ -481,6 +481,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
     for (size_t i = (size_t)bid * kThreads + tid; i < n16; i += (size_t)gridDim.x * kThreads) reinterpret_cast<u32x4*>(other)[i] = s4;
   }
+  ex.report(a.state, a.error);
   if (tid == 0) {   // the last workgroup to get here: all have read the counters
     const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n == (int)gridDim.x - 1) {
@@ -539,8 +540,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
 
   Exchange ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange, (short)0, (int)(2 * a.set_bytes), 0x00027000);
-  ex.error = a.error;
-  ex.dead = false;
+  ex.dead = a.state[kGaveUp] != 0;
   const int group_bytes = Rg::size * D * rp;
   auto at = [&](int l, int region) { return ((start + l) & 1) * (int)a.set_bytes + grp * group_bytes + region * D * rp; };
   const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
@@ -991,6 +991,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   const int last = a.layers - 1;
   if constexpr (PRE) own_norm(last, Rg::fs, layer_p(a.b2, last), a.lnfg, a.lnfb, last, -1, a.x_out, a.hidden);
   else own_norm(last, Rg::fs, layer_p(a.b2, last), layer_p(a.ln3g, last), layer_p(a.ln3b, last), last, -1, nullptr, a.hidden);
+  ex.report(a.state, a.error);
   if (tid == 0) {   // the last workgroup to get here: all have read the counters
     const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n == (int)gridDim.x - 1) {
@@ -1081,6 +1082,8 @@ hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipS
   hipError_t e = hipMemsetAsync(exchange, 0xFF, bytes, s);
   return e == hipSuccess ? hipMemsetAsync(state, 0, 8 * 4, s) : e;
 }
+
+hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s) { return hipMemsetD32Async((hipDeviceptr_t)(state + kGaveUp), 1, 1, s); }
 
 hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s) {
   const Choice c = choose_rows(args.M, d);

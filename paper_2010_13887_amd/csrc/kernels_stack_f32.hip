@@ -60,8 +60,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
 
   Exchange ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange, (short)0, (int)(2 * a.set_bytes), 0x00027000);
-  ex.error = a.error;
-  ex.dead = false;
+  ex.dead = a.state[kGaveUp] != 0;
   const int group_bytes = Rg::size * D * rp;
   auto at = [&](int l, int region) { return ((start + l) & 1) * (int)a.set_bytes + grp * group_bytes + region * D * rp; };
   const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
@@ -391,6 +390,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
   }
   const int last = a.layers - 1;
   own_norm(last, Rg::fs, layer_p(a.b2, last), layer_p(a.ln3g, last), layer_p(a.ln3b, last), last, -1, reinterpret_cast<float*>(a.hidden));
+  ex.report(a.state, a.error);
   if (tid == 0) {   // the last workgroup to get here: all have read the counters
     const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n == (int)gridDim.x - 1) {

@@ -179,7 +179,8 @@ struct StackArgs {
   char* exchange;           // two sets of set_bytes each
   size_t set_bytes;
   int32_t* state;           // few rows: [0] launches so far, [1 + p] rows of set p to be refilled, [4] arrivals; many:
-                            // [0] slot of the next layer, [1] bytes of the other one to be refilled, [4] arrivals
+                            // [0] slot of the next layer, [1] bytes of the other one to be refilled, [4] arrivals;
+                            // both: [5] a wait ran out
   int* error;               // pinned host memory: set when a wait ran out
   int M, beam, layers, T, anc_ld;
   float eps;
@@ -190,6 +191,7 @@ bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers)
 enum StackKind { kStackNone, kStackFew, kStackMany, kStackF32 };
 StackKind stack_kind(int arch, int M, int d);   // of a supported shape: which kernel takes these rows on the current device
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init
+hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s);   // as if a wait had run out
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
 size_t stack_rows_bytes(int arch, int M, int d);   // of one set
 hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s);

@@ -1449,6 +1449,14 @@ int lsq_debug_check_canaries(void) {
   return damaged;
 }
 
+int lsq_debug_end_stack_waits(void) {
+  if (g.state < 2) return fail(LSQ_E_STATE, "lsq_init has not been called");
+  if (!g.stack_ok) return LSQ_OK;
+  HIPCHK(launch_stack_end_waits(at<int32_t>(g.plan.stack_state), g.stream));
+  HIPCHK(launch_stack_end_waits(at<int32_t>(g.plan.stack_state) + 8, g.stream));
+  return LSQ_OK;
+}
+
 int lsq_get_beams(int32_t* out_ids, int32_t* out_lens, float* out_scores) {
   if (g.state < 3) return fail(LSQ_E_STATE, "lsq_encode has not been called");
   if (!out_ids || !out_lens || !out_scores) return fail(LSQ_E_ARG, "an output pointer is null");

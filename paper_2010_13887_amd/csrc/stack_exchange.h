@@ -22,10 +22,13 @@ __device__ __forceinline__ unsigned publish_word(unsigned v) { return v == kSent
 // up to 1 % by it and keep theirs.
 __device__ __forceinline__ const __attribute__((address_space(4))) StackArgs* now() { return arguments<StackArgs>(); }
 
+// The word of StackArgs::state that is set at the end of a launch in which a wait ran out.  A launch that finds it set looks
+// once where it would wait: the steps queued behind the one that gave up end at once instead of each waiting out the limit.
+constexpr int kGaveUp = 5;
+
 struct Exchange {
   __amdgpu_buffer_rsrc_t rsrc;
-  int* error;
-  bool dead;
+  bool dead;   // what this workgroup reads from now on may be missing
 
   // v[i] = the 16 bytes at base(i) + lane(i) once all of them have been written (base: the same in all lanes)
   template <int N, typename B, typename L>
@@ -42,6 +45,11 @@ struct Exchange {
       asm volatile("" ::: "memory");
     }
     dead = true;
+  }
+  // at the end of the kernel: tells the launches behind this one, and the host
+  __device__ __forceinline__ void report(int32_t* state, int* error) {
+    if (!dead) return;
+    __hip_atomic_store(state + kGaveUp, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   __device__ __forceinline__ void put(int base, int lane, unsigned v) {

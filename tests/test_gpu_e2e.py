@@ -384,3 +384,23 @@ def test_small_model_step_matches_oracle(lsq, d, heads, ffn, vocab, beam, dtype)
         assert same.mean() >= (0.3 if dtype else 0.9)
         np.testing.assert_allclose(scores[same], one[2][same], rtol=0, atol=5e-2 if dtype else 1e-3)
         assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("d,batch,dtype", [(512, 2, 1), (512, 12, 1), (512, 3, 0)])   # groups of 8 rows, of more, float32
+def test_steps_behind_a_wait_that_ran_out_end_at_once(lsq, d, batch, dtype):
+    """Where a wait inside the stack kernel has run out, the steps that are already queued behind it do not wait as well:
+    64 of them end in less than one limit (half a second), and the next translation is whole again."""
+    import time
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=203, max_pos=96, dtype=dtype, cap_extra=64)
+    w = S.custom(hp, [8] * batch, beam=4, max_len=80, std=0.03 if dtype else 0.1)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, batch, 4, 80) as eng:
+        want = eng.translate(w.src_ids, w.src_lens, sync_every=64)
+        eng.encode(w.src_ids, w.src_lens)
+        lsq.lsq_debug_end_stack_waits()
+        t0 = time.perf_counter()
+        with pytest.raises(lsq.LsqError):
+            eng.decode_steps(64)
+        assert time.perf_counter() - t0 < 0.4
+        for a, b in zip(eng.translate(w.src_ids, w.src_lens, sync_every=64), want):
+            assert np.array_equal(a, b)
