@@ -908,20 +908,17 @@ int enqueue_step() {
   return LSQ_OK;
 }
 
-// after a wait for the stream: whether a workgroup of the decoder stack kernel gave up waiting for the others
-int stack_waits_ended() {
-  if (*(volatile int32_t*)&g.page->error) return fail(LSQ_E_HIP, "decoder stack kernel: a workgroup waited too long for the others");
-  return LSQ_OK;
-}
+// after a wait for the stream or for a step: whether a workgroup of a decoder stack kernel gave up waiting for the others
+bool stack_gave_up() { return *(volatile int32_t*)&g.page->error != 0; }
 
 // Waits until `steps` steps of this translation are done and returns how many sentences go on.  The step's last kernel
 // writes both into pinned memory, where they are seen several microseconds before a copy of the counter and a wait for
 // the stream would have returned; the stream is asked now and then, in case it ended without them.
-int read_active(int steps, int* out) {
+int wait_active(int steps, int* out) {
   const volatile unsigned long long* word = &g.page->step;
   for (unsigned spin = 1;; ++spin) {
     const unsigned long long v = *word;
-    if ((int)(v >> 32) >= steps) { *out = (int)(v & 0xFFFFFFFFu); return stack_waits_ended(); }
+    if ((int)(v >> 32) >= steps) { *out = (int)(v & 0xFFFFFFFFu); return LSQ_OK; }
     if (spin % 65536 == 0) {
       const hipError_t e = hipStreamQuery(g.stream);
       if (e != hipErrorNotReady) {
@@ -937,7 +934,75 @@ int read_active(int steps, int* out) {
   HIPCHK(hipMemcpyAsync(&n, at<int32_t>(g.plan.active) + steps - 1, 4, hipMemcpyDeviceToHost, g.stream));
   HIPCHK(hipStreamSynchronize(g.stream));
   *out = n;
-  return stack_waits_ended();
+  return LSQ_OK;
+}
+
+// Host copies of what the decoding of a decoder-only model starts from, behind those of the prefill in the staging buffer.
+struct GptStart {
+  int32_t *order, *tokens, *len, *step;
+  GptStart() {
+    order = g.pinned + (size_t)3 * g.max_batch * g.max_len + g.max_batch + 1 + 2 * g.max_batch;
+    tokens = order + g.max_batch + 2;                        // [batch, T+1] token histories
+    len = tokens + (size_t)g.max_batch * (g.max_len + 1);    // [batch] index of the last token
+    step = len + g.max_batch;                                // step_state
+  }
+  void stage(Staging& st, int batch) const {
+    const Plan& p = g.plan;
+    st.add(at<int32_t>(p.tokens), tokens, (size_t)batch * (g.max_len + 1)); st.add(at<int32_t>(p.len), len, batch);
+    st.add(at<int32_t>(p.step_state), step, 4); st.add(at<int32_t>(p.score), nullptr, batch);
+    st.add(at<int32_t>(p.active), nullptr, g.max_len + 1);
+  }
+};
+
+// Hypotheses of an encoded batch before the first step, and the first step's decoder input (BOS at position 0; later ones
+// are left by each step's re-rank kernel).
+int start_beams(int batch) {
+  const Plan& p = g.plan;
+  const HParams& hp = g.hp;
+  HIPCHK(launch_beam_reset(at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
+                           at<int32_t>(p.active), at<int32_t>(p.step_state), g.anc_on ? at<int32_t>(p.anc) : nullptr,
+                           at<int32_t>(p.pen_n), batch, g.beam, g.beam / g.groups, g.max_len, hp.bos, hp.pad, g.stream));
+  if (hp.sample_topk == 0 || g.sample_fold)
+    HIPCHK(launch_embed_last(hp.dtype, g.E, at<float>(p.pe), at<int32_t>(p.tokens), at<int32_t>(p.len), g.ws + p.d_x0,
+                             batch * g.beam, hp.d, g.max_len, at<int32_t>(p.step_state), sqrtf((float)hp.d), g.stream));
+  return LSQ_OK;
+}
+
+// A wait inside a decoder stack kernel ran out: something else holds the compute units that its workgroups need (another
+// process, a kernel on another stream).  From here on this model runs the separate kernels, which need no company; the
+// translation is decoded anew from its start, since the tokens of the failed step have gone into everything after it.  What the
+// encoder (the prefill) left is only read by the decoder, and the start is still in the staging buffer.
+int decode_again() {
+  HIPCHK(hipStreamSynchronize(g.stream));
+  const int steps = g.t;
+  g.stack_ok = false;
+  g.page->error = 0;
+  g.page->step = 0;
+  if (g.hp.arch == 1) {
+    Staging st{};
+    GptStart().stage(st, g.batch);
+    HIPCHK(launch_staging(st, g.stream));
+  } else if (int rc = start_beams(g.batch)) {
+    return rc;
+  }
+  for (g.t = 0; g.t < steps;)
+    if (int rc = enqueue_step()) return rc;
+  return LSQ_OK;
+}
+
+// A new translation takes the place of the one before, of which nothing runs any more.
+void forget_translation() {
+  if (stack_gave_up()) g.stack_ok = false;   // in a step that nobody waited for: see decode_again
+  g.page->error = 0;
+  g.page->step = 0;
+}
+
+// wait_active; if a stack kernel gave up on the way, the same for the translation decoded again
+int read_active(int steps, int* out) {
+  int rc = wait_active(steps, out);
+  if (rc || !stack_gave_up()) return rc;
+  rc = decode_again();
+  return rc ? rc : wait_active(steps, out);
 }
 
 // Decoder-only model: "encode" takes the prompts (all of one length P), runs the blocks over their
@@ -958,18 +1023,16 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
   int32_t* h_sent = h_pos + Rmax;
   int32_t* h_off = h_sent + Rmax;
   int32_t* h_len = h_off + g.max_batch + 1;
-  int32_t* h_order = h_len + 2 * g.max_batch;
-  int32_t* h_tok = h_order + g.max_batch + 2;                  // [batch, T+1] token histories
-  int32_t* h_row = h_tok + (size_t)g.max_batch * (T + 1);      // [batch] index of the last token
-  int32_t* h_step = h_row + g.max_batch;                       // step_state
+  const GptStart start;
+  forget_translation();
   g.order.resize(batch);
   for (int b = 0; b < batch; ++b) {
     g.order[b] = b;
-    h_order[b] = b;
+    start.order[b] = b;
     h_off[b] = b * (P - 1);
     h_len[b] = P - 1;
-    h_row[b] = P - 1;
-    for (int j = 0; j <= T; ++j) h_tok[(size_t)b * (T + 1) + j] = j < P ? ids[(size_t)b * stride + j] : hp.pad;
+    start.len[b] = P - 1;
+    for (int j = 0; j <= T; ++j) start.tokens[(size_t)b * (T + 1) + j] = j < P ? ids[(size_t)b * stride + j] : hp.pad;
     for (int j = 0; j + 1 < P; ++j) {
       h_ids[b * (P - 1) + j] = ids[(size_t)b * stride + j];
       h_pos[b * (P - 1) + j] = j;
@@ -977,16 +1040,15 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
     }
   }
   h_off[batch] = R;
-  h_step[0] = P - 1; h_step[1] = 0; h_step[2] = P - 1; h_step[3] = 0;
+  start.step[0] = P - 1; start.step[1] = 0; start.step[2] = P - 1; start.step[3] = 0;
   g.alive_at.assign(g.max_len + 1, 0);
   for (int t = 0; t < n_new && t <= g.max_len; ++t) g.alive_at[t] = batch;
   Staging st{};
   if (R > 0) {
     st.add(at<int32_t>(p.e_ids), h_ids, R); st.add(at<int32_t>(p.e_pos), h_pos, R); st.add(at<int32_t>(p.e_sent), h_sent, R);
   }
-  st.add(at<int32_t>(p.src_off), h_off, batch + 1); st.add(at<int32_t>(p.src_len), h_len, batch); st.add(at<int32_t>(p.order), h_order, batch);
-  st.add(at<int32_t>(p.tokens), h_tok, (size_t)batch * (T + 1)); st.add(at<int32_t>(p.len), h_row, batch);
-  st.add(at<int32_t>(p.step_state), h_step, 4); st.add(at<int32_t>(p.score), nullptr, batch); st.add(at<int32_t>(p.active), nullptr, T + 1);
+  st.add(at<int32_t>(p.src_off), h_off, batch + 1); st.add(at<int32_t>(p.src_len), h_len, batch); st.add(at<int32_t>(p.order), start.order, batch);
+  start.stage(st, batch);
   HIPCHK(launch_staging(st, s));
 
   const int dt = hp.dtype, d = hp.d, F = hp.F, H = hp.H;
@@ -1193,11 +1255,6 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
     R += n;
   }
   HIPCHK(hipStreamSynchronize(g.stream));   // the staging buffer may still feed an earlier copy
-  if (g.page->error) {   // an earlier translation was given up: its exchange regions are in no known state
-    HIPCHK(reset_stack());
-    g.page->error = 0;
-  }
-  g.page->step = 0;
   const int groups = hp.arch == 0 ? g.groups_next : 1;
   if (g.beam % groups != 0) return fail(LSQ_E_ARG, "beam %d is not a multiple of %d groups", g.beam, groups);
   const bool anc_on = hp.arch == 0 && g.beam > 1 && g.refresh_mode == 1;
@@ -1215,6 +1272,7 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
     g.anc_on = anc_on;
   }
   if (hp.arch == 1) return encode_gpt(src_ids, src_lens, batch, src_stride);
+  forget_translation();
   const Plan& p = g.plan;
   const size_t Rmax = (size_t)g.max_batch * g.max_len;
   int32_t* h_ids = g.pinned;
@@ -1275,11 +1333,6 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
   for (int l = 0; l < hp.n_dec; ++l)
     HIPCHK(launch_gemm(dt, x, g.dec[l].Wkv, g.dec[l].bkv, plain_out(g.ws + p.cross + l * cross_l, 2 * d), (int)R,
                        2 * d, d, 0, s));
-  HIPCHK(launch_beam_reset(at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
-                           at<int32_t>(p.active), at<int32_t>(p.step_state), g.anc_on ? at<int32_t>(p.anc) : nullptr,
-                           at<int32_t>(p.pen_n), batch, g.beam, g.beam / g.groups, g.max_len, hp.bos,
-                           hp.pad, s));
-  // the first step's decoder input (BOS at position 0); later ones are left by each step's re-rank kernel
   // sampling decoding: one launch for retrieve + draw + next input when every row count of this translation has a
   // logit product that leaves group statistics (decided here, for the whole translation)
   bool fold = false;
@@ -1293,9 +1346,7 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
     g.graph_hidden_in_alt.clear();
   }
   g.sample_fold = fold;
-  if (hp.sample_topk == 0 || g.sample_fold)
-    HIPCHK(launch_embed_last(dt, g.E, at<float>(p.pe), at<int32_t>(p.tokens), at<int32_t>(p.len), g.ws + p.d_x0,
-                             batch * g.beam, d, g.max_len, at<int32_t>(p.step_state), sqrtf((float)d), s));
+  if (int rc = start_beams(batch)) return rc;
   for (size_t c : p.dec_canaries) HIPCHK(hipMemsetAsync(g.ws + c, kCanaryByte, kCanaryBytes, s));
   g.batch = batch;
   g.rows_enc = (int)R;
@@ -1466,21 +1517,25 @@ int lsq_get_beams(int32_t* out_ids, int32_t* out_lens, float* out_scores) {
   int32_t* ids = g.results ? g.results : at<int32_t>(p.out_ids);
   int32_t* lens = g.results ? ids + (size_t)M * T : at<int32_t>(p.out_lens);
   float* scores = g.results ? (float*)(lens + M) : at<float>(p.out_scores);
-  HIPCHK(launch_finalize(at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), ids, lens, scores, at<int32_t>(p.order),
-                         g.batch, g.beam, T, g.hp.arch == 1 ? 0.0f : g.hp.alpha, g.hp.pad, g.hp.arch == 1 ? g.prompt_len : 1,
-                         g.stream));
-  if (!g.results) {
-    HIPCHK(hipMemcpyAsync(out_ids, ids, (size_t)M * T * 4, hipMemcpyDeviceToHost, g.stream));
-    HIPCHK(hipMemcpyAsync(out_lens, lens, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
-    HIPCHK(hipMemcpyAsync(out_scores, scores, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
+  for (;;) {
+    HIPCHK(launch_finalize(at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), ids, lens, scores, at<int32_t>(p.order),
+                           g.batch, g.beam, T, g.hp.arch == 1 ? 0.0f : g.hp.alpha, g.hp.pad, g.hp.arch == 1 ? g.prompt_len : 1,
+                           g.stream));
+    if (!g.results) {
+      HIPCHK(hipMemcpyAsync(out_ids, ids, (size_t)M * T * 4, hipMemcpyDeviceToHost, g.stream));
+      HIPCHK(hipMemcpyAsync(out_lens, lens, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
+      HIPCHK(hipMemcpyAsync(out_scores, scores, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
+    }
+    HIPCHK(hipStreamSynchronize(g.stream));
+    if (!stack_gave_up()) break;   // (after the last count was read: a step issued when everything had finished)
+    if (int rc = decode_again()) return rc;
   }
-  HIPCHK(hipStreamSynchronize(g.stream));
   if (g.results) {
     memcpy(out_ids, ids, (size_t)M * T * 4);
     memcpy(out_lens, lens, (size_t)M * 4);
     memcpy(out_scores, scores, (size_t)M * 4);
   }
-  return stack_waits_ended();
+  return LSQ_OK;
 }
 
 void lsq_free(void) {
@@ -1503,6 +1558,9 @@ void lsq_free(void) {
 int lsq_debug_read(int what, void* host_dst, size_t bytes) {
   if (g.state < 3) return fail(LSQ_E_STATE, "lsq_encode has not been called");
   if (!host_dst) return fail(LSQ_E_ARG, "host_dst is null");
+  HIPCHK(hipStreamSynchronize(g.stream));
+  if (stack_gave_up())
+    if (int rc = decode_again()) return rc;
   const Plan& p = g.plan;
   const HParams& hp = g.hp;
   const size_t M = (size_t)g.batch * g.beam, T = g.max_len, d = hp.d, R = g.rows_enc;
