@@ -160,8 +160,8 @@ int lsq_set_layernorm_fusion(int on);
  * small models (d = 64 or 128, heads of 16 or 32; plain beam search) run a whole step as one launch;
  * other float16 shapes with d = 256 or 512 and beam <= 4 run each attention sublayer of a decoder layer as one
  * launch up to its output projection (sec. 2.1 taken further; lsq_k_self_attention_block,
- * lsq_k_cross_attention_block).  The workgroups of an all-layers launch wait for one another, each wait at most half a
- * second: where something else holds the compute units for longer (another process, a kernel on another stream), the
+ * lsq_k_cross_attention_block).  The workgroups of an all-layers launch wait for one another: streams with
+ * a mask of compute units (at lsq_init) do without that kernel, and no wait is longer than half a second: where something else holds the compute units for longer (another process, a kernel on another stream), the
  * translation is decoded again from its start with the separate kernels, which the model keeps until lsq_free.
  * 0 switches all of these off; default and largest value 64.  Same tokens as the separate
  * kernels; scores equal to rounding (other summation orders).  Also off when lsq_set_layernorm_fusion(0).  May

@@ -20,6 +20,8 @@
 // All workgroups must be resident at once: the launcher checks the occupancy, and every wait is bounded (kSpinLimit
 // polls, then the error flag is set, nothing is waited for any more, and this launch and those queued behind it run to their
 // end).
+#include <cstdlib>
+
 #include "stack_exchange.h"
 
 namespace lsq {
@@ -1076,6 +1078,23 @@ StackKind stack_kind(int arch, int M, int d) {
   const bool many = r.x != 0 && rows_kernel_of(r.dk, r.x, arch == 1) && resident(rows_kernel_of(r.dk, r.x, arch == 1));
   if (few && (!many || M <= (d == 768 ? 40 : d == 1024 ? 6 : 8))) return kStackFew;
   return many ? kStackMany : kStackNone;
+}
+
+bool stream_has_every_cu(hipStream_t s) {
+  for (const char* name : {"HSA_CU_MASK", "ROC_GLOBAL_CU_MASK"}) {   // masks for every queue of the process
+    const char* v = std::getenv(name);
+    if (v && *v) return false;
+  }
+  int dev = 0, cus = 0;
+  uint32_t mask[32] = {};
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus > 32 * 32 || hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  for (int i = 0; i < cus; ++i)
+    if (!(mask[i / 32] >> (i % 32) & 1)) return false;
+  return true;
 }
 
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s) {

@@ -188,6 +188,9 @@ struct StackArgs {
 };
 size_t stack_exchange_bytes(int arch, int M, int d, int layers);   // of one set
 bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers);
+// Whether kernels on this stream may use every compute unit of the current device: the workgroups of the stack kernels wait for
+// one another, and behind a mask some of them would only start once others have given up.
+bool stream_has_every_cu(hipStream_t s);
 enum StackKind { kStackNone, kStackFew, kStackMany, kStackF32 };
 StackKind stack_kind(int arch, int M, int d);   // of a supported shape: which kernel takes these rows on the current device
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init

@@ -472,7 +472,7 @@ int setup_stack() {
   a.state = at<int32_t>(p.stack_state); a.error = &g.page->error;
   a.layers = L; a.T = g.max_len; a.anc_ld = g.max_len + 1; a.eps = hp.eps;
   a.beam = g.beam;
-  g.stack_ok = p.stack_rows_set != 0;
+  g.stack_ok = p.stack_rows_set != 0 && stream_has_every_cu(g.stream);
   if (small) {
     char* E = g.ws + p.wpacked + L * layer_bytes_f32(hp);
     if (hp.dtype == DT_F32) HIPCHK(launch_pack_f32(g.E, E, hp.V, d, g.stream));

@@ -62,7 +62,8 @@ struct Exchange {
   }
 };
 
-// Whether every workgroup of a launch of 256 is resident at once on the current device.
+// Whether every workgroup of a launch of 256 is resident at once on the current device, as far as the device goes; whether
+// the stream has all of it: stream_has_every_cu.
 inline bool resident(const void* kernel) {
   static std::unordered_map<const void*, bool> known;
   const auto it = known.find(kernel);
