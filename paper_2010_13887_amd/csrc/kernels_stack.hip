@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
 
   Exchange ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
-  ex.dead = a.state[kGaveUp] != 0;
+  ex.dead = seq < 0;
   const int row_bytes = a.layers * Rg::size * D;
   const int rp = max(a.rows_per_group, kMinRows);   // rows a writer's piece has room for
   auto at = [&](int l, int region) { return (grp * row_bytes + (l * Rg::size + region) * D) * rp; };
@@ -489,7 +489,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     if (n == (int)gridDim.x - 1) {
       a.state[4] = 0;
       a.state[1 + parity] = G * rp;
-      a.state[0] = seq + 1;
+      __hip_atomic_fetch_xor(a.state, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -537,12 +537,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   const int grp = (bid >> 3) % G, j = (bid >> 3) / G * 8 + (bid & 7);
   const int cg = j >> 2, ks = j & 3;
   const int rp = a.rows_per_group, r0 = grp * rp, rows = min(rp, a.M - r0);
-  const int start = a.state[0], dirty = a.state[1], pos = *a.tpos;
+  const int seq = a.state[0], start = seq & 1, dirty = a.state[1], pos = *a.tpos;
   const bool owner = j < rows;
 
   Exchange ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange, (short)0, (int)(2 * a.set_bytes), 0x00027000);
-  ex.dead = a.state[kGaveUp] != 0;
+  ex.dead = seq < 0;
   const int group_bytes = Rg::size * D * rp;
   auto at = [&](int l, int region) { return ((start + l) & 1) * (int)a.set_bytes + grp * group_bytes + region * D * rp; };
   const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
@@ -999,7 +999,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     if (n == (int)gridDim.x - 1) {
       a.state[4] = 0;
       a.state[1] = G * group_bytes;
-      a.state[0] = (start + a.layers) & 1;
+      __hip_atomic_fetch_xor(a.state, a.layers & 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -1102,7 +1102,7 @@ hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipS
   return e == hipSuccess ? hipMemsetAsync(state, 0, 8 * 4, s) : e;
 }
 
-hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s) { return hipMemsetD32Async((hipDeviceptr_t)(state + kGaveUp), 1, 1, s); }
+hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s) { return hipMemsetAsync(reinterpret_cast<char*>(state) + 3, 0x80, 1, s); }
 
 hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s) {
   const Choice c = choose_rows(args.M, d);

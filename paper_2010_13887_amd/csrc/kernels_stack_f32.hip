@@ -55,12 +55,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
   const int j = (bid & 7) * (W / 8) + jx;   // neighbouring columns on one XCD: its L2 reads whole lines
   const int cg = j >> 2, ks = j & 3;
   const int rp = a.rows_per_group, r0 = grp * rp, rows = min(rp, a.M - r0);
-  const int start = a.state[0], dirty = a.state[1], pos = *a.tpos;
+  const int seq = a.state[0], start = seq & 1, dirty = a.state[1], pos = *a.tpos;
   const bool owner = j < rows;
 
   Exchange ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange, (short)0, (int)(2 * a.set_bytes), 0x00027000);
-  ex.dead = a.state[kGaveUp] != 0;
+  ex.dead = seq < 0;
   const int group_bytes = Rg::size * D * rp;
   auto at = [&](int l, int region) { return ((start + l) & 1) * (int)a.set_bytes + grp * group_bytes + region * D * rp; };
   const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
@@ -396,7 +396,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
     if (n == (int)gridDim.x - 1) {
       a.state[4] = 0;
       a.state[1] = G * group_bytes;
-      a.state[0] = (start + a.layers) & 1;
+      __hip_atomic_fetch_xor(a.state, a.layers & 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }

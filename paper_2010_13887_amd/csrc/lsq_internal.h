@@ -178,9 +178,9 @@ struct StackArgs {
   half_t *hidden, *x_out;   // normalised rows for the vocabulary product; pre-LN: the residual stream
   char* exchange;           // two sets of set_bytes each
   size_t set_bytes;
-  int32_t* state;           // few rows: [0] launches so far, [1 + p] rows of set p to be refilled, [4] arrivals; many:
+  int32_t* state;           // few rows: [0] set of the next launch, [1 + p] rows of set p to be refilled, [4] arrivals; many:
                             // [0] slot of the next layer, [1] bytes of the other one to be refilled, [4] arrivals;
-                            // both: [5] a wait ran out
+                            // both: [0] negative once a wait has run out
   int* error;               // pinned host memory: set when a wait ran out
   int M, beam, layers, T, anc_ld;
   float eps;

@@ -22,9 +22,10 @@ __device__ __forceinline__ unsigned publish_word(unsigned v) { return v == kSent
 // up to 1 % by it and keep theirs.
 __device__ __forceinline__ const __attribute__((address_space(4))) StackArgs* now() { return arguments<StackArgs>(); }
 
-// The word of StackArgs::state that is set at the end of a launch in which a wait ran out.  A launch that finds it set looks
-// once where it would wait: the steps queued behind the one that gave up end at once instead of each waiting out the limit.
-constexpr int kGaveUp = 5;
+// Set in the first word of StackArgs::state at the end of a launch in which a wait ran out (the word the kernels read first
+// anyway: a word of its own and its test before every wait cost 0.5 us a step).  A launch that finds it set looks once where it would wait: the steps queued
+// behind the one that gave up end at once instead of each waiting out the limit.
+constexpr int kGaveUp = (int)0x80000000u;
 
 struct Exchange {
   __amdgpu_buffer_rsrc_t rsrc;
@@ -33,14 +34,14 @@ struct Exchange {
   // v[i] = the 16 bytes at base(i) + lane(i) once all of them have been written (base: the same in all lanes)
   template <int N, typename B, typename L>
   __device__ __forceinline__ void wait(B base, L lane, u32x4 (&v)[N]) {
-    for (int left = dead ? 1 : kSpinLimit;;) {
+    for (int left = kSpinLimit;;) {
 #pragma unroll
       for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane(i), base(i), kAgent);
       unsigned worst = 0;
 #pragma unroll
       for (int i = 0; i < N; ++i) worst = max(max(worst, max(v[i].x, v[i].y)), max(v[i].z, v[i].w));
       if (__all(worst != kSentinel)) return;
-      if (--left == 0) break;
+      if (dead || --left == 0) break;
       __builtin_amdgcn_s_sleep(1);
       asm volatile("" ::: "memory");
     }
@@ -49,7 +50,7 @@ struct Exchange {
   // at the end of the kernel: tells the launches behind this one, and the host
   __device__ __forceinline__ void report(int32_t* state, int* error) {
     if (!dead) return;
-    __hip_atomic_store(state + kGaveUp, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_or(state, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   __device__ __forceinline__ void put(int base, int lane, unsigned v) {
