@@ -1067,16 +1067,50 @@ bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers)
          stack_exchange_bytes(arch, kStackRowsMax, d, layers) < (1u << 30);
 }
 
-// Which kernel takes M rows on the current device.  Measured, layers of one step in us (8-row groups / more rows):
+// Which kernel takes M rows on the current device.  Measured at short histories, layers of one step in us (8-row groups /
+// more rows):
 //   d = 512, 6 layers:    4 rows 92 / 98, 32 rows 116 / 108, 64 rows 117 / 116, 128 rows - / 137, 256 rows - / 196
 //   d = 768, 12 layers:   1 row 137 / 158, 8 rows 158 / 165, 32 rows 209 / 213, 40 rows 198 / 199, 64 rows - / 255
 //   d = 1024, 6 layers:   4 rows 122 / 126, 8 rows 134 / 128, 32 rows 174 / 147, 64 rows - / 189, 128 rows - / 266
-StackKind stack_kind(int arch, int M, int d) {
+// A (row, head) pair has 256 keys in flight in groups of 8 rows (128 with X = 1), 64 or 32 in groups of 16 or 32; the separate
+// kernels give it four wavefronts and read a history that the rows of a sentence share once.  So the order changes with the
+// length.  Whole steps in us, 8-row groups / more rows / separate launches, beam 4 and a source of 30 tokens:
+//   position                  16                496               1008              1900
+//   d = 512,   32 rows        132 / 127 / 220   181 / 249 / 331   230 / 377 / 420   315 / 614 / 580
+//              64 rows        134 / 136 / 252   225 / 276 / 368   324 / 434 / 480   484 / 699 / 648
+//             128 rows        -   / 157 / 301   -   / 335 / 475   -   / 535 / 657   -   / 839 / 815
+//             256 rows        -   / 215 / 339   -   / 570 / 673   -   / 935 / 970   -   / 1528 / 1342
+//   d = 768,   40 rows        172 / 172 / 298   265 / -   / 400   359 / -   / 473   509 / -   / 541
+//              48 rows        -   / 161 / 286   -   / 318 / 441   -   / 483 / 541   -   / 764 / 662
+//             160 rows        -   / 241 / 374   -   / 598 / 682   -   / 972 / 960   -   / 1554 / 1216
+//   d = 1024,   8 rows        164 / 159 / 272   197 / 273 / 317   245 / 410 / 357   324 / 635 / 388
+//              16 rows        185 / 172 / 337   226 / 293 / 414   276 / 428 / 455   347 / 649 / 474
+//              32 rows        219 / 184 / 318   297 / 319 / 404   383 / 465 / 469   523 / 702 / 538
+//              64 rows        -   / 210 / 344   -   / 378 / 514   -   / 550 / 623   -   / 828 / 732
+//             128 rows        -   / 272 / 383   -   / 606 / 693   -   / 945 / 899   -   / 1495 / 1173
+// 8-row groups / more rows, nearer: d = 512, 12 rows 132 / 131 at 104, 137 / 153 at 240; 32 rows 134 / 138, 149 / 174; 64 rows
+// 142 / 153, 175 / 200; one row per sentence (every row reads a history of its own in either) 16 rows 134 / 141 at 240, 32 rows
+// 149 / 150, 64 rows 169 / 172.  d = 1024, 8 rows 168 / 174 at 104; 16 rows 185 / 185, 191 / 199 at 160; 32 rows 252 / 245 at
+// 240, 274 / 278 at 352; one per sentence 8 rows 175 / 180 at 240, 16 rows 209 / 209 at 352, 32 rows 293 / 262 at 496.
+// One row per sentence shares nothing, and only the widest case crosses: d = 1024, 128 rows 898 / 958 at 1008, 1418 / 1391 at
+// 1900; d = 768 pre-LN, 160 rows 2307 / 2493 at 1980.  A source key counts as a quarter or half of one of the history (position
+// 16, sources of 2000: d = 512, 128 rows 460 / 458, 256 rows 791 / 784; d = 1024, 32 rows 363 / 433, 128 rows 862 / 825).
+StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src) {
   if (M < 1) return kStackNone;
   const Choice c = choose(arch, M, d), r = choose_rows(M, d);
-  const bool few = c.x != 0 && M <= kStackRowsMax && kernel_of(c.dk, c.x, arch == 1) && resident(kernel_of(c.dk, c.x, arch == 1));
-  const bool many = r.x != 0 && rows_kernel_of(r.dk, r.x, arch == 1) && resident(rows_kernel_of(r.dk, r.x, arch == 1));
-  if (few && (!many || M <= (d == 768 ? 40 : d == 1024 ? 6 : 8))) return kStackFew;
+  bool few = c.x != 0 && M <= kStackRowsMax && kernel_of(c.dk, c.x, arch == 1) && resident(kernel_of(c.dk, c.x, arch == 1));
+  bool many = r.x != 0 && rows_kernel_of(r.dk, r.x, arch == 1) && resident(rows_kernel_of(r.dk, r.x, arch == 1));
+  constexpr int never = 1 << 30;
+  const int len = pos + src / 4;
+  // where the lines above cross: 8-row groups against separate launches (extrapolated past 1900; 1 sentence of d = 1024
+  // 460 / 464 at 3900), more rows against them, 8-row groups against more rows
+  if (beam > 1 && d > 512 && len > (c.x == 1 ? 2000 : 2700)) few = false;
+  if (r.x == 1 && beam > 1 && len > 1300) many = false;
+  if (r.x == 2 && pos + src / 2 > (beam > 1 ? (d == 512 ? 1120 : d == 768 ? 960 : 830) : (d == 1024 ? 1600 : never))) many = false;
+  const int few_from = d == 768    ? (M <= 40 ? 0 : never)
+                       : d == 1024 ? (M <= 6 ? 0 : beam > 1 ? (M <= 16 ? 112 : 352) : M <= 16 ? 352 : never)
+                                   : (M <= 8 ? 0 : beam > 1 ? 112 : 240);
+  if (few && (!many || len >= few_from)) return kStackFew;
   return many ? kStackMany : kStackNone;
 }
 

@@ -401,19 +401,17 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
   }
 }
 
-struct ChoiceF32 { const void* kernel; int groups, rows; };
+struct ChoiceF32 { const void* kernel; int groups, rows, nb; };
 
 // As many groups as 256 CUs hold: they share the weights through the L2 of their XCD, and a row costs matrix time.
 // A whole translation at d = 512, beam 4, against separate launches (ms): 1 sentence 14.3 / 38.2, 8 19.7 / 53.7, 32 32.9 / 83.3,
-// 50 with beam 5 (250 rows) 49.9 / 94.4: wherever it fits it wins.
-// A whole translation at d = 512, beam 4, against separate launches (ms): 1 sentence 14.3 / 38.2, 8 19.7 / 53.7, 32 32.9 / 83.3,
-// 50 with beam 5 (250 rows) 49.9 / 94.4: wherever it fits it wins.
+// 50 with beam 5 (250 rows) 49.9 / 94.4: at short histories it wins wherever it fits.
 ChoiceF32 choose_f32(int M, int d) {
   ChoiceF32 c = {};
   c.groups = min(256 / (d / 16), M);
   c.rows = (M + c.groups - 1) / c.groups;
   c.groups = (M + c.rows - 1) / c.rows;
-  const int nb = c.rows <= 4 ? 1 : c.rows <= 8 ? 2 : c.rows <= 16 ? 4 : c.rows <= min(32, d / 16) ? 8 : 0;
+  const int nb = c.nb = c.rows <= 4 ? 1 : c.rows <= 8 ? 2 : c.rows <= 16 ? 4 : c.rows <= min(32, d / 16) ? 8 : 0;
 #define LSQ_F32(DKV, NBV) if (d == 256 * DKV && nb == NBV) c.kernel = (const void*)decoder_stack_f32_kernel<DKV, NBV>
   LSQ_F32(1, 1); LSQ_F32(1, 2); LSQ_F32(1, 4); LSQ_F32(2, 1); LSQ_F32(2, 2); LSQ_F32(2, 4); LSQ_F32(2, 8);
 #undef LSQ_F32
@@ -428,10 +426,21 @@ bool stack_f32_shape_supported(int dtype, int arch, int H, int d, int F) {
   return dtype == DT_F32 && arch == 0 && (d == 256 || d == 512) && H * 64 == d && F == 4 * d;
 }
 
-bool stack_f32_supported(int M, int d) {
+// Where the attention of long histories makes it fall behind: a (row, head) pair has 64 / NB keys in flight, the separate
+// kernels have more and read what the rows of a sentence share once.  Whole steps in us, this kernel / separate launches, beam 4
+// (position 16, 496, 1008, 1900):
+//   d = 512:   4 rows 149 / 427, 218 / 495, 297 / 544, 467 / 600 (2900: 665 / 683); 64 rows 216 / 802, 422 / 956, 633 / 1098, 970 / 1246
+//            128 rows 298 / 762, 684 / 1071, 1097 / 1344, 1723 / 1651; 192 rows 425 / 827, 1138 / 1286, 1877 / 1716, 3078 / 2279
+//            256 rows 489 / 869, 1284 / 1410, 2085 / 1932, 3349 / 2569; position 16, sources of 500 885 / 1016, of 2000 2196 / 1435
+//   d = 256:  64 rows 140 / 469, 216 / 561, 313 / 623, 483 / 698; 256 rows 251 / 546, 569 / 716, 916 / 857, 1535 / 1109
+// One row per sentence (nothing shared), d = 512: 128 rows 303 / 774 .. 1455 / 1760, 200 rows 457 / 797, 1014 / 1222, 1580 / 1636, 2543 / 2340
+bool stack_f32_supported(int M, int d, int beam, int pos, int src) {
   if (M < 1) return false;
   const ChoiceF32 c = choose_f32(M, d);
-  return c.kernel && resident(c.kernel);
+  if (!c.kernel || !resident(c.kernel)) return false;
+  const int len = pos + src * c.nb / 8;
+  if (beam > 1) return len <= (c.nb <= 2 ? 3000 : c.nb == 8 ? 730 : d == 512 ? 1650 : 850);
+  return c.nb < 8 || len <= 1200;
 }
 
 size_t pack_f32_bytes(int N, int K) { return (size_t)(N + 63) / 64 * 64 * K * 4; }

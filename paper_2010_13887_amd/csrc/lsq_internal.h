@@ -192,7 +192,8 @@ bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers)
 // one another, and behind a mask some of them would only start once others have given up.
 bool stream_has_every_cu(hipStream_t s);
 enum StackKind { kStackNone, kStackFew, kStackMany, kStackF32 };
-StackKind stack_kind(int arch, int M, int d);   // of a supported shape: which kernel takes these rows on the current device
+// of a supported shape: which kernel takes these rows on the current device, at a history of `pos` positions and sources of at most `src` tokens
+StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src);
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init
 hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s);   // as if a wait had run out
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
@@ -201,7 +202,7 @@ hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hip
 // float32 (kernels_stack_f32.hip): the matrices are copies made by launch_pack_f32 (16-column units, columns up to a multiple of 64, K of 4), vectors, cache and rows float32
 size_t stack_f32_bytes(int M, int d);
 bool stack_f32_shape_supported(int dtype, int arch, int H, int d, int F);
-bool stack_f32_supported(int M, int d);   // of a supported shape: these rows, on the current device
+bool stack_f32_supported(int M, int d, int beam, int pos, int src);   // as stack_kind
 size_t pack_f32_bytes(int N, int K);
 hipError_t launch_pack_f32(const void* plain, void* packed, int N, int K, hipStream_t s);
 hipError_t launch_decoder_stack_f32(const StackArgs& args, int d, hipStream_t s);

@@ -487,10 +487,14 @@ int setup_stack() {
   return LSQ_OK;
 }
 
+// positions that the next step finds in the cache
+int history() { return (g.hp.arch == 1 ? g.prompt_len - 1 : 0) + g.t; }
+
 StackKind use_stack(int M) {
   if (!g.stack_ok || !g.fuse_ln || (M > g.block_rows && g.block_rows < (int)kBlockRowsMax)) return kStackNone;
-  if (g.hp.dtype == DT_F32) return stack_f32_supported(M, g.hp.d) ? kStackF32 : kStackNone;
-  return stack_kind(g.hp.arch, M, g.hp.d);
+  const int pos = history(), src = g.hp.arch == 1 ? 0 : g.src_longest;
+  if (g.hp.dtype == DT_F32) return stack_f32_supported(M, g.hp.d, g.beam, pos, src) ? kStackF32 : kStackNone;
+  return stack_kind(g.hp.arch, M, g.hp.d, g.beam, pos, src);
 }
 
 // plain beam search with a small model: the whole step in one launch.  Up to as many sentences as the chip runs at once:

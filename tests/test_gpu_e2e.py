@@ -467,3 +467,49 @@ def test_masked_queues_run_the_separate_kernels(lsq, monkeypatch):
     same = (got[0] == want[0]).all(axis=-1)
     assert same.mean() >= 0.9                          # a near-tie may flip: sums in another order, float16
     np.testing.assert_allclose(got[2][same], want[2][same], rtol=0, atol=2e-3)
+
+
+def _long_workload(d, heads, lens, beam, steps, dtype, n_dec=2, ffn=None, vocab=203, std=None):
+    """A model that does not end its sentences: EOS lies far behind along the shift of the last LayerNorm."""
+    hp = S.HParams(n_enc=1, n_dec=n_dec, d_model=d, n_heads=heads, d_ffn=ffn or 4 * d, vocab=vocab, max_pos=512, dtype=dtype,
+                   cap_extra=steps)
+    w = S.custom(hp, lens, beam=beam, max_len=max(lens) + steps, std=std or (0.03 if dtype else 0.1))
+    E = np.random.default_rng(d).standard_normal((vocab, d)) * w.std
+    E[hp.eos_id] = -16.0 / d
+    return w, w.blob(ln_jitter=0.1, overrides={"E": E, f"dec{n_dec - 1}.ln3_b": np.ones(d)})
+
+
+@pytest.mark.parametrize("d,batch,beam,dtype,steps", [
+    (256, 1, 2, 1, 270),     # groups of 8 rows: 256 keys a trip
+    (512, 10, 4, 1, 140),    # ... 128 keys a trip, from position 112 on; groups of 16 rows before
+    (768, 12, 4, 1, 72),     # groups of 16 rows: 64 keys a trip
+    (512, 40, 4, 1, 72),     # groups of 32 rows: 32 keys a trip
+    (512, 2, 1, 0, 72), (512, 16, 4, 0, 72), (256, 33, 4, 0, 72), (512, 40, 4, 0, 72),   # float32: 64, 32, 16 and 8 keys a trip
+])
+def test_decoder_stack_past_its_first_trip_for_keys(lsq, d, batch, beam, dtype, steps):
+    """One sentence of the batch in lock-step with the oracle until the histories (and the slab table) have been read in
+    several trips, beside a source of 70 tokens."""
+    w, blob = _long_workload(d, d // 64, [3 + (5 * i) % 7 for i in range(batch - 1)] + [70], beam, steps, dtype)
+    with lsq.Engine(blob, batch, beam, w.max_len) as eng:
+        assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[batch - 1])["steps"] == steps
+
+
+def test_long_histories_leave_the_stack_kernel(lsq):
+    """256 rows, d = 256, float32: from a history of 850 on (less half of the source) the separate launches are ahead and take
+    over in the middle of a translation.  The same tokens as with the separate launches alone."""
+    w, blob = _long_workload(256, 4, [8] * 64, 4, 860, 0, n_dec=1)
+    out = {}
+    try:
+        for rows in (0, 64):
+            lsq.lsq_set_attention_blocks(rows)
+            with lsq.Engine(blob, 64, 4, w.max_len) as eng:
+                lsq.lsq_profile_enable(True)
+                out[rows] = eng.translate(w.src_ids, w.src_lens, sync_every=64)
+                stack = lsq.lsq_profile_read()["decoder_stack"][1]
+                lsq.lsq_profile_enable(False)
+                assert stack == (850 - 4 + 1 if rows else 0)
+    finally:
+        lsq.lsq_set_attention_blocks(64)
+    same = (out[0][0] == out[64][0]).all(axis=-1)
+    assert same.mean() >= 0.9                              # float32 sums in another order: a near-tie may flip
+    np.testing.assert_allclose(out[0][2][same], out[64][2][same], rtol=0, atol=1e-3)
