@@ -382,6 +382,26 @@ bool small_step_supported(int arch, int H, int d, int F, int V, int k) {
          (size_t)(V + 63) / 64 * 64 * d <= (1u << 17) && k <= LSQ_MAX_BEAM_ && topk_groups_supported(V, k, 0);
 }
 
+// Where one workgroup per sentence is ahead of the separate launches.  It takes the K*H (row, head) pairs of a layer eight at a
+// time through 64 keys a trip (2.2 us for a trip of the history at heads of 16 in float32, 1.7 in float16, half of that for the
+// source, twice that at heads of 32), while the separate launches spread them over the chip and cost little more at any
+// length.  Whole steps in us, this kernel / separate launches, float32 (position 4, 104, 240, 496, 1008; sources of 8):
+//   d = 64, 1 layer, 4 heads:   2 x 4 rows 33 / 57, 38 / 58, 47 / 58, 64 / 59, 99 / 63;   32 x 4 33 / 81, 38 / 81, 48 / 83, 65 / 84, 108 / 94
+//                               2 x 8      47 / 69, 57 / 70, 76 / 71, 111 / 73;           64 x 8 47 / 90, 58 / 91, 78 / 97, 117 / 106
+//   d = 128, 2 layers, 8 heads: 2 x 4      79 / 103, 100 / 105, 135 / 106, 208 / 112;     32 x 4 78 / 144, 105 / 147, 144 / 156, 217 / 170
+//                               2 x 8      115 / 120, 157 / 123, 239 / 125;             256 x 4 90 / 189, 111 / 194, 165 / 223, 283 / 307, 580 / 493
+//   ... 6 layers:               2 x 4      217 / 271, 282 / 272, 403 / 279;               32 x 4 215 / 406, 279 / 412, 400 / 429, 626 / 449
+//   sources of 64, 128, 256, 500 at position 4, d = 128, 2 layers: 2 x 4 84 / 101, 93 / 101, 111 / 102, 146 / 103;
+//                                                               32 x 8 127 / 168, 147 / 169, 183 / 172, 254 / 177
+// and the same order in float16 with both sides 15 % lower.  The lines cross at 16 to 66 trips (a trip of the history and heads of 16
+// counting two), more with more rows, whose separate launches take longer, and fewer with more layers, over which the
+// launches outside of them are spread.
+bool small_step_ahead(int batch, int k, int H, int d, int layers, int pos, int src) {
+  const int M = batch * k, per_layer = (k * H + kWaves - 1) / kWaves * (d / H / 16);
+  const int trips = per_layer * (2 * (pos / 64 + 1) + (src + 63) / 64);
+  return trips <= 21 + min(M, 16) / 2 + min(M, 128) / 16 + max(M - 128, 0) / 32 - 3 * (layers - 1) / 2;
+}
+
 hipError_t launch_small_step(int dtype, int batch, int k, const StackArgs& args, const SearchArgs& search, hipStream_t s) {
   const void* kernel = small_kernel_of(dtype, k);
   if (!kernel || batch < 1) return hipErrorInvalidValue;

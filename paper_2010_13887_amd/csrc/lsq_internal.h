@@ -275,6 +275,7 @@ struct SearchArgs {
   unsigned long long* report;
 };
 bool small_step_supported(int arch, int H, int d, int F, int V, int k);
+bool small_step_ahead(int batch, int k, int H, int d, int layers, int pos, int src);   // ... and faster so, at this history and these sources
 hipError_t launch_small_step(int dtype, int batch, int k, const StackArgs& args, const SearchArgs& search, hipStream_t s);
 hipError_t launch_beam_refine(const float* cand_score, const int32_t* cand_idx, float* score,
                               int32_t* tokens, int32_t* len, int32_t* fin, int32_t* parent,

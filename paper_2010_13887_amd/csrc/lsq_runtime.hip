@@ -501,7 +501,8 @@ StackKind use_stack(int M) {
 // a workgroup's step takes as long as the separate launches of some hundred rows.
 bool use_small(int B) {
   return g.small_ok && g.fuse_ln && (B * g.beam <= g.block_rows || g.block_rows == (int)kBlockRowsMax) && B <= 256 && g.groups == 1 &&
-         g.hp.sample_topk == 0 && g.topk_stats && g.merge_rerank;
+         g.hp.sample_topk == 0 && g.topk_stats && g.merge_rerank &&
+         small_step_ahead(B, g.beam, g.hp.H, g.hp.d, g.hp.n_dec, history(), g.src_longest);
 }
 
 hipError_t launch_stack(StackKind kind, StackArgs a) {

@@ -513,3 +513,38 @@ def test_long_histories_leave_the_stack_kernel(lsq):
     same = (out[0][0] == out[64][0]).all(axis=-1)
     assert same.mean() >= 0.9                              # float32 sums in another order: a near-tie may flip
     np.testing.assert_allclose(out[0][2][same], out[64][2][same], rtol=0, atol=1e-3)
+
+
+@pytest.mark.parametrize("d,heads,beam,dtype,src", [(64, 4, 2, 1, 70), (128, 4, 1, 1, 9), (64, 2, 4, 0, 70), (128, 8, 2, 0, 130)])
+def test_small_model_step_past_its_first_trip_for_keys(lsq, d, heads, beam, dtype, src):
+    """The one-launch step of a small model in lock-step with the oracle until histories and slab table have been read in
+    several trips of 64, with sources of one trip, two and three."""
+    w, blob = _long_workload(d, heads, [2, src], beam, 80, dtype, n_dec=1, vocab=97, std=0.08 if dtype else 0.3)
+    with lsq.Engine(blob, 2, beam, w.max_len) as eng:
+        lsq.lsq_profile_enable(True)
+        res = lockstep(lsq, eng, blob, w, max_steps=80, sentences=[1])
+        launches = lsq.lsq_profile_read()
+        lsq.lsq_profile_enable(False)
+        assert res["steps"] == 80 and launches["decoder_stack"][1] == 80 and launches["gemm_vocab"][1] == 0
+
+
+def test_long_histories_leave_the_small_model_kernel(lsq):
+    """8 heads and 2 layers, 8 rows: past a history of 128 positions the separate launches take over in
+    the middle of a translation; the same tokens as with the separate launches alone."""
+    w, blob = _long_workload(128, 8, [9, 4], 4, 170, 0, vocab=97, std=0.3)
+    out = {}
+    try:
+        for rows in (0, 64):
+            lsq.lsq_set_attention_blocks(rows)
+            with lsq.Engine(blob, 2, 4, w.max_len) as eng:
+                lsq.lsq_profile_enable(True)
+                out[rows] = eng.translate(w.src_ids, w.src_lens, sync_every=64)
+                launches = lsq.lsq_profile_read()
+                lsq.lsq_profile_enable(False)
+                # 4 passes of 8 pairs, a trip of the history counts 2: 4 (2 * 2 + 1) = 20 trips are within the bound, 4 (2 * 3 + 1) are not
+                assert launches["decoder_stack"][1] == (128 if rows else 0)
+    finally:
+        lsq.lsq_set_attention_blocks(64)
+    same = (out[0][0] == out[64][0]).all(axis=-1)
+    assert same.mean() >= 0.9                              # float32 sums in another order: a near-tie may flip
+    np.testing.assert_allclose(out[0][2][same], out[64][2][same], rtol=0, atol=1e-3)
