@@ -24,6 +24,7 @@ __device__ __forceinline__ float activate(float v, int act) {
   if (act == 2) return tanh_gelu(v);
   return v;
 }
+__device__ __forceinline__ float activate_f32(float v, int act) { return act == 2 ? tanh_gelu_f32(v) : activate(v, act); }
 
 // four floats that are only 4-byte aligned: still one store instruction (the target allows dword-aligned
 // multi-dword accesses to global memory, and the compiler uses them for this type)
@@ -156,7 +157,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__
       int n = n0 + tx * 4 + j;
       if (n >= N) continue;
       float v = acc[i][j] + (bias ? bias[n] : 0.f);
-      v = activate(v, act);
+      v = activate_f32(v, act);
       store_one<float>(out, m, n, v, tp);
     }
   }
@@ -1028,7 +1029,7 @@ __global__ void __launch_bounds__(256) gemm_f32_stream_kernel(const float* __res
       const int r = vg * 4 + e;
       v[e] = (red[0][i][r][lane] + red[1][i][r][lane]) + (red[2][i][r][lane] + red[3][i][r][lane]);
       if (bias) v[e] += bias[min(n + e, N - 1)];
-      v[e] = activate(v[e], act);
+      v[e] = activate_f32(v[e], act);
     }
     if (m < M && n < N) store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp);
     if (stats) {   // as in gemm_f16_skinny_kernel

@@ -95,6 +95,31 @@ def test_gemm_gelu(env, M, N, K, half):
     np.testing.assert_allclose(C.cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
 
 
+@pytest.mark.parametrize("rows", [True, False])
+def test_float32_gelu_keeps_the_last_places(env, rows):
+    """GELU of float32 products, of values the product itself leaves exact: many rows (tiled kernel) and many columns of one
+    row (streaming kernel).  For positive values the formula ends in one fused operation (half a unit in the last place) whose
+    subtrahend v s carries the roundings of s: at v = 1 (s = 0.16, 2u = 1.7) 0.16 (1.5 * 1.7 + 2) = 0.7 units, less beyond, below at
+    most 1.5.  For negative ones the exponent's roundings are scaled by its size, 2 |u|."""
+    lsq, torch = env
+    v = np.random.default_rng(7).uniform(-9, 9, 1 << 16 if rows else 60000).astype(np.float32)
+    v[:3] = 0, 1e30, 3e38
+    pad = np.zeros((v.size, 8), np.float32)
+    pad[:, 0] = v
+    one = np.zeros((4, 8) if rows else (1, 8), np.float32)
+    one[:, 0] = 1
+    A, B = (pad, one) if rows else (one, pad)
+    C = torch.empty(A.shape[0], B.shape[0], dtype=torch.float32, device="cuda")
+    lsq.k_gemm(_dev(torch, A), _dev(torch, B), None, C, gelu=True)
+    got = C.cpu().numpy()[:, 0] if rows else C.cpu().numpy()[0]
+    x = v.astype(np.float64)
+    u2 = 2 * np.sqrt(2 / np.pi) * (x + 0.044715 * x ** 3)
+    with np.errstate(over="ignore"):
+        want = x / (1 + np.exp(-u2))
+    bound = np.where(v >= 1, 1.5, np.where(v >= 0, 2.0, 4 * np.abs(u2) + 6)) * np.spacing(np.abs(want).astype(np.float32)).astype(np.float64)
+    assert (np.abs(got - want) <= bound).all()
+
+
 @pytest.mark.parametrize("M,N,K", [(7393, 2304, 64), (7300, 2290, 128), (3000, 777, 64), (250, 32001, 64), (4096, 4090, 192)])
 @pytest.mark.parametrize("half_out", [False, True])
 def test_gemm_large_tiles(env, M, N, K, half_out):
