@@ -146,8 +146,8 @@ int lsq_set_cache_refresh(int mode);
  * LayerNorm" into the product that consumes the normalised rows (sec. 2.1 taken
  * one step further: 18 fewer launches per step), and with at most 64 rows (beams
  * of at most 4, heads of 64) the cross-attention kernel normalises its rows and
- * makes its queries itself (12 fewer); with more rows it still makes its queries,
- * from rows the LayerNorm kernel has normalised (6 fewer).  on = 0 keeps the stand-alone LayerNorm
+ * makes its queries itself (12 fewer); with more rows it still makes its queries
+ * where that is ahead, from rows the LayerNorm kernel has normalised (6 fewer).  on = 0 keeps the stand-alone LayerNorm
  * kernel at every size.  The row arithmetic is the same either way; the
  * cross-attention kernel that makes its own queries takes its sums in another
  * order (fewer split-K slabs, keys shared by four wavefronts), so results agree

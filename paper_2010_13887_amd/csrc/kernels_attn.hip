@@ -711,8 +711,6 @@ __global__ void __launch_bounds__(512) cross_attention_q_kernel(const half_t* __
   }
 }
 
-// Measured on whole steps of the big model: 0.678 -> 0.671 ms at 512 rows, nothing at 128 (a sentence of 125 keys
-// takes four dependent trips for its keys whichever kernel attends, and here they start only after the product).
 // sentences per workgroup: 8 (32 rows at beam 4) once that still gives a workgroup per CU, fewer below
 static int cross_q_group(int batch, int H) {
   int GS = 8;
@@ -720,11 +718,14 @@ static int cross_q_group(int batch, int H) {
   return GS;
 }
 
-// Ahead of the two separate launches where its workgroups, of at least two sentences each, fill the CUs in one round (whole
-// translations, 16 heads of the big model: 32 sentences = 256 workgroups 46.2 -> 45.4 ms, 30 and 28 sentences level, 48
-// sentences = 384 workgroups 51.9 -> 54.4 ms, 20 sentences level; 8 heads of d = 512, 32 sentences = 256 workgroups of one
-// sentence: 34.7 -> 34.8 ms), but not above 256 rows (128 sentences of equal length level, of mixed lengths 67.5 -> 68.3 ms, d = 512,
-// 100 sentences 38.7 -> 42.0: a workgroup waits for its longest sentence).
+// Ahead of the two separate launches where its workgroups, of at least two sentences each, fill the CUs in one round and there
+// are at most 256 rows.  The stack kernel takes the row counts below where the shape has one, which leaves 61 to 64 sentences
+// at 16 heads.  Whole steps there, this launch / two, us, sources of 10, 30 and 60 tokens: 61 sentences of 4 hypotheses
+// 448 / 465, 459 / 468, 467 / 474; 64 of 4 448 / 464, 462 / 467, 469 / 475; 64 of 3 429 / 449, 437 / 458, 445 / 469; 62 of 3
+// 425 / 447, 434 / 456, 440 / 467; 128 of 2 458 / 465, 466 / 471, 473 / 479.  Shapes without a stack kernel (d_ffn = 2 d), 30
+// tokens: 16 heads, 31 sentences 364 / 378, 32 of 3 353 / 375; 8 heads, 63 of 4 310 / 312, 64 of 3 302 / 317.  Not one round (translations of
+// the big model, 48 sentences = 384 workgroups): 51.9 -> 54.4 ms; workgroups of one sentence (8 heads, 32 sentences): 34.7 -> 34.8;
+// above 256 rows (128 sentences of mixed lengths 67.5 -> 68.3, d = 512, 100 sentences 38.7 -> 42.0) a workgroup waits for its longest sentence.
 bool cross_attention_q_worthwhile(int batch, int beam, int H) {
   if (batch * beam > 256) return false;
   const int GS = cross_q_group(batch, H);
