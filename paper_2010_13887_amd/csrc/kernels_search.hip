@@ -833,7 +833,7 @@ __global__ void __launch_bounds__(64) sample_kernel(const float* __restrict__ ca
 }
 
 // Retrieve (the k largest logits from the logit product's group statistics) and draw in one launch: a wavefront
-// per row, four rows per workgroup; the candidates stay in LDS, the first lane draws.  nx.E given (encoder-decoder
+// per row, four rows per workgroup; the candidates stay in LDS, the row's wavefront draws.  nx.E given (encoder-decoder
 // models): the row's next decoder input is written as well (a finished row: nothing; its logits are not used).
 template <int GPL>
 __global__ void __launch_bounds__(256) retrieve_sample_kernel(const float* __restrict__ logits, const float* __restrict__ stats,

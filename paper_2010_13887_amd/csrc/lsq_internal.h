@@ -197,7 +197,7 @@ StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src);
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init
 hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s);   // as if a wait had run out
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
-size_t stack_rows_bytes(int arch, int M, int d);   // of one set
+size_t stack_rows_bytes(int arch, int M, int d);   // of one set; 0: no such kernel for this width
 hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s);
 // float32 (kernels_stack_f32.hip): the matrices are copies made by launch_pack_f32 (16-column units, columns up to a multiple of 64, K of 4), vectors, cache and rows float32
 size_t stack_f32_bytes(int M, int d);

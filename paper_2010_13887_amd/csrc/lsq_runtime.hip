@@ -181,7 +181,7 @@ constexpr unsigned char kCanaryByte = 0xA5;
 struct Plan {
   std::vector<size_t> canaries;       // red zones behind the regions that live as long as the model
   std::vector<size_t> dec_canaries;   // ... behind the decoder's intermediates (valid from the end of lsq_encode on)
-  size_t stack_exchange, stack_set, stack_rows_exchange, stack_rows_set, stack_state;   // decoder stack in one launch (few rows); stack_rows_set = 0: not for this shape
+  size_t stack_exchange, stack_set, stack_rows_exchange, stack_rows_set, stack_state;   // decoder stack in one launch: 8-row groups; more rows, float32 (sets of 0 bytes: no such kernel for this shape)
   size_t weights, wpacked, pe, cache, cross, score, tokens, len, fin, parent, anc, pen_tok, pen_n, cand_plain, cap, order, src_off, src_len, active, step_state,
       cand_score, cand_idx, out_ids, out_lens, out_scores, scratch, total;
   // encoder view of scratch
@@ -280,10 +280,11 @@ size_t blob_bytes(const HParams& hp) {
   return n;
 }
 
-// Fragment-ordered second copies of the float16 matrices (products of at most 64 rows read these).
 // packed float32 matrices of one decoder layer of an encoder-decoder model
 size_t layer_bytes_f32(const HParams& hp) { return ((size_t)6 * hp.d * hp.d + (size_t)2 * hp.d * hp.F) * 4; }
 
+// Second copies of the matrices in the order in which the kernels' lanes hold them: float16 for the products of at most 64 rows
+// and the stack kernels, float32 for the stack and the small-model kernels.
 size_t packed_weight_bytes(const HParams& hp) {
   if (hp.dtype != DT_F16) {   // the decoder's matrices, for the kernels that run whole steps
     const bool small = small_step_supported(hp.arch, hp.H, hp.d, hp.F, hp.V, 1);
@@ -409,7 +410,8 @@ int setup_stack() {
   g.stack_ok = false;
   g.small_ok = false;
   const bool small = small_step_supported(hp.arch, hp.H, hp.d, hp.F, hp.V, g.beam);
-  if (!p.stack_rows_set && !small) return LSQ_OK;
+  const bool stack = p.stack_set || p.stack_rows_set;
+  if (!stack && !small) return LSQ_OK;
   const int d = hp.d, F = hp.F, L = hp.n_dec;
   const size_t es = esz();
   StackArgs& a = g.stack;
@@ -472,7 +474,7 @@ int setup_stack() {
   a.state = at<int32_t>(p.stack_state); a.error = &g.page->error;
   a.layers = L; a.T = g.max_len; a.anc_ld = g.max_len + 1; a.eps = hp.eps;
   a.beam = g.beam;
-  g.stack_ok = p.stack_rows_set != 0 && stream_has_every_cu(g.stream);
+  g.stack_ok = stack && stream_has_every_cu(g.stream);
   if (small) {
     char* E = g.ws + p.wpacked + L * layer_bytes_f32(hp);
     if (hp.dtype == DT_F32) HIPCHK(launch_pack_f32(g.E, E, hp.V, d, g.stream));
@@ -516,8 +518,11 @@ hipError_t launch_stack(StackKind kind, StackArgs a) {
 
 hipError_t reset_stack() {
   const Plan& p = g.plan;
-  hipError_t e = !p.stack_set ? hipSuccess : launch_stack_reset(g.ws + p.stack_exchange, 2 * p.stack_set, at<int32_t>(p.stack_state), g.stream);
-  return e == hipSuccess ? launch_stack_reset(g.ws + p.stack_rows_exchange, 2 * p.stack_rows_set, at<int32_t>(p.stack_state) + 8, g.stream) : e;
+  int32_t* state = at<int32_t>(p.stack_state);
+  hipError_t e = hipSuccess;
+  if (p.stack_set) e = launch_stack_reset(g.ws + p.stack_exchange, 2 * p.stack_set, state, g.stream);
+  if (e == hipSuccess && p.stack_rows_set) e = launch_stack_reset(g.ws + p.stack_rows_exchange, 2 * p.stack_rows_set, state + 8, g.stream);
+  return e;
 }
 
 // All launches of one decode step for the first B sentences (B*k rows).  Nothing here depends on
@@ -1209,7 +1214,7 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
 
   g.hp = hp;
   g.plan = plan;
-  if (plan.stack_rows_set) HIPCHK(reset_stack());
+  HIPCHK(reset_stack());
   g.max_batch = max_batch; g.beam = beam; g.max_len = max_len;
   size_t i = 0;
   g.E = dev[i++];
