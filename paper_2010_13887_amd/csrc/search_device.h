@@ -26,7 +26,10 @@ __device__ __forceinline__ bool precedes(float s1, int i1, float s2, int i2) {
 // Rows where more than QMAX groups or CMAX tokens reach R (long runs of equal logits) fall back to k
 // exact rounds over the whole row.  Same output as row_topk_kernel (no diverse groups); raw: the k largest
 // logits themselves (sampling), no score, no normaliser.
-constexpr int kTopkGroupsQ = 64, kTopkGroupsC = 128;   // groups / tokens that may reach the threshold before the fallback
+// Groups / tokens that may reach the threshold before the fallback, in which one wavefront goes over the row k times (4.5 ms at
+// k = 32, 50257 tokens).  With k = 32 of nearly flat logits some 43 groups reach it, 58 to 70 in one row out of 300: a list of 64
+// overflowed in every other generation of 32 rows x 128 tokens (33.5 -> 37.8 ms).
+constexpr int kTopkGroupsQ = 128, kTopkGroupsC = 160;
 
 // One row by one wavefront; ql, cs, ci: the wavefront's own LDS lists (kTopkGroupsQ, kTopkGroupsC entries); os, oi:
 // where the k pairs go (global memory or LDS).

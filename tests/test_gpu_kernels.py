@@ -689,6 +689,29 @@ def test_largest_logits_from_group_statistics(env, M, V, k, case):
     assert (got_i[:, kk:] == -1).all() and np.isneginf(got_s[:, kk:]).all()
 
 
+@pytest.mark.parametrize("n", [64, 65, 127, 128, 129, 160])
+def test_as_many_groups_as_the_list_holds(env, n):
+    """k = 32: n groups of 32 tokens reach the threshold (the 32nd best of 64 interleaved sets of groups), around the length of the
+    kernel's list of them and past it, where the row is searched in full."""
+    lsq, torch = env
+    rng = np.random.default_rng(n)
+    V, k = 32 * 640, 32
+    G = V // 32
+    logits = (rng.standard_normal((2, V)) * 0.1).astype(np.float32)
+    for r in range(2):
+        sets = rng.permutation(64)[:32]
+        high = [s for s in sets] + [s + 64 * q for q in range(1, 10) for s in sets[1:]][: n - 32]   # set sets[0]: one group, the lowest
+        logits[r, np.array(high) * 32 + rng.integers(0, 32, n)] = np.concatenate([[2.0], 3.0 + rng.permutation(n - 1) / 64])
+    grp = logits.reshape(2, G, 32)
+    stats = np.stack([grp.max(-1), np.exp(grp - grp.max(-1, keepdims=True)).sum(-1)], axis=-1).astype(np.float32)
+    os_ = torch.zeros(2, k, dtype=torch.float32, device="cuda")
+    oi = torch.zeros(2, k, dtype=torch.int32, device="cuda")
+    lsq.k_row_topk_groups(_dev(torch, logits), _dev(torch, stats), None, None, k, 2, os_, oi, raw=True)
+    order = np.argsort(-logits, axis=1, kind="stable")[:, :k]
+    assert np.array_equal(oi.cpu().numpy(), order)
+    assert np.array_equal(os_.cpu().numpy(), np.take_along_axis(logits, order, 1))
+
+
 def _state(rng, B, k, V, T, t, eos, finished_frac):
     M = B * k
     tokens = rng.integers(4, V, size=(M, T + 1)).astype(np.int32)
