@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
 
   Exchange ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange, (short)0, (int)(2 * a.set_bytes), 0x00027000);
-  ex.dead = seq < 0;
+  ex.polls = seq < 0 ? 1 : kSpinLimit;
   const int group_bytes = Rg::size * D * rp;
   auto at = [&](int l, int region) { return ((start + l) & 1) * (int)a.set_bytes + grp * group_bytes + region * D * rp; };
   const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};

@@ -23,33 +23,33 @@ __device__ __forceinline__ unsigned publish_word(unsigned v) { return v == kSent
 __device__ __forceinline__ const __attribute__((address_space(4))) StackArgs* now() { return arguments<StackArgs>(); }
 
 // Set in the first word of StackArgs::state at the end of a launch in which a wait ran out (the word the kernels read first
-// anyway: a word of its own and its test before every wait cost 0.5 us a step).  A launch that finds it set looks once where it would wait: the steps queued
+// anyway: a word of its own cost 0.5 us a step).  A launch that finds it set looks once where it would wait: the steps queued
 // behind the one that gave up end at once instead of each waiting out the limit.
 constexpr int kGaveUp = (int)0x80000000u;
 
 struct Exchange {
   __amdgpu_buffer_rsrc_t rsrc;
-  bool dead;   // what this workgroup reads from now on may be missing
+  int polls;   // of a wait; 1: one has run out, what this wavefront reads from now on may be missing
 
   // v[i] = the 16 bytes at base(i) + lane(i) once all of them have been written (base: the same in all lanes)
   template <int N, typename B, typename L>
   __device__ __forceinline__ void wait(B base, L lane, u32x4 (&v)[N]) {
-    for (int left = kSpinLimit;;) {
+    for (int left = polls;;) {
 #pragma unroll
       for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane(i), base(i), kAgent);
       unsigned worst = 0;
 #pragma unroll
       for (int i = 0; i < N; ++i) worst = max(max(worst, max(v[i].x, v[i].y)), max(v[i].z, v[i].w));
       if (__all(worst != kSentinel)) return;
-      if (dead || --left == 0) break;
+      if (--left == 0) break;
       __builtin_amdgcn_s_sleep(1);
       asm volatile("" ::: "memory");
     }
-    dead = true;
+    polls = 1;
   }
   // at the end of the kernel: tells the launches behind this one, and the host
   __device__ __forceinline__ void report(int32_t* state, int* error) {
-    if (!dead) return;
+    if (polls > 1) return;
     __hip_atomic_fetch_or(state, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
