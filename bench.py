@@ -105,6 +105,15 @@ def class_work(name, hp, B, k, t_mean, s_mean):
         return (2.0 * M * 4 * d * d + 4.0 * M * t_mean * d, 4 * d * d * es + 2 * M * t_mean * d * es + (2 + hp.n_heads) * M * d * 4)
     if name == "cross_block":    # LayerNorm over the head slabs + Q + attention + per-head output projection
         return (2.0 * M * 2 * d * d + 4.0 * M * s_mean * d, 2 * d * d * es + 2 * B * s_mean * d * es + 2 * hp.n_heads * M * d * 4)
+    if name == "decoder_stack":  # all decoder layers: every matrix, the histories and the sources' keys and values once; the
+        # whole step where the model is small enough for that (the embedding and the logits as well)
+        cross = hp.arch == 0
+        w = (6 if cross else 4) * d * d + 2 * d * F
+        flops = L * (2.0 * M * w + 4.0 * M * t_mean * d + (4.0 * M * s_mean * d if cross else 0.0))
+        nbytes = L * (w + 2 * M * t_mean * d + (2 * B * s_mean * d if cross else 0)) * es + 2 * M * d * es
+        if cross and d <= 128:
+            flops, nbytes = flops + 2.0 * M * V * d, nbytes + V * d * es + M * V * 4
+        return (flops, nbytes)
     if name == "add_layernorm":
         return (8.0 * M * d, 3 * M * d * es)
     if name == "embed":
