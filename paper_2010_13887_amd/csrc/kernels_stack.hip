@@ -61,7 +61,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   __shared__ __attribute__((aligned(16))) sum_t us[kRows][D + 16 / ES];   // residual sums (pre-LN: the residual stream)
   __shared__ __attribute__((aligned(16))) float part[kWaves][NU > UQ ? NU : UQ][kRows][16];
   __shared__ __attribute__((aligned(16))) float part2[kWaves][kRows][16];
-  __shared__ float att_o[kWaves][64], att_m[kWaves], att_l[kWaves];
+  __shared__ __attribute__((aligned(16))) float att_o[kWaves][64];
+  __shared__ float att_m[kWaves], att_l[kWaves];
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -530,7 +531,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   __shared__ __attribute__((aligned(16))) float part[kWaves][4][R][16];
   __shared__ __attribute__((aligned(16))) half_t xrow[D];                  // the residual of the row this workgroup owns
   __shared__ float stat[DK][2];
-  __shared__ float att_o[kWaves][64], att_m[kWaves], att_l[kWaves];
+  __shared__ __attribute__((aligned(16))) float att_o[kWaves][64];
+  __shared__ float att_m[kWaves], att_l[kWaves];
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
