@@ -31,13 +31,6 @@ namespace {
 constexpr int kRows = 8;               // rows of a group
 constexpr int kMinRows = 4;            // a writer's piece is at least as large as for these: several writers in one line slow each other down
 
-// Byte offsets of a row's intermediates inside one layer's region (d: row width)
-template <bool PRE> struct Region {
-  static constexpr int qkv = 0, ctx = 6, u1 = 8;
-  static constexpr int q2 = PRE ? 0 : 12, ctx2 = PRE ? 0 : 14, u2 = PRE ? 0 : 16;   // cross-attention: post-LN models
-  static constexpr int ff = PRE ? 10 : 20, u3 = PRE ? 18 : 28, size = PRE ? 20 : 32;
-};
-
 // DK: d / 256.  X: workgroups of a group per 16 columns of d (W = d / 16 * X): the products with d columns take 16 / X
 // columns per workgroup, those with 3d and 4d columns ceil(3 / X) and 4 / X units of 16.  PRE: pre-LN, no cross-attention.
 //
@@ -1023,9 +1016,10 @@ Choice choose(int arch, int M, int d) {
 
 const void* kernel_of(int dk, int x, int pre) {
 #define LSQ_STACK(DKV, XV) if (dk == DKV && x == XV) return pre ? (const void*)decoder_stack_kernel<DKV, XV, true> : (const void*)decoder_stack_kernel<DKV, XV, false>
-  if (!pre && x == 4) return dk == 1 ? (const void*)decoder_stack_kernel<1, 4, false> : dk == 2 ? (const void*)decoder_stack_kernel<2, 4, false> : nullptr;
+  if (!pre && x == 4) return dk == 1 ? (const void*)decoder_stack_kernel<1, 4, false> : nullptr;
+  if (dk == 2)   // post-LN models: the die kernel, at every length
+    return !pre ? nullptr : x == 1 ? (const void*)decoder_stack_kernel<2, 1, true> : x == 2 ? (const void*)decoder_stack_kernel<2, 2, true> : nullptr;
   LSQ_STACK(1, 1); LSQ_STACK(1, 2);
-  LSQ_STACK(2, 1); LSQ_STACK(2, 2);
   LSQ_STACK(3, 1); LSQ_STACK(3, 2);
   LSQ_STACK(4, 1); LSQ_STACK(4, 2);
 #undef LSQ_STACK
@@ -1057,6 +1051,7 @@ const void* rows_kernel_of(int dk, int mb, int pre) {
 }  // namespace
 
 size_t stack_exchange_bytes(int arch, int M, int d, int layers) {
+  if (const size_t n = die_exchange_bytes(arch, M, d, layers)) return n;
   return (size_t)(min(M, kStackRowsMax) + kRows) * layers * (arch == 1 ? Region<true>::size : Region<false>::size) * d;
 }
 
@@ -1099,8 +1094,9 @@ bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers)
 // One row per sentence shares nothing, and only the widest case crosses: d = 1024, 128 rows 898 / 958 at 1008, 1418 / 1391 at
 // 1900; d = 768 pre-LN, 160 rows 2307 / 2493 at 1980.  A source key counts as a quarter or half of one of the history (position
 // 16, sources of 2000: d = 512, 128 rows 460 / 458, 256 rows 791 / 784; d = 1024, 32 rows 363 / 433, 128 rows 862 / 825).
-StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src) {
+StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool dies) {
   if (M < 1) return kStackNone;
+  if (dies && die_supported(arch, M, d, beam, pos, src)) return kStackDie;
   const Choice c = choose(arch, M, d), r = choose_rows(M, d);
   bool few = c.x != 0 && M <= kStackRowsMax && kernel_of(c.dk, c.x, arch == 1) && resident(kernel_of(c.dk, c.x, arch == 1));
   bool many = r.x != 0 && rows_kernel_of(r.dk, r.x, arch == 1) && resident(rows_kernel_of(r.dk, r.x, arch == 1));

@@ -1,0 +1,700 @@
+// Decoder layers of one step in one launch, each group of rows on a die of its own (float16, heads of 64, FFN of 4d).
+//
+// The chip is eight dies with 32 compute units and an L2 each.  What the workgroups of one die hand each other need not leave
+// its L2: plain stores, which end there, read with agent-scope loads, which look there (a workgroup's own L1 is passed by).
+// Measured, 32 workgroups that all write a slice and read all of 8 KB: 0.50 us per exchange, against 0.99 with agent-scope
+// stores and 1.16 among 128 workgroups all over the chip (kernels_stack.hip).  The price is that every die reads all weights:
+// 1.34 TB/s for one die or two, 1.0 for four, 0.92 for all eight (7.4 TB/s together, from the memory-side cache).  So this is for
+// models whose layers are small (d = 512: 44 MB, 48 us).
+//
+// A compute unit's loads come back in the order in which they were issued, whoever issued them: one that finds its line in the
+// L2 takes 240 clocks on an idle unit, 560 / 790 / 1590 / 2640 behind 8 / 16 / 32 / 64 KB of weights.  When weights are
+// requested therefore decides how long an exchange takes: each time a wait has ended and there is something to compute.
+//
+// Group g is workgroups g, g + 8, g + 16 ..: workgroups are dealt to the dies in turn.  die_placement() looks whether they are when
+// a model is loaded, and every workgroup looks whether it is where it was then: one that is not gives up at once, which ends as
+// any wait that runs out does (kernels_stack.hip).  The exchange itself is that of kernels_stack.hip too: data that is its own flag.
+#include "stack_exchange.h"
+
+namespace lsq {
+
+namespace {
+
+constexpr int kDieThreads = 1024;      // eight wavefronts that multiply, eight that exchange
+constexpr int kDieGroup = 32;          // workgroups of a group: one per compute unit of a die
+constexpr int kDies = 8;
+
+typedef half_t half2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ unsigned die_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)); }   // XCC_ID, 4 bits
+__global__ void die_of_workgroup_kernel(unsigned* out) {
+  if (threadIdx.x == 0) out[blockIdx.x] = die_id();
+}
+
+__device__ __forceinline__ void workgroup_barrier() {   // LDS only: loads stay in flight
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void pin() { asm volatile("" ::: "memory"); }   // requests stay where they are written
+
+// error against 64 bits: that of a chain of float multiply-adds
+__device__ __forceinline__ float dot8(const half8_t& x, const half8_t& y) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_fdot2(half2_t{x[2 * i], x[2 * i + 1]}, half2_t{y[2 * i], y[2 * i + 1]}, s, false);
+  return s;
+}
+
+// Sums over the eight lane groups of values that belong to columns c8 .. c8 + 7 in each: a lane is left with two of them,
+// own_column() and the next, in v[0] and v[1] (14 instructions; all eight in every lane would be 72).
+__device__ __forceinline__ void column_sums(float (&v)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v[i]), __builtin_bit_cast(unsigned, v[i + 4]), false, false);
+    const unsigned x = r[0], y = r[1];
+    v[i] = __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v[i]), __builtin_bit_cast(unsigned, v[i + 2]), false, false);
+    const unsigned x = r[0], y = r[1];
+    v[i] = __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
+  }
+  v[0] = add_lane_xor<8>(v[0]);
+  v[1] = add_lane_xor<8>(v[1]);
+}
+__device__ __forceinline__ int own_column(int lane) { return (lane & 7) * 8 + (lane >> 4 & 1) * 2 + (lane >> 5) * 4; }   // of the head's 64
+
+// ---------------------------------------------------------------------------------------------
+// Few rows, d = 512: up to 16 a die.  Eight wavefronts hold the matrices in registers (an eighth of k each), ask for the next
+// ones and multiply; the other eight look for the exchanged values, normalise, attend, add the eight partial sums up and
+// publish.  Nobody waits for a value behind weights of its own this way, and 128 registers are enough for either.
+// Measured, layers of one step in us (before: groups of 8 rows or of 16 all over the chip): 4 rows 91 -> 77, 32 rows 109 -> 90,
+// 64 rows 117 -> 99, 128 rows 137 -> 123.  Bound by the chain of eight exchanges and products a layer (10 us without
+// weights) and by the weights behind which the exchanges queue (6 us of a layer's 12.5 on a single die, 8 on eight).
+template <int R, bool PRE>
+__global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArgs a) {
+  constexpr int DK = 2, D = 256 * DK, H = D / 64, W = kDieGroup, NT = D / W;
+  constexpr int TEAMS = R * H / W, NSH = kWaves / TEAMS;         // wavefronts that share a (row, head) pair
+  constexpr int U = 4;                                           // keys of a lane group in flight
+  using Rg = Region<PRE>;
+  constexpr int ES = PRE ? 2 : 4;                                // bytes of a residual sum
+  constexpr int VP = 16 / ES, NP = D / (64 * VP);                // values of a 16-byte piece, pieces of a row per lane
+  constexpr int RW = (R + kWaves - 1) / kWaves;                  // rows of a wavefront
+  using sum_t = std::conditional_t<PRE, half_t, float>;
+  static_assert(NT == 16, "one unit of columns per workgroup");
+
+  __shared__ __attribute__((aligned(16))) half_t xs[R][D + 8];             // normalised rows
+  __shared__ __attribute__((aligned(16))) half_t us[PRE ? R : 1][D + 8];   // pre-LN: the residual stream
+  __shared__ __attribute__((aligned(16))) half_t st[R][4 * D + 8];         // contexts, FFN activations
+  __shared__ __attribute__((aligned(16))) float part[kWaves][4][R][16];
+  __shared__ __attribute__((aligned(16))) float att_o[kWaves][64];
+  __shared__ float att_m[kWaves], att_l[kWaves];
+  __shared__ unsigned first_key[kWaves][U][64];
+  __shared__ __attribute__((aligned(16))) half_t vec[2][7][D];   // of a layer: gains and shifts, biases
+
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = a.groups, grp = blockIdx.x & (kDies - 1);
+  int j = blockIdx.x >> 3;
+  if (grp >= G) return;
+  const int r0 = grp * a.rows_per_group, rows = min(a.rows_per_group, a.M - r0);
+  const int seq = a.state[0], parity = seq & 1, dirty = a.state[2 - parity], pos = *a.tpos;
+
+  Exchange<0> ex;   // plain stores: they stop at the die's L2, where the readers' agent-scope loads look
+  ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
+  ex.polls = seq < 0 || die_id() != (a.dies >> (4 * grp) & 15) ? 1 : kSpinLimit;
+  const int layer_bytes = Rg::size * D * R;
+  auto at = [&](int l, int region) { return grp * a.layers * layer_bytes + l * layer_bytes + region * D * R; };
+
+  if (wave < kWaves) {
+    // ================ products: wavefront w has an eighth of k; matrices wait in registers
+    const int lane = tid & 63, kc = lane >> 4, fm = lane & (R - 1);
+    const unsigned lane16 = (unsigned)(kc >> 1) * 1024 + ((lane & 15) + 32 * (kc & 1)) * 16;
+    // the first of this wavefront's S k-steps of a unit of 16 columns
+    auto slice = [&](const half_t* Wp, int unit, int S) {
+      return reinterpret_cast<const char*>(global(Wp)) + (size_t)(unit >> 1) * (S * 16384) + (unit & 1) * 256 + wave * S * 2048;
+    };
+    const char* p_q[3] = {slice(a.Wqkv, j, DK), slice(a.Wqkv, j + W, DK), slice(a.Wqkv, j + 2 * W, DK)};
+    const char* p_1[4] = {slice(a.W1, j, DK), slice(a.W1, j + W, DK), slice(a.W1, j + 2 * W, DK), slice(a.W1, j + 3 * W, DK)};
+    const char *p_o = slice(a.Wo, j, DK), *p_2 = slice(a.W2, j, 4 * DK);
+    const char *p_c = PRE ? nullptr : slice(a.Wq, j, DK), *p_e = PRE ? nullptr : slice(a.Woc, j, DK);
+    auto frag = [&](const char* p, int s) { return *reinterpret_cast<const half8_t*>(p + s * 2048 + lane16); };
+    const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](const half8_t* w, auto units, auto steps, const half_t* in, int ld) {
+      constexpr int N = decltype(units)::value, S = decltype(steps)::value;
+      floatx4 acc[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] = zero4;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const half8_t x8 = *reinterpret_cast<const half8_t*>(in + fm * ld + (wave * S + s) * 32 + kc * 8);
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i * S + s], x8, acc[i], 0, 0, 0);
+      }
+      if ((lane & 15) < R) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) *reinterpret_cast<floatx4*>(&part[wave][i][lane & 15][kc * 4]) = acc[i];
+      }
+    };
+    using n1 = std::integral_constant<int, 1>;
+    using n3 = std::integral_constant<int, 3>;
+    using n4 = std::integral_constant<int, 4>;
+    using k1 = std::integral_constant<int, DK>;
+    using k4 = std::integral_constant<int, 4 * DK>;
+    // w1: the second half of it Wo's until that is used; q: Wq and Woc once Wqkv is used
+    half8_t w1[8], q[6], w2[8], wo[PRE ? 2 : 1];
+    auto some = [&](half8_t* w, const char* p, size_t o, int s, int n) {
+#pragma unroll
+      for (int i = 0; i < n; ++i) w[i] = frag(p + o, s + i);
+    };
+    half8_t* const o_at = PRE ? wo : w1 + 6;
+    size_t o = 0;   // of the layer
+    for (int i = 0; i < 3; ++i) some(q + 2 * i, p_q[i], 0, 0, 2);
+    some(o_at, p_o, 0, 0, 2);
+    pin();
+    const half_t* const x = &xs[0][0];
+    const half_t* const y = &st[0][0];
+    // Each time the exchanging wavefronts have what they looked for there is nothing to wait for in memory for a
+    // while, and the next matrices are requested.
+    if constexpr (!PRE) {
+    for (int l = 0; l < a.layers; ++l) {
+      const size_t next = l + 1 < a.layers ? o + a.packed_stride : o;
+      workgroup_barrier(); some(w1 + 0, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 2); some(w2 + 0, p_2, o, 0, 1); pin(); workgroup_barrier();
+      multiply(q, n3{}, k1{}, x, D + 8); workgroup_barrier();
+      workgroup_barrier(); some(q, p_c, o, 0, 2); some(q + 2, p_e, o, 0, 2); some(w1 + 4, p_1[2], o, 0, 2); pin(); workgroup_barrier();
+      workgroup_barrier();  multiply(o_at, n1{}, k1{}, y, 4 * D + 8); pin(); workgroup_barrier();
+      workgroup_barrier(); some(w1 + 6, p_1[3], o, 0, 2); some(w2 + 1, p_2, o, 1, 3); pin(); workgroup_barrier();
+      multiply(q, n1{}, k1{}, x, D + 8); workgroup_barrier();
+      workgroup_barrier(); some(w2 + 4, p_2, o, 4, 4); pin(); workgroup_barrier();
+      workgroup_barrier();  multiply(q + 2, n1{}, k1{}, y, 4 * D + 8); pin(); workgroup_barrier();
+      workgroup_barrier(); some(q + 0, p_q[0], next, 0, 2); some(q + 2, p_q[1], next, 0, 2); some(q + 4, p_q[2], next, 0, 2); pin(); workgroup_barrier();
+      multiply(w1, n4{}, k1{}, x, D + 8); workgroup_barrier();
+      workgroup_barrier(); some(o_at, p_o, next, 0, 2); multiply(w2, n1{}, k4{}, y, 4 * D + 8); pin(); workgroup_barrier();
+      o = next;
+    }
+    } else {
+    for (int l = 0; l < a.layers; ++l) {
+      const size_t next = l + 1 < a.layers ? o + a.packed_stride : o;
+      workgroup_barrier();                                                // sums of the layer before
+      some(w1, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 2);
+      if constexpr (PRE) some(w1 + 4, p_1[2], o, 0, 1);
+      pin();
+      workgroup_barrier();                                                // input rows
+      multiply(q, n3{}, k1{}, x, D + 8);
+      workgroup_barrier();
+      workgroup_barrier();                                                // q, k, v
+      if constexpr (!PRE) { some(q, p_c, o, 0, 2); some(q + 2, p_e, o, 0, 2); some(w1 + 4, p_1[2], o, 0, 2); some(w2, p_2, o, 0, 1); }
+      else { some(w1 + 5, p_1[2], o, 1, 1); some(w1 + 6, p_1[3], o, 0, 2); some(w2, p_2, o, 0, 2); }
+      pin();
+      workgroup_barrier();                                                // attention
+      workgroup_barrier();                                                // context
+      if constexpr (PRE) some(w2 + 2, p_2, o, 2, 5);
+      multiply(o_at, n1{}, k1{}, y, 4 * D + 8);
+      pin();
+      workgroup_barrier();
+      if constexpr (!PRE) {
+        workgroup_barrier();                                              // sums
+        some(w1 + 6, p_1[3], o, 0, 2); some(w2 + 1, p_2, o, 1, 2);
+        pin();
+        workgroup_barrier();                                              // rows
+        multiply(q, n1{}, k1{}, x, D + 8);
+        workgroup_barrier();
+        workgroup_barrier();                                              // queries
+        some(w2 + 3, p_2, o, 3, 5);
+        pin();
+        workgroup_barrier();                                              // attention
+        workgroup_barrier();                                              // context
+        multiply(q + 2, n1{}, k1{}, y, 4 * D + 8);
+        pin();
+        workgroup_barrier();
+      }
+      workgroup_barrier();                                                // sums
+      if constexpr (PRE) some(w2 + 7, p_2, o, 7, 1); else some(q + 4, p_q[2], next, 0, 2);
+      some(q, p_q[0], next, 0, 2); some(q + 2, p_q[1], next, 0, 2);
+      pin();
+      workgroup_barrier();                                                // rows
+      multiply(w1, n4{}, k1{}, x, D + 8);
+      workgroup_barrier();
+      workgroup_barrier();                                                // activations
+      if constexpr (PRE) some(q + 4, p_q[2], next, 0, 2);
+      some(o_at, p_o, next, 0, 2);
+      multiply(w2, n1{}, k4{}, y, 4 * D + 8);
+      pin();
+      workgroup_barrier();
+      o = next;
+    }
+    }
+    if (tid == 0) {   // the last workgroup to get here: all have read the counters
+      const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (n == G * W - 1) {
+        a.state[4] = 0;
+        a.state[1 + parity] = G * R;
+        __hip_atomic_fetch_xor(a.state, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    return;
+  }
+
+  // ================ exchange, LayerNorm, attention
+  int xt = tid - kWaves * 64, lane = tid & 63, xw = wave - kWaves;
+  // gains, shifts and this workgroup's biases: 16 bytes of one of them per lane, on their way to LDS
+  const char* vec_at;   // of the next layer
+  if (xw < 6) {
+    const half_t* v = xw == 0 ? a.ln1g : xw == 1 ? a.ln1b : xw == 2 ? a.ln2g : xw == 3 || PRE ? a.ln2b : xw == 4 ? a.ln3g : a.ln3b;
+    vec_at = reinterpret_cast<const char*>(v + lane * 8);
+  } else {
+    const int u = min(lane >> 1, 10);   // units: q k v | o | c | e | w1 x 4 | w2
+    const half_t* v = u < 3 ? a.bqkv : u == 3 || (PRE && u < 6) ? a.bo : u == 4 ? a.bq : u == 5 ? a.boc : u < 10 ? a.b1 : a.b2;
+    vec_at = reinterpret_cast<const char*>(v + (u < 3 ? j + W * u : u < 6 || u == 10 ? j : j + W * (u - 6)) * 16 + (lane & 1) * 8);
+  }
+  auto vectors = [&] { const half8_t v = *reinterpret_cast<const half8_t*>(global(vec_at)); vec_at += a.plain_stride; return v; };
+  auto keep_vectors = [&](int l, const half8_t& v) {
+    if (xw < 6) *reinterpret_cast<half8_t*>(&vec[l & 1][xw][lane * 8]) = v;
+    else if (xw == 6 && lane < 22) *reinterpret_cast<half8_t*>(&vec[l & 1][6][lane * 8]) = v;
+  };
+  keep_vectors(0, vectors());
+  // ---- what the products leave: unit, row and pair of columns that this thread finishes
+  int ui = xt / (8 * R), um = xt / 8 % R, un = xt % 8 * 2;
+  auto total = [&](float& v0, float& v1) {
+    v0 = part[0][ui][um][un]; v1 = part[0][ui][um][un + 1];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) { v0 += part[w][ui][um][un]; v1 += part[w][ui][um][un + 1]; }
+  };
+  auto bias = [&](int l, int unit) { return *reinterpret_cast<const half2_t*>(&vec[l & 1][6][unit * 16 + un]); };
+  auto residual = [&](int l, int region, int unit) {
+    if (ui < 1 && um < rows) {
+      float v0, v1;
+      total(v0, v1);
+      const half2_t bi = bias(l, unit);
+      const half_t* x = PRE ? &us[um][j * 16 + un] : &xs[um][j * 16 + un];
+      const float s0 = (float)x[0] + (v0 + (float)bi[0]), s1 = (float)x[1] + (v1 + (float)bi[1]);
+      if constexpr (PRE) ex.put2(at(l, region), (j * R + um) * 32 + un * 2, (half_t)s0, (half_t)s1);
+      else ex.put2(at(l, region), (j * R + um) * 64 + un * 4, s0, s1);
+    }
+  };
+  // ---- rows: wavefront w normalises rows w and w + 8 into xs
+  auto normalise = [&](float (&v)[NP][VP], const half_t (&g)[NP][VP], const half_t (&b)[NP][VP], half_t (&o)[NP][VP]) {
+    float sum = 0.f, sq = 0.f;
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+      for (int i = 0; i < VP; ++i) sum += v[q][i];
+    const float mean = wave_sum(sum) * (1.0f / D);
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+      for (int i = 0; i < VP; ++i) { v[q][i] -= mean; sq += v[q][i] * v[q][i]; }
+    // 1 / sqrt by one Newton step: worst 1.53, mean 0.30 units in the last place against 64 bits (division by the root: 1.96, 0.38)
+    const float var = wave_sum(sq) * (1.0f / D) + a.eps, r = __builtin_amdgcn_rsqf(var);
+    const float rstd = r * (1.5f - 0.5f * var * r * r);
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+      for (int i = 0; i < VP; ++i) o[q][i] = (half_t)((float)g[q][i] * (v[q][i] * rstd) + (float)b[q][i]);
+  };
+  typedef half_t piece_t __attribute__((ext_vector_type(VP)));
+  auto pieces = [&](const half_t* p, half_t (&o)[NP][VP]) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const piece_t h = *reinterpret_cast<const piece_t*>(p + (q * 64 + lane) * VP);
+#pragma unroll
+      for (int i = 0; i < VP; ++i) o[q][i] = h[i];
+    }
+  };
+  auto put_pieces = [&](half_t* p, const half_t (&o)[NP][VP]) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      piece_t h;
+#pragma unroll
+      for (int i = 0; i < VP; ++i) h[i] = o[q][i];
+      *reinterpret_cast<piece_t*>(p + (q * 64 + lane) * VP) = h;
+    }
+  };
+  auto gather_norm = [&](int l, int region, const half_t* g, const half_t* b, half_t* out_x, half_t* out_y, auto then) {
+    half_t g8[NP][VP], b8[NP][VP];
+    u32x4 raw[RW * NP];
+    const int base = at(l, region);
+    if (xw < rows) {
+    pieces(g, g8);
+    pieces(b, b8);
+    ex.wait([&](int) { return base; },
+            [&](int i) {
+              const int m = min(xw + i / NP * kWaves, rows - 1), q = i % NP * 64 + lane;   // a writer has NT ES bytes of a row
+              return (q / (NT * ES / 16) * R + m) * (NT * ES) + q % (NT * ES / 16) * 16;
+            }, raw);
+    }
+    then();
+#pragma unroll
+    for (int rr = 0; rr < RW; ++rr) {
+      const int m = xw + rr * kWaves;
+      if (m >= rows) break;
+      float v[NP][VP];
+      half_t o[NP][VP];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        typedef sum_t vec_t __attribute__((ext_vector_type(VP)));
+        const vec_t s = __builtin_bit_cast(vec_t, raw[rr * NP + q]);
+#pragma unroll
+        for (int i = 0; i < VP; ++i) v[q][i] = (float)s[i];
+        if constexpr (PRE) {
+          *reinterpret_cast<vec_t*>(&us[m][(q * 64 + lane) * VP]) = s;
+          if (out_x) *reinterpret_cast<vec_t*>(out_x + (size_t)(r0 + m) * D + (q * 64 + lane) * VP) = s;
+        }
+      }
+      normalise(v, g8, b8, o);
+      put_pieces(xs[m], o);
+      if (out_y) put_pieces(out_y + (size_t)(r0 + m) * D, o);
+    }
+  };
+  // ---- staging of what the products without LayerNorm read
+  auto stage_ctx = [&](int l, int region) {
+    constexpr int N = (R * D / 8 + 511) / 512;
+    if (xw * 64 >= rows * (D / 8)) return;
+    u32x4 raw[N];
+    const int base = at(l, region);
+    ex.wait([&](int) { return base; }, [&](int i) { return min(i * 512 + xt, rows * (D / 8) - 1) * 16; }, raw);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int p = i * 512 + xt;
+      if (p < rows * (D / 8)) *reinterpret_cast<u32x4*>(&st[p / (D / 8)][p % (D / 8) * 8]) = raw[i];
+    }
+  };
+  auto stage_ff = [&](int l) {
+    constexpr int N = R * D / 2 / 512;   // 16-byte pieces of units of 16 columns
+    u32x4 raw[N];
+    const int base = at(l, Rg::ff);
+    auto row = [&](int p) { return min(p / 2 % R, rows - 1); };
+    ex.wait([&](int) { return base; },
+            [&](int i) { const int p = i * 512 + xt; return (p / (2 * R) * R + row(p)) * 32 + (p & 1) * 16; }, raw);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int p = i * 512 + xt;
+      *reinterpret_cast<u32x4*>(&st[p / 2 % R][p / (2 * R) * 16 + (p & 1) * 8]) = raw[i];
+    }
+  };
+  // ---- attention of one (row, head) pair per team of NSH wavefronts, of which n have 32 keys or more to look at; a lane
+  // group of 8 holds a key's 64 values
+  const int team = xw / NSH, ash = xw % NSH;
+  int gk = lane >> 3, c8 = (lane & 7) * 8;
+  const int pair = j + W * team, am = min(pair / H, rows - 1), ah = pair % H;
+  const int arow = r0 + am, sent = arow / a.beam;
+  auto team_of = [&](int nkeys) { return pair < rows * H ? min(nkeys <= 32 ? 1 : nkeys <= 64 ? 2 : nkeys <= 128 ? 4 : 8, NSH) : 0; };
+  const int n_self = team_of(pos);
+  const bool table = !PRE && a.anc != nullptr;
+  const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
+  auto slot_of = [&](int p) { return table ? min(max(slots[p], 0), a.beam - 1) : 0; };   // of the sentence's rows
+  auto key_offset = [&](int slot, int p) { return ((slot * a.T + p) * D + c8) * 2; };
+#pragma unroll
+  for (int u = 0; u < U; ++u) {   // the first trip's places in the cache, the same in all layers
+    const int p = max(min(ash + (gk + u * 8) * n_self, pos - 1), 0);
+    first_key[xw][u][lane] = key_offset(slot_of(p), p);
+  }
+  int src_off = 0, src_len = 0;
+  if constexpr (!PRE) { src_off = a.src_off[sent]; src_len = a.src_len[sent]; }
+  const int n_cross = team_of(src_len);
+  half8_t kn[U], vn[U];
+  auto request = [&](bool self, const half_t* Kb, const half_t* Vb, int nkeys, int n, int jb, auto first) {
+    const size_t own = self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0;
+    const char* Kh = reinterpret_cast<const char*>(Kb + own + ah * 64);
+    const char* Vh = reinterpret_cast<const char*>(Vb + own + ah * 64);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u > 0 && jb + u * 8 * n >= nkeys) continue;   // nobody in this wavefront has such a key
+      unsigned o;
+      if (self && first) {
+        o = first_key[xw][u][lane];
+      } else {
+        const int p = max(min(jb + (gk + u * 8) * n, nkeys - 1), 0);
+        o = self ? key_offset(slot_of(p), p) : (p * (2 * D) + c8) * 2;
+      }
+      kn[u] = *reinterpret_cast<const half8_t*>(Kh + o);
+      vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
+    }
+  };
+  auto attend = [&](int l, bool self, const half_t* Kb, const half_t* Vb, int nkeys, int n) {
+    const int region_out = self ? Rg::ctx : Rg::ctx2;
+    constexpr float qscale = 0.125f * 1.44269504088896340736f;   // scores in units of log 2
+    half8_t q, knew, vnew;
+    if (ash < n) {
+      const int lo = (c8 >> 4) * R * 32 + (c8 & 8) * 2;
+      if (self) {
+        u32x4 raw[3];
+        const int base = at(l, Rg::qkv) + (ah * 4 * R + am) * 32;
+        ex.wait([&](int i) { return base + i * (D / 16 * 32) * R; }, [&](int) { return lo; }, raw);
+        q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
+      } else {
+        u32x4 raw[1];
+        const int base = at(l, Rg::q2) + (ah * 4 * R + am) * 32;
+        ex.wait([&](int) { return base; }, [&](int) { return lo; }, raw);
+        q = __builtin_bit_cast(half8_t, raw[0]);
+      }
+    }
+    workgroup_barrier();
+    if (ash < n) {
+      float m = -INFINITY, z = 0.f, acc[8];   // m: of the wavefront
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+      for (int jb = ash; jb < nkeys; jb += U * 8 * n) {   // the same trips in every lane of the wavefront
+        float sc[U], mx = m;
+        half8_t vv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          sc[u] = -INFINITY;
+          if (jb + u * 8 * n >= nkeys) continue;
+          const float s = group_sum<8>(dot8(q, kn[u])) * qscale;
+          if (jb + (gk + u * 8) * n < nkeys) sc[u] = s;
+          vv[u] = vn[u];
+          mx = fmaxf(mx, sc[u]);
+        }
+        const int jn = jb + U * 8 * n;
+        if (jn < nkeys) request(self, Kb, Vb, nkeys, n, jn, std::false_type{});
+        for_lane_bits<8>([&](auto bit) { mx = max_lane_xor<decltype(bit)::value>(mx); });
+        const float corr = __builtin_amdgcn_exp2f(m - mx);   // mx is finite: the wavefront has a key in this trip
+        m = mx;
+        z *= corr;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] *= corr;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (jb + u * 8 * n >= nkeys) continue;
+          const float p = __builtin_amdgcn_exp2f(sc[u] - mx);   // 0 past the last key, which is there again
+          z += p;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc[i] += p * (float)vv[u][i];
+        }
+      }
+      if (self && ash == n - 1) {   // the new position, counted once: by the team's last wavefront
+        const float s = group_sum<8>(dot8(q, knew)) * qscale, mx = fmaxf(m, s);
+        const float corr = __builtin_amdgcn_exp2f(m - mx), p = gk == 0 ? __builtin_amdgcn_exp2f(s - mx) : 0.f;
+        m = mx;
+        z = z * corr + p;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = acc[i] * corr + p * (float)vnew[i];
+      }
+      column_sums(acc);
+      for_lane_bits<8>([&](auto bit) { z = add_lane_xor<decltype(bit)::value>(z); });
+      if (n == 1) {
+        const float inv = 1.0f / z;
+        if ((lane & 8) == 0) ex.put2(at(l, region_out), am * (D * 2) + (ah * 64 + own_column(lane)) * 2, (half_t)(acc[0] * inv), (half_t)(acc[1] * inv));
+      } else {
+        typedef float floatx2 __attribute__((ext_vector_type(2)));
+        *reinterpret_cast<floatx2*>(&att_o[xw][own_column(lane)]) = floatx2{acc[0], acc[1]};
+        if (lane == 0) { att_m[xw] = m; att_l[xw] = z; }
+      }
+    }
+    workgroup_barrier();
+    if (n > 1 && ash == 0) {   // the team's first wavefront: two columns a lane, in both halves alike
+      typedef float floatx2 __attribute__((ext_vector_type(2)));
+      const int c = (lane & 31) * 2;
+      auto merge = [&](auto parts) {
+        constexpr int P = decltype(parts)::value;
+        if constexpr (P <= NSH) {
+          float pm[P], mx = -INFINITY, z = 0.f, o0 = 0.f, o1 = 0.f;
+          floatx2 po[P];
+#pragma unroll
+          for (int w = 0; w < P; ++w) { pm[w] = att_m[xw + w]; po[w] = *reinterpret_cast<const floatx2*>(&att_o[xw + w][c]); }
+#pragma unroll
+          for (int w = 0; w < P; ++w) mx = fmaxf(mx, pm[w]);
+#pragma unroll
+          for (int w = 0; w < P; ++w) {
+            const float cw = __builtin_amdgcn_exp2f(pm[w] - mx);
+            z += att_l[xw + w] * cw;
+            o0 += po[w][0] * cw;
+            o1 += po[w][1] * cw;
+          }
+          const float inv = 1.0f / z;
+          if (lane < 32) ex.put2(at(l, region_out), am * (D * 2) + (ah * 64 + c) * 2, (half_t)(o0 * inv), (half_t)(o1 * inv));
+        }
+      };
+      if (n == 2) merge(std::integral_constant<int, 2>{});
+      else if (n == 4) merge(std::integral_constant<int, 4>{});
+      else merge(std::integral_constant<int, 8>{});
+    }
+  };
+
+  for (int l = 0; l < a.layers; ++l) {
+    // what is derived from a thread's place is derived anew in every layer instead of waiting in registers
+    asm volatile("" : "+v"(xt), "+v"(lane), "+v"(ui), "+v"(um), "+v"(un), "+v"(gk), "+v"(c8));
+    asm volatile("" : "+s"(xw), "+s"(j));
+    const half_t* Kc = reinterpret_cast<const half_t*>(global(now()->cache) + (size_t)(2 * l) * now()->cache_stride);
+    const half_t* Vc = reinterpret_cast<const half_t*>(global(now()->cache) + (size_t)(2 * l + 1) * now()->cache_stride);
+    half8_t ahead = {};
+    auto sums_here = [&] {
+      if (l + 1 < a.layers) ahead = vectors();
+      if (ash < n_self) request(true, Kc, Vc, pos, n_self, ash, std::true_type{});
+      pin();
+      workgroup_barrier();
+    };
+    if (l == 0) {
+      sums_here();
+#pragma unroll
+      for (int rr = 0; rr < RW; ++rr) {
+        const int m = xw + rr * kWaves, r = r0 + m;
+        if (m >= rows) break;
+        if constexpr (PRE) {
+          half_t g8[NP][VP], b8[NP][VP], o[NP][VP];
+          float v[NP][VP];
+          pieces(a.ln1g, g8);
+          pieces(a.ln1b, b8);
+          const half_t* e = a.E + (size_t)embedding_row(a.tokens[(size_t)r * (a.T + 1) + a.len[r]]) * D;
+          embed_row<half_t>(e, a.pe + (size_t)pos * D, us[m], D, 1.0f, lane, 64);   // the lane's own pieces
+          pieces(us[m], o);
+#pragma unroll
+          for (int q = 0; q < NP; ++q)
+#pragma unroll
+            for (int i = 0; i < VP; ++i) v[q][i] = (float)o[q][i];
+          normalise(v, g8, b8, o);
+          put_pieces(xs[m], o);
+        } else {
+          half_t o[NP][VP];
+          pieces(a.x0 + (size_t)r * D, o);
+          put_pieces(xs[m], o);
+        }
+      }
+    } else {
+      if constexpr (PRE) gather_norm(l - 1, Rg::u3, vec[l & 1][0], vec[l & 1][1], nullptr, nullptr, sums_here);
+      else gather_norm(l - 1, Rg::u3, vec[(l - 1) & 1][4], vec[(l - 1) & 1][5], nullptr, nullptr, sums_here);
+    }
+    workgroup_barrier();                                                  // 1
+    workgroup_barrier();                                                  // 2
+    if (ui < 3 && um < rows) {
+      float v0, v1;
+      total(v0, v1);
+      const half2_t bi = bias(l, ui);
+      const half_t h0 = (half_t)(v0 + (float)bi[0]), h1 = (half_t)(v1 + (float)bi[1]);
+      ex.put2(at(l, Rg::qkv), ((j + W * ui) * R + um) * 32 + un * 2, h0, h1);
+      if (ui >= 1) *reinterpret_cast<half2_t*>(const_cast<half_t*>(ui == 1 ? Kc : Vc) + ((size_t)(r0 + um) * a.T + pos) * D + j * 16 + un) = half2_t{h0, h1};
+    }
+    attend(l, true, Kc, Vc, pos, n_self);                               // 3 inside
+    if (l + 1 < a.layers) keep_vectors(l + 1, ahead);
+    stage_ctx(l, Rg::ctx);
+    workgroup_barrier();                                                  // 4
+    workgroup_barrier();                                                  // 5
+    residual(l, Rg::u1, 3);
+    if constexpr (!PRE) {
+      const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
+      gather_norm(l, Rg::u1, vec[l & 1][0], vec[l & 1][1], nullptr, nullptr, [&] {
+        if (ash < n_cross) request(false, kvb, kvb + D, src_len, n_cross, ash, std::true_type{});
+        pin();
+        workgroup_barrier();
+      });
+      workgroup_barrier();                                                // 6
+      workgroup_barrier();                                                // 7
+      if (ui < 1 && um < rows) {
+        float v0, v1;
+        total(v0, v1);
+        const half2_t bi = bias(l, 4);
+        ex.put2(at(l, Rg::q2), (j * R + um) * 32 + un * 2, (half_t)(v0 + (float)bi[0]), (half_t)(v1 + (float)bi[1]));
+      }
+      attend(l, false, kvb, kvb + D, src_len, n_cross);                  // 8 inside
+      stage_ctx(l, Rg::ctx2);
+      workgroup_barrier();                                                // 9
+      workgroup_barrier();                                                // 10
+      residual(l, Rg::u2, 5);
+    }
+    gather_norm(l, PRE ? Rg::u1 : Rg::u2, vec[l & 1][2], vec[l & 1][3], nullptr, nullptr, workgroup_barrier);
+    workgroup_barrier();                                                  // 11
+    workgroup_barrier();                                                  // 12
+    if (ui < 4 && um < rows) {
+      float v0, v1;
+      total(v0, v1);
+      const half2_t bi = bias(l, 6 + ui);
+      v0 += (float)bi[0]; v1 += (float)bi[1];
+      if constexpr (PRE) { v0 = tanh_gelu(v0); v1 = tanh_gelu(v1); }
+      else { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
+      ex.put2(at(l, Rg::ff), ((j + W * ui) * R + um) * 32 + un * 2, (half_t)v0, (half_t)v1);
+    }
+    {   // the other set is for the next launch
+      const size_t n16 = (size_t)dirty * a.layers * (Rg::size * D) / 16, all = (size_t)(G * W) * (kWaves * 64);
+      const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
+      for (size_t i = (size_t)(grp * W + j) * (kWaves * 64) + xt + l * all; i < n16; i += a.layers * all)
+        reinterpret_cast<u32x4*>(a.exchange + (size_t)(1 - parity) * a.set_bytes)[i] = s4;
+    }
+    stage_ff(l);
+    workgroup_barrier();                                                  // 13
+    workgroup_barrier();                                                  // 14
+    residual(l, Rg::u3, 10);
+  }
+  if (j == 0) {   // the rows for the vocabulary product
+    if constexpr (PRE) gather_norm(a.layers - 1, Rg::u3, a.lnfg, a.lnfb, a.x_out, a.hidden, [] {});
+    else gather_norm(a.layers - 1, Rg::u3, vec[(a.layers - 1) & 1][4], vec[(a.layers - 1) & 1][5], nullptr, a.hidden, [] {});
+  }
+  ex.report(a.state, a.error);
+}
+
+
+}  // namespace
+
+// How M rows are dealt out.  Short histories, whole translations of 75 steps in ms, groups of 4 / 8 rows: 12 rows 7.44 / 7.69,
+// 16 rows 8.19 / 7.97, 24 rows 8.35 / 8.08, 32 rows 8.73 / 8.92 (fewer dies share the memory-side cache's rate, more have shorter
+// chains).  Long ones: over as many dies as there are sentences for, since a die reads its rows' histories at its own rate
+// (one row per sentence, us a step at positions 240 / 1008: 16 pre-LN rows on two dies 201 / 361, on eight 170 / 256; 4 rows of a post-LN model
+// on one 100 / 139, on four 97 / 124).
+struct DieChoice { int R, rows, groups; };
+static DieChoice choose_die(int M, int beam, int len) {
+  DieChoice c = {M <= 12 || (M > 24 && M <= 32) ? 4 : M <= 64 ? 8 : 16, 0, 0};
+  if (len > 128) {
+    const int each = (M + kDies - 1) / kDies, whole = (each + beam - 1) / beam * beam;
+    c.rows = whole <= 16 ? whole : each;
+    c.R = c.rows <= 4 ? 4 : c.rows <= 8 ? 8 : 16;
+  } else {
+    const int n = (M + c.R - 1) / c.R;
+    c.rows = (M + n - 1) / n;
+  }
+  c.groups = (M + c.rows - 1) / c.rows;
+  return c;
+}
+
+static const void* die_kernel_of(int R, bool pre) {
+  return R == 4 ? (pre ? (const void*)decoder_die_kernel<4, true> : (const void*)decoder_die_kernel<4, false>)
+       : R == 8 ? (pre ? (const void*)decoder_die_kernel<8, true> : (const void*)decoder_die_kernel<8, false>)
+                : (pre ? (const void*)decoder_die_kernel<16, true> : (const void*)decoder_die_kernel<16, false>);
+}
+
+// Against the kernels of kernels_stack.hip and the separate launches, us a step at positions 16 / 112 / 240 / 496 / 1008 / 1900 (die, others):
+//   post-LN, 4 rows of a sentence   93  95 103 121 150 195,  111 112 116 131 160 208
+//   32 rows, beam 4                112 116 128 161 210 296,  127 135 146 181 230 316
+//   64 rows, beam 4                121 128 160 214 315 471,  135 143 175 225 324 484
+//   128 rows, beam 4               141 183 238 336 544 845,  156 190 241 335 536 801
+//   128 rows, one per sentence     146 183 224 299 470 735,  165 191 232 309 479 750
+//   pre-LN, 12 layers, 32 rows     160 175 202 244 318 457,  174 198 206 244 320 467
+//   pre-LN, 64 rows                179 218 266 339 479 766,  187 222 246 325 474 758
+//   pre-LN, 128 rows               218 289 380 525 823   -,  231 275 357 509 815   -
+// A source key counts as half of one of the history (128 rows, sources of 500 and 2000: 232 463, 229 446).
+bool die_supported(int arch, int M, int d, int beam, int pos, int src) {
+  if (d != 512 || M < 1 || M > 16 * kDies) return false;
+  const int most = arch == 1 ? (M <= 32 ? 300 : M <= 64 ? 160 : 56) : M > 64 && beam > 1 ? 400 : 1 << 30;
+  return pos + src / 2 <= most && resident(die_kernel_of(choose_die(M, beam, pos).R, arch == 1), kDieThreads);
+}
+
+size_t die_exchange_bytes(int arch, int M, int d, int layers) {
+  // groups of 4 rows: at most M and 8 of them; of 8 and 16: more than half full, and the 8-row groups of kernels_stack.hip
+  const int rows = min(16 * kDies, max(4 * min(kDies, M), 2 * M + 16));
+  return d == 512 ? (size_t)rows * layers * (arch == 1 ? Region<true>::size : Region<false>::size) * d : 0;
+}
+
+hipError_t launch_decoder_die(int arch, const StackArgs& args, int pos, hipStream_t s) {
+  StackArgs a = args;
+  const DieChoice c = choose_die(a.M, a.beam, pos);
+  a.groups = c.groups;
+  a.rows_per_group = c.rows;
+  void* kargs[] = {&a};
+  return hipLaunchKernel(die_kernel_of(c.R, arch == 1), dim3(kDies * kDieGroup), dim3(kDieThreads), kargs, 0, s);
+}
+
+hipError_t die_placement(unsigned* scratch, uint32_t* dies, hipStream_t s) {
+  unsigned id[kDies * kDieGroup] = {};
+  die_of_workgroup_kernel<<<kDies * kDieGroup, kDieThreads, 0, s>>>(scratch);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpyAsync(id, scratch, sizeof(id), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  *dies = 0;
+  for (int b = 0; b < kDies; ++b) *dies |= (id[b] & 15) << (4 * b);
+  for (int b = 0; b < kDies * kDieGroup; ++b)
+    if (id[b] != id[b % kDies]) *dies = kNoDies;
+  return e;
+}
+
+}  // namespace lsq

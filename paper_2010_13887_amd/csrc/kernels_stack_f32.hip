@@ -58,7 +58,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
   const int seq = a.state[0], start = seq & 1, dirty = a.state[1], pos = *a.tpos;
   const bool owner = j < rows;
 
-  Exchange ex;
+  Exchange<> ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange, (short)0, (int)(2 * a.set_bytes), 0x00027000);
   ex.polls = seq < 0 ? 1 : kSpinLimit;
   const int group_bytes = Rg::size * D * rp;

@@ -184,6 +184,7 @@ struct StackArgs {
   int* error;               // pinned host memory: set when a wait ran out
   int M, beam, layers, T, anc_ld;
   float eps;
+  uint32_t dies;            // see die_placement
   int groups, rows_per_group;   // filled in by the launcher
 };
 size_t stack_exchange_bytes(int arch, int M, int d, int layers);   // of one set
@@ -191,12 +192,20 @@ bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers)
 // Whether kernels on this stream may use every compute unit of the current device: the workgroups of the stack kernels wait for
 // one another, and behind a mask some of them would only start once others have given up.
 bool stream_has_every_cu(hipStream_t s);
-enum StackKind { kStackNone, kStackFew, kStackMany, kStackF32 };
+enum StackKind { kStackNone, kStackDie, kStackFew, kStackMany, kStackF32 };
 // of a supported shape: which kernel takes these rows on the current device, at a history of `pos` positions and sources of at most `src` tokens
-StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src);
+// dies: die_placement has found every workgroup where the die kernels want it
+StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool dies);
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init
 hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s);   // as if a wait had run out
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
+// groups of rows on a die each (kernels_stack_die.hip); exchange region and state are those of launch_decoder_stack
+bool die_supported(int arch, int M, int d, int beam, int pos, int src);   // ... and ahead at this history and these sources
+size_t die_exchange_bytes(int arch, int M, int d, int layers);   // of one set; 0: no such kernel for this width
+hipError_t launch_decoder_die(int arch, const StackArgs& args, int pos, hipStream_t s);
+constexpr uint32_t kNoDies = 0xFFFFFFFFu;
+// which die workgroups b, b + 8, b + 16 .. of a launch run on, 4 bits each; kNoDies: not the same one.  scratch: 1 KB.  Waits for the stream.
+hipError_t die_placement(unsigned* scratch, uint32_t* dies, hipStream_t s);
 size_t stack_rows_bytes(int arch, int M, int d);   // of one set; 0: no such kernel for this width
 hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s);
 // float32 (kernels_stack_f32.hip): the matrices are copies made by launch_pack_f32 (16-column units, columns up to a multiple of 64, K of 4), vectors, cache and rows float32

@@ -475,6 +475,8 @@ int setup_stack() {
   a.layers = L; a.T = g.max_len; a.anc_ld = g.max_len + 1; a.eps = hp.eps;
   a.beam = g.beam;
   g.stack_ok = stack && stream_has_every_cu(g.stream);
+  a.dies = kNoDies;
+  if (g.stack_ok && p.stack_set) HIPCHK(die_placement(reinterpret_cast<unsigned*>(g.ws + p.d_tmp), &a.dies, g.stream));
   if (small) {
     char* E = g.ws + p.wpacked + L * layer_bytes_f32(hp);
     if (hp.dtype == DT_F32) HIPCHK(launch_pack_f32(g.E, E, hp.V, d, g.stream));
@@ -496,7 +498,7 @@ StackKind use_stack(int M) {
   if (!g.stack_ok || !g.fuse_ln || (M > g.block_rows && g.block_rows < (int)kBlockRowsMax)) return kStackNone;
   const int pos = history(), src = g.hp.arch == 1 ? 0 : g.src_longest;
   if (g.hp.dtype == DT_F32) return stack_f32_supported(M, g.hp.d, g.beam, pos, src) ? kStackF32 : kStackNone;
-  return stack_kind(g.hp.arch, M, g.hp.d, g.beam, pos, src);
+  return stack_kind(g.hp.arch, M, g.hp.d, g.beam, pos, src, g.stack.dies != kNoDies);
 }
 
 // plain beam search with a small model: the whole step in one launch.  Up to as many sentences as the chip runs at once:
@@ -508,6 +510,7 @@ bool use_small(int B) {
 }
 
 hipError_t launch_stack(StackKind kind, StackArgs a) {
+  if (kind == kStackDie) return launch_decoder_die(g.hp.arch, a, history(), g.stream);
   if (kind == kStackFew) return launch_decoder_stack(g.hp.arch, a, g.hp.d, g.stream);
   a.exchange = g.ws + g.plan.stack_rows_exchange;
   a.set_bytes = g.plan.stack_rows_set;

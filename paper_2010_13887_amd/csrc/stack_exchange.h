@@ -27,6 +27,15 @@ __device__ __forceinline__ const __attribute__((address_space(4))) StackArgs* no
 // behind the one that gave up end at once instead of each waiting out the limit.
 constexpr int kGaveUp = (int)0x80000000u;
 
+// Byte offsets of a row's intermediates inside one layer's region (d: row width): kernels in which every workgroup normalises
+template <bool PRE> struct Region {
+  static constexpr int qkv = 0, ctx = 6, u1 = 8;
+  static constexpr int q2 = PRE ? 0 : 12, ctx2 = PRE ? 0 : 14, u2 = PRE ? 0 : 16;   // cross-attention: post-LN models
+  static constexpr int ff = PRE ? 10 : 20, u3 = PRE ? 18 : 28, size = PRE ? 20 : 32;
+};
+
+// STORE: cache policy of what is published; 0 where all readers are on the writer's die (kernels_stack_die.hip)
+template <int STORE = kAgent>
 struct Exchange {
   __amdgpu_buffer_rsrc_t rsrc;
   int polls;   // of a wait; 1: one has run out, what this wavefront reads from now on may be missing
@@ -54,9 +63,14 @@ struct Exchange {
     __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   __device__ __forceinline__ void put(int base, int lane, unsigned v) {
-    __builtin_amdgcn_raw_buffer_store_b32(publish_word(v), rsrc, lane, base, kAgent);
+    __builtin_amdgcn_raw_buffer_store_b32(publish_word(v), rsrc, lane, base, STORE);
   }
   __device__ __forceinline__ void put(int base, int lane, float v) { put(base, lane, __builtin_bit_cast(unsigned, v)); }
+  __device__ __forceinline__ void put2(int base, int lane, float a, float b) {   // 8 bytes
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 w = {publish_word(__builtin_bit_cast(unsigned, a)), publish_word(__builtin_bit_cast(unsigned, b))};
+    __builtin_amdgcn_raw_buffer_store_b64(w, rsrc, lane, base, STORE);
+  }
   __device__ __forceinline__ void put2(int base, int lane, half_t a, half_t b) {
     typedef half_t half2_t __attribute__((ext_vector_type(2)));
     put(base, lane, __builtin_bit_cast(unsigned, half2_t{a, b}));
@@ -65,14 +79,14 @@ struct Exchange {
 
 // Whether every workgroup of a launch of 256 is resident at once on the current device, as far as the device goes; whether
 // the stream has all of it: stream_has_every_cu.
-inline bool resident(const void* kernel) {
+inline bool resident(const void* kernel, int threads = kThreads) {
   static std::unordered_map<const void*, bool> known;
   const auto it = known.find(kernel);
   if (it != known.end()) return it->second;
   int dev = 0, cus = 0, per_cu = 0;
   const bool ok = hipGetDevice(&dev) == hipSuccess &&
                   hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                  hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) == hipSuccess && cus * per_cu >= 256;
+                  hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) == hipSuccess && cus * per_cu >= 256;
   known[kernel] = ok;
   return ok;
 }

@@ -1,0 +1,58 @@
+"""Decoder layers with each group of rows on a die of its own (float16, d = 512): edges of the group sizes, of the wavefronts that
+share a pair's keys, and of the lengths at which rows are dealt out differently."""
+import numpy as np
+import pytest
+
+import lsq_synth as S
+from tests.parity import lockstep, lockstep_gpt
+from tests.test_gpu_e2e import _long_workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lsq():
+    import paper_2010_13887_amd as m
+    return m
+
+
+@pytest.mark.parametrize("d,batch,beam", [
+    (512, 1, 1), (512, 13, 1), (512, 5, 5), (512, 33, 1), (512, 13, 5), (512, 16, 8),   # groups of 4, 8, 4, 8, 16 and 16 rows, ragged but the last
+])
+def test_groups_of_rows_match_oracle(lsq, d, batch, beam):
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=203, max_pos=32, dtype=1, cap_extra=3)
+    w = S.custom(hp, [1 + (5 * i) % 7 for i in range(batch)], beam=beam, max_len=12, std=0.03, seed=batch)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, batch, beam, 12) as eng:
+        lsq.lsq_profile_enable(True)
+        lockstep(lsq, eng, blob, w, max_steps=3)
+        assert lsq.lsq_profile_read()["decoder_stack"][1] == 3
+        lsq.lsq_profile_enable(False)
+        one, two = (eng.translate(w.src_ids, w.src_lens, sync_every=n) for n in (1, 4))
+        assert all(np.array_equal(a, b) for a, b in zip(one, two))
+        assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("d,batch,beam,steps", [
+    (512, 2, 2, 140),     # one group of 4 rows: 32, 64, 128 and 256 keys a trip; from position 129 on a group per sentence
+    (512, 30, 4, 72),     # groups of 16 rows: 64 keys a trip
+])
+def test_long_histories_match_oracle(lsq, d, batch, beam, steps):
+    w, blob = _long_workload(d, d // 64, [3 + (5 * i) % 7 for i in range(batch - 1)] + [70], beam, steps, 1)
+    with lsq.Engine(blob, batch, beam, w.max_len) as eng:
+        assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[batch - 1])["steps"] == steps
+
+
+@pytest.mark.parametrize("batch,prompt", [(40, 156), (100, 52)])
+def test_prompts_across_the_change_of_kernel_match_oracle(lsq, batch, prompt):
+    """Decoder-only model: past positions 160 and 56 the 8-row groups and the groups of 16 all over the chip take over."""
+    hp = S.HParams(arch=1, n_enc=0, n_dec=2, d_model=512, n_heads=8, d_ffn=2048, vocab=203, max_pos=200, act=1, norm=1, dtype=1,
+                   sample_topk=4, cap_extra=8)
+    w = S.custom(hp, [prompt] * batch, beam=1, max_len=prompt + 8, std=0.04)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, batch, 1, w.max_len) as eng:
+        lsq.lsq_profile_enable(True)
+        res = lockstep_gpt(lsq, eng, blob, w)
+        launches = lsq.lsq_profile_read()["decoder_stack"][1]
+        lsq.lsq_profile_enable(False)
+        assert res["steps"] == 8 and launches == 8
