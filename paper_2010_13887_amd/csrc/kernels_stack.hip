@@ -58,11 +58,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   __shared__ float att_m[kWaves], att_l[kWaves];
 
   int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.groups, bid = blockIdx.x;
-  const int grp = (bid >> 3) % G, j = (bid >> 3) / G * 8 + (bid & 7);
-  const int r0 = grp * a.rows_per_group, rows = min(a.rows_per_group, a.M - r0);
-  const int seq = a.state[0], parity = seq & 1, dirty = a.state[2 - parity], pos = *a.tpos;
+  int grp = (bid >> 3) % G, j = (bid >> 3) / G * 8 + (bid & 7);
+  int r0 = grp * a.rows_per_group, rows = min(a.rows_per_group, a.M - r0);
+  const int seq = a.state[0], parity = seq & 1, dirty = a.state[2 - parity];
+  int pos = *a.tpos;
 
   Exchange ex;
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
@@ -361,15 +362,21 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     }
   };
 
+  // What is derived from a workgroup's place (row offsets, bounds, bases) is derived anew in every stage instead of waiting in scalar
+  // registers: 32 to 59 of them were spilled into lanes.  Whole translations: d = 1024, 4 rows 11.21 -> 10.99 ms (75 steps); d = 768 pre-LN,
+  // 8 rows 8.45 -> 8.18, 32 rows 10.61 -> 10.43 (104 steps).
+  auto renew = [&] { asm volatile("" : "+s"(wave), "+s"(j), "+s"(grp), "+s"(r0), "+s"(rows), "+s"(pos)); };
+
   // ======== the layers.  Every matrix slice is requested at least one exchange before it is multiplied.
   load_units(wq, layer_w(now()->Wqkv, 0), 3 * (D / 16));
   for (int l = 0; l < a.layers; ++l) {
-    // What is derived from a thread's place is derived anew in every layer instead of waiting in registers: without it d = 1024
-    // spills (32 rows 204 -> 174 us a step's layers); d = 512 gains 2 %, d = 768 would lose 2 %.
+    // The same for a thread's place, once a layer: without it d = 1024 spills (32 rows 204 -> 174 us a step's layers); d = 512
+    // gains 2 %, d = 768 would lose 2 %.
     if constexpr (DK != 3) {
       asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(lane16), "+v"(lane_nt), "+v"(lane_qt));
       asm volatile("" : "+v"(gk), "+v"(c8), "+v"(jfirst));
     }
+    renew();
     half_t* Kc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l) * now()->cache_stride);
     half_t* Vc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l + 1) * now()->cache_stride);
     // A. the layer's input rows; q, k, v
@@ -417,7 +424,9 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       }
     }
     // B, C. self-attention, its output projection
+    renew();
     attend(l, true, Kc, Vc, pos);
+    renew();
     project(wo, l, Rg::ctx, false, Rg::u1, layer_p(now()->bo, l), [&] {
       if constexpr (PRE) load_cols(w2, layer_w(now()->W2, l), 4 * D, NT);
       else load_cols(we, layer_w(now()->Woc, l), D, NT);
@@ -444,9 +453,11 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       }
       // E, F. cross-attention, its output projection
       const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
+      renew();
       attend(l, false, kvb, kvb + D, src_len);
       project(we, l, Rg::ctx2, false, Rg::u2, layer_p(now()->boc, l), [&] { load_cols(w2, layer_w(now()->W2, l), 4 * D, NT); });
     }
+    renew();
     // G. LayerNorm, first FFN product
     const int fcol = (j + W * qi) * 16 + qn;
     half2_t fb = {0, 0};
@@ -528,12 +539,13 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   __shared__ float att_m[kWaves], att_l[kWaves];
 
   int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.groups, bid = blockIdx.x;
-  const int grp = (bid >> 3) % G, j = (bid >> 3) / G * 8 + (bid & 7);
-  const int cg = j >> 2, ks = j & 3;
-  const int rp = a.rows_per_group, r0 = grp * rp, rows = min(rp, a.M - r0);
-  const int seq = a.state[0], start = seq & 1, dirty = a.state[1], pos = *a.tpos;
+  int grp = (bid >> 3) % G, j = (bid >> 3) / G * 8 + (bid & 7);
+  int cg = j >> 2, ks = j & 3;
+  int rp = a.rows_per_group, r0 = grp * rp, rows = min(rp, a.M - r0);
+  const int seq = a.state[0], dirty = a.state[1];
+  int start = seq & 1, pos = *a.tpos;
   const bool owner = j < rows;
 
   Exchange ex;
@@ -596,8 +608,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   };
   auto pin = [] { asm volatile("" ::: "memory"); };
 
-  auto layer_w = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(p) + (size_t)l * a.packed_stride); };
-  auto layer_p = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(p) + (size_t)l * a.plain_stride); };
+  auto layer_w = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(global(p)) + (size_t)l * now()->packed_stride); };
+  auto layer_p = [&](const half_t* p, int l) { return reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(global(p)) + (size_t)l * now()->plain_stride); };
   auto half4_at = [](const half_t* b, unsigned col) { return *reinterpret_cast<const half4_t*>(reinterpret_cast<const char*>(b) + col * 2u); };
 
   // ---- the owner's part: residual row + partial sums of a projection -> normalised row.  Thread t has columns 4t .. 4t+3.
@@ -871,17 +883,24 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     }
   };
 
-  // ======== the layers
-  load_units(wq, layer_w(a.Wqkv, 0));
-  for (int l = 0; l < a.layers; ++l) {
-    // What is derived from a thread's place is derived anew in every layer instead of waiting in registers: without it d = 1024
-    // spills (128 rows 275 -> 266 us a step's layers); narrower models would lose 2 to 4 %.
+  // What is derived from a workgroup's place is derived anew in every stage, and pointers are read where they are used, instead of
+  // waiting in scalar registers (69 to 157 of them were spilled; 16 at most are left).  d = 1024 needs it for what is derived from a thread's
+  // place as well (it spills otherwise); narrower models would lose 3 to 7 %.  Whole translations of 75 steps: d = 1024, 128 rows
+  // 21.4 -> 21.1 ms; d = 512, 200 rows 15.1 -> 14.7, one per sentence 16.6 -> 16.1; d = 768 pre-LN, 120 rows 17.15 -> 16.9 (104 steps).
+  auto renew = [&] {
+    asm volatile("" : "+s"(wave), "+s"(j), "+s"(cg), "+s"(ks), "+s"(grp), "+s"(rp), "+s"(r0), "+s"(rows), "+s"(pos), "+s"(start));
     if constexpr (DK == 4) {
       asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(lane16), "+v"(oc), "+v"(ui), "+v"(um), "+v"(un));
       asm volatile("" : "+v"(gk), "+v"(c8), "+v"(jfirst));
     }
-    half_t* Kc = reinterpret_cast<half_t*>(a.cache + (size_t)(2 * l) * a.cache_stride);
-    half_t* Vc = reinterpret_cast<half_t*>(a.cache + (size_t)(2 * l + 1) * a.cache_stride);
+  };
+
+  // ======== the layers
+  load_units(wq, layer_w(now()->Wqkv, 0));
+  for (int l = 0; l < a.layers; ++l) {
+    renew();
+    half_t* Kc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l) * now()->cache_stride);
+    half_t* Vc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l + 1) * now()->cache_stride);
     // the layer's input rows
     if (l == 0) {
       if (owner) {
@@ -906,21 +925,21 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
         }
       }
     } else {
-      if constexpr (PRE) own_norm(l - 1, Rg::fs, layer_p(a.b2, l - 1), layer_p(a.ln1g, l), layer_p(a.ln1b, l), l, Rg::xi, nullptr, nullptr);
-      else own_norm(l - 1, Rg::fs, layer_p(a.b2, l - 1), layer_p(a.ln3g, l - 1), layer_p(a.ln3b, l - 1), l, Rg::xi, nullptr, nullptr);
+      if constexpr (PRE) own_norm(l - 1, Rg::fs, layer_p(now()->b2, l - 1), layer_p(now()->ln1g, l), layer_p(now()->ln1b, l), l, Rg::xi, nullptr, nullptr);
+      else own_norm(l - 1, Rg::fs, layer_p(now()->b2, l - 1), layer_p(now()->ln3g, l - 1), layer_p(now()->ln3b, l - 1), l, Rg::xi, nullptr, nullptr);
     }
     // q, k, v
     {
       const int qcol = (j + W * ui) * 16 + un;
       half4_t qb = {};
       const bool qlive = ui < 3 && um < rows;
-      if (qlive) qb = half4_at(layer_p(a.bqkv, l), qcol);
+      if (qlive) qb = half4_at(layer_p(now()->bqkv, l), qcol);
       if (attends) request_keys(true, Kc, Vc, pos, jfirst);   // needs nothing of this step
       pin();
       u32x4 raw[CHX];
       stage_rows(raw, at(l, Rg::xi), D, 0);
       multiply_units(wq);
-      load_quarter(wo, layer_w(a.Wo, l));
+      load_quarter(wo, layer_w(now()->Wo, l));
       pin();
       __syncthreads();
       if (qlive) {
@@ -935,33 +954,37 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
         }
       }
     }
+    renew();
     attend(l, true, Kc, Vc, pos, nullptr);
+    renew();
     project_quarter(wo, l, Rg::ctx, Rg::os, [&] {
-      if constexpr (PRE) load_units(w1, layer_w(a.W1, l));
-      else load_quarter(wo, layer_w(a.Wq, l));
+      if constexpr (PRE) load_units(w1, layer_w(now()->W1, l));
+      else load_quarter(wo, layer_w(now()->Wq, l));
     });
     if constexpr (PRE) {
-      own_norm(l, Rg::os, layer_p(a.bo, l), layer_p(a.ln2g, l), layer_p(a.ln2b, l), l, Rg::x1, nullptr, nullptr);
+      own_norm(l, Rg::os, layer_p(now()->bo, l), layer_p(now()->ln2g, l), layer_p(now()->ln2b, l), l, Rg::x1, nullptr, nullptr);
     } else {
-      const half_t* kvb = reinterpret_cast<const half_t*>(a.cross + (size_t)l * a.cross_stride) + (size_t)src_off * 2 * D;
-      own_norm(l, Rg::os, layer_p(a.bo, l), layer_p(a.ln1g, l), layer_p(a.ln1b, l), l, Rg::x1, nullptr, nullptr);
+      const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
+      own_norm(l, Rg::os, layer_p(now()->bo, l), layer_p(now()->ln1g, l), layer_p(now()->ln1b, l), l, Rg::x1, nullptr, nullptr);
       if (attends) request_keys(false, kvb, kvb + D, src_len, jfirst);
       pin();
-      project_quarter(wo, l, Rg::x1, Rg::qs, [&] { load_quarter(wo, layer_w(a.Woc, l)); });
-      attend(l, false, kvb, kvb + D, src_len, layer_p(a.bq, l));
-      project_quarter(wo, l, Rg::ctx2, Rg::cs, [&] { load_units(w1, layer_w(a.W1, l)); });
-      own_norm(l, Rg::cs, layer_p(a.boc, l), layer_p(a.ln2g, l), layer_p(a.ln2b, l), l, Rg::x2, nullptr, nullptr);
+      project_quarter(wo, l, Rg::x1, Rg::qs, [&] { load_quarter(wo, layer_w(now()->Woc, l)); });
+      renew();
+      attend(l, false, kvb, kvb + D, src_len, layer_p(now()->bq, l));
+      project_quarter(wo, l, Rg::ctx2, Rg::cs, [&] { load_units(w1, layer_w(now()->W1, l)); });
+      own_norm(l, Rg::cs, layer_p(now()->boc, l), layer_p(now()->ln2g, l), layer_p(now()->ln2b, l), l, Rg::x2, nullptr, nullptr);
     }
     // first FFN product
+    renew();
     {
       const int fcol = (j + W * ui) * 16 + un;
       const bool flive = ui < 4 && um < rows;
       half4_t fb = {};
-      if (flive) fb = half4_at(layer_p(a.b1, l), fcol);
+      if (flive) fb = half4_at(layer_p(now()->b1, l), fcol);
       u32x4 raw[CHX];
       stage_rows(raw, at(l, PRE ? Rg::x1 : Rg::x2), D, 0);
       multiply_units(w1);
-      load_ffn2(w2, layer_w(a.W2, l));
+      load_ffn2(w2, layer_w(now()->W2, l));
       pin();
       __syncthreads();
       if (flive) {
@@ -978,7 +1001,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     // second FFN product
     stage_units(at(l, Rg::ff) + ks * (D / 16) * rp * 32);
     multiply_units(w2);
-    if (l + 1 < a.layers) load_units(wq, layer_w(a.Wqkv, l + 1));
+    if (l + 1 < a.layers) load_units(wq, layer_w(now()->Wqkv, l + 1));
     pin();
     __syncthreads();
     if (ui < 4 && um < rows) {
@@ -987,8 +1010,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     }
   }
   const int last = a.layers - 1;
-  if constexpr (PRE) own_norm(last, Rg::fs, layer_p(a.b2, last), a.lnfg, a.lnfb, last, -1, a.x_out, a.hidden);
-  else own_norm(last, Rg::fs, layer_p(a.b2, last), layer_p(a.ln3g, last), layer_p(a.ln3b, last), last, -1, nullptr, a.hidden);
+  if constexpr (PRE) own_norm(last, Rg::fs, layer_p(now()->b2, last), a.lnfg, a.lnfb, last, -1, a.x_out, a.hidden);
+  else own_norm(last, Rg::fs, layer_p(now()->b2, last), layer_p(now()->ln3g, last), layer_p(now()->ln3b, last), last, -1, nullptr, a.hidden);
   ex.report(a.state, a.error);
   if (tid == 0) {   // the last workgroup to get here: all have read the counters
     const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

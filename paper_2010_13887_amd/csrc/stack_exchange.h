@@ -18,8 +18,8 @@ constexpr int kThreads = 512, kWaves = 8;
 __device__ __forceinline__ unsigned publish_word(unsigned v) { return v == kSentinel ? 0x7FFF7FFFu : v; }   // one NaN for another
 
 // The pointers of a layer are read where they are used (see arguments): 60 scalar registers less to spill.  Layers of a step
-// in groups of 8 rows: d = 512, 4 rows 92.9 -> 91.6 us, 32 rows 114.3 -> 112.3; the kernels for more rows and for float32 lost
-// up to 1 % by it and keep theirs.
+// in groups of 8 rows: d = 512, 4 rows 92.9 -> 91.6 us, 32 rows 114.3 -> 112.3; the kernel for float32 lost up to 1 % by it and
+// keeps its own.
 __device__ __forceinline__ const __attribute__((address_space(4))) StackArgs* now() { return arguments<StackArgs>(); }
 
 // Set in the first word of StackArgs::state at the end of a launch in which a wait ran out (the word the kernels read first
