@@ -476,7 +476,7 @@ int setup_stack() {
   a.beam = g.beam;
   g.stack_ok = stack && stream_has_every_cu(g.stream);
   a.dies = kNoDies;
-  if (g.stack_ok && p.stack_set) HIPCHK(die_placement(reinterpret_cast<unsigned*>(g.ws + p.d_tmp), &a.dies, g.stream));
+  if (g.stack_ok && p.stack_set && die_exchange_bytes(hp.arch, g.max_batch * g.beam, d, L)) HIPCHK(die_placement(reinterpret_cast<unsigned*>(g.ws + p.d_tmp), &a.dies, g.stream));
   if (small) {
     char* E = g.ws + p.wpacked + L * layer_bytes_f32(hp);
     if (hp.dtype == DT_F32) HIPCHK(launch_pack_f32(g.E, E, hp.V, d, g.stream));
