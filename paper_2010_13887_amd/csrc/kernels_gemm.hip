@@ -911,6 +911,108 @@ __global__ void __launch_bounds__(256) gemm_f16_skinny_kernel(const half_t* __re
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The vocabulary product of 9 to 32 rows (float output, no bias, weights in fragment order): a stream of 50 to 130 MB.
+// In the kernel above every 32 columns bring the input rows along, as many bytes as their weights and in pieces of 32 bytes (32 rows
+// of d = 768), and 50257 columns are one and a half rounds of its workgroups.  Here one workgroup per compute unit puts the rows into
+// LDS once, in fragment order, and each of its wavefronts has one block of 32 columns and all of k: nothing to wait for after
+// the first barrier, P = 32 KB of weights in flight per wavefront (16 and 24 up to 1 % of a step slower).  Four accumulators take the
+// k-steps in turn and are added in pairs: the sums of the kernel above, bit for bit.
+// In the step at 32 rows: 50257 columns of d = 768 24.9 -> 19.3 us (77 MB, 4.0 TB/s), 32000 of d = 1024 17.0 -> 14.7 (66 MB, 4.5 TB/s); bound by
+// memory and some 3 us of launch, staging and the last wavefronts.
+template <int KS, int T>
+__global__ void __launch_bounds__(T) gemm_f16_stream_kernel(const half_t* __restrict__ A, const half_t* __restrict__ Bp, int M, int N,
+                                                            const int32_t* __restrict__ tpos, int vec_ok, GemmOut out) {
+  constexpr int P = 32;
+  constexpr int kPiece = 32 * 16 + 16;   // bytes of 8 columns of all rows; 16 more: writers of 16 such pieces meet all banks
+  constexpr int CH = 32 * KS * 2 / T;    // 16-byte pieces of the rows per thread
+  __shared__ __attribute__((aligned(16))) char rows[KS * 2 * kPiece];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const long tp = tpos ? *tpos : 0;
+  const int block = (int)blockIdx.x + (int)gridDim.x * wave, blocks = (N + 31) / 32;
+  // a wavefront without a block: nothing in range, so its requests return zeros and read nothing (a branch around them would make
+  // all wavefronts wait for their weights at the barrier)
+  const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<half_t*>(Bp) + (size_t)min(block, blocks - 1) * KS * 512, (short)0, block < blocks ? KS * 1024 : 0, 0x00027000);
+  auto request = [&](int ks) { return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(weights, lane * 16, ks * 1024, 0)); };
+  half8_t in[CH], w[P];
+  const unsigned pieces = M * (KS * 2);
+#pragma unroll
+  for (int i = 0; i < CH; ++i) in[i] = *reinterpret_cast<const half8_t*>(A + min((unsigned)(i * T + tid), pieces - 1) * 8u);
+  __builtin_amdgcn_sched_barrier(0);   // requests are answered in order: the rows first
+#pragma unroll
+  for (int i = 0; i < P; ++i) w[i] = request(i);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < CH; ++i) {
+    const unsigned p = min((unsigned)(i * T + tid), pieces - 1);   // the last piece again past the end: the same value
+    *reinterpret_cast<half8_t*>(&rows[p % (KS * 2) * kPiece + p / (KS * 2) * 16]) = in[i];
+  }
+  __syncthreads();
+  if (block >= blocks) return;
+  floatx16 acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
+  const int m = lane & 31, at = (lane >> 5) * kPiece + min(m, M - 1) * 16;   // rows past the last one repeat it
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    acc[ks & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[ks % P], *reinterpret_cast<const half8_t*>(&rows[ks * 2 * kPiece + at]), acc[ks & 3], 0, 0, 0);
+    if (ks + P < KS) w[ks % P] = request(ks + P);
+    if ((ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+  float mx = -INFINITY, z = 0.f;
+#pragma unroll
+  for (int vg = 0; vg < 4; ++vg) {
+    const int n = block * 32 + vg * 8 + (lane >> 5) * 4;
+    float v[4], vm = -INFINITY, vz = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]);
+    if (m < M && n < N) store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp);
+    if (!out.stats) continue;
+    // as in the kernel above, whose wavefronts have eight columns each
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < N) vm = fmaxf(vm, v[e]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < N) vz += __expf(v[e] - vm);
+    const float m2 = lane_xor<32>(vm), z2 = lane_xor<32>(vz);
+    merge_stat(vm, vz, m2, z2);
+    if (vg == 0) { mx = vm; z = vz; }
+    else merge_stat(mx, z, vm, vz);
+  }
+  if (out.stats && lane < 32 && m < M) {
+    float* st = out.stats + ((size_t)m * out.stats_groups + block) * 2;
+    st[0] = mx;
+    st[1] = z;
+  }
+}
+
+constexpr int kStreamGrid = 256;   // one workgroup per compute unit, of at most eight wavefronts with a block of 32 columns each
+
+// Vocabulary-sized products.  Up to 8 rows the kernel above is level or ahead (its rows are few lines then; whole calls, above | this: d = 1024
+// of 4 rows 11.13 | 11.15 ms, 8 rows 11.93 | 11.96; d = 768 pre-LN of 1 row 10.15 | 10.16), from 16 on this one (d = 1024: 12.78 | 12.70, 32
+// rows 14.20 | 13.90; d = 768: 13.85 | 13.77, 24 rows 15.56 | 15.33, 32 rows 16.24 | 15.91).  d = 512 is level at 32 rows (8.4 | 8.4 us) and
+// behind below; two blocks of rows are behind the tiled kernel (64 rows of 32000 x 1024: 18.2 | 20.7 us).
+static bool stream_supported(int M, int N, int K) {
+  return M > 8 && M <= 32 && (N + 127) / 128 >= 125 && N <= kStreamGrid * 8 * 32 && (K == 768 || K == 1024);
+}
+
+static void run_stream(const half_t* A, const half_t* Bp, const GemmOut& out, int M, int N, int K, int vec_ok, hipStream_t s) {
+  const bool few = (N + 31) / 32 <= kStreamGrid * 4;   // four wavefronts are enough
+#define LSQ_STREAM(KS_, T_) gemm_f16_stream_kernel<KS_, T_><<<kStreamGrid, T_, 0, s>>>(A, Bp, M, N, out.tpos, vec_ok, out)
+  if (K == 768) {
+    if (few) LSQ_STREAM(48, 256);
+    else LSQ_STREAM(48, 512);
+  } else {
+    if (few) LSQ_STREAM(64, 256);
+    else LSQ_STREAM(64, 512);
+  }
+#undef LSQ_STREAM
+}
+
 constexpr int kSkinnyRows = 64;   // above this the LDS-tiled kernel is faster
 
 // Products with an epilogue (bias, activation, cache append, statistics): between 33 and 64 rows the skinny kernel's
@@ -1394,10 +1496,12 @@ hipError_t launch_gemm(int dtype, const void* A, const void* B, const void* bias
   // (32 rows of 32000 x 1024: 22.6 -> 14.4 us, of 50257 x 768: 31.9 -> 19.5 us), but inside a step, where much of the
   // embedding is still in the memory-side cache, it is level or behind (32 rows of 32000 x 512: 9.6 -> 12.0 us in the
   // step; translations of Transformer-base 25.1 -> 25.6 ms, of the GPT-2-small shape 57.1 -> 56.8 ms).
-  // Fragment-ordered weights are read by the skinny kernel only.
+  // Fragment-ordered weights are read by the skinny and the streaming kernel only.
   const bool wide = (N + 127) / 128 >= 125 && M > 32;
-  if ((b_packed || (skinny_rows(M, K) && !wide)) && K % 16 == 0) {
-    const half_t* bpk = b_packed ? b : packed_of(B, N, K);
+  const half_t* bpk = b_packed ? b : packed_of(B, N, K);
+  if (bpk && out.f32_out && !bi && !act && stream_supported(M, N, K)) {
+    run_stream(a, bpk, out, M, N, K, vec_ok, s);
+  } else if ((b_packed || (skinny_rows(M, K) && !wide)) && K % 16 == 0) {
     if (out.f32_out) run_skinny<false, float>(a, b, bpk, bi, out, M, N, K, act, vec_ok, 1, s);
     else run_skinny<false, half_t>(a, b, bpk, bi, out, M, N, K, act, vec_ok, 1, s);
   } else if (M <= 32)

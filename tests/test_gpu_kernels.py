@@ -807,3 +807,20 @@ def test_cache_reorder(env, layers, B, k, T, d, npos, half):
     ref = cache.copy()
     ref[:, :, :npos] = cache[:, rows, :npos]               # positions beyond npos are untouched
     assert np.array_equal(dc.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("M,N,K", [(9, 15873, 768), (32, 32768, 768), (31, 32769, 768), (32, 50257, 768), (17, 32003, 1024),
+                                   (32, 65536, 1024), (16, 65505, 1024), (32, 15904, 1024)])
+def test_vocabulary_product_with_fragment_ordered_weights(env, M, N, K):
+    """The kernel that keeps all input rows in LDS: the bits of the row-major product (the skinny kernel, the same summation
+    order); few and many wavefronts, some without a block of columns, ragged columns, rows left alone."""
+    lsq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn(M, K, generator=g, device="cuda").half()
+    W = (torch.randn(N, K, generator=g, device="cuda") * 0.2).half()
+    C = torch.full((M + 1, N), 7.0, dtype=torch.float32, device="cuda")
+    ref = torch.empty(M, N, dtype=torch.float32, device="cuda")
+    lsq.k_gemm(A, lsq.k_pack_weights(W), None, C[:M], packed=True)
+    lsq.k_gemm(A, W, None, ref)
+    assert torch.equal(C[:M], ref)
+    assert (C[M] == 7.0).all()
