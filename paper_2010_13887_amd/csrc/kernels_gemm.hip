@@ -70,12 +70,7 @@ __device__ __forceinline__ void store4(const GemmOut& out, int m, int n, const f
 // A 32x32 accumulator block of a tile kernel, lane: row m = .. + (lane & 31), columns nb + 8 vg + 4 (lane >> 5) + 0..3; nb the
 // same in all lanes.  Where the block's columns lie in one segment its address is made once and the activation is chosen
 // once: with a segment and an activation looked up for every four values the epilogue of a 256x256 tile took 20 us.
-template <typename OutT, bool SPLIT>
-__device__ __forceinline__ void store_block(const GemmOut& out, int m, int nb, const floatx16& acc, const float (&bv)[4][4], int act,
-                                            int M, int N, int vec_ok, int slab, long tp) {
-  if (m >= M || nb >= N) return;
-  const int hf = ((int)threadIdx.x & 63) >> 5;
-  float v[4][4];
+__device__ __forceinline__ void finish_block(const floatx16& acc, const float (&bv)[4][4], int act, float (&v)[4][4]) {
 #pragma unroll
   for (int vg = 0; vg < 4; ++vg)
 #pragma unroll
@@ -93,6 +88,14 @@ __device__ __forceinline__ void store_block(const GemmOut& out, int m, int nb, c
         for (int e = 0; e < 4; ++e) v[vg][e] = activate(v[vg][e], 2);
     }
   }
+}
+template <typename OutT, bool SPLIT>
+__device__ __forceinline__ void store_block(const GemmOut& out, int m, int nb, const floatx16& acc, const float (&bv)[4][4], int act,
+                                            int M, int N, int vec_ok, int slab, long tp) {
+  if (m >= M || nb >= N) return;
+  const int hf = ((int)threadIdx.x & 63) >> 5;
+  float v[4][4];
+  finish_block(acc, bv, act, v);
   const int s = segment_of(out, nb), n0 = s * out.seg_n;
   if (vec_ok == 1 && (SPLIT || nb + 32 <= n0 + out.seg_n || n0 + out.seg_n >= N) && nb + 32 <= N) {
     OutT* dst = SPLIT ? reinterpret_cast<OutT*>(out.ptr[0]) + ((size_t)slab * M + m) * N + nb
@@ -577,7 +580,7 @@ __global__ void __launch_bounds__(64 * (BM / 32) * (BN / 32)) gemm_f16_direct_ke
 template <int BM, int BN, int BK, int WM, int WN, int D, typename OutT>
 __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), BM * BN <= 128 * 128 && sizeof(OutT) == 2 ? 4 : 2) gemm_f16_large_kernel(const half_t* __restrict__ A, const half_t* __restrict__ B,
                                                        int M, int N, int K, const int32_t* __restrict__ tpos,
-                                                       const half_t* __restrict__ bias, int act, int vec_ok,
+                                                       const half_t* __restrict__ bias, int act, int vec_ok, int whole_rows,
                                                        GemmOut out) {
   constexpr int LDK = BK + 8;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -701,11 +704,46 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), BM * BN <= 128 * 1
     }
   }
   if (BIAS_LATE) load_bias();
+  if (whole_rows) {
+    // 32 rows at a time through this wavefront's own part of the LDS (the last barrier of the k-loop has freed it), so that a
+    // store instruction writes whole lines (straight from the accumulators a lane has 8 bytes of a row, and a line of float16 is
+    // written in eight pieces).  Time of a 256x256 tile that does not depend on k 20 -> 12 us: 7648 x 3072 x 768 60.4 -> 49.2 us (733 TFLOP/s),
+    // 3600 x 4096 x 1024 45.5 -> 36.6, float output 7648 x 768 x 3072 53.6 -> 48.8, 512 x 32000 x 1024 47.0 -> 45.1.
+    constexpr int LDO = WN + 16 / sizeof(OutT), C = 16 / sizeof(OutT), CPR = WN / C, RPI = 64 / CPR;
+    static_assert((BM / WM) * (BN / WN) * 32 * LDO * sizeof(OutT) <= 2 * (BM + BN) * LDK * sizeof(half_t), "fits the operand tiles");
+    typedef OutT piece_t __attribute__((ext_vector_type(C)));
+    typedef OutT quad_t __attribute__((ext_vector_type(4)));
+    OutT* part = reinterpret_cast<OutT*>(lds_tiles) + wave * 32 * LDO;
+    const int nb = n0 + wn, seg = nb < N ? segment_of(out, nb) : 0;
+    OutT* dst = reinterpret_cast<OutT*>(out.ptr[seg]) + tp * out.tmul[seg] + (nb - seg * out.seg_n);
+    const int row = lane / CPR, col = lane % CPR * C;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-      store_block<OutT, false>(out, m0 + wm + i * 32 + (lane & 31), n0 + wn + j * 32, acc[i][j], bv[j], act, M, N, vec_ok, 0, tp);
+      for (int j = 0; j < TN; ++j) {
+        float v[4][4];
+        finish_block(acc[i][j], bv[j], act, v);
+#pragma unroll
+        for (int vg = 0; vg < 4; ++vg)
+          *reinterpret_cast<quad_t*>(&part[(lane & 31) * LDO + j * 32 + vg * 8 + (lane >> 5) * 4]) =
+              quad_t{(OutT)v[vg][0], (OutT)v[vg][1], (OutT)v[vg][2], (OutT)v[vg][3]};
+      }
+      __builtin_amdgcn_wave_barrier();   // LDS serves a wavefront's accesses in order
+#pragma unroll
+      for (int t = 0; t < 32 / RPI; ++t) {
+        const piece_t x = *reinterpret_cast<const piece_t*>(&part[(t * RPI + row) * LDO + col]);
+        const int m = m0 + wm + i * 32 + t * RPI + row;
+        if (m < M && nb + col < N) *reinterpret_cast<piece_t*>(dst + (long)m * out.ld[seg] + col) = x;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        store_block<OutT, false>(out, m0 + wm + i * 32 + (lane & 31), n0 + wn + j * 32, acc[i][j], bv[j], act, M, N, vec_ok, 0, tp);
+  }
   if constexpr (std::is_same<OutT, float>::value) {
     // (largest, sum of exponentials) of every (row, 32-column group): a wave tile holds a group's 32 columns of a
     // row in the two lanes (m, half 0) and (m, half 1)
@@ -1327,17 +1365,22 @@ static void run_f16_large(const half_t* A, const half_t* B, const half_t* bias, 
   dim3 grid(((N + BN - 1) / BN) * ((M + BM - 1) / BM));
   constexpr size_t lds = gemm_lds_bytes<BM, BN, BK>();
   constexpr int NT = 64 * (BM / WM) * (BN / WN);
+  // whole rows of a wavefront's columns can be stored 16 bytes at a time: one segment or segments of whole wave tiles, aligned
+  const int nseg = (N + out.seg_n - 1) / out.seg_n, c = out.f32_out ? 4 : 8;
+  int whole_rows = vec_ok == 1 && N % c == 0 && (nseg == 1 || out.seg_n % 64 == 0);
+  for (int i = 0; i < nseg; ++i)
+    if (out.ld[i] % c != 0 || out.tmul[i] % c != 0 || (reinterpret_cast<uintptr_t>(out.ptr[i]) & 15) != 0) whole_rows = 0;
   // LDS above the default 64 KB limit is opted into once per kernel
   if (out.f32_out) {
     auto kern = gemm_f16_large_kernel<BM, BN, BK, WM, WN, 2, float>;
     static bool raised = false;
     if (!raised) { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); raised = true; }
-    kern<<<grid, dim3(NT), lds, s>>>(A, B, M, N, K, out.tpos, bias, act, vec_ok, out);
+    kern<<<grid, dim3(NT), lds, s>>>(A, B, M, N, K, out.tpos, bias, act, vec_ok, whole_rows, out);
   } else {
     auto kern = gemm_f16_large_kernel<BM, BN, BK, WM, WN, 2, half_t>;
     static bool raised = false;
     if (!raised) { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); raised = true; }
-    kern<<<grid, dim3(NT), lds, s>>>(A, B, M, N, K, out.tpos, bias, act, vec_ok, out);
+    kern<<<grid, dim3(NT), lds, s>>>(A, B, M, N, K, out.tpos, bias, act, vec_ok, whole_rows, out);
   }
 }
 
@@ -1417,16 +1460,17 @@ bool gemm_writes_stats(int dtype, int M, int N, int K) {
 // reads per FLOP, 256x128 and 128x128 some 10 and 15 % more time per FLOP; but a last round of workgroups that leaves most
 // CUs idle costs as much as a full one.  So: the largest (share of the rounds' capacity that is work) x (rate of the tile).
 // Where that is below 0.9, the rows that fill whole rounds of 256x256 tiles go first, the rest as a product of its own.
-// Measured, us, 256x256 / 256x128 / 128x128: 7648 x 3072 x 768 73 / 70 / 72 (in two parts 66), 7648 x 768 x 3072 82 / 54 / 64 (float output), 3600 x
-// 4096 x 1024 53 / 60 / 57, 3600 x 1024 x 1024 34 / 22 / 17 (float), 32000 columns x 1024: 512 rows 55 / 59 / 65, 256 rows 47 / 31 / 35;
-// 7648 x 2304 x 768 65 / 64 / 58, in two parts 53.
+// Measured, us, 256x256 / 256x128 / 128x128: 7648 x 3072 x 768 53 / 55 / 51 (in two parts 50), 7648 x 768 x 3072 76 / 51 / 62 (float output), 3600 x
+// 4096 x 1024 38 / 45 / 43, 3600 x 1024 x 1024 32 / 22 / 16 (float), 30 / 19 / 14 (float16: up to 256 tiles have a CU each), 32000 columns x
+// 1024: 512 rows 46 / 51 / 67, 256 rows 36 / 27 / 35, 128 rows 32 / 22 / 17; 7648 x 2304 x 768 52 / 51 / 43, in two parts 42.
 static hipError_t launch_large(const half_t* a, const half_t* b, const half_t* bi, const GemmOut& out, int M, int N, int K, int act,
                                int vec_ok, hipStream_t s) {
   auto share = [&](int bm, int bn, int slots) {
     const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn), rounds = (tiles + slots - 1) / slots;
     return (double)M * N / ((double)rounds * slots * bm * bn);
   };
-  const double s256 = share(256, 256, 256), s2x1 = 0.9 * share(256, 128, 256), s128 = 0.85 * share(128, 128, out.f32_out ? 256 : 512);
+  const bool pairs = !out.f32_out && (long)((M + 127) / 128) * ((N + 127) / 128) > 256;   // two of the smallest tiles share a CU
+  const double s256 = share(256, 256, 256), s2x1 = 0.9 * share(256, 128, 256), s128 = 0.85 * share(128, 128, pairs ? 512 : 256);
   const int nt = (N + 255) / 256;
   const long whole = (long)((M + 255) / 256) * nt / 256 * 256;   // workgroups of the full rounds
   const int first = (int)(whole / nt) * 256;                     // rows they take
