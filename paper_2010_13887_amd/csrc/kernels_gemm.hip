@@ -950,6 +950,37 @@ __global__ void __launch_bounds__(256) gemm_f16_skinny_kernel(const half_t* __re
 }
 
 // ---------------------------------------------------------------------------------------------
+// The end of the two kernels below: a wavefront's block of 32 columns, lane: row m, columns 8 vg + 4 (lane >> 5) + 0..3.
+__device__ __forceinline__ void vocabulary_block(const floatx16 (&acc)[4], const GemmOut& out, int m, int block, int M, int N, int vec_ok,
+                                                 long tp, int lane) {
+  float mx = -INFINITY, z = 0.f;
+#pragma unroll
+  for (int vg = 0; vg < 4; ++vg) {
+    const int n = block * 32 + vg * 8 + (lane >> 5) * 4;
+    float v[4], vm = -INFINITY, vz = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]);
+    if (m < M && n < N) store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp);
+    if (!out.stats) continue;
+    // as in gemm_f16_skinny_kernel, whose wavefronts have eight columns each
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < N) vm = fmaxf(vm, v[e]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < N) vz += __expf(v[e] - vm);
+    const float m2 = lane_xor<32>(vm), z2 = lane_xor<32>(vz);
+    merge_stat(vm, vz, m2, z2);
+    if (vg == 0) { mx = vm; z = vz; }
+    else merge_stat(mx, z, vm, vz);
+  }
+  if (out.stats && lane < 32 && m < M) {
+    float* st = out.stats + ((size_t)m * out.stats_groups + block) * 2;
+    st[0] = mx;
+    st[1] = z;
+  }
+}
+
 // The vocabulary product of 9 to 32 rows (float output, no bias, weights in fragment order): a stream of 50 to 130 MB.
 // In the kernel above every 32 columns bring the input rows along, as many bytes as their weights and in pieces of 32 bytes (32 rows
 // of d = 768), and 50257 columns are one and a half rounds of its workgroups.  Here one workgroup per compute unit puts the rows into
@@ -1000,32 +1031,7 @@ __global__ void __launch_bounds__(T) gemm_f16_stream_kernel(const half_t* __rest
     if (ks + P < KS) w[ks % P] = request(ks + P);
     if ((ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
-  float mx = -INFINITY, z = 0.f;
-#pragma unroll
-  for (int vg = 0; vg < 4; ++vg) {
-    const int n = block * 32 + vg * 8 + (lane >> 5) * 4;
-    float v[4], vm = -INFINITY, vz = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]);
-    if (m < M && n < N) store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp);
-    if (!out.stats) continue;
-    // as in the kernel above, whose wavefronts have eight columns each
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (n + e < N) vm = fmaxf(vm, v[e]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (n + e < N) vz += __expf(v[e] - vm);
-    const float m2 = lane_xor<32>(vm), z2 = lane_xor<32>(vz);
-    merge_stat(vm, vz, m2, z2);
-    if (vg == 0) { mx = vm; z = vz; }
-    else merge_stat(mx, z, vm, vz);
-  }
-  if (out.stats && lane < 32 && m < M) {
-    float* st = out.stats + ((size_t)m * out.stats_groups + block) * 2;
-    st[0] = mx;
-    st[1] = z;
-  }
+  vocabulary_block(acc, out, m, block, M, N, vec_ok, tp, lane);
 }
 
 constexpr int kStreamGrid = 256;   // one workgroup per compute unit, of at most eight wavefronts with a block of 32 columns each
@@ -1201,6 +1207,58 @@ __global__ void __launch_bounds__(256) gemm_f32_stream_kernel(const float* __res
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The vocabulary product of float32 models, up to 32 rows: as gemm_f16_stream_kernel.  Weights are row-major (a request of a wavefront
+// is 32 bytes of 32 rows).  The sums of the kernel above, bit for bit.  In the step, 32 rows of 32000 x 512: 20.0 -> 16.8 us (66 MB,
+// 3.9 TB/s); bound by memory, beside 7 us of matrix instructions per wavefront.
+template <int KS, int T>
+__global__ void __launch_bounds__(T) gemm_f32_vocabulary_kernel(const float* __restrict__ A, const float* __restrict__ B, int M, int N,
+                                                                const int32_t* __restrict__ tpos, int vec_ok, GemmOut out) {
+  constexpr int P = 32, K = KS * 8;
+  constexpr int kPiece = 32 * 16 + 16;   // bytes of 4 columns of all rows
+  constexpr int CH = 32 * KS * 2 / T;    // 16-byte pieces of the rows per thread
+  __shared__ __attribute__((aligned(16))) char rows[KS * 2 * kPiece];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const long tp = tpos ? *tpos : 0;
+  const int block = (int)blockIdx.x + (int)gridDim.x * wave, blocks = (N + 31) / 32;
+  const int first = min(block, blocks - 1) * 32, has = min(32, N - first);   // rows of B
+  // a wavefront without a block: nothing in range, its requests read nothing
+  const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(B) + (size_t)first * K, (short)0, block < blocks ? has * K * 4 : 0, 0x00027000);
+  const int lane_at = min(lane & 31, has - 1) * (K * 4) + (lane >> 5) * 16;
+  auto request = [&](int ks) { return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(weights, lane_at + ks * 32, 0, 0)); };
+  floatx4 in[CH], w[P];
+  const unsigned pieces = M * (KS * 2);
+#pragma unroll
+  for (int i = 0; i < CH; ++i) in[i] = *reinterpret_cast<const floatx4*>(A + min((unsigned)(i * T + tid), pieces - 1) * 4u);
+  __builtin_amdgcn_sched_barrier(0);   // requests are answered in order: the rows first
+#pragma unroll
+  for (int i = 0; i < P; ++i) w[i] = request(i);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < CH; ++i) {
+    const unsigned p = min((unsigned)(i * T + tid), pieces - 1);   // the last piece again past the end: the same value
+    *reinterpret_cast<floatx4*>(&rows[p % (KS * 2) * kPiece + p / (KS * 2) * 16]) = in[i];
+  }
+  __syncthreads();
+  if (block >= blocks) return;
+  floatx16 acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
+  const int m = lane & 31, at = (lane >> 5) * kPiece + min(m, M - 1) * 16;   // rows past the last one repeat it
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const floatx4 x = *reinterpret_cast<const floatx4*>(&rows[ks * 2 * kPiece + at]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[ks & 3] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[ks % P][q], x[q], acc[ks & 3], 0, 0, 0);
+    if (ks + P < KS) w[ks % P] = request(ks + P);
+    if ((ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+  vocabulary_block(acc, out, m, block, M, N, vec_ok, tp, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1456,6 +1514,23 @@ bool gemm_writes_stats(int dtype, int M, int N, int K) {
   return M > 0 && N > 0 && K > 0 && K % 8 == 0;
 }
 
+// Vocabulary-sized float32 products of up to 32 rows; alone, gemm_f32_stream_kernel | this one, us: 32000 x 512 of 1 row 16.5 | 15.2, 8 rows 17.2 |
+// 15.0, 32 rows 21.2 | 15.7; 32000 x 1024 32.0 | 25.7, 32 rows 42.4 | 26.8; 50257 x 768 55 | 40, 32 rows 77.5 | 41.2.  Other k: not built.
+static bool f32_vocabulary_supported(int M, int N, int K) {
+  return M <= 32 && (N + 127) / 128 >= 125 && N <= kStreamGrid * 8 * 32 && (K == 512 || K == 768 || K == 1024);
+}
+
+static void run_f32_vocabulary(const float* A, const float* B, const GemmOut& out, int M, int N, int K, int vec_ok, hipStream_t s) {
+  const bool few = (N + 31) / 32 <= kStreamGrid * 4;   // four wavefronts are enough
+#define LSQ_VOCABULARY(KS_)                                                                                              \
+  if (few) gemm_f32_vocabulary_kernel<KS_, 256><<<kStreamGrid, 256, 0, s>>>(A, B, M, N, out.tpos, vec_ok, out);         \
+  else gemm_f32_vocabulary_kernel<KS_, 512><<<kStreamGrid, 512, 0, s>>>(A, B, M, N, out.tpos, vec_ok, out)
+  if (K == 512) { LSQ_VOCABULARY(64); }
+  else if (K == 768) { LSQ_VOCABULARY(96); }
+  else { LSQ_VOCABULARY(128); }
+#undef LSQ_VOCABULARY
+}
+
 // Products of 200 and more 128x128 tiles: which tiles.  256x256 (144 KB of LDS, eight wavefronts of 128x64) need the fewest LDS
 // reads per FLOP, 256x128 and 128x128 some 10 and 15 % more time per FLOP; but a last round of workgroups that leaves most
 // CUs idle costs as much as a full one.  So: the largest (share of the rounds' capacity that is work) x (rate of the tile).
@@ -1507,7 +1582,9 @@ hipError_t launch_gemm(int dtype, const void* A, const void* B, const void* bias
       const float* b = (const float*)B;
       const float* bi = (const float*)bias;
       const int per_wave = (K / 8 + 3) / 4;
-      if (M <= 32) {
+      if (!bi && !act && f32_vocabulary_supported(M, N, K)) {
+        run_f32_vocabulary(a, b, out, M, N, K, vec_ok, s);
+      } else if (M <= 32) {
         dim3 grid((N + 31) / 32, 1, 1), blk(256);
         if (per_wave <= 8) gemm_f32_stream_kernel<1, 8><<<grid, blk, 0, s>>>(a, b, M, N, K, out.tpos, bi, act, vec_ok, out);
         else gemm_f32_stream_kernel<1, 16><<<grid, blk, 0, s>>>(a, b, M, N, K, out.tpos, bi, act, vec_ok, out);

@@ -824,3 +824,19 @@ def test_vocabulary_product_with_fragment_ordered_weights(env, M, N, K):
     lsq.k_gemm(A, W, None, ref)
     assert torch.equal(C[:M], ref)
     assert (C[M] == 7.0).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 15873, 512), (32, 32000, 512), (5, 32769, 512), (31, 50257, 768), (32, 32003, 768),
+                                   (32, 32000, 1024), (9, 65536, 1024), (17, 65505, 512)])
+def test_vocabulary_product_of_float32(env, M, N, K):
+    """The kernel that keeps all input rows in LDS: the bits of the general float32 kernel (which a bias, here of zeros, selects)."""
+    lsq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn(M, K, generator=g, device="cuda")
+    W = torch.randn(N, K, generator=g, device="cuda") * 0.2
+    C = torch.full((M + 1, N), 7.0, dtype=torch.float32, device="cuda")
+    ref = torch.empty(M, N, dtype=torch.float32, device="cuda")
+    lsq.k_gemm(A, W, None, C[:M])
+    lsq.k_gemm(A, W, torch.zeros(N, device="cuda"), ref)
+    assert torch.equal(C[:M], ref)
+    assert (C[M] == 7.0).all()
