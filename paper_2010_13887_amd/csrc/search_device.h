@@ -33,7 +33,7 @@ constexpr int kTopkGroupsQ = 128, kTopkGroupsC = 160;
 
 // One row by one wavefront; ql, cs, ci: the wavefront's own LDS lists (kTopkGroupsQ, kTopkGroupsC entries); os, oi:
 // where the k pairs go (global memory or LDS).
-template <int GPL>
+template <int GPL, int PB = 8>
 __device__ __forceinline__ void topk_groups_row(const float* __restrict__ logits, const float* __restrict__ stats,
                                                 const float* __restrict__ score, const int32_t* __restrict__ fin,
                                                 int r, int V, int G, int k, int eos, float* os, int32_t* oi, int lane,
@@ -115,7 +115,6 @@ __device__ __forceinline__ void topk_groups_row(const float* __restrict__ logits
   int nc = 0;
   if (nq <= QMAX) {
     // two groups per pass (lanes 0-31 one, lanes 32-63 the next), the logits of PB passes requested together
-    constexpr int PB = 8;
     for (int p0 = 0; p0 < nq && nc <= CMAX; p0 += 2 * PB) {
       float xs[PB];
       int vs[PB];
@@ -141,12 +140,21 @@ __device__ __forceinline__ void topk_groups_row(const float* __restrict__ logits
   }
   __builtin_amdgcn_wave_barrier();
   if (nq <= QMAX && nc <= CMAX) {
-    for (int c = lane; c < nc; c += 64) {
-      const float sc = cs_w[c];
-      const int v = ci_w[c];
+    if (nc <= 64) {
+      const float sc = lane < nc ? cs_w[lane] : -INFINITY;
+      const int v = lane < nc ? ci_w[lane] : 0x7fffffff;
       int rank = 0;
-      for (int o = 0; o < nc; ++o) rank += precedes(cs_w[o], ci_w[o], sc, v) ? 1 : 0;
-      if (rank < k) { os[rank] = sc; oi[rank] = v; }
+      for (int o = 0; o < nc; ++o)
+        rank += precedes(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc), o)), __builtin_amdgcn_readlane(v, o), sc, v) ? 1 : 0;
+      if (lane < nc && rank < k) { os[rank] = sc; oi[rank] = v; }
+    } else {
+      for (int c = lane; c < nc; c += 64) {
+        const float sc = cs_w[c];
+        const int v = ci_w[c];
+        int rank = 0;
+        for (int o = 0; o < nc; ++o) rank += precedes(cs_w[o], ci_w[o], sc, v) ? 1 : 0;
+        if (rank < k) { os[rank] = sc; oi[rank] = v; }
+      }
     }
     if (lane >= nc && lane < k) { os[lane] = -INFINITY; oi[lane] = -1; }   // vocabulary smaller than k
     return;
@@ -177,22 +185,28 @@ __device__ __forceinline__ void topk_groups_row(const float* __restrict__ logits
   }
 }
 
+// Two float16 of a word: x * scale + p, rounded once, to float16.  As written out: left to itself the compiler takes this
+// instruction for some elements and a float32 sum with a conversion behind it for others, differently for every number of chunks
+// below, and then one row's input depends on how many rows are made at once.
+__device__ __forceinline__ unsigned scaled_sum(unsigned x, float scale, float p0, float p1) {
+  unsigned y;   // written by halves: a wait state before each reader, which the compiler cannot add in here
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]\n\ts_nop 1\n\t"
+      "v_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\ts_nop 1" : "=&v"(y) : "v"(x), "v"(scale), "v"(p0), "v"(p1));
+  return y;
+}
+
 // x[base + i] = E[tok[i]] * scale + pe[pos] for the k rows of a sentence (tok[i] < 0: row left alone), by one
-// wavefront: the rows' 16-byte chunks are dealt out over the lanes and requested eight per lane at a time, so the
-// k gathers travel together instead of one row after the other.  The arithmetic is embed_row's.
-template <typename T>
-__device__ __forceinline__ void next_input_rows(const NextInput& nx, const int* tok, int base, int k, int pos, int lane) {
+// wavefront: the rows' 16-byte chunks are dealt out over the lanes and requested up to eight per lane at a time, so the
+// k gathers travel together instead of one row after the other.  One row of d = 512 is one chunk per lane: eight, seven of them
+// repetitions, with the two savings in topk_groups_row, cost 1.0 to 1.3 us of a search kernel of 8.6 to 10.5.
+// The arithmetic is embed_row's.
+template <typename T, int U>
+__device__ __forceinline__ void next_input_chunks(const NextInput& nx, const int* tok, int base, int k, int pos, int lane) {
   const int d = nx.d;
   const T* E = (const T*)nx.E;
   T* x = (T*)nx.x;
   const float* pe = nx.pe + (size_t)pos * d;
-  if ((d & 7) != 0) {
-    for (int i = 0; i < k; ++i)
-      if (tok[i] >= 0) embed_row<T>(E + (size_t)tok[i] * d, pe, x + (size_t)(base + i) * d, d, nx.scale, lane, 64);
-    return;
-  }
   using raw_t = typename Vec8<T>::raw_t;
-  constexpr int U = 8;
   const int cpr = d >> 3, total = k * cpr;
   for (int u0 = 0; u0 < total; u0 += 64 * U) {
     raw_t e[U];
@@ -210,15 +224,37 @@ __device__ __forceinline__ void next_input_rows(const NextInput& nx, const int* 
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      float v[8];
-      Vec8<T>::unpack(e[u], v);
+      if constexpr (sizeof(T) == 2) {
+        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+        const u32x4 w = __builtin_bit_cast(u32x4, e[u]);
+        const u32x4 y = {scaled_sum(w.x, nx.scale, pa[u][0], pa[u][1]), scaled_sum(w.y, nx.scale, pa[u][2], pa[u][3]),
+                         scaled_sum(w.z, nx.scale, pb[u][0], pb[u][1]), scaled_sum(w.w, nx.scale, pb[u][2], pb[u][3])};
+        if (row[u] >= 0) *reinterpret_cast<raw_t*>(x + (size_t)row[u] * d + col[u]) = __builtin_bit_cast(raw_t, y);
+      } else {
+        float v[8];
+        Vec8<T>::unpack(e[u], v);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        v[c] = __fadd_rn(__fmul_rn(v[c], nx.scale), pa[u][c]);
-        v[4 + c] = __fadd_rn(__fmul_rn(v[4 + c], nx.scale), pb[u][c]);
+        for (int c = 0; c < 4; ++c) {
+          v[c] = __builtin_fmaf(v[c], nx.scale, pa[u][c]);
+          v[4 + c] = __builtin_fmaf(v[4 + c], nx.scale, pb[u][c]);
+        }
+        if (row[u] >= 0) Vec8<T>::store(x + (size_t)row[u] * d + col[u], v);
       }
-      if (row[u] >= 0) Vec8<T>::store(x + (size_t)row[u] * d + col[u], v);
     }
+  }
+}
+template <typename T>
+__device__ __forceinline__ void next_input_rows(const NextInput& nx, const int* tok, int base, int k, int pos, int lane) {
+  const int d = nx.d, chunks = k * (d >> 3);
+  if ((d & 7) != 0) {
+    for (int i = 0; i < k; ++i)
+      if (tok[i] >= 0) embed_row<T>((const T*)nx.E + (size_t)tok[i] * d, nx.pe + (size_t)pos * d, (T*)nx.x + (size_t)(base + i) * d, d, nx.scale, lane, 64);
+  } else if (chunks <= 64) {
+    next_input_chunks<T, 1>(nx, tok, base, k, pos, lane);
+  } else if (chunks <= 128) {
+    next_input_chunks<T, 2>(nx, tok, base, k, pos, lane);
+  } else {
+    next_input_chunks<T, 8>(nx, tok, base, k, pos, lane);
   }
 }
 
@@ -328,7 +364,7 @@ __device__ __forceinline__ void retrieve_rerank_sentence(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   constexpr int k = K, kk = K * K;   // known to the compiler: a wavefront on its own takes 8 cycles for every instruction
   const int base = b * k, row = base + wave;
-  topk_groups_row<GPL>(logits, stats, score, fin, row, V, G, k, eos, sh.cand_s + wave * k, sh.cand_i + wave * k, lane,
+  topk_groups_row<GPL, K <= 4 ? 4 : 8>(logits, stats, score, fin, row, V, G, k, eos, sh.cand_s + wave * k, sh.cand_i + wave * k, lane,
                        sh.ql[wave], sh.cs[wave], sh.ci[wave]);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the histories are here before any wavefront of the sentence overwrites them
   __syncthreads();   // blockDim.x = 64 k: every wavefront has a row

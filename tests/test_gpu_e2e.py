@@ -240,6 +240,32 @@ def test_retrieve_from_group_statistics_agrees_with_full_rows(lsq, vocab, beam):
     np.testing.assert_allclose(sc0[same], sc1[same], rtol=0, atol=2e-5)
 
 
+@pytest.mark.parametrize("beam,period", [(4, 410), (2, 410), (4, 82), (8, 82)])
+def test_retrieve_in_one_launch_agrees_with_two_on_tied_logits(lsq, beam, period):
+    """Embedding rows that repeat: 20 or 100 tokens of equal logits, each in a group of its own, so that more groups reach the
+    threshold than one pass of the merged kernel takes, with up to and more than 64 candidates: the bits of the two launches,
+    and of ties the lowest tokens."""
+    V, d = 8200, 128
+    hp = S.HParams(n_enc=1, n_dec=1, d_model=d, n_heads=2, d_ffn=256, vocab=V, max_pos=64, dtype=1, cap_extra=6)
+    w = S.custom(hp, [3, 9, 5], beam=beam, max_len=20, std=0.05)
+    blob = bytearray(w.blob(ln_jitter=0.1))
+    E = np.frombuffer(blob, np.float16, V * d, offset=256).reshape(V, d)
+    E[:] = E[np.arange(V) % period].copy()
+    out = {}
+    try:
+        for mode in (2, 1):
+            lsq.lsq_set_topk_statistics(mode)
+            with lsq.Engine(bytes(blob), 3, beam, 20) as eng:
+                out[mode] = eng.translate(w.src_ids, w.src_lens, sync_every=2)
+    finally:
+        lsq.lsq_set_topk_statistics(1)
+    for a, b in zip(out[1], out[2]):
+        assert np.array_equal(a, b)
+    ids, lens, _ = out[1]
+    first = np.asarray(ids)[..., 1] if np.asarray(ids).ndim == 3 else np.asarray(ids)[:, 1]
+    assert (np.asarray(lens) >= 1).all() and (first < period * beam).all()   # ties at one step: the first `beam` of them
+
+
 @pytest.mark.parametrize("beam,heads,refresh", [(4, 4, "table"), (3, 8, "move"), (1, 4, "table"), (2, 8, "table")])
 def test_attention_blocks_agree_with_separate_kernels(lsq, beam, heads, refresh):
     """Attention sublayers as one launch each (default, at most 64 rows alive) against the separate kernels: the
