@@ -840,3 +840,23 @@ def test_vocabulary_product_of_float32(env, M, N, K):
     lsq.k_gemm(A, W, torch.zeros(N, device="cuda"), ref)
     assert torch.equal(C[:M], ref)
     assert (C[M] == 7.0).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 264, 128), (130, 520, 256), (129, 3080, 64), (300, 4104, 128), (257, 4224, 320),
+                                   (70, 16008, 64), (601, 2056, 192), (1100, 4104, 192), (2300, 2312, 64)])
+@pytest.mark.parametrize("f32_out", [False, True])
+def test_whole_line_stores_agree_with_unaligned_output(env, M, N, K, f32_out):
+    """An output whose rows are not on 16 bytes is stored straight from the accumulators: the same bits as through LDS, in every
+    tile shape, with ragged rows and columns; nothing around the matrix is touched."""
+    lsq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, W = torch.randn(M, K, generator=g, device="cuda").half(), (torch.randn(N, K, generator=g, device="cuda") * 0.1).half()
+    bias = torch.randn(N, generator=g, device="cuda").half()
+    out = []
+    for shift in (0, 1 if f32_out else 4):
+        buf = torch.full((M * N + 64,), 7.0, dtype=torch.float32 if f32_out else torch.float16, device="cuda")
+        C = buf[16 + shift:16 + shift + M * N].view(M, N)
+        lsq.k_gemm(A, W, bias, C, relu=True)
+        assert (buf[:16 + shift] == 7.0).all() and (buf[16 + shift + M * N:] == 7.0).all()
+        out.append(C.clone())
+    assert torch.equal(out[0], out[1])
