@@ -227,12 +227,14 @@ __global__ void __launch_bounds__(64) embed_layernorm_kernel(const T* __restrict
   for (int j = 0; j < NV; ++j) {
     const int c = (j * 64 + lane) * 8;
     if (c < d) {
-      Vec8<T>::load(e + c, v[j]);
+      float p[8];
+      const typename Vec8<T>::raw_t raw = Vec8<T>::load_raw(e + c);
+      Vec8<float>::load(per + c, p);
       Vec8<T>::load(g + c, gv[j]);
       Vec8<T>::load(b + c, bv[j]);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[j][i] = (float)(T)__fadd_rn(__fmul_rn(v[j][i], scale), per[c + i]);   // as embed_row stores it
-      Vec8<T>::store(x + (size_t)r * d + c, v[j]);
+      const typename Vec8<T>::raw_t row = scaled_sums(raw, scale, p);   // as embed_row stores it
+      *reinterpret_cast<typename Vec8<T>::raw_t*>(x + (size_t)r * d + c) = row;
+      Vec8<T>::unpack(row, v[j]);
     } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i) { v[j][i] = 0.f; gv[j][i] = 0.f; bv[j][i] = 0.f; }

@@ -911,8 +911,9 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
           const half4_t e4 = half4_at(a.E + (size_t)embedding_row(a.tokens[(size_t)r * (a.T + 1) + a.len[r]]) * D, oc);
           const floatx4 p4 = *reinterpret_cast<const floatx4*>(a.pe + (size_t)pos * D + oc);
           float v[4];
+          h = scaled_sums(e4, 1.0f, p4);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) { h[i] = (half_t)__fadd_rn((float)e4[i], p4[i]); v[i] = (float)h[i]; }
+          for (int i = 0; i < 4; ++i) v[i] = (float)h[i];
           if (oact) *reinterpret_cast<half4_t*>(&xrow[oc]) = h;
           own_publish(v, g4, b4, l, Rg::xi, nullptr);
         } else {

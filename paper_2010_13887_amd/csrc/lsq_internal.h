@@ -503,21 +503,54 @@ template <> struct Vec8<float> {
 // The embedding row of a token.  A sampled row without candidates (all of its logits NaN) appends -1; it reads row 0.
 __device__ __forceinline__ int embedding_row(int token) { return max(token, 0); }
 
-// x[r,:] = store(E[id_r,:] * sqrt(d) + PE[pos_r,:]).  Product and sum are rounded separately
-// (no fused multiply-add) so the fp32 value before storage is the textbook one.
+// x * scale + p as an input row stores it, with the instructions written out: the first step's rows, those that the search kernels
+// leave for the next step and those that the stack kernels make for themselves have to be the same bits, and left to itself the compiler
+// fuses, rounds once or rounds twice as it finds convenient in each place (and with -ffp-contract differently again).
+// Two float16 of a word: one multiply-add, rounded once, to float16.
+__device__ __forceinline__ unsigned scaled_sum(unsigned x, float scale, float p0, float p1) {
+  unsigned y;   // written by halves: a wait state before each reader, which the compiler cannot add in here
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]\n\ts_nop 1\n\t"
+      "v_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\ts_nop 1" : "=&v"(y) : "v"(x), "v"(scale), "v"(p0), "v"(p1));
+  return y;
+}
+__device__ __forceinline__ half_t scaled_sum(half_t x, float scale, float p) {
+  const unsigned y = scaled_sum((unsigned)__builtin_bit_cast(unsigned short, x), scale, p, p);
+  return __builtin_bit_cast(half_t, (unsigned short)y);
+}
+__device__ __forceinline__ float scaled_sum(float x, float scale, float p) { return __builtin_fmaf(x, scale, p); }
+// N in a row
+__device__ __forceinline__ half8_t scaled_sums(const half8_t& x, float scale, const float (&p)[8]) {
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 w = __builtin_bit_cast(u32x4, x);
+  const u32x4 y = {scaled_sum(w.x, scale, p[0], p[1]), scaled_sum(w.y, scale, p[2], p[3]), scaled_sum(w.z, scale, p[4], p[5]),
+                   scaled_sum(w.w, scale, p[6], p[7])};
+  return __builtin_bit_cast(half8_t, y);
+}
+__device__ __forceinline__ half4_t scaled_sums(const half4_t& x, float scale, const floatx4& p) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 w = __builtin_bit_cast(u32x2, x);
+  const u32x2 y = {scaled_sum(w.x, scale, p[0], p[1]), scaled_sum(w.y, scale, p[2], p[3])};
+  return __builtin_bit_cast(half4_t, y);
+}
+__device__ __forceinline__ Vec8<float>::raw_t scaled_sums(const Vec8<float>::raw_t& x, float scale, const float (&p)[8]) {
+  Vec8<float>::raw_t y;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { y.a[i] = scaled_sum(x.a[i], scale, p[i]); y.b[i] = scaled_sum(x.b[i], scale, p[4 + i]); }
+  return y;
+}
+
+// x[r,:] = store(E[id_r,:] * sqrt(d) + PE[pos_r,:])
 template <typename T>
 __device__ __forceinline__ void embed_row(const T* __restrict__ e, const float* __restrict__ pe,
                                           T* __restrict__ x, int d, float scale, int lane, int nl) {
   if ((d & 7) == 0) {
     for (int c = lane * 8; c < d; c += nl * 8) {
-      float v[8];
-      Vec8<T>::load(e + c, v);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = __fadd_rn(__fmul_rn(v[i], scale), pe[c + i]);
-      Vec8<T>::store(x + c, v);
+      float p[8];
+      Vec8<float>::load(pe + c, p);
+      *reinterpret_cast<typename Vec8<T>::raw_t*>(x + c) = scaled_sums(Vec8<T>::load_raw(e + c), scale, p);
     }
   } else {
-    for (int c = lane; c < d; c += nl) x[c] = (T)__fadd_rn(__fmul_rn((float)e[c], scale), pe[c]);
+    for (int c = lane; c < d; c += nl) x[c] = scaled_sum(e[c], scale, pe[c]);
   }
 }
 

@@ -185,21 +185,11 @@ __device__ __forceinline__ void topk_groups_row(const float* __restrict__ logits
   }
 }
 
-// Two float16 of a word: x * scale + p, rounded once, to float16.  As written out: left to itself the compiler takes this
-// instruction for some elements and a float32 sum with a conversion behind it for others, differently for every number of chunks
-// below, and then one row's input depends on how many rows are made at once.
-__device__ __forceinline__ unsigned scaled_sum(unsigned x, float scale, float p0, float p1) {
-  unsigned y;   // written by halves: a wait state before each reader, which the compiler cannot add in here
-  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]\n\ts_nop 1\n\t"
-      "v_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\ts_nop 1" : "=&v"(y) : "v"(x), "v"(scale), "v"(p0), "v"(p1));
-  return y;
-}
-
 // x[base + i] = E[tok[i]] * scale + pe[pos] for the k rows of a sentence (tok[i] < 0: row left alone), by one
 // wavefront: the rows' 16-byte chunks are dealt out over the lanes and requested up to eight per lane at a time, so the
 // k gathers travel together instead of one row after the other.  One row of d = 512 is one chunk per lane: eight, seven of them
 // repetitions, with the two savings in topk_groups_row, cost 1.0 to 1.3 us of a search kernel of 8.6 to 10.5.
-// The arithmetic is embed_row's.
+// The arithmetic is embed_row's (scaled_sum).
 template <typename T, int U>
 __device__ __forceinline__ void next_input_chunks(const NextInput& nx, const int* tok, int base, int k, int pos, int lane) {
   const int d = nx.d;
@@ -224,22 +214,9 @@ __device__ __forceinline__ void next_input_chunks(const NextInput& nx, const int
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if constexpr (sizeof(T) == 2) {
-        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-        const u32x4 w = __builtin_bit_cast(u32x4, e[u]);
-        const u32x4 y = {scaled_sum(w.x, nx.scale, pa[u][0], pa[u][1]), scaled_sum(w.y, nx.scale, pa[u][2], pa[u][3]),
-                         scaled_sum(w.z, nx.scale, pb[u][0], pb[u][1]), scaled_sum(w.w, nx.scale, pb[u][2], pb[u][3])};
-        if (row[u] >= 0) *reinterpret_cast<raw_t*>(x + (size_t)row[u] * d + col[u]) = __builtin_bit_cast(raw_t, y);
-      } else {
-        float v[8];
-        Vec8<T>::unpack(e[u], v);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          v[c] = __builtin_fmaf(v[c], nx.scale, pa[u][c]);
-          v[4 + c] = __builtin_fmaf(v[4 + c], nx.scale, pb[u][c]);
-        }
-        if (row[u] >= 0) Vec8<T>::store(x + (size_t)row[u] * d + col[u], v);
-      }
+      const float p[8] = {pa[u][0], pa[u][1], pa[u][2], pa[u][3], pb[u][0], pb[u][1], pb[u][2], pb[u][3]};
+      const raw_t y = scaled_sums(e[u], nx.scale, p);
+      if (row[u] >= 0) *reinterpret_cast<raw_t*>(x + (size_t)row[u] * d + col[u]) = y;
     }
   }
 }

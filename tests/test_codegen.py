@@ -1,0 +1,50 @@
+"""What the device code has to say in so many words rather than leave to the compiler: small kernels around the library's device
+functions are compiled (no GPU needed) and their instructions looked at."""
+import collections
+import re
+import subprocess
+
+import pytest
+
+
+def _instructions(tmp_path, source, *flags):
+    """{kernel: Counter of instructions, with their cache policy bits} of a translation unit beside the library's own"""
+    from paper_2010_13887_amd import build as B
+    src = tmp_path / "unit.hip"
+    src.write_text(source)
+    out = tmp_path / "unit.s"
+    r = subprocess.run([B._hipcc(), *B.FLAGS, *flags, "-I", B.CSRC, "--cuda-device-only", "-S", str(src), "-o", str(out)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    found, name = {}, None
+    for line in out.read_text().splitlines():
+        if m := re.match(r"(\w+):", line):
+            name = m.group(1)
+        elif name and (m := re.match(r"\s+([a-z]\w+)(.*)", line)):
+            policy = " ".join(re.findall(r"\b(sc[01]|nt)\b", m.group(2)))
+            found.setdefault(name, collections.Counter())[f"{m.group(1)} {policy}".strip()] += 1
+    return found
+
+
+ROWS = """
+#include "search_device.h"
+using namespace lsq;
+extern "C" __global__ void first_f16(const half_t* e, const float* pe, half_t* x, int d, float s) { embed_row<half_t>(e, pe, x, d, s, threadIdx.x, 64); }
+extern "C" __global__ void first_f32(const float* e, const float* pe, float* x, int d, float s) { embed_row<float>(e, pe, x, d, s, threadIdx.x, 64); }
+extern "C" __global__ void unscaled_f16(const half_t* e, const float* pe, half_t* x) { embed_row<half_t>(e, pe, x, 512, 1.0f, threadIdx.x, 64); }
+extern "C" __global__ void next_f16(NextInput nx, const int* tok, int k, int pos) { next_input_rows<half_t>(nx, tok, 0, k, pos, threadIdx.x); }
+extern "C" __global__ void next_f32(NextInput nx, const int* tok, int k, int pos) { next_input_rows<float>(nx, tok, 0, k, pos, threadIdx.x); }
+"""
+
+
+@pytest.mark.parametrize("contract", ["off", "fast"])
+def test_input_rows_are_one_arithmetic_whatever_the_compiler_likes(tmp_path, contract):
+    """x * scale + p of a decoder input row: one multiply-add, rounded once to the type that is stored, in the kernels that make the
+    first step's rows and in those that make every later step's, with and without contraction."""
+    found = _instructions(tmp_path, ROWS, f"-ffp-contract={contract}")
+    for kernel in ("first_f16", "first_f32", "unscaled_f16", "next_f16", "next_f32"):
+        ops = found[kernel]
+        loose = [i for i in ops if re.match(r"v_(pk_)?add_f(16|32)|v_cvt_(pk_)?f16_f32|v_cvt_pkrtz", i)]
+        assert not loose, (kernel, loose)
+        fused = sum(n for i, n in ops.items() if re.match(r"v_fma_mix(lo|hi)_f16" if kernel.endswith("f16") else r"v_(fma|fmac)_f32", i))
+        assert fused >= 8, (kernel, ops)

@@ -99,6 +99,30 @@ def test_sampling_model_refuses_a_beam(lsq):
         lsq.Engine(bad, 1, 1, 8)
 
 
+@pytest.mark.parametrize("d,heads,dtype", [(512, 8, 1), (1024, 16, 1), (512, 8, 0), (192, 6, 1), (192, 6, 0)])
+def test_input_rows_of_the_embedding_and_of_the_search_kernel_are_the_same_bits(lsq, d, heads, dtype):
+    """The decoder's input rows made by a launch of their own at every step against those that the draw leaves for the next step, where
+    the factor sqrt(d) rounds: the same hidden rows bit for bit."""
+    hp = S.HParams(n_enc=1, n_dec=1, d_model=d, n_heads=heads, d_ffn=4 * d, vocab=203, max_pos=32, dtype=dtype, cap_extra=8,
+                   sample_topk=4, seed=3)
+    w = S.custom(hp, [5, 3, 7, 2, 6], beam=1, max_len=15, std=0.08 if dtype else 0.3)
+    blob = w.blob(ln_jitter=0.1)
+    seen = {}
+    try:
+        for mode in (1, 2):
+            lsq.lsq_set_topk_statistics(mode)
+            with lsq.Engine(blob, w.batch, 1, w.max_len) as eng:
+                eng.encode(w.src_ids, w.src_lens)
+                for step in range(4):
+                    assert eng.decode_step() > 0
+                    seen[mode, step] = [eng.debug(lsq.DBG.HIDDEN, (w.batch, d)), eng.debug(lsq.DBG.TOKENS, (w.batch, w.max_len + 1), np.int32)]
+    finally:
+        lsq.lsq_set_topk_statistics(1)
+    for step in range(4):
+        assert all(np.array_equal(a, b) for a, b in zip(seen[1, step], seen[2, step])), step
+    assert not np.array_equal(seen[1, 2][0], seen[1, 3][0])
+
+
 def test_transformer_base_top32_nucleus(lsq):
     """The paper's text-generation shape: Transformer-base, top-k 32 / top-p 0.75, batch 32; a few steps in
     lock-step, then the whole generation with properties that hold at any size."""
