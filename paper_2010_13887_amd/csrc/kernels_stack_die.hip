@@ -1,11 +1,21 @@
 // Decoder layers of one step in one launch, each group of rows on a die of its own (float16, heads of 64, FFN of 4d).
 //
 // The chip is eight dies with 32 compute units and an L2 each.  What the workgroups of one die hand each other need not leave
-// its L2: plain stores, which end there, read with agent-scope loads, which look there (a workgroup's own L1 is passed by).
+// its L2: it is stored with workgroup scope and read with agent-scope loads.  Workgroup scope is enough to reach another compute
+// unit of the die: the wavefronts of a workgroup may be spread over several of them (threadgroup split mode, -mtgsplit), for which the
+// compiler's stores of that scope carry the same bit, sc0, and nothing is done to the L2, which all compute units that a workgroup can be on
+// share.  An agent-scope load includes workgroup scope and passes the reader's own L1 by.  A store without a scope promises nothing before
+// the kernel ends, and is no faster (whole translations, 4 to 32 rows: 1.00 times).
 // Measured, 32 workgroups that all write a slice and read all of 8 KB: 0.50 us per exchange, against 0.99 with agent-scope
 // stores and 1.16 among 128 workgroups all over the chip (kernels_stack.hip).  The price is that every die reads all weights:
 // 1.34 TB/s for one die or two, 1.0 for four, 0.92 for all eight (7.4 TB/s together, from the memory-side cache).  So this is for
-// models whose layers are small (d = 512: 44 MB, 48 us).
+// models whose layers are small (d = 512: 44 MB, 48 us; d = 256, of which nothing is known, stays with kernels_stack.hip).
+//
+// Not explained: a kernel that was not kept, with 32 to 64 rows a die (129 to 512 in all), 16 KB per poll and stores without a
+// scope, had a wait that ran out once in 1500 to 7000 launches: a value was published and not seen.  This one, with 16 rows a die at
+// most, had none in 187 500 launches with the same stores.  Those stores are the only thing found in it that no memory model
+// covers; whether they were the cause is not known.  If a wait does run out no result is lost: the translation is decoded again
+// (lsq_runtime.hip, decode_again).
 //
 // A compute unit's loads come back in the order in which they were issued, whoever issued them: one that finds its line in the
 // L2 takes 240 clocks on an idle unit, 560 / 790 / 1590 / 2640 behind 8 / 16 / 32 / 64 KB of weights.  When weights are
@@ -102,7 +112,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   const int r0 = grp * a.rows_per_group, rows = min(a.rows_per_group, a.M - r0);
   const int seq = a.state[0], parity = seq & 1, dirty = a.state[2 - parity], pos = *a.tpos;
 
-  Exchange<0> ex;   // plain stores: they stop at the die's L2, where the readers' agent-scope loads look
+  Exchange<kWorkgroup> ex;   // stores that end in the die's L2, where the readers' agent-scope loads look
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
   ex.polls = seq < 0 || die_id() != (a.dies >> (4 * grp) & 15) ? 1 : kSpinLimit;
   const int layer_bytes = Rg::size * D * R;

@@ -12,6 +12,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
 constexpr int kAgent = 16;             // cache policy of agent scope: sc1
+constexpr int kWorkgroup = 1;          // ... of workgroup scope: sc0
 constexpr int kSpinLimit = 1 << 19;    // polls of about a microsecond
 constexpr int kThreads = 512, kWaves = 8;
 
@@ -34,9 +35,10 @@ template <bool PRE> struct Region {
   static constexpr int ff = PRE ? 10 : 20, u3 = PRE ? 18 : 28, size = PRE ? 20 : 32;
 };
 
-// STORE: cache policy of what is published; 0 where all readers are on the writer's die (kernels_stack_die.hip)
+// STORE: cache policy of what is published; kWorkgroup where all readers are on the writer's die (kernels_stack_die.hip)
 template <int STORE = kAgent>
 struct Exchange {
+  static_assert(STORE == kAgent || STORE == kWorkgroup, "a store without a scope need not reach another compute unit before the kernel ends");
   __amdgpu_buffer_rsrc_t rsrc;
   int polls;   // of a wait; 1: one has run out, what this wavefront reads from now on may be missing
 

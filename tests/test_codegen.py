@@ -48,3 +48,16 @@ def test_input_rows_are_one_arithmetic_whatever_the_compiler_likes(tmp_path, con
         assert not loose, (kernel, loose)
         fused = sum(n for i, n in ops.items() if re.match(r"v_fma_mix(lo|hi)_f16" if kernel.endswith("f16") else r"v_(fma|fmac)_f32", i))
         assert fused >= 8, (kernel, ops)
+
+
+def test_values_published_on_a_die_leave_the_compute_unit(tmp_path):
+    """The kernels with a group of rows per die publish with stores of workgroup scope at least: a store without a scope is for the
+    wavefront itself, and nothing says when the compute units that poll for it see it."""
+    found = _instructions(tmp_path, '#include "kernels_stack_die.hip"\n')
+    kernels = [k for k in found if "decoder_die_kernel" in k and any(i.startswith("buffer_load") for i in found[k])]
+    assert len(kernels) == 6, list(found)   # groups of 4, 8 and 16 rows, post-LN and pre-LN
+    for k in kernels:
+        stores = [i for i in found[k] if i.startswith("buffer_store")]
+        assert stores and all(" sc" in i for i in stores), (k, stores)
+        polls = [i for i in found[k] if i.startswith("buffer_load")]
+        assert all("sc1" in i for i in polls), (k, polls)
