@@ -57,6 +57,8 @@ def load_library() -> C.CDLL:
         "lsq_set_canaries": [i32],
         "lsq_debug_check_canaries": [],
         "lsq_debug_end_stack_waits": [],
+        "lsq_debug_stack_launches": [vp],
+        "lsq_debug_forget_dies": [],
         "lsq_k_layernorm_gemm": [i32, vp, i32, vp, vp, vp, vp, vp, C.c_float, vp, vp, vp, i32, i32, i32, i32, vp],
         "lsq_k_layernorm_cross_attention": [vp, i32, vp, vp, vp, vp, vp, C.c_float, vp, vp, vp, vp, vp, vp, i32, i32, i32,
                                             i32, vp],
@@ -186,6 +188,18 @@ def lsq_debug_check_canaries() -> int:
 def lsq_debug_end_stack_waits() -> None:
     """The decoder stack kernels behave from the next launch on as after a wait that ran out (test hook)."""
     _check(load_library().lsq_debug_end_stack_waits())
+
+
+def lsq_debug_stack_launches() -> dict:
+    """Launches since lsq_init of the kernels that run all decoder layers of a step, by kernel (test hook)."""
+    n = np.zeros(4, np.int64)
+    _check(load_library().lsq_debug_stack_launches(n.ctypes.data))
+    return dict(zip(("die", "groups_of_8", "groups_of_16_or_32", "float32"), n.tolist()))
+
+
+def lsq_debug_forget_dies() -> None:
+    """The loaded model does without the kernels that want each group of rows on a die of its own (test hook)."""
+    _check(load_library().lsq_debug_forget_dies())
 
 
 def lsq_set_diversity(groups: int = 1, strength: float = 0.0) -> None:

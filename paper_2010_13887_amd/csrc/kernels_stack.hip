@@ -1040,10 +1040,10 @@ Choice choose(int arch, int M, int d) {
 
 const void* kernel_of(int dk, int x, int pre) {
 #define LSQ_STACK(DKV, XV) if (dk == DKV && x == XV) return pre ? (const void*)decoder_stack_kernel<DKV, XV, true> : (const void*)decoder_stack_kernel<DKV, XV, false>
-  if (!pre && x == 4) return dk == 1 ? (const void*)decoder_stack_kernel<1, 4, false> : nullptr;
-  if (dk == 2)   // post-LN models: the die kernel, at every length
-    return !pre ? nullptr : x == 1 ? (const void*)decoder_stack_kernel<2, 1, true> : x == 2 ? (const void*)decoder_stack_kernel<2, 2, true> : nullptr;
+  if (!pre && x == 4)
+    return dk == 1 ? (const void*)decoder_stack_kernel<1, 4, false> : dk == 2 ? (const void*)decoder_stack_kernel<2, 4, false> : nullptr;
   LSQ_STACK(1, 1); LSQ_STACK(1, 2);
+  LSQ_STACK(2, 1); LSQ_STACK(2, 2);   // post-LN: where the die kernel cannot run
   LSQ_STACK(3, 1); LSQ_STACK(3, 2);
   LSQ_STACK(4, 1); LSQ_STACK(4, 2);
 #undef LSQ_STACK

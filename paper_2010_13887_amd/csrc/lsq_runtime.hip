@@ -343,6 +343,7 @@ struct Ctx {
   char* E = nullptr;
   bool stack_ok = false;        // the decoder stack kernel takes this model
   StackArgs stack{};            // ... with these arguments (all but those of a translation)
+  int64_t stack_launches[kStackF32 + 1] = {};   // of this model, by StackKind
   bool small_ok = false;        // a beam search step of this model can be one launch
   SearchArgs search{};
   std::vector<GptLayer> gpt;
@@ -510,6 +511,7 @@ bool use_small(int B) {
 }
 
 hipError_t launch_stack(StackKind kind, StackArgs a) {
+  g.stack_launches[kind] += 1;
   if (kind == kStackDie) return launch_decoder_die(g.hp.arch, a, history(), g.stream);
   if (kind == kStackFew) return launch_decoder_stack(g.hp.arch, a, g.hp.d, g.stream);
   a.exchange = g.ws + g.plan.stack_rows_exchange;
@@ -1518,6 +1520,19 @@ int lsq_debug_end_stack_waits(void) {
   if (!g.stack_ok) return LSQ_OK;
   HIPCHK(launch_stack_end_waits(at<int32_t>(g.plan.stack_state), g.stream));
   HIPCHK(launch_stack_end_waits(at<int32_t>(g.plan.stack_state) + 8, g.stream));
+  return LSQ_OK;
+}
+
+int lsq_debug_stack_launches(int64_t* counts) {
+  if (g.state < 2) return fail(LSQ_E_STATE, "lsq_init has not been called");
+  if (!counts) return fail(LSQ_E_ARG, "counts is null");
+  for (int k = kStackDie; k <= kStackF32; ++k) counts[k - kStackDie] = g.stack_launches[k];
+  return LSQ_OK;
+}
+
+int lsq_debug_forget_dies(void) {
+  if (g.state < 2) return fail(LSQ_E_STATE, "lsq_init has not been called");
+  g.stack.dies = kNoDies;
   return LSQ_OK;
 }
 

@@ -106,6 +106,9 @@ int main() {
   EXPECT(lsq_set_diversity(1, 0.f) == LSQ_OK);
   EXPECT(lsq_set_cache_refresh(7) == LSQ_E_ARG);
   EXPECT(lsq_debug_read(LSQ_DBG_SCORE, sc, sizeof sc) == LSQ_E_STATE);
+  int64_t counts[4];
+  EXPECT(lsq_debug_stack_launches(counts) == LSQ_E_STATE);
+  EXPECT(lsq_debug_forget_dies() == LSQ_E_STATE);
   EXPECT(lsq_k_packed_weight_bytes(64, 24) == 0);
   EXPECT(lsq_k_packed_weight_bytes(33, 32) == 64u * 32 * 2);
   EXPECT(lsq_k_gemm_add_layernorm_scratch(1, 512, 1024, 4096) >= 512u * 1024 * 4);

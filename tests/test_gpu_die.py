@@ -56,3 +56,17 @@ def test_prompts_across_the_change_of_kernel_match_oracle(lsq, batch, prompt):
         launches = lsq.lsq_profile_read()["decoder_stack"][1]
         lsq.lsq_profile_enable(False)
         assert res["steps"] == 8 and launches == 8
+
+
+@pytest.mark.parametrize("batch,beam,steps,expected", [
+    (1, 1, 12, {"groups_of_8": 12}), (2, 4, 12, {"groups_of_8": 12}), (16, 1, 12, {"groups_of_16_or_32": 12}),
+    (10, 4, 140, {"groups_of_16_or_32": 95, "groups_of_8": 45}),   # groups of 8 rows from position 112 on, of which a source of 70 tokens counts as 17
+])
+def test_models_without_dies_match_oracle(lsq, batch, beam, steps, expected):
+    """Where the workgroups are not found on the dies where the die kernel wants them, d = 512 runs the kernels that are spread over
+    the chip: few rows and long histories in groups of 8 rows, as other widths do."""
+    w, blob = _long_workload(512, 8, [3 + (5 * i) % 7 for i in range(batch - 1)] + [70], beam, steps, 1)
+    with lsq.Engine(blob, batch, beam, w.max_len) as eng:
+        lsq.lsq_debug_forget_dies()
+        assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[batch - 1])["steps"] == steps
+        assert {k: n for k, n in lsq.lsq_debug_stack_launches().items() if n} == expected
