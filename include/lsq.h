@@ -161,8 +161,11 @@ int lsq_set_layernorm_fusion(int on);
  * other float16 shapes with d = 256 or 512 and beam <= 4 run each attention sublayer of a decoder layer as one
  * launch up to its output projection (sec. 2.1 taken further; lsq_k_self_attention_block,
  * lsq_k_cross_attention_block).  The workgroups of an all-layers launch wait for one another: streams with
- * a mask of compute units (at lsq_init) do without that kernel, and no wait is longer than half a second: where something else holds the compute units for longer (another process, a kernel on another stream), the
- * translation is decoded again from its start with the separate kernels, which the model keeps until lsq_free.
+ * a mask of compute units (at lsq_init) do without that kernel, and no wait is longer than half a second: where
+ * something else holds the compute units for longer (another process, a kernel on another stream), the translation is
+ * decoded again from its start with kernels that need less company, which the model keeps until lsq_free: d = 512 first goes from the
+ * kernel that wants each group of rows on a die of its own to those that are spread over the chip (also where a workgroup was
+ * not on the die where lsq_init had found it), everything else to the separate kernels.
  * 0 switches all of these off; default and largest value 64.  Same tokens as the separate
  * kernels; scores equal to rounding (other summation orders).  Also off when lsq_set_layernorm_fusion(0).  May
  * be called at any time. */

@@ -14,8 +14,8 @@
 // Not explained: a kernel that was not kept, with 32 to 64 rows a die (129 to 512 in all), 16 KB per poll and stores without a
 // scope, had a wait that ran out once in 1500 to 7000 launches: a value was published and not seen.  This one, with 16 rows a die at
 // most, had none in 187 500 launches with the same stores.  Those stores are the only thing found in it that no memory model
-// covers; whether they were the cause is not known.  If a wait does run out no result is lost: the translation is decoded again
-// (lsq_runtime.hip, decode_again).
+// covers; whether they were the cause is not known.  If a wait does run out no result is lost: the translation is decoded again,
+// and the model keeps to the kernels that go by agent scope alone (lsq_runtime.hip, decode_again).
 //
 // A compute unit's loads come back in the order in which they were issued, whoever issued them: one that finds its line in the
 // L2 takes 240 clocks on an idle unit, 560 / 790 / 1590 / 2640 behind 8 / 16 / 32 / 64 KB of weights.  When weights are
@@ -23,7 +23,7 @@
 //
 // Group g is workgroups g, g + 8, g + 16 ..: workgroups are dealt to the dies in turn.  die_placement() looks whether they are when
 // a model is loaded, and every workgroup looks whether it is where it was then: one that is not gives up at once, which ends as
-// any wait that runs out does (kernels_stack.hip).  The exchange itself is that of kernels_stack.hip too: data that is its own flag.
+// any wait that runs out here does.  The exchange itself is that of kernels_stack.hip too: data that is its own flag.
 #include "stack_exchange.h"
 
 namespace lsq {

@@ -310,7 +310,8 @@ size_t device_weight_bytes(const HParams& hp) {
 
 struct HostPage {
   unsigned long long step;   // (steps taken << 32) | unfinished sentences, by the last kernel of every step
-  int32_t error;             // a workgroup of the decoder stack kernel gave up waiting
+  int32_t error;             // a workgroup of a decoder stack kernel gave up waiting
+  int32_t die_error;         // ... of one with a group of rows per die: too late, or not where it was when the model was loaded
 };
 constexpr size_t kResultsMax = 32u << 20;   // bytes of results the host keeps pinned
 
@@ -512,7 +513,10 @@ bool use_small(int B) {
 
 hipError_t launch_stack(StackKind kind, StackArgs a) {
   g.stack_launches[kind] += 1;
-  if (kind == kStackDie) return launch_decoder_die(g.hp.arch, a, history(), g.stream);
+  if (kind == kStackDie) {
+    a.error = &g.page->die_error;
+    return launch_decoder_die(g.hp.arch, a, history(), g.stream);
+  }
   if (kind == kStackFew) return launch_decoder_stack(g.hp.arch, a, g.hp.d, g.stream);
   a.exchange = g.ws + g.plan.stack_rows_exchange;
   a.set_bytes = g.plan.stack_rows_set;
@@ -924,7 +928,23 @@ int enqueue_step() {
 }
 
 // after a wait for the stream or for a step: whether a workgroup of a decoder stack kernel gave up waiting for the others
-bool stack_gave_up() { return *(volatile int32_t*)&g.page->error != 0; }
+bool stack_gave_up() {
+  const volatile HostPage* page = g.page;
+  return page->error != 0 || page->die_error != 0;
+}
+
+// What the model does without from here on, with nothing in flight: its dies where a kernel that needs them gave up (the launches queued
+// behind it found its mark, whichever they were), all stack kernels where one of the others did.
+int drop_stack() {
+  if (g.page->die_error) {
+    g.stack.dies = kNoDies;
+    HIPCHK(reset_stack());
+  } else {
+    g.stack_ok = false;
+  }
+  g.page->error = g.page->die_error = 0;
+  return LSQ_OK;
+}
 
 // Waits until `steps` steps of this translation are done and returns how many sentences go on.  The step's last kernel
 // writes both into pinned memory, where they are seen several microseconds before a copy of the counter and a wait for
@@ -984,14 +1004,14 @@ int start_beams(int batch) {
 }
 
 // A wait inside a decoder stack kernel ran out: something else holds the compute units that its workgroups need (another
-// process, a kernel on another stream).  From here on this model runs the separate kernels, which need no company; the
+// process, a kernel on another stream), or a workgroup was not on its die.  From here on this model runs the kernels that are spread
+// over the chip, or, where it was one of those, the separate kernels, which need no company; the
 // translation is decoded anew from its start, since the tokens of the failed step have gone into everything after it.  What the
 // encoder (the prefill) left is only read by the decoder, and the start is still in the staging buffer.
 int decode_again() {
   HIPCHK(hipStreamSynchronize(g.stream));
   const int steps = g.t;
-  g.stack_ok = false;
-  g.page->error = 0;
+  if (int rc = drop_stack()) return rc;
   g.page->step = 0;
   if (g.hp.arch == 1) {
     Staging st{};
@@ -1006,18 +1026,21 @@ int decode_again() {
 }
 
 // A new translation takes the place of the one before, of which nothing runs any more.
-void forget_translation() {
-  if (stack_gave_up()) g.stack_ok = false;   // in a step that nobody waited for: see decode_again
-  g.page->error = 0;
+int forget_translation() {
+  if (stack_gave_up())   // in a step that nobody waited for: see decode_again
+    if (int rc = drop_stack()) return rc;
   g.page->step = 0;
+  return LSQ_OK;
 }
 
-// wait_active; if a stack kernel gave up on the way, the same for the translation decoded again
+// wait_active; if a stack kernel gave up on the way, the same for the translation decoded again (twice where a kernel on dies and
+// then one of the others gave up)
 int read_active(int steps, int* out) {
-  int rc = wait_active(steps, out);
-  if (rc || !stack_gave_up()) return rc;
-  rc = decode_again();
-  return rc ? rc : wait_active(steps, out);
+  for (;;) {
+    if (int rc = wait_active(steps, out)) return rc;
+    if (!stack_gave_up()) return LSQ_OK;
+    if (int rc = decode_again()) return rc;
+  }
 }
 
 // Decoder-only model: "encode" takes the prompts (all of one length P), runs the blocks over their
@@ -1039,7 +1062,7 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
   int32_t* h_off = h_sent + Rmax;
   int32_t* h_len = h_off + g.max_batch + 1;
   const GptStart start;
-  forget_translation();
+  if (int rc = forget_translation()) return rc;
   g.order.resize(batch);
   for (int b = 0; b < batch; ++b) {
     g.order[b] = b;
@@ -1213,7 +1236,7 @@ int lsq_init(const void* weights, size_t weights_bytes, int max_batch, int beam,
   g.pinned_ints = (size_t)3 * max_batch * max_len + 4 * (size_t)max_batch + 2 + (size_t)max_batch * (max_len + 2) + 8;
   HIPCHK(hipHostMalloc((void**)&g.pinned, g.pinned_ints * 4, hipHostMallocCoherent));
   HIPCHK(hipHostMalloc((void**)&g.page, sizeof(HostPage), hipHostMallocCoherent));
-  *g.page = HostPage{0, 0};
+  *g.page = HostPage{};
   const size_t result_bytes = (size_t)max_batch * beam * (max_len + 2) * 4;
   if (result_bytes <= kResultsMax) HIPCHK(hipHostMalloc((void**)&g.results, result_bytes, hipHostMallocCoherent));
 
@@ -1287,7 +1310,7 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
     g.anc_on = anc_on;
   }
   if (hp.arch == 1) return encode_gpt(src_ids, src_lens, batch, src_stride);
-  forget_translation();
+  if (int rc = forget_translation()) return rc;
   const Plan& p = g.plan;
   const size_t Rmax = (size_t)g.max_batch * g.max_len;
   int32_t* h_ids = g.pinned;
@@ -1587,8 +1610,10 @@ int lsq_debug_read(int what, void* host_dst, size_t bytes) {
   if (g.state < 3) return fail(LSQ_E_STATE, "lsq_encode has not been called");
   if (!host_dst) return fail(LSQ_E_ARG, "host_dst is null");
   HIPCHK(hipStreamSynchronize(g.stream));
-  if (stack_gave_up())
+  while (stack_gave_up()) {
     if (int rc = decode_again()) return rc;
+    HIPCHK(hipStreamSynchronize(g.stream));
+  }
   const Plan& p = g.plan;
   const HParams& hp = g.hp;
   const size_t M = (size_t)g.batch * g.beam, T = g.max_len, d = hp.d, R = g.rows_enc;

@@ -70,3 +70,47 @@ def test_models_without_dies_match_oracle(lsq, batch, beam, steps, expected):
         lsq.lsq_debug_forget_dies()
         assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[batch - 1])["steps"] == steps
         assert {k: n for k, n in lsq.lsq_debug_stack_launches().items() if n} == expected
+
+
+@pytest.mark.parametrize("stop", ["at once", "under way", "in the last step"])
+def test_a_wait_that_ran_out_on_a_die_takes_the_dies_only(lsq, stop):
+    """The first wait that runs out in a model of d = 512 leaves it the kernels that are spread over the chip, the second one the separate
+    kernels; each time the translation comes out as those kernels make it, whichever call notices."""
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=512, n_heads=8, d_ffn=2048, vocab=203, max_pos=96, dtype=1, cap_extra=12)
+    w = S.custom(hp, [8, 8, 8], beam=4, max_len=20, std=0.03)
+    blob = w.blob(ln_jitter=0.1)
+    want = {}
+    for kernels in ("dies", "chip", "separate"):
+        with lsq.Engine(blob, 3, 4, 20) as eng:
+            if kernels == "chip":
+                lsq.lsq_debug_forget_dies()
+            elif kernels == "separate":
+                lsq.lsq_set_attention_blocks(0)
+            want[kernels] = eng.translate(w.src_ids, w.src_lens, sync_every=64)
+            ran = {k for k, n in lsq.lsq_debug_stack_launches().items() if n}
+            assert ran == {"dies": {"die"}, "chip": {"groups_of_16_or_32"}, "separate": set()}[kernels]
+            lsq.lsq_set_attention_blocks(64)
+
+    def stopped(eng):
+        eng.encode(w.src_ids, w.src_lens)
+        if stop != "at once":
+            eng.decode_steps(2 if stop == "under way" else int(want["dies"][1].max()) - 1)
+        lsq.lsq_debug_end_stack_waits()
+        if stop == "in the last step":
+            assert eng.decode_steps(1) >= 0
+            assert np.isfinite(eng.debug(lsq.DBG.HIDDEN, (12, 512))).all()
+        lsq.lsq_decode_all(1)   # a step is queued before the count of the one before is known
+        return eng.get_beams()
+
+    with lsq.Engine(blob, 3, 4, 20) as eng:
+        assert all(np.array_equal(a, b) for a, b in zip(eng.translate(w.src_ids, w.src_lens), want["dies"]))
+        for kernels, kind in (("chip", "groups_of_16_or_32"), ("separate", None)):
+            got = stopped(eng)
+            before = lsq.lsq_debug_stack_launches()
+            again = eng.translate(w.src_ids, w.src_lens, sync_every=64)
+            after = lsq.lsq_debug_stack_launches()
+            assert {k for k in after if after[k] > before[k]} == ({kind} if kind else set())
+            assert all(np.array_equal(a, b) for a, b in zip(again, got))
+            if kernels == "chip":
+                assert all(np.array_equal(a, b) for a, b in zip(got, want["chip"]))
+        assert lsq.lsq_debug_check_canaries() == 0
