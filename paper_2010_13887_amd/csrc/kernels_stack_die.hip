@@ -169,72 +169,83 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     // Each time the exchanging wavefronts have what they looked for there is nothing to wait for in memory for a
     // while, and the next matrices are requested.
     if constexpr (!PRE) {
-    for (int l = 0; l < a.layers; ++l) {
-      const size_t next = l + 1 < a.layers ? o + a.packed_stride : o;
-      workgroup_barrier(); some(w1 + 0, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 2); some(w2 + 0, p_2, o, 0, 1); pin(); workgroup_barrier();
-      multiply(q, n3{}, k1{}, x, D + 8); workgroup_barrier();
-      workgroup_barrier(); some(q, p_c, o, 0, 2); some(q + 2, p_e, o, 0, 2); some(w1 + 4, p_1[2], o, 0, 2); pin(); workgroup_barrier();
-      workgroup_barrier();  multiply(o_at, n1{}, k1{}, y, 4 * D + 8); pin(); workgroup_barrier();
-      workgroup_barrier(); some(w1 + 6, p_1[3], o, 0, 2); some(w2 + 1, p_2, o, 1, 3); pin(); workgroup_barrier();
-      multiply(q, n1{}, k1{}, x, D + 8); workgroup_barrier();
-      workgroup_barrier(); some(w2 + 4, p_2, o, 4, 4); pin(); workgroup_barrier();
-      workgroup_barrier();  multiply(q + 2, n1{}, k1{}, y, 4 * D + 8); pin(); workgroup_barrier();
-      workgroup_barrier(); some(q + 0, p_q[0], next, 0, 2); some(q + 2, p_q[1], next, 0, 2); some(q + 4, p_q[2], next, 0, 2); pin(); workgroup_barrier();
-      multiply(w1, n4{}, k1{}, x, D + 8); workgroup_barrier();
-      workgroup_barrier(); some(o_at, p_o, next, 0, 2); multiply(w2, n1{}, k4{}, y, 4 * D + 8); pin(); workgroup_barrier();
-      o = next;
-    }
-    } else {
-    for (int l = 0; l < a.layers; ++l) {
-      const size_t next = l + 1 < a.layers ? o + a.packed_stride : o;
-      workgroup_barrier();                                                // sums of the layer before
-      some(w1, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 2);
-      if constexpr (PRE) some(w1 + 4, p_1[2], o, 0, 1);
-      pin();
-      workgroup_barrier();                                                // input rows
-      multiply(q, n3{}, k1{}, x, D + 8);
-      workgroup_barrier();
-      workgroup_barrier();                                                // q, k, v
-      if constexpr (!PRE) { some(q, p_c, o, 0, 2); some(q + 2, p_e, o, 0, 2); some(w1 + 4, p_1[2], o, 0, 2); some(w2, p_2, o, 0, 1); }
-      else { some(w1 + 5, p_1[2], o, 1, 1); some(w1 + 6, p_1[3], o, 0, 2); some(w2, p_2, o, 0, 2); }
-      pin();
-      workgroup_barrier();                                                // attention
-      workgroup_barrier();                                                // context
-      if constexpr (PRE) some(w2 + 2, p_2, o, 2, 5);
-      multiply(o_at, n1{}, k1{}, y, 4 * D + 8);
-      pin();
-      workgroup_barrier();
-      if constexpr (!PRE) {
+      for (int l = 0; l < a.layers; ++l) {
+        const size_t next = l + 1 < a.layers ? o + a.packed_stride : o;
+        workgroup_barrier();                                              // sums of the layer before
+        some(w1, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 2); some(w2, p_2, o, 0, 1);
+        pin();
+        workgroup_barrier();                                              // input rows
+        multiply(q, n3{}, k1{}, x, D + 8);
+        workgroup_barrier();
+        workgroup_barrier();                                              // q, k, v
+        some(q, p_c, o, 0, 2); some(q + 2, p_e, o, 0, 2); some(w1 + 4, p_1[2], o, 0, 2);
+        pin();
+        workgroup_barrier();                                              // attention
+        workgroup_barrier();                                              // context
+        multiply(o_at, n1{}, k1{}, y, 4 * D + 8);
+        pin();
+        workgroup_barrier();
         workgroup_barrier();                                              // sums
-        some(w1 + 6, p_1[3], o, 0, 2); some(w2 + 1, p_2, o, 1, 2);
+        some(w1 + 6, p_1[3], o, 0, 2); some(w2 + 1, p_2, o, 1, 3);
         pin();
         workgroup_barrier();                                              // rows
         multiply(q, n1{}, k1{}, x, D + 8);
         workgroup_barrier();
         workgroup_barrier();                                              // queries
-        some(w2 + 3, p_2, o, 3, 5);
+        some(w2 + 4, p_2, o, 4, 4);
         pin();
         workgroup_barrier();                                              // attention
         workgroup_barrier();                                              // context
         multiply(q + 2, n1{}, k1{}, y, 4 * D + 8);
         pin();
         workgroup_barrier();
+        workgroup_barrier();                                              // sums
+        some(q, p_q[0], next, 0, 2); some(q + 2, p_q[1], next, 0, 2); some(q + 4, p_q[2], next, 0, 2);
+        pin();
+        workgroup_barrier();                                              // rows
+        multiply(w1, n4{}, k1{}, x, D + 8);
+        workgroup_barrier();
+        workgroup_barrier();                                              // activations
+        some(o_at, p_o, next, 0, 2);
+        multiply(w2, n1{}, k4{}, y, 4 * D + 8);
+        pin();
+        workgroup_barrier();
+        o = next;
       }
-      workgroup_barrier();                                                // sums
-      if constexpr (PRE) some(w2 + 7, p_2, o, 7, 1); else some(q + 4, p_q[2], next, 0, 2);
-      some(q, p_q[0], next, 0, 2); some(q + 2, p_q[1], next, 0, 2);
-      pin();
-      workgroup_barrier();                                                // rows
-      multiply(w1, n4{}, k1{}, x, D + 8);
-      workgroup_barrier();
-      workgroup_barrier();                                                // activations
-      if constexpr (PRE) some(q + 4, p_q[2], next, 0, 2);
-      some(o_at, p_o, next, 0, 2);
-      multiply(w2, n1{}, k4{}, y, 4 * D + 8);
-      pin();
-      workgroup_barrier();
-      o = next;
-    }
+    } else {
+      for (int l = 0; l < a.layers; ++l) {
+        const size_t next = l + 1 < a.layers ? o + a.packed_stride : o;
+        workgroup_barrier();                                              // sums of the layer before
+        some(w1, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 2);
+        some(w1 + 4, p_1[2], o, 0, 1);
+        pin();
+        workgroup_barrier();                                              // input rows
+        multiply(q, n3{}, k1{}, x, D + 8);
+        workgroup_barrier();
+        workgroup_barrier();                                              // q, k, v
+        some(w1 + 5, p_1[2], o, 1, 1); some(w1 + 6, p_1[3], o, 0, 2); some(w2, p_2, o, 0, 2);
+        pin();
+        workgroup_barrier();                                              // attention
+        workgroup_barrier();                                              // context
+        some(w2 + 2, p_2, o, 2, 5);
+        multiply(o_at, n1{}, k1{}, y, 4 * D + 8);
+        pin();
+        workgroup_barrier();
+        workgroup_barrier();                                              // sums
+        some(w2 + 7, p_2, o, 7, 1);
+        some(q, p_q[0], next, 0, 2); some(q + 2, p_q[1], next, 0, 2);
+        pin();
+        workgroup_barrier();                                              // rows
+        multiply(w1, n4{}, k1{}, x, D + 8);
+        workgroup_barrier();
+        workgroup_barrier();                                              // activations
+        some(q + 4, p_q[2], next, 0, 2);
+        some(o_at, p_o, next, 0, 2);
+        multiply(w2, n1{}, k4{}, y, 4 * D + 8);
+        pin();
+        workgroup_barrier();
+        o = next;
+      }
     }
     if (tid == 0) {   // the last workgroup to get here: all have read the counters
       const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
