@@ -16,6 +16,10 @@ def lsq():
     return m
 
 
+def _ran(lsq):
+    return {k: n for k, n in lsq.lsq_debug_stack_launches().items() if n}
+
+
 @pytest.mark.parametrize("d,batch,beam", [
     (512, 1, 1), (512, 13, 1), (512, 5, 5), (512, 33, 1), (512, 13, 5), (512, 16, 8),   # groups of 4, 8, 4, 8, 16 and 16 rows, ragged but the last
 ])
@@ -28,25 +32,33 @@ def test_groups_of_rows_match_oracle(lsq, d, batch, beam):
         lockstep(lsq, eng, blob, w, max_steps=3)
         assert lsq.lsq_profile_read()["decoder_stack"][1] == 3
         lsq.lsq_profile_enable(False)
+        assert _ran(lsq) == {"die": 3}
         one, two = (eng.translate(w.src_ids, w.src_lens, sync_every=n) for n in (1, 4))
         assert all(np.array_equal(a, b) for a, b in zip(one, two))
         assert lsq.lsq_debug_check_canaries() == 0
 
 
-@pytest.mark.parametrize("d,batch,beam,steps", [
-    (512, 2, 2, 140),     # one group of 4 rows: 32, 64, 128 and 256 keys a trip; from position 129 on a group per sentence
-    (512, 30, 4, 72),     # groups of 16 rows: 64 keys a trip
+@pytest.mark.parametrize("d,batch,beam,steps,expected", [
+    (512, 2, 2, 140, {"die": 140}),     # one group of 4 rows: 32, 64, 128 and 256 keys a trip; from position 129 on a group per sentence
+    (512, 30, 4, 72, {"die": 72}),      # groups of 16 rows: 64 keys a trip
+    (512, 17, 4, 375, {"die": 366, "groups_of_16_or_32": 9}),   # beams of more than 64 rows up to position 400, less half of the source
 ])
-def test_long_histories_match_oracle(lsq, d, batch, beam, steps):
+def test_long_histories_match_oracle(lsq, d, batch, beam, steps, expected):
     w, blob = _long_workload(d, d // 64, [3 + (5 * i) % 7 for i in range(batch - 1)] + [70], beam, steps, 1)
     with lsq.Engine(blob, batch, beam, w.max_len) as eng:
         assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[batch - 1])["steps"] == steps
+        assert _ran(lsq) == expected
 
 
-@pytest.mark.parametrize("batch,prompt", [(40, 156), (100, 52)])
-def test_prompts_across_the_change_of_kernel_match_oracle(lsq, batch, prompt):
-    """Decoder-only model: past positions 160 and 56 the 8-row groups and the groups of 16 all over the chip take over."""
-    hp = S.HParams(arch=1, n_enc=0, n_dec=2, d_model=512, n_heads=8, d_ffn=2048, vocab=203, max_pos=200, act=1, norm=1, dtype=1,
+@pytest.mark.parametrize("batch,prompt,expected", [
+    (12, 296, {"die": 6, "groups_of_8": 2}),            # up to 32 rows: up to position 300, then 128 workgroups a group
+    (40, 156, {"die": 6, "groups_of_16_or_32": 2}),     # up to 64 rows: 160
+    (40, 236, {"groups_of_16_or_32": 5, "groups_of_8": 3}),   # ... and from 240 on groups of 8 rows, of 64 workgroups
+    (100, 52, {"die": 6, "groups_of_16_or_32": 2}),     # more: 56
+])
+def test_prompts_across_the_change_of_kernel_match_oracle(lsq, batch, prompt, expected):
+    """Decoder-only model: past some position the groups all over the chip take over."""
+    hp = S.HParams(arch=1, n_enc=0, n_dec=2, d_model=512, n_heads=8, d_ffn=2048, vocab=203, max_pos=320, act=1, norm=1, dtype=1,
                    sample_topk=4, cap_extra=8)
     w = S.custom(hp, [prompt] * batch, beam=1, max_len=prompt + 8, std=0.04)
     blob = w.blob(ln_jitter=0.1)
@@ -55,7 +67,7 @@ def test_prompts_across_the_change_of_kernel_match_oracle(lsq, batch, prompt):
         res = lockstep_gpt(lsq, eng, blob, w)
         launches = lsq.lsq_profile_read()["decoder_stack"][1]
         lsq.lsq_profile_enable(False)
-        assert res["steps"] == 8 and launches == 8
+        assert res["steps"] == 8 and launches == 8 and _ran(lsq) == expected
 
 
 @pytest.mark.parametrize("batch,beam,steps,expected", [
@@ -69,7 +81,7 @@ def test_models_without_dies_match_oracle(lsq, batch, beam, steps, expected):
     with lsq.Engine(blob, batch, beam, w.max_len) as eng:
         lsq.lsq_debug_forget_dies()
         assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[batch - 1])["steps"] == steps
-        assert {k: n for k, n in lsq.lsq_debug_stack_launches().items() if n} == expected
+        assert _ran(lsq) == expected
 
 
 @pytest.mark.parametrize("stop", ["at once", "under way", "in the last step"])
@@ -87,8 +99,7 @@ def test_a_wait_that_ran_out_on_a_die_takes_the_dies_only(lsq, stop):
             elif kernels == "separate":
                 lsq.lsq_set_attention_blocks(0)
             want[kernels] = eng.translate(w.src_ids, w.src_lens, sync_every=64)
-            ran = {k for k, n in lsq.lsq_debug_stack_launches().items() if n}
-            assert ran == {"dies": {"die"}, "chip": {"groups_of_16_or_32"}, "separate": set()}[kernels]
+            assert set(_ran(lsq)) == {"dies": {"die"}, "chip": {"groups_of_16_or_32"}, "separate": set()}[kernels]
             lsq.lsq_set_attention_blocks(64)
 
     def stopped(eng):

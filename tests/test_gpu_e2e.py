@@ -412,13 +412,15 @@ def test_small_model_step_matches_oracle(lsq, d, heads, ffn, vocab, beam, dtype)
         assert lsq.lsq_debug_check_canaries() == 0
 
 
-# groups of 8 rows, of more, float32, sampling, decoder-only
-@pytest.mark.parametrize("d,batch,beam,dtype,kind", [(512, 2, 4, 1, ""), (512, 12, 4, 1, ""), (512, 3, 4, 0, ""),
-                                                     (512, 5, 1, 1, "sampling"), (256, 4, 1, 1, "decoder-only")])
-def test_translation_survives_a_wait_that_ran_out(lsq, d, batch, beam, dtype, kind):
+@pytest.mark.parametrize("d,batch,beam,dtype,kind,kernel", [
+    (512, 2, 4, 1, "", "die"), (512, 12, 4, 1, "", "die"), (512, 5, 1, 1, "sampling", "die"),
+    (256, 2, 4, 1, "", "groups_of_8"), (1024, 3, 4, 1, "", "groups_of_16_or_32"), (512, 3, 4, 0, "", "float32"),
+    (256, 4, 1, 1, "decoder-only", "groups_of_8")])
+def test_translation_survives_a_wait_that_ran_out(lsq, d, batch, beam, dtype, kind, kernel):
     """Where a wait inside a stack kernel has run out, the steps that are already queued behind it do not wait as well (64 of
-    them would take half a second each), and the translation is decoded again with the separate kernels, which the model
-    then keeps: the same tokens as before up to rounding, and from then on the same bits."""
+    them would take half a second each), and the translation is decoded again with the kernels that need less company (on dies: those
+    that are spread over the chip; otherwise the separate ones), which the model then keeps: the same tokens as before up to rounding,
+    and from then on the same bits."""
     import time
     gpt = kind == "decoder-only"
     hp = S.HParams(n_enc=0 if gpt else 1, n_dec=2, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=203, max_pos=96, dtype=dtype,
@@ -428,6 +430,7 @@ def test_translation_survives_a_wait_that_ran_out(lsq, d, batch, beam, dtype, ki
     lock = (lockstep_gpt if gpt else lockstep_sample) if kind else lockstep
     with lsq.Engine(blob, batch, beam, 80) as eng:
         want = eng.translate(w.src_ids, w.src_lens, sync_every=64)
+        assert {k for k, n in lsq.lsq_debug_stack_launches().items() if n} == {kernel}
         eng.encode(w.src_ids, w.src_lens)
         assert eng.decode_steps(7) > 0
         lsq.lsq_debug_end_stack_waits()
@@ -436,7 +439,10 @@ def test_translation_survives_a_wait_that_ran_out(lsq, d, batch, beam, dtype, ki
             pass
         assert time.perf_counter() - t0 < 2.0
         got = eng.get_beams()
+        before = lsq.lsq_debug_stack_launches()
         again = eng.translate(w.src_ids, w.src_lens)
+        after = lsq.lsq_debug_stack_launches()
+        assert (after != before) == (kernel == "die") and after[kernel] == before[kernel]
         assert all(np.array_equal(a, b) for a, b in zip(got, again))
         same = (got[0] == want[0]).all(axis=-1)
         assert same.mean() >= (0.3 if dtype else 0.9)        # 64 steps of a nearly flat distribution in float16
@@ -505,19 +511,20 @@ def _long_workload(d, heads, lens, beam, steps, dtype, n_dec=2, ffn=None, vocab=
     return w, w.blob(ln_jitter=0.1, overrides={"E": E, f"dec{n_dec - 1}.ln3_b": np.ones(d)})
 
 
-@pytest.mark.parametrize("d,batch,beam,dtype,steps", [
-    (256, 1, 2, 1, 270),     # groups of 8 rows: 256 keys a trip
-    (512, 10, 4, 1, 140),    # ... 128 keys a trip, from position 112 on; groups of 16 rows before
-    (768, 12, 4, 1, 72),     # groups of 16 rows: 64 keys a trip
-    (512, 40, 4, 1, 72),     # groups of 32 rows: 32 keys a trip
-    (512, 2, 1, 0, 72), (512, 16, 4, 0, 72), (256, 33, 4, 0, 72), (512, 40, 4, 0, 72),   # float32: 64, 32, 16 and 8 keys a trip
+@pytest.mark.parametrize("d,batch,beam,dtype,steps,kernel", [
+    (256, 1, 2, 1, 270, "groups_of_8"),           # 256 keys a trip
+    (512, 10, 4, 1, 140, "die"),                  # groups of 8 rows on dies; the other kernels at these sizes: tests/test_gpu_die.py
+    (768, 12, 4, 1, 72, "groups_of_16_or_32"),    # of 16: 64 keys a trip
+    (512, 40, 4, 1, 72, "groups_of_16_or_32"),    # of 32: 32 keys a trip
+    (512, 2, 1, 0, 72, "float32"), (512, 16, 4, 0, 72, "float32"), (256, 33, 4, 0, 72, "float32"), (512, 40, 4, 0, 72, "float32"),   # 64, 32, 16 and 8 keys a trip
 ])
-def test_decoder_stack_past_its_first_trip_for_keys(lsq, d, batch, beam, dtype, steps):
+def test_decoder_stack_past_its_first_trip_for_keys(lsq, d, batch, beam, dtype, steps, kernel):
     """One sentence of the batch in lock-step with the oracle until the histories (and the slab table) have been read in
     several trips, beside a source of 70 tokens."""
     w, blob = _long_workload(d, d // 64, [3 + (5 * i) % 7 for i in range(batch - 1)] + [70], beam, steps, dtype)
     with lsq.Engine(blob, batch, beam, w.max_len) as eng:
         assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[batch - 1])["steps"] == steps
+        assert lsq.lsq_debug_stack_launches()[kernel] == steps
 
 
 def test_long_histories_leave_the_stack_kernel(lsq):

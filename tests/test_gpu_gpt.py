@@ -187,13 +187,13 @@ def test_row_without_candidates_reads_a_row_of_the_embedding(lsq, d, batch, fusi
     np.testing.assert_allclose(K, np.broadcast_to(want, K.shape), rtol=0, atol=2e-3 * np.abs(want).max())
 
 
-@pytest.mark.parametrize("d,batch,prompt", [
-    (768, 2, 270),    # groups of 8 rows: 256 keys a trip
-    (512, 12, 236),   # groups of 16 rows (64 keys), of 8 from position 240 on
-    (768, 41, 72),    # groups of 16 rows
-    (768, 90, 40),    # groups of 32 rows: 32 keys a trip
+@pytest.mark.parametrize("d,batch,prompt,kernel", [
+    (768, 2, 270, "groups_of_8"),           # 256 keys a trip
+    (512, 12, 236, "die"),                  # groups of 8 rows on dies: 64 keys a trip
+    (768, 41, 72, "groups_of_16_or_32"),    # of 16: 64 keys a trip
+    (768, 90, 40, "groups_of_16_or_32"),    # of 32: 32 keys a trip
 ])
-def test_decoder_stack_past_its_first_trip_for_keys(lsq, d, batch, prompt):
+def test_decoder_stack_past_its_first_trip_for_keys(lsq, d, batch, prompt, kernel):
     """All blocks of a step in one launch, behind prompts so long that the history takes several trips."""
     hp = S.HParams(arch=1, n_enc=0, n_dec=2, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=203, max_pos=300, act=1, norm=1,
                    dtype=1, sample_topk=4, cap_extra=8)
@@ -204,4 +204,4 @@ def test_decoder_stack_past_its_first_trip_for_keys(lsq, d, batch, prompt):
         res = lockstep_gpt(lsq, eng, blob, w)
         launches = lsq.lsq_profile_read()["decoder_stack"][1]
         lsq.lsq_profile_enable(False)
-        assert res["steps"] == 8 and launches == 8
+        assert res["steps"] == 8 and launches == 8 and lsq.lsq_debug_stack_launches()[kernel] == 8
