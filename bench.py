@@ -37,6 +37,7 @@ blocks over the cache, logits, top-k, Philox draw); value = sampled tokens / ela
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import os
 import re
@@ -223,7 +224,10 @@ def main() -> int:
                min_ms_per_step=dts[0] / K * 1e3, max_ms_per_step=dts[-1] / K * 1e3)
 
     # ---- the curve over t: the same translation in chunks of 8 steps with a wait after each chunk
-    # (the waits make these figures slightly higher than the back-to-back ones above)
+    # (the waits make these figures slightly higher than the back-to-back ones above).  Python's collector waits: one of its full
+    # passes over torch's objects takes 39 ms, which stood in the curve as eight steps of 5 ms, always at the same place
+    gc.collect()
+    gc.disable()
     eng.encode(w.src_ids, w.src_lens)
     torch.cuda.synchronize()
     curve, t_at = [], 0
@@ -237,6 +241,7 @@ def main() -> int:
         t_at += n_done
         if a == 0 or n_done == 0:
             break
+    gc.enable()
     per_step = sorted(c["ms_per_step"] for c in curve)
     step_curve = dict(p50_ms=per_step[len(per_step) // 2], min_ms=per_step[0], max_ms=per_step[-1],
                       chunks=[[c["t"], round(c["ms_per_step"], 4)] for c in curve])
