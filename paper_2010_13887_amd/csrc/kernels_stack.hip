@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
           half8_t g8[NV], b8[NV];
           load_gain(g8, b8, a.ln1g, a.ln1b);
           const half_t* e = a.E + (size_t)embedding_row(a.tokens[(size_t)r * (a.T + 1) + a.len[r]]) * D;
-          embed_row<half_t>(e, a.pe + (size_t)pos * D, us[wave], D, 1.0f, lane, 64);
+          embed_whole_row<half_t, D>(e, a.pe + (size_t)pos * D, us[wave], 1.0f, lane);
           normalise(g8, b8, nullptr, nullptr);   // reads what this wavefront wrote
         } else {
 #pragma unroll

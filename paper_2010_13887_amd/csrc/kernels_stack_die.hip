@@ -560,7 +560,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
           pieces(a.ln1g, g8);
           pieces(a.ln1b, b8);
           const half_t* e = a.E + (size_t)embedding_row(a.tokens[(size_t)r * (a.T + 1) + a.len[r]]) * D;
-          embed_row<half_t>(e, a.pe + (size_t)pos * D, us[m], D, 1.0f, lane, 64);   // the lane's own pieces
+          embed_whole_row<half_t, D>(e, a.pe + (size_t)pos * D, us[m], 1.0f, lane);   // the lane's own pieces
           pieces(us[m], o);
 #pragma unroll
           for (int q = 0; q < NP; ++q)

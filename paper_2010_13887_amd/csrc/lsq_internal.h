@@ -509,8 +509,12 @@ __device__ __forceinline__ int embedding_row(int token) { return max(token, 0); 
 // Two float16 of a word: one multiply-add, rounded once, to float16.
 __device__ __forceinline__ unsigned scaled_sum(unsigned x, float scale, float p0, float p1) {
   unsigned y;   // written by halves: a wait state before each reader, which the compiler cannot add in here
-  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]\n\ts_nop 1\n\t"
-      "v_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\ts_nop 1" : "=&v"(y) : "v"(x), "v"(scale), "v"(p0), "v"(p1));
+  if (__builtin_constant_p(scale) && scale == 1.0f)
+    asm("v_fma_mixlo_f16 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]\n\ts_nop 1\n\t"
+        "v_fma_mixhi_f16 %0, %1, 1.0, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\ts_nop 1" : "=&v"(y) : "v"(x), "v"(p0), "v"(p1));
+  else
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]\n\ts_nop 1\n\t"
+        "v_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\ts_nop 1" : "=&v"(y) : "v"(x), "s"(scale), "v"(p0), "v"(p1));
   return y;
 }
 __device__ __forceinline__ half_t scaled_sum(half_t x, float scale, float p) {
@@ -551,6 +555,25 @@ __device__ __forceinline__ void embed_row(const T* __restrict__ e, const float* 
     }
   } else {
     for (int c = lane; c < d; c += nl) x[c] = scaled_sum(e[c], scale, pe[c]);
+  }
+}
+
+// The same by one wavefront for a row width that the compiler knows: all of the row is requested before any of it is made.
+template <typename T, int D>
+__device__ __forceinline__ void embed_whole_row(const T* __restrict__ e, const float* __restrict__ pe, T* __restrict__ x, float scale, int lane) {
+  constexpr int N = (D + 511) / 512;
+  typename Vec8<T>::raw_t raw[N];
+  float p[N][8];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const int c = min((q * 64 + lane) * 8, D - 8);
+    raw[q] = Vec8<T>::load_raw(e + c);
+    Vec8<float>::load(pe + c, p[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const typename Vec8<T>::raw_t row = scaled_sums(raw[q], scale, p[q]);
+    if ((q * 64 + lane) * 8 < D) *reinterpret_cast<typename Vec8<T>::raw_t*>(x + (q * 64 + lane) * 8) = row;
   }
 }
 

@@ -31,7 +31,7 @@ ROWS = """
 using namespace lsq;
 extern "C" __global__ void first_f16(const half_t* e, const float* pe, half_t* x, int d, float s) { embed_row<half_t>(e, pe, x, d, s, threadIdx.x, 64); }
 extern "C" __global__ void first_f32(const float* e, const float* pe, float* x, int d, float s) { embed_row<float>(e, pe, x, d, s, threadIdx.x, 64); }
-extern "C" __global__ void unscaled_f16(const half_t* e, const float* pe, half_t* x) { embed_row<half_t>(e, pe, x, 512, 1.0f, threadIdx.x, 64); }
+extern "C" __global__ void unscaled_f16(const half_t* e, const float* pe, half_t* x) { embed_whole_row<half_t, 768>(e, pe, x, 1.0f, threadIdx.x); }
 extern "C" __global__ void next_f16(NextInput nx, const int* tok, int k, int pos) { next_input_rows<half_t>(nx, tok, 0, k, pos, threadIdx.x); }
 extern "C" __global__ void next_f32(NextInput nx, const int* tok, int k, int pos) { next_input_rows<float>(nx, tok, 0, k, pos, threadIdx.x); }
 """
