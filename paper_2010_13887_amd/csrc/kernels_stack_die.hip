@@ -80,9 +80,11 @@ __device__ __forceinline__ int own_column(int lane) { return (lane & 7) * 8 + (l
 // Few rows, d = 512: up to 16 a die.  Eight wavefronts hold the matrices in registers (an eighth of k each), ask for the next
 // ones and multiply; the other eight look for the exchanged values, normalise, attend, add the eight partial sums up and
 // publish.  Nobody waits for a value behind weights of its own this way, and 128 registers are enough for either.
-// Measured, layers of one step in us (before: groups of 8 rows or of 16 all over the chip): 4 rows 91 -> 77, 32 rows 109 -> 90,
-// 64 rows 117 -> 99, 128 rows 137 -> 123.  Bound by the chain of eight exchanges and products a layer (10 us without
-// weights) and by the weights behind which the exchanges queue (6 us of a layer's 12.5 on a single die, 8 on eight).
+// Measured, layers of one step in us at positions up to 60, sources of 30 (groups of 8 or 16 rows all over the chip): 4 rows 77 (94),
+// 8 rows 78 (100), 32 rows 94 (106), 64 rows 101 (113), 128 rows 118 (130).  With every matrix requested once a launch instead of once a layer
+// (the same chain on wrong numbers): 72, 72, 74, 87, 111; pre-LN, 12 layers, 16 rows 125 -> 112, 64 rows 149 -> 112.  So it is bound by the chain
+// of eight exchanges and products, 12 us of a layer's 13 on one die or two; where eight dies read weights at once, what exchanges queue behind
+// them comes to 1 to 3 us a layer more.
 template <int R, bool PRE>
 __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArgs a) {
   constexpr int DK = 2, D = 256 * DK, H = D / 64, W = kDieGroup, NT = D / W;
@@ -645,12 +647,15 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   ex.report(a.state, a.error);
 }
 
-
 }  // namespace
 
-// How M rows are dealt out.  Short histories, whole translations of 75 steps in ms, groups of 4 / 8 rows: 12 rows 7.44 / 7.69,
-// 16 rows 8.19 / 7.97, 24 rows 8.35 / 8.08, 32 rows 8.73 / 8.92 (fewer dies share the memory-side cache's rate, more have shorter
-// chains).  Long ones: over as many dies as there are sentences for, since a die reads its rows' histories at its own rate
+// How M rows are dealt out.  Short histories, whole translations of 75 steps in ms, groups of 4 / 8 rows, each in a process of its own (two boxes
+// within 0.5 %; beam 1 and 4 or 5): 12 rows 7.36 / 7.58, 13 rows 7.85 / 7.67, 16 rows 8.2 / 7.9, 20 rows 8.3 / 7.95, 24 rows 8.35 / 8.2, 25 rows 8.36 /
+// 8.45 and 8.53 / 8.55, 28 rows 8.4 / 8.85, 30 rows 8.49 / 8.69 and 8.63 / 8.84, 32 rows 8.6 / 9.0: a fourth die that reads weights costs
+// more than the longer chain of 8 rows; groups of 4 need it from 13 rows on, groups of 8 from 25 on, where the shorter chain is ahead again.
+// (Where the weights lie in memory weighs as much: behind a dozen models in one process groups of 8 took 7.9 to 8.9 ms at 25 to
+// 32 rows, those of 4 8.4 to 8.7.)  More than 32 rows are more than eight groups of 4.
+// Long ones: over as many dies as there are sentences for, since a die reads its rows' histories at its own rate
 // (one row per sentence, us a step at positions 240 / 1008: 16 pre-LN rows on two dies 201 / 361, on eight 170 / 256; 4 rows of a post-LN model
 // on one 100 / 139, on four 97 / 124).
 struct DieChoice { int R, rows, groups; };
