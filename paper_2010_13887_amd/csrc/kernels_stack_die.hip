@@ -649,7 +649,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
 
 }  // namespace
 
-// How M rows are dealt out.  Short histories, whole translations of 75 steps in ms, groups of 4 / 8 rows, each in a process of its own (two boxes
+// How M rows are dealt out.  Short histories, whole translations of 75 steps in ms, groups of 4 / 8 rows, each in a process of its own (two machines
 // within 0.5 %; beam 1 and 4 or 5): 12 rows 7.36 / 7.58, 13 rows 7.85 / 7.67, 16 rows 8.2 / 7.9, 20 rows 8.3 / 7.95, 24 rows 8.35 / 8.2, 25 rows 8.36 /
 // 8.45 and 8.53 / 8.55, 28 rows 8.4 / 8.85, 30 rows 8.49 / 8.69 and 8.63 / 8.84, 32 rows 8.6 / 9.0: a fourth die that reads weights costs
 // more than the longer chain of 8 rows; groups of 4 need it from 13 rows on, groups of 8 from 25 on, where the shorter chain is ahead again.
