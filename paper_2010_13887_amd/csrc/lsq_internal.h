@@ -507,6 +507,7 @@ __device__ __forceinline__ int embedding_row(int token) { return max(token, 0); 
 // leave for the next step and those that the stack kernels make for themselves have to be the same bits, and left to itself the compiler
 // fuses, rounds once or rounds twice as it finds convenient in each place (and with -ffp-contract differently again).
 // Two float16 of a word: one multiply-add, rounded once, to float16.
+// A factor of one is part of the instruction: kept in a register it was there for a whole stack kernel (d = 768 pre-LN, 1 row 128.7 -> 129.4 us).
 __device__ __forceinline__ unsigned scaled_sum(unsigned x, float scale, float p0, float p1) {
   unsigned y;   // written by halves: a wait state before each reader, which the compiler cannot add in here
   if (__builtin_constant_p(scale) && scale == 1.0f)
