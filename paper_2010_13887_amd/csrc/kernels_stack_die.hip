@@ -21,9 +21,11 @@
 // L2 takes 240 clocks on an idle unit, 560 / 790 / 1590 / 2640 behind 8 / 16 / 32 / 64 KB of weights.  When weights are
 // requested therefore decides how long an exchange takes: each time a wait has ended and there is something to compute.
 //
-// Group g is workgroups g, g + 8, g + 16 ..: workgroups are dealt to the dies in turn.  die_placement() looks whether they are when
-// a model is loaded, and every workgroup looks whether it is where it was then: one that is not gives up at once, which ends as
-// any wait that runs out here does.  The exchange itself is that of kernels_stack.hip too: data that is its own flag.
+// Workgroups are dealt to the dies in turn, eight after one another to eight different ones, but which die is first is another one
+// for another stream, and changes for a stream when the process opens others (seen: 0 1 2 .. 7, then 7 0 1 .., then 5 6 7 ..).  So a group is
+// the die it finds itself on, and workgroup b's place in it is b / 8.  die_placement() looks whether eight in a row are on different dies when a
+// model is loaded.  A launch in which they were not would lack a workgroup of some group, and end as any wait that runs out here does.
+// The exchange itself is that of kernels_stack.hip too: data that is its own flag.
 #include "stack_exchange.h"
 
 namespace lsq {
@@ -108,15 +110,28 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int G = a.groups, grp = blockIdx.x & (kDies - 1);
+  const int G = a.groups, grp = die_id();
   int j = blockIdx.x >> 3;
-  if (grp >= G) return;
+  const int seq = a.state[0], parity = seq & 1;
+  // the last workgroup of the launch to get here: all have read the counters
+  auto leave = [&] {
+    const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n == kDies * W - 1) {
+      a.state[4] = 0;
+      a.state[1 + parity] = G * R;
+      __hip_atomic_fetch_xor(a.state, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  };
+  if (grp >= G) {
+    if (tid == 0) leave();
+    return;
+  }
   const int r0 = grp * a.rows_per_group, rows = min(a.rows_per_group, a.M - r0);
-  const int seq = a.state[0], parity = seq & 1, dirty = a.state[2 - parity], pos = *a.tpos;
+  const int dirty = a.state[2 - parity], pos = *a.tpos;
 
   Exchange<kWorkgroup> ex;   // stores that end in the die's L2, where the readers' agent-scope loads look
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
-  ex.polls = seq < 0 || die_id() != (a.dies >> (4 * grp) & 15) ? 1 : kSpinLimit;
+  ex.polls = seq < 0 ? 1 : kSpinLimit;
   const int layer_bytes = Rg::size * D * R;
   auto at = [&](int l, int region) { return grp * a.layers * layer_bytes + l * layer_bytes + region * D * R; };
 
@@ -249,14 +264,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
         o = next;
       }
     }
-    if (tid == 0) {   // the last workgroup to get here: all have read the counters
-      const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (n == G * W - 1) {
-        a.state[4] = 0;
-        a.state[1 + parity] = G * R;
-        __hip_atomic_fetch_xor(a.state, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
+    if (tid == 0) leave();
     return;
   }
 
@@ -710,16 +718,18 @@ hipError_t launch_decoder_die(int arch, const StackArgs& args, int pos, hipStrea
   return hipLaunchKernel(die_kernel_of(c.R, arch == 1), dim3(kDies * kDieGroup), dim3(kDieThreads), kargs, 0, s);
 }
 
-hipError_t die_placement(unsigned* scratch, uint32_t* dies, hipStream_t s) {
+hipError_t die_placement(unsigned* scratch, bool* dies, hipStream_t s) {
   unsigned id[kDies * kDieGroup] = {};
   die_of_workgroup_kernel<<<kDies * kDieGroup, kDieThreads, 0, s>>>(scratch);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(id, scratch, sizeof(id), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  *dies = 0;
-  for (int b = 0; b < kDies; ++b) *dies |= (id[b] & 15) << (4 * b);
-  for (int b = 0; b < kDies * kDieGroup; ++b)
-    if (id[b] != id[b % kDies]) *dies = kNoDies;
+  *dies = e == hipSuccess;
+  for (int b = 0; b < kDies * kDieGroup; b += kDies) {
+    unsigned found = 0;
+    for (int i = 0; i < kDies; ++i) found |= 1u << (id[b + i] & 15);
+    if (found != (1u << kDies) - 1) *dies = false;
+  }
   return e;
 }
 

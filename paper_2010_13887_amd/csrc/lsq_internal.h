@@ -184,7 +184,6 @@ struct StackArgs {
   int* error;               // pinned host memory: set when a wait ran out
   int M, beam, layers, T, anc_ld;
   float eps;
-  uint32_t dies;            // see die_placement
   int groups, rows_per_group;   // filled in by the launcher
 };
 size_t stack_exchange_bytes(int arch, int M, int d, int layers);   // of one set
@@ -203,9 +202,8 @@ hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStrea
 bool die_supported(int arch, int M, int d, int beam, int pos, int src);   // ... and ahead at this history and these sources
 size_t die_exchange_bytes(int arch, int M, int d, int layers);   // of one set; 0: no such kernel for this width
 hipError_t launch_decoder_die(int arch, const StackArgs& args, int pos, hipStream_t s);
-constexpr uint32_t kNoDies = 0xFFFFFFFFu;
-// which die workgroups b, b + 8, b + 16 .. of a launch run on, 4 bits each; kNoDies: not the same one.  scratch: 1 KB.  Waits for the stream.
-hipError_t die_placement(unsigned* scratch, uint32_t* dies, hipStream_t s);
+// Whether the workgroups of a launch are dealt to the dies in turn.  scratch: 1 KB.  Waits for the stream.
+hipError_t die_placement(unsigned* scratch, bool* dies, hipStream_t s);
 size_t stack_rows_bytes(int arch, int M, int d);   // of one set; 0: no such kernel for this width
 hipError_t launch_decoder_stack_rows(int arch, const StackArgs& args, int d, hipStream_t s);
 // float32 (kernels_stack_f32.hip): the matrices are copies made by launch_pack_f32 (16-column units, columns up to a multiple of 64, K of 4), vectors, cache and rows float32

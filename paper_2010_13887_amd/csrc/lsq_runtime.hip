@@ -343,6 +343,7 @@ struct Ctx {
   std::vector<int> alive_at;   // alive_at[t] = sentences whose cap exceeds t: the prefix step t works on
   char* E = nullptr;
   bool stack_ok = false;        // the decoder stack kernel takes this model
+  bool dies = false;            // its workgroups are dealt to the dies in turn, and no kernel that needs that has given up
   StackArgs stack{};            // ... with these arguments (all but those of a translation)
   int64_t stack_launches[kStackF32 + 1] = {};   // of this model, by StackKind
   bool small_ok = false;        // a beam search step of this model can be one launch
@@ -477,8 +478,8 @@ int setup_stack() {
   a.layers = L; a.T = g.max_len; a.anc_ld = g.max_len + 1; a.eps = hp.eps;
   a.beam = g.beam;
   g.stack_ok = stack && stream_has_every_cu(g.stream);
-  a.dies = kNoDies;
-  if (g.stack_ok && p.stack_set && die_exchange_bytes(hp.arch, g.max_batch * g.beam, d, L)) HIPCHK(die_placement(reinterpret_cast<unsigned*>(g.ws + p.d_tmp), &a.dies, g.stream));
+  g.dies = false;
+  if (g.stack_ok && p.stack_set && die_exchange_bytes(hp.arch, g.max_batch * g.beam, d, L)) HIPCHK(die_placement(reinterpret_cast<unsigned*>(g.ws + p.d_tmp), &g.dies, g.stream));
   if (small) {
     char* E = g.ws + p.wpacked + L * layer_bytes_f32(hp);
     if (hp.dtype == DT_F32) HIPCHK(launch_pack_f32(g.E, E, hp.V, d, g.stream));
@@ -500,7 +501,7 @@ StackKind use_stack(int M) {
   if (!g.stack_ok || !g.fuse_ln || (M > g.block_rows && g.block_rows < (int)kBlockRowsMax)) return kStackNone;
   const int pos = history(), src = g.hp.arch == 1 ? 0 : g.src_longest;
   if (g.hp.dtype == DT_F32) return stack_f32_supported(M, g.hp.d, g.beam, pos, src) ? kStackF32 : kStackNone;
-  return stack_kind(g.hp.arch, M, g.hp.d, g.beam, pos, src, g.stack.dies != kNoDies);
+  return stack_kind(g.hp.arch, M, g.hp.d, g.beam, pos, src, g.dies);
 }
 
 // plain beam search with a small model: the whole step in one launch.  Up to as many sentences as the chip runs at once:
@@ -937,7 +938,7 @@ bool stack_gave_up() {
 // behind it found its mark, whichever they were), all stack kernels where one of the others did.
 int drop_stack() {
   if (g.page->die_error) {
-    g.stack.dies = kNoDies;
+    g.dies = false;
     HIPCHK(reset_stack());
   } else {
     g.stack_ok = false;
@@ -1555,7 +1556,7 @@ int lsq_debug_stack_launches(int64_t* counts) {
 
 int lsq_debug_forget_dies(void) {
   if (g.state < 2) return fail(LSQ_E_STATE, "lsq_init has not been called");
-  g.stack.dies = kNoDies;
+  g.dies = false;
   return LSQ_OK;
 }
 

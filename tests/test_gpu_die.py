@@ -2,6 +2,7 @@
 share a pair's keys, and of the lengths at which rows are dealt out differently."""
 import numpy as np
 import pytest
+import torch
 
 import lsq_synth as S
 from tests.parity import lockstep, lockstep_gpt
@@ -82,6 +83,24 @@ def test_models_without_dies_match_oracle(lsq, batch, beam, steps, expected):
         lsq.lsq_debug_forget_dies()
         assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[batch - 1])["steps"] == steps
         assert _ran(lsq) == expected
+
+
+def test_other_streams_do_not_move_a_model_off_its_dies(lsq):
+    """Which die the first workgroup of a launch is on changes for a stream when the process opens others: the groups go by the die they
+    find themselves on, whatever the model's workgroups were on when it was loaded."""
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=512, n_heads=8, d_ffn=2048, vocab=203, max_pos=32, dtype=1, cap_extra=6)
+    w = S.custom(hp, [5, 7, 3, 6, 4], beam=4, max_len=14, std=0.03)
+    with lsq.Engine(w.blob(ln_jitter=0.1), 5, 4, 14) as eng:
+        want = eng.translate(w.src_ids, w.src_lens)
+        torch.zeros(1 << 16, device="cuda").sum().item()
+        streams = []
+        for _ in range(4):
+            streams.append(torch.cuda.Stream())
+            with torch.cuda.stream(streams[-1]):
+                torch.ones(1000, device="cuda").mul_(2)
+            streams[-1].synchronize()
+            assert all(np.array_equal(a, b) for a, b in zip(eng.translate(w.src_ids, w.src_lens), want))
+        assert set(_ran(lsq)) == {"die"}
 
 
 @pytest.mark.parametrize("stop", ["at once", "under way", "in the last step"])
