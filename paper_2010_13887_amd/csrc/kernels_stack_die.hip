@@ -82,11 +82,11 @@ __device__ __forceinline__ int own_column(int lane) { return (lane & 7) * 8 + (l
 // Few rows, d = 512: up to 16 a die.  Eight wavefronts hold the matrices in registers (an eighth of k each), ask for the next
 // ones and multiply; the other eight look for the exchanged values, normalise, attend, add the eight partial sums up and
 // publish.  Nobody waits for a value behind weights of its own this way, and 128 registers are enough for either.
-// Measured, layers of one step in us at positions up to 60, sources of 30 (groups of 8 or 16 rows all over the chip): 4 rows 77 (94),
-// 8 rows 78 (100), 32 rows 94 (106), 64 rows 101 (113), 128 rows 118 (130).  With every matrix requested once a launch instead of once a layer
-// (the same chain on wrong numbers): 72, 72, 74, 87, 111; pre-LN, 12 layers, 16 rows 125 -> 112, 64 rows 149 -> 112.  So it is bound by the chain
-// of eight exchanges and products, 12 us of a layer's 13 on one die or two; where eight dies read weights at once, what exchanges queue behind
-// them comes to 1 to 3 us a layer more.
+// Measured, layers of one step in us at positions up to 60, sources of 30 (groups of 8 or 16 rows all over the chip): 4 rows 70 (94),
+// 8 rows 70 (100), 32 rows 84 (106), 64 rows 91 (113), 128 rows 108 (130).  Every layer is a chain of eight exchanges and products,
+// 9 us of its 11 on one die or two; the rest is what exchanges queue behind weights (with all of them in the L2, on wrong numbers: 59, 59, 59, 70,
+// 93).  The chain is made of instructions that wait for one another: what a wavefront does on it has no branches, asks LDS for all it
+// needs at once, and what can be done while somebody else works is done then: 77, 78, 94, 101, 118 before.
 template <int R, bool PRE>
 __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArgs a) {
   constexpr int DK = 2, D = 256 * DK, H = D / 64, W = kDieGroup, NT = D / W;
@@ -105,6 +105,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   __shared__ __attribute__((aligned(16))) float part[kWaves][4][R][16];
   __shared__ __attribute__((aligned(16))) float att_o[kWaves][64];
   __shared__ float att_m[kWaves], att_l[kWaves];
+  __shared__ int arrived[kWaves], attended[kWaves];   // exchanges that a wavefront has seen the end of, attentions it has left its share of
   __shared__ unsigned first_key[kWaves][U][64];
   __shared__ __attribute__((aligned(16))) half_t vec[2][7][D];   // of a layer: gains and shifts, biases
 
@@ -133,7 +134,9 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
   ex.polls = seq < 0 ? 1 : kSpinLimit;
   const int layer_bytes = Rg::size * D * R;
-  auto at = [&](int l, int region) { return grp * a.layers * layer_bytes + l * layer_bytes + region * D * R; };
+  auto at = [&](int l, int region) { return __builtin_amdgcn_readfirstlane(grp * a.layers * layer_bytes + l * layer_bytes + region * D * R); };
+  if (tid < kWaves) { arrived[tid] = 0; attended[tid] = 0; }
+  workgroup_barrier();
 
   if (wave < kWaves) {
     // ================ products: wavefront w has an eighth of k; matrices wait in registers
@@ -179,89 +182,98 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     half8_t* const o_at = PRE ? wo : w1 + 6;
     size_t o = 0;   // of the layer
     for (int i = 0; i < 3; ++i) some(q + 2 * i, p_q[i], 0, 0, 2);
-    some(o_at, p_o, 0, 0, 2);
+    if constexpr (PRE) some(o_at, p_o, 0, 0, 2);
     pin();
     const half_t* const x = &xs[0][0];
     const half_t* const y = &st[0][0];
     // Each time the exchanging wavefronts have what they looked for there is nothing to wait for in memory for a
     // while, and the next matrices are requested.
-    if constexpr (!PRE) {
-      for (int l = 0; l < a.layers; ++l) {
-        const size_t next = l + 1 < a.layers ? o + a.packed_stride : o;
-        workgroup_barrier();                                              // sums of the layer before
-        some(w1, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 2); some(w2, p_2, o, 0, 1);
+    int exchanges = 0;
+    auto values_here = [&] {
+      for (++exchanges; !__all(__hip_atomic_load(&arrived[lane & (kWaves - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= exchanges);) __builtin_amdgcn_s_sleep(1);
+      pin();
+    };
+    for (int l = 0; l < a.layers; ++l, o += a.packed_stride) {
+      // Past the last layer: pieces that are in the L2 already, instead of 64 KB that nobody wants and the last exchange would queue
+      // behind.  (A branch around the requests would cost more: the compiler no longer knows how many are in flight.)
+      const bool more = l + 1 < a.layers;
+      const size_t next = more ? o + a.packed_stride : o;
+      const char* const n_q[3] = {more ? p_q[0] : p_2, more ? p_q[1] : p_2, more ? p_q[2] : p_2};
+      if constexpr (!PRE) {
+        // How many pieces go where: a compute unit takes in one (8 KB of its 224 of a layer) in 460 clocks where one die reads, 670 where all do, the
+        // first after 1200, and what it looks for meanwhile arrives behind them.
+        values_here();                                                    // sums of the layer before
+        some(o_at, p_o, o, 0, 2); some(w1, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 1);
         pin();
-        workgroup_barrier();                                              // input rows
+        workgroup_barrier();                                              // 1: input rows
         multiply(q, n3{}, k1{}, x, D + 8);
-        workgroup_barrier();
-        workgroup_barrier();                                              // q, k, v
-        some(q, p_c, o, 0, 2); some(q + 2, p_e, o, 0, 2); some(w1 + 4, p_1[2], o, 0, 2);
+        workgroup_barrier();                                              // 2
+        values_here();                                                    // q, k, v
+        some(q, p_c, o, 0, 2); some(q + 2, p_e, o, 0, 2);
         pin();
-        workgroup_barrier();                                              // attention
-        workgroup_barrier();                                              // context
+        workgroup_barrier();                                              // 3: context
+        some(w1 + 3, p_1[1], o, 1, 1); some(w1 + 4, p_1[2], o, 0, 1);
+        pin();
         multiply(o_at, n1{}, k1{}, y, 4 * D + 8);
         pin();
-        workgroup_barrier();
-        workgroup_barrier();                                              // sums
-        some(w1 + 6, p_1[3], o, 0, 2); some(w2 + 1, p_2, o, 1, 3);
+        workgroup_barrier();                                              // 4
+        values_here();                                                    // sums
+        some(w1 + 5, p_1[2], o, 1, 1); some(w1 + 6, p_1[3], o, 0, 2); some(w2, p_2, o, 0, 1);
         pin();
-        workgroup_barrier();                                              // rows
+        workgroup_barrier();                                              // 5: rows
         multiply(q, n1{}, k1{}, x, D + 8);
-        workgroup_barrier();
-        workgroup_barrier();                                              // queries
-        some(w2 + 4, p_2, o, 4, 4);
+        workgroup_barrier();                                              // 6
+        values_here();                                                    // queries
+        some(w2 + 1, p_2, o, 1, 2);
         pin();
-        workgroup_barrier();                                              // attention
-        workgroup_barrier();                                              // context
+        workgroup_barrier();                                              // 7: context
+        some(w2 + 3, p_2, o, 3, 2);
+        pin();
         multiply(q + 2, n1{}, k1{}, y, 4 * D + 8);
         pin();
-        workgroup_barrier();
-        workgroup_barrier();                                              // sums
-        some(q, p_q[0], next, 0, 2); some(q + 2, p_q[1], next, 0, 2); some(q + 4, p_q[2], next, 0, 2);
+        workgroup_barrier();                                              // 8
+        values_here();                                                    // sums
+        some(w2 + 5, p_2, o, 5, 3);
+        some(q, n_q[0], next, 0, 2); some(q + 2, n_q[1], next, 0, 1);
         pin();
-        workgroup_barrier();                                              // rows
+        workgroup_barrier();                                              // 9: rows
         multiply(w1, n4{}, k1{}, x, D + 8);
-        workgroup_barrier();
-        workgroup_barrier();                                              // activations
-        some(o_at, p_o, next, 0, 2);
+        workgroup_barrier();                                              // 10
+        workgroup_barrier();                                              // 11: activations
+        some(q + 3, n_q[1], next, 1, 1); some(q + 4, n_q[2], next, 0, 2);
+        pin();
         multiply(w2, n1{}, k4{}, y, 4 * D + 8);
         pin();
-        workgroup_barrier();
-        o = next;
-      }
-    } else {
-      for (int l = 0; l < a.layers; ++l) {
-        const size_t next = l + 1 < a.layers ? o + a.packed_stride : o;
-        workgroup_barrier();                                              // sums of the layer before
+        workgroup_barrier();                                              // 12
+      } else {
+        values_here();                                                    // sums of the layer before
         some(w1, p_1[0], o, 0, 2); some(w1 + 2, p_1[1], o, 0, 2);
         some(w1 + 4, p_1[2], o, 0, 1);
         pin();
-        workgroup_barrier();                                              // input rows
+        workgroup_barrier();                                              // 1: input rows
         multiply(q, n3{}, k1{}, x, D + 8);
-        workgroup_barrier();
-        workgroup_barrier();                                              // q, k, v
+        workgroup_barrier();                                              // 2
+        values_here();                                                    // q, k, v
         some(w1 + 5, p_1[2], o, 1, 1); some(w1 + 6, p_1[3], o, 0, 2); some(w2, p_2, o, 0, 2);
         pin();
-        workgroup_barrier();                                              // attention
-        workgroup_barrier();                                              // context
+        workgroup_barrier();                                              // 3: context
         some(w2 + 2, p_2, o, 2, 5);
         multiply(o_at, n1{}, k1{}, y, 4 * D + 8);
         pin();
-        workgroup_barrier();
-        workgroup_barrier();                                              // sums
+        workgroup_barrier();                                              // 4
+        values_here();                                                    // sums
         some(w2 + 7, p_2, o, 7, 1);
-        some(q, p_q[0], next, 0, 2); some(q + 2, p_q[1], next, 0, 2);
+        some(q, n_q[0], next, 0, 2); some(q + 2, n_q[1], next, 0, 2);
         pin();
-        workgroup_barrier();                                              // rows
+        workgroup_barrier();                                              // 9: rows
         multiply(w1, n4{}, k1{}, x, D + 8);
-        workgroup_barrier();
-        workgroup_barrier();                                              // activations
-        some(q + 4, p_q[2], next, 0, 2);
-        some(o_at, p_o, next, 0, 2);
+        workgroup_barrier();                                              // 10
+        workgroup_barrier();                                              // 11: activations
+        some(q + 4, n_q[2], next, 0, 2);
+        some(o_at, more ? p_o : p_2, next, 0, 2);
         multiply(w2, n1{}, k4{}, y, 4 * D + 8);
         pin();
-        workgroup_barrier();
-        o = next;
+        workgroup_barrier();                                              // 12
       }
     }
     if (tid == 0) leave();
@@ -285,22 +297,39 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     if (xw < 6) *reinterpret_cast<half8_t*>(&vec[l & 1][xw][lane * 8]) = v;
     else if (xw == 6 && lane < 22) *reinterpret_cast<half8_t*>(&vec[l & 1][6][lane * 8]) = v;
   };
-  keep_vectors(0, vectors());
-  // ---- what the products leave: unit, row and pair of columns that this thread finishes
-  int ui = xt / (8 * R), um = xt / 8 % R, un = xt % 8 * 2;
-  auto total = [&](float& v0, float& v1) {
-    v0 = part[0][ui][um][un]; v1 = part[0][ui][um][un + 1];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) { v0 += part[w][ui][um][un]; v1 += part[w][ui][um][un + 1]; }
+  half8_t ahead = vectors();
+  // an exchange has ended for this wavefront: the others may request weights
+  int exchanges = 0;
+  auto seen = [&] {
+    ++exchanges;
+    __hip_atomic_store(&arrived[xw], exchanges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   };
-  auto bias = [&](int l, int unit) { return *reinterpret_cast<const half2_t*>(&vec[l & 1][6][unit * 16 + un]); };
-  auto residual = [&](int l, int region, int unit) {
+  // ---- What the products leave: unit, row and pair of columns that this thread finishes.  Everything it needs besides is read
+  // while the products run.  With 4 rows other wavefronts than those that look for the rows next.
+  constexpr int SKIP = R == 4 ? 256 : 0;
+  int ui = (xt ^ SKIP) / (8 * R), um = xt / 8 % R, un = xt % 8 * 2;
+  half2_t bi = {0, 0}, xr = {0, 0};
+  auto prepare = [&](int l, int units, int first) {
+    if (ui < units) bi = *reinterpret_cast<const half2_t*>(&vec[l & 1][6][(first + ui) * 16 + un]);
+    if (units == 1) xr = *reinterpret_cast<const half2_t*>(PRE ? &us[um][j * 16 + un] : &xs[um][j * 16 + un]);
+  };
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
+  auto total = [&](float& v0, float& v1) {   // + bias
+    floatx2 p[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) p[w] = *reinterpret_cast<const floatx2*>(&part[w][ui][um][un]);
+    // all of them requested before the first is added: left to itself the compiler takes a trip to LDS for each
+    asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(p[4]), "+v"(p[5]), "+v"(p[6]), "+v"(p[7]));
+    v0 = p[0][0]; v1 = p[0][1];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) { v0 += p[w][0]; v1 += p[w][1]; }
+    v0 += (float)bi[0]; v1 += (float)bi[1];
+  };
+  auto residual = [&](int l, int region) {
     if (ui < 1 && um < rows) {
       float v0, v1;
       total(v0, v1);
-      const half2_t bi = bias(l, unit);
-      const half_t* x = PRE ? &us[um][j * 16 + un] : &xs[um][j * 16 + un];
-      const float s0 = (float)x[0] + (v0 + (float)bi[0]), s1 = (float)x[1] + (v1 + (float)bi[1]);
+      const float s0 = (float)xr[0] + v0, s1 = (float)xr[1] + v1;
       if constexpr (PRE) ex.put2(at(l, region), (j * R + um) * 32 + un * 2, (half_t)s0, (half_t)s1);
       else ex.put2(at(l, region), (j * R + um) * 64 + un * 4, s0, s1);
     }
@@ -343,7 +372,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
       *reinterpret_cast<piece_t*>(p + (q * 64 + lane) * VP) = h;
     }
   };
-  auto gather_norm = [&](int l, int region, const half_t* g, const half_t* b, half_t* out_x, half_t* out_y, auto then) {
+  auto gather_norm = [&](int l, int region, const half_t* g, const half_t* b, half_t* out_x, half_t* out_y) {
     half_t g8[NP][VP], b8[NP][VP];
     u32x4 raw[RW * NP];
     const int base = at(l, region);
@@ -356,7 +385,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
               return (q / (NT * ES / 16) * R + m) * (NT * ES) + q % (NT * ES / 16) * 16;
             }, raw);
     }
-    then();
+    seen();
 #pragma unroll
     for (int rr = 0; rr < RW; ++rr) {
       const int m = xw + rr * kWaves;
@@ -382,13 +411,14 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   // ---- staging of what the products without LayerNorm read
   auto stage_ctx = [&](int l, int region) {
     constexpr int N = (R * D / 8 + 511) / 512;
-    if (xw * 64 >= rows * (D / 8)) return;
+    const int first = xt ^ SKIP;   // with 4 rows not the wavefronts that attend first
+    if ((xw ^ (SKIP / 64)) * 64 >= rows * (D / 8)) return;
     u32x4 raw[N];
     const int base = at(l, region);
-    ex.wait([&](int) { return base; }, [&](int i) { return min(i * 512 + xt, rows * (D / 8) - 1) * 16; }, raw);
+    ex.wait([&](int) { return base; }, [&](int i) { return min(i * 512 + first, rows * (D / 8) - 1) * 16; }, raw);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int p = i * 512 + xt;
+      const int p = i * 512 + first;
       if (p < rows * (D / 8)) *reinterpret_cast<u32x4*>(&st[p / (D / 8)][p % (D / 8) * 8]) = raw[i];
     }
   };
@@ -412,27 +442,31 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   const int pair = j + W * team, am = min(pair / H, rows - 1), ah = pair % H;
   const int arow = r0 + am, sent = arow / a.beam;
   auto team_of = [&](int nkeys) { return pair < rows * H ? min(nkeys <= 32 ? 1 : nkeys <= 64 ? 2 : nkeys <= 128 ? 4 : 8, NSH) : 0; };
-  const int n_self = team_of(pos);
+  int n_self = 0, n_cross = 0, src_off = 0, src_len = 0;
   const bool table = !PRE && a.anc != nullptr;
   const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
   auto slot_of = [&](int p) { return table ? min(max(slots[p], 0), a.beam - 1) : 0; };   // of the sentence's rows
   auto key_offset = [&](int slot, int p) { return ((slot * a.T + p) * D + c8) * 2; };
+  // what attention goes by, looked up while the first product runs
+  auto look_up = [&] {
+    n_self = team_of(pos);
 #pragma unroll
-  for (int u = 0; u < U; ++u) {   // the first trip's places in the cache, the same in all layers
-    const int p = max(min(ash + (gk + u * 8) * n_self, pos - 1), 0);
-    first_key[xw][u][lane] = key_offset(slot_of(p), p);
-  }
-  int src_off = 0, src_len = 0;
-  if constexpr (!PRE) { src_off = a.src_off[sent]; src_len = a.src_len[sent]; }
-  const int n_cross = team_of(src_len);
+    for (int u = 0; u < U; ++u) {   // the first trip's places in the cache, the same in all layers
+      const int p = max(min(ash + (gk + u * 8) * n_self, pos - 1), 0);
+      first_key[xw][u][lane] = key_offset(slot_of(p), p);
+    }
+    if constexpr (!PRE) {
+      src_off = a.src_off[sent]; src_len = a.src_len[sent];
+      n_cross = team_of(src_len);
+    }
+  };
   half8_t kn[U], vn[U];
   auto request = [&](bool self, const half_t* Kb, const half_t* Vb, int nkeys, int n, int jb, auto first) {
     const size_t own = self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0;
     const char* Kh = reinterpret_cast<const char*>(Kb + own + ah * 64);
     const char* Vh = reinterpret_cast<const char*>(Vb + own + ah * 64);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (u > 0 && jb + u * 8 * n >= nkeys) continue;   // nobody in this wavefront has such a key
+    for (int u = 0; u < U; ++u) {   // past the last key: that one again
       unsigned o;
       if (self && first) {
         o = first_key[xw][u][lane];
@@ -444,13 +478,18 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
       vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
     }
   };
-  auto attend = [&](int l, bool self, const half_t* Kb, const half_t* Vb, int nkeys, int n) {
-    const int region_out = self ? Rg::ctx : Rg::ctx2;
+  // One trip for up to 32 keys of a wavefront, as code without branches: the chain of instructions, not their number, is what
+  // counts for a wavefront that has its SIMD to itself.
+  int attentions = 0;
+  auto attend = [&](int l, auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n) {
+    constexpr bool self = decltype(of_self)::value;
+    constexpr int region_out = self ? Rg::ctx : Rg::ctx2;
     constexpr float qscale = 0.125f * 1.44269504088896340736f;   // scores in units of log 2
     half8_t q, knew, vnew;
+    ++attentions;
     if (ash < n) {
       const int lo = (c8 >> 4) * R * 32 + (c8 & 8) * 2;
-      if (self) {
+      if constexpr (self) {
         u32x4 raw[3];
         const int base = at(l, Rg::qkv) + (ah * 4 * R + am) * 32;
         ex.wait([&](int i) { return base + i * (D / 16 * 32) * R; }, [&](int) { return lo; }, raw);
@@ -462,9 +501,41 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
         q = __builtin_bit_cast(half8_t, raw[0]);
       }
     }
-    workgroup_barrier();
-    if (ash < n) {
-      float m = -INFINITY, z = 0.f, acc[8];   // m: of the wavefront
+    seen();
+    if (ash >= n) return;
+    float m, z, acc[8];   // m: of the wavefront
+    if (nkeys <= U * 8 * n) {
+      float sc[U + 1], p[U + 1];
+#pragma unroll
+      for (int u = 0; u < U; ++u) sc[u] = dot8(q, kn[u]);
+      if constexpr (self) sc[U] = dot8(q, knew);
+#pragma unroll
+      for (int u = 0; u < U + self; ++u) sc[u] = group_sum<8>(sc[u]) * qscale;
+#pragma unroll
+      for (int u = 0; u < U; ++u) sc[u] = ash + (gk + u * 8) * n < nkeys ? sc[u] : -INFINITY;
+      m = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+      if constexpr (self) {   // the new position, counted once: by the team's last wavefront
+        sc[U] = ash == n - 1 && gk == 0 ? sc[U] : -INFINITY;
+        m = fmaxf(m, sc[U]);
+        if (nkeys == 0) {   // what the cache holds was never written
+#pragma unroll
+          for (int u = 0; u < U; ++u) vn[u] = half8_t{};
+        }
+      }
+      for_lane_bits<8>([&](auto bit) { m = max_lane_xor<decltype(bit)::value>(m); });   // finite: the wavefront has a key
+#pragma unroll
+      for (int u = 0; u < U + self; ++u) p[u] = __builtin_amdgcn_exp2f(sc[u] - m);   // 0 past the last key, which is there again
+      z = (p[0] + p[1]) + (p[2] + p[3]);
+      if constexpr (self) z += p[U];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        acc[i] = p[0] * (float)vn[0][i];
+#pragma unroll
+        for (int u = 1; u < U; ++u) acc[i] += p[u] * (float)vn[u][i];
+        if constexpr (self) acc[i] += p[U] * (float)vnew[i];
+      }
+    } else {
+      m = -INFINITY; z = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] = 0.f;
       for (int jb = ash; jb < nkeys; jb += U * 8 * n) {   // the same trips in every lane of the wavefront
@@ -472,10 +543,8 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
         half8_t vv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          sc[u] = -INFINITY;
-          if (jb + u * 8 * n >= nkeys) continue;
           const float s = group_sum<8>(dot8(q, kn[u])) * qscale;
-          if (jb + (gk + u * 8) * n < nkeys) sc[u] = s;
+          sc[u] = jb + (gk + u * 8) * n < nkeys ? s : -INFINITY;
           vv[u] = vn[u];
           mx = fmaxf(mx, sc[u]);
         }
@@ -489,14 +558,13 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
         for (int i = 0; i < 8; ++i) acc[i] *= corr;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          if (jb + u * 8 * n >= nkeys) continue;
-          const float p = __builtin_amdgcn_exp2f(sc[u] - mx);   // 0 past the last key, which is there again
+          const float p = __builtin_amdgcn_exp2f(sc[u] - mx);
           z += p;
 #pragma unroll
           for (int i = 0; i < 8; ++i) acc[i] += p * (float)vv[u][i];
         }
       }
-      if (self && ash == n - 1) {   // the new position, counted once: by the team's last wavefront
+      if (self && ash == n - 1) {   // the new position
         const float s = group_sum<8>(dot8(q, knew)) * qscale, mx = fmaxf(m, s);
         const float corr = __builtin_amdgcn_exp2f(m - mx), p = gk == 0 ? __builtin_amdgcn_exp2f(s - mx) : 0.f;
         m = mx;
@@ -504,45 +572,52 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = acc[i] * corr + p * (float)vnew[i];
       }
-      column_sums(acc);
-      for_lane_bits<8>([&](auto bit) { z = add_lane_xor<decltype(bit)::value>(z); });
-      if (n == 1) {
-        const float inv = 1.0f / z;
-        if ((lane & 8) == 0) ex.put2(at(l, region_out), am * (D * 2) + (ah * 64 + own_column(lane)) * 2, (half_t)(acc[0] * inv), (half_t)(acc[1] * inv));
-      } else {
-        typedef float floatx2 __attribute__((ext_vector_type(2)));
-        *reinterpret_cast<floatx2*>(&att_o[xw][own_column(lane)]) = floatx2{acc[0], acc[1]};
-        if (lane == 0) { att_m[xw] = m; att_l[xw] = z; }
-      }
     }
-    workgroup_barrier();
-    if (n > 1 && ash == 0) {   // the team's first wavefront: two columns a lane, in both halves alike
-      typedef float floatx2 __attribute__((ext_vector_type(2)));
-      const int c = (lane & 31) * 2;
-      auto merge = [&](auto parts) {
-        constexpr int P = decltype(parts)::value;
-        if constexpr (P <= NSH) {
-          float pm[P], mx = -INFINITY, z = 0.f, o0 = 0.f, o1 = 0.f;
-          floatx2 po[P];
+    column_sums(acc);
+    for_lane_bits<8>([&](auto bit) { z = add_lane_xor<decltype(bit)::value>(z); });
+    auto inverse = [](float v) {   // one Newton step; v is at least 1
+      const float r = __builtin_amdgcn_rcpf(v);
+      return fmaf(fmaf(-v, r, 1.0f), r, r);
+    };
+    if (n == 1) {
+      const float inv = inverse(z);
+      if ((lane & 8) == 0) ex.put2(at(l, region_out), am * (D * 2) + (ah * 64 + own_column(lane)) * 2, (half_t)(acc[0] * inv), (half_t)(acc[1] * inv));
+      return;
+    }
+    *reinterpret_cast<floatx2*>(&att_o[xw][own_column(lane)]) = floatx2{acc[0], acc[1]};
+    if (lane == 0) { att_m[xw] = m; att_l[xw] = z; }
+    if (ash > 0) {   // LDS takes a wavefront's stores in order
+      __hip_atomic_store(&attended[xw], attentions, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      return;
+    }
+    // the team's first wavefront: two columns a lane, in both halves alike
+    while (!__all(__hip_atomic_load(&attended[xw + max(min(lane, n - 1), 1)], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= attentions)) {}
+    const int c = (lane & 31) * 2;
+    auto merge = [&](auto parts) {
+      constexpr int P = decltype(parts)::value;
+      if constexpr (P <= NSH) {
+        float pm[P], pl[P], mx = -INFINITY, zt = 0.f, o0 = 0.f, o1 = 0.f;
+        floatx2 po[P];
 #pragma unroll
-          for (int w = 0; w < P; ++w) { pm[w] = att_m[xw + w]; po[w] = *reinterpret_cast<const floatx2*>(&att_o[xw + w][c]); }
+        for (int w = 0; w < P; ++w) { pm[w] = att_m[xw + w]; pl[w] = att_l[xw + w]; po[w] = *reinterpret_cast<const floatx2*>(&att_o[xw + w][c]); }
 #pragma unroll
-          for (int w = 0; w < P; ++w) mx = fmaxf(mx, pm[w]);
+        for (int w = 0; w < P; ++w) asm volatile("" : "+v"(pm[w]), "+v"(pl[w]), "+v"(po[w]));
 #pragma unroll
-          for (int w = 0; w < P; ++w) {
-            const float cw = __builtin_amdgcn_exp2f(pm[w] - mx);
-            z += att_l[xw + w] * cw;
-            o0 += po[w][0] * cw;
-            o1 += po[w][1] * cw;
-          }
-          const float inv = 1.0f / z;
-          if (lane < 32) ex.put2(at(l, region_out), am * (D * 2) + (ah * 64 + c) * 2, (half_t)(o0 * inv), (half_t)(o1 * inv));
+        for (int w = 0; w < P; ++w) mx = fmaxf(mx, pm[w]);
+#pragma unroll
+        for (int w = 0; w < P; ++w) {
+          const float cw = __builtin_amdgcn_exp2f(pm[w] - mx);
+          zt += pl[w] * cw;
+          o0 += po[w][0] * cw;
+          o1 += po[w][1] * cw;
         }
-      };
-      if (n == 2) merge(std::integral_constant<int, 2>{});
-      else if (n == 4) merge(std::integral_constant<int, 4>{});
-      else merge(std::integral_constant<int, 8>{});
-    }
+        const float inv = inverse(zt);
+        if (lane < 32) ex.put2(at(l, region_out), am * (D * 2) + (ah * 64 + c) * 2, (half_t)(o0 * inv), (half_t)(o1 * inv));
+      }
+    };
+    if (n == 2) merge(std::integral_constant<int, 2>{});
+    else if (n == 4) merge(std::integral_constant<int, 4>{});
+    else merge(std::integral_constant<int, 8>{});
   };
 
   for (int l = 0; l < a.layers; ++l) {
@@ -551,15 +626,8 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     asm volatile("" : "+s"(xw), "+s"(j));
     const half_t* Kc = reinterpret_cast<const half_t*>(global(now()->cache) + (size_t)(2 * l) * now()->cache_stride);
     const half_t* Vc = reinterpret_cast<const half_t*>(global(now()->cache) + (size_t)(2 * l + 1) * now()->cache_stride);
-    half8_t ahead = {};
-    auto sums_here = [&] {
-      if (l + 1 < a.layers) ahead = vectors();
-      if (ash < n_self) request(true, Kc, Vc, pos, n_self, ash, std::true_type{});
-      pin();
-      workgroup_barrier();
-    };
     if (l == 0) {
-      sums_here();
+      seen();
 #pragma unroll
       for (int rr = 0; rr < RW; ++rr) {
         const int m = xw + rr * kWaves, r = r0 + m;
@@ -584,73 +652,89 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
           put_pieces(xs[m], o);
         }
       }
+      keep_vectors(0, ahead);
     } else {
-      if constexpr (PRE) gather_norm(l - 1, Rg::u3, vec[l & 1][0], vec[l & 1][1], nullptr, nullptr, sums_here);
-      else gather_norm(l - 1, Rg::u3, vec[(l - 1) & 1][4], vec[(l - 1) & 1][5], nullptr, nullptr, sums_here);
+      if (ash < n_self) request(true, Kc, Vc, pos, n_self, ash, std::true_type{});
+      pin();
+      if constexpr (PRE) gather_norm(l - 1, Rg::u3, vec[l & 1][0], vec[l & 1][1], nullptr, nullptr);
+      else gather_norm(l - 1, Rg::u3, vec[(l - 1) & 1][4], vec[(l - 1) & 1][5], nullptr, nullptr);
     }
+    // Between two barriers of a pair the products run, and there is time for what need not wait for them.
     workgroup_barrier();                                                  // 1
+    prepare(l, 3, 0);
+    if (l + 1 < a.layers) ahead = vectors();
+    pin();
     workgroup_barrier();                                                  // 2
     if (ui < 3 && um < rows) {
       float v0, v1;
       total(v0, v1);
-      const half2_t bi = bias(l, ui);
-      const half_t h0 = (half_t)(v0 + (float)bi[0]), h1 = (half_t)(v1 + (float)bi[1]);
+      const half_t h0 = (half_t)v0, h1 = (half_t)v1;
       ex.put2(at(l, Rg::qkv), ((j + W * ui) * R + um) * 32 + un * 2, h0, h1);
       if (ui >= 1) *reinterpret_cast<half2_t*>(const_cast<half_t*>(ui == 1 ? Kc : Vc) + ((size_t)(r0 + um) * a.T + pos) * D + j * 16 + un) = half2_t{h0, h1};
     }
-    attend(l, true, Kc, Vc, pos, n_self);                               // 3 inside
+    if (l == 0) {
+      look_up();
+      if (ash < n_self) request(true, Kc, Vc, pos, n_self, ash, std::true_type{});
+      pin();
+    }
+    attend(l, std::true_type{}, Kc, Vc, pos, n_self);
     if (l + 1 < a.layers) keep_vectors(l + 1, ahead);
     stage_ctx(l, Rg::ctx);
+    workgroup_barrier();                                                  // 3
+    prepare(l, 1, 3);
+    pin();
     workgroup_barrier();                                                  // 4
-    workgroup_barrier();                                                  // 5
-    residual(l, Rg::u1, 3);
+    residual(l, Rg::u1);
     if constexpr (!PRE) {
       const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
-      gather_norm(l, Rg::u1, vec[l & 1][0], vec[l & 1][1], nullptr, nullptr, [&] {
-        if (ash < n_cross) request(false, kvb, kvb + D, src_len, n_cross, ash, std::true_type{});
-        pin();
-        workgroup_barrier();
-      });
+      if (ash < n_cross) request(false, kvb, kvb + D, src_len, n_cross, ash, std::true_type{});
+      pin();
+      gather_norm(l, Rg::u1, vec[l & 1][0], vec[l & 1][1], nullptr, nullptr);
+      workgroup_barrier();                                                // 5
+      prepare(l, 1, 4);
+      pin();
       workgroup_barrier();                                                // 6
-      workgroup_barrier();                                                // 7
       if (ui < 1 && um < rows) {
         float v0, v1;
         total(v0, v1);
-        const half2_t bi = bias(l, 4);
-        ex.put2(at(l, Rg::q2), (j * R + um) * 32 + un * 2, (half_t)(v0 + (float)bi[0]), (half_t)(v1 + (float)bi[1]));
+        ex.put2(at(l, Rg::q2), (j * R + um) * 32 + un * 2, (half_t)v0, (half_t)v1);
       }
-      attend(l, false, kvb, kvb + D, src_len, n_cross);                  // 8 inside
+      attend(l, std::false_type{}, kvb, kvb + D, src_len, n_cross);
       stage_ctx(l, Rg::ctx2);
-      workgroup_barrier();                                                // 9
-      workgroup_barrier();                                                // 10
-      residual(l, Rg::u2, 5);
+      workgroup_barrier();                                                // 7
+      prepare(l, 1, 5);
+      pin();
+      workgroup_barrier();                                                // 8
+      residual(l, Rg::u2);
     }
-    gather_norm(l, PRE ? Rg::u1 : Rg::u2, vec[l & 1][2], vec[l & 1][3], nullptr, nullptr, workgroup_barrier);
-    workgroup_barrier();                                                  // 11
-    workgroup_barrier();                                                  // 12
+    gather_norm(l, PRE ? Rg::u1 : Rg::u2, vec[l & 1][2], vec[l & 1][3], nullptr, nullptr);
+    workgroup_barrier();                                                  // 9
+    prepare(l, 4, 6);
+    pin();
+    workgroup_barrier();                                                  // 10
     if (ui < 4 && um < rows) {
       float v0, v1;
       total(v0, v1);
-      const half2_t bi = bias(l, 6 + ui);
-      v0 += (float)bi[0]; v1 += (float)bi[1];
       if constexpr (PRE) { v0 = tanh_gelu(v0); v1 = tanh_gelu(v1); }
       else { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
       ex.put2(at(l, Rg::ff), ((j + W * ui) * R + um) * 32 + un * 2, (half_t)v0, (half_t)v1);
     }
+    stage_ff(l);
+    workgroup_barrier();                                                  // 11
+    prepare(l, 1, 10);
     {   // the other set is for the next launch
       const size_t n16 = (size_t)dirty * a.layers * (Rg::size * D) / 16, all = (size_t)(G * W) * (kWaves * 64);
       const u32x4 s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
       for (size_t i = (size_t)(grp * W + j) * (kWaves * 64) + xt + l * all; i < n16; i += a.layers * all)
         reinterpret_cast<u32x4*>(a.exchange + (size_t)(1 - parity) * a.set_bytes)[i] = s4;
     }
-    stage_ff(l);
-    workgroup_barrier();                                                  // 13
-    workgroup_barrier();                                                  // 14
-    residual(l, Rg::u3, 10);
+    pin();
+    workgroup_barrier();                                                  // 12
+    residual(l, Rg::u3);
   }
   if (j == 0) {   // the rows for the vocabulary product
-    if constexpr (PRE) gather_norm(a.layers - 1, Rg::u3, a.lnfg, a.lnfb, a.x_out, a.hidden, [] {});
-    else gather_norm(a.layers - 1, Rg::u3, vec[(a.layers - 1) & 1][4], vec[(a.layers - 1) & 1][5], nullptr, a.hidden, [] {});
+    if constexpr (PRE) gather_norm(a.layers - 1, Rg::u3, a.lnfg, a.lnfb, a.x_out, a.hidden);
+    else gather_norm(a.layers - 1, Rg::u3, vec[(a.layers - 1) & 1][4], vec[(a.layers - 1) & 1][5], nullptr, a.hidden);
   }
   ex.report(a.state, a.error);
 }
