@@ -169,7 +169,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     load_gain(g8, b8, g, b);
     u32x4 raw[CH];
     const int base = at(l, region);
-    ex.wait([&](int) { return base; }, [&](int i) { return piece_at[i]; }, raw);
+    ex.wait<kLead>([&](int) { return base; }, [&](int i) { return piece_at[i]; }, raw);
 #pragma unroll
     for (int i = 0; i < CH; ++i) *reinterpret_cast<u32x4*>(&us[piece_row[i]][piece_col[i]]) = raw[i];
     __syncthreads();
@@ -247,12 +247,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       if (self) {
         u32x4 raw[3];
         const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 32;
-        ex.wait([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
+        ex.wait<kLead>([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
         q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
       } else {
         u32x4 raw[1];
         const int base = at(l, Rg::q2) + (ah * 64 / QT * rp + am) * (QT * 2);
-        ex.wait([&](int) { return base; }, [&](int) { return c8 / QT * rp * (QT * 2) + c8 % QT * 2; }, raw);
+        ex.wait<kLead>([&](int) { return base; }, [&](int) { return c8 / QT * rp * (QT * 2) + c8 % QT * 2; }, raw);
         q = __builtin_bit_cast(half8_t, raw[0]);
       }
       float m = -INFINITY, z = 0.f, acc[8];   // m: of the wavefront
@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     u32x4 raw[N];
     const int step = units ? 64 * rp : 64, base = at(l, region_in) + wave * N * step;
     const int lo = units ? ((kc >> 1) * rp + min(fm, rows - 1)) * 32 + (kc & 1) * 16 : min(fm, rows - 1) * (D * 2) + kc * 16;
-    ex.wait([&](int i) { return base + i * step; }, [&](int) { return lo; }, raw);
+    ex.wait<kLead>([&](int i) { return base + i * step; }, [&](int) { return lo; }, raw);
     floatx4 acc[2] = {zero4, zero4};
 #pragma unroll
     for (int s = 0; s < N; ++s)
@@ -651,7 +651,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       u32x4 raw[4];
       const int base = at(lin, region_in) + j * 256;
       const int lo = (int)(oc >> 6) * (rp * 256) + (int)(oc & 63) * 4;
-      ex.wait([&](int i) { return base + i * (CG * 256) * rp; }, [&](int) { return lo; }, raw);
+      ex.wait<kLead>([&](int i) { return base + i * (CG * 256) * rp; }, [&](int) { return lo; }, raw);
       const half4_t x4 = *reinterpret_cast<const half4_t*>(&xrow[oc]);
       const floatx4 f0 = __builtin_bit_cast(floatx4, raw[0]), f1 = __builtin_bit_cast(floatx4, raw[1]),
                     f2 = __builtin_bit_cast(floatx4, raw[2]), f3 = __builtin_bit_cast(floatx4, raw[3]);
@@ -675,7 +675,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     const int t = tid;
     const int per_row = cols / 8;   // rows the group does not have: its last one again
     auto row_of = [&](int p) { return min(p / per_row, rows - 1); };
-    ex.wait([&](int) { return base + col0 * 2; },
+    ex.wait<kLead>([&](int) { return base + col0 * 2; },
             [&](int i) { const int p = i * kThreads + t; return row_of(p) * (D * 2) + p % per_row * 16; }, raw);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -690,7 +690,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     u32x4 raw[CHX];
     const int t = tid;
     constexpr int per_unit = R * 2;
-    ex.wait([&](int) { return base; },
+    ex.wait<kLead + 6>([&](int) { return base; },
             [&](int i) { const int p = i * kThreads + t; return p / per_unit * (rp * 32) + min(p % per_unit >> 1, rows - 1) * 32 + (p & 1) * 16; }, raw);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -797,12 +797,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       if (self) {
         u32x4 raw[3];
         const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 32;
-        ex.wait([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
+        ex.wait<kLead + 6>([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
         q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
       } else {
         u32x4 raw[8];   // four slabs of the head's 64 columns
         const int base = at(l, Rg::qs) + (ah * rp + am) * 256;
-        ex.wait([&](int i) { return base + (i >> 1) * (CG * 256) * rp; }, [&](int i) { return c8 * 4 + (i & 1) * 16; }, raw);
+        ex.wait<kLead>([&](int i) { return base + (i >> 1) * (CG * 256) * rp; }, [&](int i) { return c8 * 4 + (i & 1) * 16; }, raw);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           float v = __builtin_bit_cast(floatx4, raw[i >> 2])[i & 3];

@@ -35,6 +35,8 @@ namespace {
 constexpr int kDieThreads = 1024;      // eight wavefronts that multiply, eight that exchange
 constexpr int kDieGroup = 32;          // workgroups of a group: one per compute unit of a die
 constexpr int kDies = 8;
+constexpr int kDieLead = 6;            // as kLead: layers of a step in us with 0 / 4 / 6 / 8 / 12: 4 rows 73.0 72.4 70.4 71.6 73.1, 32 rows 85.9 85.4 85.0
+                                       // 84.7 85.3, 64 rows 92.9 89.9 90.6 91.3 92.7, 128 rows 109.7 106.7 105.9 106.0 108.5
 
 typedef half_t half2_t __attribute__((ext_vector_type(2)));
 
@@ -82,8 +84,8 @@ __device__ __forceinline__ int own_column(int lane) { return (lane & 7) * 8 + (l
 // Few rows, d = 512: up to 16 a die.  Eight wavefronts hold the matrices in registers (an eighth of k each), ask for the next
 // ones and multiply; the other eight look for the exchanged values, normalise, attend, add the eight partial sums up and
 // publish.  Nobody waits for a value behind weights of its own this way, and 128 registers are enough for either.
-// Measured, layers of one step in us at positions up to 60, sources of 30 (groups of 8 or 16 rows all over the chip): 4 rows 70 (94),
-// 8 rows 70 (100), 32 rows 84 (106), 64 rows 91 (113), 128 rows 108 (130).  Every layer is a chain of eight exchanges and products,
+// Measured, layers of one step in us at positions up to 60, sources of 30 (groups of 8 or 16 rows all over the chip): 4 rows 69 (94),
+// 8 rows 69 (100), 32 rows 83 (106), 64 rows 89 (113), 128 rows 104 (130).  Every layer is a chain of eight exchanges and products,
 // 9 us of its 11 on one die or two; the rest is what exchanges queue behind weights (with all of them in the L2, on wrong numbers: 59, 59, 59, 70,
 // 93).  The chain is made of instructions that wait for one another: what a wavefront does on it has no branches, asks LDS for all it
 // needs at once, and what can be done while somebody else works is done then: 77, 78, 94, 101, 118 before.
@@ -379,7 +381,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     if (xw < rows) {
     pieces(g, g8);
     pieces(b, b8);
-    ex.wait([&](int) { return base; },
+    ex.wait<kDieLead>([&](int) { return base; },
             [&](int i) {
               const int m = min(xw + i / NP * kWaves, rows - 1), q = i % NP * 64 + lane;   // a writer has NT ES bytes of a row
               return (q / (NT * ES / 16) * R + m) * (NT * ES) + q % (NT * ES / 16) * 16;
@@ -415,7 +417,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     if ((xw ^ (SKIP / 64)) * 64 >= rows * (D / 8)) return;
     u32x4 raw[N];
     const int base = at(l, region);
-    ex.wait([&](int) { return base; }, [&](int i) { return min(i * 512 + first, rows * (D / 8) - 1) * 16; }, raw);
+    ex.wait<kDieLead>([&](int) { return base; }, [&](int i) { return min(i * 512 + first, rows * (D / 8) - 1) * 16; }, raw);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int p = i * 512 + first;
@@ -427,7 +429,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     u32x4 raw[N];
     const int base = at(l, Rg::ff);
     auto row = [&](int p) { return min(p / 2 % R, rows - 1); };
-    ex.wait([&](int) { return base; },
+    ex.wait<kDieLead>([&](int) { return base; },
             [&](int i) { const int p = i * 512 + xt; return (p / (2 * R) * R + row(p)) * 32 + (p & 1) * 16; }, raw);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -492,12 +494,12 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
       if constexpr (self) {
         u32x4 raw[3];
         const int base = at(l, Rg::qkv) + (ah * 4 * R + am) * 32;
-        ex.wait([&](int i) { return base + i * (D / 16 * 32) * R; }, [&](int) { return lo; }, raw);
+        ex.wait<kDieLead>([&](int i) { return base + i * (D / 16 * 32) * R; }, [&](int) { return lo; }, raw);
         q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
       } else {
         u32x4 raw[1];
         const int base = at(l, Rg::q2) + (ah * 4 * R + am) * 32;
-        ex.wait([&](int) { return base; }, [&](int) { return lo; }, raw);
+        ex.wait<kDieLead>([&](int) { return base; }, [&](int) { return lo; }, raw);
         q = __builtin_bit_cast(half8_t, raw[0]);
       }
     }

@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
       u32x4 raw[4];
       const int base = at(l, region_in) + j * 256;
       const int lo = (oc >> 6) * (rp * 256) + (oc & 63) * 4;
-      ex.wait([&](int i) { return base + i * (CG * 256) * rp; }, [&](int) { return lo; }, raw);
+      ex.wait<kLeadF32>([&](int i) { return base + i * (CG * 256) * rp; }, [&](int) { return lo; }, raw);
       v = *reinterpret_cast<const floatx4*>(&xrow[oc]) +
           ((((__builtin_bit_cast(floatx4, raw[0]) + __builtin_bit_cast(floatx4, raw[1])) + __builtin_bit_cast(floatx4, raw[2])) +
             __builtin_bit_cast(floatx4, raw[3])) + bi);
@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
   // ---- staging: all of a workgroup's accesses so far are acknowledged on the way
   auto stage = [&](auto& raw, int pieces, auto from, auto to) {   // piece p of 16 bytes: from(p) in the exchange, to(p) in LDS
     constexpr int N = sizeof(raw) / sizeof(raw[0]);
-    ex.wait([&](int) { return 0; }, [&](int i) { return from(min(i * kThreads + tid, pieces - 1)); }, raw);
+    ex.wait<kLeadF32>([&](int) { return 0; }, [&](int i) { return from(min(i * kThreads + tid, pieces - 1)); }, raw);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
@@ -232,13 +232,13 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_f32_kernel(const Stack
       if (self) {
         u32x4 raw[3];
         const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 192;
-        ex.wait([&](int i) { return base + i * 64; }, [&](int) { return (c4 >> 4) * rp * 192 + (c4 & 15) * 4; }, raw);
+        ex.wait<kLeadF32>([&](int i) { return base + i * 64; }, [&](int) { return (c4 >> 4) * rp * 192 + (c4 & 15) * 4; }, raw);
         q = __builtin_bit_cast(floatx4, raw[0]); knew = __builtin_bit_cast(floatx4, raw[1]); vnew = __builtin_bit_cast(floatx4, raw[2]);
       } else {
         const floatx4 bq = *reinterpret_cast<const floatx4*>(bias_q + ah * 64 + c4);
         u32x4 raw[4];   // four slabs of the head's 64 columns
         const int base = at(l, Rg::qs) + (ah * rp + am) * 256;
-        ex.wait([&](int i) { return base + i * (CG * 256) * rp; }, [&](int) { return c4 * 4; }, raw);
+        ex.wait<kLeadF32>([&](int i) { return base + i * (CG * 256) * rp; }, [&](int) { return c4 * 4; }, raw);
         q = (((__builtin_bit_cast(floatx4, raw[0]) + __builtin_bit_cast(floatx4, raw[1])) + __builtin_bit_cast(floatx4, raw[2])) +
              __builtin_bit_cast(floatx4, raw[3])) + bq;
       }

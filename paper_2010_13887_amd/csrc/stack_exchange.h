@@ -15,6 +15,12 @@ constexpr int kAgent = 16;             // cache policy of agent scope: sc1
 constexpr int kWorkgroup = 1;          // ... of workgroup scope: sc0
 constexpr int kSpinLimit = 1 << 19;    // polls of about a microsecond
 constexpr int kThreads = 512, kWaves = 8;
+// A wait starts when there is nothing left to do, long before the value can be there: what is looked for too early is in the way of the stores it
+// waits for and of the weights, and comes back behind them.  So the first look is LEAD times 64 clocks late.  Whole passes in ms with 0 / 4 / 8 / 12 / 16 /
+// 20: Transformer-big, 1 sentence 11.76 11.51 11.10 10.90 10.85 10.90, 32 sentences 28.7 28.2 28.0 27.7 27.7 27.8; decoder-only, d = 768, 1 row 10.2 9.98
+// 9.56 9.45 9.6 10.1, 32 rows 30.95 30.4 29.5 29.3 29.2 29.4; float32, d = 512, 32 rows 17.86 17.74 17.90 17.92 17.85 18.4.  Stage by stage the
+// groups of 16 and 32 rows gain 0.5 to 1 % with 18 where keys of a large group or the FFN's activations are waited for.
+constexpr int kLead = 12, kLeadF32 = 4;
 
 __device__ __forceinline__ unsigned publish_word(unsigned v) { return v == kSentinel ? 0x7FFF7FFFu : v; }   // one NaN for another
 
@@ -42,9 +48,14 @@ struct Exchange {
   __amdgpu_buffer_rsrc_t rsrc;
   int polls;   // of a wait; 1: one has run out, what this wavefront reads from now on may be missing
 
-  // v[i] = the 16 bytes at base(i) + lane(i) once all of them have been written (base: the same in all lanes)
-  template <int N, typename B, typename L>
+  // v[i] = the 16 bytes at base(i) + lane(i) once all of them have been written (base: the same in all lanes).  LEAD: units of
+  // 64 clocks before the first look, see kLead.
+  template <int LEAD, int N, typename B, typename L>
   __device__ __forceinline__ void wait(B base, L lane, u32x4 (&v)[N]) {
+    if constexpr (LEAD > 0) {
+      __builtin_amdgcn_s_sleep(LEAD);
+      asm volatile("" ::: "memory");
+    }
     for (int left = polls;;) {
 #pragma unroll
       for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane(i), base(i), kAgent);
