@@ -22,7 +22,7 @@
 // end).
 #include <cstdlib>
 
-#include "stack_exchange.h"
+#include "stack_attend.h"
 
 namespace lsq {
 
@@ -42,20 +42,17 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   constexpr int NU = 4 / X, UQ = (3 + X - 1) / X;
   constexpr int QT = NT < 8 ? 8 : NT;                          // query columns of the cross-attention per workgroup
   constexpr int TEAMS = X == 1 ? 2 : 1, NSH = kWaves / TEAMS;   // wavefronts that share a (row, head) pair
-  constexpr int U = 4;                                         // keys of a lane group in flight
   using Rg = Region<PRE>;
   constexpr int NV = (D + 511) / 512;
   constexpr int ES = PRE ? 2 : 4;                              // bytes of a residual sum
   constexpr int CH = (kRows * D * ES / 16 + kThreads - 1) / kThreads;   // 16-byte pieces of all rows' sums per thread
   using sum_t = std::conditional_t<PRE, half_t, float>;
-  typedef half_t half2_t __attribute__((ext_vector_type(2)));
 
   __shared__ __attribute__((aligned(16))) half_t xs[kRows][D + 8];    // normalised rows
   __shared__ __attribute__((aligned(16))) sum_t us[kRows][D + 16 / ES];   // residual sums (pre-LN: the residual stream)
   __shared__ __attribute__((aligned(16))) float part[kWaves][NU > UQ ? NU : UQ][kRows][16];
   __shared__ __attribute__((aligned(16))) float part2[kWaves][kRows][16];
-  __shared__ __attribute__((aligned(16))) float att_o[kWaves][64];
-  __shared__ float att_m[kWaves], att_l[kWaves];
+  __shared__ __attribute__((aligned(16))) Shares shares;
 
   int tid = threadIdx.x, lane = tid & 63;
   int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -201,129 +198,84 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     for (int w = 1; w < kWaves; ++w) { v0 += part[w][i][m][n]; v1 += part[w][i][m][n + 1]; }
   };
 
-  // ---- attention of one (row, head) pair per team of NSH wavefronts; a lane group of 8 holds a key's 64 values
+  // ---- attention of one (row, head) pair per team of NSH wavefronts (stack_attend.h)
   const int team = wave / NSH, ash = wave % NSH;
   int gk = lane >> 3, c8 = (lane & 7) * 8;
   const int pair = j + W * team, am = min(pair / H, rows - 1), ah = pair % H;
-  const bool attends = pair < rows * H;
   const int arow = r0 + am, sent = arow / a.beam;
-  const int jstep = 8 * NSH;
-  int jfirst = ash + gk * NSH;
-  int slot0[U];
   const bool table = !PRE && a.anc != nullptr;
   const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
   auto slot_of = [&](int p) { return table ? min(max(slots[p], 0), a.beam - 1) : 0; };   // of the sentence's rows
+  auto key_offset = [&](int p) { return (unsigned)((slot_of(p) * a.T + p) * D + c8) * 2u; };
+  const bool attends = pair < rows * H;
+  const int n_self = attends ? team_for<NSH>(pos) : 0;
+  unsigned first_key[kTrip];   // the first trip's places in the cache, the same in all layers
 #pragma unroll
-  for (int u = 0; u < U; ++u) slot0[u] = slot_of(max(min(jfirst + u * jstep, pos - 1), 0));
-  int src_off = 0, src_len = 0;
-  if constexpr (!PRE) { src_off = a.src_off[sent]; src_len = a.src_len[sent]; }
+  for (int u = 0; u < kTrip; ++u) first_key[u] = key_offset(max(min(ash + (gk + u * 8) * n_self, pos - 1), 0));
+  int src_off = 0, src_len = 0, n_cross = 0;
+  if constexpr (!PRE) {
+    src_off = a.src_off[sent]; src_len = a.src_len[sent];
+    n_cross = attends ? team_for<NSH>(src_len) : 0;
+  }
+  if (tid < kWaves) shares.left[tid] = 0;   // the first rows' barrier is ahead
+  int attentions = 0;
 
-  auto dot8 = [](const half8_t& x, const half8_t& y) {   // measured error against 64 bits: that of a chain of float multiply-adds
-    float s = 0.f;
+  // Wavefronts that have nothing to look at go on to wait for the context.
+  auto attend = [&](int l, auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n) {
+    constexpr bool self = decltype(of_self)::value;
+    ++attentions;
+    if (ash >= n) return;
+    half8_t kn[kTrip], vn[kTrip];
+    const size_t own = self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0;
+    const char* Kh = reinterpret_cast<const char*>(Kb + own + ah * 64);
+    const char* Vh = reinterpret_cast<const char*>(Vb + own + ah * 64);
+    auto request = [&](int jb, auto first) {   // past the last key: that one again
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_fdot2(half2_t{x[2 * i], x[2 * i + 1]}, half2_t{y[2 * i], y[2 * i + 1]}, s, false);
-    return s;
-  };
-  auto attend = [&](int l, bool self, const half_t* Kb, const half_t* Vb, int nkeys) {
-    if (attends) {
-      half8_t kn[U], vn[U];
-      const size_t own = self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0;
-      const char* Kh = reinterpret_cast<const char*>(Kb + own + ah * 64);
-      const char* Vh = reinterpret_cast<const char*>(Vb + own + ah * 64);
-      auto request = [&](int jb) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (u > 0 && jb - gk * NSH + u * jstep >= nkeys) continue;   // nobody in this wavefront has such a key
-          const int p = max(min(jb + u * jstep, nkeys - 1), 0);
-          const unsigned o = ((self ? ((jb == jfirst ? slot0[u] : slot_of(p)) * a.T + p) * D : p * (2 * D)) + c8) * 2u;
-          kn[u] = *reinterpret_cast<const half8_t*>(Kh + o);
-          vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
-        }
-      };
-      request(jfirst);
-      pin();
-      constexpr float qscale = 0.125f * 1.44269504088896340736f;   // scores in units of log 2
-      half8_t q, knew, vnew;
-      if (self) {
-        u32x4 raw[3];
-        const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 32;
-        ex.wait<kLead>([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
-        q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
-      } else {
-        u32x4 raw[1];
-        const int base = at(l, Rg::q2) + (ah * 64 / QT * rp + am) * (QT * 2);
-        ex.wait<kLead>([&](int) { return base; }, [&](int) { return c8 / QT * rp * (QT * 2) + c8 % QT * 2; }, raw);
-        q = __builtin_bit_cast(half8_t, raw[0]);
+      for (int u = 0; u < kTrip; ++u) {
+        const int p = max(min(jb + (gk + u * 8) * n, nkeys - 1), 0);
+        const unsigned o = !self ? (unsigned)(p * (2 * D) + c8) * 2u : first ? first_key[u] : key_offset(p);
+        kn[u] = *reinterpret_cast<const half8_t*>(Kh + o);
+        vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
       }
-      float m = -INFINITY, z = 0.f, acc[8];   // m: of the wavefront
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-      for (int jb = jfirst; jb - gk * NSH < nkeys; jb += U * jstep) {   // the same trips in every lane of the wavefront
-        float sc[U], mx = m;
-        half8_t vv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          sc[u] = -INFINITY;
-          if (jb - gk * NSH + u * jstep >= nkeys) continue;
-          const float s = group_sum<8>(dot8(q, kn[u])) * qscale;
-          if (jb + u * jstep < nkeys) sc[u] = s;
-          vv[u] = vn[u];
-          mx = fmaxf(mx, sc[u]);
-        }
-        const int jn = jb + U * jstep;
-        if (jn - gk * NSH < nkeys) request(jn);
-        for_lane_bits<8>([&](auto bit) { mx = max_lane_xor<decltype(bit)::value>(mx); });
-        const float corr = __builtin_amdgcn_exp2f(m - mx);   // mx is finite: the wavefront has a key in this trip
-        m = mx;
-        z *= corr;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] *= corr;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (jb - gk * NSH + u * jstep >= nkeys) continue;
-          const bool live = jb + u * jstep < nkeys;
-          const float p = live ? __builtin_amdgcn_exp2f(sc[u] - mx) : 0.f;
-          z += p;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) acc[i] += p * (live ? (float)vv[u][i] : 0.f);
-        }
-      }
-      if (self && ash == NSH - 1) {   // the new position, counted once: by the team's last wavefront
-        const float s = group_sum<8>(dot8(q, knew)) * qscale, mx = fmaxf(m, s);
-        const float corr = __builtin_amdgcn_exp2f(m - mx), p = gk == 0 ? __builtin_amdgcn_exp2f(s - mx) : 0.f;
-        m = mx;
-        z = z * corr + p;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = acc[i] * corr + p * (float)vnew[i];
-      }
-      for_lane_bits<8>([&](auto bit) {
-        constexpr int O = decltype(bit)::value;
-        z = add_lane_xor<O>(z);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = add_lane_xor<O>(acc[i]);
-      });
-      if (gk == 0) {
-        *reinterpret_cast<floatx4*>(&att_o[wave][c8]) = floatx4{acc[0], acc[1], acc[2], acc[3]};
-        *reinterpret_cast<floatx4*>(&att_o[wave][c8 + 4]) = floatx4{acc[4], acc[5], acc[6], acc[7]};
-        if (lane == 0) { att_m[wave] = m; att_l[wave] = z; }
-      }
+    };
+    request(ash, std::true_type{});
+    pin();
+    half8_t q, knew = {}, vnew = {};
+    if constexpr (self) {
+      u32x4 raw[3];
+      const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 32;
+      ex.wait<kLead>([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
+      q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
+    } else {
+      u32x4 raw[1];
+      const int base = at(l, Rg::q2) + (ah * 64 / QT * rp + am) * (QT * 2);
+      ex.wait<kLead>([&](int) { return base; }, [&](int) { return c8 / QT * rp * (QT * 2) + c8 % QT * 2; }, raw);
+      q = __builtin_bit_cast(half8_t, raw[0]);
     }
-    __syncthreads();
-    const int tm = tid >> 5, c = (tid & 31) * 2, pr = j + W * tm;   // two values of a pair's context each
-    if (tm < TEAMS && pr < rows * H) {
-      float mx = -INFINITY, z = 0.f, o0 = 0.f, o1 = 0.f;
-#pragma unroll
-      for (int w = 0; w < NSH; ++w) mx = fmaxf(mx, att_m[tm * NSH + w]);
-#pragma unroll
-      for (int w = 0; w < NSH; ++w) {
-        const float cw = __builtin_amdgcn_exp2f(att_m[tm * NSH + w] - mx);
-        z += att_l[tm * NSH + w] * cw;
-        o0 += att_o[tm * NSH + w][c] * cw;
-        o1 += att_o[tm * NSH + w][c + 1] * cw;
-      }
-      const float inv = 1.0f / z;
-      ex.put2(at(l, self ? Rg::ctx : Rg::ctx2), pr / H * (D * 2) + (pr % H * 64 + c) * 2, (half_t)(o0 * inv), (half_t)(o1 * inv));
+    Attention t;
+    auto live = [&](int jb) { return [&, jb](int u) { return jb + (gk + u * 8) * n < nkeys; }; };
+    const bool add = ash == n - 1 && gk == 0;   // the new position, counted once
+    const int span = kTripKeys * n;
+    if (nkeys <= span) {
+      t.first<self>(q, kn, vn, knew, vnew, add, nkeys == 0, live(ash), [] {});
+    } else {
+      t.first<self>(q, kn, vn, knew, vnew, add, false, live(ash), [&] { request(ash + span, std::false_type{}); });
+      for (int jb = ash + span; jb < nkeys; jb += span)   // the same trips in every lane of the wavefront
+        t.more(q, kn, vn, live(jb), [&] { if (jb + span < nkeys) request(jb + span, std::false_type{}); });
     }
+    t.sum();
+    const int base = at(l, self ? Rg::ctx : Rg::ctx2) + am * (D * 2) + ah * 128;
+    if (n == 1) {
+      const float inv = inverse(t.z);
+      if ((lane & 8) == 0) ex.put2(base, own_column(lane) * 2, (half_t)(t.acc[0] * inv), (half_t)(t.acc[1] * inv));
+      return;
+    }
+    shares.leave(wave, lane, t);
+    if (ash > 0) return shares.tell(wave, attentions);
+    const int c = (lane & 31) * 2;
+    float v0, v1;
+    shares.collect<NSH>(wave, n, attentions, lane, c, v0, v1);
+    if (lane < 32) ex.put2(base, c * 2, (half_t)v0, (half_t)v1);
   };
 
   // ---- a product whose input rows (N k-steps of 32 per wavefront) come straight from the exchange (row-major or units of
@@ -374,7 +326,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     // gains 2 %, d = 768 would lose 2 %.
     if constexpr (DK != 3) {
       asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(lane16), "+v"(lane_nt), "+v"(lane_qt));
-      asm volatile("" : "+v"(gk), "+v"(c8), "+v"(jfirst));
+      asm volatile("" : "+v"(gk), "+v"(c8));
     }
     renew();
     half_t* Kc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l) * now()->cache_stride);
@@ -425,7 +377,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     }
     // B, C. self-attention, its output projection
     renew();
-    attend(l, true, Kc, Vc, pos);
+    attend(l, std::true_type{}, Kc, Vc, pos, n_self);
     renew();
     project(wo, l, Rg::ctx, false, Rg::u1, layer_p(now()->bo, l), [&] {
       if constexpr (PRE) load_cols(w2, layer_w(now()->W2, l), 4 * D, NT);
@@ -454,7 +406,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       // E, F. cross-attention, its output projection
       const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
       renew();
-      attend(l, false, kvb, kvb + D, src_len);
+      attend(l, std::false_type{}, kvb, kvb + D, src_len, n_cross);
       project(we, l, Rg::ctx2, false, Rg::u2, layer_p(now()->boc, l), [&] { load_cols(w2, layer_w(now()->W2, l), 4 * D, NT); });
     }
     renew();
@@ -523,20 +475,22 @@ template <int DK, int MB, bool PRE>
 __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const StackArgs a) {
   constexpr int D = 256 * DK, H = D / 64, W = D / 16, R = 16 * MB, CG = D / 64;
   constexpr int TEAMS = R / 4, NSH = kWaves / TEAMS;
-  constexpr int U = 4;                              // keys of a lane group in flight
   constexpr int KS = 2 * DK;                        // k-steps of a quarter of k
   constexpr int CHX = MB * DK;                      // 16-byte pieces per thread of R rows of d halves
   constexpr int CHQ = (MB * DK + 3) / 4;            // ... of a quarter of them
   using Rg = RowsRegion<PRE>;
-  typedef half_t half2_t __attribute__((ext_vector_type(2)));
   typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-  __shared__ __attribute__((aligned(16))) half_t st[R][D + 8];             // staged input rows
-  __shared__ __attribute__((aligned(16))) float part[kWaves][4][R][16];
+  // staged input rows; sums over the wavefronts.  Between a product and the next, 8 KB of either are a wavefront's: its second trip of keys.
+  constexpr int kKeyBytes = 2 * kTrip * 1024, kStaged = R * (D + 8) * 2, kParts = kWaves * 4 * R * 16 * 4;
+  __shared__ __attribute__((aligned(16))) char st_room[kStaged > kWaves * kKeyBytes ? kStaged : kWaves * kKeyBytes];
+  __shared__ __attribute__((aligned(16))) char part_room[kParts > kWaves * kKeyBytes ? kParts : kWaves * kKeyBytes];
+  half_t (&st)[R][D + 8] = *reinterpret_cast<half_t (*)[R][D + 8]>(st_room);
+  float (&part)[kWaves][4][R][16] = *reinterpret_cast<float (*)[kWaves][4][R][16]>(part_room);
   __shared__ __attribute__((aligned(16))) half_t xrow[D];                  // the residual of the row this workgroup owns
   __shared__ float stat[DK][2];
-  __shared__ __attribute__((aligned(16))) float att_o[kWaves][64];
-  __shared__ float att_m[kWaves], att_l[kWaves];
+  __shared__ __attribute__((aligned(16))) Shares shares;
+  __shared__ unsigned first_key[kWaves][2][kTrip][8];   // of the first two trips, per lane group: places in the cache, the same in all layers
 
   int tid = threadIdx.x, lane = tid & 63;
   int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -565,6 +519,11 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     const u32x2 w = {publish_word(__builtin_bit_cast(unsigned, half2_t{h0, h1})), publish_word(__builtin_bit_cast(unsigned, half2_t{h2, h3}))};
     __builtin_amdgcn_raw_buffer_store_b64(w, ex.rsrc, lo, base, kAgent);
     __builtin_amdgcn_raw_buffer_store_b64(u32x2{kSentinel, kSentinel}, ex.rsrc, lo, base + other(l), kAgent);
+  };
+
+  auto put2h = [&](int l, int base, int lo, half_t h0, half_t h1) {
+    ex.put2(base, lo, h0, h1);
+    __builtin_amdgcn_raw_buffer_store_b32(kSentinel, ex.rsrc, lo, base + other(l), kAgent);
   };
 
   {   // the slot the last launch ended with: this group's part (needed from layer 1 on), and what no group of this launch has
@@ -750,137 +709,128 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     pin();
   };
 
-  // ---- attention (see decoder_stack_kernel)
+  // ---- attention (see decoder_stack_kernel).  A team has one wavefront or two, so from 33 or 65 positions on a wavefront makes several trips:
+  // 9900 of the 94 000 clocks of a layer of 128 rows at d = 1024 and 45 positions, 2400 where one trip is enough.
   const int team = wave / NSH, ash = wave % NSH;
   int gk = lane >> 3, c8 = (lane & 7) * 8;
   const int pair = j + W * team, am = min(pair / H, rows - 1), ah = pair % H;
-  const bool attends = pair < rows * H;
   const int arow = r0 + am, sent = arow / a.beam;
-  const int jstep = 8 * NSH;
-  int jfirst = ash + gk * NSH;
-  int slot0[U];
   const bool table = !PRE && a.anc != nullptr;
   const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
-  auto slot_of = [&](int p) { return table ? min(max(slots[p], 0), a.beam - 1) : 0; };
+  auto key_at = [&](int jb, int u, int n, int nkeys) { return max(min(jb + (gk + u * 8) * n, nkeys - 1), 0); };   // past the last key: that one again
+  auto key_offset = [&](int slot, int p) { return (unsigned)((min(max(slot, 0), a.beam - 1) * a.T + p) * D) * 2u; };
+  const bool attends = pair < rows * H;
+  const int n_self = attends ? team_for<NSH>(pos) : 0;
+  {
+    int s0[2][kTrip];
 #pragma unroll
-  for (int u = 0; u < U; ++u) slot0[u] = slot_of(max(min(jfirst + u * jstep, pos - 1), 0));
-  int src_off = 0, src_len = 0;
-  if constexpr (!PRE) { src_off = a.src_off[sent]; src_len = a.src_len[sent]; }
-  auto dot8 = [](const half8_t& x, const half8_t& y) {
-    float s = 0.f;
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_fdot2(half2_t{x[2 * i], x[2 * i + 1]}, half2_t{y[2 * i], y[2 * i + 1]}, s, false);
-    return s;
+      for (int u = 0; u < kTrip; ++u) s0[t][u] = table ? slots[key_at(ash + t * kTripKeys * n_self, u, n_self, pos)] : 0;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int u = 0; u < kTrip; ++u) first_key[wave][t][u][gk] = key_offset(s0[t][u], key_at(ash + t * kTripKeys * n_self, u, n_self, pos));
+  }
+  int src_off = 0, src_len = 0, n_cross = 0;
+  if constexpr (!PRE) {
+    src_off = a.src_off[sent]; src_len = a.src_len[sent];
+    n_cross = attends ? team_for<NSH>(src_len) : 0;
+  }
+  if (tid < kWaves) shares.left[tid] = 0;   // the first rows' barrier is ahead
+  int attentions = 0;
+  auto base_of = [&](bool self, const half_t* b) {
+    return reinterpret_cast<const char*>(b + (self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0) + ah * 64);
   };
-  half8_t kn[U], vn[U];
-  auto request_keys = [&](bool self, const half_t* Kb, const half_t* Vb, int nkeys, int jb) {
-    const size_t own = self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0;
-    const char* Kh = reinterpret_cast<const char*>(Kb + own + ah * 64);
-    const char* Vh = reinterpret_cast<const char*>(Vb + own + ah * 64);
+  half8_t kn[kTrip], vn[kTrip];
+  auto request_keys = [&](auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n) {   // the first trip, into registers
+    constexpr bool self = decltype(of_self)::value;
+    if (ash >= n) return;
+    const char *Kh = base_of(self, Kb), *Vh = base_of(self, Vb);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (u > 0 && jb - gk * NSH + u * jstep >= nkeys) continue;
-      const int p = max(min(jb + u * jstep, nkeys - 1), 0);
-      const unsigned o = ((self ? ((jb == jfirst ? slot0[u] : slot_of(p)) * a.T + p) * D : p * (2 * D)) + c8) * 2u;
+    for (int u = 0; u < kTrip; ++u) {
+      const unsigned o = (self ? first_key[wave][0][u][gk] : (unsigned)(key_at(ash, u, n, nkeys) * (2 * D)) * 2u) + c8 * 2;
       kn[u] = *reinterpret_cast<const half8_t*>(Kh + o);
       vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
     }
   };
-  // the first keys and values have been requested (request_keys from jfirst on) an exchange earlier
-  auto attend = [&](int l, bool self, const half_t* Kb, const half_t* Vb, int nkeys, const half_t* bias_q) {
-    if (attends) {
-      half8_t bq8 = {};
-      if (!self) bq8 = *reinterpret_cast<const half8_t*>(reinterpret_cast<const char*>(bias_q) + (unsigned)(ah * 64 + c8) * 2u);
-      pin();
-      constexpr float qscale = 0.125f * 1.44269504088896340736f;
-      half8_t q, knew, vnew;
-      if (self) {
-        u32x4 raw[3];
-        const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 32;
-        ex.wait<kLead + 6>([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
-        q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
-      } else {
-        u32x4 raw[8];   // four slabs of the head's 64 columns
-        const int base = at(l, Rg::qs) + (ah * rp + am) * 256;
-        ex.wait<kLead>([&](int i) { return base + (i >> 1) * (CG * 256) * rp; }, [&](int i) { return c8 * 4 + (i & 1) * 16; }, raw);
+  // The second trip and those behind it go straight into LDS, the second requested when the wavefront begins to wait for its query: a
+  // trip requested when the one before is multiplied came 3 us later, places in the cache first, and there are no registers to request it
+  // earlier (eight keys per lane group: 38 to 64 spilled, 128 rows 13 % slower).  Whole translations in ms with this and attention without
+  // branches and barriers: d = 1024, 32 sentences 27.6 -> 26.0; d = 512, 60 sentences 20.1 -> 19.2.  slot: of the trip after it.
+  int slot[kTrip];
+  auto keys_to_lds = [&](auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n, int jb, char* room, auto second) {
+    constexpr bool self = decltype(of_self)::value;
+    const char *Kh = base_of(self, Kb) + c8 * 2, *Vh = base_of(self, Vb) + c8 * 2;
+    char* mine = room + wave * kKeyBytes;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          float v = __builtin_bit_cast(floatx4, raw[i >> 2])[i & 3];
+    for (int u = 0; u < kTrip; ++u) {
+      const int p = key_at(jb, u, n, nkeys);
+      const unsigned o = !self ? (unsigned)(p * (2 * D)) * 2u : second ? first_key[wave][1][u][gk] : key_offset(slot[u], p);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Kh + o), (__attribute__((address_space(3))) void*)(mine + u * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Vh + o), (__attribute__((address_space(3))) void*)(mine + (kTrip + u) * 1024), 16, 0, 0);
+    }
+    if (self && table && jb + kTripKeys * n < nkeys) {
 #pragma unroll
-          for (int sl = 1; sl < 4; ++sl) v += __builtin_bit_cast(floatx4, raw[sl * 2 + (i >> 2)])[i & 3];
-          q[i] = (half_t)(v + (float)bq8[i]);
-        }
-      }
-      float m = -INFINITY, z = 0.f, acc[8];
+      for (int u = 0; u < kTrip; ++u) slot[u] = slots[key_at(jb + kTripKeys * n, u, n, nkeys)];
+    }
+  };
+  // the first keys and values have been requested (request_keys) an exchange earlier; room: of the keys behind them
+  auto attend = [&](int l, auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n, const half_t* bias_q, char* room) {
+    constexpr bool self = decltype(of_self)::value;
+    ++attentions;
+    if (ash >= n) return;
+    const int span = kTripKeys * n;
+    if (nkeys > span) keys_to_lds(of_self, Kb, Vb, nkeys, n, ash + span, room, std::true_type{});
+    half8_t bq8 = {};
+    if (!self) bq8 = *reinterpret_cast<const half8_t*>(reinterpret_cast<const char*>(bias_q) + (unsigned)(ah * 64 + c8) * 2u);
+    pin();
+    half8_t q, knew = {}, vnew = {};
+    if constexpr (self) {
+      u32x4 raw[3];
+      const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 32;
+      ex.wait<kLead + 6>([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
+      q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
+    } else {
+      u32x4 raw[8];   // four slabs of the head's 64 columns
+      const int base = at(l, Rg::qs) + (ah * rp + am) * 256;
+      ex.wait<kLead>([&](int i) { return base + (i >> 1) * (CG * 256) * rp; }, [&](int i) { return c8 * 4 + (i & 1) * 16; }, raw);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-      for (int jb = jfirst; jb - gk * NSH < nkeys; jb += U * jstep) {
-        float sc[U], mx = m;
-        half8_t vv[U];
+      for (int i = 0; i < 8; ++i) {
+        float v = __builtin_bit_cast(floatx4, raw[i >> 2])[i & 3];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          sc[u] = -INFINITY;
-          if (jb - gk * NSH + u * jstep >= nkeys) continue;
-          const float s = group_sum<8>(dot8(q, kn[u])) * qscale;
-          if (jb + u * jstep < nkeys) sc[u] = s;
-          vv[u] = vn[u];
-          mx = fmaxf(mx, sc[u]);
-        }
-        const int jn = jb + U * jstep;
-        if (jn - gk * NSH < nkeys) request_keys(self, Kb, Vb, nkeys, jn);
-        for_lane_bits<8>([&](auto bit) { mx = max_lane_xor<decltype(bit)::value>(mx); });
-        const float corr = __builtin_amdgcn_exp2f(m - mx);
-        m = mx;
-        z *= corr;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] *= corr;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (jb - gk * NSH + u * jstep >= nkeys) continue;
-          const bool live = jb + u * jstep < nkeys;
-          const float p = live ? __builtin_amdgcn_exp2f(sc[u] - mx) : 0.f;
-          z += p;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) acc[i] += p * (live ? (float)vv[u][i] : 0.f);
-        }
-      }
-      if (self && ash == NSH - 1) {
-        const float s = group_sum<8>(dot8(q, knew)) * qscale, mx = fmaxf(m, s);
-        const float corr = __builtin_amdgcn_exp2f(m - mx), p = gk == 0 ? __builtin_amdgcn_exp2f(s - mx) : 0.f;
-        m = mx;
-        z = z * corr + p;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = acc[i] * corr + p * (float)vnew[i];
-      }
-      for_lane_bits<8>([&](auto bit) {
-        constexpr int O = decltype(bit)::value;
-        z = add_lane_xor<O>(z);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = add_lane_xor<O>(acc[i]);
-      });
-      if (gk == 0) {
-        *reinterpret_cast<floatx4*>(&att_o[wave][c8]) = floatx4{acc[0], acc[1], acc[2], acc[3]};
-        *reinterpret_cast<floatx4*>(&att_o[wave][c8 + 4]) = floatx4{acc[4], acc[5], acc[6], acc[7]};
-        if (lane == 0) { att_m[wave] = m; att_l[wave] = z; }
+        for (int sl = 1; sl < 4; ++sl) v += __builtin_bit_cast(floatx4, raw[sl * 2 + (i >> 2)])[i & 3];
+        q[i] = (half_t)(v + (float)bq8[i]);
       }
     }
-    __syncthreads();
-    const int tm = tid >> 4, c = (tid & 15) * 4, pr = j + W * tm;   // four values of a pair's context each
-    if (tm < TEAMS && pr < rows * H) {
-      float mx = -INFINITY, z = 0.f;
-      floatx4 o = zero4;
+    Attention t;
+    auto live = [&](int jb) { return [&, jb](int u) { return jb + (gk + u * 8) * n < nkeys; }; };
+    t.first<self>(q, kn, vn, knew, vnew, ash == n - 1 && gk == 0, nkeys == 0, live(ash), [] {});
+    for (int jb = ash + span; jb < nkeys; jb += span) {   // the same trips in every lane of the wavefront
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const char* mine = room + wave * kKeyBytes + lane * 16;
 #pragma unroll
-      for (int w = 0; w < NSH; ++w) mx = fmaxf(mx, att_m[tm * NSH + w]);
-#pragma unroll
-      for (int w = 0; w < NSH; ++w) {
-        const float cw = __builtin_amdgcn_exp2f(att_m[tm * NSH + w] - mx);
-        z += att_l[tm * NSH + w] * cw;
-        o += *reinterpret_cast<const floatx4*>(&att_o[tm * NSH + w][c]) * cw;
+      for (int u = 0; u < kTrip; ++u) {
+        kn[u] = *reinterpret_cast<const half8_t*>(mine + u * 1024);
+        vn[u] = *reinterpret_cast<const half8_t*>(mine + (kTrip + u) * 1024);
       }
-      const float inv = 1.0f / z;
-      put4h(l, at(l, self ? Rg::ctx : Rg::ctx2), pr / H * (D * 2) + (pr % H * 64 + c) * 2, (half_t)(o[0] * inv), (half_t)(o[1] * inv),
-            (half_t)(o[2] * inv), (half_t)(o[3] * inv));
+      asm volatile("" : "+v"(kn[0]), "+v"(kn[1]), "+v"(kn[2]), "+v"(kn[3]), "+v"(vn[0]), "+v"(vn[1]), "+v"(vn[2]), "+v"(vn[3]) :: "memory");
+      if (jb + span < nkeys) keys_to_lds(of_self, Kb, Vb, nkeys, n, jb + span, room, std::false_type{});
+      t.more(q, kn, vn, live(jb), [] {});
     }
+    t.sum();
+    const int base = at(l, self ? Rg::ctx : Rg::ctx2) + am * (D * 2) + ah * 128;
+    if (NSH == 1 || n == 1) {
+      const float inv = inverse(t.z);
+      if ((lane & 8) == 0) put2h(l, base, own_column(lane) * 2, (half_t)(t.acc[0] * inv), (half_t)(t.acc[1] * inv));
+      return;
+    }
+    shares.leave(wave, lane, t);
+    if (ash > 0) return shares.tell(wave, attentions);
+    const int c = (lane & 31) * 2;
+    float v0, v1;
+    shares.collect<NSH>(wave, n, attentions, lane, c, v0, v1);
+    if (lane < 32) put2h(l, base, c * 2, (half_t)v0, (half_t)v1);
   };
 
   // What is derived from a workgroup's place is derived anew in every stage, and pointers are read where they are used, instead of
@@ -891,7 +841,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     asm volatile("" : "+s"(wave), "+s"(j), "+s"(cg), "+s"(ks), "+s"(grp), "+s"(rp), "+s"(r0), "+s"(rows), "+s"(pos), "+s"(start));
     if constexpr (DK == 4) {
       asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(lane16), "+v"(oc), "+v"(ui), "+v"(um), "+v"(un));
-      asm volatile("" : "+v"(gk), "+v"(c8), "+v"(jfirst));
+      asm volatile("" : "+v"(gk), "+v"(c8));
     }
   };
 
@@ -935,7 +885,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       half4_t qb = {};
       const bool qlive = ui < 3 && um < rows;
       if (qlive) qb = half4_at(layer_p(now()->bqkv, l), qcol);
-      if (attends) request_keys(true, Kc, Vc, pos, jfirst);   // needs nothing of this step
+      request_keys(std::true_type{}, Kc, Vc, pos, n_self);   // needs nothing of this step
       pin();
       u32x4 raw[CHX];
       stage_rows(raw, at(l, Rg::xi), D, 0);
@@ -956,7 +906,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       }
     }
     renew();
-    attend(l, true, Kc, Vc, pos, nullptr);
+    attend(l, std::true_type{}, Kc, Vc, pos, n_self, nullptr, st_room);
     renew();
     project_quarter(wo, l, Rg::ctx, Rg::os, [&] {
       if constexpr (PRE) load_units(w1, layer_w(now()->W1, l));
@@ -967,11 +917,11 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     } else {
       const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
       own_norm(l, Rg::os, layer_p(now()->bo, l), layer_p(now()->ln1g, l), layer_p(now()->ln1b, l), l, Rg::x1, nullptr, nullptr);
-      if (attends) request_keys(false, kvb, kvb + D, src_len, jfirst);
+      request_keys(std::false_type{}, kvb, kvb + D, src_len, n_cross);
       pin();
       project_quarter(wo, l, Rg::x1, Rg::qs, [&] { load_quarter(wo, layer_w(now()->Woc, l)); });
       renew();
-      attend(l, false, kvb, kvb + D, src_len, layer_p(now()->bq, l));
+      attend(l, std::false_type{}, kvb, kvb + D, src_len, n_cross, layer_p(now()->bq, l), part_room);
       project_quarter(wo, l, Rg::ctx2, Rg::cs, [&] { load_units(w1, layer_w(now()->W1, l)); });
       own_norm(l, Rg::cs, layer_p(now()->boc, l), layer_p(now()->ln2g, l), layer_p(now()->ln2b, l), l, Rg::x2, nullptr, nullptr);
     }
@@ -1111,13 +1061,23 @@ bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers)
 //              32 rows        219 / 184 / 318   297 / 319 / 404   383 / 465 / 469   523 / 702 / 538
 //              64 rows        -   / 210 / 344   -   / 378 / 514   -   / 550 / 623   -   / 828 / 732
 //             128 rows        -   / 272 / 383   -   / 606 / 693   -   / 945 / 899   -   / 1495 / 1173
-// 8-row groups / more rows, nearer: d = 512, 12 rows 132 / 131 at 104, 137 / 153 at 240; 32 rows 134 / 138, 149 / 174; 64 rows
-// 142 / 153, 175 / 200; one row per sentence (every row reads a history of its own in either) 16 rows 134 / 141 at 240, 32 rows
-// 149 / 150, 64 rows 169 / 172.  d = 1024, 8 rows 168 / 174 at 104; 16 rows 185 / 185, 191 / 199 at 160; 32 rows 252 / 245 at
-// 240, 274 / 278 at 352; one per sentence 8 rows 175 / 180 at 240, 16 rows 209 / 209 at 352, 32 rows 293 / 262 at 496.
+// Those of more rows are older than the second trip of keys through LDS (decoder_stack_rows_kernel), which a history needs from 33 or 65
+// positions on; with it, whole steps in us, 8-row groups / more rows, and separate launches where they come near, source of 30 tokens:
+//   positions                 20-60          60-120         120-200        200-320        320-440        440-560              940-1060
+//   d = 1024,   8 rows        143 / 155      156 / 164      155 / 165      166 / 180      181 / 196
+//              16 rows        156 / 163      153 / 169      165 / 173      180 / 190      190 / 208
+//              20 rows        172 / 170      182 / 175
+//              24 rows        180 / 172      187 / 185      208 / 188      218 / 201      247 / 225
+//              32 rows        188 / 180      198 / 181      205 / 192      228 / 210      257 / 228      272 / 251            340 / 322
+//             128 rows        -   / 257                                                                  -   / 540 / 667      -   / 828 / 859
+//   d = 768,   24 rows        203 / 217      211 / 220      224 / 241      243 / 251      278 / 286
+//              36 rows        206 / 224      219 / 233      232 / 251      252 / 269      291 / 317
+//              48 rows (96 workgroups of 8-row groups each would not fit)                                -   / 365 / 597      -   / 603 / 862
+// So 8-row groups have d = 1024 as long as one of them is enough; 9 to 16 rows from 112 positions on (nearer the line of 3 to 6 per cent is
+// left as it was: those translations are short); d = 768 as long as they fit the chip.
 // One row per sentence shares nothing, and only the widest case crosses: d = 1024, 128 rows 898 / 958 at 1008, 1418 / 1391 at
-// 1900; d = 768 pre-LN, 160 rows 2307 / 2493 at 1980.  A source key counts as a quarter or half of one of the history (position
-// 16, sources of 2000: d = 512, 128 rows 460 / 458, 256 rows 791 / 784; d = 1024, 32 rows 363 / 433, 128 rows 862 / 825).
+// 1900 (before the trip through LDS); d = 768 pre-LN, 160 rows 2307 / 2493 at 1980.  A source key counts as a quarter or half of one of the history
+// (position 16, sources of 2000: d = 512, 128 rows 460 / 458, 256 rows 791 / 784; d = 1024, 32 rows 363 / 433, 128 rows 862 / 825).
 StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool dies) {
   if (M < 1) return kStackNone;
   if (dies && die_supported(arch, M, d, beam, pos, src)) return kStackDie;
@@ -1130,9 +1090,9 @@ StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool di
   // 460 / 464 at 3900), more rows against them, 8-row groups against more rows
   if (beam > 1 && d > 512 && len > (c.x == 1 ? 2000 : 2700)) few = false;
   if (r.x == 1 && beam > 1 && len > 1300) many = false;
-  if (r.x == 2 && pos + src / 2 > (beam > 1 ? (d == 512 ? 1120 : d == 768 ? 960 : 830) : (d == 1024 ? 1600 : never))) many = false;
+  if (r.x == 2 && pos + src / 2 > (beam > 1 ? (d == 512 ? 1120 : d == 768 ? 960 : 1100) : (d == 1024 ? 1600 : never))) many = false;
   const int few_from = d == 768    ? (M <= 40 ? 0 : never)
-                       : d == 1024 ? (M <= 6 ? 0 : beam > 1 ? (M <= 16 ? 112 : 352) : M <= 16 ? 352 : never)
+                       : d == 1024 ? (M <= 8 ? 0 : M <= 16 ? (beam > 1 ? 112 : 352) : never)
                                    : (M <= 8 ? 0 : beam > 1 ? 112 : 240);
   if (few && (!many || len >= few_from)) return kStackFew;
   return many ? kStackMany : kStackNone;

@@ -26,7 +26,7 @@
 // the die it finds itself on, and workgroup b's place in it is b / 8.  die_placement() looks whether eight in a row are on different dies when a
 // model is loaded.  A launch in which they were not would lack a workgroup of some group, and end as any wait that runs out here does.
 // The exchange itself is that of kernels_stack.hip too: data that is its own flag.
-#include "stack_exchange.h"
+#include "stack_attend.h"
 
 namespace lsq {
 
@@ -37,8 +37,6 @@ constexpr int kDieGroup = 32;          // workgroups of a group: one per compute
 constexpr int kDies = 8;
 constexpr int kDieLead = 6;            // as kLead: layers of a step in us with 0 / 4 / 6 / 8 / 12: 4 rows 73.0 72.4 70.4 71.6 73.1, 32 rows 85.9 85.4 85.0
                                        // 84.7 85.3, 64 rows 92.9 89.9 90.6 91.3 92.7, 128 rows 109.7 106.7 105.9 106.0 108.5
-
-typedef half_t half2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ unsigned die_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)); }   // XCC_ID, 4 bits
 __global__ void die_of_workgroup_kernel(unsigned* out) {
@@ -51,34 +49,6 @@ __device__ __forceinline__ void workgroup_barrier() {   // LDS only: loads stay 
   asm volatile("" ::: "memory");
 }
 __device__ __forceinline__ void pin() { asm volatile("" ::: "memory"); }   // requests stay where they are written
-
-// error against 64 bits: that of a chain of float multiply-adds
-__device__ __forceinline__ float dot8(const half8_t& x, const half8_t& y) {
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_fdot2(half2_t{x[2 * i], x[2 * i + 1]}, half2_t{y[2 * i], y[2 * i + 1]}, s, false);
-  return s;
-}
-
-// Sums over the eight lane groups of values that belong to columns c8 .. c8 + 7 in each: a lane is left with two of them,
-// own_column() and the next, in v[0] and v[1] (14 instructions; all eight in every lane would be 72).
-__device__ __forceinline__ void column_sums(float (&v)[8]) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v[i]), __builtin_bit_cast(unsigned, v[i + 4]), false, false);
-    const unsigned x = r[0], y = r[1];
-    v[i] = __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v[i]), __builtin_bit_cast(unsigned, v[i + 2]), false, false);
-    const unsigned x = r[0], y = r[1];
-    v[i] = __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
-  }
-  v[0] = add_lane_xor<8>(v[0]);
-  v[1] = add_lane_xor<8>(v[1]);
-}
-__device__ __forceinline__ int own_column(int lane) { return (lane & 7) * 8 + (lane >> 4 & 1) * 2 + (lane >> 5) * 4; }   // of the head's 64
 
 // ---------------------------------------------------------------------------------------------
 // Few rows, d = 512: up to 16 a die.  Eight wavefronts hold the matrices in registers (an eighth of k each), ask for the next
@@ -93,7 +63,6 @@ template <int R, bool PRE>
 __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArgs a) {
   constexpr int DK = 2, D = 256 * DK, H = D / 64, W = kDieGroup, NT = D / W;
   constexpr int TEAMS = R * H / W, NSH = kWaves / TEAMS;         // wavefronts that share a (row, head) pair
-  constexpr int U = 4;                                           // keys of a lane group in flight
   using Rg = Region<PRE>;
   constexpr int ES = PRE ? 2 : 4;                                // bytes of a residual sum
   constexpr int VP = 16 / ES, NP = D / (64 * VP);                // values of a 16-byte piece, pieces of a row per lane
@@ -105,10 +74,9 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   __shared__ __attribute__((aligned(16))) half_t us[PRE ? R : 1][D + 8];   // pre-LN: the residual stream
   __shared__ __attribute__((aligned(16))) half_t st[R][4 * D + 8];         // contexts, FFN activations
   __shared__ __attribute__((aligned(16))) float part[kWaves][4][R][16];
-  __shared__ __attribute__((aligned(16))) float att_o[kWaves][64];
-  __shared__ float att_m[kWaves], att_l[kWaves];
-  __shared__ int arrived[kWaves], attended[kWaves];   // exchanges that a wavefront has seen the end of, attentions it has left its share of
-  __shared__ unsigned first_key[kWaves][U][64];
+  __shared__ __attribute__((aligned(16))) Shares shares;
+  __shared__ int arrived[kWaves];   // exchanges that a wavefront has seen the end of
+  __shared__ unsigned first_key[kWaves][kTrip][64];
   __shared__ __attribute__((aligned(16))) half_t vec[2][7][D];   // of a layer: gains and shifts, biases
 
   const int tid = threadIdx.x;
@@ -137,7 +105,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   ex.polls = seq < 0 ? 1 : kSpinLimit;
   const int layer_bytes = Rg::size * D * R;
   auto at = [&](int l, int region) { return __builtin_amdgcn_readfirstlane(grp * a.layers * layer_bytes + l * layer_bytes + region * D * R); };
-  if (tid < kWaves) { arrived[tid] = 0; attended[tid] = 0; }
+  if (tid < kWaves) { arrived[tid] = 0; shares.left[tid] = 0; }
   workgroup_barrier();
 
   if (wave < kWaves) {
@@ -315,7 +283,6 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     if (ui < units) bi = *reinterpret_cast<const half2_t*>(&vec[l & 1][6][(first + ui) * 16 + un]);
     if (units == 1) xr = *reinterpret_cast<const half2_t*>(PRE ? &us[um][j * 16 + un] : &xs[um][j * 16 + un]);
   };
-  typedef float floatx2 __attribute__((ext_vector_type(2)));
   auto total = [&](float& v0, float& v1) {   // + bias
     floatx2 p[kWaves];
 #pragma unroll
@@ -437,13 +404,12 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
       *reinterpret_cast<u32x4*>(&st[p / 2 % R][p / (2 * R) * 16 + (p & 1) * 8]) = raw[i];
     }
   };
-  // ---- attention of one (row, head) pair per team of NSH wavefronts, of which n have 32 keys or more to look at; a lane
-  // group of 8 holds a key's 64 values
+  // ---- attention of one (row, head) pair per team of NSH wavefronts, of which n have keys to look at (stack_attend.h)
   const int team = xw / NSH, ash = xw % NSH;
   int gk = lane >> 3, c8 = (lane & 7) * 8;
   const int pair = j + W * team, am = min(pair / H, rows - 1), ah = pair % H;
   const int arow = r0 + am, sent = arow / a.beam;
-  auto team_of = [&](int nkeys) { return pair < rows * H ? min(nkeys <= 32 ? 1 : nkeys <= 64 ? 2 : nkeys <= 128 ? 4 : 8, NSH) : 0; };
+  auto team_of = [&](int nkeys) { return pair < rows * H ? team_for<NSH>(nkeys) : 0; };
   int n_self = 0, n_cross = 0, src_off = 0, src_len = 0;
   const bool table = !PRE && a.anc != nullptr;
   const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
@@ -453,7 +419,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   auto look_up = [&] {
     n_self = team_of(pos);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {   // the first trip's places in the cache, the same in all layers
+    for (int u = 0; u < kTrip; ++u) {   // the first trip's places in the cache, the same in all layers
       const int p = max(min(ash + (gk + u * 8) * n_self, pos - 1), 0);
       first_key[xw][u][lane] = key_offset(slot_of(p), p);
     }
@@ -462,13 +428,13 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
       n_cross = team_of(src_len);
     }
   };
-  half8_t kn[U], vn[U];
+  half8_t kn[kTrip], vn[kTrip];
   auto request = [&](bool self, const half_t* Kb, const half_t* Vb, int nkeys, int n, int jb, auto first) {
     const size_t own = self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0;
     const char* Kh = reinterpret_cast<const char*>(Kb + own + ah * 64);
     const char* Vh = reinterpret_cast<const char*>(Vb + own + ah * 64);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {   // past the last key: that one again
+    for (int u = 0; u < kTrip; ++u) {   // past the last key: that one again
       unsigned o;
       if (self && first) {
         o = first_key[xw][u][lane];
@@ -480,14 +446,10 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
       vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
     }
   };
-  // One trip for up to 32 keys of a wavefront, as code without branches: the chain of instructions, not their number, is what
-  // counts for a wavefront that has its SIMD to itself.
   int attentions = 0;
   auto attend = [&](int l, auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n) {
     constexpr bool self = decltype(of_self)::value;
-    constexpr int region_out = self ? Rg::ctx : Rg::ctx2;
-    constexpr float qscale = 0.125f * 1.44269504088896340736f;   // scores in units of log 2
-    half8_t q, knew, vnew;
+    half8_t q, knew = {}, vnew = {};
     ++attentions;
     if (ash < n) {
       const int lo = (c8 >> 4) * R * 32 + (c8 & 8) * 2;
@@ -505,121 +467,30 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     }
     seen();
     if (ash >= n) return;
-    float m, z, acc[8];   // m: of the wavefront
-    if (nkeys <= U * 8 * n) {
-      float sc[U + 1], p[U + 1];
-#pragma unroll
-      for (int u = 0; u < U; ++u) sc[u] = dot8(q, kn[u]);
-      if constexpr (self) sc[U] = dot8(q, knew);
-#pragma unroll
-      for (int u = 0; u < U + self; ++u) sc[u] = group_sum<8>(sc[u]) * qscale;
-#pragma unroll
-      for (int u = 0; u < U; ++u) sc[u] = ash + (gk + u * 8) * n < nkeys ? sc[u] : -INFINITY;
-      m = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-      if constexpr (self) {   // the new position, counted once: by the team's last wavefront
-        sc[U] = ash == n - 1 && gk == 0 ? sc[U] : -INFINITY;
-        m = fmaxf(m, sc[U]);
-        if (nkeys == 0) {   // what the cache holds was never written
-#pragma unroll
-          for (int u = 0; u < U; ++u) vn[u] = half8_t{};
-        }
-      }
-      for_lane_bits<8>([&](auto bit) { m = max_lane_xor<decltype(bit)::value>(m); });   // finite: the wavefront has a key
-#pragma unroll
-      for (int u = 0; u < U + self; ++u) p[u] = __builtin_amdgcn_exp2f(sc[u] - m);   // 0 past the last key, which is there again
-      z = (p[0] + p[1]) + (p[2] + p[3]);
-      if constexpr (self) z += p[U];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        acc[i] = p[0] * (float)vn[0][i];
-#pragma unroll
-        for (int u = 1; u < U; ++u) acc[i] += p[u] * (float)vn[u][i];
-        if constexpr (self) acc[i] += p[U] * (float)vnew[i];
-      }
+    Attention t;
+    auto live = [&](int jb) { return [&, jb](int u) { return jb + (gk + u * 8) * n < nkeys; }; };
+    const bool add = ash == n - 1 && gk == 0;   // the new position, counted once
+    const int span = kTripKeys * n;
+    if (nkeys <= span) {
+      t.first<self>(q, kn, vn, knew, vnew, add, nkeys == 0, live(ash), [] {});
     } else {
-      m = -INFINITY; z = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-      for (int jb = ash; jb < nkeys; jb += U * 8 * n) {   // the same trips in every lane of the wavefront
-        float sc[U], mx = m;
-        half8_t vv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const float s = group_sum<8>(dot8(q, kn[u])) * qscale;
-          sc[u] = jb + (gk + u * 8) * n < nkeys ? s : -INFINITY;
-          vv[u] = vn[u];
-          mx = fmaxf(mx, sc[u]);
-        }
-        const int jn = jb + U * 8 * n;
-        if (jn < nkeys) request(self, Kb, Vb, nkeys, n, jn, std::false_type{});
-        for_lane_bits<8>([&](auto bit) { mx = max_lane_xor<decltype(bit)::value>(mx); });
-        const float corr = __builtin_amdgcn_exp2f(m - mx);   // mx is finite: the wavefront has a key in this trip
-        m = mx;
-        z *= corr;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] *= corr;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const float p = __builtin_amdgcn_exp2f(sc[u] - mx);
-          z += p;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) acc[i] += p * (float)vv[u][i];
-        }
-      }
-      if (self && ash == n - 1) {   // the new position
-        const float s = group_sum<8>(dot8(q, knew)) * qscale, mx = fmaxf(m, s);
-        const float corr = __builtin_amdgcn_exp2f(m - mx), p = gk == 0 ? __builtin_amdgcn_exp2f(s - mx) : 0.f;
-        m = mx;
-        z = z * corr + p;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = acc[i] * corr + p * (float)vnew[i];
-      }
+      t.first<self>(q, kn, vn, knew, vnew, add, false, live(ash), [&] { request(self, Kb, Vb, nkeys, n, ash + span, std::false_type{}); });
+      for (int jb = ash + span; jb < nkeys; jb += span)   // the same trips in every lane of the wavefront
+        t.more(q, kn, vn, live(jb), [&] { if (jb + span < nkeys) request(self, Kb, Vb, nkeys, n, jb + span, std::false_type{}); });
     }
-    column_sums(acc);
-    for_lane_bits<8>([&](auto bit) { z = add_lane_xor<decltype(bit)::value>(z); });
-    auto inverse = [](float v) {   // one Newton step; v is at least 1
-      const float r = __builtin_amdgcn_rcpf(v);
-      return fmaf(fmaf(-v, r, 1.0f), r, r);
-    };
+    t.sum();
+    const int base = at(l, self ? Rg::ctx : Rg::ctx2), lo = am * (D * 2) + ah * 128;
     if (n == 1) {
-      const float inv = inverse(z);
-      if ((lane & 8) == 0) ex.put2(at(l, region_out), am * (D * 2) + (ah * 64 + own_column(lane)) * 2, (half_t)(acc[0] * inv), (half_t)(acc[1] * inv));
+      const float inv = inverse(t.z);
+      if ((lane & 8) == 0) ex.put2(base, lo + own_column(lane) * 2, (half_t)(t.acc[0] * inv), (half_t)(t.acc[1] * inv));
       return;
     }
-    *reinterpret_cast<floatx2*>(&att_o[xw][own_column(lane)]) = floatx2{acc[0], acc[1]};
-    if (lane == 0) { att_m[xw] = m; att_l[xw] = z; }
-    if (ash > 0) {   // LDS takes a wavefront's stores in order
-      __hip_atomic_store(&attended[xw], attentions, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-      return;
-    }
-    // the team's first wavefront: two columns a lane, in both halves alike
-    while (!__all(__hip_atomic_load(&attended[xw + max(min(lane, n - 1), 1)], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= attentions)) {}
-    const int c = (lane & 31) * 2;
-    auto merge = [&](auto parts) {
-      constexpr int P = decltype(parts)::value;
-      if constexpr (P <= NSH) {
-        float pm[P], pl[P], mx = -INFINITY, zt = 0.f, o0 = 0.f, o1 = 0.f;
-        floatx2 po[P];
-#pragma unroll
-        for (int w = 0; w < P; ++w) { pm[w] = att_m[xw + w]; pl[w] = att_l[xw + w]; po[w] = *reinterpret_cast<const floatx2*>(&att_o[xw + w][c]); }
-#pragma unroll
-        for (int w = 0; w < P; ++w) asm volatile("" : "+v"(pm[w]), "+v"(pl[w]), "+v"(po[w]));
-#pragma unroll
-        for (int w = 0; w < P; ++w) mx = fmaxf(mx, pm[w]);
-#pragma unroll
-        for (int w = 0; w < P; ++w) {
-          const float cw = __builtin_amdgcn_exp2f(pm[w] - mx);
-          zt += pl[w] * cw;
-          o0 += po[w][0] * cw;
-          o1 += po[w][1] * cw;
-        }
-        const float inv = inverse(zt);
-        if (lane < 32) ex.put2(at(l, region_out), am * (D * 2) + (ah * 64 + c) * 2, (half_t)(o0 * inv), (half_t)(o1 * inv));
-      }
-    };
-    if (n == 2) merge(std::integral_constant<int, 2>{});
-    else if (n == 4) merge(std::integral_constant<int, 4>{});
-    else merge(std::integral_constant<int, 8>{});
+    shares.leave(xw, lane, t);
+    if (ash > 0) return shares.tell(xw, attentions);
+    const int c = (lane & 31) * 2;   // in both halves of the wavefront alike
+    float v0, v1;
+    shares.collect<NSH>(xw, n, attentions, lane, c, v0, v1);
+    if (lane < 32) ex.put2(base, lo + c * 2, (half_t)v0, (half_t)v1);
   };
 
   for (int l = 0; l < a.layers; ++l) {

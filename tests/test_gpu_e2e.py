@@ -527,6 +527,20 @@ def test_decoder_stack_past_its_first_trip_for_keys(lsq, d, batch, beam, dtype, 
         assert lsq.lsq_debug_stack_launches()[kernel] == steps
 
 
+@pytest.mark.parametrize("d,batch,beam,steps", [
+    (1024, 5, 4, 132),   # groups of 16 rows, two wavefronts a head: both from 33 keys on, through LDS from 65 and again from 129 on
+    (1024, 17, 4, 68),   # groups of 32 rows, one wavefront: 32 keys a trip
+    (768, 21, 5, 100),   # a fourth trip, whose places in the cache are looked up two trips ahead
+])
+def test_trips_of_keys_through_lds_match_oracle(lsq, d, batch, beam, steps):
+    """Groups of 16 and 32 rows at every length around the ends of their trips, sources of 1, 33 and 65 tokens among them."""
+    w, blob = _long_workload(d, d // 64, [1, 33] + [3 + (5 * i) % 7 for i in range(batch - 3)] + [65], beam, steps, 1)
+    with lsq.Engine(blob, batch, beam, w.max_len) as eng:
+        assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[0, 1, batch - 1])["steps"] == steps
+        assert lsq.lsq_debug_stack_launches()["groups_of_16_or_32"] == steps
+        assert lsq.lsq_debug_check_canaries() == 0
+
+
 def test_long_histories_leave_the_stack_kernel(lsq):
     """256 rows, d = 256, float32: from a history of 850 on (less half of the source) the separate launches are ahead and take
     over in the middle of a translation.  The same tokens as with the separate launches alone."""
