@@ -39,7 +39,7 @@ constexpr int kMinRows = 4;            // a writer's piece is at least as large 
 template <int DK, int X, bool PRE>
 __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs a) {
   constexpr int D = 256 * DK, H = D / 64, W = D / 16 * X, NT = 16 / X;
-  constexpr int NU = 4 / X, UQ = (3 + X - 1) / X;
+  constexpr int NU = 4 / X, UQ = X == 2 ? 3 : (3 + X - 1) / X;   // X = 2: three units of 8 columns of q, k, v
   constexpr int QT = NT < 8 ? 8 : NT;                          // query columns of the cross-attention per workgroup
   constexpr int TEAMS = X == 1 ? 2 : 1, NSH = kWaves / TEAMS;   // wavefronts that share a (row, head) pair
   using Rg = Region<PRE>;
@@ -70,13 +70,20 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   auto at = [&](int l, int region) { return (grp * row_bytes + (l * Rg::size + region) * D) * rp; };
 
   // ---- matrix fragments: lane (n = lane & 15, kc = lane >> 4) of a 32-wide k-step holds W[col + n][32 s + 8 kc ..]
-  int fm = lane & 7, kc = lane >> 4;
+  // The 16 x 16 products have room for twice the rows of a group: rows 0..7 of the one operand hold k-step 2 i, rows 8..15 k-step 2 i + 1 of the
+  // same rows, and of the columns' side the matrices that have only 8 columns here do the same (PAIR).  Of the product the
+  // quadrants in which both are the same k-step are what is wanted (fold): half the requests for exchanged values, which a wavefront
+  // waits for, and for those matrices; a CU takes 16 clocks for any request, whether its lanes ask for the same lines or not.  Whole translations
+  // in ms with this and the sums of sum_of: d = 1024, 4 rows 10.6 -> 10.1, 8 rows 14.2 -> 13.2; d = 768 pre-LN, 8 rows 10.2 -> 9.8, 32 rows 29.3 -> 28.8.
+  int fm = lane & 7, kc = lane >> 4, odd = lane >> 3 & 1;
+  constexpr bool PAIR = NT == 8, PAIRQ = QT == 8;
+  constexpr int DKP = (DK + 1) / 2;
   auto frag_lane = [&](int nt) { return (unsigned)(kc >> 1) * 1024 + ((lane & (nt - 1)) + 32 * (kc & 1)) * 16; };
   unsigned lane16 = frag_lane(16), lane_nt = frag_lane(NT), lane_qt = frag_lane(QT);
   auto frag_col = [&](const half_t* Wp, int K, int col) {   // its first k-step, in bytes
     return reinterpret_cast<const char*>(Wp) + (size_t)(col >> 5) * (K / 16) * 1024 + (col & 31) * 16;
   };
-  half8_t wq[UQ][DK], wo[DK], wc[PRE ? 1 : DK], we[PRE ? 1 : DK], w1[NU][DK], w2[4 * DK];
+  half8_t wq[UQ][PAIR ? DKP : DK], wo[PAIR ? DKP : DK], wc[PRE ? 1 : PAIRQ ? DKP : DK], we[PRE ? 1 : PAIR ? DKP : DK], w1[NU][DK], w2[PAIR ? 2 * DK : 4 * DK];
   auto load_units = [&](auto& w, const half_t* Wp, int total) {
     constexpr int N = sizeof(w) / sizeof(w[0]);
 #pragma unroll
@@ -86,12 +93,32 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       for (int s = 0; s < DK; ++s) w[i][s] = *reinterpret_cast<const half8_t*>(p + s * 2048 + lane16);
     }
   };
-  auto load_cols = [&](auto& w, const half_t* Wp, int K, int nt) {   // nt of d columns (the last ones again where there are none left)
-    constexpr int N = sizeof(w) / sizeof(w[0]);
-    const char* p = frag_col(Wp, K, min(j * nt, D - nt)) + wave * (N * 2048);
-    const unsigned lo = nt == QT ? lane_qt : lane_nt;
+  // `steps` k-steps of this wavefront; in pairs: of an odd number the last one again
+  auto load_steps = [&](auto& w, const char* p, unsigned lo, auto steps, auto paired) {
+    constexpr int N = decltype(steps)::value;
+    if constexpr (decltype(paired)::value) {
 #pragma unroll
-    for (int s = 0; s < N; ++s) w[s] = *reinterpret_cast<const half8_t*>(p + s * 2048 + lo);
+      for (int s = 0; s < (N + 1) / 2; ++s) w[s] = *reinterpret_cast<const half8_t*>(p + s * 4096 + (2 * s + 1 < N ? lo + odd * 2048 : lo));
+    } else {
+#pragma unroll
+      for (int s = 0; s < N; ++s) w[s] = *reinterpret_cast<const half8_t*>(p + s * 2048 + lo);
+    }
+  };
+  using k1 = std::integral_constant<int, DK>;
+  using k4 = std::integral_constant<int, 4 * DK>;
+  auto load_cols = [&](auto& w, const half_t* Wp, auto steps, auto columns) {   // columns of d (the last ones again where there are none left)
+    constexpr int S = decltype(steps)::value, C = decltype(columns)::value;
+    load_steps(w, frag_col(Wp, S * 256, min(j * C, D - C)) + wave * (S * 2048), C == QT ? lane_qt : lane_nt, steps, std::bool_constant<C == 8>{});
+  };
+  using cn = std::integral_constant<int, NT>;
+  using cq = std::integral_constant<int, QT>;
+  auto load_qkv = [&](auto& w, const half_t* Wp) {
+    if constexpr (PAIR) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) load_steps(w[i], frag_col(Wp, D, (j + W * i) * 8) + wave * (DK * 2048), lane_nt, k1{}, std::true_type{});
+    } else {
+      load_units(w, Wp, 3 * (D / 16));
+    }
   };
   // two biases, unconverted: a conversion here would wait for everything requested before them
   auto bias_pair = [](const half_t* b, unsigned col) { return *reinterpret_cast<const half2_t*>(reinterpret_cast<const char*>(b) + col * 2u); };
@@ -192,11 +219,50 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       for (int i = 0; i < N; ++i) *reinterpret_cast<floatx4*>(&part[wave][i][lane & 15][kc * 4]) = acc[i];
     }
   };
-  auto total_of = [&](int i, int m, int n, float& v0, float& v1) {   // columns n, n + 1, over the wavefronts in order
-    v0 = part[0][i][m][n]; v1 = part[0][i][m][n + 1];
+  // both halves of k of rows 0..7, in the lanes of the even one: a: of both, or of the even k-steps only, b: of the odd ones
+  auto fold = [&](const floatx4& a, const floatx4& b, auto paired) {
+    floatx4 v;
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) { v0 += part[w][i][m][n]; v1 += part[w][i][m][n + 1]; }
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (decltype(paired)::value) {
+        float lower, upper;
+        lane_pair<32>(a[i], lower, upper);
+        v[i] = lower + lane_xor<8>(upper);
+      } else {
+        v[i] = a[i] + lane_xor<8>(b[i]);
+      }
+    }
+    return v;
   };
+  auto multiply_pairs = [&](const auto& w) {   // input rows from xs, units of 8 columns
+    constexpr int N = sizeof(w) / sizeof(w[0]);
+    floatx4 acc[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = zero4;
+#pragma unroll
+    for (int s = 0; s < DKP; ++s) {
+      half8_t x8 = *reinterpret_cast<const half8_t*>(&xs[fm][(wave * DK + min(2 * s + odd, DK - 1)) * 32 + kc * 8]);
+      if (2 * s + 1 >= DK && odd) x8 = half8_t{};
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i][s], x8, acc[i], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const floatx4 v = fold(acc[i], acc[i], std::true_type{});
+      if ((lane & 15) < kRows && kc < 2) *reinterpret_cast<floatx4*>(&part[wave][i][lane & 15][kc * 4]) = v;
+    }
+  };
+  auto sum_of = [&](const float (&p)[kRows][16], int stride, int m, int n, float& v0, float& v1) {   // columns n, n + 1, over the wavefronts in order
+    floatx2 t[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) t[w] = *reinterpret_cast<const floatx2*>(&p[m][n] + w * stride);
+    // all of them requested before the first is added: left to itself the compiler takes a trip to LDS for each
+    asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "+v"(t[5]), "+v"(t[6]), "+v"(t[7]));
+    v0 = t[0][0]; v1 = t[0][1];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) { v0 += t[w][0]; v1 += t[w][1]; }
+  };
+  auto total_of = [&](int i, int m, int n, float& v0, float& v1) { sum_of(part[0][i], sizeof(part[0]) / 4, m, n, v0, v1); };
 
   // ---- attention of one (row, head) pair per team of NSH wavefronts (stack_attend.h)
   const int team = wave / NSH, ash = wave % NSH;
@@ -243,8 +309,9 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     half8_t q, knew = {}, vnew = {};
     if constexpr (self) {
       u32x4 raw[3];
-      const int base = at(l, Rg::qkv) + (ah * 4 * rp + am) * 32;
-      ex.wait<kLead>([&](int i) { return base + i * (D / 16 * 32) * rp; }, [&](int) { return (c8 >> 4) * rp * 32 + (c8 & 8) * 2; }, raw);
+      constexpr int UC = PAIR ? 8 : 16;   // columns of a unit
+      const int base = at(l, Rg::qkv) + (ah * (64 / UC) * rp + am) * (UC * 2);
+      ex.wait<kLead>([&](int i) { return base + i * (D * 2) * rp; }, [&](int) { return c8 / UC * rp * (UC * 2) + c8 % UC * 2; }, raw);
       q = __builtin_bit_cast(half8_t, raw[0]); knew = __builtin_bit_cast(half8_t, raw[1]); vnew = __builtin_bit_cast(half8_t, raw[2]);
     } else {
       u32x4 raw[1];
@@ -281,35 +348,43 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   // ---- a product whose input rows (N k-steps of 32 per wavefront) come straight from the exchange (row-major or units of
   // 16 columns), this workgroup's NT columns; then the residual: region_out <- x + (in . W + bias).  `request`: what is
   // wanted next.
-  auto project = [&](const auto& w, int l, int region_in, bool units, int region_out, const half_t* bias, auto request) {
-    constexpr int N = sizeof(w) / sizeof(w[0]);
+  auto project = [&](const auto& w, auto steps, int l, int region_in, bool units, int region_out, const half_t* bias, auto request) {
+    constexpr int N = decltype(steps)::value, NB = (N + 1) / 2;
     const int om = tid / (NT / 2), on = tid % (NT / 2) * 2;
     half2_t bi = {0, 0};
     if (om < rows) bi = bias_pair(bias, j * NT + on);
-    u32x4 raw[N];
+    u32x4 raw[NB];
     const int step = units ? 64 * rp : 64, base = at(l, region_in) + wave * N * step;
     const int lo = units ? ((kc >> 1) * rp + min(fm, rows - 1)) * 32 + (kc & 1) * 16 : min(fm, rows - 1) * (D * 2) + kc * 16;
-    ex.wait<kLead>([&](int i) { return base + i * step; }, [&](int) { return lo; }, raw);
+    const int lo2 = lo + odd * step;
+    ex.wait<kLead>([&](int i) { return base + 2 * i * step; }, [&](int i) { return 2 * i + 1 < N ? lo2 : lo; }, raw);
     floatx4 acc[2] = {zero4, zero4};
 #pragma unroll
-    for (int s = 0; s < N; ++s)
-      acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[s], __builtin_bit_cast(half8_t, raw[s]), acc[s & 1], 0, 0, 0);
-    if ((lane & 15) < kRows && kc * 4 < NT) *reinterpret_cast<floatx4*>(&part2[wave][lane & 15][kc * 4]) = acc[0] + acc[1];
+    for (int i = 0; i < NB; ++i) {
+      half8_t x8 = __builtin_bit_cast(half8_t, raw[i]);
+      if constexpr (PAIR) {
+        if (2 * i + 1 >= N && odd) x8 = half8_t{};
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i], x8, acc[0], 0, 0, 0);
+      } else {
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[2 * i], x8, acc[0], 0, 0, 0);
+        if (2 * i + 1 < N) acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[min(2 * i + 1, N - 1)], x8, acc[1], 0, 0, 0);
+      }
+    }
+    const floatx4 sum = fold(acc[0], acc[1], std::bool_constant<PAIR>{});
+    if ((lane & 15) < kRows && kc * 4 < NT) *reinterpret_cast<floatx4*>(&part2[wave][lane & 15][kc * 4]) = sum;
     request();
     pin();
+    half2_t x = {0, 0};
+    if (om < rows) x = *reinterpret_cast<const half2_t*>(PRE ? reinterpret_cast<const half_t*>(&us[om][j * NT + on]) : &xs[om][j * NT + on]);
     __syncthreads();
     if (om < rows) {
-      float v0 = part2[0][om][on], v1 = part2[0][om][on + 1];
-#pragma unroll
-      for (int q = 1; q < kWaves; ++q) { v0 += part2[q][om][on]; v1 += part2[q][om][on + 1]; }
+      float v0, v1;
+      sum_of(part2[0], kRows * 16, om, on, v0, v1);
       const int base_out = at(l, region_out) + j * rp * (NT * ES), o = om * (NT * ES) + on * ES;
       if constexpr (PRE) {
-        const half_t* x = &us[om][j * NT + on];
         ex.put2(base_out, o, (half_t)((float)x[0] + (v0 + (float)bi[0])), (half_t)((float)x[1] + (v1 + (float)bi[1])));
       } else {
-        const half_t* x = &xs[om][j * NT + on];
-        ex.put(base_out, o, (float)x[0] + (v0 + (float)bi[0]));
-        ex.put(base_out, o + 4, (float)x[1] + (v1 + (float)bi[1]));
+        ex.put2(base_out, o, (float)x[0] + (v0 + (float)bi[0]), (float)x[1] + (v1 + (float)bi[1]));
       }
     }
   };
@@ -320,12 +395,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   auto renew = [&] { asm volatile("" : "+s"(wave), "+s"(j), "+s"(grp), "+s"(r0), "+s"(rows), "+s"(pos)); };
 
   // ======== the layers.  Every matrix slice is requested at least one exchange before it is multiplied.
-  load_units(wq, layer_w(now()->Wqkv, 0), 3 * (D / 16));
+  load_qkv(wq, layer_w(now()->Wqkv, 0));
   for (int l = 0; l < a.layers; ++l) {
     // The same for a thread's place, once a layer: without it d = 1024 spills (32 rows 204 -> 174 us a step's layers); d = 512
     // gains 2 %, d = 768 would lose 2 %.
     if constexpr (DK != 3) {
-      asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(lane16), "+v"(lane_nt), "+v"(lane_qt));
+      asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(odd), "+v"(lane16), "+v"(lane_nt), "+v"(lane_qt));
       asm volatile("" : "+v"(gk), "+v"(c8));
     }
     renew();
@@ -335,8 +410,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     const int qi = tid >> 6, qm = (tid >> 3) & 7, qn = (tid & 7) * 2;   // unit, row, pair of columns this thread finishes
     const half_t* bq3 = layer_p(now()->bqkv, l);
     half2_t qb = {0, 0};
-    const int qcol = (j + W * qi) * 16 + qn;
-    const bool qlive = qi < UQ && qcol < 3 * D && qm < rows;
+    const int qu = PAIR ? 8 : 16, qcol = (j + W * qi) * qu + qn;   // columns of a unit
+    const bool qlive = qi < UQ && qn < qu && qcol < 3 * D && qm < rows;
     if (qlive) qb = bias_pair(bq3, qcol);
     if (l == 0) {
       if (wave < rows) {
@@ -359,17 +434,18 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       if constexpr (PRE) gather_norm(l - 1, Rg::u3, layer_p(now()->ln1g, l), layer_p(now()->ln1b, l), nullptr, nullptr);
       else gather_norm(l - 1, Rg::u3, layer_p(now()->ln3g, l - 1), layer_p(now()->ln3b, l - 1), nullptr, nullptr);
     }
-    multiply_units(wq);
-    load_cols(wo, layer_w(now()->Wo, l), D, NT);
+    if constexpr (PAIR) multiply_pairs(wq);
+    else multiply_units(wq);
+    load_cols(wo, layer_w(now()->Wo, l), k1{}, cn{});
     if constexpr (PRE) load_units(w1, layer_w(now()->W1, l), 4 * (D / 16));
-    else load_cols(wc, layer_w(now()->Wq, l), D, QT);
+    else load_cols(wc, layer_w(now()->Wq, l), k1{}, cq{});
     pin();
     __syncthreads();
     if (qlive) {
       float v0, v1;
       total_of(qi, qm, qn, v0, v1);
       const half_t h0 = (half_t)(v0 + (float)qb[0]), h1 = (half_t)(v1 + (float)qb[1]);
-      ex.put2(at(l, Rg::qkv) + j * rp * 32, (W * qi * rp + qm) * 32 + qn * 2, h0, h1);
+      ex.put2(at(l, Rg::qkv) + j * rp * (qu * 2), (W * qi * rp + qm) * (qu * 2) + qn * 2, h0, h1);
       if (qcol >= D) {
         char* cache = reinterpret_cast<char*>((qcol < 2 * D ? Kc : Vc) + ((size_t)r0 * a.T + pos) * D);
         *reinterpret_cast<half2_t*>(cache + (unsigned)(qm * a.T * D + (qcol < 2 * D ? qcol - D : qcol - 2 * D)) * 2u) = half2_t{h0, h1};
@@ -379,9 +455,9 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     renew();
     attend(l, std::true_type{}, Kc, Vc, pos, n_self);
     renew();
-    project(wo, l, Rg::ctx, false, Rg::u1, layer_p(now()->bo, l), [&] {
-      if constexpr (PRE) load_cols(w2, layer_w(now()->W2, l), 4 * D, NT);
-      else load_cols(we, layer_w(now()->Woc, l), D, NT);
+    project(wo, k1{}, l, Rg::ctx, false, Rg::u1, layer_p(now()->bo, l), [&] {
+      if constexpr (PRE) load_cols(w2, layer_w(now()->W2, l), k4{}, cn{});
+      else load_cols(we, layer_w(now()->Woc, l), k1{}, cn{});
     });
     if constexpr (!PRE) {
       // D. LayerNorm, query product of the cross-attention
@@ -390,11 +466,15 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       half2_t pb = {0, 0};
       if (plive) pb = bias_pair(layer_p(now()->bq, l), j * QT + pn);
       gather_norm(l, Rg::u1, layer_p(now()->ln1g, l), layer_p(now()->ln1b, l), nullptr, nullptr);
-      floatx4 acc = zero4;
+      if constexpr (PAIRQ) {
+        multiply_pairs(reinterpret_cast<const half8_t (&)[1][PRE ? 1 : DKP]>(wc));
+      } else {
+        floatx4 acc = zero4;
 #pragma unroll
-      for (int s = 0; s < DK; ++s)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wc[PRE ? 0 : s], *reinterpret_cast<const half8_t*>(&xs[fm][(wave * DK + s) * 32 + kc * 8]), acc, 0, 0, 0);
-      if ((lane & 15) < kRows) *reinterpret_cast<floatx4*>(&part[wave][0][lane & 15][kc * 4]) = acc;
+        for (int s = 0; s < DK; ++s)
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wc[PRE ? 0 : s], *reinterpret_cast<const half8_t*>(&xs[fm][(wave * DK + s) * 32 + kc * 8]), acc, 0, 0, 0);
+        if ((lane & 15) < kRows) *reinterpret_cast<floatx4*>(&part[wave][0][lane & 15][kc * 4]) = acc;
+      }
       load_units(w1, layer_w(now()->W1, l), 4 * (D / 16));
       pin();
       __syncthreads();
@@ -407,7 +487,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
       renew();
       attend(l, std::false_type{}, kvb, kvb + D, src_len, n_cross);
-      project(we, l, Rg::ctx2, false, Rg::u2, layer_p(now()->boc, l), [&] { load_cols(w2, layer_w(now()->W2, l), 4 * D, NT); });
+      project(we, k1{}, l, Rg::ctx2, false, Rg::u2, layer_p(now()->boc, l), [&] { load_cols(w2, layer_w(now()->W2, l), k4{}, cn{}); });
     }
     renew();
     // G. LayerNorm, first FFN product
@@ -426,8 +506,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       ex.put2(at(l, Rg::ff) + j * rp * 32, (W * qi * rp + qm) * 32 + qn * 2, (half_t)v0, (half_t)v1);
     }
     // H. second FFN product
-    project(w2, l, Rg::ff, true, Rg::u3, layer_p(now()->b2, l), [&] {
-      if (l + 1 < a.layers) load_units(wq, layer_w(now()->Wqkv, l + 1), 3 * (D / 16));
+    project(w2, k4{}, l, Rg::ff, true, Rg::u3, layer_p(now()->b2, l), [&] {
+      if (l + 1 < a.layers) load_qkv(wq, layer_w(now()->Wqkv, l + 1));
     });
   }
   // ======== the rows for the vocabulary product; everything else ends here

@@ -527,6 +527,18 @@ def test_decoder_stack_past_its_first_trip_for_keys(lsq, d, batch, beam, dtype, 
         assert lsq.lsq_debug_stack_launches()[kernel] == steps
 
 
+@pytest.mark.parametrize("d,batch,beam", [
+    (768, 1, 1), (768, 4, 4), (768, 2, 3),      # three k-steps a wavefront, eight columns a workgroup: the last pair is half empty
+    (768, 3, 7), (1024, 1, 8), (256, 2, 8),     # sixteen columns; four k-steps; one
+])
+def test_pairs_of_k_steps_match_oracle(lsq, d, batch, beam):
+    """Groups of 8 rows: two k-steps share a 16 x 16 product."""
+    w, blob = _long_workload(d, d // 64, [2 + (5 * i) % 7 for i in range(batch)], beam, 4, 1)
+    with lsq.Engine(blob, batch, beam, w.max_len) as eng:
+        assert lockstep(lsq, eng, blob, w, max_steps=4)["steps"] == 4
+        assert lsq.lsq_debug_stack_launches()["groups_of_8"] == 4
+
+
 @pytest.mark.parametrize("d,batch,beam,steps", [
     (1024, 5, 4, 132),   # groups of 16 rows, two wavefronts a head: both from 33 keys on, through LDS from 65 and again from 129 on
     (1024, 17, 4, 68),   # groups of 32 rows, one wavefront: 32 keys a trip
