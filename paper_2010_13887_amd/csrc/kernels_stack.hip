@@ -541,7 +541,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
 //     are read once and not by everybody;
 //   * products with d columns are split 4-fold over k (64 columns and a quarter of k per workgroup): each reads a quarter
 //     of the input rows and leaves a float slab; the query product's slabs are added by the attention that needs them;
-//   * input rows are staged in LDS by all threads.
+//   * a product with columns for every workgroup takes its input rows straight from the exchange, an eighth of k per wavefront; the split ones
+//     stage their quarter in LDS.
 // Exchange regions exist for two layers; a workgroup that publishes into layer l's resets what it wrote for layer l - 1
 // at the same place (consumed by then: it could not have got here otherwise) and has waited for the acknowledgement
 // before its next publication but one, on which everybody's way to layer l + 1 depends.  A launch starts with the slot
@@ -556,17 +557,19 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   constexpr int D = 256 * DK, H = D / 64, W = D / 16, R = 16 * MB, CG = D / 64;
   constexpr int TEAMS = R / 4, NSH = kWaves / TEAMS;
   constexpr int KS = 2 * DK;                        // k-steps of a quarter of k
-  constexpr int CHX = MB * DK;                      // 16-byte pieces per thread of R rows of d halves
-  constexpr int CHQ = (MB * DK + 3) / 4;            // ... of a quarter of them
+  constexpr int CHQ = (MB * DK + 3) / 4;            // 16-byte pieces per thread of a quarter of R rows of d halves
   using Rg = RowsRegion<PRE>;
   typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-  // staged input rows; sums over the wavefronts.  Between a product and the next, 8 KB of either are a wavefront's: its second trip of keys.
-  constexpr int kKeyBytes = 2 * kTrip * 1024, kStaged = R * (D + 8) * 2, kParts = kWaves * 4 * R * 16 * 4;
-  __shared__ __attribute__((aligned(16))) char st_room[kStaged > kWaves * kKeyBytes ? kStaged : kWaves * kKeyBytes];
-  __shared__ __attribute__((aligned(16))) char part_room[kParts > kWaves * kKeyBytes ? kParts : kWaves * kKeyBytes];
-  half_t (&st)[R][D + 8] = *reinterpret_cast<half_t (*)[R][D + 8]>(st_room);
-  float (&part)[kWaves][4][R][16] = *reinterpret_cast<float (*)[kWaves][4][R][16]>(part_room);
+  // Staged quarters of input rows, and the second FFN product's sums over the wavefronts; the other products' sums.  Between a product and the
+  // next, 8 KB of either are a wavefront's: its second trip of keys.
+  constexpr int kKeyBytes = 2 * kTrip * 1024, kParts = kWaves * 4 * R * 16 * 4, kRoom = kParts > kWaves * kKeyBytes ? kParts : kWaves * kKeyBytes;
+  using sums_t = float[kWaves][4][R][16];
+  __shared__ __attribute__((aligned(16))) char st_room[kRoom];
+  __shared__ __attribute__((aligned(16))) char part_room[kRoom];
+  half_t (&st)[R][D / 4 + 8] = *reinterpret_cast<half_t (*)[R][D / 4 + 8]>(st_room);
+  sums_t &part = *reinterpret_cast<sums_t*>(part_room), &part2 = *reinterpret_cast<sums_t*>(st_room);
+  static_assert(sizeof(st) <= kRoom && sizeof(sums_t) <= kRoom, "");
   __shared__ __attribute__((aligned(16))) half_t xrow[D];                  // the residual of the row this workgroup owns
   __shared__ float stat[DK][2];
   __shared__ __attribute__((aligned(16))) Shares shares;
@@ -708,43 +711,42 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     own_publish(v, g4, b4, l, region_out, out_y);
   };
 
-  // ---- staging: `pieces` of 16 bytes per thread; all of a workgroup's accesses so far are acknowledged on the way
-  auto stage_rows = [&](auto& raw, int base, int cols, int col0) {   // rows of d halves, `cols` columns from col0
-    constexpr int N = sizeof(raw) / sizeof(raw[0]);
+  // ---- a quarter of the input rows into LDS; all of a workgroup's accesses so far are acknowledged on the way
+  auto stage_quarter = [&](int base) {
+    u32x4 raw[CHQ];
     const int t = tid;
-    const int per_row = cols / 8;   // rows the group does not have: its last one again
-    auto row_of = [&](int p) { return min(p / per_row, rows - 1); };
-    ex.wait<kLead>([&](int) { return base + col0 * 2; },
-            [&](int i) { const int p = i * kThreads + t; return row_of(p) * (D * 2) + p % per_row * 16; }, raw);
+    constexpr int per_row = D / 32;   // rows the group does not have: its last one again
+    ex.wait<kLead>([&](int) { return base + ks * (D / 2); },
+            [&](int i) { const int p = i * kThreads + t; return min(p / per_row, rows - 1) * (D * 2) + p % per_row * 16; }, raw);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
+    for (int i = 0; i < CHQ; ++i) {
       const int p = i * kThreads + t;
       if (p < R * per_row) *reinterpret_cast<u32x4*>(&st[p / per_row][p % per_row * 8]) = raw[i];
     }
     __syncthreads();
   };
-  auto stage_units = [&](int base) {   // a quarter of the FFN activations: d columns in units of 16
-    u32x4 raw[CHX];
-    const int t = tid;
-    constexpr int per_unit = R * 2;
-    ex.wait<kLead + 6>([&](int) { return base; },
-            [&](int i) { const int p = i * kThreads + t; return p / per_unit * (rp * 32) + min(p % per_unit >> 1, rows - 1) * 32 + (p & 1) * 16; }, raw);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < CHX; ++i) {
-      const int p = i * kThreads + t;
-      *reinterpret_cast<u32x4*>(&st[p % per_unit >> 1][p / per_unit * 16 + (p & 1) * 8]) = raw[i];
-    }
-    __syncthreads();
-  };
 
-  // ---- products
+  // ---- products.  An eighth of k per wavefront, so nobody else needs what a wavefront reads of the input rows: straight from the exchange
+  // to the matrix cores (through LDS: two barriers and 128 KB of traffic more).  Whole translations in ms: d = 1024, 32 sentences
+  // 25.96 -> 25.30, 8 sentences 18.3 -> 17.2; d = 512, 60 sentences 19.5 -> 18.7; d = 768 pre-LN, 64 rows 15.65 -> 14.87.
+  // Accesses so far are acknowledged on the way, and the barrier between the sums and their readers is passed before anything that
+  // depends on them is published.
   const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  auto multiply_units = [&](const auto& w) {   // an eighth of the staged columns per wavefront
+  auto multiply_units = [&](const auto& w, auto lead, int base, auto units, sums_t& sums) {
     constexpr int N = sizeof(w) / sizeof(w[0]);
+    constexpr bool U = decltype(units)::value;   // rows in units of 16 columns; otherwise row by row
+    u32x4 raw[DK * MB];
+    int lo[MB];
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+      const int m = min(b * 16 + fm, rows - 1);
+      lo[b] = U ? ((kc >> 1) * rp + m) * 32 + (kc & 1) * 16 : m * (D * 2) + kc * 16;
+    }
+    const int step = U ? rp * 64 : 64, first = base + wave * DK * step;
+    ex.wait<decltype(lead)::value>([&](int i) { return first + i / MB * step; }, [&](int i) { return lo[i % MB]; }, raw);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     floatx4 acc[N][MB];
 #pragma unroll
     for (int i = 0; i < N; ++i)
@@ -753,27 +755,31 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
 #pragma unroll
     for (int s = 0; s < DK; ++s)
 #pragma unroll
-      for (int b = 0; b < MB; ++b) {
-        const half8_t x8 = *reinterpret_cast<const half8_t*>(&st[b * 16 + fm][(wave * DK + s) * 32 + kc * 8]);
+      for (int b = 0; b < MB; ++b)
 #pragma unroll
-        for (int i = 0; i < N; ++i) acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i][s], x8, acc[i][b], 0, 0, 0);
-      }
+        for (int i = 0; i < N; ++i)
+          acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i][s], __builtin_bit_cast(half8_t, raw[s * MB + b]), acc[i][b], 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < N; ++i)
 #pragma unroll
-      for (int b = 0; b < MB; ++b) *reinterpret_cast<floatx4*>(&part[wave][i][b * 16 + fm][kc * 4]) = acc[i][b];
+      for (int b = 0; b < MB; ++b) *reinterpret_cast<floatx4*>(&sums[wave][i][b * 16 + fm][kc * 4]) = acc[i][b];
   };
+  using lead_t = std::integral_constant<int, kLead>;
+  using late_t = std::integral_constant<int, kLead + 6>;
   // four columns of a unit and row per thread: unit tid / (4 R), row, columns
   int ui = tid / (4 * R), um = tid % (4 * R) / 4, un = tid % 4 * 4;
-  auto total4 = [&](int i) {
-    floatx4 v = *reinterpret_cast<const floatx4*>(&part[0][i][um][un]);
+  auto total4 = [&](const sums_t& sums, int i) {
+    floatx4 t[kWaves];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) v += *reinterpret_cast<const floatx4*>(&part[w][i][um][un]);
+    for (int w = 0; w < kWaves; ++w) t[w] = *reinterpret_cast<const floatx4*>(&sums[w][i][um][un]);
+    asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "+v"(t[5]), "+v"(t[6]), "+v"(t[7]));   // all requested before the first is added
+    floatx4 v = t[0];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) v += t[w];
     return v;
   };
   auto project_quarter = [&](const auto& w, int l, int region_in, int region_out, auto request) {   // ks-th quarter of k, 64 columns
-    u32x4 raw[CHQ];
-    stage_rows(raw, at(l, region_in), D / 4, ks * (D / 4));
+    stage_quarter(at(l, region_in));
     if (wave < 4 * MB) {
       floatx4 acc[2] = {zero4, zero4};
       const int b = wave >> 2;
@@ -967,14 +973,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       if (qlive) qb = half4_at(layer_p(now()->bqkv, l), qcol);
       request_keys(std::true_type{}, Kc, Vc, pos, n_self);   // needs nothing of this step
       pin();
-      u32x4 raw[CHX];
-      stage_rows(raw, at(l, Rg::xi), D, 0);
-      multiply_units(wq);
+      multiply_units(wq, lead_t{}, at(l, Rg::xi), std::false_type{}, part);
       load_quarter(wo, layer_w(now()->Wo, l));
       pin();
       __syncthreads();
       if (qlive) {
-        const floatx4 v = total4(ui);
+        const floatx4 v = total4(part, ui);
         half_t h[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) h[i] = (half_t)(v[i] + (float)qb[i]);
@@ -1012,14 +1016,12 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       const bool flive = ui < 4 && um < rows;
       half4_t fb = {};
       if (flive) fb = half4_at(layer_p(now()->b1, l), fcol);
-      u32x4 raw[CHX];
-      stage_rows(raw, at(l, PRE ? Rg::x1 : Rg::x2), D, 0);
-      multiply_units(w1);
+      multiply_units(w1, lead_t{}, at(l, PRE ? Rg::x1 : Rg::x2), std::false_type{}, part);
       load_ffn2(w2, layer_w(now()->W2, l));
       pin();
       __syncthreads();
       if (flive) {
-        const floatx4 v = total4(ui);
+        const floatx4 v = total4(part, ui);
         half_t h[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1029,14 +1031,13 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
         put4h(l, at(l, Rg::ff) + j * rp * 32, (W * ui * rp + um) * 32 + un * 2, h[0], h[1], h[2], h[3]);
       }
     }
-    // second FFN product
-    stage_units(at(l, Rg::ff) + ks * (D / 16) * rp * 32);
-    multiply_units(w2);
+    // Second FFN product.  The first one's sums may still be read by wavefronts whose activations nobody here waits for.
+    multiply_units(w2, late_t{}, at(l, Rg::ff) + ks * (D / 16) * rp * 32, std::true_type{}, part2);
     if (l + 1 < a.layers) load_units(wq, layer_w(now()->Wqkv, l + 1));
     pin();
     __syncthreads();
     if (ui < 4 && um < rows) {
-      const floatx4 v = total4(ui);
+      const floatx4 v = total4(part2, ui);
       put4(l, at(l, Rg::fs) + (ks * CG + cg) * rp * 256, um * 256 + (ui * 16 + un) * 4, v[0], v[1], v[2], v[3]);
     }
   }
@@ -1141,20 +1142,23 @@ bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers)
 //              32 rows        219 / 184 / 318   297 / 319 / 404   383 / 465 / 469   523 / 702 / 538
 //              64 rows        -   / 210 / 344   -   / 378 / 514   -   / 550 / 623   -   / 828 / 732
 //             128 rows        -   / 272 / 383   -   / 606 / 693   -   / 945 / 899   -   / 1495 / 1173
-// Those of more rows are older than the second trip of keys through LDS (decoder_stack_rows_kernel), which a history needs from 33 or 65
-// positions on; with it, whole steps in us, 8-row groups / more rows, and separate launches where they come near, source of 30 tokens:
-//   positions                 20-60          60-120         120-200        200-320        320-440        440-560              940-1060
-//   d = 1024,   8 rows        143 / 155      156 / 164      155 / 165      166 / 180      181 / 196
-//              16 rows        156 / 163      153 / 169      165 / 173      180 / 190      190 / 208
-//              20 rows        172 / 170      182 / 175
-//              24 rows        180 / 172      187 / 185      208 / 188      218 / 201      247 / 225
-//              32 rows        188 / 180      198 / 181      205 / 192      228 / 210      257 / 228      272 / 251            340 / 322
-//             128 rows        -   / 257                                                                  -   / 540 / 667      -   / 828 / 859
-//   d = 768,   24 rows        203 / 217      211 / 220      224 / 241      243 / 251      278 / 286
-//              36 rows        206 / 224      219 / 233      232 / 251      252 / 269      291 / 317
-//              48 rows (96 workgroups of 8-row groups each would not fit)                                -   / 365 / 597      -   / 603 / 862
-// So 8-row groups have d = 1024 as long as one of them is enough; 9 to 16 rows from 112 positions on (nearer the line of 3 to 6 per cent is
-// left as it was: those translations are short); d = 768 as long as they fit the chip.
+// All of that is older than the second trip of keys through LDS, which groups of 16 and 32 rows need from 33 or 65 positions on, the products that read
+// their rows straight from the exchange, and the pairs of k-steps of 8-row groups.  With them, whole steps in us, 8-row groups / more rows, sources of
+// 30 tokens:
+//   positions                 20-60          60-120         120-200        200-320        320-440
+//   d = 1024,   8 rows        135 / 141      146 / 149      144 / 151
+//              12 rows        136 / 147      143 / 152      152 / 160      159 / 169
+//              16 rows        144 / 151      145 / 152      157 / 163      168 / 174      183 / 195
+//              24 rows        180 / 172      187 / 185      208 / 188      218 / 201      247 / 225    (24 and 32 rows: the second trip only)
+//              32 rows        188 / 180      198 / 181      205 / 192      228 / 210      257 / 228
+//   d = 768,   16 rows        170 / 185      178 / 193      193 / 205      206 / 221
+//              24 rows        197 / 197      209 / 202      221 / 220      239 / 231
+//              32 rows        201 / 202      214 / 211      226 / 223      248 / 242      290 / 285
+//              40 rows        211 / 214      224 / 224      239 / 241      269 / 265      316 / 319
+// and, with the second trip only, more rows / separate launches at positions 440-560 and 940-1060: d = 1024, 128 rows 540 / 667, 828 / 859;
+// d = 768, 48 rows 365 / 597, 603 / 862.
+// So 8-row groups have d = 1024 as long as one of them is enough, and 9 to 16 rows from 112 positions on (nearer, where the difference is a few
+// microseconds a step, the line is the old one); d = 768 as long as they fit the chip, level from 24 rows on.
 // One row per sentence shares nothing, and only the widest case crosses: d = 1024, 128 rows 898 / 958 at 1008, 1418 / 1391 at
 // 1900 (before the trip through LDS); d = 768 pre-LN, 160 rows 2307 / 2493 at 1980.  A source key counts as a quarter or half of one of the history
 // (position 16, sources of 2000: d = 512, 128 rows 460 / 458, 256 rows 791 / 784; d = 1024, 32 rows 363 / 433, 128 rows 862 / 825).
