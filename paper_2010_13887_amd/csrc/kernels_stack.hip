@@ -219,6 +219,15 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       for (int i = 0; i < N; ++i) *reinterpret_cast<floatx4*>(&part[wave][i][lane & 15][kc * 4]) = acc[i];
     }
   };
+  auto other_half = [](const half8_t& v) {   // of lane ^ 8
+    u32x4 r = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned x = r[i];
+      r[i] = __builtin_bit_cast(unsigned, lane_xor<8>(__builtin_bit_cast(float, x)));
+    }
+    return __builtin_bit_cast(half8_t, r);
+  };
   // both halves of k of rows 0..7, in the lanes of the even one: a: of both, or of the even k-steps only, b: of the odd ones
   auto fold = [&](const floatx4& a, const floatx4& b, auto paired) {
     floatx4 v;
@@ -234,23 +243,21 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     }
     return v;
   };
-  auto multiply_pairs = [&](const auto& w) {   // input rows from xs, units of 8 columns
+  auto multiply_pairs = [&](const auto& w) {   // input rows from xs, units of 8 columns; k-step after k-step, as in multiply_units
     constexpr int N = sizeof(w) / sizeof(w[0]);
     floatx4 acc[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) acc[i] = zero4;
 #pragma unroll
-    for (int s = 0; s < DKP; ++s) {
-      half8_t x8 = *reinterpret_cast<const half8_t*>(&xs[fm][(wave * DK + min(2 * s + odd, DK - 1)) * 32 + kc * 8]);
-      if (2 * s + 1 >= DK && odd) x8 = half8_t{};
+    for (int s = 0; s < DK; ++s) {   // the odd ones' columns lie in lanes 8..15
+      const half8_t x8 = *reinterpret_cast<const half8_t*>(&xs[fm][(wave * DK + s) * 32 + kc * 8]);
 #pragma unroll
-      for (int i = 0; i < N; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i][s], x8, acc[i], 0, 0, 0);
+      for (int i = 0; i < N; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(s & 1 ? other_half(w[i][s / 2]) : w[i][s / 2], x8, acc[i], 0, 0, 0);
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const floatx4 v = fold(acc[i], acc[i], std::true_type{});
-      if ((lane & 15) < kRows && kc < 2) *reinterpret_cast<floatx4*>(&part[wave][i][lane & 15][kc * 4]) = v;
-    }
+    for (int i = 0; i < N; ++i)
+      if ((lane & 15) < kRows && kc < 2) *reinterpret_cast<floatx4*>(&part[wave][i][lane & 15][kc * 4]) = acc[i];
   };
   auto sum_of = [&](const float (&p)[kRows][16], int stride, int m, int n, float& v0, float& v1) {   // columns n, n + 1, over the wavefronts in order
     floatx2 t[kWaves];
@@ -264,7 +271,9 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   };
   auto total_of = [&](int i, int m, int n, float& v0, float& v1) { sum_of(part[0][i], sizeof(part[0]) / 4, m, n, v0, v1); };
 
-  // ---- attention of one (row, head) pair per team of NSH wavefronts (stack_attend.h)
+  // ---- attention of one (row, head) pair per team of NSH wavefronts (stack_attend.h).  All of them share the keys, however few there are:
+  // which has which is part of the order of the sums.  (As many as have 32 keys each: Transformer-big, 1 sentence 10.19 -> 10.01 ms, decoder-only,
+  // d = 768, 1 row 8.92 -> 8.75, and other tokens now and then.)
   const int team = wave / NSH, ash = wave % NSH;
   int gk = lane >> 3, c8 = (lane & 7) * 8;
   const int pair = j + W * team, am = min(pair / H, rows - 1), ah = pair % H;
@@ -274,37 +283,41 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   auto slot_of = [&](int p) { return table ? min(max(slots[p], 0), a.beam - 1) : 0; };   // of the sentence's rows
   auto key_offset = [&](int p) { return (unsigned)((slot_of(p) * a.T + p) * D + c8) * 2u; };
   const bool attends = pair < rows * H;
-  const int n_self = attends ? team_for<NSH>(pos) : 0;
   unsigned first_key[kTrip];   // the first trip's places in the cache, the same in all layers
 #pragma unroll
-  for (int u = 0; u < kTrip; ++u) first_key[u] = key_offset(max(min(ash + (gk + u * 8) * n_self, pos - 1), 0));
-  int src_off = 0, src_len = 0, n_cross = 0;
-  if constexpr (!PRE) {
-    src_off = a.src_off[sent]; src_len = a.src_len[sent];
-    n_cross = attends ? team_for<NSH>(src_len) : 0;
-  }
+  for (int u = 0; u < kTrip; ++u) first_key[u] = key_offset(max(min(ash + (gk + u * 8) * NSH, pos - 1), 0));
+  int src_off = 0, src_len = 0;
+  if constexpr (!PRE) { src_off = a.src_off[sent]; src_len = a.src_len[sent]; }
   if (tid < kWaves) shares.left[tid] = 0;   // the first rows' barrier is ahead
   int attentions = 0;
 
   // Wavefronts that have nothing to look at go on to wait for the context.
-  auto attend = [&](int l, auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n) {
+  auto attend = [&](int l, auto of_self, const half_t* Kb, const half_t* Vb, int nkeys) {
     constexpr bool self = decltype(of_self)::value;
     ++attentions;
-    if (ash >= n) return;
+    if (!attends) return;
     half8_t kn[kTrip], vn[kTrip];
     const size_t own = self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0;
     const char* Kh = reinterpret_cast<const char*>(Kb + own + ah * 64);
     const char* Vh = reinterpret_cast<const char*>(Vb + own + ah * 64);
-    auto request = [&](int jb, auto first) {   // past the last key: that one again
+    auto request = [&](int jb, auto first, auto keys) {   // past the last key: that one again
 #pragma unroll
-      for (int u = 0; u < kTrip; ++u) {
-        const int p = max(min(jb + (gk + u * 8) * n, nkeys - 1), 0);
+      for (int u = 0; u < decltype(keys)::value; ++u) {
+        const int p = max(min(jb + (gk + u * 8) * NSH, nkeys - 1), 0);
         const unsigned o = !self ? (unsigned)(p * (2 * D) + c8) * 2u : first ? first_key[u] : key_offset(p);
         kn[u] = *reinterpret_cast<const half8_t*>(Kh + o);
         vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
       }
     };
-    request(ash, std::true_type{});
+    // Eight wavefronts have 64 keys with one per lane group and 128 with two, and request no more: four each time cost 0.5 ms of 10.8 (Transformer-big,
+    // 1 sentence).  Four wavefronts (X = 1) have 32 and 64: three forms of the trip spill there, and gained nothing.
+    using c1 = std::integral_constant<int, 1>;
+    using c2 = std::integral_constant<int, 2>;
+    using c4 = std::integral_constant<int, kTrip>;
+    const bool one = NSH == 8 && nkeys <= 8 * NSH, two = NSH == 8 && nkeys <= 16 * NSH;
+    if (one) request(ash, std::true_type{}, c1{});
+    else if (two) request(ash, std::true_type{}, c2{});
+    else request(ash, std::true_type{}, c4{});
     pin();
     half8_t q, knew = {}, vnew = {};
     if constexpr (self) {
@@ -320,29 +333,24 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       q = __builtin_bit_cast(half8_t, raw[0]);
     }
     Attention t;
-    auto live = [&](int jb) { return [&, jb](int u) { return jb + (gk + u * 8) * n < nkeys; }; };
-    const bool add = ash == n - 1 && gk == 0;   // the new position, counted once
-    const int span = kTripKeys * n;
-    if (nkeys <= span) {
-      t.first<self>(q, kn, vn, knew, vnew, add, nkeys == 0, live(ash), [] {});
+    auto live = [&](int jb) { return [&, jb](int u) { return jb + (gk + u * 8) * NSH < nkeys; }; };
+    constexpr int span = kTripKeys * NSH;
+    if (one) {
+      t.first<self, 1>(q, kn, vn, knew, nkeys == 0, live(ash), [] {});
+    } else if (two) {
+      t.first<self, 2>(q, kn, vn, knew, false, live(ash), [] {});
     } else {
-      t.first<self>(q, kn, vn, knew, vnew, add, false, live(ash), [&] { request(ash + span, std::false_type{}); });
+      t.first<self>(q, kn, vn, knew, nkeys == 0, live(ash), [&] { if (nkeys > span) request(ash + span, std::false_type{}, c4{}); });
       for (int jb = ash + span; jb < nkeys; jb += span)   // the same trips in every lane of the wavefront
-        t.more(q, kn, vn, live(jb), [&] { if (jb + span < nkeys) request(jb + span, std::false_type{}); });
+        t.more(q, kn, vn, live(jb), [&] { if (jb + span < nkeys) request(jb + span, std::false_type{}, c4{}); });
     }
-    t.sum();
-    const int base = at(l, self ? Rg::ctx : Rg::ctx2) + am * (D * 2) + ah * 128;
-    if (n == 1) {
-      const float inv = inverse(t.z);
-      if ((lane & 8) == 0) ex.put2(base, own_column(lane) * 2, (half_t)(t.acc[0] * inv), (half_t)(t.acc[1] * inv));
-      return;
-    }
-    shares.leave(wave, lane, t);
+    if (self && ash == NSH - 1) t.add(vnew, gk == 0);
+    t.sum<false>();
+    shares.leave<false>(wave, lane, t);
     if (ash > 0) return shares.tell(wave, attentions);
     const int c = (lane & 31) * 2;
-    float v0, v1;
-    shares.collect<NSH>(wave, n, attentions, lane, c, v0, v1);
-    if (lane < 32) ex.put2(base, c * 2, (half_t)v0, (half_t)v1);
+    const half2_t v = shares.collect<NSH>(team * NSH, NSH, attentions, lane, c);
+    if (lane < 32) ex.put2(at(l, self ? Rg::ctx : Rg::ctx2) + am * (D * 2) + ah * 128, c * 2, v[0], v[1]);
   };
 
   // ---- a product whose input rows (N k-steps of 32 per wavefront) come straight from the exchange (row-major or units of
@@ -453,7 +461,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
     }
     // B, C. self-attention, its output projection
     renew();
-    attend(l, std::true_type{}, Kc, Vc, pos, n_self);
+    attend(l, std::true_type{}, Kc, Vc, pos);
     renew();
     project(wo, k1{}, l, Rg::ctx, false, Rg::u1, layer_p(now()->bo, l), [&] {
       if constexpr (PRE) load_cols(w2, layer_w(now()->W2, l), k4{}, cn{});
@@ -486,7 +494,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       // E, F. cross-attention, its output projection
       const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
       renew();
-      attend(l, std::false_type{}, kvb, kvb + D, src_len, n_cross);
+      attend(l, std::false_type{}, kvb, kvb + D, src_len);
       project(we, k1{}, l, Rg::ctx2, false, Rg::u2, layer_p(now()->boc, l), [&] { load_cols(w2, layer_w(now()->W2, l), k4{}, cn{}); });
     }
     renew();
@@ -803,39 +811,36 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   const int arow = r0 + am, sent = arow / a.beam;
   const bool table = !PRE && a.anc != nullptr;
   const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
-  auto key_at = [&](int jb, int u, int n, int nkeys) { return max(min(jb + (gk + u * 8) * n, nkeys - 1), 0); };   // past the last key: that one again
+  auto key_at = [&](int jb, int u, int nkeys) { return max(min(jb + (gk + u * 8) * NSH, nkeys - 1), 0); };   // past the last key: that one again
   auto key_offset = [&](int slot, int p) { return (unsigned)((min(max(slot, 0), a.beam - 1) * a.T + p) * D) * 2u; };
   const bool attends = pair < rows * H;
-  const int n_self = attends ? team_for<NSH>(pos) : 0;
+  constexpr int span = kTripKeys * NSH;
   {
     int s0[2][kTrip];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int u = 0; u < kTrip; ++u) s0[t][u] = table ? slots[key_at(ash + t * kTripKeys * n_self, u, n_self, pos)] : 0;
+      for (int u = 0; u < kTrip; ++u) s0[t][u] = table ? slots[key_at(ash + t * span, u, pos)] : 0;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int u = 0; u < kTrip; ++u) first_key[wave][t][u][gk] = key_offset(s0[t][u], key_at(ash + t * kTripKeys * n_self, u, n_self, pos));
+      for (int u = 0; u < kTrip; ++u) first_key[wave][t][u][gk] = key_offset(s0[t][u], key_at(ash + t * span, u, pos));
   }
-  int src_off = 0, src_len = 0, n_cross = 0;
-  if constexpr (!PRE) {
-    src_off = a.src_off[sent]; src_len = a.src_len[sent];
-    n_cross = attends ? team_for<NSH>(src_len) : 0;
-  }
+  int src_off = 0, src_len = 0;
+  if constexpr (!PRE) { src_off = a.src_off[sent]; src_len = a.src_len[sent]; }
   if (tid < kWaves) shares.left[tid] = 0;   // the first rows' barrier is ahead
   int attentions = 0;
   auto base_of = [&](bool self, const half_t* b) {
     return reinterpret_cast<const char*>(b + (self ? (size_t)(table ? sent * a.beam : arow) * a.T * D : 0) + ah * 64);
   };
   half8_t kn[kTrip], vn[kTrip];
-  auto request_keys = [&](auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n) {   // the first trip, into registers
+  auto request_keys = [&](auto of_self, const half_t* Kb, const half_t* Vb, int nkeys) {   // the first trip, into registers
     constexpr bool self = decltype(of_self)::value;
-    if (ash >= n) return;
+    if (!attends) return;
     const char *Kh = base_of(self, Kb), *Vh = base_of(self, Vb);
 #pragma unroll
     for (int u = 0; u < kTrip; ++u) {
-      const unsigned o = (self ? first_key[wave][0][u][gk] : (unsigned)(key_at(ash, u, n, nkeys) * (2 * D)) * 2u) + c8 * 2;
+      const unsigned o = (self ? first_key[wave][0][u][gk] : (unsigned)(key_at(ash, u, nkeys) * (2 * D)) * 2u) + c8 * 2;
       kn[u] = *reinterpret_cast<const half8_t*>(Kh + o);
       vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
     }
@@ -845,29 +850,28 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   // earlier (eight keys per lane group: 38 to 64 spilled, 128 rows 13 % slower).  Whole translations in ms with this and attention without
   // branches and barriers: d = 1024, 32 sentences 27.6 -> 26.0; d = 512, 60 sentences 20.1 -> 19.2.  slot: of the trip after it.
   int slot[kTrip];
-  auto keys_to_lds = [&](auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n, int jb, char* room, auto second) {
+  auto keys_to_lds = [&](auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int jb, char* room, auto second) {
     constexpr bool self = decltype(of_self)::value;
     const char *Kh = base_of(self, Kb) + c8 * 2, *Vh = base_of(self, Vb) + c8 * 2;
     char* mine = room + wave * kKeyBytes;
 #pragma unroll
     for (int u = 0; u < kTrip; ++u) {
-      const int p = key_at(jb, u, n, nkeys);
+      const int p = key_at(jb, u, nkeys);
       const unsigned o = !self ? (unsigned)(p * (2 * D)) * 2u : second ? first_key[wave][1][u][gk] : key_offset(slot[u], p);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Kh + o), (__attribute__((address_space(3))) void*)(mine + u * 1024), 16, 0, 0);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Vh + o), (__attribute__((address_space(3))) void*)(mine + (kTrip + u) * 1024), 16, 0, 0);
     }
-    if (self && table && jb + kTripKeys * n < nkeys) {
+    if (self && table && jb + span < nkeys) {
 #pragma unroll
-      for (int u = 0; u < kTrip; ++u) slot[u] = slots[key_at(jb + kTripKeys * n, u, n, nkeys)];
+      for (int u = 0; u < kTrip; ++u) slot[u] = slots[key_at(jb + span, u, nkeys)];
     }
   };
   // the first keys and values have been requested (request_keys) an exchange earlier; room: of the keys behind them
-  auto attend = [&](int l, auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int n, const half_t* bias_q, char* room) {
+  auto attend = [&](int l, auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, const half_t* bias_q, char* room) {
     constexpr bool self = decltype(of_self)::value;
     ++attentions;
-    if (ash >= n) return;
-    const int span = kTripKeys * n;
-    if (nkeys > span) keys_to_lds(of_self, Kb, Vb, nkeys, n, ash + span, room, std::true_type{});
+    if (!attends) return;
+    if (nkeys > span) keys_to_lds(of_self, Kb, Vb, nkeys, ash + span, room, std::true_type{});
     half8_t bq8 = {};
     if (!self) bq8 = *reinterpret_cast<const half8_t*>(reinterpret_cast<const char*>(bias_q) + (unsigned)(ah * 64 + c8) * 2u);
     pin();
@@ -890,8 +894,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       }
     }
     Attention t;
-    auto live = [&](int jb) { return [&, jb](int u) { return jb + (gk + u * 8) * n < nkeys; }; };
-    t.first<self>(q, kn, vn, knew, vnew, ash == n - 1 && gk == 0, nkeys == 0, live(ash), [] {});
+    auto live = [&](int jb) { return [&, jb](int u) { return jb + (gk + u * 8) * NSH < nkeys; }; };
+    t.first<self>(q, kn, vn, knew, nkeys == 0, live(ash), [] {});
     for (int jb = ash + span; jb < nkeys; jb += span) {   // the same trips in every lane of the wavefront
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const char* mine = room + wave * kKeyBytes + lane * 16;
@@ -901,22 +905,22 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
         vn[u] = *reinterpret_cast<const half8_t*>(mine + (kTrip + u) * 1024);
       }
       asm volatile("" : "+v"(kn[0]), "+v"(kn[1]), "+v"(kn[2]), "+v"(kn[3]), "+v"(vn[0]), "+v"(vn[1]), "+v"(vn[2]), "+v"(vn[3]) :: "memory");
-      if (jb + span < nkeys) keys_to_lds(of_self, Kb, Vb, nkeys, n, jb + span, room, std::false_type{});
+      if (jb + span < nkeys) keys_to_lds(of_self, Kb, Vb, nkeys, jb + span, room, std::false_type{});
       t.more(q, kn, vn, live(jb), [] {});
     }
-    t.sum();
+    if (self && ash == NSH - 1) t.add(vnew, gk == 0);
+    t.sum<false>();
     const int base = at(l, self ? Rg::ctx : Rg::ctx2) + am * (D * 2) + ah * 128;
-    if (NSH == 1 || n == 1) {
-      const float inv = inverse(t.z);
-      if ((lane & 8) == 0) put2h(l, base, own_column(lane) * 2, (half_t)(t.acc[0] * inv), (half_t)(t.acc[1] * inv));
-      return;
+    if constexpr (NSH == 1) {
+      const half2_t v = context_of(t.acc[0], t.acc[1], t.z);
+      if ((lane & 8) == 0) put2h(l, base, own_column<false>(lane) * 2, v[0], v[1]);
+    } else {
+      shares.leave<false>(wave, lane, t);
+      if (ash > 0) return shares.tell(wave, attentions);
+      const int c = (lane & 31) * 2;
+      const half2_t v = shares.collect<NSH>(team * NSH, NSH, attentions, lane, c);
+      if (lane < 32) put2h(l, base, c * 2, v[0], v[1]);
     }
-    shares.leave(wave, lane, t);
-    if (ash > 0) return shares.tell(wave, attentions);
-    const int c = (lane & 31) * 2;
-    float v0, v1;
-    shares.collect<NSH>(wave, n, attentions, lane, c, v0, v1);
-    if (lane < 32) put2h(l, base, c * 2, (half_t)v0, (half_t)v1);
   };
 
   // What is derived from a workgroup's place is derived anew in every stage, and pointers are read where they are used, instead of
@@ -971,7 +975,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       half4_t qb = {};
       const bool qlive = ui < 3 && um < rows;
       if (qlive) qb = half4_at(layer_p(now()->bqkv, l), qcol);
-      request_keys(std::true_type{}, Kc, Vc, pos, n_self);   // needs nothing of this step
+      request_keys(std::true_type{}, Kc, Vc, pos);   // needs nothing of this step
       pin();
       multiply_units(wq, lead_t{}, at(l, Rg::xi), std::false_type{}, part);
       load_quarter(wo, layer_w(now()->Wo, l));
@@ -990,7 +994,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
       }
     }
     renew();
-    attend(l, std::true_type{}, Kc, Vc, pos, n_self, nullptr, st_room);
+    attend(l, std::true_type{}, Kc, Vc, pos, nullptr, st_room);
     renew();
     project_quarter(wo, l, Rg::ctx, Rg::os, [&] {
       if constexpr (PRE) load_units(w1, layer_w(now()->W1, l));
@@ -1001,11 +1005,11 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
     } else {
       const half_t* kvb = reinterpret_cast<const half_t*>(global(now()->cross) + (size_t)l * now()->cross_stride) + (size_t)src_off * 2 * D;
       own_norm(l, Rg::os, layer_p(now()->bo, l), layer_p(now()->ln1g, l), layer_p(now()->ln1b, l), l, Rg::x1, nullptr, nullptr);
-      request_keys(std::false_type{}, kvb, kvb + D, src_len, n_cross);
+      request_keys(std::false_type{}, kvb, kvb + D, src_len);
       pin();
       project_quarter(wo, l, Rg::x1, Rg::qs, [&] { load_quarter(wo, layer_w(now()->Woc, l)); });
       renew();
-      attend(l, std::false_type{}, kvb, kvb + D, src_len, n_cross, layer_p(now()->bq, l), part_room);
+      attend(l, std::false_type{}, kvb, kvb + D, src_len, layer_p(now()->bq, l), part_room);
       project_quarter(wo, l, Rg::ctx2, Rg::cs, [&] { load_units(w1, layer_w(now()->W1, l)); });
       own_norm(l, Rg::cs, layer_p(now()->boc, l), layer_p(now()->ln2g, l), layer_p(now()->ln2b, l), l, Rg::x2, nullptr, nullptr);
     }

@@ -469,28 +469,27 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     if (ash >= n) return;
     Attention t;
     auto live = [&](int jb) { return [&, jb](int u) { return jb + (gk + u * 8) * n < nkeys; }; };
-    const bool add = ash == n - 1 && gk == 0;   // the new position, counted once
     const int span = kTripKeys * n;
     if (nkeys <= span) {
-      t.first<self>(q, kn, vn, knew, vnew, add, nkeys == 0, live(ash), [] {});
+      t.first<self>(q, kn, vn, knew, nkeys == 0, live(ash), [] {});
     } else {
-      t.first<self>(q, kn, vn, knew, vnew, add, false, live(ash), [&] { request(self, Kb, Vb, nkeys, n, ash + span, std::false_type{}); });
+      t.first<self>(q, kn, vn, knew, false, live(ash), [&] { request(self, Kb, Vb, nkeys, n, ash + span, std::false_type{}); });
       for (int jb = ash + span; jb < nkeys; jb += span)   // the same trips in every lane of the wavefront
         t.more(q, kn, vn, live(jb), [&] { if (jb + span < nkeys) request(self, Kb, Vb, nkeys, n, jb + span, std::false_type{}); });
     }
-    t.sum();
+    if (self && ash == n - 1) t.add(vnew, gk == 0);
+    t.sum<true>();
     const int base = at(l, self ? Rg::ctx : Rg::ctx2), lo = am * (D * 2) + ah * 128;
     if (n == 1) {
-      const float inv = inverse(t.z);
-      if ((lane & 8) == 0) ex.put2(base, lo + own_column(lane) * 2, (half_t)(t.acc[0] * inv), (half_t)(t.acc[1] * inv));
+      const half2_t v = context_of(t.acc[0], t.acc[1], t.z);
+      if ((lane & 8) == 0) ex.put2(base, lo + own_column<true>(lane) * 2, v[0], v[1]);
       return;
     }
-    shares.leave(xw, lane, t);
+    shares.leave<true>(xw, lane, t);
     if (ash > 0) return shares.tell(xw, attentions);
     const int c = (lane & 31) * 2;   // in both halves of the wavefront alike
-    float v0, v1;
-    shares.collect<NSH>(xw, n, attentions, lane, c, v0, v1);
-    if (lane < 32) ex.put2(base, lo + c * 2, (half_t)v0, (half_t)v1);
+    const half2_t v = shares.collect<NSH>(team * NSH, n, attentions, lane, c);
+    if (lane < 32) ex.put2(base, lo + c * 2, v[0], v[1]);
   };
 
   for (int l = 0; l < a.layers; ++l) {

@@ -61,3 +61,34 @@ def test_values_published_on_a_die_leave_the_compute_unit(tmp_path):
         assert stores and all(" sc" in i for i in stores), (k, stores)
         polls = [i for i in found[k] if i.startswith("buffer_load")]
         assert all("sc1" in i for i in polls), (k, polls)
+
+
+ATTEND = """
+#include "stack_attend.h"
+using namespace lsq;
+extern "C" __global__ void attend(const half8_t* kv, half_t* out, int n) {
+  const int lane = threadIdx.x;
+  half8_t kn[kTrip], vn[kTrip];
+  for (int u = 0; u < kTrip; ++u) { kn[u] = kv[u * 64 + lane]; vn[u] = kv[(kTrip + u) * 64 + lane]; }
+  Attention t;
+  auto live = [&](int u) { return u * 8 + (lane >> 3) < n; };
+  t.first<true>(kv[1000 + lane], kn, vn, kv[2000 + lane], n == 0, live, [] {});
+  t.more(kv[1000 + lane], vn, kn, live, [] {});
+  t.add(kv[3000 + lane], lane < 8);
+  t.sum<false>();
+  *reinterpret_cast<half2_t*>(out + own_column<false>(lane)) = context_of(t.acc[0], t.acc[1], t.z);
+}
+"""
+
+
+def test_attention_of_the_stack_kernels_is_one_arithmetic_whatever_the_compiler_likes(tmp_path):
+    """Its last bit decides draws: the same multiply-adds with and without contraction, a context divided by the sum of its weights
+    with a division, and rounded to float16 after the product."""
+    counts = {}
+    for contract in ("off", "fast"):
+        ops = _instructions(tmp_path, ATTEND, f"-ffp-contract={contract}")["attend"]
+        kinds = {"fma": r"v_(fma|fmac|fma_mix)_f32", "mul": r"v_mul_f32", "add": r"v_(add|sub|subrev)_f32", "exp": r"v_exp_f32", "div": r"v_div_fixup_f32"}
+        counts[contract] = {k: sum(n for i, n in ops.items() if re.match(p, i)) for k, p in kinds.items()}
+        assert not [i for i in ops if i.startswith("v_fma_mix") and "f16" in i], ops
+    assert counts["off"] == counts["fast"], counts
+    assert counts["fast"]["div"] == 1 and counts["fast"]["exp"] == 4 + 5 + 2, counts
