@@ -848,8 +848,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   // The second trip and those behind it go straight into LDS, the second requested when the wavefront begins to wait for its query: a
   // trip requested when the one before is multiplied came 3 us later, places in the cache first, and there are no registers to request it
   // earlier (eight keys per lane group: 38 to 64 spilled, 128 rows 13 % slower).  Whole translations in ms with this and attention without
-  // branches and barriers: d = 1024, 32 sentences 27.6 -> 26.0; d = 512, 60 sentences 20.1 -> 19.2.  slot: of the trip after it.
-  int slot[kTrip];
+  // branches and barriers: d = 1024, 32 sentences 27.6 -> 26.0; d = 512, 60 sentences 20.1 -> 19.2.  slot: of the trip after it; 0 without a table, where a row's history is its own.
+  int slot[kTrip] = {};
   auto keys_to_lds = [&](auto of_self, const half_t* Kb, const half_t* Vb, int nkeys, int jb, char* room, auto second) {
     constexpr bool self = decltype(of_self)::value;
     const char *Kh = base_of(self, Kb) + c8 * 2, *Vh = base_of(self, Vb) + c8 * 2;

@@ -553,6 +553,26 @@ def test_trips_of_keys_through_lds_match_oracle(lsq, d, batch, beam, steps):
         assert lsq.lsq_debug_check_canaries() == 0
 
 
+@pytest.mark.parametrize("d,batch,beam,steps", [(1024, 17, 4, 100), (1024, 5, 4, 132), (768, 21, 5, 132)])
+def test_trips_of_keys_through_lds_without_a_slab_table(lsq, d, batch, beam, steps):
+    """The third trip and those behind it in groups of 32 and 16 rows when cache rows move with the beams: every row reads its own
+    history.  In lock-step with the oracle, and the same bits as with the table."""
+    w, blob = _long_workload(d, d // 64, [5, 9] + [3 + (5 * i) % 7 for i in range(batch - 3)] + [65], beam, steps, 1)
+    out = {}
+    try:
+        for mode in (lsq.REFRESH_TABLE, lsq.REFRESH_MOVE):
+            lsq.lsq_set_cache_refresh(mode)
+            with lsq.Engine(blob, batch, beam, w.max_len) as eng:
+                out[mode] = eng.translate(w.src_ids, w.src_lens, sync_every=64)
+                assert lsq.lsq_debug_stack_launches()["groups_of_16_or_32"] > steps // 2
+                if mode == lsq.REFRESH_MOVE:
+                    assert lockstep(lsq, eng, blob, w, max_steps=steps, sentences=[0, batch - 1])["steps"] == steps
+                    assert lsq.lsq_debug_check_canaries() == 0
+    finally:
+        lsq.lsq_set_cache_refresh(lsq.REFRESH_TABLE)
+    assert all(np.array_equal(a, b) for a, b in zip(out[lsq.REFRESH_TABLE], out[lsq.REFRESH_MOVE]))
+
+
 def test_long_histories_leave_the_stack_kernel(lsq):
     """256 rows, d = 256, float32: from a history of 850 on (less half of the source) the separate launches are ahead and take
     over in the middle of a translation.  The same tokens as with the separate launches alone."""
