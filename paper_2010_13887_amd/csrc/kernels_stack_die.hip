@@ -24,8 +24,11 @@
 // Workgroups are dealt to the dies in turn, eight after one another to eight different ones, but which die is first is another one
 // for another stream, and changes for a stream when the process opens others (seen: 0 1 2 .. 7, then 7 0 1 .., then 5 6 7 ..).  So a group is
 // the die it finds itself on, and workgroup b's place in it is b / 8.  die_placement() looks whether eight in a row are on different dies when a
-// model is loaded.  A launch in which they were not would lack a workgroup of some group, and end as any wait that runs out here does.
+// model is loaded.  A launch in which they are not lacks a workgroup of some group.  The others of that group find out when a wait for it
+// runs out, half a second later; of a group that lacks them all, the last workgroup of the launch (die_count.h).  Either ends as any wait that runs
+// out here does.
 // The exchange itself is that of kernels_stack.hip too: data that is its own flag.
+#include "die_count.h"
 #include "stack_attend.h"
 
 namespace lsq {
@@ -33,8 +36,6 @@ namespace lsq {
 namespace {
 
 constexpr int kDieThreads = 1024;      // eight wavefronts that multiply, eight that exchange
-constexpr int kDieGroup = 32;          // workgroups of a group: one per compute unit of a die
-constexpr int kDies = 8;
 constexpr int kDieLead = 6;            // as kLead: layers of a step in us with 0 / 4 / 6 / 8 / 12: 4 rows 73.0 72.4 70.4 71.6 73.1, 32 rows 85.9 85.4 85.0
                                        // 84.7 85.3, 64 rows 92.9 89.9 90.6 91.3 92.7, 128 rows 109.7 106.7 105.9 106.0 108.5
 
@@ -79,18 +80,24 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   __shared__ unsigned first_key[kWaves][kTrip][64];
   __shared__ __attribute__((aligned(16))) half_t vec[2][7][D];   // of a layer: gains and shifts, biases
 
+  __shared__ uint64_t word;
+
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.groups, grp = die_id();
   int j = blockIdx.x >> 3;
   const int seq = a.state[0], parity = seq & 1;
+  if (tid == 0) word = die_word(grp, j);
   // the last workgroup of the launch to get here: all have read the counters
   auto leave = [&] {
-    const int n = __hip_atomic_fetch_add(a.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (n == kDies * W - 1) {
-      a.state[4] = 0;
-      a.state[1 + parity] = G * R;
-      __hip_atomic_fetch_xor(a.state, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int32_t* const state = now()->state;
+    uint64_t* const count = reinterpret_cast<uint64_t*>(state + 6);
+    const uint64_t n = __hip_atomic_fetch_add(count, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (die_launch_ends(n)) {
+      *count = 0;
+      state[1 + parity] = now()->groups * R;
+      __hip_atomic_fetch_xor(state, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!die_groups_there(n + word, now()->groups)) give_up(state, now()->error);
     }
   };
   if (grp >= G) {

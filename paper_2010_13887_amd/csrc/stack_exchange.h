@@ -34,6 +34,11 @@ __device__ __forceinline__ const __attribute__((address_space(4))) StackArgs* no
 // behind the one that gave up end at once instead of each waiting out the limit.
 constexpr int kGaveUp = (int)0x80000000u;
 
+__device__ __forceinline__ void give_up(int32_t* state, int* error) {   // tells the launches behind this one, and the host
+  __hip_atomic_fetch_or(state, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Byte offsets of a row's intermediates inside one layer's region (d: row width): kernels in which every workgroup normalises
 template <bool PRE> struct Region {
   static constexpr int qkv = 0, ctx = 6, u1 = 8;
@@ -69,11 +74,9 @@ struct Exchange {
     }
     polls = 1;
   }
-  // at the end of the kernel: tells the launches behind this one, and the host
+  // at the end of the kernel
   __device__ __forceinline__ void report(int32_t* state, int* error) {
-    if (polls > 1) return;
-    __hip_atomic_fetch_or(state, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (polls == 1) give_up(state, error);
   }
   __device__ __forceinline__ void put(int base, int lane, unsigned v) {
     __builtin_amdgcn_raw_buffer_store_b32(publish_word(v), rsrc, lane, base, STORE);

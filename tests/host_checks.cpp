@@ -5,9 +5,11 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "../include/lsq.h"
+#include "../paper_2010_13887_amd/csrc/die_count.h"
 
 static int failures = 0;
 #define EXPECT(cond)                                                        \
@@ -32,7 +34,59 @@ static std::vector<unsigned char> header(int arch, int n_enc, int n_dec, int d, 
   return h;
 }
 
+// A launch with a group of rows per die, by where its workgroups find themselves: every group of the launch is complete, or it has a workgroup that
+// waits for one that is missing (and gives up), or the last workgroup of the launch sees that it has none.
+static void placements() {
+  using namespace lsq;
+  constexpr int N = kDies * kDieGroup;
+  uint32_t x = 1;
+  auto random = [&] { return (x = x * 1664525u + 1013904223u) >> 8; };
+  bool complete_seen = false, missed_seen = false;
+  for (int it = 0; it < 4000; ++it) {
+    int die[N], order[N];
+    const int first = random() % kDies, kind = it % 4;
+    for (int b = 0; b < N; ++b) {
+      order[b] = b;
+      die[b] = (b + first) % kDies;                                        // in turn, from any die
+      if (kind == 1 && random() % 64 == 0) die[b] = random() % kDies;      // a few of them astray
+      if (kind == 2) die[b] = random() % (1 + random() % kDies);           // anyhow
+      if (kind == 3) die[b] = die[b] == first ? (first + 1) % kDies : die[b];   // a die that gets nothing
+    }
+    if (it % 64 == 2)
+      for (int& d : die) d = first;
+    for (int b = N - 1; b > 0; --b) std::swap(order[b], order[random() % (b + 1)]);   // the order in which they leave
+    bool has[kDies][kDieGroup] = {};
+    for (int b = 0; b < N; ++b) has[die[b]][b / kDies] = true;
+    for (int G = 1; G <= kDies; ++G) {
+      bool complete = true, waits = false;
+      for (int g = 0; g < G; ++g) {
+        int places = 0;
+        for (bool h : has[g]) places += h;
+        complete = complete && places == kDieGroup;
+        waits = waits || (places > 0 && places < kDieGroup);
+      }
+      uint64_t word = 0;
+      int ends = 0;
+      bool there = false;
+      for (int b : order) {
+        const uint64_t mine = die_word(die[b], b / kDies);
+        const bool last = die_launch_ends(word);
+        word += mine;
+        if (last) { ++ends; there = die_groups_there(word, G); }
+      }
+      EXPECT(ends == 1 && die_launch_ends(word - 1));
+      if (complete) EXPECT(there);
+      else EXPECT(waits || !there);
+      if (kind == 0) EXPECT(complete);
+      complete_seen = complete_seen || complete;
+      missed_seen = missed_seen || (!complete && !waits);
+    }
+  }
+  EXPECT(complete_seen && missed_seen);
+}
+
 int main() {
+  placements();
   size_t n = 0;
   // null / short / wrong magic
   EXPECT(lsq_workspace_bytes(nullptr, 0, 2, 4, 8, &n) == LSQ_E_ARG);
