@@ -53,6 +53,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   __shared__ __attribute__((aligned(16))) float part[kWaves][NU > UQ ? NU : UQ][kRows][16];
   __shared__ __attribute__((aligned(16))) float part2[kWaves][kRows][16];
   __shared__ __attribute__((aligned(16))) Shares shares;
+  __shared__ unsigned first_key[kWaves][kTrip][8];   // of the first trip, per lane group: places in the cache, the same in all layers
 
   int tid = threadIdx.x, lane = tid & 63;
   int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -281,11 +282,10 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   const bool table = !PRE && a.anc != nullptr;
   const int32_t* slots = table ? a.anc + (size_t)arow * a.anc_ld : nullptr;
   auto slot_of = [&](int p) { return table ? min(max(slots[p], 0), a.beam - 1) : 0; };   // of the sentence's rows
-  auto key_offset = [&](int p) { return (unsigned)((slot_of(p) * a.T + p) * D + c8) * 2u; };
+  auto key_offset = [&](int p) { return (unsigned)((slot_of(p) * a.T + p) * D) * 2u; };
   const bool attends = pair < rows * H;
-  unsigned first_key[kTrip];   // the first trip's places in the cache, the same in all layers
 #pragma unroll
-  for (int u = 0; u < kTrip; ++u) first_key[u] = key_offset(max(min(ash + (gk + u * 8) * NSH, pos - 1), 0));
+  for (int u = 0; u < kTrip; ++u) first_key[wave][u][gk] = key_offset(max(min(ash + (gk + u * 8) * NSH, pos - 1), 0));
   int src_off = 0, src_len = 0;
   if constexpr (!PRE) { src_off = a.src_off[sent]; src_len = a.src_len[sent]; }
   if (tid < kWaves) shares.left[tid] = 0;   // the first rows' barrier is ahead
@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
 #pragma unroll
       for (int u = 0; u < decltype(keys)::value; ++u) {
         const int p = max(min(jb + (gk + u * 8) * NSH, nkeys - 1), 0);
-        const unsigned o = !self ? (unsigned)(p * (2 * D) + c8) * 2u : first ? first_key[u] : key_offset(p);
+        const unsigned o = (!self ? (unsigned)(p * (2 * D)) * 2u : first ? first_key[wave][u][gk] : key_offset(p)) + c8 * 2;
         kn[u] = *reinterpret_cast<const half8_t*>(Kh + o);
         vn[u] = *reinterpret_cast<const half8_t*>(Vh + o);
       }
@@ -401,16 +401,19 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   // registers: 32 to 59 of them were spilled into lanes.  Whole translations: d = 1024, 4 rows 11.21 -> 10.99 ms (75 steps); d = 768 pre-LN,
   // 8 rows 8.45 -> 8.18, 32 rows 10.61 -> 10.43 (104 steps).
   auto renew = [&] { asm volatile("" : "+s"(wave), "+s"(j), "+s"(grp), "+s"(r0), "+s"(rows), "+s"(pos)); };
+  // The same for a thread's place, once a layer; twice where the cross-attention's registers come on top of four k-steps' in whole units.
+  // Without it d = 1024 spills (32 rows 204 -> 174 us a step's layers); d = 512 gains 2 %, d = 768 would lose 1 to 2 % (8 rows 8.82 -> 8.92 ms, 32 rows
+  // 9.55 -> 9.76; decoder-only, 32 rows 25.98 -> 26.25), and needs it for one number only.  No vector register is spilled this way.
+  auto renew_lane = [&] {
+    asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(odd), "+v"(lane16), "+v"(lane_nt), "+v"(lane_qt));
+    asm volatile("" : "+v"(gk), "+v"(c8));
+  };
 
   // ======== the layers.  Every matrix slice is requested at least one exchange before it is multiplied.
   load_qkv(wq, layer_w(now()->Wqkv, 0));
   for (int l = 0; l < a.layers; ++l) {
-    // The same for a thread's place, once a layer: without it d = 1024 spills (32 rows 204 -> 174 us a step's layers); d = 512
-    // gains 2 %, d = 768 would lose 2 %.
-    if constexpr (DK != 3) {
-      asm volatile("" : "+v"(tid), "+v"(lane), "+v"(fm), "+v"(kc), "+v"(odd), "+v"(lane16), "+v"(lane_nt), "+v"(lane_qt));
-      asm volatile("" : "+v"(gk), "+v"(c8));
-    }
+    if constexpr (DK != 3) renew_lane();
+    else if constexpr (X == 1 && !PRE) asm volatile("" : "+v"(c8));
     renew();
     half_t* Kc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l) * now()->cache_stride);
     half_t* Vc = reinterpret_cast<half_t*>(global(now()->cache) + (size_t)(2 * l + 1) * now()->cache_stride);
@@ -498,6 +501,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
       project(we, k1{}, l, Rg::ctx2, false, Rg::u2, layer_p(now()->boc, l), [&] { load_cols(w2, layer_w(now()->W2, l), k4{}, cn{}); });
     }
     renew();
+    if constexpr (DK == 4 && X == 1 && !PRE) renew_lane();
     // G. LayerNorm, first FFN product
     const int fcol = (j + W * qi) * 16 + qn;
     half2_t fb = {0, 0};

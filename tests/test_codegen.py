@@ -92,3 +92,21 @@ def test_attention_of_the_stack_kernels_is_one_arithmetic_whatever_the_compiler_
         assert not [i for i in ops if i.startswith("v_fma_mix") and "f16" in i], ops
     assert counts["off"] == counts["fast"], counts
     assert counts["fast"]["div"] == 1 and counts["fast"]["exp"] == 4 + 5 + 2, counts
+
+
+@pytest.mark.parametrize("source,kernels", [("kernels_stack.hip", 30), ("kernels_stack_die.hip", 6)])
+def test_float16_stack_kernels_spill_no_vector_register(tmp_path, source, kernels):
+    """A layer's matrices wait in registers; what does not fit beside them goes to memory and back in every layer."""
+    from paper_2010_13887_amd import build as B
+    out = tmp_path / "unit.s"
+    r = subprocess.run([B._hipcc(), *B.FLAGS, "-I", B.CSRC, "--cuda-device-only", "-S", f"{B.CSRC}/{source}", "-o", str(out)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    spilled = {}
+    for entry in out.read_text().split("\n  - .")[1:]:
+        name = re.search(r"\.name:\s+(\S*decoder_(?:stack|die)\S*)", entry)
+        count = re.search(r"\.vgpr_spill_count:\s+(\d+)", entry)
+        if name and count:
+            spilled[name.group(1)] = int(count.group(1))
+    assert len(spilled) == kernels, sorted(spilled)
+    assert not any(spilled.values()), spilled
