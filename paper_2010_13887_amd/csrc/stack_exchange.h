@@ -18,8 +18,10 @@ constexpr int kThreads = 512, kWaves = 8;
 // A wait starts when there is nothing left to do, long before the value can be there: what is looked for too early is in the way of the stores it
 // waits for and of the weights, and comes back behind them.  So the first look is LEAD times 64 clocks late.  Whole passes in ms with 0 / 4 / 8 / 12 / 16 /
 // 20: Transformer-big, 1 sentence 11.76 11.51 11.10 10.90 10.85 10.90, 32 sentences 28.7 28.2 28.0 27.7 27.7 27.8; decoder-only, d = 768, 1 row 10.2 9.98
-// 9.56 9.45 9.6 10.1, 32 rows 30.95 30.4 29.5 29.3 29.2 29.4; float32, d = 512, 32 rows 17.86 17.74 17.90 17.92 17.85 18.4.  Stage by stage the
-// groups of 16 and 32 rows gain 0.5 to 1 % with 18 where keys of a large group or the FFN's activations are waited for.
+// 9.56 9.45 9.6 10.1, 32 rows 30.95 30.4 29.5 29.3 29.2 29.4.  Stage by stage the groups of 16 and 32 rows gain 0.5 to 1 % with 18 where
+// keys of a large group or the FFN's activations are waited for.  float32, whose layers are 135 us of products, has little to gain: 0 against 4, two runs
+// of each within 0.1 %: d = 512, 32 rows 17.89 -> 17.77 and 12.40 -> 12.30 ms, 64 rows 15.03 -> 14.95, 128 rows level, 1 row 11.10 -> 11.14; d = 256, 32 rows
+// 9.31 -> 9.36, 132 rows 14.29 -> 14.25; with 8 and more 17.9 to 18.4.
 constexpr int kLead = 12, kLeadF32 = 4;
 
 __device__ __forceinline__ unsigned publish_word(unsigned v) { return v == kSentinel ? 0x7FFF7FFFu : v; }   // one NaN for another
