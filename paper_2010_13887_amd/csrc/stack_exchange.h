@@ -83,7 +83,6 @@ struct Exchange {
   __device__ __forceinline__ void put(int base, int lane, unsigned v) {
     __builtin_amdgcn_raw_buffer_store_b32(publish_word(v), rsrc, lane, base, STORE);
   }
-  __device__ __forceinline__ void put(int base, int lane, float v) { put(base, lane, __builtin_bit_cast(unsigned, v)); }
   __device__ __forceinline__ void put2(int base, int lane, float a, float b) {   // 8 bytes
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
     const u32x2 w = {publish_word(__builtin_bit_cast(unsigned, a)), publish_word(__builtin_bit_cast(unsigned, b))};
