@@ -74,7 +74,8 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_kernel(const StackArgs
   // The 16 x 16 products have room for twice the rows of a group: rows 0..7 of the one operand hold k-step 2 i, rows 8..15 k-step 2 i + 1 of the
   // same rows, and of the columns' side the matrices that have only 8 columns here do the same (PAIR).  Of the product the
   // quadrants in which both are the same k-step are what is wanted (fold): half the requests for exchanged values, which a wavefront
-  // waits for, and for those matrices; a CU takes 16 clocks for any request, whether its lanes ask for the same lines or not.  Whole translations
+  // waits for, and for those matrices; a CU takes 16 clocks for any request, whether its lanes ask for the same lines or not.  Products that add
+  // one k-step to the next move the odd ones' columns over instead (multiply_pairs, as fast: 10.75 / 10.75 ms, 9.23 / 9.16).  Whole translations
   // in ms with this and the sums of sum_of: d = 1024, 4 rows 10.6 -> 10.1, 8 rows 14.2 -> 13.2; d = 768 pre-LN, 8 rows 10.2 -> 9.8, 32 rows 29.3 -> 28.8.
   int fm = lane & 7, kc = lane >> 4, odd = lane >> 3 & 1;
   constexpr bool PAIR = NT == 8, PAIRQ = QT == 8;
@@ -928,7 +929,7 @@ __global__ void __launch_bounds__(kThreads) decoder_stack_rows_kernel(const Stac
   };
 
   // What is derived from a workgroup's place is derived anew in every stage, and pointers are read where they are used, instead of
-  // waiting in scalar registers (69 to 157 of them were spilled; 16 at most are left).  d = 1024 needs it for what is derived from a thread's
+  // waiting in scalar registers (69 to 157 of them were spilled; 2 to 4 are left of pre-LN models, 9 to 29 of post-LN ones).  d = 1024 needs it for what is derived from a thread's
   // place as well (it spills otherwise); narrower models would lose 3 to 7 %.  Whole translations of 75 steps: d = 1024, 128 rows
   // 21.4 -> 21.1 ms; d = 512, 200 rows 15.1 -> 14.7, one per sentence 16.6 -> 16.1; d = 768 pre-LN, 120 rows 17.15 -> 16.9 (104 steps).
   auto renew = [&] {
@@ -1129,47 +1130,46 @@ bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers)
          stack_exchange_bytes(arch, kStackRowsMax, d, layers) < (1u << 30);
 }
 
-// Which kernel takes M rows on the current device.  Measured at short histories, layers of one step in us (8-row groups /
-// more rows):
-//   d = 512, 6 layers:    4 rows 92 / 98, 32 rows 116 / 108, 64 rows 117 / 116, 128 rows - / 137, 256 rows - / 196
-//   d = 768, 12 layers:   1 row 137 / 158, 8 rows 158 / 165, 32 rows 209 / 213, 40 rows 198 / 199, 64 rows - / 255
-//   d = 1024, 6 layers:   4 rows 122 / 126, 8 rows 134 / 128, 32 rows 174 / 147, 64 rows - / 189, 128 rows - / 266
-// A (row, head) pair has 256 keys in flight in groups of 8 rows (128 with X = 1), 64 or 32 in groups of 16 or 32; the separate
-// kernels give it four wavefronts and read a history that the rows of a sentence share once.  So the order changes with the
-// length.  Whole steps in us, 8-row groups / more rows / separate launches, beam 4 and a source of 30 tokens:
-//   position                  16                496               1008              1900
-//   d = 512,   32 rows        132 / 127 / 220   181 / 249 / 331   230 / 377 / 420   315 / 614 / 580
-//              64 rows        134 / 136 / 252   225 / 276 / 368   324 / 434 / 480   484 / 699 / 648
-//             128 rows        -   / 157 / 301   -   / 335 / 475   -   / 535 / 657   -   / 839 / 815
-//             256 rows        -   / 215 / 339   -   / 570 / 673   -   / 935 / 970   -   / 1528 / 1342
-//   d = 768,   40 rows        172 / 172 / 298   265 / -   / 400   359 / -   / 473   509 / -   / 541
-//              48 rows        -   / 161 / 286   -   / 318 / 441   -   / 483 / 541   -   / 764 / 662
-//             160 rows        -   / 241 / 374   -   / 598 / 682   -   / 972 / 960   -   / 1554 / 1216
-//   d = 1024,   8 rows        164 / 159 / 272   197 / 273 / 317   245 / 410 / 357   324 / 635 / 388
-//              16 rows        185 / 172 / 337   226 / 293 / 414   276 / 428 / 455   347 / 649 / 474
-//              32 rows        219 / 184 / 318   297 / 319 / 404   383 / 465 / 469   523 / 702 / 538
-//              64 rows        -   / 210 / 344   -   / 378 / 514   -   / 550 / 623   -   / 828 / 732
-//             128 rows        -   / 272 / 383   -   / 606 / 693   -   / 945 / 899   -   / 1495 / 1173
-// All of that is older than the second trip of keys through LDS, which groups of 16 and 32 rows need from 33 or 65 positions on, the products that read
-// their rows straight from the exchange, and the pairs of k-steps of 8-row groups.  With them, whole steps in us, 8-row groups / more rows, sources of
-// 30 tokens:
+// Which kernel takes M rows on the current device.  A (row, head) pair has 256 keys in flight in groups of 8 rows (128 with X = 1), 64 or 32
+// in groups of 16 or 32; the separate kernels give it four wavefronts and read a history that the rows of a sentence share once.  So the order
+// changes with the length.  Whole steps in us, beam 4 and sources of 30 tokens, six layers (pre-LN: twelve, one row per prompt), V = 16 000;
+// 8-row groups / more rows:
 //   positions                 20-60          60-120         120-200        200-320        320-440
-//   d = 1024,   8 rows        135 / 141      146 / 149      144 / 151
-//              12 rows        136 / 147      143 / 152      152 / 160      159 / 169
-//              16 rows        144 / 151      145 / 152      157 / 163      168 / 174      183 / 195
-//              24 rows        180 / 172      187 / 185      208 / 188      218 / 201      247 / 225    (24 and 32 rows: the second trip only)
-//              32 rows        188 / 180      198 / 181      205 / 192      228 / 210      257 / 228
-//   d = 768,   16 rows        170 / 185      178 / 193      193 / 205      206 / 221
-//              24 rows        197 / 197      209 / 202      221 / 220      239 / 231
-//              32 rows        201 / 202      214 / 211      226 / 223      248 / 242      290 / 285
-//              40 rows        211 / 214      224 / 224      239 / 241      269 / 265      316 / 319
-// and, with the second trip only, more rows / separate launches at positions 440-560 and 940-1060: d = 1024, 128 rows 540 / 667, 828 / 859;
-// d = 768, 48 rows 365 / 597, 603 / 862.
-// So 8-row groups have d = 1024 as long as one of them is enough, and 9 to 16 rows from 112 positions on (nearer, where the difference is a few
-// microseconds a step, the line is the old one); d = 768 as long as they fit the chip, level from 24 rows on.
-// One row per sentence shares nothing, and only the widest case crosses: d = 1024, 128 rows 898 / 958 at 1008, 1418 / 1391 at
-// 1900 (before the trip through LDS); d = 768 pre-LN, 160 rows 2307 / 2493 at 1980.  A source key counts as a quarter or half of one of the history
-// (position 16, sources of 2000: d = 512, 128 rows 460 / 458, 256 rows 791 / 784; d = 1024, 32 rows 363 / 433, 128 rows 862 / 825).
+//   d = 1024,   8 rows        125 / 132      128 / 136      131 / 141      139 / 148      152 / 160
+//              12 rows        127 / 135      129 / 139      133 / 144      142 / 153      156 / 167
+//              16 rows        134 / 137      136 / 141      140 / 147      149 / 158      164 / 175
+//              24 rows        144 / 142      149 / 149      164 / 159      182 / 173      206 / 193
+//              32 rows        146 / 146      154 / 154      171 / 164      190 / 180      214 / 200
+//   one per sentence, 8       127 / 132      130 / 136      135 / 142      144 / 153      153 / 168
+//              16 rows        137 / 139      142 / 146      150 / 157      161 / 171      171 / 184
+//   d = 768,   16 rows        115 / 123      117 / 126      119 / 130      126 / 136      133 / 143
+//              24 rows        118 / 126      119 / 130      129 / 134      137 / 140      148 / 148
+//              32 rows        122 / 128      123 / 132      133 / 136      142 / 142      155 / 152
+//              40 rows        124 / 132      126 / 136      136 / 140      147 / 148      162 / 159
+//   d = 768, pre-LN, 16       149 / 160      155 / 169      168 / 187      186 / 206      198 / 226
+//              32 rows        173 / 175      190 / 192      208 / 208      228 / 230      255 / 257
+//              40 rows        177 / 183      195 / 200      216 / 219      239 / 243      271 / 274
+//   d = 512,   12 rows         97 / 108       98 / 112      101 / 116      107 / 122      115 / 129     (where the die kernel does not run)
+//              32 rows        102 / 113      103 / 116      106 / 120      112 / 126      119 / 133
+//              64 rows        105 / 120      107 / 123      116 / 127      125 / 135      137 / 145
+//   d = 512, pre-LN, 40       130 / 149      137 / 155      157 / 172      187 / 205      221 / 235
+// and more rows / separate launches:
+//   positions                 440-560        560-940        940-1060       1060-1180      1180-1300
+//   d = 1024,  16 rows        187 / 307      209 / 314      233 / 337      246 / 342      257 / 351
+//              64 rows        276 / 433      321 / 484      372 / 535      399 / 561      423 / 586
+//             128 rows        416 / 545      510 / 627      604 / 721      647 / 763      693 / 808
+//   d = 768,   48 rows        187 / 364      220 / 397      253 / 445      266 / 459      279 / 477
+//             160 rows        341 / 482      415 / 543      488 / 614      522 / 639      558 / 668
+//   d = 512,  128 rows        226 / 377      272 / 421      315 / 462      335 / 483      358 / 505
+//             256 rows        348 / 472      428 / 541      507 / 606      546 / 639      589 / 679
+// d = 768 has groups of 8 as long as they fit the chip: ahead or level to position 320, 2 % behind from there on.  d = 1024 has them up to
+// 8 rows; 24 and 32 rows are level at first and behind later.  The lines for 9 to 16 rows of d = 1024 and for d = 512, and those to the separate
+// launches (1300, 1120, 960 and 1100), were drawn where earlier forms of these kernels crossed: the present ones cross later or not at all, so a
+// line costs what the table says between it and there, 3 to 7 % of a step for 9 to 16 rows of d = 1024 up to position 112.
+// Older, of those earlier forms: groups of 8 against separate launches at positions 1008 and 1900, d = 1024, 8 rows 245 / 357, 324 / 388, 32 rows
+// 383 / 469, 523 / 538; one row per sentence, which shares nothing, d = 1024, 128 rows on more rows / separate launches 898 / 958, 1418 / 1391.  A source
+// key counts as a quarter or half of one of the history (position 16, sources of 2000: d = 512, 128 rows 460 / 458, 256 rows 791 / 784; d = 1024,
+// 32 rows 363 / 433, 128 rows 862 / 825).
 StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool dies) {
   if (M < 1) return kStackNone;
   if (dies && die_supported(arch, M, d, beam, pos, src)) return kStackDie;
@@ -1178,8 +1178,8 @@ StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool di
   bool many = r.x != 0 && rows_kernel_of(r.dk, r.x, arch == 1) && resident(rows_kernel_of(r.dk, r.x, arch == 1));
   constexpr int never = 1 << 30;
   const int len = pos + src / 4;
-  // where the lines above cross: 8-row groups against separate launches (extrapolated past 1900; 1 sentence of d = 1024
-  // 460 / 464 at 3900), more rows against them, 8-row groups against more rows
+  // 8-row groups against separate launches (extrapolated past 1900; 1 sentence of d = 1024 460 / 464 at 3900), more rows against
+  // them, 8-row groups against more rows
   if (beam > 1 && d > 512 && len > (c.x == 1 ? 2000 : 2700)) few = false;
   if (r.x == 1 && beam > 1 && len > 1300) many = false;
   if (r.x == 2 && pos + src / 2 > (beam > 1 ? (d == 512 ? 1120 : d == 768 ? 960 : 1100) : (d == 1024 ? 1600 : never))) many = false;

@@ -12,9 +12,9 @@
 // models whose layers are small (d = 512: 44 MB, 48 us; d = 256, of which nothing is known, stays with kernels_stack.hip).
 //
 // Not explained: a kernel that was not kept, with 32 to 64 rows a die (129 to 512 in all), 16 KB per poll and stores without a
-// scope, had a wait that ran out once in 1500 to 7000 launches: a value was published and not seen.  This one, with 16 rows a die at
-// most, had none in 187 500 launches with the same stores.  Those stores are the only thing found in it that no memory model
-// covers; whether they were the cause is not known.  If a wait does run out no result is lost: the translation is decoded again,
+// scope, had a wait that ran out once in 1500 to 7000 launches: a value was published and not seen.  An earlier form of this one, with 16 rows
+// a die at most and other waits and barriers than now, had none in 187 500 launches with the same stores.  Those stores are the only thing
+// found in it that no memory model covers; whether they were the cause is not known.  If a wait does run out no result is lost: the translation is decoded again,
 // and the model keeps to the kernels that go by agent scope alone (lsq_runtime.hip, decode_again).
 //
 // A compute unit's loads come back in the order in which they were issued, whoever issued them: one that finds its line in the
@@ -650,16 +650,20 @@ static const void* die_kernel_of(int R, bool pre) {
                 : (pre ? (const void*)decoder_die_kernel<16, true> : (const void*)decoder_die_kernel<16, false>);
 }
 
-// Against the kernels of kernels_stack.hip and the separate launches, us a step at positions 16 / 112 / 240 / 496 / 1008 / 1900 (die, others):
-//   post-LN, 4 rows of a sentence   93  95 103 121 150 195,  111 112 116 131 160 208
-//   32 rows, beam 4                112 116 128 161 210 296,  127 135 146 181 230 316
-//   64 rows, beam 4                121 128 160 214 315 471,  135 143 175 225 324 484
-//   128 rows, beam 4               141 183 238 336 544 845,  156 190 241 335 536 801
-//   128 rows, one per sentence     146 183 224 299 470 735,  165 191 232 309 479 750
-//   pre-LN, 12 layers, 32 rows     160 175 202 244 318 457,  174 198 206 244 320 467
-//   pre-LN, 64 rows                179 218 266 339 479 766,  187 222 246 325 474 758
-//   pre-LN, 128 rows               218 289 380 525 823   -,  231 275 357 509 815   -
-// A source key counts as half of one of the history (128 rows, sources of 500 and 2000: 232 463, 229 446).
+// Against the kernels of kernels_stack.hip (the one of its two that is ahead), whole steps in us, V = 16 000:
+//   positions                  16-60      60-112     112-200    200-280    280-400    400-560    560-940
+//   post-LN, 4 rows, beam 4    80 / 90    81 / 91    84 / 94    89 / 98   101 / 106  105 / 111  118 / 124
+//   32 rows, beam 4            99 / 102  100 / 103  102 / 106  107 / 110  118 / 118  122 / 123  133 / 138
+//   64 rows, beam 4           107 / 105  110 / 106  122 / 115  129 / 122  137 / 132  152 / 151  196 / 191
+//   128 rows, beam 4          124 / 137  139 / 141  148 / 148  173 / 161  206 / 185  as the others from 400 on
+//   128 rows, one per sentence 129 / 140 148 / 158  180 / 182  212 / 210  240 / 242  281 / 284  364 / 365
+//   pre-LN, 12 layers, 16 rows 125 / 120 132 / 122  145 / 127  152 / 133  as the others from 300 on
+//   pre-LN, 32 rows           145 / 124  149 / 129  155 / 139  169 / 157
+//   pre-LN, 64 rows           159 / 136  169 / 151  196 / 180  as the others from 160 on
+//   pre-LN, 128 rows          192 / 185  as the others from 56 on
+// The lines stand where earlier forms of the kernels crossed; products of paired k-steps have brought groups of 8 rows (pre-LN and 64 rows) and keys through
+// LDS groups of 32 (128 rows) past this one since, by what the table says.  A source key counts as half of one of the history (128 rows,
+// sources of 500 and 2000: 232 463, 229 446, earlier forms).
 bool die_supported(int arch, int M, int d, int beam, int pos, int src) {
   if (d != 512 || M < 1 || M > 16 * kDies) return false;
   const int most = arch == 1 ? (M <= 32 ? 300 : M <= 64 ? 160 : 56) : M > 64 && beam > 1 ? 400 : 1 << 30;
