@@ -539,8 +539,17 @@ def test_pairs_of_k_steps_match_oracle(lsq, d, batch, beam):
         assert lsq.lsq_debug_stack_launches()["groups_of_8"] == 4
 
 
+@pytest.mark.parametrize("lens", [(64, 65), (128, 129), (7, 257)])
+def test_sources_around_the_forms_of_a_trip_match_oracle(lsq, lens):
+    """Eight wavefronts share a source's keys: one per lane group up to 64, two up to 128, then four, and a second trip."""
+    w, blob = _long_workload(1024, 16, list(lens), 4, 3, 1)
+    with lsq.Engine(blob, 2, 4, w.max_len) as eng:
+        assert lockstep(lsq, eng, blob, w, max_steps=3)["steps"] == 3
+        assert lsq.lsq_debug_stack_launches()["groups_of_8"] == 3
+
+
 @pytest.mark.parametrize("d,batch,beam,steps", [
-    (1024, 5, 4, 132),   # groups of 16 rows, two wavefronts a head: both from 33 keys on, through LDS from 65 and again from 129 on
+    (1024, 5, 4, 132),   # groups of 16 rows, two wavefronts a head: through LDS from 65 keys on and again from 129 on
     (1024, 17, 4, 68),   # groups of 32 rows, one wavefront: 32 keys a trip
     (768, 21, 5, 100),   # a fourth trip, whose places in the cache are looked up two trips ahead
 ])

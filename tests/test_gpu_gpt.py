@@ -191,6 +191,8 @@ def test_row_without_candidates_reads_a_row_of_the_embedding(lsq, d, batch, fusi
 
 @pytest.mark.parametrize("d,batch,prompt,kernel", [
     (768, 2, 270, "groups_of_8"),           # 256 keys a trip
+    (768, 2, 61, "groups_of_8"),            # ... of which 64 take one key of each lane group, 128 two
+    (768, 12, 125, "groups_of_8"),
     (768, 32, 132, "groups_of_8"),          # four groups of rows: 128 keys a trip
     (512, 12, 236, "die"),                  # groups of 8 rows on dies: 64 keys a trip
     (768, 41, 72, "groups_of_16_or_32"),    # of 16: 64 keys a trip
