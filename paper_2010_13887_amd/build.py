@@ -11,7 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblsq.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["lsq_runtime.hip", "kernels_elementwise.hip", "kernels_attn.hip", "kernels_gemm.hip",
-           "kernels_search.hip", "kernels_stack.hip", "kernels_stack_f32.hip", "kernels_stack_die.hip", "kernels_small.hip"]
+           "kernels_search.hip", "kernels_stack.hip", "kernels_stack_f32.hip", "kernels_stack_die.hip", "kernels_small.hip",
+           "kernels_small_encoder.hip"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # the first kernel arguments arrive in scalar registers with the wavefront instead of being

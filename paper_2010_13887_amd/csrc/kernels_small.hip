@@ -7,6 +7,8 @@
 // d = 64 took 58 us, 4.8 us per product and 5.4 us from one to the next.  Here: 27 us, of which the vocabulary 5 (one CU's load
 // path), the search 5, the attentions 2.3 each and the products with what follows them 1.5 to 2 each; bound by the length of
 // the chain of instructions.  A translation of 8 steps (2 sentences, beam 4, float32) 535 -> 392 us.
+// The steps of a translation share launches: a workgroup goes from one to the next by itself, until its sentence is finished, and
+// finds its weights, histories and keys where it left them (8 steps 329 -> 309 us, 54 of 4 sentences 795 -> 690).
 //
 // Products: 4x4 matrix instructions of 16 blocks (one row block: 4 hypotheses; a lane holds one of 64 columns), k split
 // over the wavefronts that 64-column units leave idle, added through LDS.  The next product's weights are requested before
@@ -65,19 +67,17 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
   __shared__ int slabs[K][64];                                               // of the first 64 positions of every history
   __shared__ float vecs[2][13 * kD + kF];                                    // biases, gains and shifts of a layer, of the next one
   __shared__ SearchShared sh;
+  __shared__ int goes_on;
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const ArgsPtr a0 = arguments<SmallArgs>();
-  const int b = blockIdx.x, r0 = b * K, D = a0->se.d, F = a0->se.F, H = a0->se.H, V = a0->se.V, G = (V + 31) / 32;
+  int b = blockIdx.x;
+  const int D = a0->se.d, F = a0->se.F, H = a0->se.H, V = a0->se.V, G = (V + 31) / 32;
   const int layers = a0->st.layers, T1 = a0->se.T1, Tm = a0->st.T;
-  const int pos = *global(a0->st.tpos);
+  const int first = *global(a0->st.tpos), steps = a0->se.steps;
   auto layer_of = [&](const half_t* p, size_t bytes) { return reinterpret_cast<const T*>(reinterpret_cast<const char*>(global(p)) + bytes); };
   auto pin = [] { asm volatile("" ::: "memory"); };
-
-  RerankState st = {};
-  if (wave < K) st = rerank_request(global(a0->se.tokens), global(a0->se.len), global(a0->se.fin), global(a0->se.cap),
-                                    a0->se.anc ? global(a0->se.anc) : nullptr, K, T1, 0, global(a0->se.step_state), one_group(), b, lane);
 
   // ---- products.  Wavefront w: 64-column unit w / parts, part w % parts of k
   const T* wp = nullptr;
@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
     auto offset = [&](int key) {
       if (!self) return (unsigned)(min(key, last) * 2 * D + h * DH);
       int slab = slabs[row][key & 63];
-      if (c0 > 0 && table) slab = min(max(global(arguments<SmallArgs>()->se.anc)[(size_t)(r0 + row) * T1 + min(key, last)], 0), K - 1);
+      if (c0 > 0 && table) slab = min(max(global(arguments<SmallArgs>()->se.anc)[(size_t)(b * K + row) * T1 + min(key, last)], 0), K - 1);
       return (unsigned)((slab * Tm + min(key, last)) * D + h * DH);
     };
     unsigned vo[DQ];
@@ -280,28 +280,42 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
       if (i < np) w[i] = *reinterpret_cast<const vec*>(wp + i * Pc::stride);
     pin();
   };
+  // ======== the steps.  What one of them leaves in memory the next one finds there: it is the same workgroup (and on the same
+  // compute unit), so the wait and the barrier between them are enough.
+  for (int it = 0;; ++it) {
+  asm volatile("" : "+v"(tid), "+v"(lane), "+s"(b));   // as in the loop over the layers
+#pragma unroll
+  for (int i = 0; i < P; ++i) asm volatile("" : "=v"(w[i]));   // nothing of the step before is kept
+  const int pos = first + it;
+  const bool last = it + 1 == steps;
+  RerankState st = {};
+  if (wave < K) {
+    const ArgsPtr r = arguments<SmallArgs>();
+    st = rerank_request(global(r->se.tokens), global(r->se.len), global(r->se.fin), global(r->se.cap),
+                        table ? global(r->se.anc) : nullptr, K, T1, it, global(r->se.step_state), one_group(), b, lane);
+  }
   request_stage(0, 0);
   for (int i = tid; i < R * D / 4; i += kThreads) {   // rows the sentence does not have: zeros
     const int row = i >> (ds - 2), c = (i << 2) & (D - 1);
     T4 v = {};
-    if (row < K) v = *reinterpret_cast<const T4*>(reinterpret_cast<const T*>(global(a0->st.x0)) + (size_t)(r0 + row) * D + c);
+    if (row < K) v = *reinterpret_cast<const T4*>(reinterpret_cast<const T*>(global(a0->st.x0)) + (size_t)(b * K + row) * D + c);
     *reinterpret_cast<T4*>(&rowsT[XS + row * LX + c]) = v;
     if (row >= K) *reinterpret_cast<T4*>(&rowsT[CTX + row * LX + c]) = v;
   }
   for (int i = tid; i < K * 64; i += kThreads) {
     const int row = i / 64, p = min(i % 64, T1 - 1);
-    slabs[row][i % 64] = table ? min(max(global(a0->se.anc)[(size_t)(r0 + row) * T1 + p], 0), K - 1) : row;
+    slabs[row][i % 64] = table ? min(max(global(a0->se.anc)[(size_t)(b * K + row) * T1 + p], 0), K - 1) : row;
   }
-  load_vectors(0);
+  if (it == 0 || layers > 2) load_vectors(0);   // of two layers both stay where they are
   if constexpr (R > K)
-    for (int r = K; r < R; ++r)
+    if (it == 0) for (int r = K; r < R; ++r)
       for (int c = tid; c < F; c += kThreads) rowsT[FF + r * LF + c] = (T)0.f;
   __syncthreads();
   for (int l = 0, stage = 0; l < layers;) {
     // what is derived from a thread's place is derived anew instead of waiting in registers
     asm volatile("" : "+v"(tid), "+v"(lane));
     const ArgsPtr p = arguments<SmallArgs>();
-    T* Kc = reinterpret_cast<T*>(global(p->st.cache) + (size_t)(2 * l) * p->st.cache_stride) + (size_t)r0 * Tm * D;
+    T* Kc = reinterpret_cast<T*>(global(p->st.cache) + (size_t)(2 * l) * p->st.cache_stride) + (size_t)(b * K) * Tm * D;
     T* Vc = reinterpret_cast<T*>(reinterpret_cast<char*>(Kc) + p->st.cache_stride);
     const T* kvb = reinterpret_cast<const T*>(global(p->st.cross) + (size_t)l * p->st.cross_stride) + (size_t)src_off * 2 * D;
     int N, Kd;
@@ -322,7 +336,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
       const float* g = vl + VN + (stage - 1) * D;
       add_norm(ps, vl + (stage == 1 ? VO : stage == 3 ? VO + 2 * D : V2), g, g + D);
     }
-    if (stage == 4 && l + 1 < layers) load_vectors(l + 1);   // for a barrier two stages on
+    if (stage == 4 && l + 1 < layers && (it == 0 || layers > 2)) load_vectors(l + 1);   // for a barrier two stages on
     if (stage == 0)
       for (int i = tid; i < K * D / 2; i += kThreads) {   // the new keys and values
         const int row = i >> (ds - 1), c = (i << 2) & (2 * D - 1);
@@ -337,7 +351,7 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
     l = nl;
   }
   const ArgsPtr a1 = arguments<SmallArgs>();
-  for (int i = tid; i < K * D; i += kThreads) reinterpret_cast<T*>(global(a1->st.hidden))[((size_t)r0 << ds) + i] = rowsT[XS + (i >> ds) * LX + (i & (D - 1))];
+  for (int i = tid; i < K * D; i += kThreads) reinterpret_cast<T*>(global(a1->st.hidden))[((size_t)(b * K) << ds) + i] = rowsT[XS + (i >> ds) * LX + (i & (D - 1))];
 
   // ======== logits and their group statistics: 64 columns per wavefront and turn
   for (int u = wave; u * 64 < V; u += kWaves) {
@@ -353,19 +367,36 @@ __global__ void __launch_bounds__(kThreads) small_step_kernel(const SmallArgs) {
         if (row >= K) continue;
         const float v = acc[n][i], mx = group_max<32>(col < V ? v : -INFINITY);
         const float z = group_sum<32>(col < V ? __expf(v - mx) : 0.f);
-        if (col < V) global(a1->se.logits)[(size_t)(r0 + row) * V + col] = v;
-        if ((lane & 31) == 0 && col < V) *reinterpret_cast<float2*>(global(a1->se.stats) + ((size_t)(r0 + row) * G + (col >> 5)) * 2) = float2{mx, z};
+        if (col < V) global(a1->se.logits)[(size_t)(b * K + row) * V + col] = v;
+        if ((lane & 31) == 0 && col < V) *reinterpret_cast<float2*>(global(a1->se.stats) + ((size_t)(b * K + row) * G + (col >> 5)) * 2) = float2{mx, z};
       }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (wave >= K) return;   // barriers from here on are among the wavefronts that remain
-  const ArgsPtr e = arguments<SmallArgs>();
-  const NextInput next = {global(e->se.next.E), global(e->se.next.pe), global(e->se.next.x), e->se.next.d, e->se.next.dtype, e->se.next.scale};
-  retrieve_rerank_sentence<4, K>(global(e->se.logits), global(e->se.stats), global(e->se.score), global(e->se.tokens), global(e->se.len),
-                                 global(e->se.fin), global(e->se.parent), global(e->se.active), V, G, T1, global(e->se.step_state),
-                                 e->se.eos, table ? global(e->se.anc) : nullptr, next, global(e->se.cand_score),
-                                 global(e->se.cand_idx), e->se.report, b, sh, st);
+  if (wave < K) {
+    const ArgsPtr e = arguments<SmallArgs>();
+    const NextInput next = {global(e->se.next.E), global(e->se.next.pe), global(e->se.next.x), e->se.next.d, e->se.next.dtype, e->se.next.scale};
+    const bool more = retrieve_rerank_sentence<4, K>(global(e->se.logits), global(e->se.stats), global(e->se.score), global(e->se.tokens), global(e->se.len),
+                                                     global(e->se.fin), global(e->se.parent), global(e->se.active), V, G, T1, global(e->se.step_state),
+                                                     e->se.eos, table ? global(e->se.anc) : nullptr, next, global(e->se.cand_score),
+                                                     global(e->se.cand_idx), e->se.report, b, sh, st, last);
+    if (tid == 0) goes_on = more;
+  } else if (last) {
+    return;   // the barriers inside are among the wavefronts that remain
+  } else {    // as many barriers as there are inside
+    for (int p0 = 0; p0 <= pos && p0 < T1; p0 += 64) __syncthreads();
+  }
+  if (last) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (!goes_on) break;
+  }
+  // The sentence is finished before the last step of the launch: it counts as one that does not go on from there.
+  if (tid == 0) {
+    const ArgsPtr e = arguments<SmallArgs>();
+    const int before = step_arrive(global(e->se.step_state), 0), t = first + steps - 1;
+    step_finish(before, global(e->se.active), t, global(e->se.step_state), t + 1, 0, (int)gridDim.x, e->se.report);
+  }
 }
 
 const void* small_kernel_of(int dtype, int k) {

@@ -280,10 +280,32 @@ struct SearchArgs {
   float* cand_score;
   int32_t* cand_idx;
   unsigned long long* report;
+  int steps;                 // of a launch: a sentence takes them one after the other and stops when it is finished
 };
 bool small_step_supported(int arch, int H, int d, int F, int V, int k);
 bool small_step_ahead(int batch, int k, int H, int d, int layers, int pos, int src);   // ... and faster so, at this history and these sources
 hipError_t launch_small_step(int dtype, int batch, int k, const StackArgs& args, const SearchArgs& search, hipStream_t s);
+// The encoder of such a model and the start of its translation as one launch, sources of up to kSmallEncoderRows tokens (kernels_small_encoder.hip).
+// Matrices [out][in], as the products read them; layer l's tensors lie enc_stride (dec_stride) bytes further on for each layer.
+constexpr int kSmallEncoderRows = 48;
+struct SmallEncoderArgs {
+  const int32_t *h_ids, *h_off, *h_len, *h_cap, *h_order;   // pinned host memory; ids: id_stride for each sentence
+  int id_stride;
+  int32_t *src_off, *src_len, *cap, *order;
+  const void* E;
+  const float* pe;
+  const void *Wqkv, *bqkv, *Wo, *bo, *ln1g, *ln1b, *W1, *b1, *W2, *b2, *ln2g, *ln2b, *Wkv, *bkv;
+  size_t enc_stride, dec_stride, cross_stride;
+  void* memory;               // encoder output, packed rows
+  char* cross;
+  float* score;
+  int32_t *tokens, *len, *fin, *active, *step_state, *anc, *pen_n;
+  void* x0;
+  int d, F, H, enc_layers, dec_layers, k, kg, T1, bos, pad;
+  float eps, scale, qscale;
+};
+bool small_encoder_ahead(int d, int batch, int longest);   // ... and faster so
+hipError_t launch_small_encoder(int dtype, int batch, int longest, const SmallEncoderArgs& args, hipStream_t s);
 hipError_t launch_beam_refine(const float* cand_score, const int32_t* cand_idx, float* score,
                               int32_t* tokens, int32_t* len, int32_t* fin, int32_t* parent,
                               const int32_t* cap, int32_t* active, int batch, int k, int V, int T,

@@ -235,6 +235,7 @@ Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   p.out_ids = take(M * T * 4);
   p.out_lens = take(M * 4);
   p.out_scores = take(M * 4);
+  p.d_x0 = take(M * d * esz);   // decoder input of the next step, left by the kernel that settles this step's tokens (of the first one: while the encoder's scratch is in use)
   p.scratch = off;
   // encoder phase
   size_t e = p.scratch;
@@ -259,7 +260,6 @@ Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   p.d_tmp2 = dtake(std::max<size_t>(std::min<size_t>(M, kBlockRowsMax) * kMaxSplits * d * 4, head_slabs));
   p.d_y = dtake(M * d * esz);
   p.d_x2 = dtake(M * d * esz);   // second hidden-state buffer for products that normalise their own input
-  p.d_x0 = dtake(M * d * esz);   // decoder input of the next step, left by the kernel that settles this step's tokens
   p.d_stats = dtake(M * ((V + 31) / 32) * 2 * 4);   // (largest, sum of exponentials) of every 32 logits of a row
   p.d_ffn = q;
   p.d_logits = q;
@@ -348,6 +348,7 @@ struct Ctx {
   int64_t stack_launches[kStackF32 + 1] = {};   // of this model, by StackKind
   bool small_ok = false;        // a beam search step of this model can be one launch
   SearchArgs search{};
+  SmallEncoderArgs encoder{};   // ... and its encoder too
   std::vector<GptLayer> gpt;
   char *lnfg = nullptr, *lnfb = nullptr;
   int prompt_len = 0;
@@ -490,6 +491,17 @@ int setup_stack() {
                           nullptr, {g.E, at<float>(p.pe), g.ws + p.d_x0, d, hp.dtype, sqrtf((float)d)}, at<float>(p.cand_score),
                           at<int32_t>(p.cand_idx), &g.page->step};
     g.small_ok = Ep != nullptr;
+    const EncLayer& e0 = g.enc[0];
+    const DecLayer& d0 = g.dec[0];
+    auto stride = [](const char* first, const char* second) { return (size_t)(second - first); };   // tensor_walk: the same for every tensor of a layer
+    g.encoder = SmallEncoderArgs{g.pinned, nullptr, nullptr, nullptr, nullptr, 0,
+                                 at<int32_t>(p.src_off), at<int32_t>(p.src_len), at<int32_t>(p.cap), at<int32_t>(p.order), g.E, at<float>(p.pe),
+                                 e0.Wqkv, e0.bqkv, e0.Wo, e0.bo, e0.ln1g, e0.ln1b, e0.W1, e0.b1, e0.W2, e0.b2, e0.ln2g, e0.ln2b, d0.Wkv, d0.bkv,
+                                 hp.n_enc > 1 ? stride(e0.Wqkv, g.enc[1].Wqkv) : 0, L > 1 ? stride(d0.Wkv, g.dec[1].Wkv) : 0, a.cross_stride,
+                                 g.ws + p.e_x, g.ws + p.cross, at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
+                                 at<int32_t>(p.active), at<int32_t>(p.step_state), nullptr, at<int32_t>(p.pen_n), g.ws + p.d_x0,
+                                 d, F, hp.H, hp.n_enc, L, g.beam, g.beam, g.max_len + 1, hp.bos, hp.pad, hp.eps, sqrtf((float)d),
+                                 1.4426950408889634f / sqrtf((float)(d / hp.H))};
   }
   return LSQ_OK;
 }
@@ -506,10 +518,19 @@ StackKind use_stack(int M) {
 
 // plain beam search with a small model: the whole step in one launch.  Up to as many sentences as the chip runs at once:
 // a workgroup's step takes as long as the separate launches of some hundred rows.
-bool use_small(int B) {
+// ahead: of the step so many steps from now.
+bool use_small(int B, int ahead = 0) {
   return g.small_ok && g.fuse_ln && (B * g.beam <= g.block_rows || g.block_rows == (int)kBlockRowsMax) && B <= 256 && g.groups == 1 &&
          g.hp.sample_topk == 0 && g.topk_stats && g.merge_rerank &&
-         small_step_ahead(B, g.beam, g.hp.H, g.hp.d, g.hp.n_dec, history(), g.src_longest);
+         small_step_ahead(B, g.beam, g.hp.H, g.hp.d, g.hp.n_dec, history() + ahead, g.src_longest);
+}
+
+// Steps from here on that one launch of it can take, at most `most`.  Not where a launch between the steps moves the cache.
+int small_steps(int most) {
+  int n = 0;
+  const bool together = !g_prof.on && (g.anc_on || g.beam == 1);
+  while (n < (together ? most : 1) && g.t + n < g.max_len && g.alive_at[g.t + n] > 0 && use_small(g.alive_at[g.t + n], n)) ++n;
+  return n;
 }
 
 hipError_t launch_stack(StackKind kind, StackArgs a) {
@@ -540,7 +561,7 @@ hipError_t reset_stack() {
 // cross-K/V strides are those of the maximum shapes, and grids that depend on the number of cached
 // positions cover max_len of them.  The same sequence therefore serves every step with B sentences
 // alive, which is what lets it be captured once into a hipGraph and replayed.
-int launch_step(int B) {
+int launch_step(int B, int small) {
   const HParams& hp = g.hp;
   const Plan& p = g.plan;
   hipStream_t s = g.stream;
@@ -556,6 +577,7 @@ int launch_step(int B) {
   char* ffn = g.ws + p.d_ffn; char* logits = g.ws + p.d_logits;
   int32_t* step = at<int32_t>(p.step_state);
   int32_t* anc = g.anc_on ? at<int32_t>(p.anc) : nullptr;
+  const bool moves = !anc && k > 1;   // the cache's rows; a single hypothesis has no parent but itself
   const size_t slab = (size_t)M_max * T * d * es;   // one layer's K (or V) cache
   const size_t cross_l = (size_t)g.max_batch * g.max_len * 2 * d * es;
   // Under beam search the decoder input of this step is already there: the re-rank kernel of the step before
@@ -609,13 +631,14 @@ int launch_step(int B) {
     pending.on = false;
     return LSQ_OK;
   };
-  if (use_small(B)) {
+  if (small) {
     StackArgs a = g.stack;
     a.x0 = (const half_t*)x0; a.hidden = (half_t*)x_home;
     SearchArgs se = g.search;
     se.anc = anc;
+    se.steps = small;
     TIMED(PC_STACK, launch_small_step(dt, B, k, a, se, s));
-    if (!anc)
+    if (moves)
       TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
                                              0, step, T, s));
     return LSQ_OK;
@@ -748,7 +771,7 @@ int launch_step(int B) {
                                           at<int32_t>(p.parent), at<int32_t>(p.cap), at<int32_t>(p.active), B, kg, V,
                                           T, 0, step, hp.eos, anc, s, gr, next, report));
     }
-    if (!anc)
+    if (moves)
       TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
                                              0, step, T, s));
     return LSQ_OK;
@@ -759,7 +782,7 @@ int launch_step(int B) {
                                                      at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
                                                      at<int32_t>(p.parent), at<int32_t>(p.cap), at<int32_t>(p.active), B, k, V, T,
                                                      step, hp.eos, anc, s, next, at<float>(p.cand_score), at<int32_t>(p.cand_idx), report));
-    if (!anc)
+    if (moves)
       TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
                                              0, step, T, s));
     return LSQ_OK;
@@ -777,7 +800,7 @@ int launch_step(int B) {
                             at<int32_t>(p.tokens), at<int32_t>(p.len), at<int32_t>(p.fin),
                             at<int32_t>(p.parent), at<int32_t>(p.cap), at<int32_t>(p.active), B, k, V, T, 0,
                             step, hp.eos, anc, s, one_group(), next, report));
-  if (!anc)
+  if (moves)
     TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
                                            0, step, T, s));
   return LSQ_OK;
@@ -894,14 +917,15 @@ int launch_step_gpt(int B) {
 // timing is on, and for steps of a few launches (decoder stack kernel): between two graphs pass about 5 us, more than
 // those launches take on their own (Transformer-base, 1 sentence: 125.2 us a step replayed, 120.0 launched; the 15
 // launches of the tiny model: 69 and 83).
-int enqueue_step() {
-  const int B = g.alive_at[g.t];
-  auto launch = [&](int n) { return g.hp.arch == 1 ? launch_step_gpt(n) : launch_step(n); };
+// `most`: of steps that fit one launch (small models), so many of them; g.t says where it ended.
+int enqueue_step(int most) {
+  const int B = g.alive_at[g.t], small = small_steps(most);
+  auto launch = [&](int n) { return g.hp.arch == 1 ? launch_step_gpt(n) : launch_step(n, small); };
   g.hidden_in_alt = false;   // launch_step says otherwise
-  if (!g.use_graphs || g.stream == nullptr || g_prof.on || use_stack(B * g.beam) || use_small(B)) {
+  if (!g.use_graphs || g.stream == nullptr || g_prof.on || use_stack(B * g.beam) || small) {
     int rc = launch(B);
     if (rc) return rc;
-    g.t += 1;
+    g.t += std::max(small, 1);
     return LSQ_OK;
   }
   // the captured launches depend on the number of live sentences and, through the geometry of
@@ -1022,7 +1046,7 @@ int decode_again() {
     return rc;
   }
   for (g.t = 0; g.t < steps;)
-    if (int rc = enqueue_step()) return rc;
+    if (int rc = enqueue_step(steps - g.t)) return rc;
   return LSQ_OK;
 }
 
@@ -1120,6 +1144,42 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
   g.t = 0;
   g.done = false;
   g.state = 3;
+  return LSQ_OK;
+}
+
+// The encoder and the keys and values of the cross-attention as launches of their own, for R packed source rows in the staging buffer.
+int run_encoder(int batch, int R) {
+  const HParams& hp = g.hp;
+  const Plan& p = g.plan;
+  const size_t Rmax = (size_t)g.max_batch * g.max_len;
+  const int32_t *h_ids = g.pinned, *h_pos = h_ids + Rmax, *h_sent = h_pos + Rmax;
+  const int32_t *h_off = h_sent + Rmax, *h_len = h_off + g.max_batch + 1, *h_cap = h_len + g.max_batch, *h_order = h_cap + g.max_batch;
+  hipStream_t s = g.stream;
+  Staging st{};
+  st.add(at<int32_t>(p.e_ids), h_ids, R); st.add(at<int32_t>(p.e_pos), h_pos, R); st.add(at<int32_t>(p.e_sent), h_sent, R);
+  st.add(at<int32_t>(p.src_off), h_off, batch + 1); st.add(at<int32_t>(p.src_len), h_len, batch);
+  st.add(at<int32_t>(p.cap), h_cap, batch); st.add(at<int32_t>(p.order), h_order, batch);
+  HIPCHK(launch_staging(st, s));
+
+  const int dt = hp.dtype, d = hp.d, F = hp.F, H = hp.H;
+  const size_t es = esz();
+  char* x = g.ws + p.e_x; char* qkv = g.ws + p.e_qkv; char* ctx = g.ws + p.e_ctx; char* tmp = g.ws + p.e_tmp;
+  char* ffn = g.ws + p.e_ffn;
+  const int32_t* sent = at<int32_t>(p.e_sent);
+  const int32_t* off = at<int32_t>(p.src_off);
+  const int32_t* len = at<int32_t>(p.src_len);
+  HIPCHK(launch_embed_rows(dt, g.E, at<float>(p.pe), at<int32_t>(p.e_ids), at<int32_t>(p.e_pos), x, R, d, sqrtf((float)d), s));
+  for (const EncLayer& L : g.enc) {
+    HIPCHK(launch_gemm(dt, x, L.Wqkv, L.bqkv, plain_out(qkv, 3 * d), R, 3 * d, d, 0, s));
+    HIPCHK(launch_encoder_attention(dt, qkv, sent, off, len, ctx, R, H, d, 0, s));
+    if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln1g, L.ln1b, x, nullptr, (float*)tmp, R, d, d, 1, s)) return rc;
+    HIPCHK(launch_gemm(dt, x, L.W1, L.b1, plain_out(ffn, F), R, F, d, 1, s));
+    if (int rc = sublayer(-1, ffn, L.W2, L.b2, L.ln2g, L.ln2b, x, nullptr, (float*)tmp, R, d, F, 1, s)) return rc;
+  }
+  const size_t cross_l = (size_t)g.max_batch * g.max_len * 2 * d * es;   // layer stride of the maximum shape
+  for (int l = 0; l < hp.n_dec; ++l)
+    HIPCHK(launch_gemm(dt, x, g.dec[l].Wkv, g.dec[l].bkv, plain_out(g.ws + p.cross + l * cross_l, 2 * d), R,
+                       2 * d, d, 0, s));
   return LSQ_OK;
 }
 
@@ -1332,14 +1392,20 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
   g.alive_at.assign(g.max_len + 1, 0);
   for (int b = 0; b < batch; ++b)
     for (int t = 0; t < cap_of(b); ++t) g.alive_at[t] += 1;
+  const int longest = *std::max_element(src_lens, src_lens + batch);
+  // A small model: the encoder and the start of the beams as one launch (switched off with the other kernels that do a layer's work in
+  // one).  A sentence's ids then start at a multiple of `longest`.
+  const bool together = g.small_ok && g.fuse_ln && g.block_rows > 0 && hp.sample_topk == 0 && small_encoder_ahead(hp.d, batch, longest);
   int r = 0;
   for (int i = 0; i < batch; ++i) {
     const int b = g.order[i];
     h_off[i] = r;
+    if (together) memcpy(h_ids + (size_t)i * longest, src_ids + (size_t)b * src_stride, src_lens[b] * sizeof(int32_t));
     h_len[i] = src_lens[b];
     h_cap[i] = cap_of(b);
     h_order[i] = b;
     for (int j = 0; j < src_lens[b]; ++j, ++r) {
+      if (together) continue;
       h_ids[r] = src_ids[(size_t)b * src_stride + j];
       h_pos[r] = j;
       h_sent[r] = i;
@@ -1347,37 +1413,22 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
   }
   h_off[batch] = r;
   hipStream_t s = g.stream;
-  Staging st{};
-  st.add(at<int32_t>(p.e_ids), h_ids, R); st.add(at<int32_t>(p.e_pos), h_pos, R); st.add(at<int32_t>(p.e_sent), h_sent, R);
-  st.add(at<int32_t>(p.src_off), h_off, batch + 1); st.add(at<int32_t>(p.src_len), h_len, batch);
-  st.add(at<int32_t>(p.cap), h_cap, batch); st.add(at<int32_t>(p.order), h_order, batch);
-  HIPCHK(launch_staging(st, s));
-
-  const int dt = hp.dtype, d = hp.d, F = hp.F, H = hp.H;
-  const size_t es = esz();
-  char* x = g.ws + p.e_x; char* qkv = g.ws + p.e_qkv; char* ctx = g.ws + p.e_ctx; char* tmp = g.ws + p.e_tmp;
-  char* ffn = g.ws + p.e_ffn;
-  const int32_t* sent = at<int32_t>(p.e_sent);
-  const int32_t* off = at<int32_t>(p.src_off);
-  const int32_t* len = at<int32_t>(p.src_len);
-  HIPCHK(launch_embed_rows(dt, g.E, at<float>(p.pe), at<int32_t>(p.e_ids), at<int32_t>(p.e_pos), x, (int)R, d, sqrtf((float)d), s));
-  for (const EncLayer& L : g.enc) {
-    HIPCHK(launch_gemm(dt, x, L.Wqkv, L.bqkv, plain_out(qkv, 3 * d), (int)R, 3 * d, d, 0, s));
-    HIPCHK(launch_encoder_attention(dt, qkv, sent, off, len, ctx, (int)R, H, d, 0, s));
-    if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln1g, L.ln1b, x, nullptr, (float*)tmp, (int)R, d, d, 1, s)) return rc;
-    HIPCHK(launch_gemm(dt, x, L.W1, L.b1, plain_out(ffn, F), (int)R, F, d, 1, s));
-    if (int rc = sublayer(-1, ffn, L.W2, L.b2, L.ln2g, L.ln2b, x, nullptr, (float*)tmp, (int)R, d, F, 1, s)) return rc;
+  if (together) {
+    SmallEncoderArgs a = g.encoder;
+    a.h_off = h_off; a.h_len = h_len; a.h_cap = h_cap; a.h_order = h_order;
+    a.id_stride = longest;
+    a.kg = g.beam / g.groups;
+    a.anc = g.anc_on ? at<int32_t>(p.anc) : nullptr;
+    HIPCHK(launch_small_encoder(hp.dtype, batch, longest, a, s));
+  } else if (int rc = run_encoder(batch, (int)R)) {
+    return rc;
   }
-  const size_t cross_l = (size_t)g.max_batch * g.max_len * 2 * d * es;   // layer stride of the maximum shape
-  for (int l = 0; l < hp.n_dec; ++l)
-    HIPCHK(launch_gemm(dt, x, g.dec[l].Wkv, g.dec[l].bkv, plain_out(g.ws + p.cross + l * cross_l, 2 * d), (int)R,
-                       2 * d, d, 0, s));
   // sampling decoding: one launch for retrieve + draw + next input when every row count of this translation has a
   // logit product that leaves group statistics (decided here, for the whole translation)
   bool fold = false;
   if (hp.sample_topk > 0 && g.topk_stats && g.merge_rerank && topk_groups_supported(hp.V, hp.sample_topk, 1)) {
     fold = true;
-    for (int m = 1; m <= batch * g.beam; ++m) fold = fold && gemm_writes_stats(dt, m, hp.V, d);
+    for (int m = 1; m <= batch * g.beam; ++m) fold = fold && gemm_writes_stats(hp.dtype, m, hp.V, hp.d);
   }
   if (fold != g.sample_fold) {   // captured steps hold the other variant's launches
     for (auto& kv : g.graphs) (void)hipGraphExecDestroy(kv.second);
@@ -1385,11 +1436,12 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
     g.graph_hidden_in_alt.clear();
   }
   g.sample_fold = fold;
-  if (int rc = start_beams(batch)) return rc;
+  if (!together)
+    if (int rc = start_beams(batch)) return rc;
   for (size_t c : p.dec_canaries) HIPCHK(hipMemsetAsync(g.ws + c, kCanaryByte, kCanaryBytes, s));
   g.batch = batch;
   g.rows_enc = (int)R;
-  g.src_longest = *std::max_element(src_lens, src_lens + batch);
+  g.src_longest = longest;
   g.t = 0;
   g.done = false;
   g.state = 3;
@@ -1402,11 +1454,10 @@ int lsq_decode_steps(int n) {
   if (g.state < 3) return fail(LSQ_E_STATE, "lsq_encode has not been called");
   if (n < 1) return fail(LSQ_E_ARG, "n must be positive");
   if (g.done || g.t >= g.max_len || g.alive_at[g.t] == 0) return 0;
-  int issued = 0;
-  while (issued < n && g.t < g.max_len && g.alive_at[g.t] > 0) {
-    int rc = enqueue_step();
+  const int64_t end = (int64_t)g.t + n;
+  while (g.t < end && g.t < g.max_len && g.alive_at[g.t] > 0) {
+    int rc = enqueue_step((int)std::min<int64_t>(end - g.t, g.max_len));
     if (rc) return rc;
-    ++issued;
   }
   int active = 0;
   int rc = read_active(g.t, &active);
@@ -1423,7 +1474,7 @@ int lsq_decode_all(int n) {
   for (int seen = g.t; !g.done && (more() || seen < g.t);) {   // the count after `seen` steps is known
     const int next = std::min(seen + n, g.max_len);
     while (g.t < next + ahead && more()) {
-      int rc = enqueue_step();
+      int rc = enqueue_step(g.max_len);   // small models: every sentence of a launch stops where it is finished
       if (rc) return rc;
     }
     seen = std::min(next, g.t);

@@ -331,13 +331,15 @@ struct SearchShared {
   alignas(16) int cand_i[LSQ_MAX_BEAM_ * LSQ_MAX_BEAM_];
   int sh_tok[LSQ_MAX_BEAM_];
 };
+// LAST: the kernel ends with this step; otherwise its other steps follow, and what the step counter has to hear is left to the last one.
+// Returns whether the sentence goes on.
 template <int GPL, int K>
-__device__ __forceinline__ void retrieve_rerank_sentence(
+__device__ __forceinline__ bool retrieve_rerank_sentence(
     const float* logits, const float* stats, float* __restrict__ score, int32_t* __restrict__ tokens,
     int32_t* __restrict__ len, int32_t* __restrict__ fin, int32_t* __restrict__ parent,
     int32_t* __restrict__ active, int V, int G, int T1, int32_t* __restrict__ step_state, int eos,
     int32_t* __restrict__ anc, const NextInput& nx, float* __restrict__ cand_out_s, int32_t* __restrict__ cand_out_i,
-    unsigned long long* report, int b, SearchShared& sh, RerankState st) {
+    unsigned long long* report, int b, SearchShared& sh, RerankState st, bool last = true) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   constexpr int k = K, kk = K * K;   // known to the compiler: a wavefront on its own takes 8 cycles for every instruction
   const int base = b * k, row = base + wave;
@@ -366,7 +368,10 @@ __device__ __forceinline__ void retrieve_rerank_sentence(
   const int nfin = st.pfin || tok == eos || nlen >= st.cap_b ? 1 : 0;
   const int go_on = __any(win && !nfin) ? 1 : 0;
   int before = 0;
-  if (wave == 0 && lane == 0) before = step_arrive(step_state, go_on);
+  if (wave == 0 && lane == 0) {
+    if (last) before = step_arrive(step_state, go_on);
+    else if (go_on) __hip_atomic_fetch_add(&active[t], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   const unsigned long long mine = __ballot(win && rank == wave);   // at most one lane: hypothesis w's candidate
   const int from = mine ? __builtin_amdgcn_readlane(j, (int)__builtin_ctzll(mine)) : wave;
   if (lane == 0) sh.sh_tok[wave] = -1;
@@ -405,7 +410,8 @@ __device__ __forceinline__ void retrieve_rerank_sentence(
     else next_input_rows<float>(nx, &sh.sh_tok[wave], row, 1, t + 1, lane);
   }
   asm volatile("" ::"v"(touched));
-  if (wave == 0 && lane == 0) step_finish(before, active, t, step_state, t + 1, go_on, (int)gridDim.x, report);
+  if (last && wave == 0 && lane == 0) step_finish(before, active, t, step_state, t + 1, go_on, (int)gridDim.x, report);
+  return go_on;
 }
 
 }  // namespace lsq

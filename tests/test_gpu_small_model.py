@@ -1,0 +1,76 @@
+"""Small models: the encoder as one launch, and several steps of a translation as one launch (needs an MI355X)."""
+import numpy as np
+import pytest
+
+import lsq_synth as S
+from oracle import lsq_oracle as O
+from tests.parity import TOL_F16, TOL_F32, logit_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lsq():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2010_13887_amd as lib
+    lib.load_library()
+    yield lib
+    lib.lsq_free()
+
+
+@pytest.mark.parametrize("d,heads,ffn,dtype,lens", [
+    (64, 4, 64, 0, [1]), (64, 2, 448, 0, [16, 3, 17]), (128, 8, 512, 0, [1] * 66 + [32, 33]), (128, 4, 192, 0, [5] * 94 + [48, 47]),
+    (64, 4, 512, 1, [48, 2]), (64, 2, 64, 1, [15, 16]), (128, 8, 512, 1, [17] * 60 + [31, 9]), (64, 4, 128, 1, [48, 49]), (128, 4, 128, 1, [2, 1, 1]),
+])
+def test_encoder_of_a_small_model(lsq, d, heads, ffn, dtype, lens):
+    """Encoder output and cross-attention keys and values at the edges of the blocks of 16 rows, with one token, and either side of
+    the lines to the separate launches (49 tokens; d = 128: fewer than twice as many sentences as tokens), against the oracle in 64 bits."""
+    hp = S.HParams(n_enc=2, n_dec=3, d_model=d, n_heads=heads, d_ffn=ffn, vocab=97, max_pos=64, dtype=dtype, cap_extra=2)
+    w = S.custom(hp, lens, beam=2, max_len=52, std=0.1 if dtype else 0.3)
+    blob = w.blob(ln_jitter=0.1)
+    R = sum(lens)
+
+    def oracle(ctype):
+        memory, cross = O.encode(O.Model(blob, ctype=ctype, storage="wide"), w.src_ids, w.src_lens)
+        return [np.concatenate(memory)] + [np.concatenate([np.concatenate(c[l], axis=-1) for c in cross]) for l in range(hp.n_dec)]
+
+    def read(eng):
+        return [eng.debug(lsq.DBG.MEMORY, (R, d))] + [eng.debug(lsq.DBG.CROSS_KV + l, (R, 2 * d)) for l in range(hp.n_dec)]
+
+    want = oracle(np.float64)
+    # float32: as everywhere here, 1e-4 or four times what plain numpy float32 loses on this model, whichever is larger
+    tol = [TOL_F16 if dtype else max(TOL_F32, 4 * logit_error(a, b)) for a, b in zip(oracle(np.float32), want)]
+    with lsq.Engine(blob, len(lens), 2, 52) as eng:
+        eng.encode(w.src_ids, w.src_lens)
+        error = [logit_error(a, b) for a, b in zip(read(eng), want)]
+        lsq.lsq_set_attention_blocks(0)
+        try:
+            eng.encode(w.src_ids, w.src_lens)
+            separate = [logit_error(a, b) for a, b in zip(read(eng), want)]
+        finally:
+            lsq.lsq_set_attention_blocks(64)
+    print("one launch", error, "separate launches", separate, "bounds", tol)
+    assert all(e <= t for e, t in zip(error, tol))
+
+
+@pytest.mark.parametrize("d,heads,vocab,beam,dtype,n_dec", [(64, 4, 12, 3, 0, 1), (64, 2, 11, 8, 0, 3), (128, 8, 12, 4, 1, 2), (128, 4, 31, 1, 0, 1)])
+def test_steps_of_a_small_model_in_one_launch(lsq, d, heads, vocab, beam, dtype, n_dec):
+    """A translation whose steps share launches, against the same one step at a time: sentences that finish early (a small
+    vocabulary draws EOS often), caps that differ, histories past 64 positions, chunks that end in the middle."""
+    hp = S.HParams(n_enc=1, n_dec=n_dec, d_model=d, n_heads=heads, d_ffn=128, vocab=vocab, max_pos=96, dtype=dtype, cap_extra=70, seed=3)
+    w = S.custom(hp, [1, 4, 9, 2, 20], beam=beam, max_len=80, std=0.5 if not dtype else 0.15)
+    blob = w.blob(ln_jitter=0.2)
+    with lsq.Engine(blob, 6, beam, 80) as eng:
+        eng.encode(w.src_ids, w.src_lens)
+        counts = []
+        while not counts or counts[-1] > 0:
+            counts.append(lsq.lsq_decode_step())
+        want = eng.get_beams()
+        for n in (1, 7, 64, 1000):
+            got = eng.translate(w.src_ids, w.src_lens, sync_every=n)
+            assert all(np.array_equal(a, b) for a, b in zip(got, want))
+            eng.encode(w.src_ids, w.src_lens)
+            for at in range(n, len(counts), n):
+                assert lsq.lsq_decode_steps(n) == counts[at - 1] and lsq.lsq_step_index() == at
+        assert lsq.lsq_debug_check_canaries() == 0
