@@ -1311,26 +1311,43 @@ __global__ void __launch_bounds__(256) encoder_attention_kernel(const T* __restr
 //   O += P V       the contraction runs over keys, and a matrix-core operand wants 8 contraction indices
 //                  per lane.  Which key sits at which index is free as long as P and V agree, so P is used
 //                  exactly as the first product left it in the lane's registers (index j of step st =
-//                  key 16 st + 8 (j >> 2) + 4 (lane >> 5) + (j & 3)) and the V operand is gathered to
-//                  match: 8 two-byte loads per lane and step, each a 64-byte run of one key's row across
-//                  the lanes.  No LDS, no transposition, no barrier.
+//                  key 16 st + 8 (j >> 2) + 4 (lane >> 5) + (j & 3)).  V comes in whole rows, 16 bytes a lane; the lane
+//                  that has 8 dimensions of two neighbouring keys pairs them up and leaves them in LDS by
+//                  dimension, in the order in which the operand is then read, 16 bytes at a time.  The wavefront's own
+//                  LDS: no barrier.
 // Scores of keys outside a row's sentence are computed and thrown away (with sentences of about 30 tokens a
 // block of 32 rows sees two or three key blocks); the kernel is bounded by its handful of trips to
-// memory, not by the matrix cores.
+// memory, not by the matrix cores: the next block of keys and values is on its way while one is worked on.
+// V gathered two bytes at a time, the blocks dealt out over the XCDs as they came and every key tested, the kernel took 33 us for 32 prompts of 239 tokens
+// and 12 heads (now 26), 14.5 for 128 tokens (10.3), 54 for 16 of 500 (40), 10.8 for 128 sentences of 28 and 16 heads (9.7); the cache rows
+// were a launch of 7.9 us (now 2).  Eight key blocks one after the other are 9 of the 26, the rest is that every compute unit has some 55 of them.
+// Kc given (prompt of a decoder-only model): the rows' keys and values also go to the cache, [sentence][position][d].
 template <int DH>
 __global__ void __launch_bounds__(256) encoder_attention_mfma_kernel(const half_t* __restrict__ qkv,
                                                                      const int32_t* __restrict__ row_sent,
                                                                      const int32_t* __restrict__ off,
                                                                      const int32_t* __restrict__ len,
                                                                      half_t* __restrict__ out, int rows, int H, int d,
-                                                                     int causal, float scale_log2e) {
+                                                                     int causal, float scale_log2e, half_t* __restrict__ Kc,
+                                                                     half_t* __restrict__ Vc, int T_) {
   constexpr int QS = DH / 16;   // k-steps of the score product
   constexpr int NB = DH / 32;   // 32-wide blocks of output dimensions
-  const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  const int nblk = (rows + 31) / 32;
-  if (w >= nblk * H) return;
-  const int blk = w / H, h = w % H;
+  constexpr int CH = DH / 8;    // 16-byte pieces of a row
+  // values of 32 keys by dimension: 16 words of two keys each, 4 more (and 4 for every 8 dimensions) so that lanes meet different banks
+  constexpr int LD = 20, SKEW = 4;
+  __shared__ __attribute__((aligned(16))) unsigned by_dim[4][DH * LD + CH * SKEW];
+  // A workgroup has four neighbouring blocks of a head, an XCD (blockIdx % 8) neighbouring workgroups: what several blocks of a
+  // sentence read comes from the compute unit's own cache or the XCD's.
+  const int nblk = (rows + 31) / 32, quads = (nblk + 3) / 4;
+  const int xcd = blockIdx.x & 7, each = gridDim.x >> 3, more_on = gridDim.x & 7;
+  // (causal: a sentence's later blocks have more keys; every other 32 workgroups of an XCD in swapped pairs, so that a compute unit does not get
+  // nothing but those)
+  const int own = each + (xcd < more_on ? 1 : 0), i0 = blockIdx.x >> 3, i1 = i0 ^ (i0 >> 5 & 1);
+  const int unit = xcd * each + min(xcd, more_on) + (i1 < own ? i1 : i0);
+  const int h = unit / quads, blk = __builtin_amdgcn_readfirstlane((unit - h * quads) * 4 + (threadIdx.x >> 6));
+  if (blk >= nblk) return;
   const int lane = threadIdx.x & 63, m = lane & 31, hi = lane >> 5;
+  unsigned* const mine = by_dim[threadIdx.x >> 6];
   const int r = min(blk * 32 + m, rows - 1);             // this lane's row (past the end: the last row, not stored)
   const int b = row_sent[r];
   const int lo = off[b];
@@ -1339,12 +1356,47 @@ __global__ void __launch_bounds__(256) encoder_attention_mfma_kernel(const half_
   // the block's key range: from the first row's sentence start to the last row's limit
   const int k_first = __builtin_amdgcn_readlane(lo, 0);
   const int k_last = __builtin_amdgcn_readlane(hi_key, 31);
+  const int all_from = __builtin_amdgcn_readlane(lo, 31), all_to = __builtin_amdgcn_readlane(hi_key, 0);   // keys that count for all of the rows
   const half_t* qp = qkv + (size_t)r * ld + h * DH + hi * 8;
   half8_t qf[QS];
 #pragma unroll
   for (int i = 0; i < QS; ++i) qf[i] = *reinterpret_cast<const half8_t*>(qp + i * 16);
-  const half_t* kbase = qkv + d + h * DH + hi * 8;
-  const half_t* vbase = qkv + 2 * d + h * DH + m;
+  // operands of a key block: K rows (key = k0 + m); of V the lane's 8 dimensions of keys 2 p and 2 p + 1, p = lane / CH + 64 / CH * t.
+  // Byte offsets (the launcher has seen that they fit) that go 32 rows on with every block, at most to the last key.
+  const char* kbase = reinterpret_cast<const char*>(qkv + d + h * DH);
+  const char* vbase = reinterpret_cast<const char*>(qkv + 2 * d + h * DH);
+  const unsigned row_bytes = (unsigned)ld * 2, last_row = (unsigned)(k_last - 1) * row_bytes;
+  unsigned k_row = (unsigned)(k_first + m) * row_bytes, v_row = (unsigned)(k_first + lane / CH * 2) * row_bytes;
+  half8_t kf[QS], vr[NB][2];
+  auto request_keys = [&] {
+    const unsigned at = min(k_row, last_row) + hi * 16;
+#pragma unroll
+    for (int i = 0; i < QS; ++i) kf[i] = *reinterpret_cast<const half8_t*>(kbase + (at + i * 32));
+    k_row += 32 * row_bytes;
+  };
+  auto request_values = [&] {
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        vr[t][e] = *reinterpret_cast<const half8_t*>(vbase + (min(v_row + (unsigned)(128 / CH * t + e) * row_bytes, last_row) + lane % CH * 16));
+    v_row += 32 * row_bytes;
+  };
+  request_keys();
+  request_values();
+  if (Kc) {   // the rows' own keys and values: read behind the first block's, most of them the same lines
+#pragma unroll
+    for (int t = 0; t < DH / 16; ++t) {
+      const int row = t * (64 / CH) + lane / CH, at = blk * 32 + row;
+      const int sent = __shfl(b, row, kWave), pos = at - __shfl(lo, row, kWave);
+      if (at < rows) {
+        const half_t* from = qkv + (size_t)at * ld + d + h * DH + lane % CH * 8;
+        const size_t to = ((size_t)sent * T_ + pos) * d + h * DH + lane % CH * 8;
+        *reinterpret_cast<half8_t*>(Kc + to) = *reinterpret_cast<const half8_t*>(from);
+        *reinterpret_cast<half8_t*>(Vc + to) = *reinterpret_cast<const half8_t*>(from + d);
+      }
+    }
+  }
   floatx16 o[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
@@ -1352,48 +1404,54 @@ __global__ void __launch_bounds__(256) encoder_attention_mfma_kernel(const half_
     for (int e = 0; e < 16; ++e) o[nb][e] = 0.f;
   float mx = -INFINITY, sum = 0.f;
   for (int k0 = k_first; k0 < k_last; k0 += 32) {
-    // operands of this key block: K rows (key = k0 + m), V gathered in the order the scores come out
-    const int krow = min(k0 + m, k_last - 1);
-    half8_t kf[QS];
-#pragma unroll
-    for (int i = 0; i < QS; ++i) kf[i] = *reinterpret_cast<const half8_t*>(kbase + (size_t)krow * ld + i * 16);
-    half8_t vf[NB][2];
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int key = min(k0 + 16 * st + 8 * (j >> 2) + 4 * hi + (j & 3), k_last - 1);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) vf[nb][st][j] = vbase[(size_t)key * ld + nb * 32];
-      }
     floatx16 sc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) sc[e] = 0.f;
 #pragma unroll
     for (int i = 0; i < QS; ++i) sc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[i], qf[i], sc, 0, 0, 0);
+    const bool more = k0 + 32 < k_last;
+    if (more) request_keys();
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+      const int p = lane / CH + 64 / CH * t, q = p & 7;   // keys 16 (p >> 3) + 2 q, + 1
+      const int word = (p >> 3) * 8 + (q >> 1 & 1) * 4 + (q >> 2) * 2 + (q & 1);
+      const u32x4 a = __builtin_bit_cast(u32x4, vr[t][0]), c = __builtin_bit_cast(u32x4, vr[t][1]);
+      unsigned* to = mine + (lane % CH) * (8 * LD + SKEW) + word;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        to[(2 * i) * LD] = __builtin_amdgcn_perm(c[i], a[i], 0x05040100);       // low halves: (key 2 q, key 2 q + 1)
+        to[(2 * i + 1) * LD] = __builtin_amdgcn_perm(c[i], a[i], 0x07060302);   // high halves
+      }
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();   // read by other lanes of this wavefront (LDS keeps a wavefront's order)
+    if (more) request_values();
     // sc[vg * 4 + e] = q_m . k_key, key = k0 + vg * 8 + hi * 4 + e
     float bm = -INFINITY;
 #pragma unroll
-    for (int vg = 0; vg < 4; ++vg)
+    for (int e = 0; e < 16; ++e) sc[e] *= scale_log2e;
+    if (k0 < all_from || k0 + 32 > all_to) {              // somewhere a key does not count
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int key = k0 + vg * 8 + hi * 4 + e;
-        const float v = (key >= lo && key < hi_key) ? sc[vg * 4 + e] * scale_log2e : -INFINITY;
-        sc[vg * 4 + e] = v;
-        bm = fmaxf(bm, v);
+      for (int e = 0; e < 16; ++e) {
+        const int key = k0 + (e >> 2) * 8 + hi * 4 + (e & 3);
+        sc[e] = key >= lo && key < hi_key ? sc[e] : -INFINITY;
       }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) bm = fmaxf(bm, sc[e]);
     bm = max_lane_xor<32>(bm);                            // the row's other 16 keys are in lane ^ 32
     const float mn = fmaxf(mx, bm);
     const float base = mn == -INFINITY ? 0.f : mn;        // no key of this block (or any before) counts for the row
-    const float corr = exp2f(mx - base);                  // mx = -inf: 0
+    const float corr = __builtin_amdgcn_exp2f(mx - base);                  // mx = -inf: 0
     float ps = 0.f;
     half8_t pf[2];
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const float pv = exp2f(sc[st * 8 + j] - base);
-        const half_t ph = (half_t)pv;
+        const float pv = __builtin_amdgcn_exp2f(sc[st * 8 + j] - base);
+        const half_t ph = (half_t)pv;                         // (what the instruction takes for 0 is 0 in float16)
         ps += (float)ph;                                  // the sum of what the second product multiplies
         pf[st][j] = ph;
       }
@@ -1405,8 +1463,14 @@ __global__ void __launch_bounds__(256) encoder_attention_mfma_kernel(const half_
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[nb][e] *= corr;
 #pragma unroll
-      for (int st = 0; st < 2; ++st) o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[nb][st], pf[st], o[nb], 0, 0, 0);
+      for (int st = 0; st < 2; ++st) {
+        const int dim = nb * 32 + m;
+        const half8_t vf = *reinterpret_cast<const half8_t*>(mine + dim * LD + (dim >> 3) * SKEW + st * 8 + hi * 4);
+        o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[st], o[nb], 0, 0, 0);
+      }
     }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
   }
   if (blk * 32 + m >= rows) return;
   const float inv = 1.0f / sum;
@@ -1518,19 +1582,23 @@ hipError_t launch_cross_attention(int dtype, const void* q, const void* kv, cons
 
 template <typename T>
 static hipError_t enc_t(const T* qkv, const int32_t* row_sent, const int32_t* off, const int32_t* len, T* out,
-                        int rows, int H, int d, int causal, hipStream_t s) {
+                        int rows, int H, int d, int causal, hipStream_t s, T* Kc, T* Vc, const int32_t* pos, int T_) {
   int dh = d / H;
   float scale = 1.0f / sqrtf((float)dh);
   if constexpr (std::is_same<T, half_t>::value) {
     if ((dh == 32 || dh == 64 || dh == 128) && d % 8 == 0 && (reinterpret_cast<uintptr_t>(qkv) & 15) == 0 &&
         (reinterpret_cast<uintptr_t>(out) & 7) == 0) {
-      dim3 g((((rows + 31) / 32) * H + 3) / 4), b(256);
+      dim3 g(((rows + 31) / 32 + 3) / 4 * H), b(256);
       const float sl = scale * 1.4426950408889634f;
-      if (dh == 32) encoder_attention_mfma_kernel<32><<<g, b, 0, s>>>(qkv, row_sent, off, len, out, rows, H, d, causal, sl);
-      else if (dh == 64) encoder_attention_mfma_kernel<64><<<g, b, 0, s>>>(qkv, row_sent, off, len, out, rows, H, d, causal, sl);
-      else encoder_attention_mfma_kernel<128><<<g, b, 0, s>>>(qkv, row_sent, off, len, out, rows, H, d, causal, sl);
+      if (dh == 32) encoder_attention_mfma_kernel<32><<<g, b, 0, s>>>(qkv, row_sent, off, len, out, rows, H, d, causal, sl, Kc, Vc, T_);
+      else if (dh == 64) encoder_attention_mfma_kernel<64><<<g, b, 0, s>>>(qkv, row_sent, off, len, out, rows, H, d, causal, sl, Kc, Vc, T_);
+      else encoder_attention_mfma_kernel<128><<<g, b, 0, s>>>(qkv, row_sent, off, len, out, rows, H, d, causal, sl, Kc, Vc, T_);
       return hipGetLastError();
     }
+  }
+  if (Kc) {
+    const hipError_t e = launch_scatter_kv(std::is_same<T, half_t>::value ? DT_F16 : DT_F32, qkv, row_sent, pos, Kc, Vc, rows, d, T_, s);
+    if (e != hipSuccess) return e;
   }
   dim3 g((rows * H + 3) / 4), b(256);
   LSQ_DISPATCH_DH(dh, (encoder_attention_kernel<T, DH><<<g, b, 0, s>>>(qkv, row_sent, off, len, out, rows, H, d, causal, scale)));
@@ -1539,12 +1607,12 @@ static hipError_t enc_t(const T* qkv, const int32_t* row_sent, const int32_t* of
 
 hipError_t launch_encoder_attention(int dtype, const void* qkv, const int32_t* row_sent, const int32_t* off,
                                     const int32_t* len, void* out, int rows, int H, int d, int causal,
-                                    hipStream_t s) {
+                                    hipStream_t s, void* Kc, void* Vc, const int32_t* pos, int T) {
   if (rows <= 0) return hipSuccess;
   if ((long)rows * 3 * d * 4 > 0xffffffffL) return hipErrorInvalidValue;   // a lane's byte offset inside a sentence is 32 bits wide
   if (dtype == DT_F16)
-    return enc_t<half_t>((const half_t*)qkv, row_sent, off, len, (half_t*)out, rows, H, d, causal, s);
-  return enc_t<float>((const float*)qkv, row_sent, off, len, (float*)out, rows, H, d, causal, s);
+    return enc_t<half_t>((const half_t*)qkv, row_sent, off, len, (half_t*)out, rows, H, d, causal, s, (half_t*)Kc, (half_t*)Vc, pos, T);
+  return enc_t<float>((const float*)qkv, row_sent, off, len, (float*)out, rows, H, d, causal, s, (float*)Kc, (float*)Vc, pos, T);
 }
 
 }  // namespace lsq

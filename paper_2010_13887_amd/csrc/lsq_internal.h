@@ -157,9 +157,11 @@ bool cross_attention_q_worthwhile(int batch, int beam, int H);   // where it is 
 hipError_t launch_cross_attention_q(const void* x, const void* Wq_packed, const void* bq, const void* kv,
                                     const int32_t* off, const int32_t* len, void* out, int batch, int beam, int H,
                                     int d, hipStream_t s);
+// Kc, Vc given: the rows' keys and values also go to the cache, [sentence][T positions][d]; pos[row] = row - off[its sentence]
 hipError_t launch_encoder_attention(int dtype, const void* qkv, const int32_t* row_sent,
                                     const int32_t* off, const int32_t* len, void* out, int rows, int H,
-                                    int d, int causal, hipStream_t s);
+                                    int d, int causal, hipStream_t s, void* Kc = nullptr, void* Vc = nullptr,
+                                    const int32_t* pos = nullptr, int T = 0);
 
 // All decoder layers of a step in one launch (kernels_stack.hip).  Matrices: fragment-ordered copies; the
 // pointers are those of layer 0, layer l's lie packed_stride / plain_stride bytes further on for each layer.

@@ -1128,8 +1128,7 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
       const GptLayer& L = g.gpt[l];
       char* Kc = g.ws + p.cache + (size_t)(2 * l) * slab;
       HIPCHK(launch_gemm(dt, y, L.Wqkv, L.bqkv, plain_out(qkv, 3 * d), R, 3 * d, d, 0, s));
-      HIPCHK(launch_scatter_kv(dt, qkv, sent, pos, Kc, Kc + slab, R, d, T, s));
-      HIPCHK(launch_encoder_attention(dt, qkv, sent, at<int32_t>(p.src_off), at<int32_t>(p.src_len), ctx, R, H, d, 1, s));
+      HIPCHK(launch_encoder_attention(dt, qkv, sent, at<int32_t>(p.src_off), at<int32_t>(p.src_len), ctx, R, H, d, 1, s, Kc, Kc + slab, pos, T));
       if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln2g, L.ln2b, x, y, (float*)tmp, R, d, d, 1, s)) return rc;
       HIPCHK(launch_gemm(dt, y, L.W1, L.b1, plain_out(ffn, F), R, F, d, 2, s));
       const bool last = l + 1 == hp.n_dec;
