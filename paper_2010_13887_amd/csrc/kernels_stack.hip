@@ -1190,6 +1190,25 @@ StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool di
   return many ? kStackMany : kStackNone;
 }
 
+// More rows than `stack_kind` has a kernel for as two launches, one after the other, of the kernel for 17 to 128 of them.  d = 1024, sources of 30 tokens, whole
+// steps in us, two launches / separate launches:
+//   positions          5-25        25-50       50-75
+//   beam 4, 132 rows   351 / 409   361 / 414   374 / 427
+//           160        374 / 415   393 / 425   408 / 437
+//           192        394 / 431   418 / 440   434 / 455
+//           208        412 / 434   439 / 444   453 / 461
+//           224        424 / 441   450 / 453   463 / 466
+//           256        444 / 445   469 / 459   484 / 474
+//   beam 5, 160        370 / 432   387 / 440   400 / 452
+//           200        402 / 441   426 / 451   441 / 466
+//   beam 2, 160        392 / 425   407 / 435   423 / 446
+//           200        417 / 436   442 / 446   458 / 459
+// A position costs two launches 0.8 us and the separate ones 0.55; the rows of a sentence share less of their history where there are two of
+// them.  The lines are where these lead to; a source key counts as half a position.
+bool stack_twice(int arch, int M, int d, int beam, int pos, int src) {
+  return arch == 0 && d == 1024 && beam >= 2 && M <= 208 && pos + src / 2 <= 105 + 2 * (208 - M) - (beam == 2 ? 40 : 0);
+}
+
 bool stream_has_every_cu(hipStream_t s) {
   for (const char* name : {"HSA_CU_MASK", "ROC_GLOBAL_CU_MASK"}) {   // masks for every queue of the process
     const char* v = std::getenv(name);

@@ -197,6 +197,7 @@ enum StackKind { kStackNone, kStackDie, kStackFew, kStackMany, kStackF32 };
 // of a supported shape: which kernel takes these rows on the current device, at a history of `pos` positions and sources of at most `src` tokens
 // dies: die_placement has found every workgroup where the die kernels want it
 StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool dies);
+bool stack_twice(int arch, int M, int d, int beam, int pos, int src);   // more rows than that: whether two launches are ahead of the separate kernels
 hipError_t launch_stack_reset(char* exchange, size_t bytes, int32_t* state, hipStream_t s);   // both sets, at init
 hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s);   // as if a wait had run out
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);

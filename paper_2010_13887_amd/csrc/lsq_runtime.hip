@@ -516,6 +516,14 @@ StackKind use_stack(int M) {
   return stack_kind(g.hp.arch, M, g.hp.d, g.beam, pos, src, g.dies);
 }
 
+// Rows that one launch of a stack kernel takes of M (0: the separate kernels do): all of them, or, where two launches are ahead
+// (stack_twice), the larger half in whole sentences.
+int stack_part(int M) {
+  if (use_stack(M)) return M;
+  const int k = g.beam, half = (M / k + 1) / 2 * k;
+  return g.hp.dtype == DT_F16 && stack_twice(g.hp.arch, M, g.hp.d, k, history(), g.src_longest) && use_stack(half) && use_stack(M - half) ? half : 0;
+}
+
 // plain beam search with a small model: the whole step in one launch.  Up to as many sentences as the chip runs at once:
 // a workgroup's step takes as long as the separate launches of some hundred rows.
 // ahead: of the step so many steps from now.
@@ -643,11 +651,16 @@ int launch_step(int B, int small) {
                                              0, step, T, s));
     return LSQ_OK;
   }
-  const StackKind stack = use_stack(M);
-  if (stack) {
+  const int part = stack_part(M);
+  const bool stack = part > 0;
+  for (int r0 = 0; r0 < M && stack; r0 += part) {   // sentences meet nowhere in it: one launch after the other
     StackArgs a = g.stack;
-    a.M = M; a.anc = anc; a.x0 = (const half_t*)x0; a.hidden = (half_t*)x_home;
-    TIMED(PC_STACK, launch_stack(stack, a));
+    a.M = std::min(part, M - r0);
+    a.anc = anc ? anc + (size_t)r0 * a.anc_ld : nullptr;
+    a.x0 = (const half_t*)(x0 + (size_t)r0 * d * es); a.hidden = (half_t*)(x_home + (size_t)r0 * d * es);
+    a.cache += (size_t)r0 * T * d * es;
+    a.src_off += r0 / k; a.src_len += r0 / k;
+    TIMED(PC_STACK, launch_stack(use_stack(a.M), a));
     x = x_home;
   }
   for (int l = 0; l < (stack ? 0 : hp.n_dec); ++l) {
@@ -922,7 +935,7 @@ int enqueue_step(int most) {
   const int B = g.alive_at[g.t], small = small_steps(most);
   auto launch = [&](int n) { return g.hp.arch == 1 ? launch_step_gpt(n) : launch_step(n, small); };
   g.hidden_in_alt = false;   // launch_step says otherwise
-  if (!g.use_graphs || g.stream == nullptr || g_prof.on || use_stack(B * g.beam) || small) {
+  if (!g.use_graphs || g.stream == nullptr || g_prof.on || stack_part(B * g.beam) || small) {
     int rc = launch(B);
     if (rc) return rc;
     g.t += std::max(small, 1);
