@@ -192,6 +192,17 @@ struct Plan {
 
 size_t packed_weight_bytes(const HParams& hp);
 
+// Source rows up to which the encoder's (the prefill's) output projections and second FFN products are split over k: 32 to 512 workgroups instead of
+// the 16 to 100 that their tiles are.  Encodings in us, split / not, rows     25        50        100       136       280       400       512
+//   Transformer-base                                                      210/235   250/294   243/272   249/274   274/299   285/308   291/317
+//   Transformer-big                                                       253/304   282/342   290/345   312/360   360/396   378/412   378/406
+//   d = 768 decoder-only, 12 layers (with the prompt's cache rows stored
+//   by the attention kernel, 20 to 40 us of it)                           371/495   443/551   471/564   501/591   533/602   591/628   577/619
+// From some 570 rows on the tiles fill the chip (gemm_partial_splits).  Decoder-only models stop at 256: a sampled text hangs on the order of sums now
+// and then, and beyond there is little to be had for it.
+constexpr int kEncoderSplitRows = 512;
+int encoder_splits(int arch, int R) { return R <= (arch == 1 ? kEncoderSplitRows / 2 : kEncoderSplitRows) ? (int)kMaxSplits : 1; }
+
 Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   Plan p;
   const size_t esz = hp.dtype == DT_F16 ? 2 : 4;
@@ -242,8 +253,8 @@ Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   auto etake = [&](size_t bytes) { size_t o = e; e += up(bytes); return o; };
   p.e_ids = etake(R * 4); p.e_pos = etake(R * 4); p.e_sent = etake(R * 4);
   p.e_x = etake(R * d * esz); p.e_qkv = etake(R * 3 * d * esz); p.e_ctx = etake(R * d * esz);
-  p.e_tmp = etake(R * d * 4); p.e_ffn = etake(R * F * esz);
-  p.e_y = etake(R * d * esz);     // pre-LN models: normalised copy of the residual stream   // e_tmp: one fp32 slab (no split-K at encoder sizes)
+  p.e_tmp = etake(std::max(R, kMaxSplits * std::min<size_t>(R, kEncoderSplitRows)) * d * 4); p.e_ffn = etake(R * F * esz);
+  p.e_y = etake(R * d * esz);     // pre-LN models: normalised copy of the residual stream   // e_tmp: fp32 slabs, one from kEncoderSplitRows rows on
   // decoder phase
   size_t q = p.scratch;
   auto dtake = [&](size_t bytes) {
@@ -1142,11 +1153,11 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
       char* Kc = g.ws + p.cache + (size_t)(2 * l) * slab;
       HIPCHK(launch_gemm(dt, y, L.Wqkv, L.bqkv, plain_out(qkv, 3 * d), R, 3 * d, d, 0, s));
       HIPCHK(launch_encoder_attention(dt, qkv, sent, at<int32_t>(p.src_off), at<int32_t>(p.src_len), ctx, R, H, d, 1, s, Kc, Kc + slab, pos, T));
-      if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln2g, L.ln2b, x, y, (float*)tmp, R, d, d, 1, s)) return rc;
+      if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln2g, L.ln2b, x, y, (float*)tmp, R, d, d, encoder_splits(hp.arch, R), s)) return rc;
       HIPCHK(launch_gemm(dt, y, L.W1, L.b1, plain_out(ffn, F), R, F, d, 2, s));
       const bool last = l + 1 == hp.n_dec;
       if (int rc = sublayer(-1, ffn, L.W2, L.b2, last ? g.lnfg : g.gpt[l + 1].ln1g, last ? g.lnfb : g.gpt[l + 1].ln1b,
-                            x, y, (float*)tmp, R, d, F, 1, s)) return rc;
+                            x, y, (float*)tmp, R, d, F, encoder_splits(hp.arch, R), s)) return rc;
     }
   }
   for (size_t c : p.dec_canaries) HIPCHK(hipMemsetAsync(g.ws + c, kCanaryByte, kCanaryBytes, s));
@@ -1184,9 +1195,9 @@ int run_encoder(int batch, int R) {
   for (const EncLayer& L : g.enc) {
     HIPCHK(launch_gemm(dt, x, L.Wqkv, L.bqkv, plain_out(qkv, 3 * d), R, 3 * d, d, 0, s));
     HIPCHK(launch_encoder_attention(dt, qkv, sent, off, len, ctx, R, H, d, 0, s));
-    if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln1g, L.ln1b, x, nullptr, (float*)tmp, R, d, d, 1, s)) return rc;
+    if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln1g, L.ln1b, x, nullptr, (float*)tmp, R, d, d, encoder_splits(hp.arch, R), s)) return rc;
     HIPCHK(launch_gemm(dt, x, L.W1, L.b1, plain_out(ffn, F), R, F, d, 1, s));
-    if (int rc = sublayer(-1, ffn, L.W2, L.b2, L.ln2g, L.ln2b, x, nullptr, (float*)tmp, R, d, F, 1, s)) return rc;
+    if (int rc = sublayer(-1, ffn, L.W2, L.b2, L.ln2g, L.ln2b, x, nullptr, (float*)tmp, R, d, F, encoder_splits(hp.arch, R), s)) return rc;
   }
   const size_t cross_l = (size_t)g.max_batch * g.max_len * 2 * d * es;   // layer stride of the maximum shape
   for (int l = 0; l < hp.n_dec; ++l)
@@ -1489,7 +1500,7 @@ int lsq_decode_all(int n) {
       int rc = enqueue_step(g.max_len);   // small models: every sentence of a launch stops where it is finished
       if (rc) return rc;
     }
-    seen = std::min(next, g.t);
+      seen = std::min(next, g.t);
     int active = 0;
     int rc = read_active(seen, &active);
     if (rc) return rc;
