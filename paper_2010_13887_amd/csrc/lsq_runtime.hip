@@ -337,6 +337,7 @@ struct Ctx {
   int batch = 0, rows_enc = 0, t = 0;
   int src_longest = 1;         // longest source sentence of this translation
   bool done = false;
+  int finalized = -1;          // steps of this translation behind which its results are already on their way (queue_results_early)
   std::vector<int> order;      // internal (sorted) sentence index -> caller's index
   bool use_graphs = true;
   int refresh_mode = 1;   // how the next lsq_encode keeps the cache in step with the beams: 0 move rows, 1 slab table
@@ -1062,6 +1063,7 @@ int decode_again() {
   const int steps = g.t;
   if (int rc = drop_stack()) return rc;
   g.page->step = 0;
+  g.finalized = -1;
   if (g.hp.arch == 1) {
     Staging st{};
     GptStart().stage(st, g.batch);
@@ -1071,6 +1073,24 @@ int decode_again() {
   }
   for (g.t = 0; g.t < steps;)
     if (int rc = enqueue_step(steps - g.t)) return rc;
+  return LSQ_OK;
+}
+
+hipError_t queue_results(int32_t* ids, int32_t* lens, float* scores) {
+  const Plan& p = g.plan;
+  return launch_finalize(at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), ids, lens, scores, at<int32_t>(p.order), g.batch,
+                         g.beam, g.max_len, g.hp.arch == 1 ? 0.0f : g.hp.alpha, g.hp.pad, g.hp.arch == 1 ? g.prompt_len : 1, g.stream);
+}
+
+// Once no step is left to be issued, the results follow the last one without waiting for the host to see it end and the caller to ask for
+// them.  8 steps of the tiny model 274 -> 266 us, 16 steps behind 32 prompts 6460 -> 6435; a translation that is waited for after every step
+// gains little, since its results are there too soon (asking the stream instead of waiting for it: 266 -> 291).
+int queue_results_early() {
+  if (!g.results || g.finalized == g.t || (g.t < g.max_len && g.alive_at[g.t] > 0)) return LSQ_OK;
+  const size_t M = (size_t)g.batch * g.beam;
+  int32_t* lens = g.results + M * g.max_len;
+  HIPCHK(queue_results(g.results, lens, (float*)(lens + M)));
+  g.finalized = g.t;
   return LSQ_OK;
 }
 
@@ -1166,6 +1186,7 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
   g.prompt_len = P;
   g.t = 0;
   g.done = false;
+  g.finalized = -1;
   g.state = 3;
   return LSQ_OK;
 }
@@ -1467,6 +1488,7 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
   g.src_longest = longest;
   g.t = 0;
   g.done = false;
+  g.finalized = -1;
   g.state = 3;
   return LSQ_OK;
 }
@@ -1482,6 +1504,7 @@ int lsq_decode_steps(int n) {
     int rc = enqueue_step((int)std::min<int64_t>(end - g.t, g.max_len));
     if (rc) return rc;
   }
+  if (int rc = queue_results_early()) return rc;
   int active = 0;
   int rc = read_active(g.t, &active);
   if (rc) return rc;
@@ -1500,7 +1523,8 @@ int lsq_decode_all(int n) {
       int rc = enqueue_step(g.max_len);   // small models: every sentence of a launch stops where it is finished
       if (rc) return rc;
     }
-      seen = std::min(next, g.t);
+    if (int rc = queue_results_early()) return rc;
+    seen = std::min(next, g.t);
     int active = 0;
     int rc = read_active(seen, &active);
     if (rc) return rc;
@@ -1644,9 +1668,8 @@ int lsq_get_beams(int32_t* out_ids, int32_t* out_lens, float* out_scores) {
   int32_t* lens = g.results ? ids + (size_t)M * T : at<int32_t>(p.out_lens);
   float* scores = g.results ? (float*)(lens + M) : at<float>(p.out_scores);
   for (;;) {
-    HIPCHK(launch_finalize(at<float>(p.score), at<int32_t>(p.tokens), at<int32_t>(p.len), ids, lens, scores, at<int32_t>(p.order),
-                           g.batch, g.beam, T, g.hp.arch == 1 ? 0.0f : g.hp.alpha, g.hp.pad, g.hp.arch == 1 ? g.prompt_len : 1,
-                           g.stream));
+    if (!g.results || g.finalized != g.t) HIPCHK(queue_results(ids, lens, scores));
+    g.finalized = -1;
     if (!g.results) {
       HIPCHK(hipMemcpyAsync(out_ids, ids, (size_t)M * T * 4, hipMemcpyDeviceToHost, g.stream));
       HIPCHK(hipMemcpyAsync(out_lens, lens, (size_t)M * 4, hipMemcpyDeviceToHost, g.stream));
