@@ -5,7 +5,7 @@
 // activation buffer, K and V straight into the caches) are fused into the epilogue.
 #include <unordered_map>
 
-#include "lsq_internal.h"
+#include "vocabulary_block.h"
 
 namespace lsq {
 
@@ -1007,37 +1007,6 @@ __global__ void __launch_bounds__(256) gemm_f16_skinny_kernel(const half_t* __re
 }
 
 // ---------------------------------------------------------------------------------------------
-// The end of the two kernels below: a wavefront's block of 32 columns, lane: row m, columns 8 vg + 4 (lane >> 5) + 0..3.
-__device__ __forceinline__ void vocabulary_block(const floatx16 (&acc)[4], const GemmOut& out, int m, int block, int M, int N, int vec_ok,
-                                                 long tp, int lane) {
-  float mx = -INFINITY, z = 0.f;
-#pragma unroll
-  for (int vg = 0; vg < 4; ++vg) {
-    const int n = block * 32 + vg * 8 + (lane >> 5) * 4;
-    float v[4], vm = -INFINITY, vz = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]);
-    if (m < M && n < N) store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp);
-    if (!out.stats) continue;
-    // as in gemm_f16_skinny_kernel, whose wavefronts have eight columns each
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (n + e < N) vm = fmaxf(vm, v[e]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (n + e < N) vz += __expf(v[e] - vm);
-    const float m2 = lane_xor<32>(vm), z2 = lane_xor<32>(vz);
-    merge_stat(vm, vz, m2, z2);
-    if (vg == 0) { mx = vm; z = vz; }
-    else merge_stat(mx, z, vm, vz);
-  }
-  if (out.stats && lane < 32 && m < M) {
-    float* st = out.stats + ((size_t)m * out.stats_groups + block) * 2;
-    st[0] = mx;
-    st[1] = z;
-  }
-}
-
 // The vocabulary product of 9 to 32 rows (float output, no bias, weights in fragment order): a stream of 50 to 130 MB.
 // In the kernel above every 32 columns bring the input rows along, as many bytes as their weights and in pieces of 32 bytes (32 rows
 // of d = 768), and 50257 columns are one and a half rounds of its workgroups.  Here one workgroup per compute unit puts the rows into
@@ -1088,7 +1057,8 @@ __global__ void __launch_bounds__(T) gemm_f16_stream_kernel(const half_t* __rest
     if (ks + P < KS) w[ks % P] = request(ks + P);
     if ((ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
-  vocabulary_block(acc, out, m, block, M, N, vec_ok, tp, lane);
+  vocabulary_block([&](int vg, int e) { return (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]); },
+                   [&](int n, const float (&v)[4]) { store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp); }, out.stats, out.stats_groups, m, block, M, N, lane);
 }
 
 constexpr int kStreamGrid = 256;   // one workgroup per compute unit, of at most eight wavefronts with a block of 32 columns each
@@ -1315,7 +1285,8 @@ __global__ void __launch_bounds__(T) gemm_f32_vocabulary_kernel(const float* __r
     if (ks + P < KS) w[ks % P] = request(ks + P);
     if ((ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
-  vocabulary_block(acc, out, m, block, M, N, vec_ok, tp, lane);
+  vocabulary_block([&](int vg, int e) { return (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]); },
+                   [&](int n, const float (&v)[4]) { store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp); }, out.stats, out.stats_groups, m, block, M, N, lane);
 }
 
 // ---------------------------------------------------------------------------------------------

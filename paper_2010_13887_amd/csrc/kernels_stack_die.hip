@@ -30,11 +30,15 @@
 // The exchange itself is that of kernels_stack.hip too: data that is its own flag.
 #include "die_count.h"
 #include "stack_attend.h"
+#include "vocabulary_block.h"
 
 namespace lsq {
 
 namespace {
 
+constexpr int kVocabularyRows = 8;     // largest group, and most rows in all, of a launch that takes the vocabulary product along
+constexpr int kVocabularyMax = 32;
+constexpr int kVocabularyPace = 20;    // 64 clocks between two of a wavefront's requests: launches of 4 rows 72.3 us with 0, 71.7 with 20, 71.9 with 64
 constexpr int kDieThreads = 1024;      // eight wavefronts that multiply, eight that exchange
 constexpr int kDieLead = 6;            // as kLead: layers of a step in us with 0 / 4 / 6 / 8 / 12: 4 rows 73.0 72.4 70.4 71.6 73.1, 32 rows 85.9 85.4 85.0
                                        // 84.7 85.3, 64 rows 92.9 89.9 90.6 91.3 92.7, 128 rows 109.7 106.7 105.9 106.0 108.5
@@ -81,6 +85,10 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   __shared__ __attribute__((aligned(16))) half_t vec[2][7][D];   // of a layer: gains and shifts, biases
 
   __shared__ uint64_t word;
+  constexpr bool VOC = R <= kVocabularyRows;   // group sizes with which dies may be left over
+  __shared__ __attribute__((aligned(16))) half_t voc_rows[VOC ? kVocabularyMax : 1][D + 8];
+  __shared__ float voc_part[VOC ? kWaves : 1][16][64];
+  __shared__ int ticket, in_vain;
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -95,12 +103,108 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     const uint64_t n = __hip_atomic_fetch_add(count, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (die_launch_ends(n)) {
       *count = 0;
-      state[1 + parity] = now()->groups * R;
+      state[1 + parity] = now()->groups * R + (VOC && now()->V ? 1 : 0);   // the rows for the vocabulary product: in the place of one row more
       __hip_atomic_fetch_xor(state, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!die_groups_there(n + word, now()->groups)) give_up(state, now()->error);
+      const bool helped = !VOC || !now()->V || __hip_atomic_exchange(state + 5, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (kDies - now()->groups) * kDieGroup;
+      if (!helped || !die_groups_there(n + word, now()->groups)) give_up(state, now()->error);
     }
   };
+  const int row_bytes = a.layers * Rg::size * D;
+  const int hidden_at = G * R * row_bytes;   // of the exchange: the rows for the vocabulary product, [row][d], agent scope
   if (grp >= G) {
+    if constexpr (VOC) {
+      if (a.V > 0) {
+        // ================ A die to spare: its workgroups have the vocabulary's columns, in blocks of 32.  A pair of wavefronts has a block, either
+        // half of its k-steps, which wait in registers for the rows: nothing is left to be fetched once these are there.  Which workgroup has which
+        // blocks is drawn, so that it does not depend on how the workgroups were dealt out.  4 rows, 32000 columns: launch 67.3 -> 71.5 us instead of a
+        // product of 6.2 behind it; what is left of it is an exchange over the whole chip, the products' eight dependent steps and the statistics.
+        if (tid == 0) {
+          const int mine = __hip_atomic_fetch_add(now()->state + 5, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          ticket = mine;
+          in_vain = 0;
+          asm volatile("s_waitcnt vmcnt(0)" ::"v"(mine) : "memory");   // before this workgroup is counted as one that has left
+          leave();
+        }
+        workgroup_barrier();
+        const int lane = tid & 63, half = wave & 1, pair = wave >> 1, helpers = (kDies - G) * kDieGroup;
+        const int V = a.V, blocks = (V + 31) / 32, block = __builtin_amdgcn_readfirstlane(ticket) + pair * helpers;
+        const half_t* wp = global(a.Ep) + ((size_t)min(block, blocks - 1) * (D / 16) + half * 2) * 512 + lane * 8;
+        half8_t w[D / 32];   // k-steps 4 q + 2 half + e
+        // (all at once they would be in the way of what the other dies wait for)
+        if (block < blocks) {
+#pragma unroll
+          for (int i = 0; i < D / 32; ++i) {
+            w[i] = *reinterpret_cast<const half8_t*>(wp + ((i >> 1) * 4 + (i & 1)) * 512);
+            pin();
+            __builtin_amdgcn_s_sleep(kVocabularyPace);
+          }
+        }
+        pin();
+        Exchange<> ex;
+        ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
+        ex.polls = seq < 0 ? 1 : kSpinLimit;
+        const int M = a.M;
+        if (wave == 0) {   // a look now and then, until the rows are nearly there
+          u32x4 one;
+          for (int left = ex.polls;;) {
+            one = __builtin_amdgcn_raw_buffer_load_b128(ex.rsrc, M * (D * 2), hidden_at, kAgent);
+            if (__all(max(max(one.x, one.y), max(one.z, one.w)) != kSentinel)) break;
+            if (--left == 0) {
+              in_vain = 1;
+              break;
+            }
+            __builtin_amdgcn_s_sleep(16);
+            asm volatile("" ::: "memory");
+          }
+        }
+        workgroup_barrier();
+        if (in_vain) ex.polls = 1;
+        const int pieces = M * (D / 8);
+        for (int p0 = 0; p0 < pieces; p0 += kDieThreads) {
+          if (p0 + wave * 64 >= pieces) break;
+          const int p = min(p0 + tid, pieces - 1);
+          u32x4 raw[1];
+          ex.wait<0>([&](int) { return hidden_at; }, [&](int) { return p * 16; }, raw);
+          *reinterpret_cast<u32x4*>(&voc_rows[p / (D / 8)][p % (D / 8) * 8]) = raw[0];
+        }
+        workgroup_barrier();
+        // the sums of gemm_f16_skinny_kernel: four of them take the k-steps in turn and are added in pairs
+        const int m = lane & 31;
+        const half_t* xr = &voc_rows[min(m, M - 1)][(lane >> 5) * 8];
+        floatx16 acc[2];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
+        if (block < blocks) {
+#pragma unroll
+          for (int i = 0; i < D / 32; ++i)
+            acc[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[i], *reinterpret_cast<const half8_t*>(xr + ((i >> 1) * 4 + half * 2 + (i & 1)) * 16), acc[i & 1], 0, 0, 0);
+          acc[0] += acc[1];
+          if (half)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) voc_part[pair][e][lane] = acc[0][e];
+        }
+        workgroup_barrier();
+        if (!half && block < blocks) {
+          float other[16];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) other[e] = voc_part[pair][e][lane];
+          float* const out = global(now()->logits) + (size_t)m * V;
+          vocabulary_block([&](int vg, int e) { return acc[0][vg * 4 + e] + other[vg * 4 + e]; },
+                           [&](int n, const float (&v)[4]) {
+                             if ((V & 3) == 0) {
+                               *reinterpret_cast<floatx4*>(out + n) = floatx4{v[0], v[1], v[2], v[3]};
+                             } else {
+#pragma unroll
+                               for (int e = 0; e < 4; ++e)
+                                 if (n + e < V) out[n + e] = v[e];
+                             }
+                           },
+                           global(now()->stats), blocks, m, block, M, V, lane);
+        }
+        ex.report(now()->state, now()->error);
+        return;
+      }
+    }
     if (tid == 0) leave();
     return;
   }
@@ -348,7 +452,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
       *reinterpret_cast<piece_t*>(p + (q * 64 + lane) * VP) = h;
     }
   };
-  auto gather_norm = [&](int l, int region, const half_t* g, const half_t* b, half_t* out_x, half_t* out_y) {
+  auto gather_norm = [&](int l, int region, const half_t* g, const half_t* b, half_t* out_x, half_t* out_y, bool publish = false) {
     half_t g8[NP][VP], b8[NP][VP];
     u32x4 raw[RW * NP];
     const int base = at(l, region);
@@ -380,6 +484,14 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
         }
       }
       normalise(v, g8, b8, o);
+      if (publish) {   // to the other dies
+        Exchange<> all;
+        all.rsrc = ex.rsrc;
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+#pragma unroll
+          for (int i = 0; i < VP; i += 2) all.put2(hidden_at, (r0 + m) * (D * 2) + ((q * 64 + lane) * VP + i) * 2, o[q][i], o[q][i + 1]);
+      }
       put_pieces(xs[m], o);
       if (out_y) put_pieces(out_y + (size_t)(r0 + m) * D, o);
     }
@@ -587,6 +699,11 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
       residual(l, Rg::u2);
     }
     gather_norm(l, PRE ? Rg::u1 : Rg::u2, vec[l & 1][2], vec[l & 1][3], nullptr, nullptr);
+    if (VOC && l + 1 == a.layers && now()->V > 0 && grp == 0 && j == 1 && xt < 4) {   // the rows for the vocabulary product are two exchanges away
+      Exchange<> all;
+      all.rsrc = ex.rsrc;
+      all.put(hidden_at, now()->M * (D * 2) + xt * 4, 0);
+    }
     workgroup_barrier();                                                  // 9
     prepare(l, 4, 6);
     pin();
@@ -612,8 +729,9 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
     residual(l, Rg::u3);
   }
   if (j == 0) {   // the rows for the vocabulary product
-    if constexpr (PRE) gather_norm(a.layers - 1, Rg::u3, a.lnfg, a.lnfb, a.x_out, a.hidden);
-    else gather_norm(a.layers - 1, Rg::u3, vec[(a.layers - 1) & 1][4], vec[(a.layers - 1) & 1][5], nullptr, a.hidden);
+    const bool publish = VOC && now()->V > 0;
+    if constexpr (PRE) gather_norm(a.layers - 1, Rg::u3, a.lnfg, a.lnfb, a.x_out, a.hidden, publish);
+    else gather_norm(a.layers - 1, Rg::u3, vec[(a.layers - 1) & 1][4], vec[(a.layers - 1) & 1][5], nullptr, a.hidden, publish);
   }
   ex.report(a.state, a.error);
 }
@@ -670,9 +788,17 @@ bool die_supported(int arch, int M, int d, int beam, int pos, int src) {
   return pos + src / 2 <= most && resident(die_kernel_of(choose_die(M, beam, pos).R, arch == 1), kDieThreads);
 }
 
+// Groups that leave dies over, whose registers hold the vocabulary: eight blocks of 32 columns a workgroup.
+bool die_takes_vocabulary(int arch, int M, int layers, int beam, int pos, int V) {
+  const DieChoice c = choose_die(M, beam, pos);
+  const int places = layers * (arch == 1 ? Region<true>::size : Region<false>::size) / 2;   // rows of d float16 that the exchange region of one row has room for
+  return M <= min(places - 1, kVocabularyMax) && c.R <= kVocabularyRows && c.groups <= kDies / 2 && (V + 31) / 32 <= kWaves * (kDies - c.groups) * kDieGroup;
+}
+
 size_t die_exchange_bytes(int arch, int M, int d, int layers) {
   // groups of 4 rows: at most M and 8 of them; of 8 and 16: more than half full, and the 8-row groups of kernels_stack.hip
-  const int rows = min(16 * kDies, max(4 * min(kDies, M), 2 * M + 16));
+  // one row more: what the vocabulary product reads
+  const int rows = min(16 * kDies, max(4 * min(kDies, M), 2 * M + 16)) + 1;
   return d == 512 ? (size_t)rows * layers * (arch == 1 ? Region<true>::size : Region<false>::size) * d : 0;
 }
 

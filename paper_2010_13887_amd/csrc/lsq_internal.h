@@ -180,13 +180,17 @@ struct StackArgs {
   half_t *hidden, *x_out;   // normalised rows for the vocabulary product; pre-LN: the residual stream
   char* exchange;           // two sets of set_bytes each
   size_t set_bytes;
-  int32_t* state;           // few rows: [0] set of the next launch, [1 + p] rows of set p to be refilled, [4] arrivals; many:
+  int32_t* state;           // few rows: [0] set of the next launch, [1 + p] rows of set p to be refilled, [4] arrivals ([5] tickets, [6, 7] arrivals: die kernel); many:
                             // [0] slot of the next layer, [1] bytes of the other one to be refilled, [4] arrivals;
                             // both: [0] negative once a wait has run out
   int* error;               // pinned host memory: set when a wait ran out
   int M, beam, layers, T, anc_ld;
   float eps;
   int groups, rows_per_group;   // filled in by the launcher
+  // die kernel: V > 0: the launch also leaves the logits and their group statistics, as the vocabulary product would (die_takes_vocabulary)
+  int V;
+  const half_t* Ep;             // fragment-ordered embedding
+  float *logits, *stats;
 };
 size_t stack_exchange_bytes(int arch, int M, int d, int layers);   // of one set
 bool stack_shape_supported(int dtype, int arch, int H, int d, int F, int layers);
@@ -203,6 +207,7 @@ hipError_t launch_stack_end_waits(int32_t* state, hipStream_t s);   // as if a w
 hipError_t launch_decoder_stack(int arch, const StackArgs& args, int d, hipStream_t s);
 // groups of rows on a die each (kernels_stack_die.hip); exchange region and state are those of launch_decoder_stack
 bool die_supported(int arch, int M, int d, int beam, int pos, int src);   // ... and ahead at this history and these sources
+bool die_takes_vocabulary(int arch, int M, int layers, int beam, int pos, int V);   // ... with dies to spare for the vocabulary product
 size_t die_exchange_bytes(int arch, int M, int d, int layers);   // of one set; 0: no such kernel for this width
 hipError_t launch_decoder_die(int arch, const StackArgs& args, int pos, hipStream_t s);
 // Whether the workgroups of a launch are dealt to the dies in turn.  scratch: 1 KB.  Waits for the stream.

@@ -567,6 +567,17 @@ hipError_t launch_stack(StackKind kind, StackArgs a) {
   return launch_decoder_stack_rows(g.hp.arch, a, g.hp.d, g.stream);
 }
 
+// Whether a launch of a stack kernel leaves the logits and their statistics as well; if so it is told where.
+bool with_vocabulary(StackKind kind, StackArgs* a) {
+  if (kind != kStackDie || !die_takes_vocabulary(g.hp.arch, a->M, g.hp.n_dec, g.beam, history(), g.hp.V)) return false;
+  a->Ep = (const half_t*)gemm_packed_weights(g.E, g.hp.V, g.hp.d);
+  if (!a->Ep) return false;
+  a->V = g.hp.V;
+  a->logits = at<float>(g.plan.d_logits);
+  a->stats = at<float>(g.plan.d_stats);
+  return true;
+}
+
 hipError_t reset_stack() {
   const Plan& p = g.plan;
   int32_t* state = at<int32_t>(p.stack_state);
@@ -663,8 +674,16 @@ int launch_step(int B, int small) {
                                              0, step, T, s));
     return LSQ_OK;
   }
+  // Plain beam search and sampling: the logit product also leaves (largest, sum of exponentials) of every 32 logits of a row,
+  // and the retrieve kernel works from those instead of reading the rows (sec. 2.2, with the product's column
+  // groups as the groups)
+  const bool sampling = hp.sample_topk > 0;
+  const bool from_stats = (sampling && g.sample_fold) ||
+                          (g.topk_stats && (g.groups == 1 || g.merge_rerank) && gemm_writes_stats(dt, M, V, d) &&
+                           topk_groups_supported(V, sampling ? hp.sample_topk : k, sampling ? 1 : 0));
   const int part = stack_part(M);
   const bool stack = part > 0;
+  bool logits_done = false;
   for (int r0 = 0; r0 < M && stack; r0 += part) {   // sentences meet nowhere in it: one launch after the other
     StackArgs a = g.stack;
     a.M = std::min(part, M - r0);
@@ -672,7 +691,9 @@ int launch_step(int B, int small) {
     a.x0 = (const half_t*)(x0 + (size_t)r0 * d * es); a.hidden = (half_t*)(x_home + (size_t)r0 * d * es);
     a.cache += (size_t)r0 * T * d * es;
     a.src_off += r0 / k; a.src_len += r0 / k;
-    TIMED(PC_STACK, launch_stack(use_stack(a.M), a));
+    const StackKind kind = use_stack(a.M);
+    logits_done = from_stats && with_vocabulary(kind, &a);
+    TIMED(PC_STACK, launch_stack(kind, a));
     x = x_home;
   }
   for (int l = 0; l < (stack ? 0 : hp.n_dec); ++l) {
@@ -744,15 +765,9 @@ int launch_step(int B, int small) {
     pending.on = false;
   }
   g.hidden_in_alt = (x != x_home);   // which of the two hidden-state buffers the last LayerNorm wrote
-  // Plain beam search: the logit product also leaves (largest, sum of exponentials) of every 32 logits of a row,
-  // and the retrieve kernel works from those instead of reading the rows (sec. 2.2, with the product's column
-  // groups as the groups)
-  const bool sampling = hp.sample_topk > 0;
-  const bool from_stats = (sampling && g.sample_fold) ||
-                          (g.topk_stats && (g.groups == 1 || g.merge_rerank) && gemm_writes_stats(dt, M, V, d) &&
-                           topk_groups_supported(V, sampling ? hp.sample_topk : k, sampling ? 1 : 0));
   if (from_stats) { lo.stats = at<float>(p.d_stats); lo.stats_groups = (V + 31) / 32; }
-  if (int rc = product(PC_GEMM_VOCAB, g.E, nullptr, lo, V, 0)) return rc;
+  if (!logits_done)
+    if (int rc = product(PC_GEMM_VOCAB, g.E, nullptr, lo, V, 0)) return rc;
   if (hp.sample_topk > 0) {
     // sampling decoding (sec. 3.4): one hypothesis per sentence, nothing to re-rank or to refresh
     if (g.sample_fold) {
@@ -857,10 +872,14 @@ int launch_step_gpt(int B) {
     if (attention_blocks_supported(dt, M, 1, H, d)) nq = 1;
     if (M * H > 256 && M % 2 == 0 && attention_blocks_supported(dt, M, 2, H, d)) nq = 2;
   }
+  // the k largest logits of a row from the product's group statistics (as under beam search, without a normaliser)
+  const bool from_stats = g.topk_stats && gemm_writes_stats(dt, M, V, d) && topk_groups_supported(V, ks, 1);
+  bool logits_done = false;
   const StackKind stack = use_stack(M);
   if (stack) {
     StackArgs a = g.stack;
     a.M = M; a.anc = nullptr; a.hidden = (half_t*)y; a.x_out = (half_t*)x;
+    logits_done = from_stats && with_vocabulary(stack, &a);
     TIMED(PC_STACK, launch_stack(stack, a));
   } else if (nq) {
     char* x_alt = g.ws + p.d_x2;
@@ -914,10 +933,8 @@ int launch_step_gpt(int B) {
   }
   GemmOut lo = plain_out(logits, V);
   lo.f32_out = 1;
-  // the k largest logits of a row from the product's group statistics (as under beam search, without a normaliser)
-  const bool from_stats = g.topk_stats && gemm_writes_stats(dt, M, V, d) && topk_groups_supported(V, ks, 1);
   if (from_stats) { lo.stats = at<float>(p.d_stats); lo.stats_groups = (V + 31) / 32; }
-  TIMED(PC_GEMM_VOCAB, launch_gemm(dt, y, g.E, nullptr, lo, M, V, d, 0, s));
+  if (!logits_done) TIMED(PC_GEMM_VOCAB, launch_gemm(dt, y, g.E, nullptr, lo, M, V, d, 0, s));
   if (from_stats && g.merge_rerank) {
     TIMED(PC_RETRIEVE_RERANK, launch_retrieve_sample((const float*)logits, at<float>(p.d_stats), at<int32_t>(p.tokens),
                                                      at<int32_t>(p.len), at<float>(p.score), at<int32_t>(p.active), step, M, V, ks,

@@ -144,3 +144,33 @@ def test_a_wait_that_ran_out_on_a_die_takes_the_dies_only(lsq, stop):
             if kernels == "chip":
                 assert all(np.array_equal(a, b) for a, b in zip(got, want["chip"]))
         assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("batch,beam,vocab,taken", [
+    (1, 1, 1003, True),       # a block that ends inside its 32 columns and outside a group of 4
+    (1, 4, 7200, True),       # 225 blocks for 224 workgroups: the first one has two
+    (2, 4, 49149, True),      # two groups leave 192 workgroups of eight blocks, 49152 columns
+    (2, 4, 49153, False),
+    (24, 1, 40960, True),     # most rows; three groups: 40960 columns
+    (25, 1, 1003, False),     # no die to spare
+])
+def test_dies_to_spare_take_the_vocabulary_product(lsq, batch, beam, vocab, taken):
+    """Its logits against the oracle's, and the same bits as the separate product: row by row the same translation."""
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=512, n_heads=8, d_ffn=2048, vocab=vocab, max_pos=32, dtype=1, cap_extra=3)
+    w = S.custom(hp, [1 + (5 * i) % 7 for i in range(batch)], beam=beam, max_len=12, std=0.03, seed=batch)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, batch, beam, 12) as eng:
+        lsq.lsq_profile_enable(True)
+        lockstep(lsq, eng, blob, w, max_steps=3, sentences=[batch - 1])
+        launches = lsq.lsq_profile_read()
+        lsq.lsq_profile_enable(False)
+        assert launches["decoder_stack"][1] == 3 and launches["gemm_vocab"][1] == (0 if taken else 3)
+        logits = eng.debug(lsq.DBG.LOGITS, (batch * beam, vocab))
+        hidden = torch.from_numpy(eng.debug(lsq.DBG.HIDDEN, (batch * beam, 512))).half().cuda()
+        E = torch.from_numpy(np.frombuffer(blob, np.float16, vocab * 512, 256).reshape(vocab, 512).copy()).cuda()
+        separate = torch.empty(batch * beam, vocab, dtype=torch.float32, device="cuda")
+        packed = lsq.k_pack_weights(E)
+        lsq.k_gemm(hidden, packed, None, separate, packed=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(separate.cpu().numpy(), logits)
+        assert lsq.lsq_debug_check_canaries() == 0
