@@ -788,7 +788,14 @@ bool die_supported(int arch, int M, int d, int beam, int pos, int src) {
   return pos + src / 2 <= most && resident(die_kernel_of(choose_die(M, beam, pos).R, arch == 1), kDieThreads);
 }
 
-// Groups that leave dies over, whose registers hold the vocabulary: eight blocks of 32 columns a workgroup.
+// Groups that leave dies over, whose registers hold the vocabulary: eight blocks of 32 columns a workgroup.  Whole steps in us, a product of its own / here, V = 32 000,
+// sources of 30 tokens:
+//   positions                  5-25           25-50          50-75          75-110         110-200        200-300
+//    4 rows, beam 4         82.1 / 79.4    81.1 / 79.2    81.7 / 79.7    82.9 / 80.8    85.9 / 83.8    92.5 / 90.3
+//   12 rows, beam 4         85.6 / 84.0    85.7 / 84.0    86.2 / 84.6    86.8 / 85.2    89.8 / 88.0    96.7 / 95.4
+//   24 rows, beam 4         93.4 / 90.5    93.7 / 91.1    95.4 / 92.4    97.6 / 94.6   102.6 / 101.5  109.6 / 109.4
+//   24 rows, one per sentence 92.3 / 89.9  94.0 / 91.8    96.4 / 94.6    99.4 / 97.7
+// (1 row 75.7 / 74.1.)  Where groups of 4 or 8 need more than four dies the rest of the registers would not hold 32 000 columns.
 bool die_takes_vocabulary(int arch, int M, int layers, int beam, int pos, int V) {
   const DieChoice c = choose_die(M, beam, pos);
   const int places = layers * (arch == 1 ? Region<true>::size : Region<false>::size) / 2;   // rows of d float16 that the exchange region of one row has room for
