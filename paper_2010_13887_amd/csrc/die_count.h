@@ -19,4 +19,16 @@ constexpr bool die_groups_there(uint64_t after, int groups) {
   return true;
 }
 
+// A workgroup of a die to spare that goes on behind its word (it has the vocabulary product): the last workgroup of the launch to add its word moves
+// the launch counter on, which says which of the two sets this launch exchanges in.  So only the first thread looks at the counter, draws the
+// workgroup's columns and hands both on to the other wavefronts; `leave` adds the word once look and draw are over (both are complete when the
+// function that is passed returns).
+template <typename Look, typename Draw, typename Hand, typename Leave>
+constexpr void die_spare_signs_off(Look look, Draw draw, Hand hand, Leave leave) {
+  const int seq = look();
+  const int columns = draw();
+  hand(seq, columns);
+  leave();
+}
+
 }  // namespace lsq

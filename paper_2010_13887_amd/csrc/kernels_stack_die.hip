@@ -88,7 +88,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
   constexpr bool VOC = R <= kVocabularyRows;   // group sizes with which dies may be left over
   __shared__ __attribute__((aligned(16))) half_t voc_rows[VOC ? kVocabularyMax : 1][D + 8];
   __shared__ float voc_part[VOC ? kWaves : 1][16][64];
-  __shared__ int ticket, in_vain;
+  __shared__ int launch_seq, ticket, in_vain;
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,14 +118,26 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
         // half of its k-steps, which wait in registers for the rows: nothing is left to be fetched once these are there.  Which workgroup has which
         // blocks is drawn, so that it does not depend on how the workgroups were dealt out.  4 rows, 32000 columns: launch 67.3 -> 71.5 us instead of a
         // product of 6.2 behind it; what is left of it is an exchange over the whole chip, the products' eight dependent steps and the statistics.
-        if (tid == 0) {
-          const int mine = __hip_atomic_fetch_add(now()->state + 5, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ticket = mine;
-          in_vain = 0;
-          asm volatile("s_waitcnt vmcnt(0)" ::"v"(mine) : "memory");   // before this workgroup is counted as one that has left
-          leave();
-        }
+        // (the other wavefronts' own `seq` may be of any age by now: what this launch exchanges in is what the first thread saw)
+        if (tid == 0)
+          die_spare_signs_off(
+              [&] {
+                asm volatile("" ::"s"(seq) : "memory");   // here
+                return seq;
+              },
+              [&] {
+                const int mine = __hip_atomic_fetch_add(now()->state + 5, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::"v"(mine) : "memory");
+                return mine;
+              },
+              [&](int launch, int columns) {
+                launch_seq = launch;
+                ticket = columns;
+                in_vain = 0;
+              },
+              leave);
         workgroup_barrier();
+        const int of_launch = __builtin_amdgcn_readfirstlane(launch_seq);
         const int lane = tid & 63, half = wave & 1, pair = wave >> 1, helpers = (kDies - G) * kDieGroup;
         const int V = a.V, blocks = (V + 31) / 32, block = __builtin_amdgcn_readfirstlane(ticket) + pair * helpers;
         const half_t* wp = global(a.Ep) + ((size_t)min(block, blocks - 1) * (D / 16) + half * 2) * 512 + lane * 8;
@@ -141,8 +153,8 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
         }
         pin();
         Exchange<> ex;
-        ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)parity * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
-        ex.polls = seq < 0 ? 1 : kSpinLimit;
+        ex.rsrc = __builtin_amdgcn_make_buffer_rsrc(a.exchange + (size_t)(of_launch & 1) * a.set_bytes, (short)0, (int)a.set_bytes, 0x00027000);
+        ex.polls = of_launch < 0 ? 1 : kSpinLimit;
         const int M = a.M;
         if (wave == 0) {   // a look now and then, until the rows are nearly there
           u32x4 one;

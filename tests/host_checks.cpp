@@ -85,8 +85,55 @@ static void placements() {
   EXPECT(complete_seen && missed_seen);
 }
 
+// The workgroups of dies to spare, which go on behind their words: whatever the others do between any two of their steps, each wavefront
+// works on the set that the launch began with, and the columns are dealt out once each.  Wavefronts that look for themselves
+// behind the word, as they may when nothing is handed on, must be seen to miss it: otherwise this could not tell.
+static void spare_workgroups() {
+  using namespace lsq;
+  constexpr int N = kDies * kDieGroup;
+  uint32_t x = 7;
+  auto random = [&] { return (x = x * 1664525u + 1013904223u) >> 8; };
+  int64_t missed = 0;
+  for (int it = 0; it < 2000; ++it) {
+    const int G = 1 + it % (kDies - 1), first = it / 7 & 1;
+    int order[N], next = 0, seq = first, tickets = 0;
+    uint64_t count = 0;
+    bool taken[N] = {};
+    for (int b = 0; b < N; ++b) order[b] = b;
+    for (int b = N - 1; b > 0; --b) std::swap(order[b], order[random() % (b + 1)]);
+    auto run = [&](auto&& self) -> void {
+      if (next == N) return;
+      const int b = order[next++], die = b % kDies;
+      auto others = [&] { while (random() % 3 == 0 && next < N) self(self); };
+      auto leave = [&] {
+        others();
+        const bool last = die_launch_ends(count);
+        count += die_word(die, b / kDies);
+        if (last) seq ^= 1;
+        others();
+      };
+      others();
+      if (die < G) {   // a working group's: looked long ago
+        leave();
+        return;
+      }
+      int handed = -1, columns = -1;
+      die_spare_signs_off([&] { const int seen = seq; others(); return seen; }, [&] { const int mine = tickets++; others(); return mine; },
+                          [&](int launch, int mine) { handed = launch; columns = mine; others(); }, leave);
+      EXPECT(handed == first);
+      EXPECT(columns >= 0 && columns < (kDies - G) * kDieGroup && !taken[columns]);
+      if (columns >= 0 && columns < N) taken[columns] = true;
+      missed += seq != first;
+    };
+    while (next < N) run(run);
+    EXPECT(tickets == (kDies - G) * kDieGroup && seq == (first ^ 1));
+  }
+  EXPECT(missed > 0);
+}
+
 int main() {
   placements();
+  spare_workgroups();
   size_t n = 0;
   // null / short / wrong magic
   EXPECT(lsq_workspace_bytes(nullptr, 0, 2, 4, 8, &n) == LSQ_E_ARG);
