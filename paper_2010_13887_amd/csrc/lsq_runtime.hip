@@ -192,17 +192,6 @@ struct Plan {
 
 size_t packed_weight_bytes(const HParams& hp);
 
-// Source rows up to which the encoder's (the prefill's) output projections and second FFN products are split over k: 32 to 512 workgroups instead of
-// the 16 to 100 that their tiles are.  Encodings in us, split / not, rows     25        50        100       136       280       400       512
-//   Transformer-base                                                      210/235   250/294   243/272   249/274   274/299   285/308   291/317
-//   Transformer-big                                                       253/304   282/342   290/345   312/360   360/396   378/412   378/406
-//   d = 768 decoder-only, 12 layers (with the prompt's cache rows stored
-//   by the attention kernel, 20 to 40 us of it)                           371/495   443/551   471/564   501/591   533/602   591/628   577/619
-// From some 570 rows on the tiles fill the chip (gemm_partial_splits).  Decoder-only models stop at 256: a sampled text hangs on the order of sums now
-// and then, and beyond there is little to be had for it.
-constexpr int kEncoderSplitRows = 512;
-int encoder_splits(int arch, int R) { return R <= (arch == 1 ? kEncoderSplitRows / 2 : kEncoderSplitRows) ? (int)kMaxSplits : 1; }
-
 Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   Plan p;
   const size_t esz = hp.dtype == DT_F16 ? 2 : 4;
@@ -253,8 +242,8 @@ Plan make_plan(const HParams& hp, size_t weight_bytes, int B, int k, int T) {
   auto etake = [&](size_t bytes) { size_t o = e; e += up(bytes); return o; };
   p.e_ids = etake(R * 4); p.e_pos = etake(R * 4); p.e_sent = etake(R * 4);
   p.e_x = etake(R * d * esz); p.e_qkv = etake(R * 3 * d * esz); p.e_ctx = etake(R * d * esz);
-  p.e_tmp = etake(std::max(R, kMaxSplits * std::min<size_t>(R, kEncoderSplitRows)) * d * 4); p.e_ffn = etake(R * F * esz);
-  p.e_y = etake(R * d * esz);     // pre-LN models: normalised copy of the residual stream   // e_tmp: fp32 slabs, one from kEncoderSplitRows rows on
+  p.e_tmp = etake(R * d * 4); p.e_ffn = etake(R * F * esz);
+  p.e_y = etake(R * d * esz);     // pre-LN models: normalised copy of the residual stream   // e_tmp: one fp32 slab (see run_encoder)
   // decoder phase
   size_t q = p.scratch;
   auto dtake = [&](size_t bytes) {
@@ -1190,11 +1179,11 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
       char* Kc = g.ws + p.cache + (size_t)(2 * l) * slab;
       HIPCHK(launch_gemm(dt, y, L.Wqkv, L.bqkv, plain_out(qkv, 3 * d), R, 3 * d, d, 0, s));
       HIPCHK(launch_encoder_attention(dt, qkv, sent, at<int32_t>(p.src_off), at<int32_t>(p.src_len), ctx, R, H, d, 1, s, Kc, Kc + slab, pos, T));
-      if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln2g, L.ln2b, x, y, (float*)tmp, R, d, d, encoder_splits(hp.arch, R), s)) return rc;
+      if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln2g, L.ln2b, x, y, (float*)tmp, R, d, d, 1, s)) return rc;
       HIPCHK(launch_gemm(dt, y, L.W1, L.b1, plain_out(ffn, F), R, F, d, 2, s));
       const bool last = l + 1 == hp.n_dec;
       if (int rc = sublayer(-1, ffn, L.W2, L.b2, last ? g.lnfg : g.gpt[l + 1].ln1g, last ? g.lnfb : g.gpt[l + 1].ln1b,
-                            x, y, (float*)tmp, R, d, F, encoder_splits(hp.arch, R), s)) return rc;
+                            x, y, (float*)tmp, R, d, F, 1, s)) return rc;
     }
   }
   for (size_t c : p.dec_canaries) HIPCHK(hipMemsetAsync(g.ws + c, kCanaryByte, kCanaryBytes, s));
@@ -1209,6 +1198,11 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
 }
 
 // The encoder and the keys and values of the cross-attention as launches of their own, for R packed source rows in the staging buffer.
+// Output projections and second FFN products are not split over k, here and in the prefill, though their tiles are only 16 to 100 workgroups up to
+// some 500 rows: the split goes by the number of rows, and a sentence's rows (a sampled text) would depend on what is encoded beside it.  It would
+// bring an encoding of 25 / 100 / 250 / 500 rows from 242 / 276 / 283 / 307 us to 223 / 259 / 278 / 301 (Transformer-base; Transformer-big 295 / 340 /
+// 362 / 396 to 248 / 288 / 320 / 375; 12 decoder-only layers of d = 768, 25 / 100 / 250 rows, 461 / 525 / 575 to 390 / 466 / 520), its error against 64
+// bits being the same.
 int run_encoder(int batch, int R) {
   const HParams& hp = g.hp;
   const Plan& p = g.plan;
@@ -1233,9 +1227,9 @@ int run_encoder(int batch, int R) {
   for (const EncLayer& L : g.enc) {
     HIPCHK(launch_gemm(dt, x, L.Wqkv, L.bqkv, plain_out(qkv, 3 * d), R, 3 * d, d, 0, s));
     HIPCHK(launch_encoder_attention(dt, qkv, sent, off, len, ctx, R, H, d, 0, s));
-    if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln1g, L.ln1b, x, nullptr, (float*)tmp, R, d, d, encoder_splits(hp.arch, R), s)) return rc;
+    if (int rc = sublayer(-1, ctx, L.Wo, L.bo, L.ln1g, L.ln1b, x, nullptr, (float*)tmp, R, d, d, 1, s)) return rc;
     HIPCHK(launch_gemm(dt, x, L.W1, L.b1, plain_out(ffn, F), R, F, d, 1, s));
-    if (int rc = sublayer(-1, ffn, L.W2, L.b2, L.ln2g, L.ln2b, x, nullptr, (float*)tmp, R, d, F, encoder_splits(hp.arch, R), s)) return rc;
+    if (int rc = sublayer(-1, ffn, L.W2, L.b2, L.ln2g, L.ln2b, x, nullptr, (float*)tmp, R, d, F, 1, s)) return rc;
   }
   const size_t cross_l = (size_t)g.max_batch * g.max_len * 2 * d * es;   // layer stride of the maximum shape
   for (int l = 0; l < hp.n_dec; ++l)
