@@ -1204,9 +1204,11 @@ StackKind stack_kind(int arch, int M, int d, int beam, int pos, int src, bool di
 //   beam 2, 160        392 / 425   407 / 435   423 / 446
 //           200        417 / 436   442 / 446   458 / 459
 // A position costs two launches 0.8 us and the separate ones 0.55; the rows of a sentence share less of their history where there are two of
-// them.  The lines are where these lead to; a source key counts as half a position.
+// them.  The lines are where these lead to; a source key counts as half a position.  Past 208 rows what is left of it is short-lived: 4 % at 224 rows in the
+// first 25 positions, under 1 % behind them.  Fewer than 129 rows fit one launch: where stack_kind has none for them it is because the separate ones
+// are ahead of it, or because the caller wants it so.
 bool stack_twice(int arch, int M, int d, int beam, int pos, int src) {
-  return arch == 0 && d == 1024 && beam >= 2 && M <= 208 && pos + src / 2 <= 105 + 2 * (208 - M) - (beam == 2 ? 40 : 0);
+  return arch == 0 && d == 1024 && beam >= 2 && M > 128 && M <= 208 && pos + src / 2 <= 105 + 2 * (208 - M) - (beam == 2 ? 40 : 0);
 }
 
 bool stream_has_every_cu(hipStream_t s) {

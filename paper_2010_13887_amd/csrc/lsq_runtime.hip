@@ -518,11 +518,11 @@ StackKind use_stack(int M) {
 }
 
 // Rows that one launch of a stack kernel takes of M (0: the separate kernels do): all of them, or, where two launches are ahead
-// (stack_twice), the larger half in whole sentences.
+// (stack_twice), the larger half in whole sentences.  A limit on the rows (lsq_set_attention_blocks) is one on M, not on the halves.
 int stack_part(int M) {
   if (use_stack(M)) return M;
   const int k = g.beam, half = (M / k + 1) / 2 * k;
-  return g.hp.dtype == DT_F16 && stack_twice(g.hp.arch, M, g.hp.d, k, history(), g.src_longest) && use_stack(half) && use_stack(M - half) ? half : 0;
+  return g.hp.dtype == DT_F16 && g.block_rows == (int)kBlockRowsMax && stack_twice(g.hp.arch, M, g.hp.d, k, history(), g.src_longest) && use_stack(half) && use_stack(M - half) ? half : 0;
 }
 
 // plain beam search with a small model: the whole step in one launch.  Up to as many sentences as the chip runs at once:

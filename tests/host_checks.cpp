@@ -11,6 +11,8 @@
 #include "../include/lsq.h"
 #include "../paper_2010_13887_amd/csrc/die_count.h"
 
+namespace lsq { bool stack_twice(int arch, int M, int d, int beam, int pos, int src); }   // kernels_stack.hip
+
 static int failures = 0;
 #define EXPECT(cond)                                                        \
   do {                                                                      \
@@ -131,9 +133,21 @@ static void spare_workgroups() {
   EXPECT(missed > 0);
 }
 
+// Two launches of the stack kernel: only for rows that one cannot hold.
+static void two_launches() {
+  using lsq::stack_twice;
+  for (int M : {1, 20, 66, 128})
+    for (int pos : {0, 5, 100, 300, 2000})
+      for (int beam : {1, 2, 4}) EXPECT(!stack_twice(0, M, 1024, beam, pos, 30));
+  EXPECT(stack_twice(0, 132, 1024, 4, 5, 30) && stack_twice(0, 208, 1024, 4, 5, 30) && stack_twice(0, 130, 1024, 2, 5, 30));
+  EXPECT(!stack_twice(0, 212, 1024, 4, 5, 30) && !stack_twice(0, 208, 1024, 4, 91, 30) && !stack_twice(0, 132, 1024, 1, 5, 30));
+  EXPECT(!stack_twice(1, 132, 1024, 4, 5, 30) && !stack_twice(0, 132, 768, 4, 5, 30));
+}
+
 int main() {
   placements();
   spare_workgroups();
+  two_launches();
   size_t n = 0;
   // null / short / wrong magic
   EXPECT(lsq_workspace_bytes(nullptr, 0, 2, 4, 8, &n) == LSQ_E_ARG);

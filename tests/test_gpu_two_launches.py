@@ -30,3 +30,22 @@ def test_rows_dealt_out_to_two_launches(lsq, batch, beam, twice):
         one, two = (eng.translate(w.src_ids, w.src_lens, sync_every=n) for n in (1, 4))
         assert all(np.array_equal(a, b) for a, b in zip(one, two))
         assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("batch", [5, 40])
+def test_a_limit_on_the_rows_is_not_met_by_halves(lsq, batch):
+    """20 rows where 16 are allowed: neither one launch nor two; 160 rows, of which two launches would have 80 each, likewise."""
+    hp = S.HParams(n_enc=1, n_dec=2, d_model=1024, n_heads=16, d_ffn=4096, vocab=203, max_pos=32, dtype=1, cap_extra=3)
+    w = S.custom(hp, [1 + (5 * i) % 7 for i in range(batch)], beam=4, max_len=12, std=0.03)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, batch, 4, 12) as eng:
+        lsq.lsq_set_attention_blocks(16 if batch == 5 else 63)
+        try:
+            eng.encode(w.src_ids, w.src_lens)
+            assert eng.decode_steps(2) > 0
+            assert not any(lsq.lsq_debug_stack_launches().values())
+        finally:
+            lsq.lsq_set_attention_blocks(64)
+        assert eng.decode_steps(1) > 0
+        assert lsq.lsq_debug_stack_launches()["groups_of_16_or_32"] == (1 if batch == 5 else 2)
+        assert lsq.lsq_debug_check_canaries() == 0
