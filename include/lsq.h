@@ -109,7 +109,9 @@ int lsq_decode_steps(int n);
 
 /* Steps until nothing is unfinished (0), with a wait for the count of unfinished sentences after every n steps.
  * n = 1: the next step is queued before the wait for the one before it, so that the device does not idle while
- * the host reads a count (5 us of 119 a step); at most one step is issued after everything finished. */
+ * the host reads a count (5 us of 119 a step); at most one step is issued after everything finished.
+ * Small models (see lsq_set_attention_blocks): steps share launches, in which a sentence stops by itself where it is finished, and there
+ * is one wait for all of a launch; results and lsq_step_index are the same. */
 int lsq_decode_all(int n);
 
 /* Copies the hypotheses out, best first per sentence by length-normalised
@@ -213,7 +215,8 @@ int lsq_debug_end_stack_waits(void);
 int lsq_debug_stack_launches(int64_t* counts);
 int lsq_debug_forget_dies(void);
 
-/* Number of decode steps taken since the last lsq_encode. */
+/* Number of decode steps taken since the last lsq_encode, those issued after everything finished among them.  Behind an
+ * lsq_decode_all whose steps shared launches: as if it had waited after every n (the first such call copies the counts from the device). */
 int lsq_step_index(void);
 
 /* ------------------------------------------------------------------------- */

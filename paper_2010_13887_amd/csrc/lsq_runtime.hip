@@ -326,6 +326,7 @@ struct Ctx {
   int batch = 0, rows_enc = 0, t = 0;
   int src_longest = 1;         // longest source sentence of this translation
   bool done = false;
+  int all_from = 0, all_n = 0; // lsq_decode_all(all_n) from step all_from on left it to the kernel where to stop (settle_steps; 0: it did not)
   int finalized = -1;          // steps of this translation behind which its results are already on their way (queue_results_early)
   std::vector<int> order;      // internal (sorted) sentence index -> caller's index
   bool use_graphs = true;
@@ -1088,6 +1089,21 @@ hipError_t queue_results(int32_t* ids, int32_t* lens, float* scores) {
                          g.beam, g.max_len, g.hp.arch == 1 ? 0.0f : g.hp.alpha, g.hp.pad, g.hp.arch == 1 ? g.prompt_len : 1, g.stream);
 }
 
+// Where steps of a small model share launches, lsq_decode_all issues all that are left of them, and every sentence stops where it is finished.  For
+// whoever asks: how many it would have issued with a wait after every n.
+int settle_steps() {
+  if (g.all_n == 0) return LSQ_OK;
+  std::vector<int32_t> active(g.t - g.all_from);
+  HIPCHK(hipMemcpyAsync(active.data(), at<int32_t>(g.plan.active) + g.all_from, active.size() * 4, hipMemcpyDeviceToHost, g.stream));
+  HIPCHK(hipStreamSynchronize(g.stream));
+  const int taken = (int)(std::find(active.begin(), active.end(), 0) - active.begin()) + 1;   // the last of them left nothing unfinished
+  const int n = g.all_n, t = std::min(g.t, g.all_from + (n == 1 ? taken + 1 : (taken + n - 1) / n * n));
+  if (g.finalized == g.t) g.finalized = t;
+  g.t = t;
+  g.all_n = 0;
+  return LSQ_OK;
+}
+
 // Once no step is left to be issued, the results follow the last one without waiting for the host to see it end and the caller to ask for
 // them.  8 steps of the tiny model 274 -> 266 us, 16 steps behind 32 prompts 6460 -> 6435; a translation that is waited for after every step
 // gains little, since its results are there too soon (asking the stream instead of waiting for it: 266 -> 291).
@@ -1193,6 +1209,7 @@ int encode_gpt(const int32_t* ids, const int32_t* lens, int batch, int stride) {
   g.t = 0;
   g.done = false;
   g.finalized = -1;
+  g.all_n = 0;
   g.state = 3;
   return LSQ_OK;
 }
@@ -1500,6 +1517,7 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
   g.t = 0;
   g.done = false;
   g.finalized = -1;
+  g.all_n = 0;
   g.state = 3;
   return LSQ_OK;
 }
@@ -1527,7 +1545,7 @@ int lsq_decode_all(int n) {
   if (g.state < 3) return fail(LSQ_E_STATE, "lsq_encode has not been called");
   if (n < 1) return fail(LSQ_E_ARG, "n must be positive");
   auto more = [] { return g.t < g.max_len && g.alive_at[g.t] > 0; };
-  const int ahead = n == 1 ? 1 : 0;
+  const int ahead = n == 1 ? 1 : 0, from = g.t;
   for (int seen = g.t; !g.done && (more() || seen < g.t);) {   // the count after `seen` steps is known
     const int next = std::min(seen + n, g.max_len);
     while (g.t < next + ahead && more()) {
@@ -1539,7 +1557,10 @@ int lsq_decode_all(int n) {
     int active = 0;
     int rc = read_active(seen, &active);
     if (rc) return rc;
-    if (active == 0) g.done = true;
+    if (active == 0) {
+      g.done = true;
+      if (g.t > seen + ahead) { g.all_from = from; g.all_n = n; }
+    }
   }
   return 0;
 }
@@ -1624,7 +1645,11 @@ int lsq_set_cache_refresh(int mode) {
   return LSQ_OK;
 }
 
-int lsq_step_index(void) { return g.state >= 3 ? g.t : 0; }
+int lsq_step_index(void) {
+  if (g.state < 3) return 0;
+  if (int rc = settle_steps()) return rc;
+  return g.t;
+}
 
 int lsq_set_canaries(int on) {
   if (g.state >= 2) return fail(LSQ_E_STATE, "a model is loaded: the memory plan is fixed; call lsq_free first");
@@ -1723,6 +1748,7 @@ int lsq_debug_read(int what, void* host_dst, size_t bytes) {
     if (int rc = decode_again()) return rc;
     HIPCHK(hipStreamSynchronize(g.stream));
   }
+  if (int rc = settle_steps()) return rc;
   const Plan& p = g.plan;
   const HParams& hp = g.hp;
   const size_t M = (size_t)g.batch * g.beam, T = g.max_len, d = hp.d, R = g.rows_enc;

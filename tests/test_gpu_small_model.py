@@ -74,3 +74,27 @@ def test_steps_of_a_small_model_in_one_launch(lsq, d, heads, vocab, beam, dtype,
             for at in range(n, len(counts), n):
                 assert lsq.lsq_decode_steps(n) == counts[at - 1] and lsq.lsq_step_index() == at
         assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("beam,cap", [(3, 70), (1, 70), (3, 2)])
+def test_steps_counted_where_they_shared_a_launch(lsq, beam, cap):
+    """decode_all(n) counts its steps as a wait after every n of them would, wherever the sentences finished in a shared launch."""
+    hp = S.HParams(n_enc=1, n_dec=1, d_model=64, n_heads=4, d_ffn=128, vocab=11, max_pos=96, dtype=0, cap_extra=cap, seed=1)
+    w = S.custom(hp, [1, 4, 9, 2], beam=beam, max_len=80, std=0.3)
+    with lsq.Engine(w.blob(ln_jitter=0.2), 4, beam, 80) as eng:
+        eng.encode(w.src_ids, w.src_lens)
+        finished = 1
+        while lsq.lsq_decode_step() > 0:
+            finished += 1
+        want, last = eng.get_beams(), int((w.src_lens + cap).max())
+        assert finished == {(3, 70): 13, (1, 70): 23, (3, 2): 6}[beam, cap] < last   # EOS, or the cap of a shorter sentence, ends them
+        for n in (1, 2, 5, 64):
+            for before in (0, 1):   # steps taken one by one before
+                eng.encode(w.src_ids, w.src_lens)
+                for _ in range(before):
+                    lsq.lsq_decode_step()
+                lsq.lsq_decode_all(n)
+                steps = finished - before
+                assert lsq.lsq_step_index() == min(last, before + (steps + 1 if n == 1 else -(-steps // n) * n))
+                assert lsq.lsq_decode_step() == 0
+                assert all(np.array_equal(a, b) for a, b in zip(eng.get_beams(), want))
