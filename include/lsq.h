@@ -237,7 +237,8 @@ int lsq_profile_read(double* ms, int64_t* launches, int n);
  * is always delivered as float32 whatever the model's storage type. `bytes`
  * must equal the size of the item.  M = batch*beam rows, T = max_len.          */
 enum {
-  LSQ_DBG_LOGITS = 0,     /* float [M, vocab]  logits of the last step (always fp32); rows of sentences past their cap are stale */
+  LSQ_DBG_LOGITS = 0,     /* float [M, vocab]  logits of the last step (always fp32); rows of sentences past their cap (small
+                             models: of finished ones), here and below, are those of the last step the sentence took part in */
   LSQ_DBG_SCORE = 1,      /* float [M]         raw hypothesis scores                   */
   LSQ_DBG_TOKENS = 2,     /* int32 [M, T+1]    token histories, BOS first              */
   LSQ_DBG_LEN = 3,        /* int32 [M]                                                 */
@@ -248,7 +249,7 @@ enum {
   LSQ_DBG_HIDDEN = 8,     /* float [M, d]      decoder output of the last step         */
   LSQ_DBG_MEMORY = 9,     /* float [sum(src_lens), d] encoder output, sentences packed */
   LSQ_DBG_CROSS_KV = 100, /* +layer: float [sum(src_lens), 2d]                          */
-  LSQ_DBG_CACHE_K = 200,  /* +layer: float [M, T, d]                                    */
+  LSQ_DBG_CACHE_K = 200,  /* +layer: float [M, T, d]           positions that the sentence did not reach are stale */
   LSQ_DBG_CACHE_V = 300   /* +layer: float [M, T, d]                                    */
 };
 int lsq_debug_read(int what, void* host_dst, size_t bytes);

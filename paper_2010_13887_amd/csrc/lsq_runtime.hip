@@ -1798,10 +1798,12 @@ int lsq_debug_read(int what, void* host_dst, size_t bytes) {
     HIPCHK(hipMemcpyAsync(anc.data(), g.ws + p.anc, anc.size() * 4, hipMemcpyDeviceToHost, g.stream));
     HIPCHK(hipStreamSynchronize(g.stream));
     std::vector<float> moved(n);
-    const size_t written = std::min((size_t)g.t, T);   // positions 0..t-1 hold keys/values; the rest is stale either way
+    // positions 0..t-1 hold keys/values, as far as their sentence went (its entries behind that may never have been written); the rest is stale either way
+    const size_t written = std::min((size_t)g.t, T);
     for (size_t r = 0; r < M; ++r)
       for (size_t j = 0; j < T; ++j) {
-        const size_t from = j < written ? r - r % g.beam + (size_t)anc[r * (T + 1) + j] : r;
+        const size_t slab = (size_t)std::min(std::max(anc[r * (T + 1) + j], 0), g.beam - 1);   // as the kernels take them
+        const size_t from = j < written ? r - r % g.beam + slab : r;
         memcpy(&moved[(r * T + j) * d], &raw[(from * T + j) * d], d * 4);
       }
     raw.swap(moved);

@@ -98,3 +98,39 @@ def test_steps_counted_where_they_shared_a_launch(lsq, beam, cap):
                 assert lsq.lsq_step_index() == min(last, before + (steps + 1 if n == 1 else -(-steps // n) * n))
                 assert lsq.lsq_decode_step() == 0
                 assert all(np.array_equal(a, b) for a, b in zip(eng.get_beams(), want))
+
+
+def test_cache_of_sentences_that_ended_inside_a_launch(lsq):
+    """Keys and values as the debug reader hands them back, in a workspace whose every byte was something else: those of the steps that a
+    sentence took, whether its launch went on without it or not."""
+    import torch
+    hp = S.HParams(n_enc=1, n_dec=1, d_model=64, n_heads=4, d_ffn=128, vocab=11, max_pos=96, dtype=0, cap_extra=70, seed=1)
+    w = S.custom(hp, [1, 4, 9, 2], beam=3, max_len=80, std=0.3)
+    blob = w.blob(ln_jitter=0.2)
+    nbytes = lsq.lsq_workspace_bytes(blob, 4, 3, 80)
+    workspace = torch.full((nbytes,), 0x7F, dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    lsq.lsq_set_workspace(workspace.data_ptr(), nbytes, stream.cuda_stream)
+    try:
+        lsq.lsq_init(blob, 4, 3, 80)
+
+        def caches():
+            return [lsq.lsq_debug_read(kind, (4, 3, 80, 64)) for kind in (lsq.DBG.CACHE_K, lsq.DBG.CACHE_V)]
+
+        lsq.lsq_encode(w.src_ids, w.src_lens)
+        lsq.lsq_decode_all(64)
+        got = caches()
+        lsq.lsq_encode(w.src_ids, w.src_lens)
+        steps = np.zeros(4, int)
+        for t in range(1, 14):
+            lsq.lsq_decode_step()
+            fin = lsq.lsq_debug_read(lsq.DBG.FINISHED, (4, 3), np.int32)
+            steps[(steps == 0) & fin.all(axis=1)] = t
+        want = caches()
+        assert steps.max() == 13 and steps.min() < 13 and (steps > 0).all()
+        for b in range(4):
+            for a, e in zip(got, want):
+                assert np.isfinite(a[b, :, :steps[b]]).all() and np.array_equal(a[b, :, :steps[b]], e[b, :, :steps[b]])
+    finally:
+        lsq.lsq_free()
