@@ -210,9 +210,11 @@ int lsq_debug_end_stack_waits(void);
 
 /* Test hooks: counts[0..3] = launches since lsq_init of the kernels that run all decoder layers of a step, of those with
  * each group of rows on a die of its own, with groups of 8 rows, with groups of 16 or 32, and of float32 models.
+ * lsq_debug_small_launches: counts[0..2] = encodings of a small model in one launch, launches with whole decode steps of it, steps in those, since lsq_init.
  * lsq_debug_forget_dies: the loaded model runs from its next step on as if its workgroups had not been found on the dies in turn, as
  * the first of these kernels wants them. */
 int lsq_debug_stack_launches(int64_t* counts);
+int lsq_debug_small_launches(int64_t* counts);
 int lsq_debug_forget_dies(void);
 
 /* Number of decode steps taken since the last lsq_encode, those issued after everything finished among them.  Behind an

@@ -58,6 +58,7 @@ def load_library() -> C.CDLL:
         "lsq_debug_check_canaries": [],
         "lsq_debug_end_stack_waits": [],
         "lsq_debug_stack_launches": [vp],
+        "lsq_debug_small_launches": [vp],
         "lsq_debug_forget_dies": [],
         "lsq_k_layernorm_gemm": [i32, vp, i32, vp, vp, vp, vp, vp, C.c_float, vp, vp, vp, i32, i32, i32, i32, vp],
         "lsq_k_layernorm_cross_attention": [vp, i32, vp, vp, vp, vp, vp, C.c_float, vp, vp, vp, vp, vp, vp, i32, i32, i32,
@@ -195,6 +196,13 @@ def lsq_debug_stack_launches() -> dict:
     n = np.zeros(4, np.int64)
     _check(load_library().lsq_debug_stack_launches(n.ctypes.data))
     return dict(zip(("die", "groups_of_8", "groups_of_16_or_32", "float32"), n.tolist()))
+
+
+def lsq_debug_small_launches() -> dict:
+    """Of a small model since lsq_init: encodings in one launch, launches with whole decode steps, steps in those."""
+    n = np.zeros(3, np.int64)
+    _check(load_library().lsq_debug_small_launches(n.ctypes.data))
+    return dict(zip(("encoders", "launches", "steps"), n.tolist()))
 
 
 def lsq_debug_forget_dies() -> None:

@@ -348,6 +348,7 @@ struct Ctx {
   bool dies = false;            // its workgroups are dealt to the dies in turn, and no kernel that needs that has given up
   StackArgs stack{};            // ... with these arguments (all but those of a translation)
   int64_t stack_launches[kStackF32 + 1] = {};   // of this model, by StackKind
+  int64_t small_launches[3] = {};   // of this model: encoders in one launch, launches with decode steps, steps in those
   bool small_ok = false;        // a beam search step of this model can be one launch
   SearchArgs search{};
   SmallEncoderArgs encoder{};   // ... and its encoder too
@@ -659,6 +660,8 @@ int launch_step(int B, int small) {
     se.anc = anc;
     se.steps = small;
     TIMED(PC_STACK, launch_small_step(dt, B, k, a, se, s));
+    g.small_launches[1] += 1;
+    g.small_launches[2] += small;
     if (moves)
       TIMED(PC_REORDER, launch_cache_reorder(dt, g.ws + p.cache, at<int32_t>(p.parent), 2 * hp.n_dec, B, M_max, k, T, d,
                                              0, step, T, s));
@@ -1492,6 +1495,7 @@ int lsq_encode(const int32_t* src_ids, const int32_t* src_lens, int batch, int s
     a.kg = g.beam / g.groups;
     a.anc = g.anc_on ? at<int32_t>(p.anc) : nullptr;
     HIPCHK(launch_small_encoder(hp.dtype, batch, longest, a, s));
+    g.small_launches[0] += 1;
   } else if (int rc = run_encoder(batch, (int)R)) {
     return rc;
   }
@@ -1685,6 +1689,13 @@ int lsq_debug_stack_launches(int64_t* counts) {
   if (g.state < 2) return fail(LSQ_E_STATE, "lsq_init has not been called");
   if (!counts) return fail(LSQ_E_ARG, "counts is null");
   for (int k = kStackDie; k <= kStackF32; ++k) counts[k - kStackDie] = g.stack_launches[k];
+  return LSQ_OK;
+}
+
+int lsq_debug_small_launches(int64_t* counts) {
+  if (g.state < 2) return fail(LSQ_E_STATE, "lsq_init has not been called");
+  if (!counts) return fail(LSQ_E_ARG, "counts is null");
+  std::copy(std::begin(g.small_launches), std::end(g.small_launches), counts);
   return LSQ_OK;
 }
 

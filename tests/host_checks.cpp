@@ -223,6 +223,7 @@ int main() {
   EXPECT(lsq_debug_read(LSQ_DBG_SCORE, sc, sizeof sc) == LSQ_E_STATE);
   int64_t counts[4];
   EXPECT(lsq_debug_stack_launches(counts) == LSQ_E_STATE);
+  EXPECT(lsq_debug_small_launches(counts) == LSQ_E_STATE);
   EXPECT(lsq_debug_forget_dies() == LSQ_E_STATE);
   EXPECT(lsq_k_packed_weight_bytes(64, 24) == 0);
   EXPECT(lsq_k_packed_weight_bytes(33, 32) == 64u * 32 * 2);
