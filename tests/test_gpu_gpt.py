@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 
 import lsq_synth as S
-from tests.parity import lockstep_gpt
+from oracle import lsq_oracle as O
+from tests.parity import TOL_F16, TOL_F32, lockstep_gpt, logit_error
 
 pytestmark = pytest.mark.gpu
 
@@ -226,3 +227,24 @@ def test_draws_do_not_turn(lsq, batch, kernel, text):
         ids, _, _ = eng.translate(prompts, w.src_lens, sync_every=32)
         assert lsq.lsq_debug_stack_launches()[kernel] == 120
     assert zlib.crc32(ids.tobytes()) == text
+
+
+@pytest.mark.parametrize("heads,dh,P", [(4, 64, 2), (4, 64, 34), (2, 128, 131), (8, 32, 66), (8, 16, 40)])
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_prefill_leaves_keys_and_values_in_the_cache(lsq, heads, dh, P, dtype):
+    """Every position of every prompt but its last, of both layers; blocks of 32 rows that lie across prompts, and the launches that
+    copy the rows where the attention kernel does not (float32, heads of 16)."""
+    d, B = heads * dh, 5
+    hp = S.HParams(arch=1, n_enc=0, n_dec=2, d_model=d, n_heads=heads, d_ffn=2 * d, vocab=101, dtype=dtype, max_pos=160, act=1, norm=1,
+                   cap_extra=3, sample_topk=2)
+    w = S.custom(hp, [P] * B, beam=1, max_len=P + 4, std=0.1)
+    blob = w.blob(ln_jitter=0.1)
+    model = O.Model(blob, ctype=np.float64, storage="wide")
+    st = O.GptState(model, w.src_ids[:, :P], P + 4)
+    O.gpt_prefill(model, st)
+    with lsq.Engine(blob, B + 1, 1, P + 4) as eng:
+        eng.encode(w.src_ids, w.src_lens)
+        for l in range(2):
+            for kind, want in ((lsq.DBG.CACHE_K, st.Kc[l]), (lsq.DBG.CACHE_V, st.Vc[l])):
+                got = eng.debug(kind + l, (B, P + 4, d))[:, :P - 1]
+                assert logit_error(got.reshape(-1, d), want[:, :P - 1].reshape(-1, d)) <= (TOL_F16 if dtype else TOL_F32)

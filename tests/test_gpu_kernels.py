@@ -281,7 +281,10 @@ def test_self_attention_through_slab_table(env, B, k, H, dh, T, nkeys, half):
                                        # key blocks, blocks of 32 rows that hold many one-token sentences, a last block of
                                        # one row, a sentence ending exactly on a block boundary
                                        ([300, 2, 257], 2, 64), ([1] * 70 + [3], 4, 64), ([32, 32, 1], 2, 32),
-                                       ([31, 33, 64, 2], 2, 128), ([700], 1, 64)])
+                                       ([31, 33, 64, 2], 2, 128), ([700], 1, 64),
+                                       # ... more than 32 workgroups an XCD, of which every other 32 change places in pairs: as
+                                       # many on every XCD, and one more on two of them, whose last one has no partner
+                                       ([97, 31, 300, 1, 250, 64, 410], 32, 32), ([200, 953], 29, 64)])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("half", [False, True])
 def test_encoder_attention(env, lens, H, dh, causal, half):
