@@ -36,7 +36,7 @@ namespace lsq {
 
 namespace {
 
-constexpr int kVocabularyRows = 8;     // largest group, and most rows in all, of a launch that takes the vocabulary product along
+constexpr int kVocabularyRows = 8;     // largest group, and most rows in all, of a launch that takes the vocabulary product along (die_takes_vocabulary)
 constexpr int kVocabularyMax = 32;
 constexpr int kVocabularyPace = 20;    // 64 clocks between two of a wavefront's requests: launches of 4 rows 72.3 us with 0, 71.7 with 20, 71.9 with 64
 constexpr int kDieThreads = 1024;      // eight wavefronts that multiply, eight that exchange
@@ -807,7 +807,12 @@ bool die_supported(int arch, int M, int d, int beam, int pos, int src) {
 //   12 rows, beam 4         85.6 / 84.0    85.7 / 84.0    86.2 / 84.6    86.8 / 85.2    89.8 / 88.0    96.7 / 95.4
 //   24 rows, beam 4         93.4 / 90.5    93.7 / 91.1    95.4 / 92.4    97.6 / 94.6   102.6 / 101.5  109.6 / 109.4
 //   24 rows, one per sentence 92.3 / 89.9  94.0 / 91.8    96.4 / 94.6    99.4 / 97.7
-// (1 row 75.7 / 74.1.)  Where groups of 4 or 8 need more than four dies the rest of the registers would not hold 32 000 columns.
+// (1 row 75.7 / 74.1.)  Past position 128, where rows go to as many dies as there are sentences, 28 and 32 rows of beams 7 and 8 are four groups as well (positions
+// 132-160, 160-200, 200-250: 119 / 117, 121 / 117, 122 / 118; 123 / 121, 128 / 123, 129 / 125).  Pre-LN, 12 layers, up to position 110: 4 rows 116 / 114 ...
+// 123 / 121, 12 rows 129 / 128 ... 136 / 135, 24 rows 139 / 138 ... 150 / 149; level behind 128.
+// More than four groups: the dies left over would hold 24 576, 16 384 and 8192 columns.  Seven (25 to 28 rows) are behind with V = 8000, post-LN 91.9 / 92.9,
+// 93.1 / 93.8, pre-LN 136.9 / 138.1, 143.3 / 144.6: one die has the whole product then.  Five and six, which there are past position 128 only,
+// would be 1 to 1.5 us of 90 to 98 ahead; the line does not tell them apart.
 bool die_takes_vocabulary(int arch, int M, int layers, int beam, int pos, int V) {
   const DieChoice c = choose_die(M, beam, pos);
   const int places = layers * (arch == 1 ? Region<true>::size : Region<false>::size) / 2;   // rows of d float16 that the exchange region of one row has room for

@@ -151,8 +151,8 @@ def test_a_wait_that_ran_out_on_a_die_takes_the_dies_only(lsq, stop):
     (1, 4, 7200, True),       # 225 blocks for 224 workgroups: the first one has two
     (2, 4, 49149, True),      # two groups leave 192 workgroups of eight blocks, 49152 columns
     (2, 4, 49153, False),
-    (24, 1, 40960, True),     # most rows; three groups: 40960 columns
-    (25, 1, 1003, False),     # no die to spare
+    (24, 1, 40960, True),     # most rows at this history; three groups: 40960 columns
+    (25, 1, 1003, False),     # seven groups: one die to spare, which would be behind
 ])
 def test_dies_to_spare_take_the_vocabulary_product(lsq, batch, beam, vocab, taken):
     """Its logits against the oracle's, and the same bits as the separate product: row by row the same translation."""
@@ -173,4 +173,30 @@ def test_dies_to_spare_take_the_vocabulary_product(lsq, batch, beam, vocab, take
         lsq.k_gemm(hidden, packed, None, separate, packed=True)
         torch.cuda.synchronize()
         assert np.array_equal(separate.cpu().numpy(), logits)
+        assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("batch,beam", [(4, 8), (4, 7)])
+def test_dies_to_spare_take_the_vocabulary_product_of_32_rows(lsq, batch, beam):
+    """Past position 128 a sentence of 7 or 8 hypotheses is a group: four groups, and as many rows as the dies to spare have room for."""
+    hp = S.HParams(n_enc=1, n_dec=3, d_model=512, n_heads=8, d_ffn=2048, vocab=1003, max_pos=160, dtype=1, cap_extra=140)
+    w = S.custom(hp, [3] * batch, beam=beam, max_len=143, std=0.03)
+    blob = w.blob(ln_jitter=0.1)
+    with lsq.Engine(blob, batch, beam, 143) as eng:
+        eng.encode(w.src_ids, w.src_lens)
+        E = torch.from_numpy(np.frombuffer(blob, np.float16, 1003 * 512, 256).reshape(1003, 512).copy()).cuda()
+        packed = lsq.k_pack_weights(E)
+        for first, n, taken in ((0, 129, False), (129, 2, True), (131, 1, True)):
+            lsq.lsq_profile_enable(True)
+            assert eng.decode_steps(n) == batch
+            launches = lsq.lsq_profile_read()
+            lsq.lsq_profile_enable(False)
+            assert launches["decoder_stack"][1] == n and launches["gemm_vocab"][1] == (0 if taken else n)
+            logits = eng.debug(lsq.DBG.LOGITS, (batch * beam, 1003))
+            hidden = torch.from_numpy(eng.debug(lsq.DBG.HIDDEN, (batch * beam, 512))).half().cuda()
+            separate = torch.empty(batch * beam, 1003, dtype=torch.float32, device="cuda")
+            lsq.k_gemm(hidden, packed, None, separate, packed=True)
+            torch.cuda.synchronize()
+            assert np.isfinite(logits).all() and np.array_equal(separate.cpu().numpy(), logits)
+        assert lsq.lsq_debug_stack_launches()["die"] == 132
         assert lsq.lsq_debug_check_canaries() == 0
