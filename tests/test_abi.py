@@ -102,3 +102,23 @@ def test_corrupt_headers_are_refused_not_trusted(lib):
                 refused += 1
                 assert len(lib.lsq_last_error()) > 0
         assert refused > 100                                  # most damage is caught by a range or size check
+
+
+def test_decoder_input_lies_in_the_scratch_that_encoder_and_decoder_share(lib):
+    """One hypothesis more per sentence, where the encoder's scratch is the larger one: the plan grows by what outlives the encoder (cache, beam
+    state, results) and by nothing else."""
+    import paper_2010_13887_amd as lsq
+    B, T, d, n_dec, V = 6, 200, 384, 2, 11
+    hp = S.HParams(n_enc=1, n_dec=n_dec, d_model=d, n_heads=6, d_ffn=2 * d, vocab=V, max_pos=T, dtype=0, cap_extra=5)   # no stack kernel, no small model
+    blob = S.make_blob(hp)
+
+    def up(n):
+        return -(-n // 256) * 256
+
+    def outlives(k):
+        M = B * k
+        return up(n_dec * 2 * M * T * d * 4) + 2 * up(M * (T + 1) * 4) + up(M * T * 4) + 7 * up(M * 4) + 3 * up(M * k * 4)
+
+    for k in (1, 2, 3):
+        grown = lsq.lsq_workspace_bytes(blob, B, k + 1, T) - lsq.lsq_workspace_bytes(blob, B, k, T)
+        assert grown == outlives(k + 1) - outlives(k)
