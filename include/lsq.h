@@ -160,7 +160,7 @@ int lsq_set_layernorm_fusion(int on);
  * and d = 256, 512, 768 or 1024 (float32: 256 or 512, encoder-decoder) ALL decoder layers of a step are one
  * launch (max_rows = 64: also above 64 rows, up to 128 for d = 1024, 160 for 768, 256 for 512,
  * float32 256; 129 to 208 rows of d = 1024 and beams of at least 2: two such launches while the histories are short);
- * small models (d = 64 or 128, heads of 16 or 32; plain beam search) run a whole step as one launch;
+ * small models (d = 64 or 128, heads of 16 or 32; plain beam search) run whole steps as one launch, unless max_rows = 0 the encoder too;
  * other float16 shapes with d = 256 or 512 and beam <= 4 run each attention sublayer of a decoder layer as one
  * launch up to its output projection (sec. 2.1 taken further; lsq_k_self_attention_block,
  * lsq_k_cross_attention_block).  The workgroups of an all-layers launch wait for one another: streams with
