@@ -981,7 +981,7 @@ __global__ void __launch_bounds__(256) gemm_f16_skinny_kernel(const half_t* __re
         for (int e = 0; e < 4; ++e)
           if (n + e < N) z += __expf(v[e] - mx);
         const float m2 = lane_xor<32>(mx), z2 = lane_xor<32>(z);
-        merge_stat(mx, z, m2, z2);
+        merge_stat_exact(mx, z, m2, z2);
         if (lane < 32) { st_m[wave][i][lane] = mx; st_z[wave][i][lane] = z; }
       }
     }
@@ -996,7 +996,7 @@ __global__ void __launch_bounds__(256) gemm_f16_skinny_kernel(const half_t* __re
           if (m >= M) continue;
           float mx = st_m[0][i][lane], z = st_z[0][i][lane];
 #pragma unroll
-          for (int w = 1; w < 4; ++w) merge_stat(mx, z, st_m[w][i][lane], st_z[w][i][lane]);
+          for (int w = 1; w < 4; ++w) merge_stat_exact(mx, z, st_m[w][i][lane], st_z[w][i][lane]);
           float* st = out.stats + ((size_t)m * out.stats_groups + blockIdx.x) * 2;
           st[0] = mx;
           st[1] = z;
@@ -1057,7 +1057,7 @@ __global__ void __launch_bounds__(T) gemm_f16_stream_kernel(const half_t* __rest
     if (ks + P < KS) w[ks % P] = request(ks + P);
     if ((ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
-  vocabulary_block([&](int vg, int e) { return (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]); },
+  vocabulary_block<false>([&](int vg, int e) { return (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]); },
                    [&](int n, const float (&v)[4]) { store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp); }, out.stats, out.stats_groups, m, block, M, N, lane);
 }
 
@@ -1285,7 +1285,7 @@ __global__ void __launch_bounds__(T) gemm_f32_vocabulary_kernel(const float* __r
     if (ks + P < KS) w[ks % P] = request(ks + P);
     if ((ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
-  vocabulary_block([&](int vg, int e) { return (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]); },
+  vocabulary_block<false>([&](int vg, int e) { return (acc[0][vg * 4 + e] + acc[1][vg * 4 + e]) + (acc[2][vg * 4 + e] + acc[3][vg * 4 + e]); },
                    [&](int n, const float (&v)[4]) { store4<float, false>(out, m, n, v, M, N, vec_ok, 0, tp); }, out.stats, out.stats_groups, m, block, M, N, lane);
 }
 

@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(kDieThreads) decoder_die_kernel(const StackArg
 #pragma unroll
           for (int e = 0; e < 16; ++e) other[e] = voc_part[pair][e][lane];
           float* const out = global(now()->logits) + (size_t)m * V;
-          vocabulary_block([&](int vg, int e) { return acc[0][vg * 4 + e] + other[vg * 4 + e]; },
+          vocabulary_block<true>([&](int vg, int e) { return acc[0][vg * 4 + e] + other[vg * 4 + e]; },
                            [&](int n, const float (&v)[4]) {
                              if ((V & 3) == 0) {
                                *reinterpret_cast<floatx4*>(out + n) = floatx4{v[0], v[1], v[2], v[3]};

@@ -650,6 +650,13 @@ __device__ __forceinline__ void merge_stat(float& m, float& z, float m2, float z
   if (mn != -INFINITY) z = z * __expf(m - mn) + z2 * __expf(m2 - mn);
   m = mn;
 }
+// ... with the roundings written out, for kernels that leave the same bits as one another: which of the two products goes into the multiply-add
+// is the compiler's choice above, and not the same everywhere.
+__device__ __forceinline__ void merge_stat_exact(float& m, float& z, float m2, float z2) {
+  const float mn = fmaxf(m, m2);
+  if (mn != -INFINITY) z = fmaf(z2, __expf(m2 - mn), z * __expf(m - mn));
+  m = mn;
+}
 
 // v <- v + ((p[0] + p[1] + ... + p[S-1]) + t), slabs added in index order, nothing contracted
 template <int SMAX>

@@ -6,8 +6,13 @@ namespace lsq {
 
 // Lane: row m, columns 8 vg + 4 (lane >> 5) + 0..3 of the block; value(vg, e) says what they are, store(n, v) keeps columns n .. n + 3.
 // stats (may be null): [row][groups] pairs (largest, sum of exponentials), in the order of gemm_f16_skinny_kernel, whose wavefronts have eight columns each.
-template <typename V, typename S>
+// EXACT: its bits too.
+template <bool EXACT, typename V, typename S>
 __device__ __forceinline__ void vocabulary_block(V&& value, S&& store, float* stats, int groups, int m, int block, int M, int N, int lane) {
+  auto merge = [](float& m1, float& z1, float m2, float z2) {
+    if constexpr (EXACT) merge_stat_exact(m1, z1, m2, z2);
+    else merge_stat(m1, z1, m2, z2);
+  };
   float mx = -INFINITY, z = 0.f;
 #pragma unroll
   for (int vg = 0; vg < 4; ++vg) {
@@ -24,9 +29,9 @@ __device__ __forceinline__ void vocabulary_block(V&& value, S&& store, float* st
     for (int e = 0; e < 4; ++e)
       if (n + e < N) vz += __expf(v[e] - vm);
     const float m2 = lane_xor<32>(vm), z2 = lane_xor<32>(vz);
-    merge_stat(vm, vz, m2, z2);
+    merge(vm, vz, m2, z2);
     if (vg == 0) { mx = vm; z = vz; }
-    else merge_stat(mx, z, vm, vz);
+    else merge(mx, z, vm, vz);
   }
   if (stats && lane < 32 && m < M) {
     float* st = stats + ((size_t)m * groups + block) * 2;

@@ -200,3 +200,31 @@ def test_dies_to_spare_take_the_vocabulary_product_of_32_rows(lsq, batch, beam):
             assert np.isfinite(logits).all() and np.array_equal(separate.cpu().numpy(), logits)
         assert lsq.lsq_debug_stack_launches()["die"] == 132
         assert lsq.lsq_debug_check_canaries() == 0
+
+
+@pytest.mark.parametrize("vocab,batch,beam", [(37, 10, 1), (203, 1, 4), (224, 1, 4), (1000, 2, 4), (7200, 5, 3)])
+def test_dies_to_spare_leave_the_statistics_of_the_separate_product(lsq, vocab, batch, beam):
+    """Candidates' scores bit for bit those that the retrieve kernel makes of the separate product's logits and group statistics: few groups, where a
+    last bit of one sum of exponentials is not lost among the others."""
+    hp = S.HParams(n_enc=1, n_dec=3, d_model=512, n_heads=8, d_ffn=2048, vocab=vocab, max_pos=32, dtype=1, cap_extra=25, seed=34)
+    w = S.custom(hp, [10] * batch, beam=beam, max_len=32, std=0.05)
+    blob = w.blob(ln_jitter=0.1)
+    M = batch * beam
+    E = torch.from_numpy(np.frombuffer(blob, np.float16, vocab * 512, 256).reshape(vocab, 512).copy()).cuda()
+    with lsq.Engine(blob, batch, beam, 32) as eng:
+        eng.encode(w.src_ids, w.src_lens)
+        for step in range(8):
+            score = torch.from_numpy(eng.debug(lsq.DBG.SCORE, (M,))).cuda()
+            finished = torch.from_numpy(eng.debug(lsq.DBG.FINISHED, (M,), np.int32)).cuda()
+            assert eng.decode_step() > 0
+            hidden = torch.from_numpy(eng.debug(lsq.DBG.HIDDEN, (M, 512))).half().cuda()
+            logits = torch.empty(M, vocab, dtype=torch.float32, device="cuda")
+            stats = torch.empty(M, (vocab + 31) // 32, 2, dtype=torch.float32, device="cuda")
+            lsq.k_gemm_logits(hidden, E, logits, stats)
+            want, idx = torch.empty(M, beam, device="cuda"), torch.empty(M, beam, dtype=torch.int32, device="cuda")
+            lsq.k_row_topk_groups(logits, stats, score, finished, beam, hp.eos_id, want, idx)
+            torch.cuda.synchronize()
+            assert np.array_equal(eng.debug(lsq.DBG.LOGITS, (M, vocab)), logits.cpu().numpy()), step
+            assert np.array_equal(eng.debug(lsq.DBG.CAND_IDX, (M, beam), np.int32), idx.cpu().numpy()), step
+            assert np.array_equal(eng.debug(lsq.DBG.CAND_SCORE, (M, beam)), want.cpu().numpy()), step
+        assert lsq.lsq_debug_stack_launches()["die"] == 8
