@@ -1105,7 +1105,11 @@ int settle_steps() {
   HIPCHK(hipMemcpyAsync(active.data(), at<int32_t>(g.plan.active) + g.all_from, active.size() * 4, hipMemcpyDeviceToHost, g.stream));
   HIPCHK(hipStreamSynchronize(g.stream));
   const int taken = (int)(std::find(active.begin(), active.end(), 0) - active.begin()) + 1;   // the last of them left nothing unfinished
-  const int n = g.all_n, t = std::min(g.t, g.all_from + (n == 1 ? taken + 1 : (taken + n - 1) / n * n));
+  int end = g.t;   // of the translation: what a last round of n had left to issue may reach beyond the shared launch
+  while (end < g.max_len && g.alive_at[end] > 0) ++end;
+  const int n = g.all_n;
+  const int64_t rounds = n == 1 ? taken + 1 : ((int64_t)taken + n - 1) / n * n;
+  const int t = (int)std::min<int64_t>(end, g.all_from + rounds);
   if (g.finalized == g.t) g.finalized = t;
   g.t = t;
   g.all_n = 0;

@@ -157,6 +157,29 @@ def test_steps_counted_where_they_shared_a_launch(lsq, beam, cap):
                 assert all(np.array_equal(a, b) for a, b in zip(eng.get_beams(), want))
 
 
+def test_steps_counted_past_the_end_of_a_shared_launch(lsq):
+    """A launch ends behind step 64, where the separate ones are ahead; the sentence is finished inside it.  Waits after every n would have come
+    upon that behind a round whose last steps lie beyond the launch."""
+    hp = S.HParams(n_enc=1, n_dec=1, d_model=128, n_heads=8, d_ffn=128, vocab=11, max_pos=200, dtype=0, cap_extra=90, seed=30)
+    w = S.custom(hp, [4], beam=8, max_len=99, std=0.12)
+    with lsq.Engine(w.blob(ln_jitter=0.2), 1, 8, 99) as eng:
+        eng.encode(w.src_ids, w.src_lens)
+        finished = 1
+        while lsq.lsq_decode_step() > 0:
+            finished += 1
+        want = eng.get_beams()
+        assert finished == 42
+        for n, index in ((1, 43), (20, 60), (33, 66), (41, 82), (42, 42), (64, 64)):
+            eng.encode(w.src_ids, w.src_lens)
+            before = lsq.lsq_debug_small_launches()
+            lsq.lsq_decode_all(n)
+            after = lsq.lsq_debug_small_launches()
+            assert after["launches"] == before["launches"] + 1 and after["steps"] == before["steps"] + 64
+            assert lsq.lsq_step_index() == index
+            assert lsq.lsq_decode_step() == 0
+            assert all(np.array_equal(a, b) for a, b in zip(eng.get_beams(), want))
+
+
 def test_cache_of_sentences_that_ended_inside_a_launch(lsq, foul_workspace):
     """Keys and values as the debug reader hands them back, in a workspace whose every byte was something else: those of the steps that a
     sentence took, whether its launch went on without it or not."""
