@@ -110,3 +110,28 @@ def test_float16_stack_kernels_spill_no_vector_register(tmp_path, source, kernel
             spilled[name.group(1)] = int(count.group(1))
     assert len(spilled) == kernels, sorted(spilled)
     assert not any(spilled.values()), spilled
+
+
+MERGE = """
+#include "lsq_internal.h"
+using namespace lsq;
+extern "C" __global__ void merge(const float* s, float* o) {
+  __shared__ float m[4][64], z[4][64];
+  const int lane = threadIdx.x;
+  for (int w = 0; w < 4; ++w) { m[w][lane] = s[w * 128 + lane]; z[w][lane] = s[w * 128 + 64 + lane]; }
+  __syncthreads();
+  float mx = m[0][lane ^ 1], sum = z[0][lane ^ 1];
+  for (int w = 1; w < 4; ++w) merge_stat_exact(mx, sum, m[w][lane ^ 1], z[w][lane ^ 1]);
+  o[lane] = mx;
+  o[64 + lane] = sum;
+}
+"""
+
+
+def test_statistics_are_merged_in_one_arithmetic_without_a_branch(tmp_path):
+    """What two kernels share bit for bit: a multiply-add and a product a merge, with and without contraction, and nothing that waits behind a
+    branch for its operands."""
+    for contract in ("off", "fast"):
+        ops = _instructions(tmp_path, MERGE, f"-ffp-contract={contract}")["merge"]
+        assert sum(n for i, n in ops.items() if re.match(r"v_(fma|fmac)_f32", i)) == 3, (contract, ops)
+        assert not [i for i in ops if i.startswith("s_cbranch") or "saveexec" in i], (contract, ops)
